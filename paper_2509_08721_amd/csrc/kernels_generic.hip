@@ -525,14 +525,92 @@ hipError_t g_advantages(const float* rewards, int S, int G, float* out, hipStrea
 
 // ---------------------------------------------------------------------------------------
 // Clipped surrogate of the local GRPO update (Sec. 4.2: no KL term, asymmetric clip).
-// Pass 1: every block walks a contiguous slice of the [S, T] tokens and leaves (sum of
-// min(rho A, clip(rho) A), number of masked tokens) in its slot; pass 2: one block adds the
-// slots in index order (fp64) and writes loss and count; pass 3: the gradient, which needs
-// the count.  rho and the branch decision are fp32; no atomics, so the result is reproducible.
+// The gradient needs the number of masked tokens, the loss the fp64 sum of the terms; rho and the branch decision are
+// fp32; no atomics and one fixed order of additions, so the result is reproducible.  A few hundred KB at most go through
+// these kernels: launches and dependent round trips are what they cost.
+// Up to kSurrogateOneLaunch tokens: one launch.  Block 0 sums the loss over all tokens; block b > 0 writes the
+// gradient of its 1024 tokens and counts the masked tokens of the whole set by itself (n mask bytes out of the L2, 16 at
+// a time).  Above that block 0's serial walk and the n bytes per block cost more than a second launch: the tokens are
+// summed by kLossBlocks blocks into slots, and every block of the second kernel adds the slots again (4 KB, the same
+// order) instead of waiting for a third.  One thread adding 256 slots one after the other, and a launch of its own
+// for it, was most of the call before: 64 x 384 tokens 26 -> 8 us a call, launched back to back.
 // ---------------------------------------------------------------------------------------
 constexpr int kLossBlocks = 256;
+constexpr size_t kSurrogateOneLaunch = 32768;
 struct LossPartial { double sum; long long count; };
 
+// (sum, count) over the THREADS threads of a block, in every thread; the order of additions is fixed
+template <int THREADS>
+__device__ __forceinline__ void block_loss_sum(double& sum, long long& count) {
+  constexpr int NW = THREADS / 64;
+  __shared__ double s_sum[NW];
+  __shared__ long long s_cnt[NW];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    sum += __shfl_xor(sum, o, 64);
+    count += __shfl_xor(count, o, 64);
+  }
+  if ((threadIdx.x & 63) == 0) { s_sum[threadIdx.x >> 6] = sum; s_cnt[threadIdx.x >> 6] = count; }
+  __syncthreads();
+  sum = s_sum[0]; count = s_cnt[0];
+#pragma unroll
+  for (int w = 1; w < NW; ++w) { sum += s_sum[w]; count += s_cnt[w]; }
+}
+__device__ __forceinline__ float loss_value(double sum, long long count) {
+  return count > 0 ? (float)(-sum / (double)count) : 0.f;
+}
+
+// The terms of tokens first, first + stride, ... < end; the row of a token is kept by stepping, not by dividing.
+__device__ __forceinline__ void surrogate_walk(const float* __restrict__ logp_new, const float* __restrict__ logp_old,
+                                               const uint8_t* __restrict__ mask, const float* __restrict__ adv, unsigned T,
+                                               size_t first, size_t end, unsigned stride, float eps_low, float eps_high,
+                                               double& sum, long long& count) {
+  size_t s = first / T;
+  unsigned t = (unsigned)(first - s * T);
+  const unsigned ds = stride / T, dt = stride - ds * T;
+#pragma unroll 8
+  for (size_t i = first; i < end; i += stride) {
+    const bool on = mask[i] != 0;
+    float rho; bool act;
+    const float term = surrogate_term(logp_new[i], logp_old[i], adv[s], eps_low, eps_high, rho, act);
+    if (on) { sum += (double)term; ++count; }   // values under a clear mask may be anything, NaN included
+    s += ds; t += dt;
+    if (t >= T) { t -= T; ++s; }
+  }
+}
+
+// mask: 16-byte aligned
+__global__ void __launch_bounds__(1024) k_surrogate_one(const float* __restrict__ logp_new, const float* __restrict__ logp_old,
+                                                        const uint8_t* __restrict__ mask, const float* __restrict__ adv, int T,
+                                                        int n, float eps_low, float eps_high, float* __restrict__ out_loss,
+                                                        float* __restrict__ out) {
+  double sum = 0.0;
+  long long count = 0;
+  if (blockIdx.x == 0) {
+    surrogate_walk(logp_new, logp_old, mask, adv, (unsigned)T, threadIdx.x, (size_t)n, 1024u, eps_low, eps_high, sum, count);
+    block_loss_sum<1024>(sum, count);
+    if (threadIdx.x == 0) out_loss[0] = loss_value(sum, count);
+    return;
+  }
+  const int i = (blockIdx.x - 1) * 1024 + threadIdx.x;
+  float a = 0.f, rho = 0.f;
+  bool act = false;
+  if (i < n && mask[i]) {
+    a = adv[i / T];
+    surrogate_term(logp_new[i], logp_old[i], a, eps_low, eps_high, rho, act);
+  }
+  int c = 0;
+  for (int j = threadIdx.x; j < (n >> 4); j += 1024) {
+    const uint4 m = ((const uint4*)mask)[j];
+    const unsigned w[4] = {m.x, m.y, m.z, m.w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) c += __popc((((w[e] & 0x7f7f7f7fu) + 0x7f7f7f7fu) | w[e]) & 0x80808080u);   // non-zero bytes
+  }
+  if ((int)threadIdx.x < (n & 15)) c += mask[(n & ~15) + threadIdx.x] != 0;
+  count = c;
+  block_loss_sum<1024>(sum, count);
+  if (i < n) out[i] = surrogate_dlogp(a, rho, act, count);
+}
 __global__ void __launch_bounds__(256) k_surrogate_partial(const float* __restrict__ logp_new, const float* __restrict__ logp_old,
                                                            const uint8_t* __restrict__ mask, const float* __restrict__ adv,
                                                            int T, size_t n, float eps_low, float eps_high,
@@ -541,61 +619,50 @@ __global__ void __launch_bounds__(256) k_surrogate_partial(const float* __restri
   const size_t i0 = (size_t)blockIdx.x * per, i1 = (i0 + per < n) ? i0 + per : n;
   double sum = 0.0;
   long long cnt = 0;
-  for (size_t i = i0 + threadIdx.x; i < i1; i += 256) {
-    if (!mask[i]) continue;
-    float rho; bool act;
-    sum += (double)surrogate_term(logp_new[i], logp_old[i], adv[i / T], eps_low, eps_high, rho, act);
-    ++cnt;
-  }
-  __shared__ double s_sum[256];
-  __shared__ long long s_cnt[256];
-  s_sum[threadIdx.x] = sum; s_cnt[threadIdx.x] = cnt;
-  __syncthreads();
-  if (threadIdx.x == 0) {   // thread order: the same sum whatever the hardware does
-    double t = 0.0; long long c = 0;
-    for (int j = 0; j < 256; ++j) { t += s_sum[j]; c += s_cnt[j]; }
-    part[blockIdx.x].sum = t; part[blockIdx.x].count = c;
-  }
+  surrogate_walk(logp_new, logp_old, mask, adv, (unsigned)T, i0 + threadIdx.x, i1, 256u, eps_low, eps_high, sum, cnt);
+  block_loss_sum<256>(sum, cnt);
+  if (threadIdx.x == 0) { part[blockIdx.x].sum = sum; part[blockIdx.x].count = cnt; }
 }
-__global__ void k_surrogate_finish(LossPartial* __restrict__ part, int n_part, float* __restrict__ out_loss) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  double t = 0.0; long long c = 0;
-  for (int j = 0; j < n_part; ++j) { t += part[j].sum; c += part[j].count; }
-  part[n_part].sum = t; part[n_part].count = c;   // slot n_part: the totals, read by the gradient pass
-  out_loss[0] = c > 0 ? (float)(-t / (double)c) : 0.f;
-}
-__global__ void __launch_bounds__(256) k_surrogate_grad(const float* __restrict__ logp_new, const float* __restrict__ logp_old,
-                                                        const uint8_t* __restrict__ mask, const float* __restrict__ adv,
-                                                        int T, size_t n, float eps_low, float eps_high,
-                                                        const LossPartial* __restrict__ total, float* __restrict__ out) {
+// adds the kLossBlocks slots, writes the loss (block 0) and the gradient of this block's 256 tokens (out may be null)
+__global__ void __launch_bounds__(256) k_surrogate_apply(const float* __restrict__ logp_new, const float* __restrict__ logp_old,
+                                                         const uint8_t* __restrict__ mask, const float* __restrict__ adv,
+                                                         int T, size_t n, float eps_low, float eps_high,
+                                                         const LossPartial* __restrict__ part, float* __restrict__ out_loss,
+                                                         float* __restrict__ out) {
+  static_assert(kLossBlocks == 256, "one slot per thread");
+  double sum = part[threadIdx.x].sum;
+  long long count = part[threadIdx.x].count;
   const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n) return;
-  float g = 0.f;
-  if (mask[i]) {
-    const float a = adv[i / T];
-    float rho; bool act;
+  float a = 0.f, rho = 0.f;
+  bool act = false;
+  if (out && i < n && mask[i]) {
+    a = adv[i / T];
     surrogate_term(logp_new[i], logp_old[i], a, eps_low, eps_high, rho, act);
-    g = surrogate_dlogp(a, rho, act, total->count);
   }
-  out[i] = g;
+  block_loss_sum<256>(sum, count);
+  if (blockIdx.x == 0 && threadIdx.x == 0) out_loss[0] = loss_value(sum, count);
+  if (out && i < n) out[i] = surrogate_dlogp(a, rho, act, count);
 }
 size_t g_surrogate_workspace_bytes() { return (kLossBlocks + 1) * sizeof(LossPartial); }
 hipError_t g_surrogate_loss(const float* logp_new, const float* logp_old, const uint8_t* mask, const float* adv, int S, int T,
                             float eps_low, float eps_high, float* out_loss, float* out_dlogp, void* workspace,
                             hipStream_t st) {
   const size_t n = (size_t)S * T;
+  if (n <= kSurrogateOneLaunch && ((uintptr_t)mask & 15) == 0) {
+    const unsigned grad_blocks = out_dlogp ? (unsigned)((n + 1023) / 1024) : 0u;
+    return launch(KID_MISC, k_surrogate_one, dim3(1 + grad_blocks), dim3(1024), 0, st, logp_new, logp_old, mask, adv, T, (int)n,
+                  eps_low, eps_high, out_loss, out_dlogp);
+  }
   LossPartial* part = (LossPartial*)workspace;
-  hipError_t e = launch(KID_MISC, k_surrogate_partial, dim3(kLossBlocks), dim3(256), 0, st, logp_new, logp_old, mask, adv, T,
-                        n, eps_low, eps_high, part);
+  const hipError_t e = launch(KID_MISC, k_surrogate_partial, dim3(kLossBlocks), dim3(256), 0, st, logp_new, logp_old, mask, adv,
+                              T, n, eps_low, eps_high, part);
   if (e != hipSuccess) return e;
-  e = launch(KID_MISC, k_surrogate_finish, dim3(1), dim3(64), 0, st, part, kLossBlocks, out_loss);
-  if (e != hipSuccess || !out_dlogp) return e;
-  return launch(KID_MISC, k_surrogate_grad, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, logp_new, logp_old, mask,
-                adv, T, n, eps_low, eps_high, (const LossPartial*)(part + kLossBlocks), out_dlogp);
+  return launch(KID_MISC, k_surrogate_apply, dim3(out_dlogp ? (unsigned)((n + 255) / 256) : 1u), dim3(256), 0, st, logp_new,
+                logp_old, mask, adv, T, n, eps_low, eps_high, (const LossPartial*)part, out_loss, out_dlogp);
 }
 
 // ---------------------------------------------------------------------------------------
-// The same three passes for callers that cannot allocate (code under graph capture, serving loops, harnesses that
+// The same kernels for callers that cannot allocate (code under graph capture, serving loops, harnesses that
 // forbid hipMalloc): the block partials and the totals live in a file-scope device array instead of a workspace.
 // Every device holds its own copy of the array; its address is looked up once per device, with that device
 // current, and kept.  All 256 partial slots and the totals slot are overwritten by every call before they are

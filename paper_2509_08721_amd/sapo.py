@@ -160,17 +160,27 @@ def _check(rc: int):
         raise SapoError(rc, load_library().sapo_last_error().decode())
 
 
+_torch_module = None
+
+
 def _torch():
-    import torch
-    if not torch.cuda.is_available():
-        raise RuntimeError("no GPU visible: libsapo has no CPU path")
-    return torch
+    """torch, once a GPU has been seen (asking again on every call cost more than a small call's launches)."""
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        if not torch.cuda.is_available():
+            raise RuntimeError("no GPU visible: libsapo has no CPU path")
+        torch.cuda.init()
+        _torch_module = torch
+    return _torch_module
 
 
 def _stream_ptr(stream=None) -> int:
     torch = _torch()
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return int(s.cuda_stream)
+    if stream is not None:
+        return int(stream.cuda_stream)
+    # the raw handle of the current device's current stream, without building a Stream object around it
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def make_config(shape) -> sapo_model_config:
