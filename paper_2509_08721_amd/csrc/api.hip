@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "common.h"
+#include "small.h"
 
 using namespace sapo;
 
@@ -75,7 +76,7 @@ void prof_events(int kid, hipEvent_t* e0, hipEvent_t* e1) {
 static const char* const kKernelNames[KID_COUNT] = {
     "k_embed", "k_rmsnorm", "k_gemm", "k_rope_append", "k_attention", "k_swiglu", "k_sample_rows", "k_score_rows",
     "misc", "k_gemm_big", "k_lmhead_score", "k_lmhead_score_merge", "k_gemm_skinny", "k_lmhead_sample",
-    "k_lmhead_sample_merge", "k_decode_attention", "k_flash_attention", "k_gemm_big_decode", "k_decode_layers", "k_decode_attention_shared"};
+    "k_lmhead_sample_merge", "k_decode_attention", "k_flash_attention", "k_gemm_big_decode", "k_decode_layers", "k_decode_attention_shared", "k_small"};
 
 extern "C" int sapo_profile_kernel_count(void) { return KID_COUNT; }
 extern "C" const char* sapo_profile_kernel_name(int i) { return (i >= 0 && i < KID_COUNT) ? kKernelNames[i] : ""; }
@@ -130,6 +131,7 @@ struct sapo_weights {
   float* final_norm = nullptr;
   float2* rope = nullptr;        // [max_seq][hd / 2] (cos, sin)
   PersistLayer* persist_tbl = nullptr;   // MFMA path: per-layer pointers for the persistent decode kernel (device)
+  SmallLayer* small_tbl = nullptr;       // small decoders: per-layer pointers (device); NULL: another path runs
   unsigned* pack_range = nullptr;        // MFMA path, device: kPackRangeSlots pairs (outside half's range, below its normal range)
   long long half_tiny = 0;               // [1] of the last packing
   mutable unsigned long long* clamp_counter = nullptr;   // device; non-null while a debug forward counts clamped activations
@@ -182,9 +184,12 @@ static int validate_config(const sapo_model_config* c) {
 
 // The MFMA kernels need bf16 storage and tile-aligned shapes; everything else runs on the
 // shape-generic kernels.  SAPO_FORCE_GENERIC=1 in the environment forces the generic kernels.
-static bool mfma_eligible(const sapo_model_config* c) {
+static bool force_generic() {
   const char* f = getenv("SAPO_FORCE_GENERIC");
-  if (f && f[0] == '1') return false;
+  return f && f[0] == '1';
+}
+static bool mfma_eligible(const sapo_model_config* c) {
+  if (force_generic()) return false;
   const int q = c->n_q_heads * c->head_dim, kv = c->n_kv_heads * c->head_dim;
   return c->dtype == SAPO_DTYPE_BF16 && (c->head_dim == 64 || c->head_dim == 128) && c->d_model % 128 == 0 &&
          q % 128 == 0 && (q + 2 * kv) % 128 == 0 && kv % 32 == 0 && c->d_ff % 64 == 0 && c->vocab % 128 == 0 &&
@@ -203,6 +208,7 @@ extern "C" int sapo_weights_uses_mfma(const sapo_weights* w) { return (w && w->m
 static int dev_alloc(sapo_weights* w, size_t bytes, void** out);
 static void drop_decode_graph(const sapo_weights* w);
 static int upload_persist_table(sapo_weights* w);
+static int upload_small_table(sapo_weights* w);
 
 extern "C" int sapo_weights_set_qkv_bias(sapo_weights* w, int layer, const float* bq, const float* bk, const float* bv,
                                          void* stream) {
@@ -221,6 +227,7 @@ extern "C" int sapo_weights_set_qkv_bias(sapo_weights* w, int layer, const float
   if (fresh) {
     drop_decode_graph(w);   // a captured decode step holds the old kernel arguments (no bias pointer)
     if (w->persist_tbl && (rc = upload_persist_table(w))) return rc;
+    if (w->small_tbl && (rc = upload_small_table(w))) return rc;
   }
   return SAPO_OK;
 }
@@ -256,6 +263,34 @@ static int upload_persist_table(sapo_weights* w) {
   int rc;
   if ((rc = dev_alloc(w, (size_t)L * sizeof(PersistLayer), (void**)&w->persist_tbl))) return rc;
   HIP_CK(hipMemcpy(w->persist_tbl, tbl.data(), (size_t)L * sizeof(PersistLayer), hipMemcpyHostToDevice));
+  return SAPO_OK;
+}
+
+// Small decoders (kernels_small.hip): one workgroup takes a sequence through the whole call.  Per decode step it
+// streams the model through one compute unit (about 80 GB/s) and pays its barriers (about 5 us per layer); the
+// shape-generic path pays its 11 launches per layer, about 5 us each.  The line is drawn where the former is at most half
+// of the latter with one round of workgroups, so that a batch of two rounds (512 sequences) is still no slower.  Tiny
+// configuration: 18 us per step (the estimate says 19) against 135.
+static bool small_eligible(const sapo_weights* w) {
+  const sapo_model_config& c = w->cfg;
+  if (w->mfma || force_generic() || c.n_layers == 0) return false;
+  if (c.d_model % 4 || c.head_dim % 4 || c.d_ff % 4) return false;
+  const double q = (double)c.n_q_heads * c.head_dim, kv = (double)c.n_kv_heads * c.head_dim, d = c.d_model;
+  const double bytes = w->elt * (c.n_layers * (d * (2 * q + 2 * kv) + 3 * d * c.d_ff) + d * c.vocab);
+  const double step_us = bytes / 80e3 + 5.0 * c.n_layers + 3.0, launches_us = 5.0 * (11.0 * c.n_layers + 4.0);
+  return 2.0 * step_us <= launches_us;
+}
+static int upload_small_table(sapo_weights* w) {
+  const int L = w->cfg.n_layers;
+  std::vector<SmallLayer> tbl(L);
+  for (int l = 0; l < L; ++l) {
+    const LayerWeights& lw = w->layers[l];
+    tbl[l].wqkv = lw.wqkv; tbl[l].wo = lw.wo; tbl[l].wgu = lw.wgu; tbl[l].wdown = lw.wdown;
+    tbl[l].attn_norm = lw.attn_norm; tbl[l].ffn_norm = lw.ffn_norm; tbl[l].bqkv = lw.bqkv;
+  }
+  int rc;
+  if ((rc = dev_alloc(w, (size_t)L * sizeof(SmallLayer), (void**)&w->small_tbl))) return rc;
+  HIP_CK(hipMemcpy(w->small_tbl, tbl.data(), (size_t)L * sizeof(SmallLayer), hipMemcpyHostToDevice));
   return SAPO_OK;
 }
 
@@ -343,6 +378,7 @@ static int create_impl(sapo_weights* w, const void* const* t, hipStream_t st) {
                   "the 16-bit matrix-core path cannot hold them", too_large);
   }
   if (!w->persist_tbl && (rc = upload_persist_table(w))) return rc;
+  if (!w->small_tbl && small_eligible(w) && (rc = upload_small_table(w))) return rc;
   if (w->rope) return SAPO_OK;   // a refill: the table depends on the configuration only
   // rotary table in double on the host: angle(pos, i) = pos * theta^(-2 i / hd)
   const int half = c.head_dim / 2;
@@ -473,6 +509,16 @@ static KVCache layer_cache(const sapo_weights* w, const CacheBufs& cb, int l) {
 static int clear_cache(const CacheBufs& cb, int n_layers, hipStream_t st) {
   HIP_CK(g_fill_i32((int*)cb.pool, 0, cb.pool_bytes * 2 * n_layers / 4, st));
   return SAPO_OK;
+}
+
+static SmallModel small_model(const sapo_weights* w, const CacheBufs& cb) {
+  const sapo_model_config& c = w->cfg;
+  SmallModel m;
+  m.L = c.n_layers; m.d = c.d_model; m.hq = c.n_q_heads; m.hkv = c.n_kv_heads; m.hd = c.head_dim; m.F = c.d_ff; m.V = c.vocab;
+  m.eps = c.rms_eps;
+  m.embed = w->embed; m.lm_head = w->lm_head; m.final_norm = w->final_norm; m.rope = w->rope; m.layers = w->small_tbl;
+  m.pool = cb.pool; m.pool_bytes = cb.pool_bytes;
+  return m;
 }
 
 // ---------------------------------------------------------------------------------------
@@ -821,6 +867,31 @@ static int rollout_impl(const sapo_weights* w, const int32_t* prompts, const int
   const sapo_model_config& c = w->cfg;
   const int dt = c.dtype, d = c.d_model, S = pl.S;
   const float* gain_first = c.n_layers > 0 ? w->layers[0].attn_norm : w->final_norm;
+  const bool ragged = lens_host != nullptr;
+  if (ragged) {
+    for (int p = 0; p < P; ++p)
+      if (lens_host[p] < 1 || lens_host[p] > Lp)
+        return fail(SAPO_EINVAL, "prompt %d has length %d, outside 1 .. %d", p, lens_host[p], Lp);
+  }
+  if (w->small_tbl) {
+    // the cache of this path holds P Lp + S N positions in a row: no more than the pages carved for the call
+    const SmallModel m = small_model(w, pl.cache);
+    if (small_prefill_fits(m, Lp) && small_decode_fits(m, Lp + max_new) &&
+        small_rows_fit(m, (size_t)P * Lp + (size_t)S * max_new, (size_t)S * max_new)) {
+      if (ragged) HIP_CK(hipMemcpyAsync(pl.lens, lens_host, (size_t)P * sizeof(int), hipMemcpyHostToDevice, st));
+      SmallPrefill pa{};
+      pa.tokens = prompts; pa.T = Lp; pa.lens = ragged ? pl.lens : nullptr; pa.h_last = pl.h_last;
+      pa.h_rows = pl.fwd.h; pa.q_rows = pl.fwd.q;
+      HIP_CK(small_prefill(dt, m, pa, P, st));
+      SmallDecode da{};
+      da.P = P; da.Lp = Lp; da.G = G; da.N = max_new; da.ctx_max = Lp + max_new; da.lens = pa.lens; da.h_last = pl.h_last;
+      da.temperature = temperature; da.seed_lo = (uint32_t)(seed & 0xffffffffu); da.seed_hi = (uint32_t)(seed >> 32);
+      da.stop_token = stop_token; da.out_tokens = out_tokens; da.out_logprobs = out_logprobs; da.out_lengths = out_lengths;
+      HIP_CK(small_decode(dt, m, da, S, st));
+      w->last_stats[0] = max_new - 1; w->last_stats[1] = 0; w->last_stats[2] = S; w->last_stats[3] = 0;
+      return SAPO_OK;
+    }
+  }
   auto parts_after_layers = [&](const RolloutPlan::Level& lv) {
     return c.n_layers == 0 ? 1 : (w->mfma && lv.dec.down_splits > 0) ? (d + 1023) / 1024 : d / 16;
   };
@@ -884,11 +955,7 @@ static int rollout_impl(const sapo_weights* w, const int32_t* prompts, const int
     HIP_CK(g_fill_i32(pl.step + 2, (int)sp.seed_hi, 1, st));
     HIP_CK(g_fill_i32(pl.step + 3, tbits, 1, st));
   }
-  const bool ragged = lens_host != nullptr;
   if (ragged) {
-    for (int p = 0; p < P; ++p)
-      if (lens_host[p] < 1 || lens_host[p] > Lp)
-        return fail(SAPO_EINVAL, "prompt %d has length %d, outside 1 .. %d", p, lens_host[p], Lp);
     HIP_CK(hipMemcpyAsync(pl.lens, lens_host, (size_t)P * sizeof(int), hipMemcpyHostToDevice, st));
     HIP_CK(g_page_table_ragged(pl.cache.page_table, S, pl.pages_per_seq, G, pl.full_prompt_pages, pl.own_pages, P, pl.lens,
                                st));
@@ -1175,6 +1242,22 @@ static int score_impl(const sapo_weights* w, const int32_t* tokens, const uint8_
   hipStream_t st = (hipStream_t)stream;
   const sapo_model_config& c = w->cfg;
 
+  if (w->small_tbl) {
+    const SmallModel m = small_model(w, pl.cache);
+    if (small_prefill_fits(m, T) && small_rows_fit(m, (size_t)pl.chunk_seqs * T, (size_t)pl.chunk_seqs * T)) {
+      const bool whole = pl.chunk_seqs >= S;   // groups do not straddle passes: the advantages ride along
+      if (!whole) HIP_CK(g_advantages(rewards, S, G, out_advantages, st));
+      for (int s0 = 0; s0 < S; s0 += pl.chunk_seqs) {
+        SmallPrefill pa{};
+        pa.tokens = tokens + (size_t)s0 * T; pa.T = T; pa.mask = completion_mask + (size_t)s0 * T;
+        pa.out_logprobs = out_logprobs + (size_t)s0 * T; pa.inv_t = 1.0f / temperature;
+        pa.h_rows = pl.fwd.h; pa.q_rows = pl.fwd.q;
+        if (whole) { pa.rewards = rewards; pa.out_adv = out_advantages; pa.G = G; }
+        HIP_CK(small_prefill(c.dtype, m, pa, S - s0 < pl.chunk_seqs ? S - s0 : pl.chunk_seqs, st));
+      }
+      return SAPO_OK;
+    }
+  }
   // log softmax(z / T): z is linear in the final norm's gains, so the temperature goes into them
   const float* final_gain = w->final_norm;
   if (temperature != 1.0f) {

@@ -209,7 +209,7 @@ enum KernelId {
   KID_EMBED = 0, KID_RMSNORM, KID_GEMM_GENERIC, KID_ROPE_APPEND, KID_ATTN_GENERIC, KID_SWIGLU, KID_SAMPLE_ROWS,
   KID_SCORE_ROWS, KID_MISC, KID_GEMM_BIG, KID_LMHEAD_SCORE, KID_LMHEAD_SCORE_MERGE, KID_GEMM_SKINNY,
   KID_LMHEAD_SAMPLE, KID_LMHEAD_SAMPLE_MERGE, KID_DECODE_ATTN, KID_FLASH_ATTN, KID_GEMM_BIG_DECODE, KID_DECODE_LAYERS,
-  KID_DECODE_ATTN_SHARED, KID_COUNT
+  KID_DECODE_ATTN_SHARED, KID_SMALL, KID_COUNT
 };
 extern bool g_prof_on;
 // A pair of events for one profiled launch of kernel `kid` (recorded for sapo_profile_stop).

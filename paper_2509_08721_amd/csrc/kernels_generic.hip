@@ -1,6 +1,7 @@
 // Shape-generic kernels: any model shape, fp32 or bf16 storage, plain ALU arithmetic.
 // They run the fp32 configuration and every step that has no tile-aligned MFMA kernel.
 #include "common.h"
+#include "small.h"
 #include "surrogate.h"
 #include "train.h"
 #include <mutex>
@@ -456,19 +457,7 @@ hipError_t g_score_rows(const float* logits, int n_rows, int row_offset, int V, 
 __global__ void k_advantages(const float* __restrict__ r, int n_groups, int G, float* __restrict__ out) {
   const int g = blockIdx.x * blockDim.x + threadIdx.x;
   if (g >= n_groups) return;
-  const float* rg = r + (size_t)g * G;
-  bool all_equal = true;
-  double sum = 0.0;
-  for (int i = 0; i < G; ++i) { sum += (double)rg[i]; all_equal = all_equal && (rg[i] == rg[0]); }
-  if (all_equal) {
-    for (int i = 0; i < G; ++i) out[(size_t)g * G + i] = 0.f;
-    return;
-  }
-  const double mu = sum / G;
-  double var = 0.0;
-  for (int i = 0; i < G; ++i) { const double dlt = (double)rg[i] - mu; var += dlt * dlt; }
-  const double sd = sqrt(var / G);
-  for (int i = 0; i < G; ++i) out[(size_t)g * G + i] = (float)(((double)rg[i] - mu) / (sd + 1e-6));
+  group_advantages(r + (size_t)g * G, G, out + (size_t)g * G);
 }
 __global__ void k_scale_f32(const float* __restrict__ x, float a, float* __restrict__ y, size_t n) {
   const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;

@@ -1,0 +1,96 @@
+"""The small-decoder kernels (one workgroup per sequence) against the shape-generic ones, which the other tests hold to
+the oracle: tile edges, both prefill forms, every attention form, ragged prompts, stop tokens, biases."""
+import os
+from dataclasses import replace
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2509_08721_amd import sapo, workloads as W
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = {
+    "tiny": W.TINY,
+    "hd12": replace(W.TINY, n_q_heads=9, n_kv_heads=3, head_dim=12, d_model=36, d_ff=100, vocab=301),   # no matrix-core attention
+    "hd32": replace(W.TINY, n_q_heads=2, n_kv_heads=1, head_dim=32, d_model=132, d_ff=260, n_layers=3, vocab=1003),
+    "hd64": replace(W.TINY, n_q_heads=10, n_kv_heads=5, head_dim=64, d_model=60, d_ff=64, n_layers=1, vocab=600),
+}
+
+
+def handles(shape, seed, bias=False):
+    w = W.perturb_norm_gains(W.make_weights(shape, seed, std=0.05), seed)
+    if bias:
+        w = W.add_qkv_bias(w, shape, seed)
+    small = sapo.sapo_weights_create(shape, w)
+    os.environ["SAPO_FORCE_GENERIC"] = "1"
+    try:
+        generic = sapo.sapo_weights_create(shape, w)
+    finally:
+        del os.environ["SAPO_FORCE_GENERIC"]
+    return small, generic
+
+
+def kernels_of(call):
+    """The kernels a call launches."""
+    sapo.sapo_profile_start()
+    call()
+    return set(sapo.sapo_profile_stop())
+
+
+@pytest.mark.parametrize("name", list(SHAPES))
+@pytest.mark.parametrize("S,T,G", [(1, 1, 1), (4, 15, 2), (3, 16, 3), (6, 17, 2), (5, 33, 1), (2, 130, 1)])
+def test_small_scoring(name, S, T, G):
+    shape = SHAPES[name]
+    small, generic = handles(shape, 11, bias=name == "hd32")
+    rng = np.random.default_rng(S * T)
+    tok = torch.from_numpy(rng.integers(0, shape.vocab, (S, T)).astype(np.int32)).cuda()
+    mask = torch.from_numpy((rng.random((S, T)) < 0.5).astype(np.uint8)).cuda()
+    rew = torch.from_numpy((rng.random(S) < 0.5).astype(np.float32)).cuda()
+    assert kernels_of(lambda: sapo.sapo_score_logprobs(small, tok, mask, rew, G)) == {"k_small"}
+    for temp in (1.0, 0.7):
+        a = sapo.sapo_score_logprobs_at(small, tok, mask, rew, G, temp)
+        b = sapo.sapo_score_logprobs_at(generic, tok, mask, rew, G, temp)
+        assert float((a[0] - b[0]).abs().max()) <= 2e-5 and torch.equal(a[1], b[1])
+
+
+@pytest.mark.parametrize("name", list(SHAPES))
+@pytest.mark.parametrize("P,G,Lp,N", [(1, 1, 1, 1), (2, 3, 16, 5), (3, 2, 17, 40), (2, 2, 100, 3)])
+def test_small_rollouts(name, P, G, Lp, N):
+    shape = SHAPES[name]
+    small, generic = handles(shape, 12, bias=name == "hd64")
+    rng = np.random.default_rng(P * Lp + N)
+    prompts = torch.from_numpy(rng.integers(0, shape.vocab, (P, Lp)).astype(np.int32)).cuda()
+    for temp in (1.0, 0.0):
+        a = sapo.sapo_rollout_generate(small, prompts, G, N, temp, 5)
+        b = sapo.sapo_rollout_generate(generic, prompts, G, N, temp, 5)
+        assert torch.equal(a[0], b[0]) and float((a[1] - b[1]).abs().max()) <= 2e-5
+    # prompts of different lengths, with a stop token that some row emits
+    lens = [int(x) for x in rng.integers(1, Lp + 1, P)]
+    stop = int(a[0][0, N // 2])
+    for st in (-1, stop):
+        a = sapo.sapo_rollout_generate_ragged(small, prompts, lens, G, N, 1.0, 6, stop_token=st)
+        b = sapo.sapo_rollout_generate_ragged(generic, prompts, lens, G, N, 1.0, 6, stop_token=st)
+        assert torch.equal(a[0], b[0]) and float((a[1] - b[1]).abs().max()) <= 2e-5
+        assert st < 0 or torch.equal(a[2], b[2])
+
+
+def test_small_bf16_follows_the_generic_kernels():
+    shape = replace(W.TINY, dtype="bf16")
+    small, generic = handles(shape, 13)
+    assert not small.uses_mfma
+    rng = np.random.default_rng(3)
+    tok = torch.from_numpy(rng.integers(0, shape.vocab, (4, 50)).astype(np.int32)).cuda()
+    mask = torch.ones((4, 50), dtype=torch.uint8, device="cuda")
+    rew = torch.zeros(4, device="cuda")
+    a, b = (sapo.sapo_score_logprobs(h, tok, mask, rew, 2)[0] for h in (small, generic))
+    assert float((a - b).abs().max()) <= 2e-2     # roundings to bf16 may fall either way
+
+
+def test_large_models_do_not_take_the_small_path():
+    shape = replace(W.TINY, d_model=512, n_q_heads=8, n_kv_heads=8, head_dim=64, d_ff=2048)
+    w = sapo.sapo_weights_create(shape, W.make_weights(shape, 1))
+    tok = torch.zeros((1, 8), dtype=torch.int32, device="cuda")
+    names = kernels_of(lambda: sapo.sapo_score_logprobs(w, tok, torch.ones_like(tok, dtype=torch.uint8), torch.zeros(1, device="cuda"), 1))
+    assert "k_small" not in names
