@@ -9,6 +9,7 @@
 // log-prob tolerances (with bf16 activations the rounding points alone put the 1.5B-class model's
 // logits 6e-2 away from the definition).
 #include "common.h"
+#include <type_traits>
 
 namespace sapo {
 
@@ -93,32 +94,42 @@ hipError_t m_pack_weight(const void* src, int n_rows, int K, void* dst, int dst_
 // wave = one contiguous 1 KiB block):
 //   W32[((fblk * KS + ks) * 64 + lane)] = W[fblk*32 + lane%32][ks*16 + (lane/32)*8 .. +7],  KS = K / 16
 //   X32[((tblk * KS + ks) * 64 + lane)] = X[tblk*32 + lane%32][ks*16 + (lane/32)*8 .. +7]
-// so a fragment moves from global memory to LDS with one direct-to-LDS load per wave and is read
-// back with one conflict-free ds_read_b128.
-// Workgroup tile 256 tokens x 128 features, 4 waves as 2 (tokens) x 2 (features), each 128 x 64 =
-// 4 x 2 MFMA tiles; 32 k per stage (24 fragments), three stages in an LDS ring with two in flight.
-// Two workgroups fit a compute unit (72 KiB LDS, <= 256 registers), which is what overlaps one
-// workgroup's barrier and LDS latency with the other's MFMAs.
-// The direct-to-LDS loads are issued from inline assembly: the compiler would otherwise wait for
-// all of them before any LDS read, which removes the prefetch distance.  Their completion is
-// awaited with explicit s_waitcnt vmcnt(N) (loads retire in order).
-// Accumulator layout: acc[fi][tj][4 r + j] = C[tok = tj*32 + lane%32][feat = fi*32 + 8 r + (lane/32)*4 + j].
+// Workgroup tile 128 TJ tokens x 128 features, 4 waves, each 32 TJ tokens x all 128 features = 4 x TJ MFMA tiles; H
+// 16-k steps per stage.  The token operand goes from global memory straight into the registers of the one wave that
+// uses it, two stages ahead; the feature operand, which all four waves read, goes through a three-stage LDS ring filled by
+// direct-to-LDS copies.  What bounds the loop is the LDS: with both operands in the ring and waves of 128 tokens x
+// 64 features (what this replaces) a wave read 0.75 KB and the copies wrote 0.375 KB of LDS per MFMA, more than a compute
+// unit's LDS delivers in the MFMA's time; now it is 0.5 + 0.125 KB.  Stand-alone, random operands (old -> H = 2 -> H = 4):
+// 49152 x 9728 x 896 870 -> 770 -> 697 us, 49152 x 896 x 4864 401 -> 387 -> 368 us, 49152 x 17920 x 1536 2350 -> 2170 ->
+// 2125 us (1.27 PFLOP/s; the rest is the clock that the matrix cores hold under this load).
+// TJ = 2: two workgroups per compute unit (48 KiB LDS, <= 256 registers), which is what overlaps one workgroup's barrier
+// and LDS latency with the other's MFMAs; TJ = 1: three.
+// All requests of the loop are issued from inline assembly and awaited with explicit s_waitcnt vmcnt(N) (they retire in
+// order): the compiler would wait for the copies before any LDS read, and for the newest request before the oldest
+// register's use.
+// Accumulator layout: acc[fi][tj][4 r + j] = C[tok = wave * 32 TJ + tj*32 + lane%32][feat = fi*32 + 8 r + (lane/32)*4 + j].
 // ---------------------------------------------------------------------------------------
 __host__ __device__ __forceinline__ size_t x32_chunk(int tok, int k, int KS) {
   return (((size_t)(tok >> 5) * KS + (k >> 4)) * 64) + (tok & 31) + 32 * ((k >> 3) & 1);
 }
 
-constexpr int kStageFrags = 24;   // 16 token fragments + 8 feature fragments per 32-k stage
-constexpr int kStages = 3;
-constexpr int kBigLds = kStages * kStageFrags * 1024;
+constexpr int kRing = 3;                                            // stages of the LDS ring
+constexpr int ring_bytes(int H) { return kRing * 4 * H * 1024; }     // 4 H fragments of 1 KiB per stage
+constexpr int kBigLds = ring_bytes(4);
 
 __device__ __forceinline__ unsigned lds_addr(const void* p) {
   return (unsigned)(size_t)(const __attribute__((address_space(3))) void*)p;
 }
-// one wave-wide 1 KiB copy global -> LDS: lane l's 16 bytes land at lds + 16 l
-__device__ __forceinline__ void dma16(const void* g, unsigned lds) {
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(lds), "v"(g) : "memory");
+// one wave-wide 1 KiB copy global -> LDS: lane l's 16 bytes (at base + off(l)) land at lds + 16 l (no immediate offset: the
+// instruction would add it to the LDS address as well)
+__device__ __forceinline__ void dma16(const void* base, unsigned off, unsigned lds) {
+  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory");
 }
+// one wave-wide 1 KiB load into registers; the value is there after a wait and a landed() that names it
+template <int IMM> __device__ __forceinline__ void reg16(u32x4& d, const void* base, unsigned off) {
+  asm volatile("global_load_dwordx4 %0, %1, %2 offset:%3" : "=v"(d) : "v"(off), "s"(base), "n"(IMM) : "memory");
+}
+__device__ __forceinline__ void landed(u32x4& d) { asm volatile("" : "+v"(d)); }
 template <int N> __device__ __forceinline__ void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
 }
@@ -147,100 +158,149 @@ static int big_grid(int NX, int NY) {
   return 8 * ((NX + 7) / 8) * ((((NY + 7) / 8) + 7) / 8) * 64;
 }
 
-// acc = X[tblk0*32 .. +255][:] . W[fblk0*32 .. +127][:]^T over the whole K.  Token blocks past the end
-// are clamped to the last one (their results are never stored).
-struct NoPrologue { __device__ __forceinline__ void operator()() const {} };
-// `prologue` runs once the first two stages are requested (loads it issues ride on the same latency).
-// NS: depth of the LDS ring (NS - 1 stages in flight).
-// TJ: 32-token blocks per wave (4: a 256-token tile, the default; 2: a 128-token tile with a third workgroup per
-// compute unit, for launches whose 256-token tiles would leave the last round of workgroups mostly empty).
-template <int NS = kStages, class Prologue = NoPrologue, int TJ = 4>
-__device__ __forceinline__ void big_mainloop(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, int n_tblk,
-                                             int KS, int tblk0, int fblk0, uint4* smem, f32x16 (&acc)[2][TJ],
-                                             Prologue prologue = Prologue(), int st0 = 0, int n_stages = -1) {
-  constexpr int TF = 4 * TJ;        // token fragments of a stage (2 TJ token blocks x 2 k halves)
-  constexpr int SF = TF + 8;        // fragments of a stage
-  constexpr int NF = SF / 4;        // requests per wave and stage
-  static_assert(TJ == 4 || TJ == 2, "tile of 256 or 128 tokens");
-  const int tid = threadIdx.x, wave = wave_index(tid), lane = tid & 63;
-  const int wf = wave & 1, wt = wave >> 1;
-  const int nst = n_stages < 0 ? (KS >> 1) : n_stages;   // stages of 32 k; a split-K workgroup runs st0 .. st0 + nst - 1
-  const uint4* src[NF];
-  unsigned dst[NF];
+// The k loop of one tile.  begin() requests the first two stages, run() multiplies all of them; a caller that walks several
+// tiles may call begin() for the next one before it is done with the accumulators, after a barrier (the ring is free
+// once every wave has left run()).
+template <int TJ, int H>
+struct TileLoop {
+  static constexpr int NF = H;                // ring copies per wave and stage (4 H fragments, 4 waves)
+  static constexpr int PER = NF + TJ * H;     // requests per wave and stage
+  static_assert(H == 2 || H == 4, "stage of 32 or 64 k");
+  u32x4 x[2][H][TJ];
+  const char* wbase;          // this wave's feature fragments: block wave * 4 / 4, or half of one (H = 2: two fragments each)
+  const char* xbase[TJ];
+  const char* xrow;           // start of the token operand
+  unsigned off, ring;         // lane offset; LDS address of this wave's fragments in the ring's stage 0
+  int nst;
+
+  // X rows tblk0 * 32 .. (token blocks past the last one, n_tblk - 1, repeat it: their results are never stored), W rows
+  // fblk0 * 32 .. + 127, n_stages stages of 16 H k from 16-k step ks0 on
+  __device__ __forceinline__ void tokens(const uint4* Xp, int n_tblk, int KS, int tblk0, int ks0) {
+    const int wave = wave_index(threadIdx.x);
 #pragma unroll
-  for (int i = 0; i < NF; ++i) {
-    const int f = wave * NF + i;
-    if (f < TF) {
-      int tb = tblk0 + (f >> 1);
-      if (tb > n_tblk - 1) tb = n_tblk - 1;
-      src[i] = Xp + ((size_t)tb * KS + 2 * st0 + (f & 1)) * 64 + lane;
-    } else {
-      const int g = f - TF;
-      src[i] = Wp + ((size_t)(fblk0 + (g >> 1)) * KS + 2 * st0 + (g & 1)) * 64 + lane;
+    for (int t = 0; t < TJ; ++t) {
+      const int tb = min(tblk0 + wave * TJ + t, n_tblk - 1);
+      xbase[t] = (const char*)(Xp + ((size_t)tb * KS + ks0) * 64);
     }
-    dst[i] = __builtin_amdgcn_readfirstlane(lds_addr(smem + f * 64));
   }
-  auto issue = [&](int st) {
-    const unsigned sbase = (unsigned)((st % NS) * SF * 1024);
+  // ring fragment f of a stage: feature block f / H, 16-k step f % H; wave w copies fragments w H .. w H + H - 1, the H
+  // steps of feature block w
+  __device__ __forceinline__ void features(const uint4* Wp, int KS, int fblk0, int ks0, int n_stages, const uint4* smem) {
+    const int wave = wave_index(threadIdx.x);
+    wbase = (const char*)(Wp + ((size_t)(fblk0 + wave) * KS + ks0) * 64);
+    ring = __builtin_amdgcn_readfirstlane(lds_addr(smem)) + (unsigned)(wave * H * 1024);
+    off = (threadIdx.x & 63) * 16;
+    nst = n_stages;
+  }
+  template <int I> __device__ __forceinline__ void request_w(int st) {
+    dma16(wbase + (size_t)st * (H * 1024) + I * 1024, off, ring + (unsigned)((st % kRing) * (4 * H * 1024) + I * 1024));
+  }
+  template <int HH> __device__ __forceinline__ void request_x(int p, int st) {
 #pragma unroll
-    for (int i = 0; i < NF; ++i) dma16(src[i] + (size_t)st * 128, dst[i] + sbase);
-  };
+    for (int t = 0; t < TJ; ++t) reg16<HH * 1024>(x[p][HH][t], xbase[t] + (size_t)st * (H * 1024), off);
+  }
+  __device__ __forceinline__ void begin() {
+    auto stage = [&](auto pc) {
+      constexpr int p = decltype(pc)::value;
+      request_w<0>(p); request_w<1>(p);
+      if constexpr (H == 4) { request_w<2>(p); request_w<3>(p); }
+      request_x<0>(p, p); request_x<1>(p, p);
+      if constexpr (H == 4) { request_x<2>(p, p); request_x<3>(p, p); }
+    };
+    stage(std::integral_constant<int, 0>());
+    if (nst > 1) stage(std::integral_constant<int, 1>());
+  }
+  template <int P> __device__ __forceinline__ void stage(int st, const uint4* smem, f32x16 (&acc)[4][TJ]) {
+    // this wave's requests of stage st have landed once at most the next stage's are outstanding ...
+    if (st + 1 < nst) wait_vmcnt<PER>(); else wait_vmcnt<0>();
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+    for (int h = 0; h < H; ++h)
 #pragma unroll
-    for (int b = 0; b < TJ; ++b)
+      for (int t = 0; t < TJ; ++t) landed(x[P][h][t]);
+    wg_barrier();   // ... and everybody's; stage st - 1 is consumed
+    const bool more = st + 2 < nst;
+    const uint4* buf = smem + (st % kRing) * (4 * H * 64) + (threadIdx.x & 63);
+    auto step = [&](auto hc) {
+      constexpr int h = decltype(hc)::value;
+      Frag w[4];
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
-  wg_barrier();   // a previous pass over the ring (fused LM head) is over in every wave
+      for (int f = 0; f < 4; ++f) w[f].u = buf[(f * H + h) * 64];
+      __builtin_amdgcn_s_setprio(1);
+      // The ring copies of stage st + 2 go out one after each of the first MFMAs, a step's registers are requested again
+      // right after their last use; the fences keep the compiler from regrouping them.
+      auto feature = [&](auto fc) {
+        constexpr int f = decltype(fc)::value;
 #pragma unroll
-  for (int p = 0; p < NS - 1; ++p)
-    if (p < nst) issue(p);
-  prologue();
-  for (int st = 0; st < nst; ++st) {
-    // this wave's part of stage st has landed once at most the newer stages' requests are outstanding
-    const int newer = min(NS - 2, nst - 1 - st);
-    if (newer >= 4) wait_vmcnt<4 * NF>();
-    else if (newer == 3) wait_vmcnt<3 * NF>();
-    else if (newer == 2) wait_vmcnt<2 * NF>();
-    else if (newer == 1) wait_vmcnt<NF>();
-    else wait_vmcnt<0>();
-    wg_barrier();                                               // ... and everybody's; stage st-1 is consumed
-    // The requests of stage st + NS - 1 go out one after each of the first MFMAs instead of in a burst behind
-    // the barrier: the burst held up the LDS reads and MFMAs queued behind it (same sums, 15 % faster on the scorer's
-    // shape in a stand-alone copy of the loop).  The fences keep the compiler from regrouping them.
-    const bool more = st + NS - 1 < nst;
-    const unsigned next_base = (unsigned)(((st + NS - 1) % NS) * SF * 1024);
-    const size_t next_off = (size_t)(st + NS - 1) * 128;
-    const uint4* buf = smem + (st % NS) * SF * 64;
-#pragma unroll
-    for (int s2 = 0; s2 < 2; ++s2) {
-      Frag xf[TJ], wfr[2];
-#pragma unroll
-      for (int tj = 0; tj < TJ; ++tj) xf[tj].u = buf[((wt * TJ + tj) * 2 + s2) * 64 + lane];
-#pragma unroll
-      for (int fi = 0; fi < 2; ++fi) wfr[fi].u = buf[(TF + (wf * 2 + fi) * 2 + s2) * 64 + lane];
-#pragma unroll
-      for (int fi = 0; fi < 2; ++fi)
-#pragma unroll
-        for (int tj = 0; tj < TJ; ++tj) {
-          acc[fi][tj] = mfma32(wfr[fi], xf[tj], acc[fi][tj]);
-          const int m = (s2 * 2 + fi) * TJ + tj;
-          if (m < NF) {
-            __builtin_amdgcn_sched_barrier(0);
-            if (more) dma16(src[m] + next_off, dst[m] + next_base);
-            __builtin_amdgcn_sched_barrier(0);
-          }
+        for (int t = 0; t < TJ; ++t) {
+          Frag xx; xx.n = x[P][h][t];
+          acc[f][t] = mfma32(w[f], xx, acc[f][t]);
         }
+        if constexpr (h == 0 && f < NF) {
+          __builtin_amdgcn_sched_barrier(0);
+          if (more) request_w<f>(st + 2);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      };
+      feature(std::integral_constant<int, 0>()); feature(std::integral_constant<int, 1>());
+      feature(std::integral_constant<int, 2>()); feature(std::integral_constant<int, 3>());
+      __builtin_amdgcn_s_setprio(0);
+      __builtin_amdgcn_sched_barrier(0);
+      if (more) request_x<h>(P, st + 2);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    step(std::integral_constant<int, 0>()); step(std::integral_constant<int, 1>());
+    if constexpr (H == 4) { step(std::integral_constant<int, 2>()); step(std::integral_constant<int, 3>()); }
+  }
+  __device__ __forceinline__ void run(const uint4* smem, f32x16 (&acc)[4][TJ]) {
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+      for (int b = 0; b < TJ; ++b)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
+    int st = 0;
+    for (; st + 1 < nst; st += 2) {
+      stage<0>(st, smem, acc);
+      stage<1>(st + 1, smem, acc);
     }
+    if (st < nst) stage<0>(st, smem, acc);
+  }
+};
+
+// 1 / rms of the wave's tokens of a tile from the parts of their sums of squares (at most 16 parts, row stride a multiple
+// of 4): requested behind the first stages, so that they ride on the same latency
+template <int TJ>
+__device__ __forceinline__ void row_scales(const float* __restrict__ ssq, int parts, float norm_dim, float eps, int tok0, int M,
+                                           float (&scale)[TJ]) {
+  const int ps = (parts + 3) & ~3;
+  float4 part[TJ][4];
+#pragma unroll
+  for (int tj = 0; tj < TJ; ++tj) {
+    const int tok = min(tok0 + tj * 32, M - 1);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      part[tj][i] = (4 * i < ps) ? *(const float4*)(ssq + (size_t)tok * ps + 4 * i) : make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+#pragma unroll
+  for (int tj = 0; tj < TJ; ++tj) {
+    float ss = 0.f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {   // padding slots are never written: select, do not add
+      ss += (4 * i + 0 < parts) ? part[tj][i].x : 0.f;
+      ss += (4 * i + 1 < parts) ? part[tj][i].y : 0.f;
+      ss += (4 * i + 2 < parts) ? part[tj][i].z : 0.f;
+      ss += (4 * i + 3 < parts) ? part[tj][i].w : 0.f;
+    }
+    scale[tj] = rsqrtf(ss / norm_dim + eps);
   }
 }
 
-template <int TJ>
-__global__ void __launch_bounds__(256, TJ == 4 ? 2 : 3) k_gemm_big(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp,
+template <int TJ, int H>
+__global__ void __launch_bounds__(256, TJ == 2 ? 2 : 3) k_gemm_big(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp,
                                                                   int M, int N, int K, BigEpi ep) {
-  constexpr int TM = 64 * TJ;   // tokens per tile
+  constexpr int TM = 128 * TJ;   // tokens per tile
   extern __shared__ uint4 smem[];
-  int bx, by, st0 = 0, n_st = K >> 5;
+  int bx, by, st0 = 0, n_st = K / (16 * H);
   if (ep.splits > 1) {
     // split-K (one token tile): XCD c runs the splits c, c + 8, ... of every feature tile, so the K range of
     // the token operand that a split reads sits in one L2; split z covers stages z nst / s .. (z + 1) nst / s
@@ -253,379 +313,275 @@ __global__ void __launch_bounds__(256, TJ == 4 ? 2 : 3) k_gemm_big(const uint4* 
   } else if (!big_raster(N >> 7, (M + TM - 1) / TM, bx, by)) {
     return;
   }
-  f32x16 acc[2][TJ];
+  f32x16 acc[4][TJ];
   const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63;
-  const int wf = wave & 1, wt = wave >> 1;
+  const int tok0 = by * TM + wave * (32 * TJ) + (lane & 31);
   float row_scale[TJ];
 #pragma unroll
   for (int tj = 0; tj < TJ; ++tj) row_scale[tj] = 1.f;
-  auto prologue = [&]() {
-    if (!ep.ssq_in) return;
-    const int ps = (ep.ssq_parts + 3) & ~3;   // row stride of the parts; at most 16 parts
-    float4 part[TJ][4];
-#pragma unroll
-    for (int tj = 0; tj < TJ; ++tj) {
-      const int tok = min(by * TM + wt * (32 * TJ) + tj * 32 + (lane & 31), M - 1);
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        part[tj][i] = (4 * i < ps) ? *(const float4*)(ep.ssq_in + (size_t)tok * ps + 4 * i) : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-#pragma unroll
-    for (int tj = 0; tj < TJ; ++tj) {
-      float ss = 0.f;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {   // padding slots are never written: select, do not add
-        ss += (4 * i + 0 < ep.ssq_parts) ? part[tj][i].x : 0.f;
-        ss += (4 * i + 1 < ep.ssq_parts) ? part[tj][i].y : 0.f;
-        ss += (4 * i + 2 < ep.ssq_parts) ? part[tj][i].z : 0.f;
-        ss += (4 * i + 3 < ep.ssq_parts) ? part[tj][i].w : 0.f;
-      }
-      row_scale[tj] = rsqrtf(ss / ep.norm_dim + ep.eps);
-    }
-  };
-  big_mainloop<kStages, decltype(prologue), TJ>(Xp, Wp, (M + 31) >> 5, K >> 4, by * (2 * TJ), bx * 4, smem, acc, prologue, st0, n_st);
-  float ssq_mine[TJ];
-#pragma unroll
-  for (int tj = 0; tj < TJ; ++tj) ssq_mine[tj] = 0.f;
-  const int tok0 = by * TM + wt * (32 * TJ) + (lane & 31);
-  const int fcol = bx * 128 + wf * 64 + (lane >> 5) * 4;   // + fi * 32 + 8 r: this lane's four features of block (fi, r)
-  float4 bb[2][4];
-  if (ep.mode == BIG_STORE_F32 && ep.bias) {
-#pragma unroll
-    for (int fi = 0; fi < 2; ++fi)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) bb[fi][r] = *(const float4*)(ep.bias + fcol + fi * 32 + 8 * r);
+  {
+    TileLoop<TJ, H> loop;
+    loop.tokens(Xp, (M + 31) >> 5, K >> 4, by * (4 * TJ), st0 * H);
+    loop.features(Wp, K >> 4, bx * 4, st0 * H, n_st, smem);
+    loop.begin();
+    if (ep.ssq_in) row_scales<TJ>(ep.ssq_in, ep.ssq_parts, ep.norm_dim, ep.eps, tok0, M, row_scale);
+    loop.run(smem, acc);
   }
+  const int fcol = bx * 128 + (lane >> 5) * 4;   // + fi * 32 + 8 r: this lane's four features of block (fi, r)
+  if (ep.ssq_in) {
 #pragma unroll
-  for (int tj = 0; tj < TJ; ++tj) {
-    const int tok = tok0 + tj * 32;
-    if (tok >= M) continue;   // lanes l and l + 32 hold the same token: they leave together
-    if (ep.ssq_in) {
-      const float sc = row_scale[tj];
+    for (int tj = 0; tj < TJ; ++tj)
 #pragma unroll
-      for (int fi = 0; fi < 2; ++fi)
+      for (int fi = 0; fi < 4; ++fi)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[fi][tj][v] *= sc;
-    }
-    if (ep.mode == BIG_SWIGLU) {
-      // fi = 0 is a gate tile, fi = 1 the matching up tile; act goes out in X32 order over F = N / 2
-      const int F = N >> 1;
-      const int f0 = (bx * 2 + wf) * 32 + (lane >> 5) * 4;
+        for (int v = 0; v < 16; ++v) acc[fi][tj][v] *= row_scale[tj];
+  }
+  if (ep.mode == BIG_SWIGLU) {
+    const int F = N >> 1;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        f16x4 o;
+    for (int tj = 0; tj < TJ; ++tj) {
+      const int tok = tok0 + tj * 32;
+      if (tok >= M) continue;   // lanes l and l + 32 hold the same token: they leave together
 #pragma unroll
-        for (int j = 0; j < 4; ++j) o[j] = from_f32<f16>(silu_f(acc[0][tj][4 * r + j]) * acc[1][tj][4 * r + j]);
-        *(f16x4*)(ep.out_act + x32_chunk(tok, f0 + 8 * r, F >> 4) * 8 + ((lane >> 5) << 2)) = o;
+      for (int pr = 0; pr < 2; ++pr) {
+        // block 2 pr is a gate tile, 2 pr + 1 the matching up tile; act goes out in X32 order over F = N / 2
+        const int f0 = (bx * 2 + pr) * 32 + (lane >> 5) * 4;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          f16x4 o;
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            o[j] = from_f32<f16>(silu_f(acc[2 * pr][tj][4 * r + j]) * acc[2 * pr + 1][tj][4 * r + j]);
+          *(f16x4*)(ep.out_act + x32_chunk(tok, f0 + 8 * r, F >> 4) * 8 + ((lane >> 5) << 2)) = o;
+        }
       }
-    } else if (ep.mode == BIG_STORE_F32) {
+    }
+  } else if (ep.mode == BIG_STORE_F32) {
 #pragma unroll
-      for (int fi = 0; fi < 2; ++fi)
+    for (int fi = 0; fi < 4; ++fi) {
+      float4 bb[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        bb[r] = ep.bias ? *(const float4*)(ep.bias + fcol + fi * 32 + 8 * r) : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+      for (int tj = 0; tj < TJ; ++tj) {
+        const int tok = tok0 + tj * 32;
+        if (tok >= M) continue;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           float4 v = make_float4(acc[fi][tj][4 * r], acc[fi][tj][4 * r + 1], acc[fi][tj][4 * r + 2], acc[fi][tj][4 * r + 3]);
-          if (ep.bias) { v.x += bb[fi][r].x; v.y += bb[fi][r].y; v.z += bb[fi][r].z; v.w += bb[fi][r].w; }
+          if (ep.bias) { v.x += bb[r].x; v.y += bb[r].y; v.z += bb[r].z; v.w += bb[r].w; }
           *(float4*)(ep.out_f32 + (size_t)tok * ep.ldc + fcol + fi * 32 + 8 * r) = v;
         }
+      }
     }
   }
   if (ep.mode == BIG_ADD_F32) {
     // Residual update.  In the accumulator layout a lane holds one token, so a load or store instruction on the
     // row-major fp32 residual touches 32 cache lines for 1 KiB.  The residual therefore moves in row layout (16 lanes
     // cover 256 contiguous bytes of a row: 8 full lines per instruction) and changes layout through LDS, once on the
-    // way in and once on the way out, a wave's 64 (128-token tiles: 32) tokens x 64 features at a time in the wave's own
-    // part of the ring (rows padded to 68 floats).  The sums, the next operand and the sums of squares are taken in the accumulator
-    // layout as before: same results bit for bit.  The second half's rows are requested before the first half's
-    // stores, since a load issued behind a store also waits for the store's acknowledgement.  A tile without rows
-    // past the end and the producer side are compile-time cases, so that the common one is straight-line code
-    // whose waits the compiler can count exactly.
-    constexpr int RS = 68, HB = TJ == 4 ? 64 : 32, T2 = HB / 32, NI = HB / 4;   // HB tokens per pass, two passes
+    // way in and once on the way out, 32 tokens x 64 features at a time in the wave's own part of the ring (rows padded
+    // to 68 floats).  The sums, the next operand and the sums of squares are taken in the accumulator layout.  The next
+    // pass's rows are requested before a pass's stores go out, since a load issued behind a store also waits for the
+    // store's acknowledgement.  A tile without rows past the end and the producer side are compile-time cases, so that
+    // the common one is straight-line code whose waits the compiler can count exactly.
+    constexpr int RS = 68, NP = 2 * TJ;   // passes: token block tj, feature half fh
     wg_barrier();   // every wave has read its last stage: the ring is free
-    float* R = (float*)smem + wave * (HB * RS);
-    const int rt = lane >> 4, rc = (lane & 15) * 4;   // row layout: token 4 i + rt of the half, features rc .. rc + 3
-    const int row0 = by * TM + wt * (32 * TJ), gcol = bx * 128 + wf * 64;
+    float* R = (float*)smem + wave * (32 * RS);
+    const int rt = lane >> 4, rc = (lane & 15) * 4;   // row layout: token 4 i + rt of the block, features rc .. rc + 3
+    const int row0 = by * TM + wave * (32 * TJ);
     auto wave_sync = [] {
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     };
+    float ssq_half[TJ][2];
     auto update = [&](auto full_c, auto prod_c) {
       constexpr bool full = decltype(full_c)::value, prod = decltype(prod_c)::value;
-      // the wave's 64 gains wait in LDS behind the four row areas (held in registers they would not fit next to the
-      // rows in flight)
-      float* G = (float*)smem + 4 * HB * RS + wave * 64;
-      if (prod && lane < 16) *(float4*)(G + 4 * lane) = *(const float4*)(ep.gain_next + gcol + 4 * lane);
-      float4 in[NI];
-      auto request = [&](int h, int i0) {   // rows 4 i + rt, i = i0 .. i0 + 7, of half h
+      // the tile's 128 gains wait in LDS behind the four row areas (in registers they would not fit next to the rows)
+      float* G = (float*)smem + 4 * 32 * RS + wave * 128;
+      if (prod && lane < 32) *(float4*)(G + 4 * lane) = *(const float4*)(ep.gain_next + bx * 128 + 4 * lane);
+      float4 in[8];
+      auto request = [&](int p) {   // pass p: token block p / 2, feature half p % 2
 #pragma unroll
-        for (int i = i0; i < i0 + 8; ++i) {
-          const int tok = row0 + h * HB + 4 * i + rt;
-          in[i] = (full || tok < M) ? *(const float4*)(ep.out_f32 + (size_t)tok * ep.ldc + gcol + rc)
+        for (int i = 0; i < 8; ++i) {
+          const int tok = row0 + (p >> 1) * 32 + 4 * i + rt;
+          in[i] = (full || tok < M) ? *(const float4*)(ep.out_f32 + (size_t)tok * ep.ldc + bx * 128 + (p & 1) * 64 + rc)
                                     : make_float4(0.f, 0.f, 0.f, 0.f);
         }
       };
+      request(0);
 #pragma unroll
-      for (int i0 = 0; i0 < NI; i0 += 8) request(0, i0);
+      for (int p = 0; p < NP; ++p) {
+        const int tj = p >> 1, fh = p & 1, tok = tok0 + tj * 32;
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-#pragma unroll
-        for (int i = 0; i < NI; ++i) *(float4*)(R + (4 * i + rt) * RS + rc) = in[i];
+        for (int i = 0; i < 8; ++i) *(float4*)(R + (4 * i + rt) * RS + rc) = in[i];
         wave_sync();
+        float ssq = 0.f;
 #pragma unroll
-        for (int t2 = 0; t2 < T2; ++t2) {
-          const int tj = T2 * h + t2, tok = tok0 + tj * 32;
-          float ssq = 0.f;
+        for (int f2 = 0; f2 < 2; ++f2)
 #pragma unroll
-          for (int fi = 0; fi < 2; ++fi)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              float4* q = (float4*)(R + (t2 * 32 + (lane & 31)) * RS + fi * 32 + 8 * r + (lane >> 5) * 4);
-              const float4 w = *q;
-              const float4 v = make_float4(acc[fi][tj][4 * r] + w.x, acc[fi][tj][4 * r + 1] + w.y,
-                                           acc[fi][tj][4 * r + 2] + w.z, acc[fi][tj][4 * r + 3] + w.w);
-              *q = v;
-              if (prod && (full || tok < M)) {
-                ssq += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
-                const float4 gn = *(const float4*)(G + fi * 32 + 8 * r + (lane >> 5) * 4);
-                f16x4 hv;
-                hv[0] = from_f32<f16>(v.x * gn.x); hv[1] = from_f32<f16>(v.y * gn.y);
-                hv[2] = from_f32<f16>(v.z * gn.z); hv[3] = from_f32<f16>(v.w * gn.w);
-                *(f16x4*)(ep.xn_out + x32_chunk(tok, fcol + fi * 32 + 8 * r, N >> 4) * 8 + ((lane >> 5) << 2)) = hv;
-              }
+          for (int r = 0; r < 4; ++r) {
+            const int fi = 2 * fh + f2;
+            float4* q = (float4*)(R + (lane & 31) * RS + f2 * 32 + 8 * r + (lane >> 5) * 4);
+            const float4 w = *q;
+            const float4 v = make_float4(acc[fi][tj][4 * r] + w.x, acc[fi][tj][4 * r + 1] + w.y,
+                                         acc[fi][tj][4 * r + 2] + w.z, acc[fi][tj][4 * r + 3] + w.w);
+            *q = v;
+            if (prod && (full || tok < M)) {
+              ssq += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+              const float4 gn = *(const float4*)(G + fi * 32 + 8 * r + (lane >> 5) * 4);
+              f16x4 hv;
+              hv[0] = from_f32<f16>(v.x * gn.x); hv[1] = from_f32<f16>(v.y * gn.y);
+              hv[2] = from_f32<f16>(v.z * gn.z); hv[3] = from_f32<f16>(v.w * gn.w);
+              *(f16x4*)(ep.xn_out + x32_chunk(tok, fcol + fi * 32 + 8 * r, N >> 4) * 8 + ((lane >> 5) << 2)) = hv;
             }
-          ssq_mine[tj] = ssq + __shfl_xor(ssq, 32, 64);
-        }
-        wave_sync();
-#pragma unroll
-        for (int i0 = 0; i0 < NI; i0 += 8) {   // eight rows at a time: sixteen out and sixteen in would not fit the registers
-          float4 out[8];
-#pragma unroll
-          for (int i = 0; i < 8; ++i) out[i] = *(const float4*)(R + (4 * (i0 + i) + rt) * RS + rc);
-          if (h == 0) request(1, i0);
-#pragma unroll
-          for (int i = 0; i < 8; ++i) {
-            const int tok = row0 + h * HB + 4 * (i0 + i) + rt;
-            if (full || tok < M) *(float4*)(ep.out_f32 + (size_t)tok * ep.ldc + gcol + rc) = out[i];
           }
+        ssq_half[tj][fh] = ssq + __shfl_xor(ssq, 32, 64);
+        wave_sync();
+        float4 out[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) out[i] = *(const float4*)(R + (4 * i + rt) * RS + rc);
+        if (p + 1 < NP) request(p + 1);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const int t = row0 + tj * 32 + 4 * i + rt;
+          if (full || t < M) *(float4*)(ep.out_f32 + (size_t)t * ep.ldc + bx * 128 + fh * 64 + rc) = out[i];
         }
-        wave_sync();   // the rows are in registers before the next half overwrites them
+        wave_sync();   // the rows are in registers before the next pass overwrites them
       }
     };
     const bool full = by * TM + TM <= M;
     if (ep.gain_next) {
       if (full) update(std::true_type(), std::true_type());
       else update(std::false_type(), std::true_type());
+      if (lane < 32) {
+        const int ps = ((N >> 7) + 3) & ~3;
+#pragma unroll
+        for (int tj = 0; tj < TJ; ++tj)
+          if (tok0 + tj * 32 < M) ep.ssq_out[(size_t)(tok0 + tj * 32) * ps + bx] = ssq_half[tj][0] + ssq_half[tj][1];
+      }
     } else {
       if (full) update(std::true_type(), std::false_type());
       else update(std::false_type(), std::false_type());
     }
   }
-  if (ep.gain_next) {   // uniform: the two feature waves of a token half meet in LDS, summed in wave order
-    __shared__ float red[256];
-    if (wf == 1 && lane < 32) {
-#pragma unroll
-      for (int tj = 0; tj < TJ; ++tj) red[wt * (32 * TJ) + tj * 32 + lane] = ssq_mine[tj];
-    }
-    __syncthreads();
-    if (wf == 0 && lane < 32) {
-      const int ps = ((N >> 7) + 3) & ~3;
-#pragma unroll
-      for (int tj = 0; tj < TJ; ++tj) {
-        const int tok = by * TM + wt * (32 * TJ) + tj * 32 + lane;
-        if (tok < M) ep.ssq_out[(size_t)tok * ps + bx] = ssq_mine[tj] + red[wt * (32 * TJ) + tj * 32 + lane];
-      }
-    }
-  }
 }
 // ---------------------------------------------------------------------------------------
 // QKV projection with the rotary embedding and the KV append in its epilogue (token-parallel path): the
-// fp32 q/k/v rows never exist in memory.  Same main loop as k_gemm_big.  A 128-feature tile is two
-// heads of 64 (one per feature wave: the rotation partner i + 32 sits in the same lane, accumulator
-// block fi = 1) or one head of 128 (the partner i + 64 sits in the other feature wave: the two waves
-// swap their accumulators through LDS, two token blocks at a time).  q goes out as half row-major
-// [M, Hq hd] (flash attention's operand), rotated k and v go to the row's cache page.
+// fp32 q/k/v rows never exist in memory.  Same main loop as k_gemm_big.  A 128-feature tile is two heads of 64 (blocks
+// 0, 1 and 2, 3) or one head of 128; the rotation partner (i + 32, resp. i + 64) sits in the same lane, one or two
+// accumulator blocks on.  q goes out as half row-major [M, Hq hd] (flash attention's operand), rotated k and v go to the
+// row's cache page.
 // ---------------------------------------------------------------------------------------
 template <int HD>
 __global__ void __launch_bounds__(256, 2) k_gemm_qkv_rope(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, int M,
                                                           int N, int K, QkvEpi ep) {
+  constexpr int TJ = 2, H = 4, NB = HD / 32, NH = 128 / HD;   // accumulator blocks of a head, heads of a tile
   extern __shared__ uint4 smem[];
   int bx, by;
   if (!big_raster(N >> 7, (M + 255) >> 8, bx, by)) return;
-  f32x16 acc[2][4];
+  f32x16 acc[4][TJ];
   const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63;
-  const int wf = wave & 1, wt = wave >> 1;
-  float row_scale[4] = {1.f, 1.f, 1.f, 1.f};
-  big_mainloop(Xp, Wp, (M + 31) >> 5, K >> 4, by * 8, bx * 4, smem, acc, [&]() {
-    if (!ep.ssq_in) return;
-    const int ps = (ep.ssq_parts + 3) & ~3;
-    float4 part[4][4];
-#pragma unroll
-    for (int tj = 0; tj < 4; ++tj) {
-      const int tok = min(by * 256 + wt * 128 + tj * 32 + (lane & 31), M - 1);
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-        part[tj][i] = (4 * i < ps) ? *(const float4*)(ep.ssq_in + (size_t)tok * ps + 4 * i) : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-#pragma unroll
-    for (int tj = 0; tj < 4; ++tj) {
-      float ss = 0.f;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        ss += (4 * i + 0 < ep.ssq_parts) ? part[tj][i].x : 0.f;
-        ss += (4 * i + 1 < ep.ssq_parts) ? part[tj][i].y : 0.f;
-        ss += (4 * i + 2 < ep.ssq_parts) ? part[tj][i].z : 0.f;
-        ss += (4 * i + 3 < ep.ssq_parts) ? part[tj][i].w : 0.f;
-      }
-      row_scale[tj] = rsqrtf(ss / ep.norm_dim + ep.eps);
-    }
-  });
+  const int tok0 = by * 256 + wave * 64 + (lane & 31);
+  float row_scale[TJ] = {1.f, 1.f};
+  {
+    TileLoop<TJ, H> loop;
+    loop.tokens(Xp, (M + 31) >> 5, K >> 4, by * 8, 0);
+    loop.features(Wp, K >> 4, bx * 4, 0, K / (16 * H), smem);
+    loop.begin();
+    if (ep.ssq_in) row_scales<TJ>(ep.ssq_in, ep.ssq_parts, ep.norm_dim, ep.eps, tok0, M, row_scale);
+    loop.run(smem, acc);
+  }
   const int hq = ep.n_q_heads, hkv = ep.kv.n_kv_heads;
-  const int head = (HD == 64) ? bx * 2 + wf : bx;            // among Hq + 2 Hkv heads
-  const bool is_v = head >= hq + hkv;
   const int half_sel = lane >> 5;
   // row scale and bias first: what is rotated is the finished projection
-  {
-    float4 bb[2][4];
 #pragma unroll
-    for (int fi = 0; fi < 2; ++fi)
+  for (int fi = 0; fi < 4; ++fi) {
+    float4 bb[4];
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-        bb[fi][r] = ep.bias ? *(const float4*)(ep.bias + bx * 128 + wf * 64 + fi * 32 + half_sel * 4 + 8 * r)
-                            : make_float4(0.f, 0.f, 0.f, 0.f);
+    for (int r = 0; r < 4; ++r)
+      bb[r] = ep.bias ? *(const float4*)(ep.bias + bx * 128 + fi * 32 + half_sel * 4 + 8 * r) : make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
-    for (int tj = 0; tj < 4; ++tj)
+    for (int tj = 0; tj < TJ; ++tj)
 #pragma unroll
-      for (int fi = 0; fi < 2; ++fi)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          acc[fi][tj][4 * r + 0] = acc[fi][tj][4 * r + 0] * row_scale[tj] + bb[fi][r].x;
-          acc[fi][tj][4 * r + 1] = acc[fi][tj][4 * r + 1] * row_scale[tj] + bb[fi][r].y;
-          acc[fi][tj][4 * r + 2] = acc[fi][tj][4 * r + 2] * row_scale[tj] + bb[fi][r].z;
-          acc[fi][tj][4 * r + 3] = acc[fi][tj][4 * r + 3] * row_scale[tj] + bb[fi][r].w;
-        }
+      for (int r = 0; r < 4; ++r) {
+        acc[fi][tj][4 * r + 0] = acc[fi][tj][4 * r + 0] * row_scale[tj] + bb[r].x;
+        acc[fi][tj][4 * r + 1] = acc[fi][tj][4 * r + 1] * row_scale[tj] + bb[r].y;
+        acc[fi][tj][4 * r + 2] = acc[fi][tj][4 * r + 2] * row_scale[tj] + bb[r].z;
+        acc[fi][tj][4 * r + 3] = acc[fi][tj][4 * r + 3] * row_scale[tj] + bb[r].w;
+      }
   }
   f16* kpool = (f16*)ep.kv.k;
   f16* vpool = (f16*)ep.kv.v;
-  // Where the four token blocks of this lane go: position, cache page, and whether anything is stored.  All four
-  // page-table lookups are in flight together (rows past the end look up row M - 1 and store nothing).
-  int pos_of[4], page_of[4];
-  bool stores[4];
+  // Where the token blocks of this lane go: position, cache page.  The page-table lookups are in flight together
+  // (rows past the end look up row M - 1 and store nothing).
+  int pos_of[TJ], page_of[TJ];
+  bool keeps[TJ];
 #pragma unroll
-  for (int tj = 0; tj < 4; ++tj) {
-    const int tok = by * 256 + wt * 128 + tj * 32 + (lane & 31), tokc = min(tok, M - 1);
+  for (int tj = 0; tj < TJ; ++tj) {
+    const int tokc = min(tok0 + tj * 32, M - 1);
     int seq;
     ep.rm.get(tokc, seq, pos_of[tj]);
-    stores[tj] = tok < M && (head < hq || ep.rm.keeps_kv(tokc));
+    keeps[tj] = ep.rm.keeps_kv(tokc);
     page_of[tj] = ep.kv.page_table[(size_t)seq * ep.kv.pages_per_seq + pos_of[tj] / kPageTokens];
   }
-  if (is_v) {
-    const int vh = head - hq - hkv;
+  const bool rotates = bx * NH < hq + hkv;   // else the tile is all V
 #pragma unroll
-    for (int tj = 0; tj < 4; ++tj) {
-      if (!stores[tj]) continue;
-      f16* vp = vpool + ((size_t)page_of[tj] * hkv + vh) * HD * kPageTokens + pos_of[tj] % kPageTokens;
-#pragma unroll
-      for (int fi = 0; fi < 2; ++fi)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int f = (HD == 64 ? 0 : wf * 64) + fi * 32 + 8 * (v >> 2) + (v & 3) + half_sel * 4;
-          vp[(size_t)f * kPageTokens] = from_f32<f16>(acc[fi][tj][v]);
-        }
-    }
-    return;
-  }
-  // start of a row's head: q row-major, k in its page slot
-  auto head_row = [&](int tj) -> f16* {
-    const int tok = by * 256 + wt * 128 + tj * 32 + (lane & 31);
-    if (head < hq) return ep.q_out + ((size_t)tok * hq + head) * HD;
-    return kpool + (((size_t)page_of[tj] * hkv + (head - hq)) * kPageTokens + pos_of[tj] % kPageTokens) * HD;
-  };
-  // The (cos, sin) pairs of a token block are requested one block ahead of the block being written, before that
-  // block's stores: a load issued behind a store waits for the store's acknowledgement as well.
-  if (HD == 64) {
-    // pair (i, i + 32): x1 = block fi = 0, x2 = block fi = 1, i = 8 r + j + 4 half_sel
-    float4 cs[2][4][2];
-    auto request = [&](int tj, float4 (&dst)[4][2]) {
+  for (int tj = 0; tj < TJ; ++tj) {
+    const int tok = tok0 + tj * 32;
+    // (cos, sin) of 32 of the block's pairs, the same for every head; the next ones (head dim 128) are requested before the
+    // stores of what these gave: a load issued behind a store waits for the store's acknowledgement as well
+    float4 cs[4][2];
+    auto request = [&](int b) {
       const float2* cs_row = ep.rope + (size_t)pos_of[tj] * (HD / 2) + half_sel * 4;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        dst[r][0] = *(const float4*)(cs_row + 8 * r);
-        dst[r][1] = *(const float4*)(cs_row + 8 * r + 2);
+        cs[r][0] = *(const float4*)(cs_row + b * 32 + 8 * r);
+        cs[r][1] = *(const float4*)(cs_row + b * 32 + 8 * r + 2);
       }
     };
-    request(0, cs[0]);
+    if (rotates) request(0);
+    if (tok >= M) continue;
 #pragma unroll
-    for (int tj = 0; tj < 4; ++tj) {
-      if (tj < 3) request(tj + 1, cs[(tj + 1) & 1]);
-      if (!stores[tj]) continue;
-      f16* dst = head_row(tj);
+    for (int hh = 0; hh < NH; ++hh) {
+      const int head = bx * NH + hh;
+      if (head >= hq && !keeps[tj]) continue;
+      if (head >= hq + hkv) {
+        const int vh = head - hq - hkv;
+        f16* vp = vpool + ((size_t)page_of[tj] * hkv + vh) * HD * kPageTokens + pos_of[tj] % kPageTokens;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int i0 = 8 * r + half_sel * 4;
-        const float4 c01 = cs[tj & 1][r][0], c23 = cs[tj & 1][r][1];
-        const float c[8] = {c01.x, c01.y, c01.z, c01.w, c23.x, c23.y, c23.z, c23.w};
-        f16x4 o1, o2;
+        for (int b = 0; b < NB; ++b)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const float x1 = acc[0][tj][4 * r + j], x2 = acc[1][tj][4 * r + j], co = c[2 * j], sn = c[2 * j + 1];
-          o1[j] = from_f32<f16>(x1 * co - x2 * sn);
-          o2[j] = from_f32<f16>(x2 * co + x1 * sn);
-        }
-        *(f16x4*)(dst + i0) = o1;
-        *(f16x4*)(dst + i0 + 32) = o2;
-      }
-    }
-    return;
-  }
-  // HD = 128, q or k head: pair (i, i + 64); this wave holds x1 (wf = 0) or x2 (wf = 1) at i = fi 32 + 8 r + j + 4 half_sel
-  // and swaps accumulators with the other feature wave through LDS, two token blocks at a time
-  float* ex = (float*)smem;   // [wt][wf][tj2][fi][v][lane]: 2 x 2 x 2 x 2 x 16 x 64 floats = 64 KiB
-  float4 cs[2][4][2];
-  auto request = [&](int tj, float4 (&dst)[2][4][2]) {
-    const float2* cs_row = ep.rope + (size_t)pos_of[tj] * (HD / 2) + half_sel * 4;
-#pragma unroll
-    for (int fi = 0; fi < 2; ++fi)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        dst[fi][r][0] = *(const float4*)(cs_row + fi * 32 + 8 * r);
-        dst[fi][r][1] = *(const float4*)(cs_row + fi * 32 + 8 * r + 2);
-      }
-  };
-#pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    wg_barrier();   // the ring (first round) or the previous round's partners have been read
-#pragma unroll
-    for (int t2 = 0; t2 < 2; ++t2)
-#pragma unroll
-      for (int fi = 0; fi < 2; ++fi)
-#pragma unroll
-        for (int v = 0; v < 16; ++v)
-          ex[((((wt * 2 + wf) * 2 + t2) * 2 + fi) * 16 + v) * 64 + lane] = acc[fi][2 * h + t2][v];
-    __syncthreads();
-#pragma unroll
-    for (int t2 = 0; t2 < 2; ++t2) {
-      const int tj = 2 * h + t2;
-      request(tj, cs);   // all of the block's pairs before its first store (a full block ahead would not fit the registers)
-      if (stores[tj]) {
-        f16* dst = head_row(tj);
-#pragma unroll
-        for (int fi = 0; fi < 2; ++fi) {
-          f32x16 other;
-#pragma unroll
-          for (int v = 0; v < 16; ++v) other[v] = ex[((((wt * 2 + (wf ^ 1)) * 2 + t2) * 2 + fi) * 16 + v) * 64 + lane];
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const int i0 = fi * 32 + 8 * r + half_sel * 4;
-            const float4 c01 = cs[fi][r][0], c23 = cs[fi][r][1];
-            const float c[8] = {c01.x, c01.y, c01.z, c01.w, c23.x, c23.y, c23.z, c23.w};
-            f16x4 o;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-              const float a = acc[fi][tj][4 * r + j], b2 = other[4 * r + j], co = c[2 * j], sn = c[2 * j + 1];
-              o[j] = from_f32<f16>(wf == 0 ? a * co - b2 * sn : a * co + b2 * sn);
-            }
-            *(f16x4*)(dst + wf * 64 + i0) = o;
+          for (int v = 0; v < 16; ++v) {
+            const int f = b * 32 + 8 * (v >> 2) + (v & 3) + half_sel * 4;
+            vp[(size_t)f * kPageTokens] = from_f32<f16>(acc[hh * NB + b][tj][v]);
           }
+        continue;
+      }
+      // start of the row's head: q row-major, k in its page slot
+      f16* dst = head < hq ? ep.q_out + ((size_t)tok * hq + head) * HD
+                           : kpool + (((size_t)page_of[tj] * hkv + (head - hq)) * kPageTokens + pos_of[tj] % kPageTokens) * HD;
+#pragma unroll
+      for (int b = 0; b < NB / 2; ++b) {
+        f16x4 o1[4], o2[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float4 c01 = cs[r][0], c23 = cs[r][1];
+          const float c[8] = {c01.x, c01.y, c01.z, c01.w, c23.x, c23.y, c23.z, c23.w};
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const float x1 = acc[hh * NB + b][tj][4 * r + j], x2 = acc[hh * NB + b + NB / 2][tj][4 * r + j];
+            const float co = c[2 * j], sn = c[2 * j + 1];
+            o1[r][j] = from_f32<f16>(x1 * co - x2 * sn);
+            o2[r][j] = from_f32<f16>(x2 * co + x1 * sn);
+          }
+        }
+        if (b + 1 < NB / 2) request(b + 1);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          *(f16x4*)(dst + b * 32 + 8 * r + half_sel * 4) = o1[r];
+          *(f16x4*)(dst + b * 32 + 8 * r + half_sel * 4 + HD / 2) = o2[r];
         }
       }
     }
@@ -635,7 +591,7 @@ __global__ void __launch_bounds__(256, 2) k_gemm_qkv_rope(const uint4* __restric
 hipError_t m_gemm_qkv_rope(const void* Xp, const void* Wp, int M, int N, int K, const QkvEpi& epi, hipStream_t st) {
   if (M == 0) return hipSuccess;
   const int hd = epi.kv.head_dim;
-  if (N % 128 != 0 || K % 32 != 0 || (hd != 64 && hd != 128) || N != (epi.n_q_heads + 2 * epi.kv.n_kv_heads) * hd)
+  if (N % 128 != 0 || K % 64 != 0 || (hd != 64 && hd != 128) || N != (epi.n_q_heads + 2 * epi.kv.n_kv_heads) * hd)
     return hipErrorInvalidValue;
   static bool attr_done = false;
   if (!attr_done) {
@@ -676,29 +632,29 @@ static bool big_prefers_small_tiles(int NX, int M) {
   return rounds_small <= rounds_big;
 }
 
-hipError_t m_gemm_big(const void* Xp, const void* Wp, int M, int N, int K, BigEpi epi, hipStream_t st) {
-  if (M == 0) return hipSuccess;
-  if (N % 128 != 0 || K % 32 != 0) return hipErrorInvalidValue;
-  constexpr int kSmallLds = kStages * (8 + 8) * 1024;   // the ring of a 128-token tile: 8 token + 8 feature fragments per stage
+template <int TJ, int H>
+static hipError_t launch_big(const void* Xp, const void* Wp, int M, int N, int K, const BigEpi& epi, int grid, hipStream_t st) {
   static bool attr_done = false;
+  // the residual update's four row areas and gains lie in the ring's memory
+  constexpr int lds = ring_bytes(H) > 4 * (32 * 68 + 128) * 4 ? ring_bytes(H) : 4 * (32 * 68 + 128) * 4;
   if (!attr_done) {
-    hipError_t e = hipFuncSetAttribute((const void*)k_gemm_big<4>, hipFuncAttributeMaxDynamicSharedMemorySize, kBigLds);
-    if (e == hipSuccess) e = hipFuncSetAttribute((const void*)k_gemm_big<2>, hipFuncAttributeMaxDynamicSharedMemorySize, kSmallLds);
+    const hipError_t e = hipFuncSetAttribute((const void*)k_gemm_big<TJ, H>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
     attr_done = true;
   }
+  return launch(epi.decode ? KID_GEMM_BIG_DECODE : KID_GEMM_BIG, k_gemm_big<TJ, H>, dim3(grid), dim3(256), lds, st,
+                (const uint4*)Xp, (const uint4*)Wp, M, N, K, epi);
+}
+hipError_t m_gemm_big(const void* Xp, const void* Wp, int M, int N, int K, BigEpi epi, hipStream_t st) {
+  if (M == 0) return hipSuccess;
+  if (N % 128 != 0 || K % (epi.splits > 1 ? 32 : 64) != 0) return hipErrorInvalidValue;
   if (epi.splits < 1 || (epi.splits > 1 && (epi.splits % 8 != 0 || K / 32 < epi.splits || M > 256 ||
                                             epi.mode != BIG_STORE_F32 || epi.ssq_in || epi.bias)))
     return hipErrorInvalidValue;
   if (epi.gain_next && epi.mode != BIG_ADD_F32) return hipErrorInvalidValue;
-  if (epi.splits == 1 && big_prefers_small_tiles(N / 128, M)) {
-    const int g2 = big_grid(N / 128, (M + 127) / 128);
-    return launch(epi.decode ? KID_GEMM_BIG_DECODE : KID_GEMM_BIG, k_gemm_big<2>, dim3(g2), dim3(256), kSmallLds, st,
-                  (const uint4*)Xp, (const uint4*)Wp, M, N, K, epi);
-  }
-  const int g = epi.splits > 1 ? epi.splits * (N / 128) : big_grid(N / 128, (M + 255) / 256);
-  return launch(epi.decode ? KID_GEMM_BIG_DECODE : KID_GEMM_BIG, k_gemm_big<4>, dim3(g), dim3(256), kBigLds, st, (const uint4*)Xp,
-                (const uint4*)Wp, M, N, K, epi);
+  if (epi.splits > 1) return launch_big<2, 2>(Xp, Wp, M, N, K, epi, epi.splits * (N / 128), st);   // a split is a number of 32-k stages
+  if (big_prefers_small_tiles(N / 128, M)) return launch_big<1, 4>(Xp, Wp, M, N, K, epi, big_grid(N / 128, (M + 127) / 128), st);
+  return launch_big<2, 4>(Xp, Wp, M, N, K, epi, big_grid(N / 128, (M + 255) / 256), st);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -758,37 +714,44 @@ __global__ void __launch_bounds__(256, 2) k_lmhead_score(const uint4* __restrict
                                                          const int* __restrict__ row_seq_pos,
                                                          const int32_t* __restrict__ tokens, int T,
                                                          float* __restrict__ partials) {
+  constexpr int TJ = 2, H = 4;
   extern __shared__ uint4 smem[];
-  __shared__ float red_m[2][256], red_l[2][256];
   const int n_rows = *n_rows_dev;
   const int n_ft = V >> 7;
   const int n_groups = (n_ft + kScoreGroup - 1) / kScoreGroup;
   int bx, by;
   if (!big_raster(n_groups, (max_rows + 255) >> 8, bx, by)) return;
-  const int tok0 = by * 256;
-  if (tok0 >= n_rows) return;
+  if (by * 256 >= n_rows) return;
   const int ft_begin = bx * kScoreGroup, ft_end = min(n_ft, ft_begin + kScoreGroup);
   const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63;
-  const int wf = wave & 1, wt = wave >> 1;
-  LseAcc lse[4];
-  int target[4];
+  const int row0 = by * 256 + wave * 64 + (lane & 31);
+  LseAcc lse[TJ];
+  int target[TJ];
 #pragma unroll
-  for (int tj = 0; tj < 4; ++tj) {
+  for (int tj = 0; tj < TJ; ++tj) {
     lse[tj].init();
-    const int row = tok0 + wt * 128 + tj * 32 + (lane & 31);
+    const int row = row0 + tj * 32;
     target[tj] = -1;
     if (row < n_rows) target[tj] = tokens[(size_t)row_seq_pos[2 * row] * T + row_seq_pos[2 * row + 1]];
   }
   float* ztarget = partials + (size_t)max_rows * 2 * n_groups;
+  TileLoop<TJ, H> loop;
+  loop.tokens(Xp, (n_rows + 31) >> 5, K >> 4, by * 8, 0);
+  loop.features(Wp, K >> 4, ft_begin * 4, 0, K / (16 * H), smem);
+  loop.begin();
   for (int ft = ft_begin; ft < ft_end; ++ft) {
-    f32x16 acc[2][4];
-    big_mainloop(Xp, Wp, (n_rows + 31) >> 5, K >> 4, by * 8, ft * 4, smem, acc);
+    f32x16 acc[4][TJ];
+    loop.run(smem, acc);
+    if (ft + 1 < ft_end) {   // the next tile's first stages are on their way during this tile's exponentials
+      wg_barrier();          // every wave has read its last stage
+      loop.features(Wp, K >> 4, (ft + 1) * 4, 0, K / (16 * H), smem);
+      loop.begin();
+    }
 #pragma unroll
-    for (int tj = 0; tj < 4; ++tj) {
-      const int row = tok0 + wt * 128 + tj * 32 + (lane & 31);
+    for (int tj = 0; tj < TJ; ++tj) {
 #pragma unroll
-      for (int fi = 0; fi < 2; ++fi) {
-        const int f0 = ft * 128 + wf * 64 + fi * 32 + (lane >> 5) * 4;
+      for (int fi = 0; fi < 4; ++fi) {
+        const int f0 = ft * 128 + fi * 32 + (lane >> 5) * 4;
         float mt = acc[fi][tj][0];
 #pragma unroll
         for (int v = 1; v < 16; ++v) mt = fmaxf(mt, acc[fi][tj][v]);
@@ -802,28 +765,20 @@ __global__ void __launch_bounds__(256, 2) k_lmhead_score(const uint4* __restrict
         if (dt >= 0 && dt < 32 && (dt & 4) == 0) {
 #pragma unroll
           for (int v = 0; v < 16; ++v)
-            if (dt == 8 * (v >> 2) + (v & 3)) ztarget[row] = acc[fi][tj][v];
+            if (dt == 8 * (v >> 2) + (v & 3)) ztarget[row0 + tj * 32] = acc[fi][tj][v];
         }
       }
     }
   }
-  // merge the two lane halves, then the two feature waves of each token half
+  // merge the two lane halves
 #pragma unroll
-  for (int tj = 0; tj < 4; ++tj) {
+  for (int tj = 0; tj < TJ; ++tj) {
     lse[tj].merge(__shfl_xor(lse[tj].m, 32, 64), __shfl_xor(lse[tj].l, 32, 64));
-    if (lane < 32) {
-      red_m[wf][wt * 128 + tj * 32 + lane] = lse[tj].m;
-      red_l[wf][wt * 128 + tj * 32 + lane] = lse[tj].l;
+    const int row = row0 + tj * 32;
+    if (lane < 32 && row < n_rows) {
+      float* p = partials + ((size_t)bx * max_rows + row) * 2;
+      p[0] = lse[tj].m; p[1] = lse[tj].l;
     }
-  }
-  __syncthreads();
-  const int row = tok0 + threadIdx.x;
-  if (row < n_rows) {
-    LseAcc a;
-    a.m = red_m[0][threadIdx.x]; a.l = red_l[0][threadIdx.x];
-    a.merge(red_m[1][threadIdx.x], red_l[1][threadIdx.x]);
-    float* p = partials + ((size_t)bx * max_rows + row) * 2;
-    p[0] = a.m; p[1] = a.l;
   }
 }
 
@@ -845,7 +800,7 @@ hipError_t m_lmhead_score(const void* Xp, const void* Wp, int max_rows, const in
                           const int* row_seq_pos, const int32_t* tokens, int T, float* partials, float* out_logprobs,
                           hipStream_t st) {
   if (max_rows == 0) return hipSuccess;
-  if (V % 128 != 0 || K % 32 != 0) return hipErrorInvalidValue;
+  if (V % 128 != 0 || K % 64 != 0) return hipErrorInvalidValue;
   static bool attr_done = false;
   if (!attr_done) {
     hipError_t e = hipFuncSetAttribute((const void*)k_lmhead_score, hipFuncAttributeMaxDynamicSharedMemorySize, kBigLds);
@@ -873,30 +828,34 @@ int m_lmhead_sample_big_groups(int V) { return V >> 7; }
 __global__ void __launch_bounds__(256, 2) k_lmhead_sample_big(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp,
                                                               int n_rows, int V, int K, SampleParams sp,
                                                               float* __restrict__ partials) {
+  constexpr int TJ = 2, H = 4;
   extern __shared__ uint4 smem[];
   int ft, by;
   if (!big_raster(V >> 7, (n_rows + 255) >> 8, ft, by)) return;
-  const int tok0 = by * 256;
   const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63;
-  const int wf = wave & 1, wt = wave >> 1;
-  f32x16 acc[2][4];
-  big_mainloop(Xp, Wp, (n_rows + 31) >> 5, K >> 4, by * 8, ft * 4, smem, acc);
+  f32x16 acc[4][TJ];
+  {
+    TileLoop<TJ, H> loop;
+    loop.tokens(Xp, (n_rows + 31) >> 5, K >> 4, by * 8, 0);
+    loop.features(Wp, K >> 4, ft * 4, 0, K / (16 * H), smem);
+    loop.begin();
+    loop.run(smem, acc);
+  }
   resolve_sample_params(sp);
   const int step = *sp.step;
   const bool noisy = sp.temperature != 0.f;
   const float inv_t = noisy ? 1.0f / sp.temperature : 1.0f;
-  wg_barrier();   // the ring is free: it carries the cross-wave merge
-  float* red = (float*)smem;   // [2][256][5]
 #pragma unroll
-  for (int tj = 0; tj < 4; ++tj) {
-    const int row_ = tok0 + wt * 128 + tj * 32 + (lane & 31);
-    const int seq = (sp.slot_seq && row_ < n_rows) ? sp.slot_seq[row_] : row_;   // the noise is keyed on the sequence
+  for (int tj = 0; tj < TJ; ++tj) {
+    const int row = by * 256 + wave * 64 + tj * 32 + (lane & 31);
+    if (by * 256 + wave * 64 + tj * 32 >= n_rows) break;   // a whole block past the end
+    const int seq = (sp.slot_seq && row < n_rows) ? sp.slot_seq[row] : row;   // the noise is keyed on the sequence
     LseAcc lse;
     BestAcc best;
     lse.init();
     best.init();
 #pragma unroll
-    for (int fi = 0; fi < 2; ++fi) {
+    for (int fi = 0; fi < 4; ++fi) {
       float mt = acc[fi][tj][0];
 #pragma unroll
       for (int v = 1; v < 16; ++v) mt = fmaxf(mt, acc[fi][tj][v]);
@@ -908,7 +867,7 @@ __global__ void __launch_bounds__(256, 2) k_lmhead_sample_big(const uint4* __res
       lse.m = mn;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int v0 = ft * 128 + wf * 64 + fi * 32 + 8 * r + (lane >> 5) * 4;
+        const int v0 = ft * 128 + fi * 32 + 8 * r + (lane >> 5) * 4;
         float gn[4] = {0.f, 0.f, 0.f, 0.f};
         if (noisy) gumbel4(sp.seed_lo, sp.seed_hi, (uint32_t)seq, (uint32_t)step, (uint32_t)(v0 >> 2), gn);
 #pragma unroll
@@ -919,33 +878,19 @@ __global__ void __launch_bounds__(256, 2) k_lmhead_sample_big(const uint4* __res
         }
       }
     }
-    // the two lane halves (fixed order); the two feature waves meet in LDS
+    // the two lane halves (fixed order)
     lse.merge(__shfl_xor(lse.m, 32, 64), __shfl_xor(lse.l, 32, 64));
     best.add(__shfl_xor(best.y, 32, 64), __shfl_xor(best.z, 32, 64), __shfl_xor(best.id, 32, 64));
-    if (lane < 32) {
-      float* p = red + ((size_t)wf * 256 + wt * 128 + tj * 32 + lane) * 5;
+    if (lane < 32 && row < n_rows) {
+      float* p = partials + ((size_t)ft * n_rows + row) * 5;
       p[0] = lse.m; p[1] = lse.l; p[2] = best.y; p[3] = best.z; ((int*)p)[4] = best.id;
     }
-  }
-  __syncthreads();
-  const int row = tok0 + threadIdx.x;
-  if (row < n_rows) {
-    LseAcc a; a.init();
-    BestAcc b; b.init();
-#pragma unroll
-    for (int w = 0; w < 2; ++w) {
-      const float* p = red + ((size_t)w * 256 + threadIdx.x) * 5;
-      a.merge(p[0], p[1]);
-      b.add(p[2], p[3], ((const int*)p)[4]);
-    }
-    float* p = partials + ((size_t)ft * n_rows + row) * 5;
-    p[0] = a.m; p[1] = a.l; p[2] = b.y; p[3] = b.z; ((int*)p)[4] = b.id;
   }
 }
 
 hipError_t m_lmhead_sample_big(const void* Xp, const void* Wp, int n_rows, int V, int K, SampleParams sp, float* partials,
                                hipStream_t st) {
-  if (n_rows <= 0 || V % 128 != 0 || K % 32 != 0) return hipErrorInvalidValue;
+  if (n_rows <= 0 || V % 128 != 0 || K % 64 != 0) return hipErrorInvalidValue;
   static bool attr_done = false;
   if (!attr_done) {
     hipError_t e = hipFuncSetAttribute((const void*)k_lmhead_sample_big, hipFuncAttributeMaxDynamicSharedMemorySize, kBigLds);
