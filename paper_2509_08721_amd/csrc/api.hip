@@ -657,6 +657,9 @@ static int run_layers_decode16(const sapo_weights* w, const FwdBufs& b, const De
     HIP_CK(d_decode_layers(pa, c.head_dim, st));
     return SAPO_OK;
   }
+  // Which launch carries the prefetch of which weights: attention, which leaves most compute units idle, gate/up's;
+  // gate/up (152 .. 304 workgroups) down's; down the next layer's QKV and O.  In QKV and O, 3 us each with hardly any
+  // bytes of their own, any prefetch lengthened the launch by more than it saved (50.2 against 46.8 ms per call).
   for (int l = 0; l < c.n_layers; ++l) {
     const LayerWeights& lw = w->layers[l];
     const KVCache kvc = layer_cache(w, cb, l);
@@ -669,7 +672,8 @@ static int run_layers_decode16(const sapo_weights* w, const FwdBufs& b, const De
     HIP_CK(d_gemm_skinny(a, SKM_STORE, st));
     ShareArgs sh_l;
     if (share && share->prefix_pairs > 0) { sh_l = *share; sh_l.layer = l; sh_l.n_layers = c.n_layers; }
-    HIP_CK(d_decode_attention(b.qkv, w->rope, rm, kvc, b.attn, S, c.n_q_heads, &sh_l, st));
+    HIP_CK(d_decode_attention(b.qkv, w->rope, rm, kvc, b.attn, S, c.n_q_heads, &sh_l,
+                              d_prefetch_skinny(lw.wgu16, S, SKM_SWIGLU, 2 * F, d), st));
     // output projection + residual; emits the FFN norm's operand
     SkinnyArgs o{};
     o.n_rows = S; o.s_pad = db.s_pad;
@@ -698,6 +702,7 @@ static int run_layers_decode16(const sapo_weights* w, const FwdBufs& b, const De
     g.Wp = (const uint4*)lw.wgu16; g.Xp = (const uint4*)db.xb; g.N = 2 * F; g.K = d;
     g.ssq_in = db.ssq_b; g.ssq_parts = d / 16;
     g.xp_out = (uint4*)b.act;
+    g.pf = d_prefetch_skinny(lw.wdown16, S, SKM_RESID, d, F);
     HIP_CK(d_gemm_skinny(g, SKM_SWIGLU, st));
     // down projection + residual; emits the next norm's operand
     SkinnyArgs dn{};
@@ -705,6 +710,10 @@ static int run_layers_decode16(const sapo_weights* w, const FwdBufs& b, const De
     dn.Wp = (const uint4*)lw.wdown16; dn.Xp = (const uint4*)b.act; dn.N = d; dn.K = F;
     dn.h = b.h; dn.gain_next = gain_after;
     dn.xp_out = (uint4*)db.xa; dn.ssq_out = db.ssq_a;
+    if (l + 1 < c.n_layers) {
+      dn.pf = d_prefetch_skinny(w->layers[l + 1].wqkv16, S, SKM_STORE, nqkv, d);
+      dn.pf2 = d_prefetch_skinny(w->layers[l + 1].wo16, S, SKM_RESID, d, q);
+    }
     HIP_CK(d_gemm_skinny(dn, SKM_RESID, st));
   }
   return SAPO_OK;
@@ -832,7 +841,8 @@ static int sample_step(const sapo_weights* w, const RolloutPlan& pl, const Rollo
   const int S = lv.slots, d = c.d_model, V = c.vocab;
   if (lv.fused_lm) {
     const float* gain_first = c.n_layers > 0 ? w->layers[0].attn_norm : w->final_norm;
-    HIP_CK(d_lmhead_sample(w->lm_head16, lv.dec.xa, d, V, lv.dec.ssq_a, ssq_parts, lv.dec.s_pad, c.rms_eps, S, sp,
+    HIP_CK(d_lmhead_sample(w->lm_head16, lv.dec.xa, d, V, lv.dec.ssq_a, ssq_parts,
+                           S <= kFewRows && !lv.dec.persistent, lv.dec.s_pad, c.rms_eps, S, sp,
                            lv.partials, w->embed, gain_first, pl.fwd.h, lv.dec.xa, lv.dec.ssq_a, st));
     return SAPO_OK;
   }

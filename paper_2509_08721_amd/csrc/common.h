@@ -395,6 +395,14 @@ hipError_t m_flash_attention(const void* q, RowMap rm, KVCache kv, void* out, in
 
 // decode kernels (kernels_decode.hip) -------------------------------------------------------
 enum { SKM_STORE = 0, SKM_RESID = 1, SKM_SWIGLU = 2 };
+// Weights (W16 fragment order) of a later launch that extra workgroups of an earlier one bring into the L2s: the first
+// ks1 k steps of every tile, the tiles of unit u (2^nt_log2 tiles) into the L2 of XCD u % 8
+struct Prefetch {
+  const uint4* p = nullptr;
+  int KS = 0, n_tiles = 0, nt_log2 = 0, ks1 = 0;
+  int blocks = 0;        // workgroups of 8 waves, a multiple of 8; 0: none
+};
+constexpr int kPrefetchKb = 18;   // blocks of 1 KiB that a prefetching wave has in flight
 struct SkinnyArgs {
   const uint4* Wp;        // weights, W16 fragment order [N/16][K/32][64]
   const uint4* Xp;        // tokens, X16 order [blocks][K/32][4][64]
@@ -411,11 +419,13 @@ struct SkinnyArgs {
   float* h;               // RESID: residual stream [n_rows, N], updated in place
   const float* gain_next; // RESID: gain of the norm that reads the updated residual [N]
   uint4* xp_out;          // RESID: half(h * gain_next), X16 order over K' = N; SWIGLU: act, X16 order over K' = N / 2
+  Prefetch pf, pf2;       // weights of later launches to bring into the L2s
   float* ssq_out;         // RESID: [N/16][s_pad] sums of h^2 over each 16-feature tile
 };
 hipError_t d_pack_weight16(const void* src, int n_rows, int K, void* dst, int dst_tile0, int dst_tile_stride,
                            hipStream_t st);
 hipError_t d_gemm_skinny(const SkinnyArgs& a, int mode, hipStream_t st);
+Prefetch d_prefetch_skinny(const void* w16, int n_rows, int mode, int N, int K);
 hipError_t d_pack_rows_x16(const float* h, const float* gain, int M, int d, void* xp, float* ssq, hipStream_t st);
 // h += sum_z partial[z] (z < splits, each [M, d], split_stride floats apart), then xp and ssq[(d + 1023) / 1024][s_pad]
 hipError_t d_resid_finish_x16(const float* partial, int splits, size_t split_stride, float* h, const float* gain, int M, int d,
@@ -423,12 +433,15 @@ hipError_t d_resid_finish_x16(const float* partial, int splits, size_t split_str
 // Row m <- the embedding of the token that sequence m (slot_seq[m] when slot_seq is given) emitted at step *step - 1
 hipError_t d_embed_x16(const int32_t* tokens, int tok_stride, const int* step, const void* embed, int M, int d,
                        const float* gain, float* h, void* xp, float* ssq, const int* slot_seq, hipStream_t st);
+// d_gemm_skinny leaves the sums of squares of at most this many rows per group of 4 features ([tile][4][16 rows] in place
+// of [tile][64 rows]) and expects them so
+constexpr int kFewRows = 16;
 bool d_lmhead_sample_supported(int K, int n_rows);
 size_t d_lmhead_sample_partial_floats();
 // Fused LM head + sampler for at most 64 sequences, followed by the merge that writes token and
 // log-prob of the step and gathers the token's embedding row for the next step (h, X16 row with
 // gain_first, one ssq part).
-hipError_t d_lmhead_sample(const void* Wp, const void* Xp, int K, int V, const float* ssq, int ssq_parts, int s_pad,
+hipError_t d_lmhead_sample(const void* Wp, const void* Xp, int K, int V, const float* ssq, int ssq_parts, bool ssq_quarters, int s_pad,
                            float eps, int n_rows, SampleParams sp, float* partials, const void* embed,
                            const float* gain_first, float* h, void* xp_first, float* ssq_first, hipStream_t st);
 // Merge of sampler partials [n_parts][row_stride][5] of n_rows sequences: token + log-prob of the step,
@@ -454,7 +467,7 @@ struct ShareArgs {
 };
 constexpr int kSharePrefixMaxColumns = 64;   // G x (query heads per KV head) the prefix workgroups can take
 hipError_t d_decode_attention(const float* qkv, const float2* rope, RowMap rm, KVCache kv, void* out_x16, int S,
-                              int n_q_heads, const ShareArgs* share, hipStream_t st);
+                              int n_q_heads, const ShareArgs* share, const Prefetch& pf, hipStream_t st);
 
 // One decode step's layers as one persistent kernel (decode_persist.hip), up to 64 rows ----------------------
 // Exchange counters between the resident workgroups; zeroed once at the start of a rollout call, then only growing

@@ -39,6 +39,11 @@ __device__ __forceinline__ f32x4 mfma16(const Frag16& a, const Frag16& b, f32x4 
 }
 __device__ __forceinline__ float silu_f(float x) { return x / (1.0f + __expf(-x)); }
 
+// Rounding written out: left to the compiler, which square is rounded on its own differs from kernel to kernel.
+__device__ __forceinline__ float sum_squares4(const float4& s) {
+  return __builtin_fmaf(s.w, s.w, __builtin_fmaf(s.z, s.z, __builtin_fmaf(s.x, s.x, s.y * s.y)));
+}
+
 // uint4 index of the chunk that holds x[tok][k .. k+7] (k a multiple of 8) in X16 order.
 __host__ __device__ __forceinline__ size_t x16_chunk(int tok, int k, int KS) {
   return ((((size_t)(tok >> 6) * KS + (k >> 5)) * 4 + ((tok >> 4) & 3)) * 64) + (tok & 15) + 16 * ((k >> 3) & 3);
@@ -103,6 +108,48 @@ __device__ __forceinline__ float ssq_scale(const float* s_part, int tok_local, i
 }
 
 // ---------------------------------------------------------------------------------------
+// Prefetch workgroup: workgroups behind a launch's own that bring weights of a later launch into the L2s.
+// A decode step is a chain of short launches, and the launches that stream (gate/up 17 MB, down 9 MB on the 0.5B
+// decoder) wait for HBM from a standing start while the others (QKV, attention, O: 4 MB in 13 us) leave it idle.
+// Lines that a kernel has read stay in its XCD's L2 across the kernel boundary, so the extra workgroups run on the XCD
+// whose workgroups will read the weights (block ids are dealt round-robin): XCD x prefetches the tiles of the units
+// x, x + 8, ... of the consumer.  0.5B, 64 rows: gate/up 8.8 -> 6.8 us, down 7.4 -> 6.3, attention (which carries
+// gate/up's 17 MB on the compute units it leaves idle) 5.8 -> 7.0; on the wrong XCD the gain is lost.
+// A wave asks for kPrefetchKb blocks of 1 KiB at once and waits for them once: with 8 in flight and several rounds the
+// launch that carries them got longer by what the consumer gained.
+// ---------------------------------------------------------------------------------------
+__device__ __forceinline__ void prefetch_role(const Prefetch& pf, int block) {
+  const int xcd = block & 7, wv = (block >> 3) * 8 + wave_index(threadIdx.x), nw = pf.blocks;   // blocks / 8 workgroups of 8 waves
+  const int n_units = pf.n_tiles >> pf.nt_log2, mine = ((n_units - xcd + 7) >> 3) << pf.nt_log2;   // tiles of this XCD
+  const int span = pf.ks1, total = mine * span, nt1 = (1 << pf.nt_log2) - 1;
+  const uint4* base = pf.p + (threadIdx.x & 63);
+  u32x4 all = {0, 0, 0, 0};
+  for (int k = wv; k < total; k += nw * kPrefetchKb) {
+    u32x4 v[kPrefetchKb];
+#pragma unroll
+    for (int r = 0; r < kPrefetchKb; ++r) {
+      const int kk = k + r * nw;
+      if (kk < total) {
+        const int m = kk / span, tile = ((((m >> pf.nt_log2) << 3) + xcd) << pf.nt_log2) + (m & nt1);
+        v[r] = *(const u32x4*)(base + ((size_t)tile * pf.KS + (kk - m * span)) * 64);
+      } else {
+        v[r] = u32x4{0, 0, 0, 0};
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < kPrefetchKb; ++r) all |= v[r];
+  }
+  asm volatile("" ::"v"(all));   // the loads are wanted for what they leave behind
+}
+
+__device__ __forceinline__ void prefetch_behind(const SkinnyArgs& a, int first) {
+  const int block = (int)blockIdx.x - first;
+  if (block < 0) return;
+  if (block < a.pf.blocks) prefetch_role(a.pf, block);
+  else prefetch_role(a.pf2, block - a.pf.blocks);
+}
+
+// ---------------------------------------------------------------------------------------
 // Skinny GEMM.  512 threads = 8 waves per workgroup.
 // A workgroup owns NT 16-feature tiles x TG 16-token groups over the whole K; wave w takes the
 // k steps w, w + 8, ... (R of them per round, all loads of a round in flight at once), and the
@@ -117,24 +164,25 @@ __device__ __forceinline__ float ssq_scale(const float* s_part, int tok_local, i
 //   RESID  : h[tok][feat] += acc;  xp_out = half(h * gain_next) in X16 order;  ssq_out[tile][tok] =
 //            sum of h^2 over the tile's 16 features
 // ---------------------------------------------------------------------------------------
-template <int NT, int TG, int R, int MODE>
+template <int NT, int TG, int TS, int R, int MODE>
 // The first arguments are passed one by one (and once more inside the struct): the hardware preloads the first 14 dwords
 // of a kernel's arguments into scalar registers when it starts a wave (-amdgpu-kernarg-preload-count), but not the
 // members of a struct passed by value.  What the kernel needs before its first requests then costs no load:
 // 0.5 us less from the start of a workgroup to its first weight request.
 __global__ void __launch_bounds__(512) k_skinny16(const uint4* Wp_, const uint4* Xp_, const float* ssq_in_, float* h_,
-                                                  const float* gain_next_, int N_, int K_, int n_rows_, int s_pad_,
-                                                  int ssq_parts_, int n_units, SkinnyArgs a_rest) {
+                                                  const float* gain_next_, int N_, int K_, int n_rows_, int ssq_parts_,
+                                                  SkinnyArgs a_rest) {
   SkinnyArgs a = a_rest;
   a.Wp = Wp_; a.Xp = Xp_; a.ssq_in = ssq_in_; a.h = h_; a.gain_next = gain_next_;
-  a.N = N_; a.K = K_; a.n_rows = n_rows_; a.s_pad = s_pad_; a.ssq_parts = ssq_parts_;
+  a.N = N_; a.K = K_; a.n_rows = n_rows_; a.ssq_parts = ssq_parts_;
+  a.s_pad = (a.n_rows + 63) & ~63;
+  const int n_units = (a.N >> 4) / NT;
   // the 8 partial results meet in LDS CH tiles at a time: [8 waves][CH * TG][64 lanes] float4 <= 128 KiB
   constexpr int CH = (NT * TG > 16) ? 16 / TG : NT;
   static_assert(NT % CH == 0 && (MODE != SKM_SWIGLU || CH % 2 == 0), "tile chunking");
   constexpr int RS = (CH * TG * 64 + 511) / 512;   // output slots per thread and chunk
   extern __shared__ float4 red[];
   __shared__ float s_part[512];
-  constexpr int TS = 4 / TG;        // workgroups per (tile unit, token block)
   const int tid = threadIdx.x, wave = wave_index(tid), lane = tid & 63;
   const int KS = a.K >> 5;
   // block id -> (unit, token block, token split).  Ids are dealt round-robin to the 8 XCDs; the workgroups
@@ -145,7 +193,11 @@ __global__ void __launch_bounds__(512) k_skinny16(const uint4* Wp_, const uint4*
   const int unit = (j / (TS * nblk)) * 8 + (blockIdx.x & 7);
   const int tb = inner / TS;
   const int tg0 = (inner % TS) * TG;
-  if (unit >= n_units) return;
+  if (unit >= n_units) {
+    const int first = (n_units + 7) / 8 * 8 * TS * nblk;
+    prefetch_behind(a_rest, first);
+    return;
+  }
   const int tile0 = unit * NT;
   f32x4 acc[NT][TG];
 #pragma unroll
@@ -283,7 +335,7 @@ __global__ void __launch_bounds__(512) k_skinny16(const uint4* Wp_, const uint4*
           *(float4*)(a.h + (size_t)tok * a.N + f0) = s;
           o[0] = from_f32<f16>(s.x * gn.x); o[1] = from_f32<f16>(s.y * gn.y);
           o[2] = from_f32<f16>(s.z * gn.z); o[3] = from_f32<f16>(s.w * gn.w);
-          q = s.x * s.x + s.y * s.y + s.z * s.z + s.w * s.w;
+          q = sum_squares4(s);
         } else {
           o[0] = o[1] = o[2] = o[3] = (f16)0.f;
         }
@@ -296,13 +348,14 @@ __global__ void __launch_bounds__(512) k_skinny16(const uint4* Wp_, const uint4*
   }
 }
 
-template <int NT, int TG, int R, int MODE>
+// TS: workgroups per (tile unit, token block); TG x TS covers the token groups of a block
+template <int NT, int TG, int TS, int R, int MODE>
 static hipError_t launch_skinny(const SkinnyArgs& a, hipStream_t st) {
   constexpr int CH = (NT * TG > 16) ? 16 / TG : NT;
   static bool attr_done = false;
   const size_t smem = (size_t)8 * CH * TG * 64 * sizeof(float4);
   if (!attr_done) {
-    hipError_t e = hipFuncSetAttribute((const void*)k_skinny16<NT, TG, R, MODE>,
+    hipError_t e = hipFuncSetAttribute((const void*)k_skinny16<NT, TG, TS, R, MODE>,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     if (e != hipSuccess) return e;
     attr_done = true;
@@ -310,9 +363,202 @@ static hipError_t launch_skinny(const SkinnyArgs& a, hipStream_t st) {
   if ((a.N / 16) % NT != 0) return hipErrorInvalidValue;
   const int units = a.N / 16 / NT;
   const int blocks = (a.n_rows + 63) / 64;
-  const int gx = (units + 7) / 8 * 8 * (4 / TG) * blocks;
-  return launch(KID_GEMM_SKINNY, k_skinny16<NT, TG, R, MODE>, dim3(gx), dim3(512), smem, st, a.Wp, a.Xp, a.ssq_in, a.h, a.gain_next,
-                a.N, a.K, a.n_rows, a.s_pad, a.ssq_parts, units, a);
+  if (TG * TS * 16 < 64 && (blocks > 1 || a.n_rows > TG * TS * 16)) return hipErrorInvalidValue;
+  if (a.s_pad != blocks * 64) return hipErrorInvalidValue;
+  const int gx = (units + 7) / 8 * 8 * TS * blocks + a.pf.blocks + a.pf2.blocks;
+  return launch(KID_GEMM_SKINNY, k_skinny16<NT, TG, TS, R, MODE>, dim3(gx), dim3(512), smem, st, a.Wp, a.Xp, a.ssq_in, a.h, a.gain_next,
+                a.N, a.K, a.n_rows, a.ssq_parts, a);
+}
+
+// One token block with 2 .. 4 groups of 16 rows: all groups in one workgroup, one group each, or two each.
+template <int NT, int R, int MODE>
+static hipError_t launch_groups(const SkinnyArgs& a, int groups, hipStream_t st) {
+  if (groups == 2) return launch_skinny<NT, 2, 1, R, MODE>(a, st);
+  if (groups == 3) return launch_skinny<NT, 3, 1, R, MODE>(a, st);
+  return launch_skinny<NT, 4, 1, R, MODE>(a, st);
+}
+template <int R, int MODE>
+static hipError_t launch_singles(const SkinnyArgs& a, int groups, hipStream_t st) {
+  if (groups == 2) return launch_skinny<1, 1, 2, R, MODE>(a, st);
+  if (groups == 3) return launch_skinny<1, 1, 3, R, MODE>(a, st);
+  return launch_skinny<1, 1, 4, R, MODE>(a, st);
+}
+template <int R, int MODE>
+static hipError_t launch_pairs(const SkinnyArgs& a, int groups, hipStream_t st) {
+  if (groups == 2) return launch_skinny<1, 2, 1, R, MODE>(a, st);
+  return launch_skinny<1, 2, 2, R, MODE>(a, st);
+}
+
+// ---------------------------------------------------------------------------------------
+// Skinny GEMM for at most 16 rows (one token group): the same sums in the same order as k_skinny16 - wave w multiplies
+// the k steps w, w + 8, ..., the 8 partial results are added through LDS in wave order - with the work cut along the
+// features instead.  With one token group there are only N / 16 tiles: the 0.5B down projection was 56 workgroups of
+// 155 KB of weights (and as much again of token operand, rows past the end included), the gate/up projection 152
+// workgroups of 115 KB that multiplied the three token groups that do not exist as well.  A workgroup here takes one
+// gate/up pair of tiles, or FR = 16 or 8 of a tile's 16 features, and lanes whose row of either operand does not
+// exist are turned away by the buffer bounds instead of fetching.  0.5B decoder, one row: gate/up 9.8 -> 7.8 us, down
+// 7.8 -> 6.7 us per launch with the weights cold, 5.5 and 5.0 us when they were prefetched.
+// ssq_out is left per group of 4 features ([tile][4][16 rows], in the same N / 16 x 64 floats): a tile's features may lie
+// in several workgroups.  The consumer adds the four in the order in which k_skinny16's producer adds them.
+// ---------------------------------------------------------------------------------------
+constexpr unsigned kFewRecords = 0x40000000u;   // bound of the buffer descriptors: a lane offset with this bit set fetches nothing
+
+// Sums of squares for at most 16 rows: thread (wave, lane) asks for parts wave, wave + 8, ...; lane = group of 4 features
+// x row.  parts == 1 (rows that come from an embedding gather): one value per row.
+__device__ __forceinline__ void ssq_publish_few(const float (&sq)[kSsqPerThread], int parts, float* s_part) {
+  const int grp = wave_index(threadIdx.x), lane = threadIdx.x & 63;
+  float s = 0.f;
+#pragma unroll
+  for (int i = 0; i < kSsqPerThread; ++i) {
+    float v = (parts > 1 || lane < 16) ? sq[i] : 0.f;
+    v = sum_xor32(sum_xor16(v));
+    s += (grp + 8 * i < parts) ? v : 0.f;
+  }
+  s_part[threadIdx.x] = s;
+}
+
+template <int FR, int R, int MODE>
+__global__ void __launch_bounds__(512) k_skinny_few(const uint4* Wp_, const uint4* Xp_, const float* ssq_in_, float* h_,
+                                                    const float* gain_next_, int N_, int K_, int n_rows_, int ssq_parts_,
+                                                    SkinnyArgs a_rest) {
+  SkinnyArgs a = a_rest;   // the leading arguments arrive preloaded (see k_skinny16)
+  a.Wp = Wp_; a.Xp = Xp_; a.ssq_in = ssq_in_; a.h = h_; a.gain_next = gain_next_;
+  a.N = N_; a.K = K_; a.n_rows = n_rows_; a.ssq_parts = ssq_parts_;
+  const int n_units = a.N / (MODE == SKM_SWIGLU ? 32 : 16);
+  static_assert(FR == 16 || (FR == 8 && MODE != SKM_SWIGLU), "whole tiles, or halves of them");
+  constexpr int PT = 16 / FR;                       // workgroups per tile (SWIGLU: tile pair)
+  constexpr int NA = MODE == SKM_SWIGLU ? 2 : 1;    // weight fragments per k step
+  __shared__ float4 red[8 * NA * 64];
+  __shared__ float s_part[512];
+  const int tid = threadIdx.x, wave = wave_index(tid), lane = tid & 63;
+  const int KS = a.K >> 5;
+  // the parts of a tile sit 8 block ids apart: one XCD fetches the lines they share
+  const int j = blockIdx.x >> 3, part = j % PT;
+  const int unit = (j / PT) * 8 + (blockIdx.x & 7);
+  if (unit >= n_units) {
+    const int first = (n_units + 7) / 8 * 8 * PT;
+    prefetch_behind(a_rest, first);
+    return;
+  }
+  const int row = lane & 15, kg = lane >> 4;
+  float sq[kSsqPerThread];
+  if (MODE != SKM_RESID) {
+#pragma unroll
+    for (int i = 0; i < kSsqPerThread; ++i) sq[i] = a.ssq_in[min(wave + 8 * i, a.ssq_parts - 1) * 64 + lane];
+  }
+  // epilogue coordinates of a lane of wave 0: row of the batch, first of its 4 features
+  const int tok = row, f0 = unit * 16 + part * FR + kg * 4;
+  const bool live = tok < a.n_rows && kg * 4 < FR;
+  float4 h_old = make_float4(0.f, 0.f, 0.f, 0.f), g_next = h_old;
+  if (MODE == SKM_RESID && wave == 0) {
+    // clamped, so that the requests sit under no lane mask
+    h_old = *(const float4*)(a.h + (size_t)min(tok, a.n_rows - 1) * a.N + min(f0, a.N - 4));
+    g_next = *(const float4*)(a.gain_next + min(f0, a.N - 4));
+  }
+  unsigned woff[NA];
+  woff[0] = row < FR ? (unsigned)(kg * 16 + part * FR + row) * 16u : kFewRecords;
+  if (NA == 2) woff[NA - 1] = (unsigned)KS * 1024u + lane * 16u;   // the up tile lies behind its gate tile
+  const unsigned xoff = row < a.n_rows ? lane * 16u : kFewRecords;
+  const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(
+      (void*)(a.Wp + (size_t)unit * (MODE == SKM_SWIGLU ? 2 : 1) * KS * 64), 0, kFewRecords, 0x00020000);
+  const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc((void*)a.Xp, 0, kFewRecords, 0x00020000);
+  f32x4 acc[NA];
+#pragma unroll
+  for (int t = 0; t < NA; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int k0 = wave; k0 < KS; k0 += 8 * R) {
+    Frag16 wf[R][NA], xf[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      // a k step past the end: the last one's weights again, against tokens that are not fetched (zero)
+      const int ks = min(k0 + 8 * i, KS - 1);
+#pragma unroll
+      for (int t = 0; t < NA; ++t) wf[i][t].n = __builtin_amdgcn_raw_buffer_load_b128(wr, woff[t], ks * 1024, 2);
+      xf[i].n = __builtin_amdgcn_raw_buffer_load_b128(xr, xoff | (k0 + 8 * i < KS ? 0u : kFewRecords), ks * 4096, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+      for (int t = 0; t < NA; ++t) acc[t] = mfma16(wf[i][t], xf[i], acc[t]);
+  }
+#pragma unroll
+  for (int t = 0; t < NA; ++t) red[(wave * NA + t) * 64 + lane] = make_float4(acc[t][0], acc[t][1], acc[t][2], acc[t][3]);
+  if (MODE != SKM_RESID) ssq_publish_few(sq, a.ssq_parts, s_part);
+  __syncthreads();
+  if (wave != 0) return;
+  auto sum8 = [&](int t, int l) -> float4 {
+    float4 s = red[t * 64 + l];
+#pragma unroll
+    for (int w = 1; w < 8; ++w) {
+      const float4 p = red[(w * NA + t) * 64 + l];
+      s.x += p.x; s.y += p.y; s.z += p.z; s.w += p.w;
+    }
+    return s;
+  };
+  float4 s = sum8(0, lane);
+  if (MODE == SKM_SWIGLU) {
+    const float4 us = sum8(NA - 1, lane);
+    const float sc = ssq_scale(s_part, tok, a.norm_dim, a.eps);
+    if (live) {
+      f16x4 o;
+      o[0] = from_f32<f16>(silu_f(s.x * sc) * (us.x * sc)); o[1] = from_f32<f16>(silu_f(s.y * sc) * (us.y * sc));
+      o[2] = from_f32<f16>(silu_f(s.z * sc) * (us.z * sc)); o[3] = from_f32<f16>(silu_f(s.w * sc) * (us.w * sc));
+      *(f16x4*)((f16*)a.xp_out + x16_chunk(tok, f0, a.N >> 6) * 8 + (f0 & 4)) = o;
+    }
+  } else if (MODE == SKM_STORE) {
+    const float sc = ssq_scale(s_part, tok, a.norm_dim, a.eps);
+    if (live) {
+      float4 o = make_float4(s.x * sc, s.y * sc, s.z * sc, s.w * sc);
+      if (a.bias) {
+        const float4 bb = *(const float4*)(a.bias + f0);
+        o.x += bb.x; o.y += bb.y; o.z += bb.z; o.w += bb.w;
+      }
+      *(float4*)(a.out_f32 + (size_t)tok * a.ldc + f0) = o;
+    }
+  } else {
+    s.x += h_old.x; s.y += h_old.y; s.z += h_old.z; s.w += h_old.w;
+    f16x4 o;
+    o[0] = from_f32<f16>(s.x * g_next.x); o[1] = from_f32<f16>(s.y * g_next.y);
+    o[2] = from_f32<f16>(s.z * g_next.z); o[3] = from_f32<f16>(s.w * g_next.w);
+    if (live) {
+      *(float4*)(a.h + (size_t)tok * a.N + f0) = s;
+      *(f16x4*)((f16*)a.xp_out + x16_chunk(tok, f0, a.N >> 5) * 8 + (f0 & 4)) = o;
+      a.ssq_out[unit * 64 + (part * (FR / 4) + kg) * 16 + tok] = sum_squares4(s);
+    }
+  }
+}
+
+template <int FR, int R, int MODE>
+static hipError_t launch_few(const SkinnyArgs& a, hipStream_t st) {
+  const int units = a.N / (MODE == SKM_SWIGLU ? 32 : 16);
+  return launch(KID_GEMM_SKINNY, k_skinny_few<FR, R, MODE>, dim3((units + 7) / 8 * 8 * (16 / FR) + a.pf.blocks + a.pf2.blocks), dim3(512), 0, st, a.Wp, a.Xp,
+                a.ssq_in, a.h, a.gain_next, a.N, a.K, a.n_rows, a.ssq_parts, a);
+}
+template <int FR, int MODE>
+static hipError_t launch_few_r(const SkinnyArgs& a, hipStream_t st) {
+  const int per_wave = ((a.K >> 5) + 7) / 8;
+  if (per_wave <= 4) return launch_few<FR, 4, MODE>(a, st);
+  if (per_wave <= 6) return launch_few<FR, 6, MODE>(a, st);
+  return launch_few<FR, 20, MODE>(a, st);
+}
+
+// Tiles that one XCD's workgroups of a launch read together, as a power of two (the unit of the block numbering above).
+static int skinny_unit_log2(int n_rows, int mode, int K) {
+  if (mode != SKM_SWIGLU) return 0;
+  return n_rows > kFewRows && K <= 1024 ? 2 : 1;
+}
+// Prefetch of a skinny GEMM's weights by an earlier launch of a step with at most 64 rows: all of them, or the leading k
+// steps of every tile where they are more than the L2s hold next to everything else (32 MB: 1.5B gate/up, 55 MB, of
+// which half: 73.9 ms per call of 64 rows against 76.6 with all and 74.6 with none).  The fraction is the same for every
+// tile: leaving whole tiles out leaves the workgroups that read those as late as before.
+Prefetch d_prefetch_skinny(const void* w16, int n_rows, int mode, int N, int K) {
+  Prefetch pf;
+  if (n_rows > 64) return pf;
+  pf.p = (const uint4*)w16;
+  pf.KS = K / 32; pf.n_tiles = N / 16; pf.nt_log2 = skinny_unit_log2(n_rows, mode, K);
+  const size_t cap_kb = 28 * 1024, kb = (size_t)pf.KS * pf.n_tiles;
+  pf.ks1 = kb <= cap_kb ? pf.KS : (int)(pf.KS * cap_kb / kb);
+  pf.blocks = (int)((pf.ks1 * (size_t)pf.n_tiles + 8 * kPrefetchKb - 1) / (8 * kPrefetchKb) + 7) / 8 * 8;
+  return pf;
 }
 
 // Blocking.  A workgroup reads NT weight tiles and TG token groups over the whole K, so what it must
@@ -325,33 +571,40 @@ hipError_t d_gemm_skinny(const SkinnyArgs& a, int mode, hipStream_t st) {
   const int per_wave = ((a.K >> 5) + 7) / 8;   // k steps per wave
   const int tiles = a.N / 16;
   const bool multi = a.n_rows > 64;
+  if (a.n_rows <= kFewRows) {
+    if (mode == SKM_SWIGLU) return a.N % 32 == 0 ? launch_few_r<16, SKM_SWIGLU>(a, st) : hipErrorInvalidValue;
+    if (mode == SKM_STORE) return launch_few_r<16, SKM_STORE>(a, st);
+    // half tiles when whole ones would occupy less than a quarter of the compute units and each is long (0.5B down:
+    // 56 tiles of 155 KB; the 1.5B one, 96 tiles of 287 KB, was slower in halves: 52.7 against 51.0 ms per call of 8 rows)
+    return a.N <= 1024 && per_wave > 8 ? launch_few_r<8, SKM_RESID>(a, st) : launch_few_r<16, SKM_RESID>(a, st);
+  }
+  const int groups = multi ? 4 : (a.n_rows + 15) / 16;   // 16-token groups of a block that hold rows (2 .. 4)
   if (mode == SKM_SWIGLU) {
     if (a.N % 64 != 0) return hipErrorInvalidValue;
-    if (multi && tiles % 8 == 0) return launch_skinny<8, 4, 2, SKM_SWIGLU>(a, st);
-    if (per_wave <= 4) return launch_skinny<4, 4, 4, SKM_SWIGLU>(a, st);
-    return launch_skinny<2, 4, 6, SKM_SWIGLU>(a, st);
+    if (multi && tiles % 8 == 0) return launch_skinny<8, 4, 1, 2, SKM_SWIGLU>(a, st);
+    if (skinny_unit_log2(a.n_rows, mode, a.K) == 2) return launch_groups<4, 4, SKM_SWIGLU>(a, groups, st);
+    return launch_groups<2, 6, SKM_SWIGLU>(a, groups, st);
   }
   // several token blocks and a narrow output: 4 x 4 blocking would leave compute units idle (1.5B QKV at 256 rows:
   // 128 workgroups of 393 KB); two tiles per workgroup double the workgroups at 295 KB each
   const bool few = multi && tiles % 4 == 0 && (tiles / 4) * ((a.n_rows + 63) / 64) < 192;
   // one token block, more 16-token workgroups than compute units (0.5B QKV: 72 tiles x 4 = 288): some compute
   // units would get two workgroups and ingest twice; 32-token workgroups (144 of them, 86 KB each) keep it one each
-  const bool tg2 = !multi && tiles * 4 > 256;
+  const bool tg2 = !multi && tiles * groups > 256;
   if (mode == SKM_STORE) {
-    if (few) return launch_skinny<2, 4, 3, SKM_STORE>(a, st);
-    if (multi && tiles % 4 == 0) return launch_skinny<4, 4, 3, SKM_STORE>(a, st);
-    if (tg2) return per_wave <= 4 ? launch_skinny<1, 2, 4, SKM_STORE>(a, st) : launch_skinny<1, 2, 8, SKM_STORE>(a, st);
-    if (per_wave <= 4) return launch_skinny<1, 1, 4, SKM_STORE>(a, st);
-    return launch_skinny<1, 1, 8, SKM_STORE>(a, st);
+    if (few) return launch_skinny<2, 4, 1, 3, SKM_STORE>(a, st);
+    if (multi && tiles % 4 == 0) return launch_skinny<4, 4, 1, 3, SKM_STORE>(a, st);
+    if (tg2) return per_wave <= 4 ? launch_pairs<4, SKM_STORE>(a, groups, st) : launch_pairs<8, SKM_STORE>(a, groups, st);
+    return per_wave <= 4 ? launch_singles<4, SKM_STORE>(a, groups, st) : launch_singles<8, SKM_STORE>(a, groups, st);
   }
-  if (few && per_wave <= 8) return launch_skinny<2, 4, 3, SKM_RESID>(a, st);
-  if (multi && per_wave <= 8 && tiles % 4 == 0) return launch_skinny<4, 4, 3, SKM_RESID>(a, st);
-  if (multi && tiles % 2 == 0) return launch_skinny<2, 2, 9, SKM_RESID>(a, st);
-  if (tg2 && per_wave <= 4) return launch_skinny<1, 2, 4, SKM_RESID>(a, st);
-  if (tg2 && per_wave <= 8) return launch_skinny<1, 2, 8, SKM_RESID>(a, st);
-  if (per_wave <= 4) return launch_skinny<1, 1, 4, SKM_RESID>(a, st);
-  if (per_wave <= 8) return launch_skinny<1, 1, 8, SKM_RESID>(a, st);
-  return launch_skinny<1, 1, 20, SKM_RESID>(a, st);
+  if (few && per_wave <= 8) return launch_skinny<2, 4, 1, 3, SKM_RESID>(a, st);
+  if (multi && per_wave <= 8 && tiles % 4 == 0) return launch_skinny<4, 4, 1, 3, SKM_RESID>(a, st);
+  if (multi && tiles % 2 == 0) return launch_skinny<2, 2, 2, 9, SKM_RESID>(a, st);
+  if (tg2 && per_wave <= 4) return launch_pairs<4, SKM_RESID>(a, groups, st);
+  if (tg2 && per_wave <= 8) return launch_pairs<8, SKM_RESID>(a, groups, st);
+  if (per_wave <= 4) return launch_singles<4, SKM_RESID>(a, groups, st);
+  if (per_wave <= 8) return launch_singles<8, SKM_RESID>(a, groups, st);
+  return launch_singles<20, SKM_RESID>(a, groups, st);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -492,7 +745,7 @@ template <int N> __device__ __forceinline__ void wait_vmcnt_d() {
 template <int U>
 __global__ void __launch_bounds__(512) k_lmhead_sample16(const uint4* __restrict__ Wp, const uint4* __restrict__ Xp, int KS,
                                                          int n_tiles, const float* __restrict__ ssq, int ssq_parts,
-                                                         int s_pad, int norm_dim, float eps, int n_rows, int seq0,
+                                                         bool ssq_quarters, int s_pad, int norm_dim, float eps, int n_rows, int seq0,
                                                          SampleParams sp, float* __restrict__ partials) {
   extern __shared__ uint4 xs[];   // [KS][4][64]
   __shared__ float s_part[512];
@@ -526,7 +779,8 @@ __global__ void __launch_bounds__(512) k_lmhead_sample16(const uint4* __restrict
     const unsigned xs0 = __builtin_amdgcn_readfirstlane(lds_addr16(xs));
     for (int b = wave * 64; b < KS * 256; b += 512) dma16_lds(Xp + b + lane, xs0 + (unsigned)b * 16u);
   }
-  ssq_publish(sq, ssq_parts, s_part);
+  if (ssq_quarters) ssq_publish_few(sq, ssq_parts, s_part);
+  else ssq_publish(sq, ssq_parts, s_part);
   wait_vmcnt_d<0>();   // this wave's blocks of the operand have landed ...
   __syncthreads();     // ... and everybody's
   if (tid < 64) s_scale[tid] = ssq_scale(s_part, tid, norm_dim, eps);
@@ -659,7 +913,7 @@ size_t d_lmhead_sample_partial_floats() { return (size_t)256 * 64 * 5; }
 
 template <int U>
 static hipError_t launch_lmhead(const uint4* Wp, const uint4* Xp, int KS, int n_tiles, const float* ssq, int ssq_parts,
-                                int s_pad, int norm_dim, float eps, int n_rows, int seq0, SampleParams sp, float* partials,
+                                bool ssq_quarters, int s_pad, int norm_dim, float eps, int n_rows, int seq0, SampleParams sp, float* partials,
                                 int n_wg, hipStream_t st) {
   static bool attr_done = false;
   const size_t smem = (size_t)KS * 256 * sizeof(uint4) < 8 * 64 * 5 * 4 ? 8 * 64 * 5 * 4 : (size_t)KS * 256 * sizeof(uint4);
@@ -668,13 +922,13 @@ static hipError_t launch_lmhead(const uint4* Wp, const uint4* Xp, int KS, int n_
     if (e != hipSuccess) return e;
     attr_done = true;
   }
-  return launch(KID_LMHEAD_SAMPLE, k_lmhead_sample16<U>, dim3(n_wg), dim3(512), smem, st, Wp, Xp, KS, n_tiles, ssq, ssq_parts, s_pad, norm_dim, eps, n_rows, seq0, sp,
+  return launch(KID_LMHEAD_SAMPLE, k_lmhead_sample16<U>, dim3(n_wg), dim3(512), smem, st, Wp, Xp, KS, n_tiles, ssq, ssq_parts, ssq_quarters, s_pad, norm_dim, eps, n_rows, seq0, sp,
                                                 partials);
 }
 
 bool d_lmhead_sample_supported(int K, int n_rows) { return n_rows <= 64 && K % 32 == 0 && (size_t)K * 128 <= 131072; }
 
-hipError_t d_lmhead_sample(const void* Wp, const void* Xp, int K, int V, const float* ssq, int ssq_parts, int s_pad,
+hipError_t d_lmhead_sample(const void* Wp, const void* Xp, int K, int V, const float* ssq, int ssq_parts, bool ssq_quarters, int s_pad,
                            float eps, int n_rows, SampleParams sp, float* partials, const void* embed,
                            const float* gain_first, float* h, void* xp_first, float* ssq_first, hipStream_t st) {
   if (!d_lmhead_sample_supported(K, n_rows) || V % 16 != 0 || ssq == nullptr || ssq_parts < 1 || ssq_parts > 8 * kSsqPerThread)
@@ -685,11 +939,11 @@ hipError_t d_lmhead_sample(const void* Wp, const void* Xp, int K, int V, const f
   hipError_t e;
   {
     if (KS % 7 == 0)
-      e = launch_lmhead<7>((const uint4*)Wp, (const uint4*)Xp, KS, n_tiles, ssq, ssq_parts, s_pad, K, eps, n_rows, 0, sp, partials, n_wg, st);
+      e = launch_lmhead<7>((const uint4*)Wp, (const uint4*)Xp, KS, n_tiles, ssq, ssq_parts, ssq_quarters, s_pad, K, eps, n_rows, 0, sp, partials, n_wg, st);
     else if (KS % 4 == 0)
-      e = launch_lmhead<4>((const uint4*)Wp, (const uint4*)Xp, KS, n_tiles, ssq, ssq_parts, s_pad, K, eps, n_rows, 0, sp, partials, n_wg, st);
+      e = launch_lmhead<4>((const uint4*)Wp, (const uint4*)Xp, KS, n_tiles, ssq, ssq_parts, ssq_quarters, s_pad, K, eps, n_rows, 0, sp, partials, n_wg, st);
     else
-      e = launch_lmhead<1>((const uint4*)Wp, (const uint4*)Xp, KS, n_tiles, ssq, ssq_parts, s_pad, K, eps, n_rows, 0, sp, partials, n_wg, st);
+      e = launch_lmhead<1>((const uint4*)Wp, (const uint4*)Xp, KS, n_tiles, ssq, ssq_parts, ssq_quarters, s_pad, K, eps, n_rows, 0, sp, partials, n_wg, st);
   }
   if (e != hipSuccess) return e;
   return d_lmhead_merge_embed(partials, n_wg, 64, n_rows, sp, embed, K, gain_first, h, xp_first, ssq_first, st);
@@ -892,11 +1146,17 @@ template <int HD, int NW, int PD, bool LDS, bool SHARE>
 __global__ void __launch_bounds__(NW * 64) k_decode_attention16(const float* __restrict__ qkv,
                                                                const float2* __restrict__ rope, const int* step_,
                                                                const int* page_table_, int Lp_, int pages_per_seq_,
-                                                               int n_kv_heads_, int n_q_heads, void* kpool_, RowMap rm,
-                                                               KVCache kv, uint4* __restrict__ out, ShareArgs sh) {
+                                                               int heads_, int n_main, void* kpool_, RowMap rm,
+                                                               KVCache kv, uint4* __restrict__ out, ShareArgs sh, Prefetch pf) {
+  if ((int)blockIdx.x >= n_main) {   // uniform over the workgroup
+    const int first = (n_main + 7) & ~7;
+    if ((int)blockIdx.x >= first) prefetch_role(pf, blockIdx.x - first);
+    return;
+  }
+  const int n_q_heads = heads_ >> 16;
   // what leads from the start of the kernel to its first requests arrives preloaded (see k_skinny16): 14 dwords
   rm.step = step_; rm.Lp = Lp_;
-  kv.page_table = page_table_; kv.pages_per_seq = pages_per_seq_; kv.n_kv_heads = n_kv_heads_; kv.k = kpool_;
+  kv.page_table = page_table_; kv.pages_per_seq = pages_per_seq_; kv.n_kv_heads = heads_ & 0xffff; kv.k = kpool_;
   constexpr int KK = HD / 32;   // k steps of S^T = K Q^T
   constexpr int DT = HD / 16;   // 16-row tiles of O^T
   constexpr int NFRAG = 2 * KK + DT;                        // 1 KiB fragments of one page pair
@@ -1211,7 +1471,7 @@ __global__ void __launch_bounds__(NW * 64) k_decode_attention16(const float* __r
 
 template <int HD, int NW, int PD, bool LDS = false, bool SHARE = false>
 static hipError_t launch_decode_attention(const float* qkv, const float2* rope, RowMap rm, KVCache kv, void* out, int S,
-                                          int n_q_heads, hipStream_t st, const ShareArgs& sh = ShareArgs()) {
+                                          int n_q_heads, hipStream_t st, const Prefetch& pf, const ShareArgs& sh = ShareArgs()) {
   static bool attr_done = false;
   static_assert(PD <= 4, "the LDS variant's waits cover up to 4 slots");
   const size_t smem = LDS ? (size_t)NW * PD * (HD / 8) * 1024
@@ -1222,13 +1482,16 @@ static hipError_t launch_decode_attention(const float* qkv, const float2* rope, 
     if (e != hipSuccess) return e;
     attr_done = true;
   }
-  return launch(SHARE ? KID_DECODE_ATTN_SHARED : KID_DECODE_ATTN, k_decode_attention16<HD, NW, PD, LDS, SHARE>,
-                dim3((SHARE ? sh.n_prefix : 0) + S * kv.n_kv_heads), dim3(NW * 64), smem, st, qkv, rope, rm.step,
-                kv.page_table, rm.Lp, kv.pages_per_seq, kv.n_kv_heads, n_q_heads, kv.k, rm, kv, (uint4*)out, sh);
+  static_assert(NW == 8 || NW == 4, "");
+  const int n_main = (SHARE ? sh.n_prefix : 0) + S * kv.n_kv_heads;
+  const int blocks = NW == 8 && pf.blocks > 0 ? ((n_main + 7) & ~7) + pf.blocks : n_main;   // prefetch workgroups have 8 waves
+  return launch(SHARE ? KID_DECODE_ATTN_SHARED : KID_DECODE_ATTN, k_decode_attention16<HD, NW, PD, LDS, SHARE>, dim3(blocks),
+                dim3(NW * 64), smem, st, qkv, rope, rm.step, kv.page_table, rm.Lp, kv.pages_per_seq,
+                kv.n_kv_heads | (n_q_heads << 16), n_main, kv.k, rm, kv, (uint4*)out, sh, pf);
 }
 
 hipError_t d_decode_attention(const float* qkv, const float2* rope, RowMap rm, KVCache kv, void* out, int S, int n_q_heads,
-                              const ShareArgs* share, hipStream_t st) {
+                              const ShareArgs* share, const Prefetch& pf, hipStream_t st) {
   if (share && share->prefix_pairs > 0) {
     // what the two-role launch assumes: rows are P x G sequences in order, all at one position, with their own
     // page-table rows; the columns of all siblings fit the prefix workgroup's four MFMA tiles
@@ -1237,7 +1500,7 @@ hipError_t d_decode_attention(const float* qkv, const float2* rope, RowMap rm, K
         share->G * rep > kSharePrefixMaxColumns || share->n_prefix != (S / share->G) * kv.n_kv_heads || !share->pre ||
         !share->flags || !share->fault || share->prefix_pairs * 32 > rm.Lp)
       return hipErrorInvalidValue;
-    return launch_decode_attention<64, 8, 3, false, true>(qkv, rope, rm, kv, out, S, n_q_heads, st, *share);
+    return launch_decode_attention<64, 8, 3, false, true>(qkv, rope, rm, kv, out, S, n_q_heads, st, pf, *share);
   }
   // SAPO_ATTN_LDS=1 in the environment: the LDS-staged variant, kept as the measured alternative (0.5B-class decoder,
   // 64 sequences, same waves and pairs in flight: 6.6 against 5.8 us per launch at contexts 128..383, 12.5 against
@@ -1245,14 +1508,14 @@ hipError_t d_decode_attention(const float* qkv, const float2* rope, RowMap rm, K
   // that a test can switch it; a captured decode step keeps the variant it was captured with.
   const char* lds_env = getenv("SAPO_ATTN_LDS");
   if (kv.head_dim == 64) {
-    if (lds_env && lds_env[0] == '1') return launch_decode_attention<64, 8, 2, true>(qkv, rope, rm, kv, out, S, n_q_heads, st);
-    return launch_decode_attention<64, 8, 3>(qkv, rope, rm, kv, out, S, n_q_heads, st);
+    if (lds_env && lds_env[0] == '1') return launch_decode_attention<64, 8, 2, true>(qkv, rope, rm, kv, out, S, n_q_heads, st, pf);
+    return launch_decode_attention<64, 8, 3>(qkv, rope, rm, kv, out, S, n_q_heads, st, pf);
   }
   if (kv.head_dim == 128) {
     // more workgroups than compute units: 4-wave workgroups with one page pair in flight per wave leave room for
     // two per compute unit, so the whole grid is resident at once (1.5B, 256 sequences: 24.7 us against 29.8)
-    if (S * kv.n_kv_heads > 256) return launch_decode_attention<128, 4, 1>(qkv, rope, rm, kv, out, S, n_q_heads, st);
-    return launch_decode_attention<128, 8, 2>(qkv, rope, rm, kv, out, S, n_q_heads, st);
+    if (S * kv.n_kv_heads > 256) return launch_decode_attention<128, 4, 1>(qkv, rope, rm, kv, out, S, n_q_heads, st, pf);
+    return launch_decode_attention<128, 8, 2>(qkv, rope, rm, kv, out, S, n_q_heads, st, pf);
   }
   return hipErrorInvalidValue;
 }
