@@ -659,7 +659,9 @@ static int run_layers_decode16(const sapo_weights* w, const FwdBufs& b, const De
   }
   // Which launch carries the prefetch of which weights: attention, which leaves most compute units idle, gate/up's;
   // gate/up (152 .. 304 workgroups) down's; down the next layer's QKV and O.  In QKV and O, 3 us each with hardly any
-  // bytes of their own, any prefetch lengthened the launch by more than it saved (50.2 against 46.8 ms per call).
+  // bytes of their own, any prefetch lengthened the launch by more than it saved (50.2 against 46.8 ms per call).  With
+  // more than 64 rows gate/up's and down's weights are not prefetched: attention fills the chip there, and the
+  // token-parallel GEMM waits for its stages rather than for HBM (1.5B, 256 rows: 71.9 against 69.3 ms per call).
   for (int l = 0; l < c.n_layers; ++l) {
     const LayerWeights& lw = w->layers[l];
     const KVCache kvc = layer_cache(w, cb, l);
@@ -673,7 +675,7 @@ static int run_layers_decode16(const sapo_weights* w, const FwdBufs& b, const De
     ShareArgs sh_l;
     if (share && share->prefix_pairs > 0) { sh_l = *share; sh_l.layer = l; sh_l.n_layers = c.n_layers; }
     HIP_CK(d_decode_attention(b.qkv, w->rope, rm, kvc, b.attn, S, c.n_q_heads, &sh_l,
-                              d_prefetch_skinny(lw.wgu16, S, SKM_SWIGLU, 2 * F, d), st));
+                              S <= 64 ? d_prefetch_skinny(lw.wgu16, S, SKM_SWIGLU, 2 * F, d) : Prefetch(), st));
     // output projection + residual; emits the FFN norm's operand
     SkinnyArgs o{};
     o.n_rows = S; o.s_pad = db.s_pad;
@@ -691,6 +693,7 @@ static int run_layers_decode16(const sapo_weights* w, const FwdBufs& b, const De
       HIP_CK(m_gemm_big(b.a, lw.wgu, S, 2 * F, d, ge, st));
       BigEpi pe{BIG_STORE_F32, db.partial, d, nullptr};
       pe.splits = db.down_splits; pe.split_stride = (size_t)S * d; pe.decode = true;
+      if (l + 1 < c.n_layers) pe.pf = d_prefetch_skinny(w->layers[l + 1].wqkv16, S, SKM_STORE, nqkv, d);
       HIP_CK(m_gemm_big(b.act, lw.wdown, S, d, F, pe, st));
       HIP_CK(d_resid_finish_x16(db.partial, db.down_splits, (size_t)S * d, b.h, gain_after, S, d, db.s_pad, db.xa, db.ssq_a,
                                 st));
@@ -702,7 +705,7 @@ static int run_layers_decode16(const sapo_weights* w, const FwdBufs& b, const De
     g.Wp = (const uint4*)lw.wgu16; g.Xp = (const uint4*)db.xb; g.N = 2 * F; g.K = d;
     g.ssq_in = db.ssq_b; g.ssq_parts = d / 16;
     g.xp_out = (uint4*)b.act;
-    g.pf = d_prefetch_skinny(lw.wdown16, S, SKM_RESID, d, F);
+    if (S <= 64) g.pf = d_prefetch_skinny(lw.wdown16, S, SKM_RESID, d, F);
     HIP_CK(d_gemm_skinny(g, SKM_SWIGLU, st));
     // down projection + residual; emits the next norm's operand
     SkinnyArgs dn{};

@@ -117,14 +117,23 @@ __device__ __forceinline__ float wave_reduce_sum(float v) {
   return v;
 }
 
+// Both halves of a 32 x 32 bit product in one instruction; written as two products the compiler keeps two.
+__device__ __forceinline__ void mul_wide(uint32_t a, uint32_t b, uint32_t& hi, uint32_t& lo) {
+  uint64_t p;
+  asm("v_mad_u64_u32 %0, vcc, %1, %2, 0" : "=v"(p) : "v"(a), "s"(b) : "vcc");
+  hi = (uint32_t)(p >> 32);
+  lo = (uint32_t)p;
+}
+
 // Philox4x32-10 (Salmon et al., SC'11): ten rounds on a 4-word counter with a 2-word key.
 struct Philox4 { uint32_t x, y, z, w; };
 __device__ __forceinline__ Philox4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
                                                  uint32_t k0, uint32_t k1) {
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
-    const uint32_t hi0 = __umulhi(0xD2511F53u, c0), lo0 = 0xD2511F53u * c0;
-    const uint32_t hi1 = __umulhi(0xCD9E8D57u, c2), lo1 = 0xCD9E8D57u * c2;
+    uint32_t hi0, lo0, hi1, lo1;
+    mul_wide(c0, 0xD2511F53u, hi0, lo0);
+    mul_wide(c2, 0xCD9E8D57u, hi1, lo1);
     const uint32_t n0 = hi1 ^ c1 ^ k0, n2 = hi0 ^ c3 ^ k1;
     c0 = n0; c1 = lo1; c2 = n2; c3 = lo0;
     k0 += 0x9E3779B9u; k1 += 0xBB67AE85u;
@@ -134,9 +143,18 @@ __device__ __forceinline__ Philox4 philox4x32_10(uint32_t c0, uint32_t c1, uint3
 
 // Standard Gumbel noise from one 32-bit random word: u = (2 (x >> 9) + 1) 2^-24 is strictly
 // inside (0, 1) and exact in fp32; g = -ln(-ln u).
+// Four values took 712 cycles of a wave, 411 of them in the logarithms, which is what bounded the LM head of 65 and more
+// rows (118 us per step at 192 rows of the 0.5B decoder).  The arguments here are normal numbers (u >= 2^-24,
+// 2^-24 < -ln u < 17), so the logarithm needs no range handling: log2 of the hardware times ln 2 as a two-part
+// constant.  Equal to logf in every bit for all 2^23 values of u; 480 cycles.
+__device__ __forceinline__ float ln_normal(float x) {
+  constexpr float c = 0x1.62e42ep-1f, c_low = 0x1.efa39ep-25f;   // ln 2 = 0x1.62e42fefa39efp-1
+  const float y = __builtin_amdgcn_logf(x), r = y * c;
+  return r + __builtin_fmaf(y, c_low, __builtin_fmaf(y, c, -r));
+}
 __device__ __forceinline__ float gumbel_from_bits(uint32_t x) {
   const float u = (float)(2u * (x >> 9) + 1u) * 5.9604644775390625e-08f;
-  return -logf(-logf(u));
+  return -ln_normal(-ln_normal(u));
 }
 
 // Noise for vocab entries 4*blk .. 4*blk+3 of (seed, seq, step): counter (blk, step, seq, 0),
@@ -334,6 +352,84 @@ hipError_t g_gumbel(uint32_t seed_lo, uint32_t seed_hi, uint32_t seq, uint32_t s
 // =======================================================================================
 namespace sapo {
 
+// Weights (fragment order: tiles of KS blocks of 1 KiB) of a later launch that extra workgroups of an earlier one bring into
+// the L2s: the first ks1 blocks of every tile, the tiles of unit u (2^nt_log2 tiles) into the L2 of XCD u % 8.
+struct Prefetch {
+  const uint4* p = nullptr;
+  int KS = 0, n_tiles = 0, nt_log2 = 0, ks1 = 0;   // ks1 = 0: nothing
+  int splits = 0;   // > 0: the operand of a split-K k_gemm_big instead: XCD x gets the K ranges of the splits x, x + 8, ...
+};
+constexpr int kPrefetchKb = 18;   // blocks of 1 KiB that a prefetching wave has in flight
+// workgroups of `waves` waves for it, a multiple of 8
+inline int prefetch_blocks(const Prefetch& pf, int waves) {
+  const long kb = (long)pf.ks1 * pf.n_tiles;
+  if (pf.splits > 0) return (int)((pf.n_tiles * (pf.splits >> 3) + waves - 1) / waves) * 8;
+  return (int)((kb + waves * kPrefetchKb - 1) / (waves * kPrefetchKb) + 7) / 8 * 8;
+}
+// All of a weight matrix, or the leading blocks of every tile where it is more than the L2s hold next to everything else
+// (32 MB: 1.5B gate/up, 55 MB, of which half: 73.9 ms per call of 64 rows against 76.6 with all and 74.6 with none).
+// The fraction is the same for every tile: leaving whole tiles out leaves the workgroups that read those as late as before.
+inline Prefetch make_prefetch(const void* w, int KS, int n_tiles, int nt_log2) {
+  Prefetch pf;
+  pf.p = (const uint4*)w; pf.KS = KS; pf.n_tiles = n_tiles; pf.nt_log2 = nt_log2;
+  const size_t cap_kb = 28 * 1024, kb = (size_t)KS * n_tiles;
+  pf.ks1 = kb <= cap_kb ? KS : (int)(KS * cap_kb / kb);
+  return pf;
+}
+typedef unsigned int prefetch_u32x4 __attribute__((ext_vector_type(4)));
+// ---------------------------------------------------------------------------------------
+// Prefetch workgroup: workgroups behind a launch's own that bring weights of a later launch into the L2s.
+// A decode step is a chain of short launches, and the launches that stream (gate/up 17 MB, down 9 MB on the 0.5B
+// decoder) wait for HBM from a standing start while the others (QKV, attention, O: 4 MB in 13 us) leave it idle.
+// Lines that a kernel has read stay in its XCD's L2 across the kernel boundary, so the extra workgroups run on the XCD
+// whose workgroups will read the weights (block ids are dealt round-robin): XCD x prefetches the tiles of the units
+// x, x + 8, ... of the consumer.  0.5B, 64 rows: gate/up 8.8 -> 6.8 us, down 7.4 -> 6.3, attention (which carries
+// gate/up's 17 MB on the compute units it leaves idle) 5.8 -> 7.0; on the wrong XCD the gain is lost.
+// A wave asks for kPrefetchKb blocks of 1 KiB at once and waits for them once: with 8 in flight and several rounds the
+// launch that carries them got longer by what the consumer gained.
+// ---------------------------------------------------------------------------------------
+template <int NW>   // waves of a workgroup
+__device__ __forceinline__ void prefetch_role(const Prefetch& pf, int block, int n_blocks) {
+  const int xcd = block & 7, wv = (block >> 3) * NW + wave_index(threadIdx.x), nw = (n_blocks >> 3) * NW;   // waves per XCD
+  const uint4* base = pf.p + (threadIdx.x & 63);
+  prefetch_u32x4 all = {0, 0, 0, 0};
+  if (pf.splits > 0) {
+    // wave -> (tile, split): the split's blocks of the tile (stages of 2 blocks, as k_gemm_big cuts them)
+    const int per = pf.splits >> 3, n_st = pf.KS >> 1;
+    for (int c = wv; c < pf.n_tiles * per; c += nw) {
+      const int tile = c / per, z = (c - tile * per) * 8 + xcd;
+      const int b0 = 2 * (int)((long)z * n_st / pf.splits), b1 = 2 * (int)((long)(z + 1) * n_st / pf.splits);
+      for (int b = b0; b < b1; b += kPrefetchKb) {
+        prefetch_u32x4 v[kPrefetchKb];
+#pragma unroll
+        for (int r = 0; r < kPrefetchKb; ++r) v[r] = *(const prefetch_u32x4*)(base + ((size_t)tile * pf.KS + min(b + r, b1 - 1)) * 64);
+#pragma unroll
+        for (int r = 0; r < kPrefetchKb; ++r) all |= v[r];
+      }
+    }
+    asm volatile("" ::"v"(all));
+    return;
+  }
+  const int n_units = pf.n_tiles >> pf.nt_log2, mine = ((n_units - xcd + 7) >> 3) << pf.nt_log2;   // tiles of this XCD
+  const int span = pf.ks1, total = mine * span, nt1 = (1 << pf.nt_log2) - 1;
+  for (int k = wv; k < total; k += nw * kPrefetchKb) {
+    prefetch_u32x4 v[kPrefetchKb];
+#pragma unroll
+    for (int r = 0; r < kPrefetchKb; ++r) {
+      const int kk = k + r * nw;
+      if (kk < total) {
+        const int m = kk / span, tile = ((((m >> pf.nt_log2) << 3) + xcd) << pf.nt_log2) + (m & nt1);
+        v[r] = *(const prefetch_u32x4*)(base + ((size_t)tile * pf.KS + (kk - m * span)) * 64);
+      } else {
+        v[r] = prefetch_u32x4{0, 0, 0, 0};
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < kPrefetchKb; ++r) all |= v[r];
+  }
+  asm volatile("" ::"v"(all));   // the loads are wanted for what they leave behind
+}
+
 struct BigEpi {
   int mode;            // see enum below
   float* out_f32;      // STORE_F32 / ADD_F32: [M, ldc]
@@ -347,7 +443,9 @@ struct BigEpi {
   // to out_f32 + z * split_stride.
   int splits = 1;
   size_t split_stride = 0;
-  bool decode = false;   // accounting only: a launch of the decode step (weight-streaming-bound)
+  bool decode = false;   // a launch of the decode step (weight-streaming-bound)
+  Prefetch pf;           // weights of a later launch to bring into the L2s
+  int main_blocks = 0;   // set by the launcher: the workgroups behind these prefetch
   const float* ssq_in = nullptr;   // [M, ssq_parts rounded up to a multiple of 4]; at most 16 parts
   int ssq_parts = 0;
   float norm_dim = 0.f, eps = 0.f;
@@ -395,14 +493,6 @@ hipError_t m_flash_attention(const void* q, RowMap rm, KVCache kv, void* out, in
 
 // decode kernels (kernels_decode.hip) -------------------------------------------------------
 enum { SKM_STORE = 0, SKM_RESID = 1, SKM_SWIGLU = 2 };
-// Weights (W16 fragment order) of a later launch that extra workgroups of an earlier one bring into the L2s: the first
-// ks1 k steps of every tile, the tiles of unit u (2^nt_log2 tiles) into the L2 of XCD u % 8
-struct Prefetch {
-  const uint4* p = nullptr;
-  int KS = 0, n_tiles = 0, nt_log2 = 0, ks1 = 0;
-  int blocks = 0;        // workgroups of 8 waves, a multiple of 8; 0: none
-};
-constexpr int kPrefetchKb = 18;   // blocks of 1 KiB that a prefetching wave has in flight
 struct SkinnyArgs {
   const uint4* Wp;        // weights, W16 fragment order [N/16][K/32][64]
   const uint4* Xp;        // tokens, X16 order [blocks][K/32][4][64]
@@ -420,6 +510,7 @@ struct SkinnyArgs {
   const float* gain_next; // RESID: gain of the norm that reads the updated residual [N]
   uint4* xp_out;          // RESID: half(h * gain_next), X16 order over K' = N; SWIGLU: act, X16 order over K' = N / 2
   Prefetch pf, pf2;       // weights of later launches to bring into the L2s
+  int pf_blocks;          // workgroups of pf (set by the launcher)
   float* ssq_out;         // RESID: [N/16][s_pad] sums of h^2 over each 16-feature tile
 };
 hipError_t d_pack_weight16(const void* src, int n_rows, int K, void* dst, int dst_tile0, int dst_tile_stride,

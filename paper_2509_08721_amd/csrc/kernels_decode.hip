@@ -107,46 +107,11 @@ __device__ __forceinline__ float ssq_scale(const float* s_part, int tok_local, i
   return 1.0f / sqrtf(s / (float)norm_dim + eps);
 }
 
-// ---------------------------------------------------------------------------------------
-// Prefetch workgroup: workgroups behind a launch's own that bring weights of a later launch into the L2s.
-// A decode step is a chain of short launches, and the launches that stream (gate/up 17 MB, down 9 MB on the 0.5B
-// decoder) wait for HBM from a standing start while the others (QKV, attention, O: 4 MB in 13 us) leave it idle.
-// Lines that a kernel has read stay in its XCD's L2 across the kernel boundary, so the extra workgroups run on the XCD
-// whose workgroups will read the weights (block ids are dealt round-robin): XCD x prefetches the tiles of the units
-// x, x + 8, ... of the consumer.  0.5B, 64 rows: gate/up 8.8 -> 6.8 us, down 7.4 -> 6.3, attention (which carries
-// gate/up's 17 MB on the compute units it leaves idle) 5.8 -> 7.0; on the wrong XCD the gain is lost.
-// A wave asks for kPrefetchKb blocks of 1 KiB at once and waits for them once: with 8 in flight and several rounds the
-// launch that carries them got longer by what the consumer gained.
-// ---------------------------------------------------------------------------------------
-__device__ __forceinline__ void prefetch_role(const Prefetch& pf, int block) {
-  const int xcd = block & 7, wv = (block >> 3) * 8 + wave_index(threadIdx.x), nw = pf.blocks;   // blocks / 8 workgroups of 8 waves
-  const int n_units = pf.n_tiles >> pf.nt_log2, mine = ((n_units - xcd + 7) >> 3) << pf.nt_log2;   // tiles of this XCD
-  const int span = pf.ks1, total = mine * span, nt1 = (1 << pf.nt_log2) - 1;
-  const uint4* base = pf.p + (threadIdx.x & 63);
-  u32x4 all = {0, 0, 0, 0};
-  for (int k = wv; k < total; k += nw * kPrefetchKb) {
-    u32x4 v[kPrefetchKb];
-#pragma unroll
-    for (int r = 0; r < kPrefetchKb; ++r) {
-      const int kk = k + r * nw;
-      if (kk < total) {
-        const int m = kk / span, tile = ((((m >> pf.nt_log2) << 3) + xcd) << pf.nt_log2) + (m & nt1);
-        v[r] = *(const u32x4*)(base + ((size_t)tile * pf.KS + (kk - m * span)) * 64);
-      } else {
-        v[r] = u32x4{0, 0, 0, 0};
-      }
-    }
-#pragma unroll
-    for (int r = 0; r < kPrefetchKb; ++r) all |= v[r];
-  }
-  asm volatile("" ::"v"(all));   // the loads are wanted for what they leave behind
-}
-
 __device__ __forceinline__ void prefetch_behind(const SkinnyArgs& a, int first) {
   const int block = (int)blockIdx.x - first;
   if (block < 0) return;
-  if (block < a.pf.blocks) prefetch_role(a.pf, block);
-  else prefetch_role(a.pf2, block - a.pf.blocks);
+  if (block < a.pf_blocks) prefetch_role<8>(a.pf, block, a.pf_blocks);
+  else prefetch_role<8>(a.pf2, block - a.pf_blocks, (int)gridDim.x - first - a.pf_blocks);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -350,7 +315,8 @@ __global__ void __launch_bounds__(512) k_skinny16(const uint4* Wp_, const uint4*
 
 // TS: workgroups per (tile unit, token block); TG x TS covers the token groups of a block
 template <int NT, int TG, int TS, int R, int MODE>
-static hipError_t launch_skinny(const SkinnyArgs& a, hipStream_t st) {
+static hipError_t launch_skinny(SkinnyArgs a, hipStream_t st) {
+  a.pf_blocks = prefetch_blocks(a.pf, 8);
   constexpr int CH = (NT * TG > 16) ? 16 / TG : NT;
   static bool attr_done = false;
   const size_t smem = (size_t)8 * CH * TG * 64 * sizeof(float4);
@@ -365,7 +331,7 @@ static hipError_t launch_skinny(const SkinnyArgs& a, hipStream_t st) {
   const int blocks = (a.n_rows + 63) / 64;
   if (TG * TS * 16 < 64 && (blocks > 1 || a.n_rows > TG * TS * 16)) return hipErrorInvalidValue;
   if (a.s_pad != blocks * 64) return hipErrorInvalidValue;
-  const int gx = (units + 7) / 8 * 8 * TS * blocks + a.pf.blocks + a.pf2.blocks;
+  const int gx = (units + 7) / 8 * 8 * TS * blocks + a.pf_blocks + prefetch_blocks(a.pf2, 8);
   return launch(KID_GEMM_SKINNY, k_skinny16<NT, TG, TS, R, MODE>, dim3(gx), dim3(512), smem, st, a.Wp, a.Xp, a.ssq_in, a.h, a.gain_next,
                 a.N, a.K, a.n_rows, a.ssq_parts, a);
 }
@@ -528,9 +494,10 @@ __global__ void __launch_bounds__(512) k_skinny_few(const uint4* Wp_, const uint
 }
 
 template <int FR, int R, int MODE>
-static hipError_t launch_few(const SkinnyArgs& a, hipStream_t st) {
+static hipError_t launch_few(SkinnyArgs a, hipStream_t st) {
+  a.pf_blocks = prefetch_blocks(a.pf, 8);
   const int units = a.N / (MODE == SKM_SWIGLU ? 32 : 16);
-  return launch(KID_GEMM_SKINNY, k_skinny_few<FR, R, MODE>, dim3((units + 7) / 8 * 8 * (16 / FR) + a.pf.blocks + a.pf2.blocks), dim3(512), 0, st, a.Wp, a.Xp,
+  return launch(KID_GEMM_SKINNY, k_skinny_few<FR, R, MODE>, dim3((units + 7) / 8 * 8 * (16 / FR) + a.pf_blocks + prefetch_blocks(a.pf2, 8)), dim3(512), 0, st, a.Wp, a.Xp,
                 a.ssq_in, a.h, a.gain_next, a.N, a.K, a.n_rows, a.ssq_parts, a);
 }
 template <int FR, int MODE>
@@ -541,24 +508,19 @@ static hipError_t launch_few_r(const SkinnyArgs& a, hipStream_t st) {
   return launch_few<FR, 20, MODE>(a, st);
 }
 
-// Tiles that one XCD's workgroups of a launch read together, as a power of two (the unit of the block numbering above).
-static int skinny_unit_log2(int n_rows, int mode, int K) {
-  if (mode != SKM_SWIGLU) return 0;
-  return n_rows > kFewRows && K <= 1024 ? 2 : 1;
+// 16-feature tiles that a workgroup of the launch below reads, as a power of two: what the block numbering calls a unit.
+static int skinny_unit_log2(int n_rows, int mode, int N, int K) {
+  const int tiles = N / 16;
+  if (n_rows <= kFewRows) return mode == SKM_SWIGLU ? 1 : 0;
+  if (n_rows <= 64) return mode != SKM_SWIGLU ? 0 : K <= 1024 ? 2 : 1;
+  if (mode == SKM_SWIGLU) return tiles % 8 == 0 ? 3 : K <= 1024 ? 2 : 1;
+  if (mode == SKM_RESID && K > 2048) return tiles % 2 == 0 ? 1 : 0;
+  if (tiles % 4 != 0) return mode == SKM_RESID && tiles % 2 == 0 ? 1 : 0;
+  return (tiles / 4) * ((n_rows + 63) / 64) < 192 ? 1 : 2;
 }
-// Prefetch of a skinny GEMM's weights by an earlier launch of a step with at most 64 rows: all of them, or the leading k
-// steps of every tile where they are more than the L2s hold next to everything else (32 MB: 1.5B gate/up, 55 MB, of
-// which half: 73.9 ms per call of 64 rows against 76.6 with all and 74.6 with none).  The fraction is the same for every
-// tile: leaving whole tiles out leaves the workgroups that read those as late as before.
+// Prefetch of a skinny GEMM's weights by an earlier launch of a step of n_rows rows.
 Prefetch d_prefetch_skinny(const void* w16, int n_rows, int mode, int N, int K) {
-  Prefetch pf;
-  if (n_rows > 64) return pf;
-  pf.p = (const uint4*)w16;
-  pf.KS = K / 32; pf.n_tiles = N / 16; pf.nt_log2 = skinny_unit_log2(n_rows, mode, K);
-  const size_t cap_kb = 28 * 1024, kb = (size_t)pf.KS * pf.n_tiles;
-  pf.ks1 = kb <= cap_kb ? pf.KS : (int)(pf.KS * cap_kb / kb);
-  pf.blocks = (int)((pf.ks1 * (size_t)pf.n_tiles + 8 * kPrefetchKb - 1) / (8 * kPrefetchKb) + 7) / 8 * 8;
-  return pf;
+  return make_prefetch(w16, K / 32, N / 16, skinny_unit_log2(n_rows, mode, N, K));
 }
 
 // Blocking.  A workgroup reads NT weight tiles and TG token groups over the whole K, so what it must
@@ -582,7 +544,7 @@ hipError_t d_gemm_skinny(const SkinnyArgs& a, int mode, hipStream_t st) {
   if (mode == SKM_SWIGLU) {
     if (a.N % 64 != 0) return hipErrorInvalidValue;
     if (multi && tiles % 8 == 0) return launch_skinny<8, 4, 1, 2, SKM_SWIGLU>(a, st);
-    if (skinny_unit_log2(a.n_rows, mode, a.K) == 2) return launch_groups<4, 4, SKM_SWIGLU>(a, groups, st);
+    if (per_wave <= 4) return launch_groups<4, 4, SKM_SWIGLU>(a, groups, st);
     return launch_groups<2, 6, SKM_SWIGLU>(a, groups, st);
   }
   // several token blocks and a narrow output: 4 x 4 blocking would leave compute units idle (1.5B QKV at 256 rows:
@@ -659,11 +621,20 @@ __global__ void __launch_bounds__(128) k_resid_finish_x16(const float* __restric
     float* hp = h + (size_t)row * d + k;
     const float4 a = *(const float4*)hp, b = *(const float4*)(hp + 4);
     v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
-#pragma unroll 4
-    for (int z = 0; z < splits; ++z) {
-      const float* pp = partial + (size_t)z * split_stride + (size_t)row * d + k;
-      const float4 pa = *(const float4*)pp, pb = *(const float4*)(pp + 4);
-      v[0] += pa.x; v[1] += pa.y; v[2] += pa.z; v[3] += pa.w; v[4] += pb.x; v[5] += pb.y; v[6] += pb.z; v[7] += pb.w;
+    // eight splits' values in flight at a time (the number of splits is a multiple of 8)
+    for (int z0 = 0; z0 < splits; z0 += 8) {
+      float4 pa[8], pb[8];
+#pragma unroll
+      for (int z = 0; z < 8; ++z) {
+        const float* pp = partial + (size_t)(z0 + z) * split_stride + (size_t)row * d + k;
+        pa[z] = *(const float4*)pp;
+        pb[z] = *(const float4*)(pp + 4);
+      }
+#pragma unroll
+      for (int z = 0; z < 8; ++z) {
+        v[0] += pa[z].x; v[1] += pa[z].y; v[2] += pa[z].z; v[3] += pa[z].w;
+        v[4] += pb[z].x; v[5] += pb[z].y; v[6] += pb[z].z; v[7] += pb[z].w;
+      }
     }
     *(float4*)hp = make_float4(v[0], v[1], v[2], v[3]);
     *(float4*)(hp + 4) = make_float4(v[4], v[5], v[6], v[7]);
@@ -1150,7 +1121,7 @@ __global__ void __launch_bounds__(NW * 64) k_decode_attention16(const float* __r
                                                                KVCache kv, uint4* __restrict__ out, ShareArgs sh, Prefetch pf) {
   if ((int)blockIdx.x >= n_main) {   // uniform over the workgroup
     const int first = (n_main + 7) & ~7;
-    if ((int)blockIdx.x >= first) prefetch_role(pf, blockIdx.x - first);
+    if ((int)blockIdx.x >= first) prefetch_role<NW>(pf, blockIdx.x - first, (int)gridDim.x - first);
     return;
   }
   const int n_q_heads = heads_ >> 16;
@@ -1482,9 +1453,8 @@ static hipError_t launch_decode_attention(const float* qkv, const float2* rope, 
     if (e != hipSuccess) return e;
     attr_done = true;
   }
-  static_assert(NW == 8 || NW == 4, "");
-  const int n_main = (SHARE ? sh.n_prefix : 0) + S * kv.n_kv_heads;
-  const int blocks = NW == 8 && pf.blocks > 0 ? ((n_main + 7) & ~7) + pf.blocks : n_main;   // prefetch workgroups have 8 waves
+  const int n_main = (SHARE ? sh.n_prefix : 0) + S * kv.n_kv_heads, n_pf = prefetch_blocks(pf, NW);
+  const int blocks = n_pf > 0 ? ((n_main + 7) & ~7) + n_pf : n_main;
   return launch(SHARE ? KID_DECODE_ATTN_SHARED : KID_DECODE_ATTN, k_decode_attention16<HD, NW, PD, LDS, SHARE>, dim3(blocks),
                 dim3(NW * 64), smem, st, qkv, rope, rm.step, kv.page_table, rm.Lp, kv.pages_per_seq,
                 kv.n_kv_heads | (n_q_heads << 16), n_main, kv.k, rm, kv, (uint4*)out, sh, pf);

@@ -161,13 +161,13 @@ static int big_grid(int NX, int NY) {
 // The k loop of one tile.  begin() requests the first two stages, run() multiplies all of them; a caller that walks several
 // tiles may call begin() for the next one before it is done with the accumulators, after a barrier (the ring is free
 // once every wave has left run()).
-template <int TJ, int H>
+template <int TJ, int H, int NW = 4>
 struct TileLoop {
-  static constexpr int NF = H;                // ring copies per wave and stage (4 H fragments, 4 waves)
-  static constexpr int PER = NF + TJ * H;     // requests per wave and stage
+  static constexpr int NF = 4 * H / NW;       // ring copies per wave and stage (4 H fragments, NW waves)
   static_assert(H == 2 || H == 4, "stage of 32 or 64 k");
+  static_assert(NW == 4 || NW == 8, "a feature block per wave, or half of one");
   u32x4 x[2][H][TJ];
-  const char* wbase;          // this wave's feature fragments: block wave * 4 / 4, or half of one (H = 2: two fragments each)
+  const char* wbase;          // this wave's fragments of the feature operand
   const char* xbase[TJ];
   const char* xrow;           // start of the token operand
   unsigned off, ring;         // lane offset; LDS address of this wave's fragments in the ring's stage 0
@@ -183,75 +183,89 @@ struct TileLoop {
       xbase[t] = (const char*)(Xp + ((size_t)tb * KS + ks0) * 64);
     }
   }
-  // ring fragment f of a stage: feature block f / H, 16-k step f % H; wave w copies fragments w H .. w H + H - 1, the H
-  // steps of feature block w
+  // ring fragment f of a stage: feature block f / H, 16-k step f % H; wave w copies fragments w NF .. w NF + NF - 1, the H
+  // steps of its feature blocks
   __device__ __forceinline__ void features(const uint4* Wp, int KS, int fblk0, int ks0, int n_stages, const uint4* smem) {
     const int wave = wave_index(threadIdx.x);
-    wbase = (const char*)(Wp + ((size_t)(fblk0 + wave) * KS + ks0) * 64);
-    ring = __builtin_amdgcn_readfirstlane(lds_addr(smem)) + (unsigned)(wave * H * 1024);
+    wbase = (const char*)(Wp + ((size_t)(fblk0 + wave * 4 / NW) * KS + ks0 + (NW == 8 ? (wave & 1) * NF : 0)) * 64);
+    ring = __builtin_amdgcn_readfirstlane(lds_addr(smem)) + (unsigned)(wave * NF * 1024);
     off = (threadIdx.x & 63) * 16;
     nst = n_stages;
   }
   template <int I> __device__ __forceinline__ void request_w(int st) {
     dma16(wbase + (size_t)st * (H * 1024) + I * 1024, off, ring + (unsigned)((st % kRing) * (4 * H * 1024) + I * 1024));
   }
+  __device__ __forceinline__ void request_ws(int st) {
+    request_w<0>(st);
+    if constexpr (NF >= 2) request_w<1>(st);
+    if constexpr (NF == 4) { request_w<2>(st); request_w<3>(st); }
+  }
   template <int HH> __device__ __forceinline__ void request_x(int p, int st) {
 #pragma unroll
     for (int t = 0; t < TJ; ++t) reg16<HH * 1024>(x[p][HH][t], xbase[t] + (size_t)st * (H * 1024), off);
   }
-  __device__ __forceinline__ void begin() {
+  // LIVE = false: a wave all of whose tokens lie past the end copies its feature blocks and multiplies nothing
+  template <bool LIVE = true> __device__ __forceinline__ void begin() {
     auto stage = [&](auto pc) {
       constexpr int p = decltype(pc)::value;
-      request_w<0>(p); request_w<1>(p);
-      if constexpr (H == 4) { request_w<2>(p); request_w<3>(p); }
-      request_x<0>(p, p); request_x<1>(p, p);
-      if constexpr (H == 4) { request_x<2>(p, p); request_x<3>(p, p); }
+      request_ws(p);
+      if constexpr (LIVE) {
+        request_x<0>(p, p); request_x<1>(p, p);
+        if constexpr (H == 4) { request_x<2>(p, p); request_x<3>(p, p); }
+      }
     };
     stage(std::integral_constant<int, 0>());
     if (nst > 1) stage(std::integral_constant<int, 1>());
   }
-  template <int P> __device__ __forceinline__ void stage(int st, const uint4* smem, f32x16 (&acc)[4][TJ]) {
+  template <int P, bool LIVE> __device__ __forceinline__ void stage(int st, const uint4* smem, f32x16 (&acc)[4][TJ]) {
+    constexpr int PER = NF + (LIVE ? TJ * H : 0);   // requests per wave and stage
     // this wave's requests of stage st have landed once at most the next stage's are outstanding ...
     if (st + 1 < nst) wait_vmcnt<PER>(); else wait_vmcnt<0>();
+    if constexpr (LIVE) {
 #pragma unroll
-    for (int h = 0; h < H; ++h)
+      for (int h = 0; h < H; ++h)
 #pragma unroll
-      for (int t = 0; t < TJ; ++t) landed(x[P][h][t]);
+        for (int t = 0; t < TJ; ++t) landed(x[P][h][t]);
+    }
     wg_barrier();   // ... and everybody's; stage st - 1 is consumed
     const bool more = st + 2 < nst;
-    const uint4* buf = smem + (st % kRing) * (4 * H * 64) + (threadIdx.x & 63);
-    auto step = [&](auto hc) {
-      constexpr int h = decltype(hc)::value;
-      Frag w[4];
+    if constexpr (!LIVE) {
+      if (more) request_ws(st + 2);
+    } else {
+      const uint4* buf = smem + (st % kRing) * (4 * H * 64) + (threadIdx.x & 63);
+      auto step = [&](auto hc) {
+        constexpr int h = decltype(hc)::value;
+        Frag w[4];
 #pragma unroll
-      for (int f = 0; f < 4; ++f) w[f].u = buf[(f * H + h) * 64];
-      __builtin_amdgcn_s_setprio(1);
-      // The ring copies of stage st + 2 go out one after each of the first MFMAs, a step's registers are requested again
-      // right after their last use; the fences keep the compiler from regrouping them.
-      auto feature = [&](auto fc) {
-        constexpr int f = decltype(fc)::value;
+        for (int f = 0; f < 4; ++f) w[f].u = buf[(f * H + h) * 64];
+        __builtin_amdgcn_s_setprio(1);
+        // The ring copies of stage st + 2 go out one after each of the first MFMAs, a step's registers are requested again
+        // right after their last use; the fences keep the compiler from regrouping them.
+        auto feature = [&](auto fc) {
+          constexpr int f = decltype(fc)::value;
 #pragma unroll
-        for (int t = 0; t < TJ; ++t) {
-          Frag xx; xx.n = x[P][h][t];
-          acc[f][t] = mfma32(w[f], xx, acc[f][t]);
-        }
-        if constexpr (h == 0 && f < NF) {
-          __builtin_amdgcn_sched_barrier(0);
-          if (more) request_w<f>(st + 2);
-          __builtin_amdgcn_sched_barrier(0);
-        }
+          for (int t = 0; t < TJ; ++t) {
+            Frag xx; xx.n = x[P][h][t];
+            acc[f][t] = mfma32(w[f], xx, acc[f][t]);
+          }
+          if constexpr (h * 4 + f < NF) {
+            __builtin_amdgcn_sched_barrier(0);
+            if (more) request_w<h * 4 + f>(st + 2);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+        };
+        feature(std::integral_constant<int, 0>()); feature(std::integral_constant<int, 1>());
+        feature(std::integral_constant<int, 2>()); feature(std::integral_constant<int, 3>());
+        __builtin_amdgcn_s_setprio(0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (more) request_x<h>(P, st + 2);
+        __builtin_amdgcn_sched_barrier(0);
       };
-      feature(std::integral_constant<int, 0>()); feature(std::integral_constant<int, 1>());
-      feature(std::integral_constant<int, 2>()); feature(std::integral_constant<int, 3>());
-      __builtin_amdgcn_s_setprio(0);
-      __builtin_amdgcn_sched_barrier(0);
-      if (more) request_x<h>(P, st + 2);
-      __builtin_amdgcn_sched_barrier(0);
-    };
-    step(std::integral_constant<int, 0>()); step(std::integral_constant<int, 1>());
-    if constexpr (H == 4) { step(std::integral_constant<int, 2>()); step(std::integral_constant<int, 3>()); }
+      step(std::integral_constant<int, 0>()); step(std::integral_constant<int, 1>());
+      if constexpr (H == 4) { step(std::integral_constant<int, 2>()); step(std::integral_constant<int, 3>()); }
+    }
   }
-  __device__ __forceinline__ void run(const uint4* smem, f32x16 (&acc)[4][TJ]) {
+  template <bool LIVE = true> __device__ __forceinline__ void run(const uint4* smem, f32x16 (&acc)[4][TJ]) {
 #pragma unroll
     for (int a = 0; a < 4; ++a)
 #pragma unroll
@@ -260,10 +274,10 @@ struct TileLoop {
         for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
     int st = 0;
     for (; st + 1 < nst; st += 2) {
-      stage<0>(st, smem, acc);
-      stage<1>(st + 1, smem, acc);
+      stage<0, LIVE>(st, smem, acc);
+      stage<1, LIVE>(st + 1, smem, acc);
     }
-    if (st < nst) stage<0>(st, smem, acc);
+    if (st < nst) stage<0, LIVE>(st, smem, acc);
   }
 };
 
@@ -295,11 +309,16 @@ __device__ __forceinline__ void row_scales(const float* __restrict__ ssq, int pa
   }
 }
 
-template <int TJ, int H>
-__global__ void __launch_bounds__(256, TJ == 2 ? 2 : 3) k_gemm_big(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp,
-                                                                  int M, int N, int K, BigEpi ep) {
-  constexpr int TM = 128 * TJ;   // tokens per tile
+template <int TJ, int H, int NW>
+__global__ void __launch_bounds__(NW * 64, TJ == 2 ? 2 : 3) k_gemm_big(const uint4* __restrict__ Xp,
+                                                                      const uint4* __restrict__ Wp, int M, int N, int K,
+                                                                      BigEpi ep) {
+  constexpr int TM = 32 * NW * TJ;   // tokens per tile
   extern __shared__ uint4 smem[];
+  if ((int)blockIdx.x >= ep.main_blocks) {
+    prefetch_role<NW>(ep.pf, blockIdx.x - ep.main_blocks, (int)gridDim.x - ep.main_blocks);
+    return;
+  }
   int bx, by, st0 = 0, n_st = K / (16 * H);
   if (ep.splits > 1) {
     // split-K (one token tile): XCD c runs the splits c, c + 8, ... of every feature tile, so the K range of
@@ -320,9 +339,14 @@ __global__ void __launch_bounds__(256, TJ == 2 ? 2 : 3) k_gemm_big(const uint4* 
 #pragma unroll
   for (int tj = 0; tj < TJ; ++tj) row_scale[tj] = 1.f;
   {
-    TileLoop<TJ, H> loop;
-    loop.tokens(Xp, (M + 31) >> 5, K >> 4, by * (4 * TJ), st0 * H);
+    TileLoop<TJ, H, NW> loop;
+    loop.tokens(Xp, (M + 31) >> 5, K >> 4, by * (NW * TJ), st0 * H);
     loop.features(Wp, K >> 4, bx * 4, st0 * H, n_st, smem);
+    if (ep.decode && by * TM + wave * (32 * TJ) >= M) {   // nothing of this wave is stored
+      loop.template begin<false>();
+      loop.template run<false>(smem, acc);
+      return;
+    }
     loop.begin();
     if (ep.ssq_in) row_scales<TJ>(ep.ssq_in, ep.ssq_parts, ep.norm_dim, ep.eps, tok0, M, row_scale);
     loop.run(smem, acc);
@@ -615,13 +639,18 @@ hipError_t m_gemm_qkv_rope(const void* Xp, const void* Wp, int M, int N, int K, 
 // 70 us, the prompt's small launches 70 -> 58 us.  With one round more - 64 x 768: 4 against 3 - the down projection
 // lost 14 %, so that case keeps the large tile).  SAPO_BIG_TILE=128 / 256 in the environment forces one or the
 // other (measurement).
-static bool big_prefers_small_tiles(int NX, int M) {
+static int n_compute_units() {
   static int n_cu = 0;
   if (n_cu == 0) {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-      n_cu = 256;
+    int dev = 0, n = 0;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+      n = 256;
+    n_cu = n;
   }
+  return n_cu;
+}
+static bool big_prefers_small_tiles(int NX, int M) {
+  const int n_cu = n_compute_units();
   const char* e = getenv("SAPO_BIG_TILE");   // read per call, so that a test can switch it
   const int forced = e ? atoi(e) : 0;
   if (forced == 128) return true;
@@ -632,18 +661,19 @@ static bool big_prefers_small_tiles(int NX, int M) {
   return rounds_small <= rounds_big;
 }
 
-template <int TJ, int H>
-static hipError_t launch_big(const void* Xp, const void* Wp, int M, int N, int K, const BigEpi& epi, int grid, hipStream_t st) {
+template <int TJ, int H, int NW = 4>
+static hipError_t launch_big(const void* Xp, const void* Wp, int M, int N, int K, BigEpi epi, int grid, hipStream_t st) {
   static bool attr_done = false;
   // the residual update's four row areas and gains lie in the ring's memory
   constexpr int lds = ring_bytes(H) > 4 * (32 * 68 + 128) * 4 ? ring_bytes(H) : 4 * (32 * 68 + 128) * 4;
   if (!attr_done) {
-    const hipError_t e = hipFuncSetAttribute((const void*)k_gemm_big<TJ, H>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    const hipError_t e = hipFuncSetAttribute((const void*)k_gemm_big<TJ, H, NW>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
     attr_done = true;
   }
-  return launch(epi.decode ? KID_GEMM_BIG_DECODE : KID_GEMM_BIG, k_gemm_big<TJ, H>, dim3(grid), dim3(256), lds, st,
-                (const uint4*)Xp, (const uint4*)Wp, M, N, K, epi);
+  epi.main_blocks = grid;   // a multiple of 8
+  return launch(epi.decode ? KID_GEMM_BIG_DECODE : KID_GEMM_BIG, k_gemm_big<TJ, H, NW>, dim3(grid + prefetch_blocks(epi.pf, NW)),
+                dim3(NW * 64), lds, st, (const uint4*)Xp, (const uint4*)Wp, M, N, K, epi);
 }
 hipError_t m_gemm_big(const void* Xp, const void* Wp, int M, int N, int K, BigEpi epi, hipStream_t st) {
   if (M == 0) return hipSuccess;
@@ -652,7 +682,17 @@ hipError_t m_gemm_big(const void* Xp, const void* Wp, int M, int N, int K, BigEp
                                             epi.mode != BIG_STORE_F32 || epi.ssq_in || epi.bias)))
     return hipErrorInvalidValue;
   if (epi.gain_next && epi.mode != BIG_ADD_F32) return hipErrorInvalidValue;
-  if (epi.splits > 1) return launch_big<2, 2>(Xp, Wp, M, N, K, epi, epi.splits * (N / 128), st);   // a split is a number of 32-k stages
+  // a split is a number of 32-k stages; 8 waves as below (1.5B, 256 rows: 18.5 -> 17.6 us)
+  if (epi.splits > 1) return launch_big<1, 2, 8>(Xp, Wp, M, N, K, epi, epi.splits * (N / 128), st);
+  if (epi.decode && M <= 256) {
+    // One token tile or two, weights that come from HBM, at most one workgroup per compute unit: what counts is how much
+    // of the chip asks and how many waves hide a stage's barrier and LDS latency.  128-token tiles when they are no
+    // more than the compute units (0.5B gate/up, 192 rows: 76 workgroups become 152, 16.3 -> 12.9 us); 8 waves of 32
+    // tokens on a 256-token tile otherwise (1.5B at 256 rows: 140 workgroups, 26 -> 23 us with two waves per SIMD).
+    if (N / 128 * ((M + 127) / 128) <= n_compute_units())
+      return launch_big<1, 4>(Xp, Wp, M, N, K, epi, big_grid(N / 128, (M + 127) / 128), st);
+    return launch_big<1, 4, 8>(Xp, Wp, M, N, K, epi, big_grid(N / 128, 1), st);
+  }
   if (big_prefers_small_tiles(N / 128, M)) return launch_big<1, 4>(Xp, Wp, M, N, K, epi, big_grid(N / 128, (M + 127) / 128), st);
   return launch_big<2, 4>(Xp, Wp, M, N, K, epi, big_grid(N / 128, (M + 255) / 256), st);
 }
@@ -838,6 +878,11 @@ __global__ void __launch_bounds__(256, 2) k_lmhead_sample_big(const uint4* __res
     TileLoop<TJ, H> loop;
     loop.tokens(Xp, (n_rows + 31) >> 5, K >> 4, by * 8, 0);
     loop.features(Wp, K >> 4, ft * 4, 0, K / (16 * H), smem);
+    if (by * 256 + wave * 64 >= n_rows) {   // no row of this wave exists
+      loop.begin<false>();
+      loop.run<false>(smem, acc);
+      return;
+    }
     loop.begin();
     loop.run(smem, acc);
   }
