@@ -12,6 +12,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <type_traits>
 #include <vector>
 
 #include "surrogate.h"
@@ -352,126 +353,373 @@ __global__ void __launch_bounds__(256) k_pack_x3_t(const float* __restrict__ src
   }
 }
 
-// RB = row blocks of 128 per tile: 1 (128 x 128, three workgroups per CU) or 2 (256 x 128 for outputs with many
-// tiles: each wave 128 x 64, two workgroups per CU, a quarter less traffic per flop on both the L2 and the LDS side)
-template <int NP, int RB>
-__global__ void __launch_bounds__(256, RB == 2 ? 2 : 3) k_gemm_x3(const u32x4_t* __restrict__ Ap, const u32x4_t* __restrict__ Bp,
+// k steps of 16 per stage of the packed GEMM: what keeps a stage at 32 .. 48 MFMAs per wave
+__host__ __device__ constexpr int x3_stage(int NP) { return NP == 3 ? 1 : NP == 2 ? 2 : 4; }
+
+__host__ __device__ constexpr int x3_tn_stage(int NP) { return NP == 1 ? 2 : 1; }   // of k_gemm_x3_tn
+
+// The A operand's products go out smallest first: (hi lo), (lo hi), (mid mid), (hi mid), (mid hi), (hi hi); two pieces take
+// the last three, one piece the last.
+template <int NP> __device__ __forceinline__ constexpr int x3_terms() { return NP == 3 ? 6 : NP == 2 ? 3 : 1; }
+__device__ constexpr int kTermA[6] = {0, 2, 1, 0, 1, 0}, kTermB[6] = {2, 0, 1, 1, 0, 0};
+
+// One wave-wide 1 KiB copy global -> LDS / load into registers (base + lane offset), awaited with x3_wait; issued from inline
+// assembly because the compiler would wait for a copy before any LDS read.
+__device__ __forceinline__ void x3_dma(const char* base, unsigned off, unsigned lds) {
+  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory");
+}
+template <int IMM> __device__ __forceinline__ void x3_reg(u32x4_t& d, const char* base, unsigned off) {
+  asm volatile("global_load_dwordx4 %0, %1, %2 offset:%3" : "=v"(d) : "v"(off), "s"(base), "n"(IMM) : "memory");
+}
+template <int N> __device__ __forceinline__ void x3_wait() {
+  __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
+}
+
+// C tile of a wave: TJ x 4 MFMA tiles; accumulator v of lane l: row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32.  A tile
+// without rows or columns past the end is stored without a comparison per value, rows by scalar base addresses.
+template <int TJ>
+__device__ __forceinline__ void x3_store_tile(const f32x16_t (&acc)[TJ][4], float* __restrict__ C, int ldc, int row0, int n0, int M,
+                                              int N, float beta) {
+  const int lane = threadIdx.x & 63;
+  auto store = [&](auto full_c, auto beta_c) __attribute__((always_inline)) {
+    constexpr bool full = decltype(full_c)::value, add = decltype(beta_c)::value;
+    const unsigned off = (unsigned)((lane >> 5) * 4 * ldc + n0 + (lane & 31)) * 4u;   // bytes behind the base of a row pair
+    const int m_lane = (lane >> 5) * 4, n = n0 + (lane & 31);
+#pragma unroll
+    for (int t = 0; t < TJ; ++t)
+#pragma unroll
+      for (int v4 = 0; v4 < 4; ++v4) {
+        char* base[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) base[u] = (char*)(C + (size_t)(row0 + t * 32 + 8 * v4 + u) * ldc);
+        float old[4][4];
+        if constexpr (add) {
+#pragma unroll
+          for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+              old[u][j] = 0.f;
+              if (full || (row0 + t * 32 + 8 * v4 + u + m_lane < M && n + j * 32 < N)) old[u][j] = *(const float*)(base[u] + off + j * 128);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const float r = add ? fmaf(beta, old[u][j], acc[t][j][4 * v4 + u]) : acc[t][j][4 * v4 + u];
+            if (full || (row0 + t * 32 + 8 * v4 + u + m_lane < M && n + j * 32 < N)) *(float*)(base[u] + off + j * 128) = r;
+          }
+      }
+  };
+  const bool full = row0 + 32 * TJ <= M && n0 + 128 <= N;
+  if (beta != 0.f) {
+    if (full) store(std::true_type(), std::true_type()); else store(std::false_type(), std::true_type());
+  } else {
+    if (full) store(std::true_type(), std::false_type()); else store(std::false_type(), std::false_type());
+  }
+}
+
+// C[M, N] = beta C + A B^T of two packed operands.  128 TJ x 128 tile, 4 waves of 32 TJ rows x all 128 columns.  The A
+// pieces go from global memory straight into the registers of the one wave that uses them, two stages ahead; the B
+// pieces, which all four waves read, through a three-stage LDS ring filled by direct-to-LDS copies.  With both operands
+// staged through LDS by way of registers (what this replaces: waves of 64 x 64 or 128 x 64) the LDS moved 0.56 - 0.75 KB
+// per MFMA, and a step's copies, which the compiler waits for in front of the LDS stores, sat at its end; now 0.31 KB.
+// TJ = 2: two workgroups per compute unit; TJ = 1: three.
+template <int NP, int TJ>
+__global__ void __launch_bounds__(256, TJ == 2 ? 2 : 3) k_gemm_x3(const u32x4_t* __restrict__ Ap, const u32x4_t* __restrict__ Bp,
                                                                   float* __restrict__ C, int ldc, int M, int N, int KB, float beta,
                                                                   int kb_split, size_t c_split) {
-  constexpr int E = NP * 256;                 // 16-byte entries per row block, operand and k step
-  constexpr int MI = 2 * RB;                  // 32-row MFMA tiles per wave
-  __shared__ u32x4_t As[2][RB * E];
-  __shared__ u32x4_t Bs[2][E];
+  constexpr int H = x3_stage(NP), NF = H * NP;     // ring copies per wave and stage; fragments of a column block
+  constexpr int PER = NF + NF * TJ;                // requests per wave and stage
+  constexpr int kRing = 3;
+  __shared__ u32x4_t ring[kRing * NF * 4 * 64];
   const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63;
   int tx, ty;
-  const int n_rb = (M + kGM - 1) / kGM;       // row blocks of the packed operand
-  if (!raster_tile((N + kGM - 1) / kGM, (n_rb + RB - 1) / RB, tx, ty)) return;
-  const int m0 = ty * kGM * RB, n0 = tx * kGM;
-  const int wm = (wave >> 1) * 64 * RB, wn = (wave & 1) * 64;
-  const u32x4_t* ap[RB];
-#pragma unroll
-  for (int r = 0; r < RB; ++r)   // a tile's last row block may not exist: it repeats the previous one and is not stored
-    ap[r] = Ap + (size_t)min(ty * RB + r, n_rb - 1) * KB * E + threadIdx.x;
-  const u32x4_t* bp = Bp + (size_t)tx * KB * E + threadIdx.x;
-  f32x16_t acc[MI][2];
-#pragma unroll
-  for (int i = 0; i < MI; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+  const int n_rb = (M + kGM - 1) / kGM;            // row blocks of the packed operand
+  if (!raster_tile((N + kGM - 1) / kGM, (n_rb + TJ - 1) / TJ, tx, ty)) return;
   // blockIdx.z takes the k steps [z kb_split, (z + 1) kb_split) and writes its own copy of C (split weight gradients)
-  const int t0 = blockIdx.z * kb_split, t1 = min(KB, t0 + kb_split);
+  const int t0 = blockIdx.z * kb_split, nst = (min(KB, t0 + kb_split) - t0) / H;
   C += (size_t)blockIdx.z * c_split;
-  u32x4_t ra[RB][NP], rb[NP];
+  const int row_w = wave * 32 * TJ;                // this wave's rows of the tile
+  // a tile's last row block may not exist: it repeats the previous one and is not stored
+  const char* xbase = (const char*)(Ap + ((size_t)min(ty * TJ + (row_w >> 7), n_rb - 1) * KB + t0) * (NP * 256) + (row_w & 127));
+  const char* wbase = (const char*)(Bp + ((size_t)tx * KB + t0) * (NP * 256) + wave * 32);
+  const unsigned off = ((lane >> 5) * 128 + (lane & 31)) * 16;
+  const unsigned lds0 =
+      __builtin_amdgcn_readfirstlane((unsigned)(size_t)(const __attribute__((address_space(3))) void*)ring) + wave * 1024u;
+  u32x4_t x[2][NF][TJ];
+  f32x16_t acc[TJ][4];
 #pragma unroll
-  for (int pc = 0; pc < NP; ++pc) {
+  for (int t = 0; t < TJ; ++t)
 #pragma unroll
-    for (int r = 0; r < RB; ++r) ra[r][pc] = ap[r][(size_t)t0 * E + pc * 256];
-    rb[pc] = bp[(size_t)t0 * E + pc * 256];
-  }
+    for (int j = 0; j < 4; ++j)
 #pragma unroll
-  for (int pc = 0; pc < NP; ++pc) {
+      for (int v = 0; v < 16; ++v) acc[t][j][v] = 0.f;
+  // fragment i = (k step of the stage) * NP + piece: a 4 KiB step of the packed operand
+  auto request_w = [&](int i, int st) { x3_dma(wbase + ((size_t)st * NF + i) * 4096, off, lds0 + ((st % kRing) * NF + i) * 4096u); };
+  auto request_x = [&](u32x4_t (&dst)[TJ], int i, int st) {
+    const char* b = xbase + ((size_t)st * NF + i) * 4096;
+    x3_reg<0>(dst[0], b, off);
+    if constexpr (TJ == 2) x3_reg<512>(dst[TJ - 1], b, off);
+  };
 #pragma unroll
-    for (int r = 0; r < RB; ++r) As[0][r * E + pc * 256 + threadIdx.x] = ra[r][pc];
-    Bs[0][pc * 256 + threadIdx.x] = rb[pc];
-  }
-  __syncthreads();
-  const int kh = lane >> 5, c = lane & 31;
-  for (int t = t0; t < t1; ++t) {
-    const int cur = (t - t0) & 1;
-    if (t + 1 < t1) {
+  for (int p = 0; p < 2; ++p)
+    if (p < nst) {
 #pragma unroll
-      for (int pc = 0; pc < NP; ++pc) {
+      for (int i = 0; i < NF; ++i) request_w(i, p);
 #pragma unroll
-        for (int r = 0; r < RB; ++r) ra[r][pc] = ap[r][(size_t)(t + 1) * E + pc * 256];
-        rb[pc] = bp[(size_t)(t + 1) * E + pc * 256];
+      for (int i = 0; i < NF; ++i) request_x(x[p][i], i, p);
+    }
+  auto stage = [&](auto pc, int st) {
+    constexpr int P = decltype(pc)::value;
+    if (st + 1 < nst) x3_wait<PER>(); else x3_wait<0>();   // this wave's requests of stage st have landed ...
+#pragma unroll
+    for (int i = 0; i < NF; ++i)
+#pragma unroll
+      for (int t = 0; t < TJ; ++t) asm volatile("" : "+v"(x[P][i][t]));
+    asm volatile("s_barrier" ::: "memory");                // ... and everybody's; stage st - 1 is consumed
+    const bool more = st + 2 < nst;
+    const u32x4_t* buf = ring + (st % kRing) * (NF * 4 * 64) + lane;
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+      Frag8 b[4][NP];
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int q = 0; q < NP; ++q) b[j][q].u = buf[((h * NP + q) * 4 + j) * 64];
+      __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+#pragma unroll
+        for (int term = 6 - x3_terms<NP>(); term < 6; ++term)
+#pragma unroll
+          for (int t = 0; t < TJ; ++t) {
+            Frag8 a; a.u = x[P][h * NP + kTermA[term]][t];
+            acc[t][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.v, b[j][kTermB[term]].v, acc[t][j], 0, 0, 0);
+          }
+        if (h * 4 + j < NF) {   // the next-but-one stage's copies go out between the MFMAs, not in one burst
+          __builtin_amdgcn_sched_barrier(0);
+          if (more) request_w(h * 4 + j, st + 2);
+          __builtin_amdgcn_sched_barrier(0);
+        }
       }
-    }
-    Frag8 b[2][NP];
+      __builtin_amdgcn_s_setprio(0);
+      __builtin_amdgcn_sched_barrier(0);
+      if (more) {
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int pc = 0; pc < NP; ++pc) b[j][pc].u = Bs[cur][(pc * 2 + kh) * 128 + wn + j * 32 + c];
-    // smallest partial products first: (hi lo), (lo hi), (mid mid), (hi mid), (mid hi), (hi hi); two pieces take the
-    // last three, one piece the last
-    constexpr int n_terms = NP == 3 ? 6 : NP == 2 ? 3 : 1;
-    constexpr int pa[6] = {0, 2, 1, 0, 1, 0}, pb[6] = {2, 0, 1, 1, 0, 0};
-#pragma unroll
-    for (int i = 0; i < MI; ++i) {
-      Frag8 a[NP];
-      const int row = wm + i * 32 + c;        // within the tile: row block row >> 7
-#pragma unroll
-      for (int pc = 0; pc < NP; ++pc) a[pc].u = As[cur][(row >> 7) * E + (pc * 2 + kh) * 128 + (row & 127)];
-#pragma unroll
-      for (int term = 6 - n_terms; term < 6; ++term)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[pa[term]].v, b[j][pb[term]].v, acc[i][j], 0, 0, 0);
-    }
-    if (t + 1 < t1) {
-#pragma unroll
-      for (int pc = 0; pc < NP; ++pc) {
-#pragma unroll
-        for (int r = 0; r < RB; ++r) As[cur ^ 1][r * E + pc * 256 + threadIdx.x] = ra[r][pc];
-        Bs[cur ^ 1][pc * 256 + threadIdx.x] = rb[pc];
+        for (int q = 0; q < NP; ++q) request_x(x[P][h * NP + q], h * NP + q, st + 2);
       }
+      __builtin_amdgcn_sched_barrier(0);
     }
+  };
+  int st = 0;
+  for (; st + 1 < nst; st += 2) {
+    stage(std::integral_constant<int, 0>(), st);
+    stage(std::integral_constant<int, 1>(), st + 1);
+  }
+  if (st < nst) stage(std::integral_constant<int, 0>(), st);
+  x3_store_tile<TJ>(acc, C, ldc, ty * kGM * TJ + row_w, tx * kGM, M, N, beta);
+}
+
+// f(0), f(1), ... f(N - 1) with the index as a compile-time constant
+template <typename F, int... I> __device__ __forceinline__ void each_of(F&& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>()), ...);
+}
+template <int N, typename F> __device__ __forceinline__ void each(F&& f) { each_of(f, std::make_integer_sequence<int, N>()); }
+
+// bf16 pieces of 8 values as MFMA fragments (the cut of x3_store)
+template <int NP> __device__ __forceinline__ void x3_cut(const float (&x)[8], Frag8 (&f)[NP]) {
+  if constexpr (NP == 3) {
+    float r[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) r[e] = x[e];
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        f[q].u[w] = __builtin_amdgcn_perm(__float_as_uint(r[2 * w + 1]), __float_as_uint(r[2 * w]), 0x07060302u);   // the high halves
+        r[2 * w] -= __uint_as_float(__float_as_uint(r[2 * w]) & 0xFFFF0000u);
+        r[2 * w + 1] -= __uint_as_float(__float_as_uint(r[2 * w + 1]) & 0xFFFF0000u);
+      }
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const __bf16 hi = (__bf16)x[e];   // round to nearest even
+      f[0].v[e] = hi;
+      if constexpr (NP == 2) f[1].v[e] = (__bf16)(x[e] - (float)hi);
+    }
+  }
+}
+
+// C[M, N] = beta C + A^T B with A [K, M] (lda) and B [K, N] (ldb) in fp32 as they lie (weight gradients: K counts tokens):
+// the operands are cut into pieces on the way in.  Packing them first cost a read of 4 and a write and read of 2 NP bytes
+// per value.  Same tile as k_gemm_x3; a wave reads the A values of its rows straight into registers (8 tokens of one row
+// per lane: 128-byte runs), cuts them itself, and cuts a quarter of the B values for everybody, which go through two LDS
+// buffers.  A stage's cuts are spread between the MFMAs of the stage before (the vector ALU works while the matrix core
+// does), and a fragment's registers are requested again as soon as it is cut, a whole stage ahead.
+template <int NP, int TJ>
+__global__ void __launch_bounds__(256, TJ == 2 ? 2 : 3) k_gemm_x3_tn(const float* __restrict__ A, int lda, const float* __restrict__ B,
+                                                                     int ldb, float* __restrict__ C, int ldc, int M, int N, int K,
+                                                                     float beta, int k_split, size_t c_split) {
+  constexpr int H = x3_tn_stage(NP), kTasks = H * (TJ + 1), KS = 16 * H;
+  __shared__ u32x4_t Bs[2][H * NP * 4 * 64];
+  const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63, kh = lane >> 5, c = lane & 31;
+  int tx, ty;
+  if (!raster_tile((N + kGM - 1) / kGM, (M + kGM * TJ - 1) / (kGM * TJ), tx, ty)) return;
+  const int k_begin = blockIdx.z * k_split, k_end = min(K, k_begin + k_split);
+  // the first stage is the one that may be partial: tokens in front of it count as zero
+  const int nst = (k_end - k_begin + KS - 1) / KS, k_first = k_end - nst * KS;
+  C += (size_t)blockIdx.z * c_split;
+  const int row0 = ty * kGM * TJ + wave * 32 * TJ;
+  // rows and columns past the end repeat the last one and are not stored
+  unsigned arow[TJ];
+#pragma unroll
+  for (int t = 0; t < TJ; ++t) arow[t] = min(row0 + t * 32 + c, M - 1);
+  const unsigned bcol = min(tx * kGM + wave * 32 + c, N - 1);
+  unsigned aoff[TJ];   // byte offsets of the lane behind a token row's base
+#pragma unroll
+  for (int t = 0; t < TJ; ++t) aoff[t] = (unsigned)(kh * 8 * lda + arow[t]) * 4u;
+  const unsigned boff = (unsigned)(kh * 8 * ldb + bcol) * 4u;
+  // Task i of a stage: fragment i % (TJ + 1) of k step i / (TJ + 1); the last fragment is the wave's part of B.
+  float raw[kTasks][8];
+  auto request = [&](auto ic, int s) __attribute__((always_inline)) {
+    constexpr int i = decltype(ic)::value, h = i / (TJ + 1), t = i % (TJ + 1);
+    const size_t k = k_first + min(s, nst - 1) * KS + h * 16;   // past the end: the last stage again, not used
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      if constexpr (t < TJ) raw[i][e] = *(const float*)((const char*)(A + (k + e) * lda) + aoff[t]);
+      else raw[i][e] = *(const float*)((const char*)(B + (k + e) * ldb) + boff);
+    }
+  };
+  Frag8 a[2][H][TJ][NP];
+  auto cut = [&](auto ic, auto pc) __attribute__((always_inline)) {
+    constexpr int i = decltype(ic)::value, h = i / (TJ + 1), t = i % (TJ + 1), p = decltype(pc)::value;
+    if constexpr (t < TJ) {
+      x3_cut<NP>(raw[i], a[p][h][t]);
+    } else {
+      Frag8 b[NP];
+      x3_cut<NP>(raw[i], b);
+#pragma unroll
+      for (int q = 0; q < NP; ++q) Bs[p][((h * NP + q) * 4 + wave) * 64 + lane] = b[q].u;
+    }
+  };
+  f32x16_t acc[TJ][4];
+#pragma unroll
+  for (int t = 0; t < TJ; ++t)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[t][j][v] = 0.f;
+  auto stage = [&](auto pc, int s) __attribute__((always_inline)) {
+    constexpr int P = decltype(pc)::value;
+    const u32x4_t* buf = Bs[P] + lane;
+    each<H * 4>([&](auto slot_c) __attribute__((always_inline)) {
+      constexpr int slot = decltype(slot_c)::value, h = slot >> 2, j = slot & 3;
+      Frag8 b[NP];
+#pragma unroll
+      for (int q = 0; q < NP; ++q) b[q].u = buf[((h * NP + q) * 4 + j) * 64];
+#pragma unroll
+      for (int term = 6 - x3_terms<NP>(); term < 6; ++term)
+#pragma unroll
+        for (int t = 0; t < TJ; ++t)
+          acc[t][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[P][h][t][kTermA[term]].v, b[kTermB[term]].v, acc[t][j], 0, 0, 0);
+      if constexpr (slot < kTasks) {
+        cut(slot_c, std::integral_constant<int, P ^ 1>());
+        request(slot_c, s + 2);
+        // one MFMA, then a few of the cut's instructions
+#pragma unroll
+        for (int m = 0; m < x3_terms<NP>() * TJ; ++m) {
+          __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x2, NP == 3 ? 48 / (6 * TJ) : 24 / (x3_terms<NP>() * TJ), 0);
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    });
     __syncthreads();
-  }
+  };
+  const std::integral_constant<int, 0> even;
+  const std::integral_constant<int, 1> odd;
+  each<kTasks>([&](auto ic) __attribute__((always_inline)) {
+    constexpr int i = decltype(ic)::value, h = i / (TJ + 1), t = i % (TJ + 1);
 #pragma unroll
-  for (int i = 0; i < MI; ++i)
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int n = n0 + wn + j * 32 + (lane & 31);
-      if (n >= N) continue;
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int m = m0 + wm + i * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-        if (m >= M) continue;
-        float* cp = C + (size_t)m * ldc + n;
-        *cp = (beta != 0.f) ? fmaf(beta, *cp, acc[i][j][v]) : acc[i][j][v];
-      }
+    for (int e = 0; e < 8; ++e) {
+      const int k = k_first + h * 16 + kh * 8 + e;
+      const size_t kc = max(k, k_begin);
+      float v;
+      if constexpr (t < TJ) v = A[kc * lda + arow[t]];
+      else v = B[kc * ldb + bcol];
+      raw[i][e] = k >= k_begin ? v : 0.f;
     }
+  });
+  each<kTasks>([&](auto i) __attribute__((always_inline)) {
+    cut(i, even);
+    request(i, 1);
+  });
+  __syncthreads();
+  int s = 0;
+  for (; s + 1 < nst; s += 2) {
+    stage(even, s);
+    stage(odd, s + 1);
+  }
+  if (s < nst) stage(even, s);
+  x3_store_tile<TJ>(acc, C, ldc, row0, tx * kGM, M, N, beta);
 }
 
 // One operand of a packed GEMM: `rows` x K values at src[row * ld + k], or src[k * ld + row] when `trans`.
 struct X3Op { const float* src; int ld, rows, K; bool trans; };
 inline size_t x3_pack_bytes(int NP, size_t rows, size_t K) {
-  return ((rows + 127) / 128 * 128) * ((K + 15) / 16 * 16) * 2 * NP;
+  return ((rows + 127) / 128 * 128) * ((K + 63) / 64 * 64) * 2 * NP;
 }
+inline int x3_steps(int K, int NP) { const int k = 16 * x3_stage(NP); return (K + k - 1) / k * x3_stage(NP); }   // padded k steps
 struct X3Bufs { void* a; void* b; size_t a_cap, b_cap; int NP; float* parts; size_t parts_cap; };
 constexpr int kMaxSplits = 16;
 __global__ void k_sum_parts(const float* __restrict__ part, int n_part, size_t n, float beta, float* __restrict__ out);
 
 hipError_t x3_pack(const X3Op& op, void* dst, size_t cap, int NP, hipStream_t st) {
   if (x3_pack_bytes(NP, op.rows, op.K) > cap) return hipErrorInvalidValue;
-  const int rows_pad = (op.rows + 127) / 128 * 128, KB = (op.K + 15) / 16;
+  const int rows_pad = (op.rows + 127) / 128 * 128, KB = x3_steps(op.K, NP);
   if (!op.trans)
     return launch(KID_MISC, k_pack_x3, dim3(rows_pad / 128, (KB + 7) / 8), dim3(256), 0, st, op.src, op.ld, op.rows, op.K, rows_pad,
                   KB, NP, (uint4*)dst);
   return launch(KID_MISC, k_pack_x3_t, dim3(rows_pad / 64, (KB * 16 + 63) / 64), dim3(256), 0, st, op.src, op.ld, op.rows, op.K,
                 rows_pad, KB, NP, (uint4*)dst);
+}
+// Tile, grid and split of a product with `rows` x `cols` outputs and KB k steps in stages of `stage`.
+struct X3Grid { int TJ, splits, per_split; dim3 grid; };
+// A product whose output tiles fill the workgroups in flight badly (weight gradients: 49 .. 532 tiles; outputs d wide:
+// 672 tiles on 512 slots are 1.3 rounds run as 2) is split along the contraction when parts_cap allows it: each part writes
+// its own product and k_sum_parts adds them in part order.  Tile height and number of parts are those with the least
+// estimated time: rounds of resident workgroups (two per compute unit at 256 rows, three at 128) of so many steps, a
+// tile's first requests and output, and the pass that adds the parts.
+X3Grid x3_grid(int NP, int rows, int cols, int KB, int stage, size_t parts_cap) {
+  const int gnx = (cols + kGM - 1) / kGM, gny = (rows + kGM - 1) / kGM;
+  const double terms = NP == 3 ? 6.0 : NP == 2 ? 3.0 : 1.0;
+  X3Grid best{};
+  double best_us = 0.0;
+  for (int TJ = 2; TJ >= 1; --TJ) {
+    const int gty = (gny + TJ - 1) / TJ;
+    const long tiles = (long)gnx * gty, slots = TJ == 2 ? 512 : 768;
+    // one 16-k step of a full round (measured: 1.6 PFLOP/s with three pieces, 0.9 with one; 10 % more for the small tile)
+    const double step_us = (TJ == 2 ? 1.0 : 0.825) * 0.336 * terms * (NP == 1 ? 1.8 : NP == 2 ? 1.2 : 1.0);
+    for (int s = 1; s <= kMaxSplits; ++s) {
+      if (s > 1 && (KB / s < 16 || (size_t)s * rows * cols > parts_cap)) break;
+      const int per = ((KB + s - 1) / s + stage - 1) / stage * stage;
+      if ((KB + per - 1) / per != s) continue;
+      const long rounds = (tiles * s + slots - 1) / slots;
+      const double sum_us = s > 1 ? 4.0 + (s + 2) * 4e-6 * rows * cols : 0.0;   // at 1 MB per us
+      const double us = rounds * (per * step_us + (TJ == 2 ? 14.0 : 10.5)) + sum_us / 4.0;
+      if (best_us == 0.0 || us < best_us * 0.98) {
+        best_us = us;
+        best.TJ = TJ; best.splits = s; best.per_split = per;
+        best.grid = dim3(raster_grid(gnx, gty), 1, s);
+      }
+    }
+  }
+  return best;
+}
+hipError_t x3_sum_parts(const X3Bufs& bufs, int splits, size_t n, float beta, float* C, hipStream_t st) {
+  return launch(KID_MISC, k_sum_parts, dim3((unsigned)((n + 1023) / 1024)), dim3(256), 0, st, (const float*)bufs.parts, splits, n, beta,
+                C);
 }
 // C[M, N] = beta C + op(A) op(B)^T-style product of two operands given row-wise over the same K
 hipError_t gemm_x3(const X3Op& A, const X3Op& B, float* C, int ldc, float beta, const X3Bufs& bufs, hipStream_t st,
@@ -483,44 +731,38 @@ hipError_t gemm_x3(const X3Op& A, const X3Op& B, float* C, int ldc, float beta, 
   if (!b_packed && (e = x3_pack(B, bufs.b, bufs.b_cap, bufs.NP, st)) != hipSuccess) return e;
   const u32x4_t* pa_ = (const u32x4_t*)(a_packed ? a_packed : bufs.a);
   const u32x4_t* pb_ = (const u32x4_t*)(b_packed ? b_packed : bufs.b);
-  const int KB = (A.K + 15) / 16;
-  const int gnx = (B.rows + kGM - 1) / kGM, gny = (A.rows + kGM - 1) / kGM;
-  // 256-row tiles when the output still has plenty of them
-  const int RB = (gnx >= 32 && (long)gnx * ((gny + 1) / 2) >= 512) ? 2 : 1;
-  const int gty = (gny + RB - 1) / RB;
-  dim3 grid(raster_grid(gnx, gty), 1);
-  // A long contraction whose output tiles do not fill the workgroups in flight (weight gradients: 49 .. 532 tiles
-  // against 768 resident workgroups, or a last round that is mostly empty): the k steps are split into parts, each
-  // part writes its own product and k_sum_parts adds them in part order.  The number of parts is the one whose
-  // rounds of resident workgroups are fullest; more parts must buy at least 4 % (they cost a pass over the output).
-  const long tiles = (long)gnx * gty;
-  int splits = 1;
-  if (split_ok && ldc == B.rows) {
-    const long slots = RB == 2 ? 512 : 768;
-    double best = 0.0;
-    for (int s_ = 1; s_ <= kMaxSplits; ++s_) {
-      if (s_ > 1 && (KB / s_ < 16 || (size_t)s_ * A.rows * B.rows > bufs.parts_cap)) break;
-      const long units = tiles * s_;
-      const double fill = (double)units / (double)((units + slots - 1) / slots * slots);
-      if (fill > best + 0.04) { best = fill; splits = s_; }
-    }
-  }
-  const int kbs = (KB + splits - 1) / splits;
-  splits = (KB + kbs - 1) / kbs;
-  grid.z = splits;
-  float* out = splits > 1 ? bufs.parts : C;
-  const size_t c_split = splits > 1 ? (size_t)A.rows * B.rows : 0;
-  const float b_ = splits > 1 ? 0.f : beta;
+  const int KB = x3_steps(A.K, bufs.NP);
+  const X3Grid g = x3_grid(bufs.NP, A.rows, B.rows, KB, x3_stage(bufs.NP), split_ok && ldc == B.rows ? bufs.parts_cap : 0);
+  float* out = g.splits > 1 ? bufs.parts : C;
+  const size_t c_split = g.splits > 1 ? (size_t)A.rows * B.rows : 0;
+  const float b_ = g.splits > 1 ? 0.f : beta;
   auto go = [&](auto kernel) {
-    return launch(KID_GEMM_GENERIC, kernel, grid, dim3(256), 0, st, pa_, pb_, out, ldc, A.rows, B.rows, KB, b_, kbs, c_split);
+    return launch(KID_GEMM_GENERIC, kernel, g.grid, dim3(256), 0, st, pa_, pb_, out, ldc, A.rows, B.rows, KB, b_, g.per_split, c_split);
   };
-  if (bufs.NP == 3) e = RB == 2 ? go(k_gemm_x3<3, 2>) : go(k_gemm_x3<3, 1>);
-  else if (bufs.NP == 2) e = RB == 2 ? go(k_gemm_x3<2, 2>) : go(k_gemm_x3<2, 1>);
-  else e = RB == 2 ? go(k_gemm_x3<1, 2>) : go(k_gemm_x3<1, 1>);
-  if (e != hipSuccess || splits == 1) return e;
-  const size_t n = (size_t)A.rows * B.rows;
-  return launch(KID_MISC, k_sum_parts, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, (const float*)bufs.parts, splits, n, beta,
-                C);
+  if (bufs.NP == 3) e = g.TJ == 2 ? go(k_gemm_x3<3, 2>) : go(k_gemm_x3<3, 1>);
+  else if (bufs.NP == 2) e = g.TJ == 2 ? go(k_gemm_x3<2, 2>) : go(k_gemm_x3<2, 1>);
+  else e = g.TJ == 2 ? go(k_gemm_x3<1, 2>) : go(k_gemm_x3<1, 1>);
+  if (e != hipSuccess || g.splits == 1) return e;
+  return x3_sum_parts(bufs, g.splits, (size_t)A.rows * B.rows, beta, C, st);
+}
+// C[M, N] = beta C + A^T B, A [K, M] and B [K, N] in fp32
+hipError_t gemm_x3_tn(const float* A, int lda, const float* B, int ldb, float* C, int M, int N, int K, float beta,
+                      const X3Bufs& bufs, hipStream_t st) {
+  if (M <= 0 || N <= 0 || K <= 0) return hipErrorInvalidValue;
+  const int KB = (K + 15) / 16;
+  const X3Grid g = x3_grid(bufs.NP, M, N, KB, x3_tn_stage(bufs.NP), bufs.parts_cap);
+  float* out = g.splits > 1 ? bufs.parts : C;
+  const size_t c_split = g.splits > 1 ? (size_t)M * N : 0;
+  const float b_ = g.splits > 1 ? 0.f : beta;
+  auto go = [&](auto kernel) {
+    return launch(KID_GEMM_GENERIC, kernel, g.grid, dim3(256), 0, st, A, lda, B, ldb, out, N, M, N, K, b_, g.per_split * 16, c_split);
+  };
+  hipError_t e;
+  if (bufs.NP == 3) e = g.TJ == 2 ? go(k_gemm_x3_tn<3, 2>) : go(k_gemm_x3_tn<3, 1>);
+  else if (bufs.NP == 2) e = g.TJ == 2 ? go(k_gemm_x3_tn<2, 2>) : go(k_gemm_x3_tn<2, 1>);
+  else e = g.TJ == 2 ? go(k_gemm_x3_tn<1, 2>) : go(k_gemm_x3_tn<1, 1>);
+  if (e != hipSuccess || g.splits == 1) return e;
+  return x3_sum_parts(bufs, g.splits, (size_t)M * N, beta, C, st);
 }
 
 template <int TA, int TB>
@@ -709,11 +951,27 @@ __global__ void __launch_bounds__(256) k_move_rows(const float* __restrict__ src
 }
 // out = (beta ? out : 0) + sum over the parts, in part order
 __global__ void k_sum_parts(const float* __restrict__ part, int n_part, size_t n, float beta, float* __restrict__ out) {
-  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+  const size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4;
   if (i >= n) return;
-  float s = beta != 0.f ? beta * out[i] : 0.f;
-  for (int p = 0; p < n_part; ++p) s += part[(size_t)p * n + i];
-  out[i] = s;
+  if (n % 4 != 0 || ((uintptr_t)out & 15) != 0) {
+    for (size_t k = i; k < min(i + 4, n); ++k) {
+      float s = beta != 0.f ? beta * out[k] : 0.f;
+      for (int p = 0; p < n_part; ++p) s += part[(size_t)p * n + k];
+      out[k] = s;
+    }
+    return;
+  }
+  float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (beta != 0.f) {
+    s = *(const float4*)(out + i);
+    s.x *= beta; s.y *= beta; s.z *= beta; s.w *= beta;
+  }
+#pragma unroll 4
+  for (int p = 0; p < n_part; ++p) {
+    const float4 v = *(const float4*)(part + (size_t)p * n + i);
+    s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+  }
+  *(float4*)(out + i) = s;
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1464,14 +1722,14 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
   const X3Bufs xb{p.packa, p.packb, p.packa_cap, p.packb_cap, pieces, p.kparts, split_parts_floats(D)};
   auto mm_nt = [&](const float* X, int ldx, const float* W, int ldw, float* C, int ldc, int M_, int N_, int K_, float beta,
                    const void* w_packed = nullptr) {   // C = beta C + X W^T
-    return gemm_x3(X3Op{X, ldx, M_, K_, false}, X3Op{W, ldw, N_, K_, false}, C, ldc, beta, xb, st, false, nullptr, w_packed);
+    return gemm_x3(X3Op{X, ldx, M_, K_, false}, X3Op{W, ldw, N_, K_, false}, C, ldc, beta, xb, st, true, nullptr, w_packed);
   };
   auto mm_nn = [&](const float* A_, int lda, const float* B_, int ldb, float* C, int ldc, int M_, int N_, int K_, float beta,
                    const void* b_packed = nullptr) {   // C = beta C + A B
     return gemm_x3(X3Op{A_, lda, M_, K_, false}, X3Op{B_, ldb, N_, K_, true}, C, ldc, beta, xb, st, true, nullptr, b_packed);
   };
   auto mm_tn = [&](const float* A_, int lda, const float* B_, int ldb, float* C, int Mg, int Ng, int Kg, float beta) {
-    return gemm_x3(X3Op{A_, lda, Mg, Kg, true}, X3Op{B_, ldb, Ng, Kg, true}, C, Ng, beta, xb, st, true);   // C = beta C + A^T B
+    return gemm_x3_tn(A_, lda, B_, ldb, C, Mg, Ng, Kg, beta, xb, st);   // C = beta C + A^T B
   };
 
   // ---- forward, every activation kept
