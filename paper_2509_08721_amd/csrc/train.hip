@@ -378,13 +378,14 @@ template <int N> __device__ __forceinline__ void x3_wait() {
 // C tile of a wave: TJ x 4 MFMA tiles; accumulator v of lane l: row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32.  A tile
 // without rows or columns past the end is stored without a comparison per value, rows by scalar base addresses.
 template <int TJ>
-__device__ __forceinline__ void x3_store_tile(const f32x16_t (&acc)[TJ][4], float* __restrict__ C, int ldc, int row0, int n0, int M,
-                                              int N, float beta) {
+__device__ __forceinline__ void x3_store_tile(const f32x16_t (&acc)[TJ][4], float* C, const float* Cin, int ldc, int row0, int n0,
+                                              int M, int N, float beta) {
   const int lane = threadIdx.x & 63;
   auto store = [&](auto full_c, auto beta_c) __attribute__((always_inline)) {
     constexpr bool full = decltype(full_c)::value, add = decltype(beta_c)::value;
     const unsigned off = (unsigned)((lane >> 5) * 4 * ldc + n0 + (lane & 31)) * 4u;   // bytes behind the base of a row pair
     const int m_lane = (lane >> 5) * 4, n = n0 + (lane & 31);
+    const ptrdiff_t d_in = (const char*)Cin - (const char*)C;
 #pragma unroll
     for (int t = 0; t < TJ; ++t)
 #pragma unroll
@@ -399,7 +400,7 @@ __device__ __forceinline__ void x3_store_tile(const f32x16_t (&acc)[TJ][4], floa
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
               old[u][j] = 0.f;
-              if (full || (row0 + t * 32 + 8 * v4 + u + m_lane < M && n + j * 32 < N)) old[u][j] = *(const float*)(base[u] + off + j * 128);
+              if (full || (row0 + t * 32 + 8 * v4 + u + m_lane < M && n + j * 32 < N)) old[u][j] = *(const float*)(base[u] + d_in + off + j * 128);
             }
         }
 #pragma unroll
@@ -427,8 +428,8 @@ __device__ __forceinline__ void x3_store_tile(const f32x16_t (&acc)[TJ][4], floa
 // TJ = 2: two workgroups per compute unit; TJ = 1: three.
 template <int NP, int TJ>
 __global__ void __launch_bounds__(256, TJ == 2 ? 2 : 3) k_gemm_x3(const u32x4_t* __restrict__ Ap, const u32x4_t* __restrict__ Bp,
-                                                                  float* __restrict__ C, int ldc, int M, int N, int KB, float beta,
-                                                                  int kb_split, size_t c_split) {
+                                                                  float* C, const float* Cin, int ldc, int M, int N, int KB,
+                                                                  float beta, int kb_split, size_t c_split) {
   constexpr int H = x3_stage(NP), NF = H * NP;     // ring copies per wave and stage; fragments of a column block
   constexpr int PER = NF + NF * TJ;                // requests per wave and stage
   constexpr int kRing = 3;
@@ -518,7 +519,7 @@ __global__ void __launch_bounds__(256, TJ == 2 ? 2 : 3) k_gemm_x3(const u32x4_t*
     stage(std::integral_constant<int, 1>(), st + 1);
   }
   if (st < nst) stage(std::integral_constant<int, 0>(), st);
-  x3_store_tile<TJ>(acc, C, ldc, ty * kGM * TJ + row_w, tx * kGM, M, N, beta);
+  x3_store_tile<TJ>(acc, C, Cin, ldc, ty * kGM * TJ + row_w, tx * kGM, M, N, beta);
 }
 
 // f(0), f(1), ... f(N - 1) with the index as a compile-time constant
@@ -559,8 +560,8 @@ template <int NP> __device__ __forceinline__ void x3_cut(const float (&x)[8], Fr
 // does), and a fragment's registers are requested again as soon as it is cut, a whole stage ahead.
 template <int NP, int TJ>
 __global__ void __launch_bounds__(256, TJ == 2 ? 2 : 3) k_gemm_x3_tn(const float* __restrict__ A, int lda, const float* __restrict__ B,
-                                                                     int ldb, float* __restrict__ C, int ldc, int M, int N, int K,
-                                                                     float beta, int k_split, size_t c_split) {
+                                                                     int ldb, float* C, int ldc, int M, int N, int K, float beta,
+                                                                     int k_split, size_t c_split) {
   constexpr int H = x3_tn_stage(NP), kTasks = H * (TJ + 1), KS = 16 * H;
   __shared__ u32x4_t Bs[2][H * NP * 4 * 64];
   const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63, kh = lane >> 5, c = lane & 31;
@@ -662,7 +663,7 @@ __global__ void __launch_bounds__(256, TJ == 2 ? 2 : 3) k_gemm_x3_tn(const float
     stage(odd, s + 1);
   }
   if (s < nst) stage(even, s);
-  x3_store_tile<TJ>(acc, C, ldc, row0, tx * kGM, M, N, beta);
+  x3_store_tile<TJ>(acc, C, C, ldc, row0, tx * kGM, M, N, beta);
 }
 
 // One operand of a packed GEMM: `rows` x K values at src[row * ld + k], or src[k * ld + row] when `trans`.
@@ -673,7 +674,7 @@ inline size_t x3_pack_bytes(int NP, size_t rows, size_t K) {
 inline int x3_steps(int K, int NP) { const int k = 16 * x3_stage(NP); return (K + k - 1) / k * x3_stage(NP); }   // padded k steps
 struct X3Bufs { void* a; void* b; size_t a_cap, b_cap; int NP; float* parts; size_t parts_cap; };
 constexpr int kMaxSplits = 16;
-__global__ void k_sum_parts(const float* __restrict__ part, int n_part, size_t n, float beta, float* __restrict__ out);
+__global__ void k_sum_parts(const float* __restrict__ part, int n_part, size_t n, float beta, const float* in, float* out);
 
 hipError_t x3_pack(const X3Op& op, void* dst, size_t cap, int NP, hipStream_t st) {
   if (x3_pack_bytes(NP, op.rows, op.K) > cap) return hipErrorInvalidValue;
@@ -717,33 +718,33 @@ X3Grid x3_grid(int NP, int rows, int cols, int KB, int stage, size_t parts_cap) 
   }
   return best;
 }
-hipError_t x3_sum_parts(const X3Bufs& bufs, int splits, size_t n, float beta, float* C, hipStream_t st) {
+hipError_t x3_sum_parts(const X3Bufs& bufs, int splits, size_t n, float beta, const float* Cin, float* C, hipStream_t st) {
   return launch(KID_MISC, k_sum_parts, dim3((unsigned)((n + 1023) / 1024)), dim3(256), 0, st, (const float*)bufs.parts, splits, n, beta,
-                C);
+                Cin, C);
 }
 // C[M, N] = beta C + op(A) op(B)^T-style product of two operands given row-wise over the same K
-hipError_t gemm_x3(const X3Op& A, const X3Op& B, float* C, int ldc, float beta, const X3Bufs& bufs, hipStream_t st,
-                   bool split_ok = false, const void* a_packed = nullptr, const void* b_packed = nullptr) {
+hipError_t gemm_x3(const X3Op& A, const X3Op& B, float* C, const float* Cin, int ldc, float beta, const X3Bufs& bufs, hipStream_t st,
+                   const void* b_packed = nullptr) {
   if (A.K != B.K || A.rows <= 0 || B.rows <= 0 || A.K <= 0) return hipErrorInvalidValue;
   hipError_t e;
-  // an operand packed earlier (a_packed / b_packed) is used as it is
-  if (!a_packed && (e = x3_pack(A, bufs.a, bufs.a_cap, bufs.NP, st)) != hipSuccess) return e;
+  if ((e = x3_pack(A, bufs.a, bufs.a_cap, bufs.NP, st)) != hipSuccess) return e;
+  // an operand packed earlier (b_packed) is used as it is
   if (!b_packed && (e = x3_pack(B, bufs.b, bufs.b_cap, bufs.NP, st)) != hipSuccess) return e;
-  const u32x4_t* pa_ = (const u32x4_t*)(a_packed ? a_packed : bufs.a);
+  const u32x4_t* pa_ = (const u32x4_t*)bufs.a;
   const u32x4_t* pb_ = (const u32x4_t*)(b_packed ? b_packed : bufs.b);
   const int KB = x3_steps(A.K, bufs.NP);
-  const X3Grid g = x3_grid(bufs.NP, A.rows, B.rows, KB, x3_stage(bufs.NP), split_ok && ldc == B.rows ? bufs.parts_cap : 0);
+  const X3Grid g = x3_grid(bufs.NP, A.rows, B.rows, KB, x3_stage(bufs.NP), ldc == B.rows ? bufs.parts_cap : 0);
   float* out = g.splits > 1 ? bufs.parts : C;
   const size_t c_split = g.splits > 1 ? (size_t)A.rows * B.rows : 0;
   const float b_ = g.splits > 1 ? 0.f : beta;
   auto go = [&](auto kernel) {
-    return launch(KID_GEMM_GENERIC, kernel, g.grid, dim3(256), 0, st, pa_, pb_, out, ldc, A.rows, B.rows, KB, b_, g.per_split, c_split);
+    return launch(KID_GEMM_GENERIC, kernel, g.grid, dim3(256), 0, st, pa_, pb_, out, Cin, ldc, A.rows, B.rows, KB, b_, g.per_split, c_split);
   };
   if (bufs.NP == 3) e = g.TJ == 2 ? go(k_gemm_x3<3, 2>) : go(k_gemm_x3<3, 1>);
   else if (bufs.NP == 2) e = g.TJ == 2 ? go(k_gemm_x3<2, 2>) : go(k_gemm_x3<2, 1>);
   else e = g.TJ == 2 ? go(k_gemm_x3<1, 2>) : go(k_gemm_x3<1, 1>);
   if (e != hipSuccess || g.splits == 1) return e;
-  return x3_sum_parts(bufs, g.splits, (size_t)A.rows * B.rows, beta, C, st);
+  return x3_sum_parts(bufs, g.splits, (size_t)A.rows * B.rows, beta, Cin, C, st);
 }
 // C[M, N] = beta C + A^T B, A [K, M] and B [K, N] in fp32
 hipError_t gemm_x3_tn(const float* A, int lda, const float* B, int ldb, float* C, int M, int N, int K, float beta,
@@ -762,7 +763,7 @@ hipError_t gemm_x3_tn(const float* A, int lda, const float* B, int ldb, float* C
   else if (bufs.NP == 2) e = g.TJ == 2 ? go(k_gemm_x3_tn<2, 2>) : go(k_gemm_x3_tn<2, 1>);
   else e = g.TJ == 2 ? go(k_gemm_x3_tn<1, 2>) : go(k_gemm_x3_tn<1, 1>);
   if (e != hipSuccess || g.splits == 1) return e;
-  return x3_sum_parts(bufs, g.splits, (size_t)M * N, beta, C, st);
+  return x3_sum_parts(bufs, g.splits, (size_t)M * N, beta, C, C, st);
 }
 
 template <int TA, int TB>
@@ -823,7 +824,114 @@ __global__ void __launch_bounds__(256) k_embed_rows(const int32_t* __restrict__ 
   for (int i = threadIdx.x; i < d; i += 256) h[m * d + i] = src[i];
 }
 
-// xn = h * rstd * gain, rstd = 1 / sqrt(mean(h^2) + eps); one workgroup per row
+// Rows of the norms: a wave takes a row, a lane its float4s lane, lane + 64, ... (NV of them: d <= 256 NV); no
+// workgroup-wide reduction, several rows in flight per compute unit.
+constexpr int kNormMaxV = 8;
+inline bool norm_rows_vectorised(int d) { return d % 4 == 0 && d <= 256 * kNormMaxV; }
+
+// xn = h * rstd * gain, rstd = 1 / sqrt(mean(h^2) + eps)
+template <int NV>
+__global__ void __launch_bounds__(256) k_rmsnorm_fwd_rows(const float* __restrict__ h, const float* __restrict__ gain, float eps,
+                                                          int M, int d, float* __restrict__ xn, float* __restrict__ rstd) {
+  const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63;
+  const size_t m = (size_t)blockIdx.x * 4 + wave;
+  if (m >= (size_t)M) return;
+  float4 x[NV];
+  float ss = 0.f;
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const int f = 4 * (lane + 64 * i);
+    x[i] = f < d ? *(const float4*)(h + m * d + f) : make_float4(0.f, 0.f, 0.f, 0.f);
+    ss = fmaf(x[i].x, x[i].x, fmaf(x[i].y, x[i].y, fmaf(x[i].z, x[i].z, fmaf(x[i].w, x[i].w, ss))));
+  }
+  ss = wave_reduce_sum(ss);
+  const float r = 1.0f / sqrtf(ss / (float)d + eps);
+  if (lane == 0) rstd[m] = r;
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const int f = 4 * (lane + 64 * i);
+    if (f >= d) continue;
+    const float4 g = *(const float4*)(gain + f);
+    *(float4*)(xn + m * d + f) = make_float4(x[i].x * r * g.x, x[i].y * r * g.y, x[i].z * r * g.z, x[i].w * r * g.w);
+  }
+}
+// Backward of the norm and the gain's gradient in one pass over dxn and h (in two they took 209 us per norm at 24576 rows
+// of 896, most of it in a kernel of 96 x 4 workgroups that walked 256 rows one after the other):
+//   dh (+)= rstd * gain * dxn - rstd^3 * h * mean_j(dxn_j gain_j h_j),   part[block] = sum over the block's rows of
+// dxn h rstd (kNormRows rows, each wave's in order, the four waves' sums in wave order)
+constexpr int kNormRows = 32;
+template <int NV>
+__global__ void __launch_bounds__(256) k_rmsnorm_bwd_rows(const float* __restrict__ dxn, const float* __restrict__ h,
+                                                          const float* __restrict__ rstd, const float* __restrict__ gain, int M,
+                                                          int d, float* __restrict__ dh, int accumulate, float* __restrict__ part) {
+  __shared__ float4 red[4][NV * 64];
+  const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63;
+  float4 g[NV], dg[NV];
+#pragma unroll
+  for (int i = 0; i < NV; ++i) {
+    const int f = 4 * (lane + 64 * i);
+    g[i] = f < d ? *(const float4*)(gain + f) : make_float4(0.f, 0.f, 0.f, 0.f);
+    dg[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+  const int m1 = min(M, ((int)blockIdx.x + 1) * kNormRows);
+  for (int m = blockIdx.x * kNormRows + wave; m < m1; m += 4) {
+    float4 x[NV], y[NV], o[NV];
+    float dot = 0.f;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const int f = 4 * (lane + 64 * i);
+      const size_t at = (size_t)m * d + f;
+      x[i] = o[i] = y[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (f < d) {
+        x[i] = *(const float4*)(dxn + at);
+        y[i] = *(const float4*)(h + at);
+        if (accumulate) o[i] = *(const float4*)(dh + at);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < NV; ++i)
+      dot = fmaf(x[i].x * g[i].x, y[i].x, fmaf(x[i].y * g[i].y, y[i].y, fmaf(x[i].z * g[i].z, y[i].z, fmaf(x[i].w * g[i].w, y[i].w, dot))));
+    dot = wave_reduce_sum(dot);
+    const float r = rstd[m], c = r * r * r * dot / (float)d;
+#pragma unroll
+    for (int i = 0; i < NV; ++i) {
+      const int f = 4 * (lane + 64 * i);
+      dg[i].x = fmaf(x[i].x * y[i].x, r, dg[i].x); dg[i].y = fmaf(x[i].y * y[i].y, r, dg[i].y);
+      dg[i].z = fmaf(x[i].z * y[i].z, r, dg[i].z); dg[i].w = fmaf(x[i].w * y[i].w, r, dg[i].w);
+      if (f < d)
+        *(float4*)(dh + (size_t)m * d + f) =
+            make_float4(o[i].x + (r * g[i].x * x[i].x - c * y[i].x), o[i].y + (r * g[i].y * x[i].y - c * y[i].y),
+                        o[i].z + (r * g[i].z * x[i].z - c * y[i].z), o[i].w + (r * g[i].w * x[i].w - c * y[i].w));
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < NV; ++i) red[wave][lane + 64 * i] = dg[i];
+  __syncthreads();
+  for (int e = threadIdx.x; 4 * e < d; e += 256) {
+    float4 s = red[0][e];
+#pragma unroll
+    for (int w = 1; w < 4; ++w) { s.x += red[w][e].x; s.y += red[w][e].y; s.z += red[w][e].z; s.w += red[w][e].w; }
+    *(float4*)(part + (size_t)blockIdx.x * d + 4 * e) = s;
+  }
+}
+// dgain += the partial sums: 16 columns per workgroup, 16 threads per column take parts k, k + 16, ...; added in that order
+__global__ void __launch_bounds__(256) k_gain_sum(const float* __restrict__ part, int n_part, int d, float* __restrict__ dgain) {
+  __shared__ float red[16][17];
+  const int c = threadIdx.x & 15, k = threadIdx.x >> 4, i = blockIdx.x * 16 + c;
+  float s = 0.f;
+  if (i < d) {
+#pragma unroll 8
+    for (int p = k; p < n_part; p += 16) s += part[(size_t)p * d + i];
+  }
+  red[k][c] = s;
+  __syncthreads();
+  if (k == 0 && i < d) {
+    for (int j = 1; j < 16; ++j) s += red[j][c];
+    dgain[i] += s;   // the gradient buffer starts at zero; micro-batches add up
+  }
+}
+
+// The same for rows that do not come in float4s: one workgroup per row
 __global__ void __launch_bounds__(256) k_rmsnorm_fwd(const float* __restrict__ h, const float* __restrict__ gain, float eps,
                                                      int d, float* __restrict__ xn, float* __restrict__ rstd) {
   __shared__ float red[4];
@@ -834,6 +942,19 @@ __global__ void __launch_bounds__(256) k_rmsnorm_fwd(const float* __restrict__ h
   const float r = 1.0f / sqrtf(ss / (float)d + eps);
   if (threadIdx.x == 0) rstd[m] = r;
   for (int i = threadIdx.x; i < d; i += 256) xn[m * d + i] = h[m * d + i] * r * gain[i];
+}
+template <typename F> hipError_t with_norm_width(int d, F&& f) {   // f(number of float4s per lane)
+  if (d <= 256) return f(std::integral_constant<int, 1>());
+  if (d <= 512) return f(std::integral_constant<int, 2>());
+  if (d <= 1024) return f(std::integral_constant<int, 4>());
+  return f(std::integral_constant<int, kNormMaxV>());
+}
+hipError_t rmsnorm_fwd(const float* h, const float* gain, float eps, int M, int d, float* xn, float* rstd, hipStream_t st) {
+  if (!norm_rows_vectorised(d))
+    return launch(KID_RMSNORM, k_rmsnorm_fwd, dim3(M), dim3(256), 0, st, h, gain, eps, d, xn, rstd);
+  return with_norm_width(d, [&](auto nv) {
+    return launch(KID_RMSNORM, k_rmsnorm_fwd_rows<decltype(nv)::value>, dim3((M + 3) / 4), dim3(256), 0, st, h, gain, eps, M, d, xn, rstd);
+  });
 }
 
 // Rotary embedding in place on the query and key heads of qkv[M, (Hq + 2 Hkv) hd]; position = row % T.
@@ -879,7 +1000,18 @@ __global__ void k_probs_from_lse(float* __restrict__ sc, const float* __restrict
   sc[idx] = (j <= i) ? expf(sc[idx] * scale - lse[r]) : 0.f;
 }
 
-// act = silu(gate) * up from gu[M, 2F] (gate columns first)
+// act = silu(gate) * up from gu[M, 2F] (gate columns first).  Workgroup (x, y): columns of row y, four per thread where F
+// allows it.
+__global__ void k_swiglu_fwd4(const float* __restrict__ gu, float* __restrict__ act, int F) {
+  const int f = (blockIdx.x * 256 + threadIdx.x) * 4;
+  if (f >= F) return;
+  const float* row = gu + (size_t)blockIdx.y * 2 * F + f;
+  const float4 g = *(const float4*)row, u = *(const float4*)(row + F);
+  float4 o;
+  o.x = g.x / (1.0f + expf(-g.x)) * u.x; o.y = g.y / (1.0f + expf(-g.y)) * u.y;
+  o.z = g.z / (1.0f + expf(-g.z)) * u.z; o.w = g.w / (1.0f + expf(-g.w)) * u.w;
+  *(float4*)(act + (size_t)blockIdx.y * F + f) = o;
+}
 __global__ void k_swiglu_fwd(const float* __restrict__ gu, float* __restrict__ act, int F, size_t total) {
   const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
   if (idx >= total) return;
@@ -910,35 +1042,79 @@ __global__ void __launch_bounds__(256) k_count_mask(const uint8_t* __restrict__ 
 }
 // Row k of `logits` belongs to row r = rows[k] of the batch (position r % T of sequence r / T), which predicts the
 // masked token at r + 1 (the list holds exactly those rows).  In place: logits -> d loss / d logits.
-__global__ void __launch_bounds__(256) k_logp_dlogits(float* __restrict__ logits, int V, const int* __restrict__ rows, int T,
-                                                      const int32_t* __restrict__ tokens, const uint8_t* __restrict__ mask,
-                                                      const float* __restrict__ logp_old, const float* __restrict__ adv,
-                                                      float eps_low, float eps_high, const long long* __restrict__ n_masked,
-                                                      float* __restrict__ logp_new) {
-  __shared__ float red[4];
+// Two passes over the row, each in float4s: log-sum-exp on a running maximum, then the gradient (the second pass finds the
+// row in the caches).  In three passes of single floats by 256 threads: 2.65 ms per chunk of 4352 x 151936 logits.
+constexpr int kLogpThreads = 512;
+__global__ void __launch_bounds__(kLogpThreads) k_logp_dlogits(float* __restrict__ logits, int V, const int* __restrict__ rows, int T,
+                                                               const int32_t* __restrict__ tokens, const uint8_t* __restrict__ mask,
+                                                               const float* __restrict__ logp_old, const float* __restrict__ adv,
+                                                               float eps_low, float eps_high, const long long* __restrict__ n_masked,
+                                                               float* __restrict__ logp_new) {
+  constexpr int NT = kLogpThreads;
+  __shared__ float red_m[NT / 64], red_l[NT / 64];
   const int r = rows[blockIdx.x];
   const int t = r % T;
   float* z = logits + (size_t)blockIdx.x * V;
+  const int V4 = (V & 3) == 0 ? V >> 2 : 0;   // rows of whole float4s (the buffer is aligned), else value by value
   if (t == T - 1 || !mask[r + 1]) {   // not in a well-formed list; uniform over the workgroup
-    for (int v = threadIdx.x; v < V; v += 256) z[v] = 0.f;
+    for (int v = threadIdx.x; v < V; v += NT) z[v] = 0.f;
     return;
   }
-  float mx = -INFINITY;
-  for (int v = threadIdx.x; v < V; v += 256) mx = fmaxf(mx, z[v]);
-  mx = block_max256(mx, red);
+  float m = -INFINITY, l = 0.f;
+  auto add = [&](float x) {
+    if (x > m) { l = l * expf(m - x) + 1.f; m = x; } else { l += expf(x - m); }
+  };
+  if (V4) {
+    for (int v0 = threadIdx.x; v0 < V4; v0 += 4 * NT) {
+      float4 x[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        x[u] = v0 + u * NT < V4 ? ((const float4*)z)[v0 + u * NT] : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+      float mx = m;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) mx = fmaxf(mx, fmaxf(fmaxf(x[u].x, x[u].y), fmaxf(x[u].z, x[u].w)));
+      if (mx == -INFINITY) continue;
+      if (mx > m) { l *= expf(m - mx); m = mx; }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) l += (expf(x[u].x - m) + expf(x[u].y - m)) + (expf(x[u].z - m) + expf(x[u].w - m));
+    }
+  } else {
+    for (int v = threadIdx.x; v < V; v += NT) add(z[v]);
+  }
+  const float mw = wave_reduce_max(m);
+  l = wave_reduce_sum(m == -INFINITY ? 0.f : l * expf(m - mw));
+  if ((threadIdx.x & 63) == 0) { red_m[threadIdx.x >> 6] = mw; red_l[threadIdx.x >> 6] = l; }
+  __syncthreads();
+  float mx = red_m[0];
+#pragma unroll
+  for (int w = 1; w < NT / 64; ++w) mx = fmaxf(mx, red_m[w]);
   float sum = 0.f;
-  for (int v = threadIdx.x; v < V; v += 256) sum += expf(z[v] - mx);
-  sum = block_sum256(sum, red);
-  const float l = mx + logf(sum);
+#pragma unroll
+  for (int w = 0; w < NT / 64; ++w) sum += red_m[w] == -INFINITY ? 0.f : red_l[w] * expf(red_m[w] - mx);
+  const float lse = mx + logf(sum);
   const int target = clamp_token(tokens[r + 1], V);
-  const float lp = z[target] - l;
+  const float lp = z[target] - lse;
   float rho; bool active;
   const float a = adv[r / T];
   surrogate_term(lp, logp_old[r + 1], a, eps_low, eps_high, rho, active);
   const float w = surrogate_dlogp(a, rho, active, *n_masked);
   __syncthreads();   // every thread has read z[target]
   if (threadIdx.x == 0) logp_new[r + 1] = lp;
-  for (int v = threadIdx.x; v < V; v += 256) z[v] = (w == 0.f) ? 0.f : w * ((v == target ? 1.f : 0.f) - expf(z[v] - l));
+  auto grad = [&](float x, int v) { return w == 0.f ? 0.f : w * ((v == target ? 1.f : 0.f) - expf(x - lse)); };
+  if (V4) {
+    for (int v0 = threadIdx.x; v0 < V4; v0 += 4 * NT) {
+      float4 x[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) x[u] = ((const float4*)z)[min(v0 + u * NT, V4 - 1)];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const int v = v0 + u * NT;
+        if (v < V4) ((float4*)z)[v] = make_float4(grad(x[u].x, 4 * v), grad(x[u].y, 4 * v + 1), grad(x[u].z, 4 * v + 2), grad(x[u].w, 4 * v + 3));
+      }
+    }
+  } else {
+    for (int v = threadIdx.x; v < V; v += NT) z[v] = grad(z[v], v);
+  }
 }
 
 // dst[k] = src[rows[k]] (gather) or dst[rows[k]] = src[k] (scatter): rows of d floats, one workgroup per listed row
@@ -949,13 +1125,13 @@ __global__ void __launch_bounds__(256) k_move_rows(const float* __restrict__ src
   float* b = dst + (scatter ? r : k) * d;
   for (int i = threadIdx.x; i < d; i += 256) b[i] = a[i];
 }
-// out = (beta ? out : 0) + sum over the parts, in part order
-__global__ void k_sum_parts(const float* __restrict__ part, int n_part, size_t n, float beta, float* __restrict__ out) {
+// out = beta in + sum over the parts, in part order (in may be out)
+__global__ void k_sum_parts(const float* __restrict__ part, int n_part, size_t n, float beta, const float* in, float* out) {
   const size_t i = ((size_t)blockIdx.x * 256 + threadIdx.x) * 4;
   if (i >= n) return;
-  if (n % 4 != 0 || ((uintptr_t)out & 15) != 0) {
+  if (n % 4 != 0 || (((uintptr_t)out | (uintptr_t)in) & 15) != 0) {
     for (size_t k = i; k < min(i + 4, n); ++k) {
-      float s = beta != 0.f ? beta * out[k] : 0.f;
+      float s = beta != 0.f ? beta * in[k] : 0.f;
       for (int p = 0; p < n_part; ++p) s += part[(size_t)p * n + k];
       out[k] = s;
     }
@@ -963,7 +1139,7 @@ __global__ void k_sum_parts(const float* __restrict__ part, int n_part, size_t n
   }
   float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
   if (beta != 0.f) {
-    s = *(const float4*)(out + i);
+    s = *(const float4*)(in + i);
     s.x *= beta; s.y *= beta; s.z *= beta; s.w *= beta;
   }
 #pragma unroll 4
@@ -1022,6 +1198,23 @@ __global__ void __launch_bounds__(256) k_gain_grad_finish(const float* __restric
   dgain[i] += s;   // the gradient buffer starts at zero; micro-batches add up
 }
 
+__device__ __forceinline__ void swiglu_grad(float g, float u, float da, float& dg, float& du) {
+  const float sg = 1.0f / (1.0f + expf(-g));
+  dg = da * u * sg * (1.0f + g * (1.0f - sg));
+  du = da * g * sg;
+}
+__global__ void k_swiglu_bwd4(const float* __restrict__ dact, const float* __restrict__ gu, float* __restrict__ dgu, int F) {
+  const int f = (blockIdx.x * 256 + threadIdx.x) * 4;
+  if (f >= F) return;
+  const float* row = gu + (size_t)blockIdx.y * 2 * F + f;
+  float* out = dgu + (size_t)blockIdx.y * 2 * F + f;
+  const float4 g = *(const float4*)row, u = *(const float4*)(row + F), da = *(const float4*)(dact + (size_t)blockIdx.y * F + f);
+  float4 dg, du;
+  swiglu_grad(g.x, u.x, da.x, dg.x, du.x); swiglu_grad(g.y, u.y, da.y, dg.y, du.y);
+  swiglu_grad(g.z, u.z, da.z, dg.z, du.z); swiglu_grad(g.w, u.w, da.w, dg.w, du.w);
+  *(float4*)out = dg;
+  *(float4*)(out + F) = du;
+}
 // dgu from dact: d gate = dact * up * sig(g) (1 + g (1 - sig(g))), d up = dact * silu(g)
 __global__ void k_swiglu_bwd(const float* __restrict__ dact, const float* __restrict__ gu, float* __restrict__ dgu, int F,
                              size_t total) {
@@ -1029,10 +1222,7 @@ __global__ void k_swiglu_bwd(const float* __restrict__ dact, const float* __rest
   if (idx >= total) return;
   const size_t m = idx / F;
   const int f = (int)(idx % F);
-  const float g = gu[m * 2 * F + f], u = gu[m * 2 * F + F + f], da = dact[idx];
-  const float sg = 1.0f / (1.0f + expf(-g));
-  dgu[m * 2 * F + f] = da * u * sg * (1.0f + g * (1.0f - sg));
-  dgu[m * 2 * F + F + f] = da * g * sg;
+  swiglu_grad(gu[m * 2 * F + f], gu[m * 2 * F + F + f], dact[idx], dgu[m * 2 * F + f], dgu[m * 2 * F + F + f]);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1222,15 +1412,18 @@ __global__ void __launch_bounds__(256, HD == 128 ? 3 : 1) k_tattn_bwd_q(const fl
   if (g == 0) delta[stat] = dl;
 }
 
-// Backward, keys and values: a wave owns 16 keys of one (sequence, KV head) and walks the query heads of the
-// group and the query tiles from its own on, in that fixed order:
+// Backward, keys and values: a wave owns 16 keys of one (sequence, KV head) and walks n_heads query heads of the group
+// (part blockIdx.y / hkv of it) and the query tiles from its own on, in that fixed order; n_heads = 1 leaves one partial
+// result per query head, which k_attn_bwd_finish adds in head order (all heads in one wave left the chip a fifth full:
+// 840 waves of up to 7 x 19 dependent tiles at 21 x 301):
 //   p = exp(scale s - lse_q), dV^T += dO^T p, dP = dO V^T, dS = scale p (dP - delta_q), dK^T += Q^T dS.
 template <int HD>
 __global__ void __launch_bounds__(256, HD == 64 ? 4 : 1) k_tattn_bwd_kv(const float* __restrict__ qkv, const float* __restrict__ dout,
                                                       const float* __restrict__ lse, const float* __restrict__ delta, int T, int hq,
-                                                      int hkv, float scale, float* __restrict__ dqkv) {
+                                                      int hkv, float scale, int n_heads, float* __restrict__ dkv, size_t row_stride,
+                                                      size_t part_stride) {
   const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
-  const int kvh = blockIdx.y, s = blockIdx.z, rep = hq / hkv;
+  const int kvh = blockIdx.y % hkv, part = blockIdx.y / hkv, s = blockIdx.z, rep = hq / hkv;
   const int k0 = (blockIdx.x * 4 + wave) * 16;
   if (k0 >= T) return;
   const int qd = hq * HD, kvd = hkv * HD;
@@ -1246,8 +1439,8 @@ __global__ void __launch_bounds__(256, HD == 64 ? 4 : 1) k_tattn_bwd_kv(const fl
   f32x4_t dk[HD / 16], dv[HD / 16];
 #pragma unroll
   for (int dt = 0; dt < HD / 16; ++dt) { dk[dt] = f32x4_t{0.f, 0.f, 0.f, 0.f}; dv[dt] = dk[dt]; }
-  for (int hh = 0; hh < rep; ++hh) {
-    const int h = kvh * rep + hh;
+  for (int hh = 0; hh < n_heads; ++hh) {
+    const int h = kvh * rep + part * n_heads + hh;
     const float* qb = base + (size_t)h * HD;
     const float* dob = dout + (size_t)s * T * qd + (size_t)h * HD;
     const float* lse_h = lse + ((size_t)s * hq + h) * T;
@@ -1273,20 +1466,60 @@ __global__ void __launch_bounds__(256, HD == 64 ? 4 : 1) k_tattn_bwd_kv(const fl
     }
   }
   if (!key_ok) return;
-  float* krow = dqkv + ((size_t)s * T + kj) * rl + qd + (size_t)kvh * HD;
+  float* krow = dkv + part * part_stride + ((size_t)s * T + kj) * row_stride + (size_t)kvh * HD;
   store_acc<HD>(krow, dk, g, 1.0f);
   store_acc<HD>(krow + kvd, dv, g, 1.0f);
 }
 
 template <int HD>
 hipError_t tattn_bwd(const float* qkv, const float* out, const float* dout, const float* lse, int S, int T, int hq, int hkv,
-                     float scale, float* dqkv, float* delta, hipStream_t st) {
+                     float scale, float* dqkv, float* delta, float* parts, hipStream_t st) {
   const unsigned tiles = (unsigned)((T + 63) / 64);
   hipError_t e = launch(KID_ATTN_GENERIC, k_tattn_bwd_q<HD>, dim3(tiles, hq, S), dim3(256), 0, st, qkv, out, dout, lse, T, hq, hkv,
                         scale, dqkv, delta);
   if (e != hipSuccess) return e;
+  const size_t qd = (size_t)hq * HD, kvd = (size_t)hkv * HD;
+  if (parts)   // [query heads of a group][S T][2 kvd]
+    return launch(KID_ATTN_GENERIC, k_tattn_bwd_kv<HD>, dim3(tiles, hq, S), dim3(256), 0, st, qkv, dout, lse, (const float*)delta, T,
+                  hq, hkv, scale, 1, parts, 2 * kvd, (size_t)S * T * 2 * kvd);
   return launch(KID_ATTN_GENERIC, k_tattn_bwd_kv<HD>, dim3(tiles, hkv, S), dim3(256), 0, st, qkv, dout, lse, (const float*)delta, T,
-                hq, hkv, scale, dqkv);
+                hq, hkv, scale, hq / hkv, dqkv + qd, qd + 2 * kvd, (size_t)0);
+}
+// The partial results of k_tattn_bwd_kv added in part order into dqkv's key and value columns, and the rotary embedding's
+// transpose on the query and key columns.  One workgroup per row; a thread takes 4 rotation pairs or 4 value columns.
+__global__ void __launch_bounds__(256) k_attn_bwd_finish(float* __restrict__ dqkv, const float* __restrict__ parts, int n_parts,
+                                                         size_t part_stride, const float2* __restrict__ rope, int T, int hq, int hkv,
+                                                         int hd) {
+  const size_t m = blockIdx.x;
+  const int half = hd >> 1, qd = hq * hd, kvd = hkv * hd, quads = half >> 2;
+  float* row = dqkv + m * (size_t)(qd + 2 * kvd);
+  const float* prow = parts + m * (size_t)(2 * kvd);
+  auto sum = [&](int c) {   // column c of [dk | dv]
+    float4 s = *(const float4*)(prow + c);
+    for (int p = 1; p < n_parts; ++p) {
+      const float4 v = *(const float4*)(prow + p * part_stride + c);
+      s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+    }
+    return s;
+  };
+  const int n_rot = (hq + hkv) * quads, n_all = n_rot + kvd / 4;
+  for (int e = threadIdx.x; e < n_all; e += 256) {
+    if (e >= n_rot) {
+      const int c = kvd + 4 * (e - n_rot);
+      *(float4*)(row + qd + c) = sum(c);
+      continue;
+    }
+    const int head = e / quads, i = 4 * (e % quads);
+    float* p = row + head * hd + i;
+    float4 a, b;
+    if (head < hq) { a = *(const float4*)p; b = *(const float4*)(p + half); }
+    else { a = sum((head - hq) * hd + i); b = sum((head - hq) * hd + i + half); }
+    const float4* cs = (const float4*)(rope + (m % T) * half + i);
+    const float4 c01 = cs[0], c23 = cs[1];   // (cos, sin) of four pairs
+    *(float4*)p = make_float4(a.x * c01.x + b.x * c01.y, a.y * c01.z + b.y * c01.w, a.z * c23.x + b.z * c23.y, a.w * c23.z + b.w * c23.w);
+    *(float4*)(p + half) =
+        make_float4(b.x * c01.x - a.x * c01.y, b.y * c01.z - a.y * c01.w, b.z * c23.x - a.z * c23.y, b.w * c23.z - a.w * c23.w);
+  }
 }
 
 // Attention backward pieces (the contractions are batched GEMMs):
@@ -1312,28 +1545,47 @@ __global__ void k_dscores(const float* __restrict__ prob, float* __restrict__ dp
   dp[idx] = pr == 0.f ? 0.f : scale * pr * (dp[idx] - delta[idx / T]);
 }
 
-// Embedding rows: dE[tokens[m]] += dh[m].  Workgroup b owns the token ids congruent to b modulo the grid size
-// and walks the rows in order m = 0, 1, ..., 256 at a time: one id, one owner, one order of additions.
-__global__ void __launch_bounds__(256) k_embed_bwd(const int32_t* __restrict__ tokens, const float* __restrict__ dh, int M, int d,
-                                                   int V, float* __restrict__ dE) {
-  __shared__ int s_tok[256];
-  for (int m0 = 0; m0 < M; m0 += 256) {
-    const int m = m0 + threadIdx.x;
-    int tok = -1;
-    if (m < M) {
-      tok = clamp_token(tokens[m], V);
-      if (tok % (int)gridDim.x != (int)blockIdx.x) tok = -1;
+// Embedding rows: dE[tokens[m]] += dh[m], in the order of the rows for every token.  The rows are taken 4096 at a time:
+// k_embed_order sorts a chunk's (token, row) pairs, k_embed_add gives every run of one token to a workgroup, which adds the
+// run's rows in order, 8 of them on their way at a time, and adds the sum to the token's row of dE; the chunks follow
+// each other on the stream.  (With one workgroup per class of tokens the most frequent token's rows were read, added to
+// memory and waited for one after the other: 4.6 ms at 64 x 384 Zipf-distributed tokens.)
+constexpr int kEmbedChunk = 4096;
+__global__ void __launch_bounds__(1024) k_embed_order(const int32_t* __restrict__ tokens, int M, int V, int* __restrict__ order) {
+  __shared__ unsigned long long key[kEmbedChunk];
+  const int m0 = blockIdx.x * kEmbedChunk, n = min(M - m0, kEmbedChunk);
+  for (int i = threadIdx.x; i < kEmbedChunk; i += 1024)
+    key[i] = i < n ? ((unsigned long long)(unsigned)clamp_token(tokens[m0 + i], V) << 32) | (unsigned)i : ~0ull;
+  for (int size = 2; size <= kEmbedChunk; size <<= 1)
+    for (int step = size >> 1; step > 0; step >>= 1) {
+      __syncthreads();
+      for (int j = threadIdx.x; j < kEmbedChunk / 2; j += 1024) {
+        const int lo = 2 * j - (j & (step - 1)), hi = lo + step;
+        const unsigned long long a = key[lo], b = key[hi];
+        if ((a > b) == ((lo & size) == 0)) { key[lo] = b; key[hi] = a; }
+      }
     }
-    __syncthreads();   // the previous round's list has been read
-    s_tok[threadIdx.x] = tok;
-    __syncthreads();
-    for (int j = 0; j < 256; ++j) {
-      const int t = s_tok[j];   // the same for every thread
-      if (t < 0) continue;
-      const float* src = dh + (size_t)(m0 + j) * d;
-      float* dst = dE + (size_t)t * d;
-      for (int i = threadIdx.x; i < d; i += 256) dst[i] += src[i];
+  __syncthreads();
+  for (int i = threadIdx.x; i < n; i += 1024) order[m0 + i] = (int)(unsigned)key[i];
+}
+// workgroup (x, y) of one wave: the run that starts at sorted position x, if one does, columns 256 y .. of it
+__global__ void __launch_bounds__(64) k_embed_add(const int32_t* __restrict__ tokens, const int* __restrict__ order, int n,
+                                                  const float* __restrict__ dh, int d, int V, float* __restrict__ dE) {
+  const int x = blockIdx.x;
+  const int tok = clamp_token(tokens[order[x]], V);
+  if (x > 0 && clamp_token(tokens[order[x - 1]], V) == tok) return;
+  int end = x + 1;
+  while (end < n && clamp_token(tokens[order[end]], V) == tok) ++end;
+  for (int c = blockIdx.y * 256 + threadIdx.x; c < min(d, ((int)blockIdx.y + 1) * 256); c += 64) {
+    float s = 0.f;
+    for (int p = x; p < end; p += 8) {
+      float v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = dh[(size_t)order[min(p + u, end - 1)] * d + c];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) s += p + u < end ? v[u] : 0.f;
     }
+    dE[(size_t)tok * d + c] += s;
   }
 }
 
@@ -1437,6 +1689,7 @@ struct TrainPlan {
   std::vector<LayerActs> layer;
   float *h_last, *rf, *xf;                      // final residual rows, their rstd, final-normed rows
   float* xfc;                                   // the final-normed rows that predict a masked token, gathered
+  int* eorder;                                  // a chunk's rows ordered by token (embedding gradient)
   int *mrows, *mpos, *mcount;                   // per micro-batch: those rows' indices (mpos: their (s, t)), their number
   float *dh, *dx, *dact, *dgu, *dao, *dqkv;     // backward temporaries
   float *delta, *prob, *dsc, *gpart, *logits, *logp_all, *loss;
@@ -1473,6 +1726,7 @@ void make_plan(const sapo_model_config& c, size_t S, size_t T, size_t S_total, c
   p.xf = A.take<float>(M * D.d);
   p.xfc = A.take<float>(M * D.d);
   p.mrows = A.take<int>(S_total * T);
+  p.eorder = A.take<int>(M);
   p.mpos = A.take<int>(2 * M);
   p.mcount = A.take<int>((S_total + S - 1) / S);
   p.dh = A.take<float>(M * D.d);
@@ -1486,7 +1740,7 @@ void make_plan(const sapo_model_config& c, size_t S, size_t T, size_t S_total, c
   const size_t n_tt = fused_attention(c) ? 0 : S * c.n_q_heads * T * T;
   p.prob = A.take<float>(n_tt);
   p.dsc = A.take<float>(n_tt);
-  p.gpart = A.take<float>(((M + 255) / 256) * std::max(D.d, D.nqkv));
+  p.gpart = A.take<float>(std::max(((M + kNormRows - 1) / kNormRows) * D.d, ((M + 255) / 256) * std::max(D.d, D.nqkv)));
   p.chunk = lm_chunk_rows(D, M);
   p.logits = A.take<float>(p.chunk * D.V);
   p.logp_all = A.take<float>(S_total * T);   // log-probs of the whole training set (micro-batches fill their rows)
@@ -1721,12 +1975,12 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
   const int pieces = tr->pieces;
   const X3Bufs xb{p.packa, p.packb, p.packa_cap, p.packb_cap, pieces, p.kparts, split_parts_floats(D)};
   auto mm_nt = [&](const float* X, int ldx, const float* W, int ldw, float* C, int ldc, int M_, int N_, int K_, float beta,
-                   const void* w_packed = nullptr) {   // C = beta C + X W^T
-    return gemm_x3(X3Op{X, ldx, M_, K_, false}, X3Op{W, ldw, N_, K_, false}, C, ldc, beta, xb, st, true, nullptr, w_packed);
+                   const float* Cin = nullptr, const void* w_packed = nullptr) {   // C = beta Cin + X W^T
+    return gemm_x3(X3Op{X, ldx, M_, K_, false}, X3Op{W, ldw, N_, K_, false}, C, Cin, ldc, beta, xb, st, w_packed);
   };
   auto mm_nn = [&](const float* A_, int lda, const float* B_, int ldb, float* C, int ldc, int M_, int N_, int K_, float beta,
                    const void* b_packed = nullptr) {   // C = beta C + A B
-    return gemm_x3(X3Op{A_, lda, M_, K_, false}, X3Op{B_, ldb, N_, K_, true}, C, ldc, beta, xb, st, true, nullptr, b_packed);
+    return gemm_x3(X3Op{A_, lda, M_, K_, false}, X3Op{B_, ldb, N_, K_, true}, C, C, ldc, beta, xb, st, b_packed);
   };
   auto mm_tn = [&](const float* A_, int lda, const float* B_, int ldb, float* C, int Mg, int Ng, int Kg, float beta) {
     return gemm_x3_tn(A_, lda, B_, ldb, C, Mg, Ng, Kg, beta, xb, st);   // C = beta C + A^T B
@@ -1738,8 +1992,7 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
   for (int l = 0; l < D.L; ++l) {
     const LayerActs& a = p.layer[l];
     const int t0 = 1 + 9 * l;   // attn_norm, wq, wk, wv, wo, ffn_norm, w_gate, w_up, w_down
-    T_CK(launch(KID_RMSNORM, k_rmsnorm_fwd, dim3(Mi), dim3(256), 0, st, (const float*)a.h, (const float*)TH(t0), c.rms_eps, d,
-                a.xn, a.r1));
+    T_CK(rmsnorm_fwd(a.h, TH(t0), c.rms_eps, Mi, d, a.xn, a.r1, st));
     T_CK(mm_nt(a.xn, d, TH(t0 + 1), d, a.qkv, nqkv, Mi, nqkv, d, 0.f));   // wq, wk, wv are adjacent
     if (tr->use_bias) T_CK(g_add_row_bias(a.qkv, TH(tr->n_in + l), Mi, nqkv, st));
     {
@@ -1761,18 +2014,17 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
                   att_scale));
       T_CK((sgemm<0, 0>(p.prob, (int)T, a.qkv + q + kv, nqkv, a.ao, q, (int)T, hd, (int)T, 0.f, st, b_pv)));
     }
-    T_CK(hipMemcpyAsync(a.h2, a.h, M * D.d * sizeof(float), hipMemcpyDeviceToDevice, st));
-    T_CK(mm_nt(a.ao, q, TH(t0 + 4), q, a.h2, d, Mi, d, q, 1.f));
-    T_CK(launch(KID_RMSNORM, k_rmsnorm_fwd, dim3(Mi), dim3(256), 0, st, (const float*)a.h2, (const float*)TH(t0 + 5), c.rms_eps,
-                d, a.xn2, a.r2));
+    T_CK(mm_nt(a.ao, q, TH(t0 + 4), q, a.h2, d, Mi, d, q, 1.f, a.h));
+    T_CK(rmsnorm_fwd(a.h2, TH(t0 + 5), c.rms_eps, Mi, d, a.xn2, a.r2, st));
     T_CK(mm_nt(a.xn2, d, TH(t0 + 6), d, a.gu, 2 * F, Mi, 2 * F, d, 0.f));   // w_gate, w_up are adjacent
-    T_CK(launch(KID_SWIGLU, k_swiglu_fwd, dim3(blocks256(M * D.F)), dim3(256), 0, st, (const float*)a.gu, a.act, F, M * D.F));
+    if (F % 4 == 0 && M <= 65535)
+      T_CK(launch(KID_SWIGLU, k_swiglu_fwd4, dim3((F / 4 + 255) / 256, Mi), dim3(256), 0, st, (const float*)a.gu, a.act, F));
+    else
+      T_CK(launch(KID_SWIGLU, k_swiglu_fwd, dim3(blocks256(M * D.F)), dim3(256), 0, st, (const float*)a.gu, a.act, F, M * D.F));
     float* h_next = (l + 1 < D.L) ? p.layer[l + 1].h : p.h_last;
-    T_CK(hipMemcpyAsync(h_next, a.h2, M * D.d * sizeof(float), hipMemcpyDeviceToDevice, st));
-    T_CK(mm_nt(a.act, F, TH(t0 + 8), F, h_next, d, Mi, d, F, 1.f));
+    T_CK(mm_nt(a.act, F, TH(t0 + 8), F, h_next, d, Mi, d, F, 1.f, a.h2));
   }
-  T_CK(launch(KID_RMSNORM, k_rmsnorm_fwd, dim3(Mi), dim3(256), 0, st, (const float*)p.h_last, (const float*)TH(t_final),
-              c.rms_eps, d, p.xf, p.rf));
+  T_CK(rmsnorm_fwd(p.h_last, TH(t_final), c.rms_eps, Mi, d, p.xf, p.rf, st));
 
   // ---- LM head, over the rows that predict a masked token only (the others have no log-prob to report and a zero
   // d logits row): their final-normed rows gathered, then chunks of them: logits, log-probs, d logits, d rows (into
@@ -1783,8 +2035,8 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
     T_CK(launch(KID_MISC, k_move_rows, dim3(n_rows), dim3(256), 0, st, (const float*)p.xf, rows, d, 0, p.xfc));
     for (size_t r0 = 0; r0 < (size_t)n_rows; r0 += p.chunk) {
       const int R = (int)(((size_t)n_rows - r0 < p.chunk) ? (size_t)n_rows - r0 : p.chunk);
-      T_CK(mm_nt(p.xfc + r0 * D.d, d, TH(t_head), d, p.logits, V, R, V, d, 0.f, p.head_nt));
-      T_CK(launch(KID_SCORE_ROWS, k_logp_dlogits, dim3(R), dim3(256), 0, st, p.logits, V, rows + r0, (int)T, tokens, completion_mask,
+      T_CK(mm_nt(p.xfc + r0 * D.d, d, TH(t_head), d, p.logits, V, R, V, d, 0.f, nullptr, p.head_nt));
+      T_CK(launch(KID_SCORE_ROWS, k_logp_dlogits, dim3(R), dim3(kLogpThreads), 0, st, p.logits, V, rows + r0, (int)T, tokens, completion_mask,
                   logp_old, advantages, eps_low, eps_high, (const long long*)p.n_masked, logp_new));
       T_CK(mm_nn(p.logits, V, TH(t_head), d, p.dh + r0 * D.d, d, R, d, V, 0.f, p.head_t));
       T_CK(mm_tn(p.logits, V, p.xfc + r0 * D.d, d, GR(t_head), V, d, R, 1.f));
@@ -1794,6 +2046,15 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
   // ---- backward through the layers
   const int n_gpart = (Mi + 255) / 256;
   auto norm_bwd = [&](const float* dxn, const float* hin, const float* rstd, int gain_tensor_idx, int accumulate) -> hipError_t {
+    if (norm_rows_vectorised(d)) {
+      const int n_part = (Mi + kNormRows - 1) / kNormRows;
+      const hipError_t e = with_norm_width(d, [&](auto nv) {
+        return launch(KID_RMSNORM, k_rmsnorm_bwd_rows<decltype(nv)::value>, dim3(n_part), dim3(256), 0, st, dxn, hin, rstd,
+                      (const float*)TH(gain_tensor_idx), Mi, d, p.dh, accumulate, p.gpart);
+      });
+      if (e != hipSuccess) return e;
+      return launch(KID_MISC, k_gain_sum, dim3((d + 15) / 16), dim3(256), 0, st, (const float*)p.gpart, n_part, d, GR(gain_tensor_idx));
+    }
     hipError_t e = launch(KID_MISC, k_gain_grad_partial, dim3((d + 255) / 256, n_gpart), dim3(256), 0, st, dxn, hin, rstd, Mi, d,
                           p.gpart);
     if (e != hipSuccess) return e;
@@ -1810,7 +2071,11 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
     // down projection
     T_CK(mm_nn(p.dh, d, TH(t0 + 8), F, p.dact, F, Mi, F, d, 0.f));
     T_CK(mm_tn(p.dh, d, a.act, F, GR(t0 + 8), d, F, Mi, 1.f));
-    T_CK(launch(KID_SWIGLU, k_swiglu_bwd, dim3(blocks256(M * D.F)), dim3(256), 0, st, (const float*)p.dact, (const float*)a.gu,
+    if (F % 4 == 0 && M <= 65535)
+      T_CK(launch(KID_SWIGLU, k_swiglu_bwd4, dim3((F / 4 + 255) / 256, Mi), dim3(256), 0, st, (const float*)p.dact,
+                  (const float*)a.gu, p.dgu, F));
+    else
+      T_CK(launch(KID_SWIGLU, k_swiglu_bwd, dim3(blocks256(M * D.F)), dim3(256), 0, st, (const float*)p.dact, (const float*)a.gu,
                 p.dgu, F, M * D.F));
     // gate / up projections
     T_CK(mm_nn(p.dgu, 2 * F, TH(t0 + 6), d, p.dx, d, Mi, d, 2 * F, 0.f));
@@ -1819,13 +2084,14 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
     // output projection
     T_CK(mm_nn(p.dh, d, TH(t0 + 4), q, p.dao, q, Mi, q, d, 0.f));
     T_CK(mm_tn(p.dh, d, a.ao, q, GR(t0 + 4), d, q, Mi, 1.f));
-    // attention and the rotary embedding
+    // attention and the rotary embedding; dgu is free here and takes the partial dk / dv
+    float* kv_parts = fused_attn && rep > 1 && 2 * D.F >= 2 * D.q ? p.dgu : nullptr;
     if (fused_attn) {
       hipError_t e = hipErrorInvalidValue;
-      if (hd == 16) e = tattn_bwd<16>(a.qkv, a.ao, p.dao, a.lse, S_, T_, hq, hkv, att_scale, p.dqkv, p.delta, st);
-      if (hd == 32) e = tattn_bwd<32>(a.qkv, a.ao, p.dao, a.lse, S_, T_, hq, hkv, att_scale, p.dqkv, p.delta, st);
-      if (hd == 64) e = tattn_bwd<64>(a.qkv, a.ao, p.dao, a.lse, S_, T_, hq, hkv, att_scale, p.dqkv, p.delta, st);
-      if (hd == 128) e = tattn_bwd<128>(a.qkv, a.ao, p.dao, a.lse, S_, T_, hq, hkv, att_scale, p.dqkv, p.delta, st);
+      if (hd == 16) e = tattn_bwd<16>(a.qkv, a.ao, p.dao, a.lse, S_, T_, hq, hkv, att_scale, p.dqkv, p.delta, kv_parts, st);
+      if (hd == 32) e = tattn_bwd<32>(a.qkv, a.ao, p.dao, a.lse, S_, T_, hq, hkv, att_scale, p.dqkv, p.delta, kv_parts, st);
+      if (hd == 64) e = tattn_bwd<64>(a.qkv, a.ao, p.dao, a.lse, S_, T_, hq, hkv, att_scale, p.dqkv, p.delta, kv_parts, st);
+      if (hd == 128) e = tattn_bwd<128>(a.qkv, a.ao, p.dao, a.lse, S_, T_, hq, hkv, att_scale, p.dqkv, p.delta, kv_parts, st);
       T_CK(e);
     } else {
       T_CK((sgemm<0, 1>(a.qkv, nqkv, a.qkv + q, nqkv, p.prob, (int)T, (int)T, (int)T, hd, 0.f, st, b_scores)));
@@ -1854,7 +2120,10 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
                           (int)T, beta, st, b_dv)));                                                               // dV += P^T dO
       }
     }
-    {
+    if (kv_parts) {
+      T_CK(launch(KID_ROPE_APPEND, k_attn_bwd_finish, dim3(Mi), dim3(256), 0, st, p.dqkv, (const float*)kv_parts, rep,
+                  M * 2 * D.kv, (const float2*)tr->rope, (int)T, hq, hkv, hd));
+    } else {
       const size_t total = M * (size_t)(hq + hkv) * (hd / 2);
       T_CK(launch(KID_ROPE_APPEND, k_rope, dim3(blocks256(total)), dim3(256), 0, st, p.dqkv, (const float2*)tr->rope, (int)T,
                   hq + hkv, hd, nqkv, -1.0f, total));
@@ -1870,7 +2139,12 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
     T_CK(mm_tn(p.dqkv, nqkv, a.xn, d, GR(t0 + 1), nqkv, d, Mi, 1.f));
     T_CK(norm_bwd(p.dx, a.h, a.r1, t0, 1));
   }
-  T_CK(launch(KID_EMBED, k_embed_bwd, dim3(512), dim3(256), 0, st, tokens, (const float*)p.dh, Mi, d, V, GR(0)));
+  T_CK(launch(KID_EMBED, k_embed_order, dim3((Mi + kEmbedChunk - 1) / kEmbedChunk), dim3(1024), 0, st, tokens, Mi, V, p.eorder));
+  for (int m0 = 0; m0 < Mi; m0 += kEmbedChunk) {
+    const int n = std::min(kEmbedChunk, Mi - m0);
+    T_CK(launch(KID_EMBED, k_embed_add, dim3(n, (d + 255) / 256), dim3(64), 0, st, tokens + m0, (const int*)(p.eorder + m0), n,
+                (const float*)(p.dh + (size_t)m0 * D.d), d, V, GR(0)));
+  }
 
   return SAPO_OK;
 }
