@@ -295,11 +295,12 @@ __device__ __forceinline__ uint32_t pack_hi(uint32_t a, uint32_t b) { return (a 
 __device__ __forceinline__ size_t x3_entry(int NP, int KB, int piece, int row, int k8) {
   return ((((size_t)(row >> 7) * KB + (k8 >> 1)) * NP + piece) * 2 + (k8 & 1)) * 128 + (row & 127);
 }
-__device__ __forceinline__ void x3_store(uint4* __restrict__ dst, int NP, int KB, int row, int k8, const float (&x)[8]) {
+template <int NP>
+__device__ __forceinline__ void x3_store(uint4* __restrict__ dst, int KB, int row, int k8, const float (&x)[8]) {
   uint32_t p[3][8];
 #pragma unroll
   for (int j = 0; j < 8; ++j) split3(x[j], p[0][j], p[1][j], p[2][j]);
-  if (NP < 3) {   // one or two pieces are roundings to nearest even (of the value, then of what is left), not bit fields
+  if constexpr (NP < 3) {   // one or two pieces are roundings to nearest even (of the value, then of what is left), not bit fields
     auto rne = [](float f) { const uint32_t u = __float_as_uint(f); return (u + 0x7FFFu + ((u >> 16) & 1u)) & 0xFFFF0000u; };
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
@@ -307,18 +308,37 @@ __device__ __forceinline__ void x3_store(uint4* __restrict__ dst, int NP, int KB
       p[1][j] = rne(x[j] - __uint_as_float(p[0][j]));
     }
   }
+#pragma unroll
   for (int pc = 0; pc < NP; ++pc)
     dst[x3_entry(NP, KB, pc, row, k8)] = make_uint4(pack_hi(p[pc][0], p[pc][1]), pack_hi(p[pc][2], p[pc][3]),
                                                     pack_hi(p[pc][4], p[pc][5]), pack_hi(p[pc][6], p[pc][7]));
 }
 // src[row * ld + k]: one workgroup per (block of 128 rows, 8 k steps); thread (row, k half) reads 8 consecutive
 // k per step, so a row is read in 64-byte runs and every piece of a step goes out as two 2 KB runs
+template <int NP>
 __global__ void __launch_bounds__(256) k_pack_x3(const float* __restrict__ src, int ld, int rows, int K, int /*rows_pad*/, int KB,
-                                                 int NP, uint4* __restrict__ dst) {
+                                                 uint4* __restrict__ dst) {
   const int row = blockIdx.x * 128 + (threadIdx.x >> 1), kh = threadIdx.x & 1;
   const float* rp = src + (size_t)row * ld;
   const bool vec = ((ld & 3) == 0) && ((((uintptr_t)src) & 15) == 0);
-  for (int kb = blockIdx.y * 8; kb < min(KB, blockIdx.y * 8 + 8); ++kb) {
+  const int kb0 = blockIdx.y * 8, n = min(KB - kb0, 8);
+  if (vec && n == 8 && (kb0 + 8) * 16 <= K && (int)blockIdx.x * 128 + 128 <= rows) {
+    // everything the thread reads is in flight at once
+    float4 v[8][2];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const float* q = rp + (kb0 + i) * 16 + kh * 8;
+      v[i][0] = *(const float4*)q;
+      v[i][1] = *(const float4*)(q + 4);
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const float x[8] = {v[i][0].x, v[i][0].y, v[i][0].z, v[i][0].w, v[i][1].x, v[i][1].y, v[i][1].z, v[i][1].w};
+      x3_store<NP>(dst, KB, row, (kb0 + i) * 2 + kh, x);
+    }
+    return;
+  }
+  for (int kb = kb0; kb < kb0 + n; ++kb) {
     const int k0 = kb * 16 + kh * 8;
     float x[8];
     if (row < rows && k0 + 8 <= K && vec) {
@@ -328,12 +348,13 @@ __global__ void __launch_bounds__(256) k_pack_x3(const float* __restrict__ src, 
 #pragma unroll
       for (int j = 0; j < 8; ++j) x[j] = (row < rows && k0 + j < K) ? rp[k0 + j] : 0.f;
     }
-    x3_store(dst, NP, KB, row, kb * 2 + kh, x);
+    x3_store<NP>(dst, KB, row, kb * 2 + kh, x);
   }
 }
 // src[k * ld + row] (rows contiguous): 64 rows x 64 k per workgroup through LDS
+template <int NP>
 __global__ void __launch_bounds__(256) k_pack_x3_t(const float* __restrict__ src, int ld, int rows, int K, int rows_pad, int KB,
-                                                   int NP, uint4* __restrict__ dst) {
+                                                   uint4* __restrict__ dst) {
   __shared__ float tile[64][65];
   const int r0 = blockIdx.x * 64, k0 = blockIdx.y * 64;
   for (int e = threadIdx.x; e < 64 * 64; e += 256) {
@@ -349,7 +370,7 @@ __global__ void __launch_bounds__(256) k_pack_x3_t(const float* __restrict__ src
     float x[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) x[j] = tile[kq * 8 + j][rr];
-    x3_store(dst, NP, KB, row, k8, x);
+    x3_store<NP>(dst, KB, row, k8, x);
   }
 }
 
@@ -679,11 +700,12 @@ __global__ void k_sum_parts(const float* __restrict__ part, int n_part, size_t n
 hipError_t x3_pack(const X3Op& op, void* dst, size_t cap, int NP, hipStream_t st) {
   if (x3_pack_bytes(NP, op.rows, op.K) > cap) return hipErrorInvalidValue;
   const int rows_pad = (op.rows + 127) / 128 * 128, KB = x3_steps(op.K, NP);
-  if (!op.trans)
-    return launch(KID_MISC, k_pack_x3, dim3(rows_pad / 128, (KB + 7) / 8), dim3(256), 0, st, op.src, op.ld, op.rows, op.K, rows_pad,
-                  KB, NP, (uint4*)dst);
-  return launch(KID_MISC, k_pack_x3_t, dim3(rows_pad / 64, (KB * 16 + 63) / 64), dim3(256), 0, st, op.src, op.ld, op.rows, op.K,
-                rows_pad, KB, NP, (uint4*)dst);
+  const dim3 grid = op.trans ? dim3(rows_pad / 64, (KB * 16 + 63) / 64) : dim3(rows_pad / 128, (KB + 7) / 8);
+  auto go = [&](auto kernel) {
+    return launch(KID_MISC, kernel, grid, dim3(256), 0, st, op.src, op.ld, op.rows, op.K, rows_pad, KB, (uint4*)dst);
+  };
+  if (op.trans) return NP == 3 ? go(k_pack_x3_t<3>) : NP == 2 ? go(k_pack_x3_t<2>) : go(k_pack_x3_t<1>);
+  return NP == 3 ? go(k_pack_x3<3>) : NP == 2 ? go(k_pack_x3<2>) : go(k_pack_x3<1>);
 }
 // Tile, grid and split of a product with `rows` x `cols` outputs and KB k steps in stages of `stage`.
 struct X3Grid { int TJ, splits, per_split; dim3 grid; };
