@@ -451,7 +451,7 @@ struct FwdBufs {      // activations for M rows
   void* attn;         // [M, q] attention output (T; row-major, or X-packed on the 64-token decode path)
   float* gu;          // [M, 2 F] (shape-generic kernels only)
   void* act;          // [M, F] (T; row-major, or X-packed on the 64-token decode path)
-  float* ssq;         // [M, d / 128 rounded up to 4] sum-of-squares parts of the residual rows (token-parallel MFMA path)
+  float* ssq;         // [M, d / 64 rounded up to 4] sum-of-squares parts of the residual rows (token-parallel MFMA path)
 };
 
 static void carve_fwd(Arena& A, const sapo_weights* w, size_t M, FwdBufs& b) {
@@ -465,7 +465,7 @@ static void carve_fwd(Arena& A, const sapo_weights* w, size_t M, FwdBufs& b) {
   b.attn = A.take_bytes(Mp * q * w->elt);
   b.gu = w->mfma ? nullptr : A.take<float>(M * 2 * F);
   b.act = A.take_bytes(Mp * F * w->elt);
-  b.ssq = w->mfma ? A.take<float>(M * ((d / 128 + 3) / 4 * 4)) : nullptr;
+  b.ssq = w->mfma ? A.take<float>(M * ((d / 64 + 3) / 4 * 4)) : nullptr;
 }
 
 struct CacheBufs {
@@ -563,7 +563,7 @@ static int run_layers_big(const sapo_weights* w, const FwdBufs& b, int M, RowMap
     if (l == 0 || !fold) {
       HIP_CK(m_rmsnorm_x32(b.h, lw.attn_norm, c.rms_eps, b.a, M, d, nullptr, st));
     } else {
-      qkv_ep.ssq_in = b.ssq; qkv_ep.ssq_parts = parts; qkv_ep.norm_dim = (float)d; qkv_ep.eps = c.rms_eps;
+      qkv_ep.ssq_in = b.ssq; qkv_ep.ssq_parts = parts; qkv_ep.ssq_halves = m_gemm_writes_halves(M, d); qkv_ep.norm_dim = (float)d; qkv_ep.eps = c.rms_eps;
     }
     unsigned long long* const clamped = w->clamp_counter;   // debug forward only: count the half values at the clamp
     if (clamped) HIP_CK(g_count_half_at_limit(b.a, M, d, 1, clamped, st));
@@ -575,7 +575,7 @@ static int run_layers_big(const sapo_weights* w, const FwdBufs& b, int M, RowMap
     BigEpi gu_ep{BIG_SWIGLU, nullptr, 0, (f16*)b.act};
     if (fold) {
       o_ep.gain_next = lw.ffn_norm; o_ep.xn_out = (f16*)b.a; o_ep.ssq_out = b.ssq;
-      gu_ep.ssq_in = b.ssq; gu_ep.ssq_parts = parts; gu_ep.norm_dim = (float)d; gu_ep.eps = c.rms_eps;
+      gu_ep.ssq_in = b.ssq; gu_ep.ssq_parts = parts; gu_ep.ssq_halves = m_gemm_writes_halves(M, d); gu_ep.norm_dim = (float)d; gu_ep.eps = c.rms_eps;
     }
     HIP_CK(m_gemm_big(b.attn, lw.wo, M, d, q, o_ep, st));
     if (!fold) HIP_CK(m_rmsnorm_x32(b.h, lw.ffn_norm, c.rms_eps, b.a, M, d, nullptr, st));

@@ -74,6 +74,10 @@ struct KVCache {
 // (left to the compiler, which product is fused depends on the instruction order it happens to pick).
 __device__ __forceinline__ float rot_first(float a, float b, float c, float s) { return __builtin_fmaf(a, c, -(b * s)); }
 __device__ __forceinline__ float rot_second(float a, float b, float c, float s) { return __builtin_fmaf(b, c, a * s); }
+// Sum of four squares, for the same reason.
+__device__ __forceinline__ float sum_squares4(const float4& s) {
+  return __builtin_fmaf(s.w, s.w, __builtin_fmaf(s.z, s.z, __builtin_fmaf(s.x, s.x, s.y * s.y)));
+}
 template <typename T> __device__ __forceinline__ float to_f32(T x) { return static_cast<float>(x); }
 template <typename T> __device__ __forceinline__ T from_f32(float x) { return static_cast<T>(x); }
 template <> __device__ __forceinline__ f16 from_f32<f16>(float x) { return (f16)fminf(fmaxf(x, -65504.f), 65504.f); }
@@ -448,12 +452,13 @@ struct BigEpi {
   int main_blocks = 0;   // set by the launcher: the workgroups behind these prefetch
   const float* ssq_in = nullptr;   // [M, ssq_parts rounded up to a multiple of 4]; at most 16 parts
   int ssq_parts = 0;
+  bool ssq_halves = false;         // every part as the two 64-feature halves it is the sum of: [M, 2 ssq_parts rounded up to a multiple of 4]
   float norm_dim = 0.f, eps = 0.f;
   // Producer side (ADD_F32 only): the updated residual row, times gain_next, goes out as half in X32
   // order (the next GEMM's operand), and its sum of squares in N / 128 parts per row.
   const float* gain_next = nullptr;   // [N]
   f16* xn_out = nullptr;
-  float* ssq_out = nullptr;           // [M, N / 128 rounded up to a multiple of 4]
+  float* ssq_out = nullptr;           // [M, N / 128 rounded up to a multiple of 4], or halves (m_gemm_writes_halves)
 };
 enum { BIG_STORE_F32 = 0, BIG_ADD_F32 = 1, BIG_SWIGLU = 2 };
 
@@ -461,6 +466,7 @@ enum { BIG_STORE_F32 = 0, BIG_ADD_F32 = 1, BIG_SWIGLU = 2 };
 struct QkvEpi {
   const float* ssq_in = nullptr;   // row scale of the folded norm, as in BigEpi
   int ssq_parts = 0;
+  bool ssq_halves = false;
   float norm_dim = 0.f, eps = 0.f;
   const float* bias = nullptr;     // [N] optional
   const float2* rope = nullptr;    // [max_seq][hd / 2] (cos, sin)
@@ -475,6 +481,8 @@ constexpr int kPackRangeSlots = 512;   // pairs of range counters behind m_pack_
 hipError_t m_pack_weight(const void* src, int n_rows, int K, void* dst, int dst_tile0, int dst_tile_stride, unsigned* range,
                          hipStream_t st);
 // Xp: tokens in X32 fragment order (rows padded to a multiple of 32); Wp: weights in W32 order
+// Whether a BIG_ADD_F32 launch of this size leaves its sums of squares in halves.
+bool m_gemm_writes_halves(int M, int N);
 hipError_t m_gemm_big(const void* Xp, const void* Wp, int M, int N, int K, BigEpi epi, hipStream_t st);
 hipError_t m_rmsnorm_x32(const float* h, const float* gain, float eps, void* out, int M, int d, const int* row_index,
                          hipStream_t st);

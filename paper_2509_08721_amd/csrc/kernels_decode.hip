@@ -39,11 +39,6 @@ __device__ __forceinline__ f32x4 mfma16(const Frag16& a, const Frag16& b, f32x4 
 }
 __device__ __forceinline__ float silu_f(float x) { return x / (1.0f + __expf(-x)); }
 
-// Rounding written out: left to the compiler, which square is rounded on its own differs from kernel to kernel.
-__device__ __forceinline__ float sum_squares4(const float4& s) {
-  return __builtin_fmaf(s.w, s.w, __builtin_fmaf(s.z, s.z, __builtin_fmaf(s.x, s.x, s.y * s.y)));
-}
-
 // uint4 index of the chunk that holds x[tok][k .. k+7] (k a multiple of 8) in X16 order.
 __host__ __device__ __forceinline__ size_t x16_chunk(int tok, int k, int KS) {
   return ((((size_t)(tok >> 6) * KS + (k >> 5)) * 4 + ((tok >> 4) & 3)) * 64) + (tok & 15) + 16 * ((k >> 3) & 3);

@@ -9,6 +9,7 @@
 // log-prob tolerances (with bf16 activations the rounding points alone put the 1.5B-class model's
 // logits 6e-2 away from the definition).
 #include "common.h"
+#include <algorithm>
 #include <type_traits>
 
 namespace sapo {
@@ -282,10 +283,29 @@ struct TileLoop {
 };
 
 // 1 / rms of the wave's tokens of a tile from the parts of their sums of squares (at most 16 parts, row stride a multiple
-// of 4): requested behind the first stages, so that they ride on the same latency
+// of 4; halves: each part as two): requested behind the first stages, so that they ride on the same latency
 template <int TJ>
-__device__ __forceinline__ void row_scales(const float* __restrict__ ssq, int parts, float norm_dim, float eps, int tok0, int M,
-                                           float (&scale)[TJ]) {
+__device__ __forceinline__ void row_scales(const float* __restrict__ ssq, int parts, bool halves, float norm_dim, float eps, int tok0,
+                                           int M, float (&scale)[TJ]) {
+  if (halves) {
+    const int ps = (2 * parts + 3) & ~3;
+#pragma unroll
+    for (int tj = 0; tj < TJ; ++tj) {
+      const int tok = min(tok0 + tj * 32, M - 1);
+      float4 half[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        half[i] = (4 * i < ps) ? *(const float4*)(ssq + (size_t)tok * ps + 4 * i) : make_float4(0.f, 0.f, 0.f, 0.f);
+      float ss = 0.f;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        ss += (2 * i + 0 < parts) ? half[i].x + half[i].y : 0.f;
+        ss += (2 * i + 1 < parts) ? half[i].z + half[i].w : 0.f;
+      }
+      scale[tj] = rsqrtf(ss / norm_dim + eps);
+    }
+    return;
+  }
   const int ps = (parts + 3) & ~3;
   float4 part[TJ][4];
 #pragma unroll
@@ -348,7 +368,7 @@ __global__ void __launch_bounds__(NW * 64, TJ == 2 ? 2 : 3) k_gemm_big(const uin
       return;
     }
     loop.begin();
-    if (ep.ssq_in) row_scales<TJ>(ep.ssq_in, ep.ssq_parts, ep.norm_dim, ep.eps, tok0, M, row_scale);
+    if (ep.ssq_in) row_scales<TJ>(ep.ssq_in, ep.ssq_parts, ep.ssq_halves, ep.norm_dim, ep.eps, tok0, M, row_scale);
     loop.run(smem, acc);
   }
   const int fcol = bx * 128 + (lane >> 5) * 4;   // + fi * 32 + 8 r: this lane's four features of block (fi, r)
@@ -453,7 +473,7 @@ __global__ void __launch_bounds__(NW * 64, TJ == 2 ? 2 : 3) k_gemm_big(const uin
                                          acc[fi][tj][4 * r + 2] + w.z, acc[fi][tj][4 * r + 3] + w.w);
             *q = v;
             if (prod && (full || tok < M)) {
-              ssq += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+              ssq += sum_squares4(v);
               const float4 gn = *(const float4*)(G + fi * 32 + 8 * r + (lane >> 5) * 4);
               f16x4 hv;
               hv[0] = from_f32<f16>(v.x * gn.x); hv[1] = from_f32<f16>(v.y * gn.y);
@@ -492,40 +512,196 @@ __global__ void __launch_bounds__(NW * 64, TJ == 2 ? 2 : 3) k_gemm_big(const uin
   }
 }
 // ---------------------------------------------------------------------------------------
+// Few tokens (prompts of a few hundred tokens, small scoring calls): the tiles above leave most of the chip idle (at 128
+// tokens the 0.5B down projection was 7 workgroups of 2.5 MB, 44 us whatever the number of tokens), and every output's
+// sum has to stay one chain of MFMAs over K.  Here a wave owns 32 tokens x NB 32-feature blocks, a workgroup WM x WN such
+// waves, and all four waves fetch: both operands go through an LDS ring of D stages of 64 k, 60 .. 144 KiB of requests in
+// flight.  Wave w fetches k step w of every stage.  Sums, epilogues and bits are those of the kernels above.  0.5B, one
+// sequence of 128 tokens: down 46 -> 24 us, O 13 -> 8, QKV 19 -> 8, gate/up 17 -> 11 (a scoring call 2.64 -> 1.53 ms); 1024
+// tokens 3.77 -> 2.95 ms.  What is left is the chain itself: 0.22 us per stage of 64 k (wait, barrier, LDS, MFMAs).
+// ---------------------------------------------------------------------------------------
+template <int WM, int WN, int NB, int D>
+struct MidLoop {
+  static constexpr int FX = WM, F = WM + WN * NB;   // token blocks, and fragments of a k step = requests per wave and stage
+  static_assert(WM * WN <= 4 && F * (D - 2) <= 63, "four waves; the counter of outstanding requests");
+  static constexpr int kBytes = D * 4 * F * 1024;
+  const char* base[F];
+  unsigned off, ring;
+  int nst;
+  __device__ __forceinline__ void begin(const uint4* Xp, const uint4* Wp, int n_tblk, int KS, int tblk0, int fblk0, const uint4* smem) {
+    const int wave = wave_index(threadIdx.x);
+#pragma unroll
+    for (int f = 0; f < F; ++f)
+      base[f] = (const char*)(f < FX ? Xp + ((size_t)min(tblk0 + f, n_tblk - 1) * KS + wave) * 64
+                                     : Wp + ((size_t)(fblk0 + f - FX) * KS + wave) * 64);
+    off = (threadIdx.x & 63) * 16;
+    ring = __builtin_amdgcn_readfirstlane(lds_addr(smem)) + (unsigned)(wave * F * 1024);
+    nst = KS >> 2;
+#pragma unroll
+    for (int p = 0; p < D - 1; ++p)
+      if (p < nst) request(p);
+  }
+  __device__ __forceinline__ void request(int st) {
+    const unsigned dst = ring + (unsigned)((st % D) * (4 * F * 1024));
+#pragma unroll
+    for (int f = 0; f < F; ++f) dma16(base[f] + (size_t)st * 4096, off, dst + f * 1024u);
+  }
+  __device__ __forceinline__ void arrive(int st) {
+    if (st + D - 2 < nst) wait_vmcnt<F * (D - 2)>(); else wait_vmcnt<0>();   // this wave's part of stage st has landed ...
+    wg_barrier();                                                           // ... everybody's has; stage st - 1 is consumed
+    if (st + D - 1 < nst) request(st + D - 1);
+  }
+  // a wave without a place in the tile only fetches
+  __device__ __forceinline__ void fetch_only() {
+    for (int st = 0; st < nst; ++st) arrive(st);
+  }
+  // wm, wn: this wave's place
+  __device__ __forceinline__ void run(const uint4* smem, int wm, int wn, f32x16 (&acc)[NB][1]) {
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[b][0][v] = 0.f;
+    const uint4* mine = smem + (threadIdx.x & 63);
+    int slot = 0;
+    for (int st = 0; st < nst; ++st) {
+      arrive(st);
+      const uint4* buf = mine + (size_t)slot * (4 * F * 64);
+      slot = slot + 1 == D ? 0 : slot + 1;
+      Frag x[4], w[4][NB];
+#pragma unroll
+      for (int h = 0; h < 4; ++h) {
+        x[h].u = buf[(h * F + wm) * 64];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) w[h][b].u = buf[(h * F + FX + wn * NB + b) * 64];
+      }
+      __builtin_amdgcn_sched_barrier(0);   // all of a stage's reads are on their way before the first MFMA
+#pragma unroll
+      for (int h = 0; h < 4; ++h)
+#pragma unroll
+        for (int b = 0; b < NB; ++b) acc[b][0] = mfma32(w[h][b], x[h], acc[b][0]);
+    }
+  }
+};
+
+// BIG_SWIGLU and BIG_ADD_F32 on tiles of 32 WM tokens x 64 WN features
+template <int WM, int WN, int D>
+__global__ void __launch_bounds__(256, 2) k_gemm_mid(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, int M, int N, int K,
+                                                  BigEpi ep) {
+  extern __shared__ uint4 smem[];
+  int bx, by;
+  if (!big_raster(N / (64 * WN), (M + 32 * WM - 1) / (32 * WM), bx, by)) return;
+  const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63;
+  const bool live = wave < WM * WN;
+  const int wm = live ? wave / WN : 0, wn = live ? wave % WN : 0;
+  const int n0 = (bx * WN + wn) * 64;                    // the wave's first feature
+  const int row0 = (by * WM + wm) * 32, tok = row0 + (lane & 31);
+  f32x16 acc[2][1];
+  float row_scale[1] = {1.f};
+  {
+    MidLoop<WM, WN, 2, D> loop;
+    loop.begin(Xp, Wp, (M + 31) >> 5, K >> 4, by * WM, bx * WN * 2, smem);
+    if (ep.ssq_in) row_scales<1>(ep.ssq_in, ep.ssq_parts, ep.ssq_halves, ep.norm_dim, ep.eps, tok, M, row_scale);
+    if (live) loop.run(smem, wm, wn, acc);
+    else loop.fetch_only();
+  }
+  if (!live) {
+    if (ep.mode != BIG_SWIGLU) wg_barrier();
+    return;
+  }
+  if (ep.ssq_in) {
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[b][0][v] *= row_scale[0];
+  }
+  if (ep.mode == BIG_SWIGLU) {
+    if (tok >= M) return;
+    const int F = N >> 1, f0 = (n0 >> 1) + (lane >> 5) * 4;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      f16x4 o;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) o[j] = from_f32<f16>(silu_f(acc[0][0][4 * r + j]) * acc[1][0][4 * r + j]);
+      *(f16x4*)(ep.out_act + x32_chunk(tok, f0 + 8 * r, F >> 4) * 8 + ((lane >> 5) << 2)) = o;
+    }
+    return;
+  }
+  // BIG_ADD_F32: one pass of k_gemm_big's residual update (32 tokens x 64 features in row layout through LDS)
+  wg_barrier();   // every wave has read its last stage: the ring is free
+  if (row0 >= M) return;
+  constexpr int RS = 68;
+  float* R = (float*)smem + wave * (32 * RS);
+  const int rt = lane >> 4, rc = (lane & 15) * 4;
+  auto wave_sync = [] {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  };
+  float4 io[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i)   // rows past the end: the last one again, not stored
+    io[i] = *(const float4*)(ep.out_f32 + (size_t)min(row0 + 4 * i + rt, M - 1) * ep.ldc + n0 + rc);
+  const bool prod = ep.gain_next != nullptr;
+  float4 gn[2][4];
+  if (prod) {
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) gn[b][r] = *(const float4*)(ep.gain_next + n0 + b * 32 + 8 * r + (lane >> 5) * 4);
+  }
+#pragma unroll
+  for (int i = 0; i < 8; ++i) *(float4*)(R + (4 * i + rt) * RS + rc) = io[i];
+  wave_sync();
+  float ssq = 0.f;
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      float4* q = (float4*)(R + (lane & 31) * RS + b * 32 + 8 * r + (lane >> 5) * 4);
+      const float4 w = *q;
+      const float4 v = make_float4(acc[b][0][4 * r] + w.x, acc[b][0][4 * r + 1] + w.y, acc[b][0][4 * r + 2] + w.z,
+                                   acc[b][0][4 * r + 3] + w.w);
+      *q = v;
+      if (prod && tok < M) {
+        ssq += sum_squares4(v);
+        f16x4 hv;
+        hv[0] = from_f32<f16>(v.x * gn[b][r].x); hv[1] = from_f32<f16>(v.y * gn[b][r].y);
+        hv[2] = from_f32<f16>(v.z * gn[b][r].z); hv[3] = from_f32<f16>(v.w * gn[b][r].w);
+        *(f16x4*)(ep.xn_out + x32_chunk(tok, n0 + (lane >> 5) * 4 + b * 32 + 8 * r, N >> 4) * 8 + ((lane >> 5) << 2)) = hv;
+      }
+    }
+  ssq += __shfl_xor(ssq, 32, 64);
+  if (prod && lane < 32 && tok < M) ep.ssq_out[(size_t)tok * (((N >> 6) + 3) & ~3) + (n0 >> 6)] = ssq;
+  wave_sync();
+#pragma unroll
+  for (int i = 0; i < 8; ++i) io[i] = *(const float4*)(R + (4 * i + rt) * RS + rc);
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+    if (row0 + 4 * i + rt < M) *(float4*)(ep.out_f32 + (size_t)(row0 + 4 * i + rt) * ep.ldc + n0 + rc) = io[i];
+}
+
+// ---------------------------------------------------------------------------------------
 // QKV projection with the rotary embedding and the KV append in its epilogue (token-parallel path): the
 // fp32 q/k/v rows never exist in memory.  Same main loop as k_gemm_big.  A 128-feature tile is two heads of 64 (blocks
 // 0, 1 and 2, 3) or one head of 128; the rotation partner (i + 32, resp. i + 64) sits in the same lane, one or two
 // accumulator blocks on.  q goes out as half row-major [M, Hq hd] (flash attention's operand), rotated k and v go to the
 // row's cache page.
 // ---------------------------------------------------------------------------------------
-template <int HD>
-__global__ void __launch_bounds__(256, 2) k_gemm_qkv_rope(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, int M,
-                                                          int N, int K, QkvEpi ep) {
-  constexpr int TJ = 2, H = 4, NB = HD / 32, NH = 128 / HD;   // accumulator blocks of a head, heads of a tile
-  extern __shared__ uint4 smem[];
-  int bx, by;
-  if (!big_raster(N >> 7, (M + 255) >> 8, bx, by)) return;
-  f32x16 acc[4][TJ];
-  const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63;
-  const int tok0 = by * 256 + wave * 64 + (lane & 31);
-  float row_scale[TJ] = {1.f, 1.f};
-  {
-    TileLoop<TJ, H> loop;
-    loop.tokens(Xp, (M + 31) >> 5, K >> 4, by * 8, 0);
-    loop.features(Wp, K >> 4, bx * 4, 0, K / (16 * H), smem);
-    loop.begin();
-    if (ep.ssq_in) row_scales<TJ>(ep.ssq_in, ep.ssq_parts, ep.norm_dim, ep.eps, tok0, M, row_scale);
-    loop.run(smem, acc);
-  }
+// The epilogue of a wave's tile of NH heads, the first of them head0.
+template <int HD, int NH, int TJ>
+__device__ __forceinline__ void qkv_epilogue(f32x16 (&acc)[NH * (HD / 32)][TJ], const QkvEpi& ep, int head0, int tok0, int M,
+                                             const float (&row_scale)[TJ]) {
+  constexpr int NB = HD / 32;   // accumulator blocks of a head
+  const int lane = threadIdx.x & 63;
   const int hq = ep.n_q_heads, hkv = ep.kv.n_kv_heads;
   const int half_sel = lane >> 5;
   // row scale and bias first: what is rotated is the finished projection
 #pragma unroll
-  for (int fi = 0; fi < 4; ++fi) {
+  for (int fi = 0; fi < NH * NB; ++fi) {
     float4 bb[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r)
-      bb[r] = ep.bias ? *(const float4*)(ep.bias + bx * 128 + fi * 32 + half_sel * 4 + 8 * r) : make_float4(0.f, 0.f, 0.f, 0.f);
+      bb[r] = ep.bias ? *(const float4*)(ep.bias + head0 * HD + fi * 32 + half_sel * 4 + 8 * r) : make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
     for (int tj = 0; tj < TJ; ++tj)
 #pragma unroll
@@ -550,7 +726,7 @@ __global__ void __launch_bounds__(256, 2) k_gemm_qkv_rope(const uint4* __restric
     keeps[tj] = ep.rm.keeps_kv(tokc);
     page_of[tj] = ep.kv.page_table[(size_t)seq * ep.kv.pages_per_seq + pos_of[tj] / kPageTokens];
   }
-  const bool rotates = bx * NH < hq + hkv;   // else the tile is all V
+  const bool rotates = head0 < hq + hkv;   // else the tile is all V
 #pragma unroll
   for (int tj = 0; tj < TJ; ++tj) {
     const int tok = tok0 + tj * 32;
@@ -569,7 +745,7 @@ __global__ void __launch_bounds__(256, 2) k_gemm_qkv_rope(const uint4* __restric
     if (tok >= M) continue;
 #pragma unroll
     for (int hh = 0; hh < NH; ++hh) {
-      const int head = bx * NH + hh;
+      const int head = head0 + hh;
       if (head >= hq && !keeps[tj]) continue;
       if (head >= hq + hkv) {
         const int vh = head - hq - hkv;
@@ -597,8 +773,8 @@ __global__ void __launch_bounds__(256, 2) k_gemm_qkv_rope(const uint4* __restric
           for (int j = 0; j < 4; ++j) {
             const float x1 = acc[hh * NB + b][tj][4 * r + j], x2 = acc[hh * NB + b + NB / 2][tj][4 * r + j];
             const float co = c[2 * j], sn = c[2 * j + 1];
-            o1[r][j] = from_f32<f16>(x1 * co - x2 * sn);
-            o2[r][j] = from_f32<f16>(x2 * co + x1 * sn);
+            o1[r][j] = from_f32<f16>(rot_first(x1, x2, co, sn));
+            o2[r][j] = from_f32<f16>(rot_second(x1, x2, co, sn));
           }
         }
         if (b + 1 < NB / 2) request(b + 1);
@@ -611,12 +787,120 @@ __global__ void __launch_bounds__(256, 2) k_gemm_qkv_rope(const uint4* __restric
     }
   }
 }
+template <int HD>
+__global__ void __launch_bounds__(256, 2) k_gemm_qkv_rope(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, int M,
+                                                          int N, int K, QkvEpi ep) {
+  constexpr int TJ = 2, H = 4, NH = 128 / HD;   // heads of a tile
+  extern __shared__ uint4 smem[];
+  int bx, by;
+  if (!big_raster(N >> 7, (M + 255) >> 8, bx, by)) return;
+  f32x16 acc[4][TJ];
+  const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63;
+  const int tok0 = by * 256 + wave * 64 + (lane & 31);
+  float row_scale[TJ] = {1.f, 1.f};
+  {
+    TileLoop<TJ, H> loop;
+    loop.tokens(Xp, (M + 31) >> 5, K >> 4, by * 8, 0);
+    loop.features(Wp, K >> 4, bx * 4, 0, K / (16 * H), smem);
+    loop.begin();
+    if (ep.ssq_in) row_scales<TJ>(ep.ssq_in, ep.ssq_parts, ep.ssq_halves, ep.norm_dim, ep.eps, tok0, M, row_scale);
+    loop.run(smem, acc);
+  }
+  qkv_epilogue<HD, NH, TJ>(acc, ep, bx * NH, tok0, M, row_scale);
+}
 
+// The same for few tokens: 32 WM tokens x one head per workgroup
+template <int HD, int WM, int D>
+__global__ void __launch_bounds__(256, 2) k_gemm_qkv_mid(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, int M, int N, int K,
+                                                      QkvEpi ep) {
+  constexpr int NB = HD / 32;
+  extern __shared__ uint4 smem[];
+  int bx, by;
+  if (!big_raster(N / HD, (M + 32 * WM - 1) / (32 * WM), bx, by)) return;
+  const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63;
+  const bool live = wave < WM;
+  const int wm = live ? wave : 0, tok = (by * WM + wm) * 32 + (lane & 31);
+  f32x16 acc[NB][1];
+  float row_scale[1] = {1.f};
+  MidLoop<WM, 1, NB, D> loop;
+  loop.begin(Xp, Wp, (M + 31) >> 5, K >> 4, by * WM, bx * NB, smem);
+  if (ep.ssq_in) row_scales<1>(ep.ssq_in, ep.ssq_parts, ep.ssq_halves, ep.norm_dim, ep.eps, tok, M, row_scale);
+  if (!live) {
+    loop.fetch_only();
+    return;
+  }
+  loop.run(smem, wm, 0, acc);
+  qkv_epilogue<HD, 1, 1>(acc, ep, bx, tok, M, row_scale);
+}
+
+static int n_compute_units() {
+  static int n_cu = 0;
+  if (n_cu == 0) {
+    int dev = 0, n = 0;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+      n = 256;
+    n_cu = n;
+  }
+  return n_cu;
+}
+// Tiles for few tokens.  A workgroup's time is what it has to take in, so the tile is the one whose fullest compute unit
+// takes in least: workgroups per unit x (tokens + features) of a tile; the large tiles' fetch (two stages ahead) counts
+// half as much again.  deep: one workgroup per unit, the whole LDS as its ring; otherwise two share it.
+enum { MID_FFN, MID_QKV64, MID_QKV128 };
+struct MidPick { int tile; bool deep; };   // tile: 0 = none of them, 1 = 32, 2 = 64 tokens x one wave's features, 3 = 64 x 128
+static MidPick pick_mid(int M, int N, int what) {
+  const int cu = n_compute_units(), nb = what == MID_QKV128 ? 128 : 64;
+  auto groups = [&](int tm, int tn) { return (long)((M + tm - 1) / tm) * ((N + tn - 1) / tn); };
+  auto load = [&](int tm, int tn, double weight) { return (double)((groups(tm, tn) + cu - 1) / cu) * (tm + tn) * weight; };
+  MidPick best{0, true};
+  if (getenv("SAPO_BIG_TILE")) return best;   // one of the large tiles is forced (measurement, tests)
+  double least = std::min(load(256, 128, 1.5), what == MID_FFN ? load(128, 128, 1.5) : 1e30);
+  const int tm[4] = {0, 32, 64, 64}, tn[4] = {0, nb, nb, 128};
+  for (int t = 1; t <= (what == MID_FFN ? 3 : 2); ++t) {
+    const long g = groups(tm[t], tn[t]);
+    if (g > 2 * cu) continue;
+    const double l = load(tm[t], tn[t], 1.0);
+    if (l < least) { least = l; best.tile = t; best.deep = g <= cu; }
+  }
+  return best;
+}
+template <typename Kernel, typename Epi>
+static hipError_t launch_mid(Kernel kernel, int lds, bool& attr_done, int grid, const uint4* X, const uint4* W, int M, int N, int K,
+                             const Epi& epi, hipStream_t st) {
+  if (!attr_done) {
+    const hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return e;
+    attr_done = true;
+  }
+  return launch(KID_GEMM_BIG, kernel, dim3(grid), dim3(256), lds, st, X, W, M, N, K, epi);
+}
+template <int WM, int WN, int D>
+static hipError_t launch_ffn_mid(const uint4* X, const uint4* W, int M, int N, int K, const BigEpi& epi, hipStream_t st) {
+  static bool attr_done = false;
+  static_assert(MidLoop<WM, WN, 2, D>::kBytes >= WM * WN * 32 * 68 * 4, "the residual update's row areas lie in the ring");
+  return launch_mid(k_gemm_mid<WM, WN, D>, MidLoop<WM, WN, 2, D>::kBytes, attr_done, big_grid(N / (64 * WN), (M + 32 * WM - 1) / (32 * WM)),
+                    X, W, M, N, K, epi, st);
+}
+template <int HD, int WM, int D>
+static hipError_t launch_qkv_mid(const uint4* X, const uint4* W, int M, int N, int K, const QkvEpi& epi, hipStream_t st) {
+  static bool attr_done = false;
+  return launch_mid(k_gemm_qkv_mid<HD, WM, D>, MidLoop<WM, 1, HD / 32, D>::kBytes, attr_done, big_grid(N / HD, (M + 32 * WM - 1) / (32 * WM)),
+                    X, W, M, N, K, epi, st);
+}
+bool m_gemm_writes_halves(int M, int N) { return pick_mid(M, N, MID_FFN).tile != 0; }
 hipError_t m_gemm_qkv_rope(const void* Xp, const void* Wp, int M, int N, int K, const QkvEpi& epi, hipStream_t st) {
   if (M == 0) return hipSuccess;
   const int hd = epi.kv.head_dim;
   if (N % 128 != 0 || K % 64 != 0 || (hd != 64 && hd != 128) || N != (epi.n_q_heads + 2 * epi.kv.n_kv_heads) * hd)
     return hipErrorInvalidValue;
+  {
+    const MidPick m = pick_mid(M, N, hd == 64 ? MID_QKV64 : MID_QKV128);
+    const uint4 *X = (const uint4*)Xp, *W = (const uint4*)Wp;
+    if (hd == 64 && m.tile == 1) return m.deep ? launch_qkv_mid<64, 1, 10>(X, W, M, N, K, epi, st) : launch_qkv_mid<64, 1, 5>(X, W, M, N, K, epi, st);
+    if (hd == 64 && m.tile == 2) return m.deep ? launch_qkv_mid<64, 2, 8>(X, W, M, N, K, epi, st) : launch_qkv_mid<64, 2, 4>(X, W, M, N, K, epi, st);
+    if (hd == 128 && m.tile == 1) return m.deep ? launch_qkv_mid<128, 1, 7>(X, W, M, N, K, epi, st) : launch_qkv_mid<128, 1, 4>(X, W, M, N, K, epi, st);
+    if (hd == 128 && m.tile == 2) return m.deep ? launch_qkv_mid<128, 2, 6>(X, W, M, N, K, epi, st) : launch_qkv_mid<128, 2, 3>(X, W, M, N, K, epi, st);
+  }
   static bool attr_done = false;
   if (!attr_done) {
     hipError_t e = hipFuncSetAttribute((const void*)k_gemm_qkv_rope<64>, hipFuncAttributeMaxDynamicSharedMemorySize, kBigLds);
@@ -639,16 +923,6 @@ hipError_t m_gemm_qkv_rope(const void* Xp, const void* Wp, int M, int N, int K, 
 // 70 us, the prompt's small launches 70 -> 58 us.  With one round more - 64 x 768: 4 against 3 - the down projection
 // lost 14 %, so that case keeps the large tile).  SAPO_BIG_TILE=128 / 256 in the environment forces one or the
 // other (measurement).
-static int n_compute_units() {
-  static int n_cu = 0;
-  if (n_cu == 0) {
-    int dev = 0, n = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-      n = 256;
-    n_cu = n;
-  }
-  return n_cu;
-}
 static bool big_prefers_small_tiles(int NX, int M) {
   const int n_cu = n_compute_units();
   const char* e = getenv("SAPO_BIG_TILE");   // read per call, so that a test can switch it
@@ -692,6 +966,13 @@ hipError_t m_gemm_big(const void* Xp, const void* Wp, int M, int N, int K, BigEp
     if (N / 128 * ((M + 127) / 128) <= n_compute_units())
       return launch_big<1, 4>(Xp, Wp, M, N, K, epi, big_grid(N / 128, (M + 127) / 128), st);
     return launch_big<1, 4, 8>(Xp, Wp, M, N, K, epi, big_grid(N / 128, 1), st);
+  }
+  if (epi.mode != BIG_STORE_F32 && !epi.decode) {
+    const MidPick m = pick_mid(M, N, MID_FFN);
+    const uint4 *X = (const uint4*)Xp, *W = (const uint4*)Wp;
+    if (m.tile == 1) return m.deep ? launch_ffn_mid<1, 1, 10>(X, W, M, N, K, epi, st) : launch_ffn_mid<1, 1, 5>(X, W, M, N, K, epi, st);
+    if (m.tile == 2) return m.deep ? launch_ffn_mid<2, 1, 8>(X, W, M, N, K, epi, st) : launch_ffn_mid<2, 1, 4>(X, W, M, N, K, epi, st);
+    if (m.tile == 3) return m.deep ? launch_ffn_mid<2, 2, 6>(X, W, M, N, K, epi, st) : launch_ffn_mid<2, 2, 3>(X, W, M, N, K, epi, st);
   }
   if (big_prefers_small_tiles(N / 128, M)) return launch_big<1, 4>(Xp, Wp, M, N, K, epi, big_grid(N / 128, (M + 127) / 128), st);
   return launch_big<2, 4>(Xp, Wp, M, N, K, epi, big_grid(N / 128, (M + 255) / 256), st);
@@ -740,29 +1021,35 @@ hipError_t m_rmsnorm_x32(const float* h, const float* gain, float eps, void* out
 
 // ---------------------------------------------------------------------------------------
 // LM head for scoring: log-softmax + target gather without materialising logits.
-// Rastered like the GEMM over (256-row tiles) x (groups of kScoreGroup 128-feature tiles): a workgroup
+// Rastered like the GEMM over (256-row tiles) x (groups of 128-feature tiles): a workgroup
 // walks the tiles of its group for its 256 rows keeping a running (max, sum exp) per row, and the
 // one lane that sees a row's target id writes the target logit.  A second kernel merges the groups
 // in a fixed order.  partials: [n_groups][max_rows][2], then ztarget [max_rows].
 // ---------------------------------------------------------------------------------------
-constexpr int kScoreGroup = 16;
-static int score_groups(int V) { return (V / 128 + kScoreGroup - 1) / kScoreGroup; }
-size_t m_lmhead_score_partial_floats(int max_rows, int V) { return (size_t)max_rows * (2 * score_groups(V) + 1); }
+// 128-feature tiles of a group: 16, fewer when that leaves compute units idle (about half of max_rows are scored; with one
+// 256-row tile 16 would be 75 workgroups, 223 us whatever the number of rows)
+static int score_group(int max_rows, int V) {
+  int g = 16;
+  while (g > 1 && (long)((V / 128 + g - 1) / g) * ((max_rows / 2 + 255) / 256) < 512) g >>= 1;
+  return g;
+}
+static int score_groups(int max_rows, int V) { const int g = score_group(max_rows, V); return (V / 128 + g - 1) / g; }
+size_t m_lmhead_score_partial_floats(int max_rows, int V) { return (size_t)max_rows * (2 * score_groups(max_rows, V) + 1); }
 
 __global__ void __launch_bounds__(256, 2) k_lmhead_score(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp,
                                                          int max_rows, const int* __restrict__ n_rows_dev, int V, int K,
                                                          const int* __restrict__ row_seq_pos,
-                                                         const int32_t* __restrict__ tokens, int T,
+                                                         const int32_t* __restrict__ tokens, int T, int group,
                                                          float* __restrict__ partials) {
   constexpr int TJ = 2, H = 4;
   extern __shared__ uint4 smem[];
   const int n_rows = *n_rows_dev;
   const int n_ft = V >> 7;
-  const int n_groups = (n_ft + kScoreGroup - 1) / kScoreGroup;
+  const int n_groups = (n_ft + group - 1) / group;
   int bx, by;
   if (!big_raster(n_groups, (max_rows + 255) >> 8, bx, by)) return;
   if (by * 256 >= n_rows) return;
-  const int ft_begin = bx * kScoreGroup, ft_end = min(n_ft, ft_begin + kScoreGroup);
+  const int ft_begin = bx * group, ft_end = min(n_ft, ft_begin + group);
   const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63;
   const int row0 = by * 256 + wave * 64 + (lane & 31);
   LseAcc lse[TJ];
@@ -822,16 +1109,20 @@ __global__ void __launch_bounds__(256, 2) k_lmhead_score(const uint4* __restrict
   }
 }
 
-__global__ void k_lmhead_score_merge(const float* __restrict__ partials, int max_rows, int n_groups,
-                                     const int* __restrict__ n_rows_dev, const int* __restrict__ row_seq_pos, int T,
-                                     float* __restrict__ out_logprobs) {
-  const int row = blockIdx.x * blockDim.x + threadIdx.x;
+// A wave per row: lane l merges the groups l, l + 64, ... in order, then the lanes pairwise.
+__global__ void __launch_bounds__(256) k_lmhead_score_merge(const float* __restrict__ partials, int max_rows, int n_groups,
+                                                            const int* __restrict__ n_rows_dev, const int* __restrict__ row_seq_pos,
+                                                            int T, float* __restrict__ out_logprobs) {
+  const int row = blockIdx.x * 4 + wave_index(threadIdx.x), lane = threadIdx.x & 63;
   if (row >= *n_rows_dev) return;
   LseAcc a; a.init();
-  for (int s = 0; s < n_groups; ++s) {
+  for (int s = lane; s < n_groups; s += 64) {
     const float* p = partials + ((size_t)s * max_rows + row) * 2;
     a.merge(p[0], p[1]);
   }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) a.merge(__shfl_xor(a.m, o, 64), __shfl_xor(a.l, o, 64));
+  if (lane != 0) return;
   const float zt = partials[(size_t)max_rows * 2 * n_groups + row];
   out_logprobs[(size_t)row_seq_pos[2 * row] * T + row_seq_pos[2 * row + 1]] = zt - (a.m + logf(a.l));
 }
@@ -847,12 +1138,12 @@ hipError_t m_lmhead_score(const void* Xp, const void* Wp, int max_rows, const in
     if (e != hipSuccess) return e;
     attr_done = true;
   }
-  const int n_groups = score_groups(V);
+  const int group = score_group(max_rows, V), n_groups = score_groups(max_rows, V);
   const hipError_t e = launch(KID_LMHEAD_SCORE, k_lmhead_score, dim3(big_grid(n_groups, (max_rows + 255) / 256)), dim3(256),
                               kBigLds, st, (const uint4*)Xp, (const uint4*)Wp, max_rows, n_rows_dev, V, K, row_seq_pos, tokens,
-                              T, partials);
+                              T, group, partials);
   if (e != hipSuccess) return e;
-  return launch(KID_LMHEAD_SCORE_MERGE, k_lmhead_score_merge, dim3((max_rows + 255) / 256), dim3(256), 0, st, partials,
+  return launch(KID_LMHEAD_SCORE_MERGE, k_lmhead_score_merge, dim3((max_rows + 3) / 4), dim3(256), 0, st, partials,
                 max_rows, n_groups, n_rows_dev, row_seq_pos, T, out_logprobs);
 }
 
@@ -1098,16 +1389,23 @@ hipError_t m_flash_attention(const void* q, RowMap rm, KVCache kv, void* out, in
   if (n_seq == 0) return hipSuccess;
   const int rep = n_q_heads / kv.n_kv_heads;
   const int nqb = (rm.T + 63) / 64;
+  // Query heads per wave.  4 at head dim 64 (2 at 128): a 7-head group goes to two workgroups (4 + 3 heads): two waves per
+  // SIMD, which hide the softmax arithmetic, pay for the second read of K / V.  With few sequences a wave's walk over the
+  // keys is what the launch takes, and fewer heads shorten it: the most that still leave a workgroup for every compute unit.
+  auto go = [&](auto kernel, int hpw) {
+    return launch(KID_FLASH_ATTN, kernel, dim3(nqb, n_seq * kv.n_kv_heads, (rep + hpw - 1) / hpw), dim3(256), 0, st, (const f16*)q, rm,
+                  kv, (f16*)out, n_q_heads);
+  };
+  auto groups = [&](int hpw) { return (long)nqb * n_seq * kv.n_kv_heads * ((rep + hpw - 1) / hpw); };
+  const long cu = n_compute_units();
   if (kv.head_dim == 64) {
-    constexpr int HPW = 4;   // a 7-head group goes to two workgroups (4 + 3 heads): two waves per SIMD, which hide
-                             // the softmax arithmetic, pay for the second read of K / V (2 heads each: slower again)
-    dim3 grid(nqb, n_seq * kv.n_kv_heads, (rep + HPW - 1) / HPW);
-    return launch(KID_FLASH_ATTN, k_flash_attention<64, HPW>, grid, dim3(256), 0, st, (const f16*)q, rm, kv, (f16*)out, n_q_heads);
+    if (groups(4) >= cu) return go(k_flash_attention<64, 4>, 4);
+    if (groups(2) >= cu) return go(k_flash_attention<64, 2>, 2);
+    return go(k_flash_attention<64, 1>, 1);
   }
   if (kv.head_dim == 128) {
-    constexpr int HPW = 2;
-    dim3 grid(nqb, n_seq * kv.n_kv_heads, (rep + HPW - 1) / HPW);
-    return launch(KID_FLASH_ATTN, k_flash_attention<128, HPW>, grid, dim3(256), 0, st, (const f16*)q, rm, kv, (f16*)out, n_q_heads);
+    if (groups(2) >= cu) return go(k_flash_attention<128, 2>, 2);
+    return go(k_flash_attention<128, 1>, 1);
   }
   return hipErrorInvalidValue;
 }
