@@ -746,7 +746,7 @@ hipError_t x3_sum_parts(const X3Bufs& bufs, int splits, size_t n, float beta, co
 }
 // C[M, N] = beta C + op(A) op(B)^T-style product of two operands given row-wise over the same K
 hipError_t gemm_x3(const X3Op& A, const X3Op& B, float* C, const float* Cin, int ldc, float beta, const X3Bufs& bufs, hipStream_t st,
-                   const void* b_packed = nullptr) {
+                   const void* b_packed = nullptr, bool split_ok = true) {
   if (A.K != B.K || A.rows <= 0 || B.rows <= 0 || A.K <= 0) return hipErrorInvalidValue;
   hipError_t e;
   if ((e = x3_pack(A, bufs.a, bufs.a_cap, bufs.NP, st)) != hipSuccess) return e;
@@ -755,7 +755,7 @@ hipError_t gemm_x3(const X3Op& A, const X3Op& B, float* C, const float* Cin, int
   const u32x4_t* pa_ = (const u32x4_t*)bufs.a;
   const u32x4_t* pb_ = (const u32x4_t*)(b_packed ? b_packed : bufs.b);
   const int KB = x3_steps(A.K, bufs.NP);
-  const X3Grid g = x3_grid(bufs.NP, A.rows, B.rows, KB, x3_stage(bufs.NP), ldc == B.rows ? bufs.parts_cap : 0);
+  const X3Grid g = x3_grid(bufs.NP, A.rows, B.rows, KB, x3_stage(bufs.NP), split_ok && ldc == B.rows ? bufs.parts_cap : 0);
   float* out = g.splits > 1 ? bufs.parts : C;
   const size_t c_split = g.splits > 1 ? (size_t)A.rows * B.rows : 0;
   const float b_ = g.splits > 1 ? 0.f : beta;
@@ -851,30 +851,30 @@ __global__ void __launch_bounds__(256) k_embed_rows(const int32_t* __restrict__ 
 constexpr int kNormMaxV = 8;
 inline bool norm_rows_vectorised(int d) { return d % 4 == 0 && d <= 256 * kNormMaxV; }
 
-// xn = h * rstd * gain, rstd = 1 / sqrt(mean(h^2) + eps)
+// xn = h * rstd * gain, rstd = 1 / sqrt(mean(h^2) + eps).  Here a lane takes the values lane, lane + 64, ...: the squares are
+// added as the workgroup-per-row kernel below adds them (four chains of every fourth block of 64, reduced one by one), so
+// that rows of any width see the same rounding: with bf16 operands a last bit of rstd decides roundings downstream.
 template <int NV>
 __global__ void __launch_bounds__(256) k_rmsnorm_fwd_rows(const float* __restrict__ h, const float* __restrict__ gain, float eps,
                                                           int M, int d, float* __restrict__ xn, float* __restrict__ rstd) {
   const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63;
   const size_t m = (size_t)blockIdx.x * 4 + wave;
   if (m >= (size_t)M) return;
-  float4 x[NV];
-  float ss = 0.f;
+  float x[4 * NV], ss[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int i = 0; i < NV; ++i) {
-    const int f = 4 * (lane + 64 * i);
-    x[i] = f < d ? *(const float4*)(h + m * d + f) : make_float4(0.f, 0.f, 0.f, 0.f);
-    ss = fmaf(x[i].x, x[i].x, fmaf(x[i].y, x[i].y, fmaf(x[i].z, x[i].z, fmaf(x[i].w, x[i].w, ss))));
+  for (int i = 0; i < 4 * NV; ++i) {
+    const int f = lane + 64 * i;
+    x[i] = f < d ? h[m * d + f] : 0.f;
+    ss[i & 3] = fmaf(x[i], x[i], ss[i & 3]);
   }
-  ss = wave_reduce_sum(ss);
-  const float r = 1.0f / sqrtf(ss / (float)d + eps);
+#pragma unroll
+  for (int c = 0; c < 4; ++c) ss[c] = wave_reduce_sum(ss[c]);
+  const float r = 1.0f / sqrtf((ss[0] + ss[1] + ss[2] + ss[3]) / (float)d + eps);
   if (lane == 0) rstd[m] = r;
 #pragma unroll
-  for (int i = 0; i < NV; ++i) {
-    const int f = 4 * (lane + 64 * i);
-    if (f >= d) continue;
-    const float4 g = *(const float4*)(gain + f);
-    *(float4*)(xn + m * d + f) = make_float4(x[i].x * r * g.x, x[i].y * r * g.y, x[i].z * r * g.z, x[i].w * r * g.w);
+  for (int i = 0; i < 4 * NV; ++i) {
+    const int f = lane + 64 * i;
+    if (f < d) xn[m * d + f] = x[i] * r * gain[f];
   }
 }
 // Backward of the norm and the gain's gradient in one pass over dxn and h (in two they took 209 us per norm at 24576 rows
@@ -1998,7 +1998,9 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
   const X3Bufs xb{p.packa, p.packb, p.packa_cap, p.packb_cap, pieces, p.kparts, split_parts_floats(D)};
   auto mm_nt = [&](const float* X, int ldx, const float* W, int ldw, float* C, int ldc, int M_, int N_, int K_, float beta,
                    const float* Cin = nullptr, const void* w_packed = nullptr) {   // C = beta Cin + X W^T
-    return gemm_x3(X3Op{X, ldx, M_, K_, false}, X3Op{W, ldw, N_, K_, false}, C, Cin, ldc, beta, xb, st, w_packed);
+    // Forward products are split over K with three pieces only: the order of additions must not depend on the batch's size
+    // where operands are rounded to bf16 (a last bit decides roundings downstream, about 1e-2 of a log-prob after 24 layers).
+    return gemm_x3(X3Op{X, ldx, M_, K_, false}, X3Op{W, ldw, N_, K_, false}, C, Cin, ldc, beta, xb, st, w_packed, pieces == 3);
   };
   auto mm_nn = [&](const float* A_, int lda, const float* B_, int ldb, float* C, int ldc, int M_, int N_, int K_, float beta,
                    const void* b_packed = nullptr) {   // C = beta C + A B
