@@ -923,8 +923,6 @@ static int rollout_impl(const sapo_weights* w, const int32_t* prompts, const int
   const bool merge_steps = w->mfma;   // both fused samplers end in the merge kernel, which then advances *step
   if (merge_steps) {
     sp.arrivals = pl.step + 8;
-    HIP_CK(g_fill_i32(pl.step + 8, 0, 1, st));
-    HIP_CK(g_fill_i32((int*)pl.pctl, 0, d_decode_layers_ctl_bytes() / 4, st));
     sp.fault = &pl.pctl->fault;
   }
   // Decode attention that reads the prompt's full pages once per group of siblings (a second kind of workgroup in the
@@ -945,8 +943,13 @@ static int rollout_impl(const sapo_weights* w, const int32_t* prompts, const int
     }
   }
   const bool stopping = stop_token >= 0;
-  HIP_CK(g_fill_i32(pl.stop, stop_token, 1, st));
-  HIP_CK(g_fill_i32(pl.stop + 1, 0, (size_t)S + 1, st));
+  {
+    RolloutBegin rb{};
+    rb.step = pl.step; rb.stop = pl.stop; rb.ctl = (int*)pl.pctl; rb.n_ctl = pl.pctl ? (int)(d_decode_layers_ctl_bytes() / 4) : 0;
+    rb.S = S; rb.stop_token = stop_token; rb.seed_lo = sp.seed_lo; rb.seed_hi = sp.seed_hi; rb.temperature = temperature;
+    rb.out_tokens = out_tokens; rb.out_logprobs = out_logprobs;
+    HIP_CK(g_rollout_begin(rb, st));
+  }
   if (stopping) {   // whatever is not generated because every sequence has ended is padding already
     HIP_CK(g_fill_i32(out_tokens, stop_token, (size_t)S * max_new, st));
     HIP_CK(g_fill_f32(out_logprobs, 0.f, (size_t)S * max_new, st));
@@ -959,15 +962,6 @@ static int rollout_impl(const sapo_weights* w, const int32_t* prompts, const int
   // with a stop token the host looks, every kStopPoll steps, how many sequences have ended
   const int kStopPoll = 32;
 
-  HIP_CK(g_fill_i32(pl.step, 0, 1, st));
-  {
-    float tf = temperature;
-    int tbits;
-    memcpy(&tbits, &tf, 4);
-    HIP_CK(g_fill_i32(pl.step + 1, (int)sp.seed_lo, 1, st));
-    HIP_CK(g_fill_i32(pl.step + 2, (int)sp.seed_hi, 1, st));
-    HIP_CK(g_fill_i32(pl.step + 3, tbits, 1, st));
-  }
   if (ragged) {
     HIP_CK(hipMemcpyAsync(pl.lens, lens_host, (size_t)P * sizeof(int), hipMemcpyHostToDevice, st));
     HIP_CK(g_page_table_ragged(pl.cache.page_table, S, pl.pages_per_seq, G, pl.full_prompt_pages, pl.own_pages, P, pl.lens,
@@ -1022,12 +1016,14 @@ static int rollout_impl(const sapo_weights* w, const int32_t* prompts, const int
   };
   const char* no_graph = getenv("SAPO_NO_GRAPH");
   const bool use_graph = st != nullptr && !g_prof_on && max_new > 2 && !(no_graph && no_graph[0] == '1');
-  // One captured step per level, kept with the weights and rebuilt when a call uses other buffers or sizes.
+  // One captured step per level, kept with the weights and rebuilt when a call uses another workspace or other sizes.  (The
+  // outputs are reached through the workspace on the MFMA path: a caller that allocates them for every call does not have
+  // every call captured again.)
   auto step_graph = [&](int li, hipGraphExec_t& exec) -> int {
     sapo_weights::DecodeGraph& dg = w->dgraph[li];
-    if (!(dg.valid && dg.out_tokens == out_tokens && dg.out_logprobs == out_logprobs && dg.workspace == workspace &&
-          dg.P == P && dg.Lp == Lp && dg.G == G && dg.N == max_new && dg.ragged == ragged &&
-          dg.share_pairs == share.prefix_pairs)) {
+    const bool same_out = w->mfma || (dg.out_tokens == out_tokens && dg.out_logprobs == out_logprobs);
+    if (!(dg.valid && same_out && dg.workspace == workspace && dg.P == P && dg.Lp == Lp && dg.G == G && dg.N == max_new &&
+          dg.ragged == ragged && dg.share_pairs == share.prefix_pairs)) {
       if (li == 0) {
         drop_decode_graph(w);   // the smaller batches' graphs belong to the same call shape
       } else if (dg.valid) {

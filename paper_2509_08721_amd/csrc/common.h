@@ -203,8 +203,8 @@ struct SampleParams {
   uint32_t seed_lo, seed_hi;
   int max_new;            // row stride of out_tokens / out_logprobs
   const int* step;        // device: index of the token being sampled (0-based)
-  const uint32_t* dyn;    // device, optional: {seed_lo, seed_hi, temperature bits} overriding the fields above
-                          // (lets one captured graph serve calls that differ only in seed / temperature)
+  const uint32_t* dyn;    // device, optional: {seed_lo, seed_hi, temperature bits} and, from word 15 on, the two output
+                          // pointers, overriding the fields here (lets one captured graph serve calls that differ in these)
   int32_t* out_tokens;    // [S, max_new]
   float* out_logprobs;    // [S, max_new]
   // Stop token (optional): stop[0] = the token id that ends a sequence (< 0: none), stop[1] = number of
@@ -288,6 +288,13 @@ __device__ __forceinline__ void resolve_sample_params(SampleParams& sp) {
   }
 }
 
+__device__ __forceinline__ void resolve_outputs(SampleParams& sp) {
+  if (sp.dyn) {
+    sp.out_tokens = *(int32_t* const*)(sp.dyn + 15);
+    sp.out_logprobs = *(float* const*)(sp.dyn + 17);
+  }
+}
+
 // generic (shape-agnostic) kernels --------------------------------------------------------
 hipError_t g_embed(int dtype, const int32_t* tokens, int tok_stride, const int* step, const void* embed,
                    float* h, int M, int d, hipStream_t st);
@@ -339,6 +346,15 @@ hipError_t g_fill_i32(int* p, int v, size_t n, hipStream_t st);
 hipError_t g_count_half_at_limit(const void* buf, int rows_valid, int row_len, int x32, unsigned long long* counter,
                                  hipStream_t st);
 hipError_t g_fill_f32(float* p, float v, size_t n, hipStream_t st);
+struct RolloutBegin {
+  int* step; int* stop; int* ctl;
+  int n_ctl, S, stop_token;
+  uint32_t seed_lo, seed_hi;
+  float temperature;
+  int32_t* out_tokens;
+  float* out_logprobs;
+};
+hipError_t g_rollout_begin(const RolloutBegin& a, hipStream_t st);
 hipError_t g_incr(int* p, hipStream_t st);
 hipError_t g_masked_rows(const uint8_t* mask, int T, int s0, int ns, int* rows /*[ns*T,2]*/, int* src_rows /*[ns*T]*/,
                          int* count, hipStream_t st);

@@ -851,10 +851,22 @@ __global__ void __launch_bounds__(128) k_lmhead_merge_embed(const float* __restr
   if (threadIdx.x < 64) {
     LseAcc a; a.init();
     BestAcc b; b.init();
-    for (int w = lane; w < n_wg; w += 64) {
-      const float* p = partials + ((size_t)w * row_stride + r) * 5;
-      a.merge(p[0], p[1]);
-      b.add(p[2], p[3], ((const int*)p)[4]);
+    resolve_outputs(sp);
+    constexpr int NB = 4;   // a lane's next partials, in flight together (256 workgroups of k_lmhead_sample16: all of them)
+    for (int w0 = lane; w0 < n_wg; w0 += 64 * NB) {
+      float v[NB][5];
+#pragma unroll
+      for (int u = 0; u < NB; ++u) {
+        const float* p = partials + ((size_t)min(w0 + 64 * u, n_wg - 1) * row_stride + r) * 5;
+#pragma unroll
+        for (int k = 0; k < 5; ++k) v[u][k] = p[k];
+      }
+#pragma unroll
+      for (int u = 0; u < NB; ++u)
+        if (w0 + 64 * u < n_wg) {
+          a.merge(v[u][0], v[u][1]);
+          b.add(v[u][2], v[u][3], __float_as_int(v[u][4]));
+        }
     }
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {

@@ -58,13 +58,39 @@ hipError_t g_count_half_at_limit(const void* buf, int rows_valid, int row_len, i
                 n_chunks, rows_valid, row_len, x32, counter);
 }
 
+// 16 bytes per thread for large aligned buffers (a call's whole KV pool): 4 bytes per thread reached 2 TB/s
+__global__ void __launch_bounds__(256) k_fill_u4(uint4* __restrict__ p, uint4 v, size_t n) {
+  for (size_t i = (size_t)blockIdx.x * 1024 + threadIdx.x; i < min(n, ((size_t)blockIdx.x + 1) * 1024); i += 256) p[i] = v;
+}
 hipError_t g_fill_i32(int* p, int v, size_t n, hipStream_t st) {
   if (n == 0) return hipSuccess;
+  if (n >= 65536 && n % 4 == 0 && ((uintptr_t)p & 15) == 0)
+    return launch(KID_MISC, k_fill_u4, dim3((unsigned)((n / 4 + 1023) / 1024)), dim3(256), 0, st, (uint4*)p,
+                  make_uint4((unsigned)v, (unsigned)v, (unsigned)v, (unsigned)v), n / 4);
   return launch(KID_MISC, k_fill_i32, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, p, v, n);
 }
 hipError_t g_fill_f32(float* p, float v, size_t n, hipStream_t st) {
   if (n == 0) return hipSuccess;
   return launch(KID_MISC, k_fill_f32, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, p, v, n);
+}
+// Everything small that a rollout call starts from, in one launch: the step counter's words (step, {seed, temperature},
+// arrivals, output pointers), the control words of the persistent step, the stop token's counters and lengths.
+__global__ void __launch_bounds__(256) k_rollout_begin(RolloutBegin a) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i < a.n_ctl) a.ctl[i] = 0;
+  if (i < a.S + 1) a.stop[1 + i] = 0;
+  if (i == 0) {
+    a.stop[0] = a.stop_token;
+    a.step[0] = 0;
+    a.step[1] = (int)a.seed_lo; a.step[2] = (int)a.seed_hi; a.step[3] = __float_as_int(a.temperature);
+    a.step[8] = 0;
+    *(int32_t**)(a.step + 16) = a.out_tokens;
+    *(float**)(a.step + 18) = a.out_logprobs;
+  }
+}
+hipError_t g_rollout_begin(const RolloutBegin& a, hipStream_t st) {
+  const int n = a.n_ctl > a.S + 1 ? a.n_ctl : a.S + 1;
+  return launch(KID_MISC, k_rollout_begin, dim3((n + 255) / 256), dim3(256), 0, st, a);
 }
 hipError_t g_incr(int* p, hipStream_t st) {
   return launch(KID_MISC, k_incr, dim3(1), dim3(64), 0, st, p);
@@ -420,6 +446,7 @@ __global__ void __launch_bounds__(256) k_sample_rows(const float* __restrict__ l
   __syncthreads();
   if (threadIdx.x == 0) {
     for (int w = 1; w < 4; ++w) best.add(sm_y[w], sm_z[w], sm_id[w]);
+    resolve_outputs(sp);
     emit_token(sp, s, step, best.id, best.z - (lse.m + logf(lse.l)));
   }
 }
