@@ -544,15 +544,16 @@ hipError_t g_advantages(const float* rewards, int S, int G, float* out, hipStrea
 // The gradient needs the number of masked tokens, the loss the fp64 sum of the terms; rho and the branch decision are
 // fp32; no atomics and one fixed order of additions, so the result is reproducible.  A few hundred KB at most go through
 // these kernels: launches and dependent round trips are what they cost.
-// Up to kSurrogateOneLaunch tokens: one launch.  Block 0 sums the loss over all tokens; block b > 0 writes the
-// gradient of its 1024 tokens and counts the masked tokens of the whole set by itself (n mask bytes out of the L2, 16 at
-// a time).  Above that block 0's serial walk and the n bytes per block cost more than a second launch: the tokens are
-// summed by kLossBlocks blocks into slots, and every block of the second kernel adds the slots again (4 KB, the same
-// order) instead of waiting for a third.  One thread adding 256 slots one after the other, and a launch of its own
-// for it, was most of the call before: 64 x 384 tokens 26 -> 8 us a call, launched back to back.
-// ---------------------------------------------------------------------------------------
+// Few tokens: one launch.  Block 0 sums the loss over all tokens; block b > 0 writes the gradient of its 1024 tokens
+// and counts the masked tokens of the whole set by itself (n mask bytes out of the L2, 16 at a time).  The instructions
+// of block 0's terms on its one CU bound it, 0.25 us per 1024 tokens with groups of four to a load (addresses, row
+// steps and mask once per group) and 0.41 us one by one: 64 x 384 tokens 10.4 -> 6.5 us, launched back to back.
+// More tokens: they are summed by kLossBlocks blocks into slots, and every block of the second kernel adds the slots
+// again (4 KB, the same order) instead of waiting for a third; 5.7 us up to 100k tokens, which is what two launches cost
+// the host.  The line lies where the one launch takes what a second one costs it more, with a caller that has work of
+// its own between two calls: 24576 tokens by four, 14336 one by one.
 constexpr int kLossBlocks = 256;
-constexpr size_t kSurrogateOneLaunch = 32768;
+constexpr size_t kSurrogateOneLaunch = 24576, kSurrogateOneLaunchBy1 = 14336;
 struct LossPartial { double sum; long long count; };
 
 // (sum, count) over the THREADS threads of a block, in every thread; the order of additions is fixed
@@ -577,25 +578,46 @@ __device__ __forceinline__ float loss_value(double sum, long long count) {
 }
 
 // The terms of tokens first, first + stride, ... < end; the row of a token is kept by stepping, not by dividing.
+// V = 4: first, end and stride count groups of four tokens of one row (T: groups per row), loaded in one go.
+template <int V>
 __device__ __forceinline__ void surrogate_walk(const float* __restrict__ logp_new, const float* __restrict__ logp_old,
                                                const uint8_t* __restrict__ mask, const float* __restrict__ adv, unsigned T,
-                                               size_t first, size_t end, unsigned stride, float eps_low, float eps_high,
+                                               unsigned first, unsigned end, unsigned stride, float eps_low, float eps_high,
                                                double& sum, long long& count) {
-  size_t s = first / T;
-  unsigned t = (unsigned)(first - s * T);
+  unsigned s = first / T;
+  unsigned t = first - s * T;
   const unsigned ds = stride / T, dt = stride - ds * T;
-#pragma unroll 8
-  for (size_t i = first; i < end; i += stride) {
-    const bool on = mask[i] != 0;
-    float rho; bool act;
-    const float term = surrogate_term(logp_new[i], logp_old[i], adv[s], eps_low, eps_high, rho, act);
-    if (on) { sum += (double)term; ++count; }   // values under a clear mask may be anything, NaN included
+  unsigned cnt = 0;
+#pragma unroll (V == 4 ? 4 : 8)
+  for (unsigned i = first; i < end; i += stride) {
+    float ln[V], lo[V], rho;
+    unsigned m;
+    bool act;
+    const float a = adv[s];
+    if (V == 4) {
+      const float4 x = ((const float4*)logp_new)[i], y = ((const float4*)logp_old)[i];
+      ln[0] = x.x; ln[1] = x.y; ln[2] = x.z; ln[3] = x.w;
+      lo[0] = y.x; lo[1] = y.y; lo[2] = y.z; lo[3] = y.w;
+      m = ((const unsigned*)mask)[i];
+    } else {
+      ln[0] = logp_new[i]; lo[0] = logp_old[i];
+      m = mask[i];
+    }
+#pragma unroll
+    for (int v = 0; v < V; ++v) {
+      const bool on = ((m >> (8 * v)) & 0xffu) != 0;
+      const float term = surrogate_term(ln[v], lo[v], a, eps_low, eps_high, rho, act);
+      sum += (double)(on ? term : 0.f);   // values under a clear mask may be anything, NaN included
+      cnt += on;
+    }
     s += ds; t += dt;
     if (t >= T) { t -= T; ++s; }
   }
+  count += cnt;
 }
 
 // mask: 16-byte aligned
+template <int V>
 __global__ void __launch_bounds__(1024) k_surrogate_one(const float* __restrict__ logp_new, const float* __restrict__ logp_old,
                                                         const uint8_t* __restrict__ mask, const float* __restrict__ adv, int T,
                                                         int n, float eps_low, float eps_high, float* __restrict__ out_loss,
@@ -603,7 +625,8 @@ __global__ void __launch_bounds__(1024) k_surrogate_one(const float* __restrict_
   double sum = 0.0;
   long long count = 0;
   if (blockIdx.x == 0) {
-    surrogate_walk(logp_new, logp_old, mask, adv, (unsigned)T, threadIdx.x, (size_t)n, 1024u, eps_low, eps_high, sum, count);
+    surrogate_walk<V>(logp_new, logp_old, mask, adv, (unsigned)T / V, threadIdx.x, (unsigned)n / V, 1024u, eps_low, eps_high,
+                      sum, count);
     block_loss_sum<1024>(sum, count);
     if (threadIdx.x == 0) out_loss[0] = loss_value(sum, count);
     return;
@@ -627,15 +650,16 @@ __global__ void __launch_bounds__(1024) k_surrogate_one(const float* __restrict_
   block_loss_sum<1024>(sum, count);
   if (i < n) out[i] = surrogate_dlogp(a, rho, act, count);
 }
+template <int V>
 __global__ void __launch_bounds__(256) k_surrogate_partial(const float* __restrict__ logp_new, const float* __restrict__ logp_old,
                                                            const uint8_t* __restrict__ mask, const float* __restrict__ adv,
-                                                           int T, size_t n, float eps_low, float eps_high,
+                                                           int T, unsigned n, float eps_low, float eps_high,
                                                            LossPartial* __restrict__ part) {
-  const size_t per = (n + gridDim.x - 1) / gridDim.x;
-  const size_t i0 = (size_t)blockIdx.x * per, i1 = (i0 + per < n) ? i0 + per : n;
+  const unsigned units = n / V, per = (units + gridDim.x - 1) / gridDim.x;
+  const unsigned i0 = min(blockIdx.x * per, units), i1 = min(i0 + per, units);
   double sum = 0.0;
   long long cnt = 0;
-  surrogate_walk(logp_new, logp_old, mask, adv, (unsigned)T, i0 + threadIdx.x, i1, 256u, eps_low, eps_high, sum, cnt);
+  surrogate_walk<V>(logp_new, logp_old, mask, adv, (unsigned)T / V, i0 + threadIdx.x, i1, 256u, eps_low, eps_high, sum, cnt);
   block_loss_sum<256>(sum, cnt);
   if (threadIdx.x == 0) { part[blockIdx.x].sum = sum; part[blockIdx.x].count = cnt; }
 }
@@ -664,14 +688,16 @@ hipError_t g_surrogate_loss(const float* logp_new, const float* logp_old, const 
                             float eps_low, float eps_high, float* out_loss, float* out_dlogp, void* workspace,
                             hipStream_t st) {
   const size_t n = (size_t)S * T;
-  if (n <= kSurrogateOneLaunch && ((uintptr_t)mask & 15) == 0) {
+  // four tokens a load where a group of four stays in one row and every group is aligned
+  const bool by4 = (T & 3) == 0 && (((uintptr_t)logp_new | (uintptr_t)logp_old) & 15) == 0 && ((uintptr_t)mask & 3) == 0;
+  if (n <= (by4 ? kSurrogateOneLaunch : kSurrogateOneLaunchBy1) && ((uintptr_t)mask & 15) == 0) {
     const unsigned grad_blocks = out_dlogp ? (unsigned)((n + 1023) / 1024) : 0u;
-    return launch(KID_MISC, k_surrogate_one, dim3(1 + grad_blocks), dim3(1024), 0, st, logp_new, logp_old, mask, adv, T, (int)n,
-                  eps_low, eps_high, out_loss, out_dlogp);
+    return launch(KID_MISC, by4 ? k_surrogate_one<4> : k_surrogate_one<1>, dim3(1 + grad_blocks), dim3(1024), 0, st, logp_new,
+                  logp_old, mask, adv, T, (int)n, eps_low, eps_high, out_loss, out_dlogp);
   }
   LossPartial* part = (LossPartial*)workspace;
-  const hipError_t e = launch(KID_MISC, k_surrogate_partial, dim3(kLossBlocks), dim3(256), 0, st, logp_new, logp_old, mask, adv,
-                              T, n, eps_low, eps_high, part);
+  const hipError_t e = launch(KID_MISC, by4 ? k_surrogate_partial<4> : k_surrogate_partial<1>, dim3(kLossBlocks), dim3(256), 0,
+                              st, logp_new, logp_old, mask, adv, T, (unsigned)n, eps_low, eps_high, part);
   if (e != hipSuccess) return e;
   return launch(KID_MISC, k_surrogate_apply, dim3(out_dlogp ? (unsigned)((n + 255) / 256) : 1u), dim3(256), 0, st, logp_new,
                 logp_old, mask, adv, T, n, eps_low, eps_high, (const LossPartial*)part, out_loss, out_dlogp);
