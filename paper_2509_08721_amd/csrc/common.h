@@ -377,13 +377,11 @@ namespace sapo {
 struct Prefetch {
   const uint4* p = nullptr;
   int KS = 0, n_tiles = 0, nt_log2 = 0, ks1 = 0;   // ks1 = 0: nothing
-  int splits = 0;   // > 0: the operand of a split-K k_gemm_big instead: XCD x gets the K ranges of the splits x, x + 8, ...
 };
 constexpr int kPrefetchKb = 18;   // blocks of 1 KiB that a prefetching wave has in flight
 // workgroups of `waves` waves for it, a multiple of 8
 inline int prefetch_blocks(const Prefetch& pf, int waves) {
   const long kb = (long)pf.ks1 * pf.n_tiles;
-  if (pf.splits > 0) return (int)((pf.n_tiles * (pf.splits >> 3) + waves - 1) / waves) * 8;
   return (int)((kb + waves * kPrefetchKb - 1) / (waves * kPrefetchKb) + 7) / 8 * 8;
 }
 // All of a weight matrix, or the leading blocks of every tile where it is more than the L2s hold next to everything else
@@ -413,23 +411,6 @@ __device__ __forceinline__ void prefetch_role(const Prefetch& pf, int block, int
   const int xcd = block & 7, wv = (block >> 3) * NW + wave_index(threadIdx.x), nw = (n_blocks >> 3) * NW;   // waves per XCD
   const uint4* base = pf.p + (threadIdx.x & 63);
   prefetch_u32x4 all = {0, 0, 0, 0};
-  if (pf.splits > 0) {
-    // wave -> (tile, split): the split's blocks of the tile (stages of 2 blocks, as k_gemm_big cuts them)
-    const int per = pf.splits >> 3, n_st = pf.KS >> 1;
-    for (int c = wv; c < pf.n_tiles * per; c += nw) {
-      const int tile = c / per, z = (c - tile * per) * 8 + xcd;
-      const int b0 = 2 * (int)((long)z * n_st / pf.splits), b1 = 2 * (int)((long)(z + 1) * n_st / pf.splits);
-      for (int b = b0; b < b1; b += kPrefetchKb) {
-        prefetch_u32x4 v[kPrefetchKb];
-#pragma unroll
-        for (int r = 0; r < kPrefetchKb; ++r) v[r] = *(const prefetch_u32x4*)(base + ((size_t)tile * pf.KS + min(b + r, b1 - 1)) * 64);
-#pragma unroll
-        for (int r = 0; r < kPrefetchKb; ++r) all |= v[r];
-      }
-    }
-    asm volatile("" ::"v"(all));
-    return;
-  }
   const int n_units = pf.n_tiles >> pf.nt_log2, mine = ((n_units - xcd + 7) >> 3) << pf.nt_log2;   // tiles of this XCD
   const int span = pf.ks1, total = mine * span, nt1 = (1 << pf.nt_log2) - 1;
   for (int k = wv; k < total; k += nw * kPrefetchKb) {
