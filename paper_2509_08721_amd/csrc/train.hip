@@ -15,6 +15,7 @@
 #include <type_traits>
 #include <vector>
 
+#include "ranges.h"
 #include "surrogate.h"
 #include "train.h"
 
@@ -588,9 +589,9 @@ __global__ void __launch_bounds__(256, TJ == 2 ? 2 : 3) k_gemm_x3_tn(const float
   const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63, kh = lane >> 5, c = lane & 31;
   int tx, ty;
   if (!raster_tile((N + kGM - 1) / kGM, (M + kGM * TJ - 1) / (kGM * TJ), tx, ty)) return;
-  const int k_begin = blockIdx.z * k_split, k_end = min(K, k_begin + k_split);
-  // the first stage is the one that may be partial: tokens in front of it count as zero
-  const int nst = (k_end - k_begin + KS - 1) / KS, k_first = k_end - nst * KS;
+  const int k_begin = blockIdx.z * k_split;
+  const StageRows rows(k_begin, min(K, k_begin + k_split), KS);
+  const int nst = rows.nst;
   C += (size_t)blockIdx.z * c_split;
   const int row0 = ty * kGM * TJ + wave * 32 * TJ;
   // rows and columns past the end repeat the last one and are not stored
@@ -606,7 +607,7 @@ __global__ void __launch_bounds__(256, TJ == 2 ? 2 : 3) k_gemm_x3_tn(const float
   float raw[kTasks][8];
   auto request = [&](auto ic, int s) __attribute__((always_inline)) {
     constexpr int i = decltype(ic)::value, h = i / (TJ + 1), t = i % (TJ + 1);
-    const size_t k = k_first + min(s, nst - 1) * KS + h * 16;   // past the end: the last stage again, not used
+    const size_t k = rows.request(s) + h * 16;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
       if constexpr (t < TJ) raw[i][e] = *(const float*)((const char*)(A + (k + e) * lda) + aoff[t]);
@@ -632,8 +633,9 @@ __global__ void __launch_bounds__(256, TJ == 2 ? 2 : 3) k_gemm_x3_tn(const float
     for (int j = 0; j < 4; ++j)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[t][j][v] = 0.f;
-  auto stage = [&](auto pc, int s) __attribute__((always_inline)) {
+  auto stage = [&](auto pc, auto last_c, int s) __attribute__((always_inline)) {
     constexpr int P = decltype(pc)::value;
+    constexpr bool last = decltype(last_c)::value;   // nothing follows: nothing is cut or requested
     const u32x4_t* buf = Bs[P] + lane;
     each<H * 4>([&](auto slot_c) __attribute__((always_inline)) {
       constexpr int slot = decltype(slot_c)::value, h = slot >> 2, j = slot & 3;
@@ -645,7 +647,7 @@ __global__ void __launch_bounds__(256, TJ == 2 ? 2 : 3) k_gemm_x3_tn(const float
 #pragma unroll
         for (int t = 0; t < TJ; ++t)
           acc[t][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[P][h][t][kTermA[term]].v, b[kTermB[term]].v, acc[t][j], 0, 0, 0);
-      if constexpr (slot < kTasks) {
+      if constexpr (slot < kTasks && !last) {
         cut(slot_c, std::integral_constant<int, P ^ 1>());
         request(slot_c, s + 2);
         // one MFMA, then a few of the cut's instructions
@@ -661,29 +663,28 @@ __global__ void __launch_bounds__(256, TJ == 2 ? 2 : 3) k_gemm_x3_tn(const float
   };
   const std::integral_constant<int, 0> even;
   const std::integral_constant<int, 1> odd;
+  // the first stage is the one that may be partial: tokens in front of it count as zero
   each<kTasks>([&](auto ic) __attribute__((always_inline)) {
     constexpr int i = decltype(ic)::value, h = i / (TJ + 1), t = i % (TJ + 1);
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const int k = k_first + h * 16 + kh * 8 + e;
-      const size_t kc = max(k, k_begin);
+      const int i_row = h * 16 + kh * 8 + e;
+      const size_t kc = rows.row(i_row);
       float v;
       if constexpr (t < TJ) v = A[kc * lda + arow[t]];
       else v = B[kc * ldb + bcol];
-      raw[i][e] = k >= k_begin ? v : 0.f;
+      raw[i][e] = rows.in(rows.k_first + i_row) ? v : 0.f;
     }
   });
-  each<kTasks>([&](auto i) __attribute__((always_inline)) {
-    cut(i, even);
-    request(i, 1);
-  });
+  each<kTasks>([&](auto i) __attribute__((always_inline)) { cut(i, even); });
+  if (rows.more()) each<kTasks>([&](auto i) __attribute__((always_inline)) { request(i, 1); });
   __syncthreads();
   int s = 0;
   for (; s + 1 < nst; s += 2) {
-    stage(even, s);
-    stage(odd, s + 1);
+    stage(even, std::false_type(), s);
+    stage(odd, std::false_type(), s + 1);
   }
-  if (s < nst) stage(even, s);
+  if (s < nst) stage(even, std::true_type(), s);
   x3_store_tile<TJ>(acc, C, C, ldc, row0, tx * kGM, M, N, beta);
 }
 

@@ -447,3 +447,33 @@ def test_update_with_projection_biases(sapo):
     ref = O.score_logprobs(O.Model(shape, new), tokens, mask)
     assert np.max(np.abs(lp_gpu.cpu().numpy() - ref)) < 1e-4
     gw.close(); tr.close()
+
+
+@pytest.mark.parametrize("pieces,grad_tol,logp_tol", [(3, 2e-4, 2e-4), (2, 1e-3, 5e-4), (1, 5e-2, 2e-2)])
+@pytest.mark.parametrize("S,T", [(1, 2), (1, 5), (2, 4), (1, 15), (2, 8), (1, 17), (1, 31), (3, 11)])
+def test_update_of_a_few_tokens(sapo, S, T, pieces, grad_tol, logp_tol):
+    """Training sets shorter than a stage of the weight-gradient products (16 token rows; 32 with one piece) or just
+    past one; the LM head's contraction is over the masked rows, fewer still.  Tolerances: those of the number of pieces
+    above, for the same models."""
+    import torch
+    from oracle import sapo_update_oracle as U
+    shape = W.MINI_BF16
+    w = W.make_weights(shape, 909)
+    rng = np.random.default_rng(100 * S + T)
+    tokens = rng.integers(0, shape.vocab, size=(S, T)).astype(np.int32)
+    mask = W.make_completion_mask(S, T, max(1, T // 2))
+    adv = np.linspace(1.0, -0.7, S).astype(np.float32)
+    params = U.parameter_list(shape, w)
+    _, lp0, _ = U.loss_and_gradients(shape, params, tokens, mask, np.zeros((S, T), np.float32), adv)
+    u = rng.uniform(-0.15, 0.15, size=lp0.shape)   # clear of the clip bounds
+    logp_old = (lp0 + u * (mask != 0)).astype(np.float32)
+    ref_loss, ref_lp, ref_g = U.loss_and_gradients(shape, params, tokens, mask, logp_old, adv)
+    tr = sapo.sapo_trainer_create(shape, w)
+    sapo.sapo_trainer_set_matmul_pieces(tr, pieces)
+    loss, lp = sapo.sapo_policy_update(tr, dev(tokens), dev(mask), dev(logp_old), dev(adv))
+    torch.cuda.synchronize()
+    assert np.max(np.abs(lp.cpu().numpy() - ref_lp)) < logp_tol and abs(float(loss.cpu()[0]) - ref_loss) < logp_tol
+    gmax = max(float(np.max(np.abs(x))) for x in ref_g)
+    for i, (g, b) in enumerate(zip(read_all(sapo, tr, 1), ref_g)):
+        assert float(np.max(np.abs(g - b))) <= grad_tol * max(float(np.max(np.abs(b))), 1e-3 * gmax) + 1e-7, i
+    tr.close()
