@@ -293,6 +293,7 @@ int sapo_assemble_training_set(const int32_t* local_tokens, const float* local_r
  *   out_dlogp           dev fp32 [S, T] or NULL: d loss / d logp_new = -A rho / N where the unclipped
  *                       branch is the minimum (A >= 0 and rho <= 1 + eps_high, or A < 0 and
  *                       rho >= 1 - eps_low), 0 elsewhere and where the mask is clear
+ *                       (may be logp_new or logp_old itself; no other overlap of buffers)
  *   workspace           dev, >= sapo_surrogate_workspace_bytes(), 256-byte aligned
  * rho and the branch are taken in fp32, the sums in fp64 in a fixed order (no atomics).
  * Returns SAPO_EINVAL for NULL buffers, non-positive sizes or eps outside [0, 1) / [0, inf).

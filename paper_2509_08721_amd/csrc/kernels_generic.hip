@@ -1,6 +1,7 @@
 // Shape-generic kernels: any model shape, fp32 or bf16 storage, plain ALU arithmetic.
 // They run the fp32 configuration and every step that has no tile-aligned MFMA kernel.
 #include "common.h"
+#include "ranges.h"
 #include "small.h"
 #include "surrogate.h"
 #include "train.h"
@@ -664,11 +665,12 @@ __global__ void __launch_bounds__(256) k_surrogate_partial(const float* __restri
   if (threadIdx.x == 0) { part[blockIdx.x].sum = sum; part[blockIdx.x].count = cnt; }
 }
 // adds the kLossBlocks slots, writes the loss (block 0) and the gradient of this block's 256 tokens (out may be null)
-__global__ void __launch_bounds__(256) k_surrogate_apply(const float* __restrict__ logp_new, const float* __restrict__ logp_old,
+// out may be logp_new or logp_old itself: a token is read and written by one thread, the slots are complete before.
+__global__ void __launch_bounds__(256) k_surrogate_apply(const float* logp_new, const float* logp_old,
                                                          const uint8_t* __restrict__ mask, const float* __restrict__ adv,
                                                          int T, size_t n, float eps_low, float eps_high,
                                                          const LossPartial* __restrict__ part, float* __restrict__ out_loss,
-                                                         float* __restrict__ out) {
+                                                         float* out) {
   static_assert(kLossBlocks == 256, "one slot per thread");
   double sum = part[threadIdx.x].sum;
   long long count = part[threadIdx.x].count;
@@ -690,7 +692,10 @@ hipError_t g_surrogate_loss(const float* logp_new, const float* logp_old, const 
   const size_t n = (size_t)S * T;
   // four tokens a load where a group of four stays in one row and every group is aligned
   const bool by4 = (T & 3) == 0 && (((uintptr_t)logp_new | (uintptr_t)logp_old) & 15) == 0 && ((uintptr_t)mask & 3) == 0;
-  if (n <= (by4 ? kSurrogateOneLaunch : kSurrogateOneLaunchBy1) && ((uintptr_t)mask & 15) == 0) {
+  // In one launch the gradient is stored while block 0 still sums: not where it goes over the log-probs.
+  const bool in_place = out_dlogp && (overlap((uintptr_t)out_dlogp, (uintptr_t)logp_new, n * sizeof(float)) ||
+                                      overlap((uintptr_t)out_dlogp, (uintptr_t)logp_old, n * sizeof(float)));
+  if (n <= (by4 ? kSurrogateOneLaunch : kSurrogateOneLaunchBy1) && ((uintptr_t)mask & 15) == 0 && !in_place) {
     const unsigned grad_blocks = out_dlogp ? (unsigned)((n + 1023) / 1024) : 0u;
     return launch(KID_MISC, by4 ? k_surrogate_one<4> : k_surrogate_one<1>, dim3(1 + grad_blocks), dim3(1024), 0, st, logp_new,
                   logp_old, mask, adv, T, (int)n, eps_low, eps_high, out_loss, out_dlogp);

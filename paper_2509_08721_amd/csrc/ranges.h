@@ -1,6 +1,8 @@
 // Index arithmetic that decides which addresses a kernel touches, in plain C++ without any HIP in it, so that a test on the
 // host can walk it over the whole range of sizes.
 #pragma once
+#include <cstddef>
+#include <cstdint>
 
 namespace sapo {
 
@@ -18,5 +20,8 @@ struct StageRows {
   constexpr bool in(int row) const { return row >= k_begin; }          // first stage: does the row count?
   constexpr int row(int i) const { return k_first + i > k_begin ? k_first + i : k_begin; }   // first stage: row i, clamped
 };
+
+// Do two buffers of n bytes each share a byte?
+constexpr bool overlap(uintptr_t a, uintptr_t b, size_t n) { return a < b ? b - a < n : a - b < n; }
 
 }  // namespace sapo

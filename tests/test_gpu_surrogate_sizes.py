@@ -33,3 +33,18 @@ def test_surrogate_mask_bytes_and_alignment(n_rows):
     assert none is None
     assert torch.equal(grad, grad2) and torch.equal(grad, grad3)
     assert float(loss) == float(loss2) == float(loss4) and float(loss3) == pytest.approx(float(loss), rel=1e-6)
+
+
+@pytest.mark.parametrize("over", ["logp_new", "logp_old"])
+@pytest.mark.parametrize("S,T", [(8, 33), (64, 384), (300, 129)])
+def test_surrogate_gradient_over_its_inputs(S, T, over):
+    """The gradient written over the log-probs it is taken from: what a call with an output of its own gives, at sizes
+    that take one launch and two otherwise."""
+    ln, lo, mask, adv = case(S, T, 300 + S)
+    ref_loss, ref_grad = run_and_check(ln, lo, mask, adv)
+    dev = [torch.from_numpy(x).cuda() for x in (ln, lo, mask, adv)]
+    out = dev[0] if over == "logp_new" else dev[1]
+    loss = torch.empty(1, device="cuda")
+    sapo.sapo_clipped_surrogate_noalloc(*dev, loss, out)
+    # the sum's order is that of the two launches: fp64, so the loss agrees to the last bits of its fp32
+    assert float(loss) == pytest.approx(ref_loss, rel=2e-7) and np.array_equal(out.cpu().numpy().astype(np.float64), ref_grad)

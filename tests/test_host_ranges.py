@@ -52,3 +52,20 @@ int main() {
   return bad != 0;
 }
 """)
+
+
+def test_buffers_that_share_a_byte_are_seen(tmp_path):
+    """Which buffers the surrogate may not write while it reads them."""
+    run(tmp_path, r"""
+int main() {
+  int bad = 0;
+  for (int a = 0; a < 12; ++a)
+    for (int b = 0; b < 12; ++b)
+      for (int n = 1; n < 8; ++n) {
+        bool shared = false;
+        for (int i = 0; i < n; ++i) for (int j = 0; j < n; ++j) shared |= a + i == b + j;
+        if (overlap(a, b, n) != shared) { ++bad; printf("%d %d of %d bytes\n", a, b, n); }
+      }
+  return bad != 0;
+}
+""")
