@@ -890,7 +890,7 @@ static int rollout_impl(const sapo_weights* w, const int32_t* prompts, const int
     // the cache of this path holds P Lp + S N positions in a row: no more than the pages carved for the call
     const SmallModel m = small_model(w, pl.cache);
     if (small_prefill_fits(m, Lp) && small_decode_fits(m, Lp + max_new) &&
-        small_rows_fit(m, (size_t)P * Lp + (size_t)S * max_new, (size_t)S * max_new)) {
+        small_rows_fit(m, (size_t)P * Lp + (size_t)S * max_new, (size_t)P * Lp, std::max((size_t)P * Lp, (size_t)S * max_new))) {
       if (ragged) HIP_CK(hipMemcpyAsync(pl.lens, lens_host, (size_t)P * sizeof(int), hipMemcpyHostToDevice, st));
       SmallPrefill pa{};
       pa.tokens = prompts; pa.T = Lp; pa.lens = ragged ? pl.lens : nullptr; pa.h_last = pl.h_last;
@@ -1253,7 +1253,8 @@ static int score_impl(const sapo_weights* w, const int32_t* tokens, const uint8_
 
   if (w->small_tbl) {
     const SmallModel m = small_model(w, pl.cache);
-    if (small_prefill_fits(m, T) && small_rows_fit(m, (size_t)pl.chunk_seqs * T, (size_t)pl.chunk_seqs * T)) {
+    const size_t rows = (size_t)pl.chunk_seqs * T;
+    if (small_prefill_fits(m, T) && small_rows_fit(m, rows, rows, rows)) {
       const bool whole = pl.chunk_seqs >= S;   // groups do not straddle passes: the advantages ride along
       if (!whole) HIP_CK(g_advantages(rewards, S, G, out_advantages, st));
       for (int s0 = 0; s0 < S; s0 += pl.chunk_seqs) {

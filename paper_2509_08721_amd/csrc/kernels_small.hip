@@ -13,7 +13,7 @@
 //                    sequence and one launch; more: one workgroup per tile and n_layers + 1 launches (tiny decoder,
 //                    scoring: two tiles 77 us in one launch, 51 us in three).
 //   k_small_decode   one workgroup per sequence: LM head, sampler, embedding and layers of one position, step after step.
-// Offsets are 32-bit: small_rows_fit (host) keeps every buffer below 2^31 bytes.
+// Offsets are 32-bit: small_rows_fit (host; the limits are in ranges.h) says for which calls they are enough.
 // What bounds them: a workgroup streams the model through one compute unit per step (about 80 GB/s), five barriers per
 // layer.  small_eligible (api.hip) says for which models that is still cheaper than the launches.
 //
@@ -24,6 +24,7 @@
 // consecutive k per lane, one per v_mfma_f32_16x16x4_f32 (any assignment of k to slots does, if both operands share it).
 // On the vector ALUs the rows' values, read from LDS once per feature, took 2 to 3 times as long.
 #include "common.h"
+#include "ranges.h"
 #include "small.h"
 #include <type_traits>
 
@@ -796,9 +797,9 @@ hipError_t set_lds_once(int dtype) {
 
 }  // namespace
 
-// cache rows of a call, and rows of its fp32 / int32 inputs and outputs
-bool small_rows_fit(const SmallModel& m, size_t cache_rows, size_t io_elems) {
-  return cache_rows * m.hkv * m.hd * 4 < ((size_t)1 << 31) && io_elems * 4 < ((size_t)1 << 31);
+// positions in the cache of a call, prompt (or scored) positions, elements of its largest int32 / fp32 input or output
+bool small_rows_fit(const SmallModel& m, size_t cache_rows, size_t prompt_rows, size_t io_elems) {
+  return small_offsets_fit(m.d, (uint64_t)m.hq * m.hd, (uint64_t)m.hkv * m.hd, cache_rows, prompt_rows, io_elems);
 }
 bool small_prefill_fits(const SmallModel& m, int T) { return prefill_lds(m, T) <= kLdsLimit; }
 bool small_decode_fits(const SmallModel& m, int ctx_max) { return decode_lds(m, ctx_max) <= kLdsLimit; }

@@ -21,6 +21,14 @@ struct StageRows {
   constexpr int row(int i) const { return k_first + i > k_begin ? k_first + i : k_begin; }   // first stage: row i, clamped
 };
 
+// The small-decoder kernels index with 32 bits: K and V of a layer (cache_rows of kv values) and the call's tokens and
+// outputs (io_elems of 4 bytes) stay below 2^31 bytes, the rows a long prompt keeps between launches (prompt_rows of d
+// residual values, and of q query values) below 2^32 elements.
+constexpr bool small_offsets_fit(uint64_t d, uint64_t q, uint64_t kv, uint64_t cache_rows, uint64_t prompt_rows, uint64_t io_elems) {
+  return cache_rows * kv < (uint64_t)1 << 29 && io_elems < (uint64_t)1 << 29 &&
+         prompt_rows * (d > q ? d : q) <= (uint64_t)1 << 32;
+}
+
 // Do two buffers of n bytes each share a byte?
 constexpr bool overlap(uintptr_t a, uintptr_t b, size_t n) { return a < b ? b - a < n : a - b < n; }
 

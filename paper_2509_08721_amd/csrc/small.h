@@ -46,7 +46,7 @@ struct SmallDecode {
   float* out_logprobs;
   int32_t* out_lengths;    // optional [S]
 };
-bool small_rows_fit(const SmallModel& m, size_t cache_rows, size_t io_elems);
+bool small_rows_fit(const SmallModel& m, size_t cache_rows, size_t prompt_rows, size_t io_elems);
 bool small_prefill_fits(const SmallModel& m, int T);
 bool small_decode_fits(const SmallModel& m, int ctx_max);
 hipError_t small_prefill(int dtype, const SmallModel& m, const SmallPrefill& a, int n_seq, hipStream_t st);

@@ -69,3 +69,31 @@ int main() {
   return bad != 0;
 }
 """)
+
+
+def test_small_decoder_offsets_stay_within_32_bits(tmp_path):
+    """Whatever the rule lets through has its largest index below 2^32 (the kernels compute (row * heads + head) * head dim +
+    dim and row * width + column in unsigned 32 bits), over the model widths and batch sizes a rollout call accepts."""
+    run(tmp_path, r"""
+int main() {
+  int bad = 0, let = 0, held = 0;
+  const uint64_t lim = (uint64_t)1 << 32;
+  for (uint64_t d : {4, 64, 128, 252, 256, 260, 512, 4096})
+    for (uint64_t q : {4, 64, 256, 300, 1024})
+      for (uint64_t kv : {4, 8, 32, 64, 256})
+        for (int lg = 0; lg <= 24; ++lg)                 // prompt positions: at most 2^24
+          for (uint64_t less : {0, 1}) {
+            const uint64_t rows = ((uint64_t)1 << lg) - (lg ? less : 0);
+            for (uint64_t gen : {1u, 1u << 10, 1u << 20, 1u << 26}) {   // generated positions
+              const uint64_t cache = rows + gen, io = rows > gen ? rows : gen;
+              if (!small_offsets_fit(d, q, kv, cache, rows, io)) { ++held; continue; }
+              ++let;
+              if (rows * d > lim || rows * q > lim || cache * kv > lim || io > lim) { ++bad; printf("d %d q %d kv %d rows %d\n", (int)d, (int)q, (int)kv, (int)rows); }
+            }
+          }
+  if (small_offsets_fit(260, 8, 8, 1 << 24, 1 << 24, 1 << 24)) { ++bad; printf("2^24 rows of 260 let through\n"); }
+  if (!small_offsets_fit(64, 64, 16, 1 << 24, 1 << 24, 1 << 24)) { ++bad; printf("2^24 rows of 64 held back\n"); }
+  printf("%d let through, %d held back\n", let, held);
+  return bad != 0 || !let || !held;
+}
+""")
