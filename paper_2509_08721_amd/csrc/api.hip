@@ -269,8 +269,8 @@ static int upload_persist_table(sapo_weights* w) {
 // Small decoders (kernels_small.hip): one workgroup takes a sequence through the whole call.  Per decode step it
 // streams the model through one compute unit (about 80 GB/s) and pays its barriers (about 5 us per layer); the
 // shape-generic path pays its 11 launches per layer, about 5 us each.  The line is drawn where the former is at most half
-// of the latter with one round of workgroups, so that a batch of two rounds (512 sequences) is still no slower.  Tiny
-// configuration: 18 us per step (the estimate says 19) against 135.
+// of the latter with one round of workgroups, so that a batch of two rounds (512 sequences) is still no slower; larger
+// batches are decided call by call (small_pays).  Tiny configuration: 18 us per step (the estimate says 19) against 135.
 static bool small_eligible(const sapo_weights* w) {
   const sapo_model_config& c = w->cfg;
   if (w->mfma || force_generic() || c.n_layers == 0) return false;
@@ -279,6 +279,26 @@ static bool small_eligible(const sapo_weights* w) {
   const double bytes = w->elt * (c.n_layers * (d * (2 * q + 2 * kv) + 3 * d * c.d_ff) + d * c.vocab);
   const double step_us = bytes / 80e3 + 5.0 * c.n_layers + 3.0, launches_us = 5.0 * (11.0 * c.n_layers + 4.0);
   return 2.0 * step_us <= launches_us;
+}
+// Is a rollout call cheaper on the small path?  256 workgroups run at once, so a step there costs rounds of 256 sequences,
+// while the generic path's launches are shared by the whole batch and only its work grows.  Estimates in us, fitted to
+// 280 comparisons of the two paths on seven decoders (1 .. 8 layers, d 32 .. 128, vocabulary 256 .. 6000), 64 .. 16384 sequences, contexts of
+// 4 .. 270 tokens; above 512 sequences they name the faster path in all but 13, the two of which are within 15 % of each
+// other in 12.  Both sides at 2 layers, d 64, vocabulary 512 (us per step, contexts of 28): small 109 / 217 / 433 / 868 at
+// 1536 / 3072 / 6144 / 12288 sequences, generic 218 / 254 / 314 / 447.  Scoring stays on the small path whatever the
+// batch: its tiles of 16 rows cost 0.2 .. 0.6 of the generic kernels at every size measured (up to 262144 tokens).
+static bool small_pays(const sapo_model_config& c, int P, int Lp, int G, int N) {
+  const double S = (double)P * G;
+  if (S <= 512) return true;
+  const double L = c.n_layers, d = c.d_model, q = (double)c.n_q_heads * c.head_dim, kv = (double)c.n_kv_heads * c.head_dim;
+  const double layers = L * (d * (2 * q + 2 * kv) + 3 * d * c.d_ff) * 1e-3, head = d * c.vocab * 1e-3;   // thousands of weights
+  const double ctx = Lp + 0.5 * N, rounds = ceil(S / 256), tiles = (double)P * ((Lp + 15) / 16);
+  const double small_us = tiles * (0.03 * (1 + L) + 0.0006 * layers) +
+                          rounds * (N * 0.05 * head + (N - 1) * (0.05 * layers + 6.2 * L + 0.63e-3 * L * kv * ctx));
+  const double generic_us = (double)P * Lp * (0.002 * (1 + L) + 5.5e-5 * layers + 1.25e-6 * L * q * Lp) +
+                            N * (L * (29 + 0.135 * (2 * d + q + c.d_ff)) + 36) +
+                            S * (N * 5.6e-5 * head + (N - 1) * (5.6e-5 * layers + 3e-6 * L * q * ctx));
+  return small_us <= generic_us;
 }
 static int upload_small_table(sapo_weights* w) {
   const int L = w->cfg.n_layers;
@@ -889,7 +909,7 @@ static int rollout_impl(const sapo_weights* w, const int32_t* prompts, const int
   if (w->small_tbl) {
     // the cache of this path holds P Lp + S N positions in a row: no more than the pages carved for the call
     const SmallModel m = small_model(w, pl.cache);
-    if (small_prefill_fits(m, Lp) && small_decode_fits(m, Lp + max_new) &&
+    if (small_pays(c, P, Lp, G, max_new) && small_prefill_fits(m, Lp) && small_decode_fits(m, Lp + max_new) &&
         small_rows_fit(m, (size_t)P * Lp + (size_t)S * max_new, (size_t)P * Lp, std::max((size_t)P * Lp, (size_t)S * max_new))) {
       if (ragged) HIP_CK(hipMemcpyAsync(pl.lens, lens_host, (size_t)P * sizeof(int), hipMemcpyHostToDevice, st));
       SmallPrefill pa{};

@@ -94,3 +94,21 @@ def test_large_models_do_not_take_the_small_path():
     tok = torch.zeros((1, 8), dtype=torch.int32, device="cuda")
     names = kernels_of(lambda: sapo.sapo_score_logprobs(w, tok, torch.ones_like(tok, dtype=torch.uint8), torch.zeros(1, device="cuda"), 1))
     assert "k_small" not in names
+
+
+def test_large_batches_leave_the_small_path():
+    """Thousands of sequences cost the small path a round of workgroups per 256 of them; from some size on the generic
+    kernels take the call.  The rows are the same: the first prompts of a large call repeat a small call's tokens."""
+    shape = W.TINY
+    small, _ = handles(shape, 14)
+    rng = np.random.default_rng(9)
+    prompts = torch.from_numpy(rng.integers(0, shape.vocab, (1536, 5)).astype(np.int32)).cuda()
+    G, N = 8, 6
+    a = sapo.sapo_rollout_generate(small, prompts[:64].contiguous(), G, N, 1.0, 5)
+    assert kernels_of(lambda: sapo.sapo_rollout_generate(small, prompts[:64].contiguous(), G, N, 1.0, 5)) == {"k_small"}
+    b = sapo.sapo_rollout_generate(small, prompts, G, N, 1.0, 5)
+    assert "k_small" not in kernels_of(lambda: sapo.sapo_rollout_generate(small, prompts, G, N, 1.0, 5))
+    assert torch.equal(a[0], b[0][:512]) and float((a[1] - b[1][:512]).abs().max()) <= 2e-5
+    # long prompts and few steps: the prompts' tiles decide, and they are cheaper on the small path
+    long = torch.from_numpy(rng.integers(0, shape.vocab, (1024, 200)).astype(np.int32)).cuda()
+    assert kernels_of(lambda: sapo.sapo_rollout_generate(small, long, 1, 2, 1.0, 5)) == {"k_small"}
