@@ -29,6 +29,47 @@ constexpr bool small_offsets_fit(uint64_t d, uint64_t q, uint64_t kv, uint64_t c
          prompt_rows * (d > q ? d : q) <= (uint64_t)1 << 32;
 }
 
+// Tile height (TJ blocks of 128 rows) and split of a packed product of the update (k_gemm_x3, k_gemm_x3_tn) with rows x cols
+// outputs and KB steps of 16 along the contraction, in stages of `stage` steps; NP bf16 pieces per value.  A product whose
+// output tiles fill the workgroups in flight badly (weight gradients: 49 .. 532 tiles; outputs d wide: 672 tiles on 512
+// slots are 1.3 rounds run as 2) is split along the contraction where parts_cap (floats) allows it: each part writes its own
+// product and k_sum_parts adds them in part order.  Taken are the height and number of parts with the least estimated time:
+// rounds of resident workgroups (two per compute unit at 256 rows, three at 128) of so many steps, a tile's first requests
+// and output, and the pass that adds the parts; among those whose chains are at most kChainSteps long.
+// Why a limit: an accumulator loses a fraction of a unit in its last place at every step, so the error against 64 bits
+// follows the longest chain, and the head's d-input product contracts over the vocabulary (9496 steps at 151936).  64 x 384
+// tokens of the 0.5B decoder, three pieces: 4 parts of 2374 steps, the fastest by 2 % of the estimate, leave
+// 1.5e-5 in the final norm's gradient and 2.4e-5 in the whole one, 16 parts of 594 steps 4.2e-6 and 1.5e-5; the update took
+// 407.7 and 406.1 ms.
+constexpr int kMaxSplits = 16, kChainSteps = 608;
+struct X3Split { int TJ, parts, per_part; };
+inline X3Split x3_split(int NP, int rows, int cols, int KB, int stage, size_t parts_cap) {
+  const int gnx = (cols + 127) / 128, gny = (rows + 127) / 128;
+  const double terms = NP == 3 ? 6.0 : NP == 2 ? 3.0 : 1.0;
+  X3Split best{2, 1, (KB + stage - 1) / stage * stage};
+  double best_us = 0.0;
+  for (int TJ = 2; TJ >= 1; --TJ) {
+    const int gty = (gny + TJ - 1) / TJ;
+    const long tiles = (long)gnx * gty, slots = TJ == 2 ? 512 : 768;
+    // one 16-k step of a full round (measured: 1.6 PFLOP/s with three pieces, 0.9 with one; 10 % more for the small tile)
+    const double step_us = (TJ == 2 ? 1.0 : 0.825) * 0.336 * terms * (NP == 1 ? 1.8 : NP == 2 ? 1.2 : 1.0);
+    for (int s = 1; s <= kMaxSplits; ++s) {
+      if (s > 1 && (KB / s < 16 || (size_t)s * rows * cols > parts_cap)) break;
+      if ((KB + s - 1) / s > kChainSteps && s < kMaxSplits && (size_t)(s + 1) * rows * cols <= parts_cap) continue;
+      const int per = ((KB + s - 1) / s + stage - 1) / stage * stage;
+      if ((KB + per - 1) / per != s) continue;
+      const long rounds = (tiles * s + slots - 1) / slots;
+      const double sum_us = s > 1 ? 4.0 + (s + 2) * 4e-6 * rows * cols : 0.0;   // at 1 MB per us
+      const double us = rounds * (per * step_us + (TJ == 2 ? 14.0 : 10.5)) + sum_us / 4.0;
+      if (best_us == 0.0 || us < best_us * 0.98) {
+        best_us = us;
+        best = X3Split{TJ, s, per};
+      }
+    }
+  }
+  return best;
+}
+
 // Do two buffers of n bytes each share a byte?
 constexpr bool overlap(uintptr_t a, uintptr_t b, size_t n) { return a < b ? b - a < n : a - b < n; }
 

@@ -695,7 +695,6 @@ inline size_t x3_pack_bytes(int NP, size_t rows, size_t K) {
 }
 inline int x3_steps(int K, int NP) { const int k = 16 * x3_stage(NP); return (K + k - 1) / k * x3_stage(NP); }   // padded k steps
 struct X3Bufs { void* a; void* b; size_t a_cap, b_cap; int NP; float* parts; size_t parts_cap; };
-constexpr int kMaxSplits = 16;
 __global__ void k_sum_parts(const float* __restrict__ part, int n_part, size_t n, float beta, const float* in, float* out);
 
 hipError_t x3_pack(const X3Op& op, void* dst, size_t cap, int NP, hipStream_t st) {
@@ -708,38 +707,11 @@ hipError_t x3_pack(const X3Op& op, void* dst, size_t cap, int NP, hipStream_t st
   if (op.trans) return NP == 3 ? go(k_pack_x3_t<3>) : NP == 2 ? go(k_pack_x3_t<2>) : go(k_pack_x3_t<1>);
   return NP == 3 ? go(k_pack_x3<3>) : NP == 2 ? go(k_pack_x3<2>) : go(k_pack_x3<1>);
 }
-// Tile, grid and split of a product with `rows` x `cols` outputs and KB k steps in stages of `stage`.
+// Tile, grid and split of a product with `rows` x `cols` outputs and KB k steps in stages of `stage` (x3_split in ranges.h).
 struct X3Grid { int TJ, splits, per_split; dim3 grid; };
-// A product whose output tiles fill the workgroups in flight badly (weight gradients: 49 .. 532 tiles; outputs d wide:
-// 672 tiles on 512 slots are 1.3 rounds run as 2) is split along the contraction when parts_cap allows it: each part writes
-// its own product and k_sum_parts adds them in part order.  Tile height and number of parts are those with the least
-// estimated time: rounds of resident workgroups (two per compute unit at 256 rows, three at 128) of so many steps, a
-// tile's first requests and output, and the pass that adds the parts.
 X3Grid x3_grid(int NP, int rows, int cols, int KB, int stage, size_t parts_cap) {
-  const int gnx = (cols + kGM - 1) / kGM, gny = (rows + kGM - 1) / kGM;
-  const double terms = NP == 3 ? 6.0 : NP == 2 ? 3.0 : 1.0;
-  X3Grid best{};
-  double best_us = 0.0;
-  for (int TJ = 2; TJ >= 1; --TJ) {
-    const int gty = (gny + TJ - 1) / TJ;
-    const long tiles = (long)gnx * gty, slots = TJ == 2 ? 512 : 768;
-    // one 16-k step of a full round (measured: 1.6 PFLOP/s with three pieces, 0.9 with one; 10 % more for the small tile)
-    const double step_us = (TJ == 2 ? 1.0 : 0.825) * 0.336 * terms * (NP == 1 ? 1.8 : NP == 2 ? 1.2 : 1.0);
-    for (int s = 1; s <= kMaxSplits; ++s) {
-      if (s > 1 && (KB / s < 16 || (size_t)s * rows * cols > parts_cap)) break;
-      const int per = ((KB + s - 1) / s + stage - 1) / stage * stage;
-      if ((KB + per - 1) / per != s) continue;
-      const long rounds = (tiles * s + slots - 1) / slots;
-      const double sum_us = s > 1 ? 4.0 + (s + 2) * 4e-6 * rows * cols : 0.0;   // at 1 MB per us
-      const double us = rounds * (per * step_us + (TJ == 2 ? 14.0 : 10.5)) + sum_us / 4.0;
-      if (best_us == 0.0 || us < best_us * 0.98) {
-        best_us = us;
-        best.TJ = TJ; best.splits = s; best.per_split = per;
-        best.grid = dim3(raster_grid(gnx, gty), 1, s);
-      }
-    }
-  }
-  return best;
+  const X3Split s = x3_split(NP, rows, cols, KB, stage, parts_cap);
+  return X3Grid{s.TJ, s.parts, s.per_part, dim3(raster_grid((cols + kGM - 1) / kGM, (rows + kGM * s.TJ - 1) / (kGM * s.TJ)), 1, s.parts)};
 }
 hipError_t x3_sum_parts(const X3Bufs& bufs, int splits, size_t n, float beta, const float* Cin, float* C, hipStream_t st) {
   return launch(KID_MISC, k_sum_parts, dim3((unsigned)((n + 1023) / 1024)), dim3(256), 0, st, (const float*)bufs.parts, splits, n, beta,

@@ -97,3 +97,34 @@ int main() {
   return bad != 0 || !let || !held;
 }
 """)
+
+
+def test_products_of_the_update_are_split_without_long_chains(tmp_path):
+    """x3_split over the products of small and large decoders: the parts cover the contraction, none is empty, and no
+    accumulator's chain is longer than 608 steps (one stage's rounding apart) unless 16 parts or the buffer for the parts do
+    not allow it."""
+    run(tmp_path, r"""
+int main() {
+  int bad = 0, limited = 0;
+  const size_t caps[] = {0, (size_t)1 << 20, (size_t)8 * 2 * 4864 * 896, (size_t)8 * 2 * 8960 * 1536};
+  for (int NP = 1; NP <= 3; ++NP)
+    for (int stage : {NP == 3 ? 1 : NP == 2 ? 2 : 4, NP == 1 ? 2 : 1})
+      for (int rows : {1, 64, 130, 896, 1152, 2500, 4352, 9728, 24576, 151936})
+        for (int cols : {48, 896, 1536, 4864, 17920})
+          for (int K : {1, 16, 100, 896, 4864, 9728, 9744, 17920, 24576, 151936, 300000})
+            for (size_t cap : caps) {
+              const int steps = (K + 15) / 16, KB = (steps + stage - 1) / stage * stage;
+              const X3Split s = x3_split(NP, rows, cols, KB, stage, cap);
+              const size_t out = (size_t)rows * cols;
+              const bool covers = s.per_part % stage == 0 && (long)s.per_part * s.parts >= KB && (long)s.per_part * (s.parts - 1) < KB;
+              const bool fits = s.parts == 1 || s.parts * out <= cap;
+              const bool could = s.parts < kMaxSplits && (s.parts + 1) * out <= cap;
+              const bool chain = s.per_part < kChainSteps + stage || !could;
+              limited += s.per_part >= kChainSteps + stage;
+              if (!covers || !fits || !chain || s.TJ < 1 || s.TJ > 2) { if (++bad < 20) printf("NP %d stage %d %d x %d K %d cap %zu: TJ %d, %d parts of %d\n", NP, stage, rows, cols, K, cap, s.TJ, s.parts, s.per_part); }
+            }
+  const X3Split head = x3_split(3, 4352, 896, 9496, 1, caps[2]);
+  if (head.per_part > kChainSteps) { ++bad; printf("head: %d parts of %d\n", head.parts, head.per_part); }
+  return bad != 0;
+}
+""")
