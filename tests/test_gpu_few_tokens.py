@@ -1,7 +1,9 @@
 """Scoring calls and prompts of few tokens: the GEMM tiles and attention splits chosen by size give every token the same bits.
 
 SAPO_BIG_TILE=256 forces the 256-token tiles (checked against the oracle in test_gpu_mfma.py and test_gpu_full.py); by
-default calls of few tokens run on k_gemm_mid / k_gemm_qkv_mid, which keep every output's chain of MFMAs.
+default calls of few tokens run on k_gemm_mid / k_gemm_qkv_mid, which keep every output's chain of MFMAs.  The query heads
+per wave of the attention and the vocabulary groups of the scorer follow the number of sequences, not that switch: a call
+of few sequences is compared with the same sequences in a larger one for those.
 """
 import os
 from dataclasses import replace
@@ -45,3 +47,28 @@ def test_scores_are_bit_identical_to_the_large_tiles(model, S, T):
     finally:
         os.environ.pop("SAPO_BIG_TILE", None)
     assert np.array_equal(lp.cpu().numpy(), ref.cpu().numpy())
+
+
+# two layers each: attention waves of 1, 2 and 4 heads at head dim 64 (1, 8 and 16 sequences of 300), 1 and 2 heads at 128;
+# scorer groups of 2, 4 and 16 vocabulary tiles
+@pytest.mark.parametrize("shape", [replace(W.HALF_B, n_layers=2), replace(W.ONE_HALF_B, n_layers=2)], ids=["hd64", "hd128"])
+def test_a_sequence_scores_the_same_alone_and_among_others(shape):
+    gw = sapo.sapo_weights_create(shape, W.make_weights(shape, 43))
+    assert gw.uses_mfma
+    rng = np.random.default_rng(44)
+    S, T = 16, 300
+    tokens = torch.from_numpy(rng.integers(0, shape.vocab, size=(S, T)).astype(np.int32)).cuda()
+    mask = torch.ones((S, T), dtype=torch.uint8, device="cuda")
+    rewards = torch.zeros(S, device="cuda")
+    positions = [(0, 0), (0, 15), (0, 16), (0, 100), (0, 255), (0, 256), (0, 299)]
+    logits = sapo.sapo_debug_logits(gw, tokens, positions)
+    lp, _ = sapo.sapo_score_logprobs(gw, tokens, mask, rewards, 1)
+    for n in (1, 2, 8):
+        few = tokens[:n].contiguous()
+        assert torch.equal(sapo.sapo_debug_logits(gw, few, positions), logits)      # layers and attention: every bit
+        a, _ = sapo.sapo_score_logprobs(gw, few, mask[:n].contiguous(), rewards[:n].contiguous(), 1)
+        # the log-sum-exp is added up in other groups: a few units in the last place of a value below 16
+        assert float((a - lp[:n]).abs().max()) <= 4 * 2.0 ** -20
+        again, _ = sapo.sapo_score_logprobs(gw, few, mask[:n].contiguous(), rewards[:n].contiguous(), 1)
+        assert torch.equal(a, again)
+    gw.close()
