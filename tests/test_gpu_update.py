@@ -477,3 +477,43 @@ def test_update_of_a_few_tokens(sapo, S, T, pieces, grad_tol, logp_tol):
     for i, (g, b) in enumerate(zip(read_all(sapo, tr, 1), ref_g)):
         assert float(np.max(np.abs(g - b))) <= grad_tol * max(float(np.max(np.abs(b))), 1e-3 * gmax) + 1e-7, i
     tr.close()
+
+
+def reference_on_gpu(shape, params, tokens, mask, logp_old, adv):
+    """The oracle's forward and loss with its float64 tensors on the GPU, for sets the CPU takes minutes for: (loss,
+    logp_new, gradients)."""
+    import torch
+    from oracle import sapo_update_oracle as U
+    with torch.device("cuda"):
+        p = [torch.tensor(np.asarray(a), dtype=torch.float64, requires_grad=True) for a in params]
+        mk = torch.tensor((mask != 0).astype(np.float64))
+        lp = torch.stack([U._sequence_logprobs(shape, p, t) for t in tokens]) * mk
+        loss = U._surrogate(lp, torch.tensor(logp_old.astype(np.float64)), mk, torch.tensor(adv.astype(np.float64)), 0.2, 0.28)
+        loss.backward()
+    return float(loss.detach()), lp.detach().cpu().numpy(), [t.grad.cpu().numpy() for t in p]
+
+
+# 4600 rows: two chunks of the embedding gradient's sort, the second a partial one; 4096: exactly one; 66560 rows: above the
+# grid's limit of the vectorised SwiGLU kernels
+@pytest.mark.parametrize("S,T,masked", [(20, 230, 60), (32, 128, 40), (260, 256, 12)])
+def test_update_of_many_rows(sapo, S, T, masked):
+    import torch
+    shape = SHAPES["tiny"]
+    from oracle import sapo_update_oracle as U
+    w = W.perturb_norm_gains(W.make_weights(shape, 31, std=0.1), 31)
+    params = U.parameter_list(shape, w)
+    rng = np.random.default_rng([31, S])
+    tokens = np.minimum(rng.geometric(0.02, size=(S, T)) - 1, shape.vocab - 1).astype(np.int32)   # long and short runs of a token
+    mask = W.make_completion_mask(S, T, masked)
+    adv = rng.standard_normal(S).astype(np.float32)
+    _, lp0, _ = reference_on_gpu(shape, params, tokens, mask, np.zeros((S, T), np.float32), adv)
+    logp_old = (lp0 + rng.uniform(-0.15, 0.15, size=lp0.shape) * (mask != 0)).astype(np.float32)   # clear of the clip bounds
+    ref_loss, ref_lp, ref_g = reference_on_gpu(shape, params, tokens, mask, logp_old, adv)
+    tr = sapo.sapo_trainer_create(shape, w)
+    loss, lp = sapo.sapo_policy_update(tr, dev(tokens), dev(mask), dev(logp_old), dev(adv))
+    torch.cuda.synchronize()
+    assert np.max(np.abs(lp.cpu().numpy() - ref_lp)) < 2e-4 and abs(float(loss.cpu()[0]) - ref_loss) < 1e-4
+    gmax = max(float(np.max(np.abs(x))) for x in ref_g)
+    for i, (g, b) in enumerate(zip(read_all(sapo, tr, 1), ref_g)):
+        assert float(np.max(np.abs(g - b))) <= 2e-4 * max(float(np.max(np.abs(b))), 1e-3 * gmax) + 1e-7, i
+    tr.close()
