@@ -531,9 +531,12 @@ hipError_t d_gemm_skinny(const SkinnyArgs& a, int mode, hipStream_t st) {
   if (a.n_rows <= kFewRows) {
     if (mode == SKM_SWIGLU) return a.N % 32 == 0 ? launch_few_r<16, SKM_SWIGLU>(a, st) : hipErrorInvalidValue;
     if (mode == SKM_STORE) return launch_few_r<16, SKM_STORE>(a, st);
-    // half tiles when whole ones would occupy less than a quarter of the compute units and each is long (0.5B down:
-    // 56 tiles of 155 KB; the 1.5B one, 96 tiles of 287 KB, was slower in halves: 52.7 against 51.0 ms per call of 8 rows)
-    return a.N <= 1024 && per_wave > 8 ? launch_few_r<8, SKM_RESID>(a, st) : launch_few_r<16, SKM_RESID>(a, st);
+    // Half tiles where twice the workgroups, with those that prefetch, still have a compute unit each, and a tile is long.
+    // 24 layers, us per layer against whole tiles at 16 rows (1 .. 8 rows: within 0.1 either way): 56 tiles of 155 KB -0.24,
+    // of 287 KB -0.52, 80 tiles of 287 KB -0.76 (160 + 56 workgroups); 96 tiles +0.9 .. +1.8 (192 + 72: some compute
+    // units get two).
+    const int halves = 2 * ((tiles + 7) / 8 * 8) + prefetch_blocks(a.pf, 8) + prefetch_blocks(a.pf2, 8);
+    return halves <= 256 && per_wave > 8 ? launch_few_r<8, SKM_RESID>(a, st) : launch_few_r<16, SKM_RESID>(a, st);
   }
   const int groups = multi ? 4 : (a.n_rows + 15) / 16;   // 16-token groups of a block that hold rows (2 .. 4)
   if (mode == SKM_SWIGLU) {

@@ -19,6 +19,8 @@ SHAPES = {
     "mini": W.MINI_BF16,
     # down projection long enough for half tiles; tile counts that are no multiple of 8
     "long_ffn": replace(W.MINI_BF16, d_model=384, d_ff=2368, n_layers=3),
+    # the widest output in half tiles, next to the prefetching workgroups
+    "wide_ffn": replace(W.MINI_BF16, d_model=1280, n_q_heads=20, d_ff=2368),
     # d > 1024: gate/up in units of two tiles, the token-parallel LM head
     "wide": replace(W.MINI_BF16_HD128, d_model=1152, d_ff=640),
 }
