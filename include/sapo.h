@@ -308,14 +308,14 @@ int sapo_clipped_surrogate(const float* logp_new, const float* logp_old, const u
  * sapo_clipped_surrogate for callers that cannot allocate device memory and have no workspace to hand over: code
  * under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments without the
  * workspace, same kernels, same results bit for bit.  The call allocates nothing (no hipMalloc / hipFree, no
- * allocating library routine): its scratch (256 block partials and the totals, 4112 bytes) is a file-scope
+ * allocating library routine): its scratch (256 block partials, 4112 bytes with a spare slot) is a file-scope
  * device array of the library, one copy per GPU, held until the process ends; its address is looked up on the
  * first call on a device.  The caller still passes inputs and outputs (device pointers).
  *   S * T at most SAPO_SURROGATE_NOALLOC_MAX_TOKENS; larger inputs are rejected with SAPO_EINVAL (as are NULL buffers,
  *   non-positive sizes and clip bounds out of range); SAPO_EHIP when the array's address cannot be obtained.
- * Every call on a GPU uses that GPU's one array (each call overwrites all of it before reading it, so nothing
- * carries over from the previous call): two calls that overlap in time on one GPU - different streams or
- * threads - race; run them in order.
+ * Every call on a GPU uses that GPU's one array (a call of more tokens than one launch takes overwrites the
+ * partials before reading them, a smaller one leaves them alone, so nothing carries over): two calls that
+ * overlap in time on one GPU - different streams or threads - race; run them in order.
  */
 #define SAPO_SURROGATE_NOALLOC_MAX_TOKENS (1L << 28)
 int sapo_clipped_surrogate_noalloc(const float* logp_new, const float* logp_old, const uint8_t* completion_mask,

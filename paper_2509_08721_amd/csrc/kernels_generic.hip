@@ -547,14 +547,17 @@ hipError_t g_advantages(const float* rewards, int S, int G, float* out, hipStrea
 // these kernels: launches and dependent round trips are what they cost.
 // Few tokens: one launch.  Block 0 sums the loss over all tokens; block b > 0 writes the gradient of its 1024 tokens
 // and counts the masked tokens of the whole set by itself (n mask bytes out of the L2, 16 at a time).  The instructions
-// of block 0's terms on its one CU bound it, 0.25 us per 1024 tokens with groups of four to a load (addresses, row
-// steps and mask once per group) and 0.41 us one by one: 64 x 384 tokens 10.4 -> 6.5 us, launched back to back.
+// of block 0's terms on its one CU bound it, 0.19 us per 1024 tokens with groups of four to a load (addresses, row
+// steps and mask once per group) and 0.29 us one by one.
 // More tokens: they are summed by kLossBlocks blocks into slots, and every block of the second kernel adds the slots
-// again (4 KB, the same order) instead of waiting for a third; 5.7 us up to 100k tokens, which is what two launches cost
-// the host.  The line lies where the one launch takes what a second one costs it more, with a caller that has work of
-// its own between two calls: 24576 tokens by four, 14336 one by one.
+// again (4 KB, the same order) instead of waiting for a third: 5.1 us on the device at any size up to 49152 tokens.
+// The line.  A call costs the host 8.2 us with one launch and 10.6 with two, so which form is faster depends on what the
+// caller waits for.  By four / one by one, the one launch is the faster form up to: 16.5k / 10.5k tokens where only the device's
+// time counts (queue full: 5.1 us each), 22k / 16k where the caller waits for every call (21.4 us each), 46k / 32k where
+// calls follow each other.  The line is 1.5 times the first: there the one launch loses 1.5 us behind a full queue and 0.4 /
+// 0 us for a caller that waits, and gains 2.4 us for one that does not.
 constexpr int kLossBlocks = 256;
-constexpr size_t kSurrogateOneLaunch = 24576, kSurrogateOneLaunchBy1 = 14336;
+constexpr size_t kSurrogateOneLaunch = 24 * 1024, kSurrogateOneLaunchBy1 = 16 * 1024;
 struct LossPartial { double sum; long long count; };
 
 // (sum, count) over the THREADS threads of a block, in every thread; the order of additions is fixed
@@ -589,7 +592,8 @@ __device__ __forceinline__ void surrogate_walk(const float* __restrict__ logp_ne
   unsigned t = first - s * T;
   const unsigned ds = stride / T, dt = stride - ds * T;
   unsigned cnt = 0;
-#pragma unroll (V == 4 ? 4 : 8)
+  constexpr int U = V == 4 ? 4 : 8;
+#pragma unroll U
   for (unsigned i = first; i < end; i += stride) {
     float ln[V], lo[V], rho;
     unsigned m;
@@ -710,10 +714,10 @@ hipError_t g_surrogate_loss(const float* logp_new, const float* logp_old, const 
 
 // ---------------------------------------------------------------------------------------
 // The same kernels for callers that cannot allocate (code under graph capture, serving loops, harnesses that
-// forbid hipMalloc): the block partials and the totals live in a file-scope device array instead of a workspace.
+// forbid hipMalloc): the block partials live in a file-scope device array instead of a workspace.
 // Every device holds its own copy of the array; its address is looked up once per device, with that device
-// current, and kept.  All 256 partial slots and the totals slot are overwritten by every call before they are
-// read, so nothing has to be cleared between calls; two calls that overlap on one device share the array and race.
+// current, and kept.  A call of two launches overwrites all 256 slots before it reads them and a call of one launch touches
+// none, so nothing has to be cleared between calls; two calls that overlap on one device share the array and race.
 // ---------------------------------------------------------------------------------------
 static __device__ __align__(256) unsigned char scratch[(kLossBlocks + 1) * sizeof(LossPartial)];   // 4112 bytes per device
 

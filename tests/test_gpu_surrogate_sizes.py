@@ -9,9 +9,9 @@ from tests.test_gpu_surrogate import case, run_and_check
 pytestmark = pytest.mark.gpu
 
 
-# 24576 and 14336 tokens (rows of whole groups of four, other rows): the last sizes of the single launch; 1023 .. 1025:
+# 24576 and 16384 tokens (rows of whole groups of four, other rows): the last sizes of the single launch; 1023 .. 1025:
 # edges of a gradient block; odd sizes: mask remainders
-@pytest.mark.parametrize("S,T", [(1, 15), (1, 17), (11, 93), (1, 1024), (5, 205), (64, 384), (3, 8196), (64, 512), (23, 623), (2, 7169), (57, 575), (8, 4097), (300, 129)])
+@pytest.mark.parametrize("S,T", [(1, 15), (1, 17), (11, 93), (1, 1024), (5, 205), (64, 384), (3, 8196), (64, 512), (23, 623), (2, 7169), (57, 575), (8, 4097), (300, 129), (8192, 2), (5462, 3)])
 def test_surrogate_sizes(S, T):
     run_and_check(*case(S, T, 100 + S))
 
