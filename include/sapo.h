@@ -213,6 +213,9 @@ int sapo_rollout_generate_ragged(const sapo_weights* w, const int32_t* prompts, 
  *                                       (r - mean) / (population std + 1e-6); exactly 0 for a
  *                                       group whose rewards are all equal
  * Requires S % G == 0, T <= cfg.max_seq.
+ * The same call gives the same bits.  A sequence's logits do not depend on how many others are scored
+ * with it; the sum of their exponentials is cut by the number of tokens in the call, so its log-probs may
+ * differ in the last bits between calls of different size.
  */
 int sapo_score_logprobs(const sapo_weights* w, const int32_t* tokens,
                         const uint8_t* completion_mask, const float* rewards, int S, int T, int G,
@@ -369,10 +372,14 @@ size_t sapo_trainer_workspace_bytes_for(const sapo_trainer* tr, int S, int T, in
  *                    additions.  SAPO_EWORKSPACE if not even one sequence fits.
  * fp32 values throughout (the large matrix products are formed from bf16 pieces on the matrix cores
  * with the accuracy of fp32 products), every sum in a fixed order (no atomics): the same call on the
- * same state gives the same bits.  The LM head runs only on the rows that predict a masked token; the host
- * sizes its products from their number, so the call waits once, at its start, for a small kernel that lists
- * them (and for whatever `stream` held before); everything else is enqueued and the call returns before the
- * update has finished.  The trainer's state is updated in place, so calls on one trainer must not overlap.  Errors: SAPO_EINVAL (NULL, sizes, eps), SAPO_EWORKSPACE.
+ * same state gives the same bits.  How the sums are cut depends on the size of the set (and of the
+ * micro-batch): with three pieces (sapo_trainer_set_matmul_pieces) a sequence's log-probs may differ in
+ * their last bits between sets of different size, with two and one they do not; gradients may with any.
+ * The LM head runs only on the rows that predict a masked token; the host sizes its products from their
+ * number, so the call waits once, at its start, for a small kernel that lists them (and for whatever
+ * `stream` held before); everything else is enqueued and the call returns before the update has finished.
+ * The trainer's state is updated in place, so calls on one trainer must not overlap.
+ * Errors: SAPO_EINVAL (NULL, sizes, eps), SAPO_EWORKSPACE.
  */
 int sapo_policy_update(sapo_trainer* tr, const int32_t* tokens, const uint8_t* completion_mask,
                        const float* logp_old, const float* advantages, int S, int T, float eps_low,

@@ -149,8 +149,11 @@ __device__ __forceinline__ Philox4 philox4x32_10(uint32_t c0, uint32_t c1, uint3
 // inside (0, 1) and exact in fp32; g = -ln(-ln u).
 // Four values took 712 cycles of a wave, 411 of them in the logarithms, which is what bounded the LM head of 65 and more
 // rows (118 us per step at 192 rows of the 0.5B decoder).  The arguments here are normal numbers (u >= 2^-24,
-// 2^-24 < -ln u < 17), so the logarithm needs no range handling: log2 of the hardware times ln 2 as a two-part
-// constant.  Equal to logf in every bit for all 2^23 values of u; 480 cycles.
+// 2^-24 < -ln u < 17), so the logarithm needs no range handling: 480 cycles.
+// ln x = y ln 2 with y = log2 x of the hardware.  ln 2 = 0x1.62e42fefa39efp-1 is taken as c + c_low: its leading 23 bits and,
+// rounded, the rest.  r = y c is rounded; fma(y, c, -r) is exactly what that rounding dropped (the two-product of an fma),
+// and y c_low joins it before the one addition to r.  logf of AMD's open device library splits ln 2 the same way, and the
+// result equals it in every bit for all 2^23 values of u.
 __device__ __forceinline__ float ln_normal(float x) {
   constexpr float c = 0x1.62e42ep-1f, c_low = 0x1.efa39ep-25f;   // ln 2 = 0x1.62e42fefa39efp-1
   const float y = __builtin_amdgcn_logf(x), r = y * c;
