@@ -498,9 +498,9 @@ def run_workload(args, workload, n_steps, n_warmup, cpu_baseline, probes):
             torch.cuda.synchronize()
             lm.append(ev[0].elapsed_time(ev[1]))
         l_ms = float(np.median(lm))
-        l_bytes = S_score * T * (4 + 4 + 1 + 4 + 1) + S_score * Tm * (4 + 4)   # mask twice, logp pair twice where set, gradient out
+        l_bytes = S_score * T * (4 + 4 + 1 + 4) + 4 * S_score                  # two log-probs, mask, gradient; advantages
         surrogate = {"ms": round(l_ms, 4), "algorithmic_bytes": l_bytes, "GBs": round(l_bytes / (l_ms * 1e-3) / 1e9, 2),
-                     "note": "three dependent launches on under 2 MB: launch-latency-bound, not a roofline case"}
+                     "note": "one launch (two above 24576 tokens) on under 2 MB: launch-latency-bound, not a roofline case"}
 
     gen_tokens = S * N if do_rollout else 0
     scored_tokens = S_score * T if do_score else 0
