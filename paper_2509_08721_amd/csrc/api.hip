@@ -280,13 +280,14 @@ static bool small_eligible(const sapo_weights* w) {
   const double step_us = bytes / 80e3 + 5.0 * c.n_layers + 3.0, launches_us = 5.0 * (11.0 * c.n_layers + 4.0);
   return 2.0 * step_us <= launches_us;
 }
-// Is a rollout call cheaper on the small path?  256 workgroups run at once, so a step there costs rounds of 256 sequences,
-// while the generic path's launches are shared by the whole batch and only its work grows.  Estimates in us, fitted to
-// 280 comparisons of the two paths on seven decoders (1 .. 8 layers, d 32 .. 128, vocabulary 256 .. 6000), 64 .. 16384 sequences, contexts of
-// 4 .. 270 tokens; above 512 sequences they name the faster path in all but 13, the two of which are within 15 % of each
-// other in 12.  Both sides at 2 layers, d 64, vocabulary 512 (us per step, contexts of 28): small 109 / 217 / 433 / 868 at
-// 1536 / 3072 / 6144 / 12288 sequences, generic 218 / 254 / 314 / 447.  Scoring stays on the small path whatever the
-// batch: its tiles of 16 rows cost 0.2 .. 0.6 of the generic kernels at every size measured (up to 262144 tokens).
+// Is a rollout call cheaper on the small path?  256 workgroups run at once, so a step there costs rounds of 256
+// sequences, while the generic path's launches are shared by the whole batch and only its work grows.  Estimates in us,
+// fitted to 280 comparisons of the two paths on seven decoders (1 .. 8 layers, d 32 .. 128, vocabulary 256 .. 6000), 64 ..
+// 16384 sequences, contexts of 4 .. 270 tokens; above 512 sequences they name the faster path in all but 13, and in 12 of
+// those the two are within 15 % of each other.  Both sides at 2 layers, d 64, vocabulary 512 (us per step, contexts of
+// 28): small 109 / 217 / 433 / 868 at 1536 / 3072 / 6144 / 12288 sequences, generic 218 / 254 / 314 / 447.  Scoring stays
+// on the small path whatever the batch: its tiles of 16 rows cost 0.2 .. 0.6 of the generic kernels at every size measured
+// (up to 262144 tokens).
 static bool small_pays(const sapo_model_config& c, int P, int Lp, int G, int N) {
   const double S = (double)P * G;
   if (S <= 512) return true;
