@@ -301,6 +301,10 @@ static bool small_pays(const sapo_model_config& c, int P, int Lp, int G, int N) 
                             S * (N * 5.6e-5 * head + (N - 1) * (5.6e-5 * layers + 3e-6 * L * q * ctx));
   return small_us <= generic_us;
 }
+static bool capturing(hipStream_t st) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  return st != nullptr && hipStreamIsCapturing(st, &status) == hipSuccess && status != hipStreamCaptureStatusNone;
+}
 static int upload_small_table(sapo_weights* w) {
   const int L = w->cfg.n_layers;
   std::vector<SmallLayer> tbl(L);
@@ -910,7 +914,8 @@ static int rollout_impl(const sapo_weights* w, const int32_t* prompts, const int
   if (w->small_tbl) {
     // the cache of this path holds P Lp + S N positions in a row: no more than the pages carved for the call
     const SmallModel m = small_model(w, pl.cache);
-    if (small_pays(c, P, Lp, G, max_new) && small_prefill_fits(m, Lp) && small_decode_fits(m, Lp + max_new) &&
+    // (under the caller's stream capture always: its launches can be recorded, the generic path captures a step of its own)
+    if ((small_pays(c, P, Lp, G, max_new) || capturing(st)) && small_prefill_fits(m, Lp) && small_decode_fits(m, Lp + max_new) &&
         small_rows_fit(m, (size_t)P * Lp + (size_t)S * max_new, (size_t)P * Lp, std::max((size_t)P * Lp, (size_t)S * max_new))) {
       if (ragged) HIP_CK(hipMemcpyAsync(pl.lens, lens_host, (size_t)P * sizeof(int), hipMemcpyHostToDevice, st));
       SmallPrefill pa{};

@@ -112,3 +112,32 @@ def test_large_batches_leave_the_small_path():
     # long prompts and few steps: the prompts' tiles decide, and they are cheaper on the small path
     long = torch.from_numpy(rng.integers(0, shape.vocab, (1024, 200)).astype(np.int32)).cuda()
     assert kernels_of(lambda: sapo.sapo_rollout_generate(small, long, 1, 2, 1.0, 5)) == {"k_small"}
+
+
+def test_large_batches_can_be_captured():
+    """Under the caller's stream capture a large batch stays on the small path, whose launches can be recorded; replays
+    repeat the eager call's tokens."""
+    shape = W.TINY
+    small, _ = handles(shape, 15)
+    rng = np.random.default_rng(10)
+    P, G, N = 1536, 8, 6
+    prompts = torch.from_numpy(rng.integers(0, shape.vocab, (P, 5)).astype(np.int32)).cuda()
+    ws = torch.empty(sapo.sapo_rollout_workspace_bytes(small, P, 5, G, N) + 256, dtype=torch.uint8, device="cuda")
+    tok = torch.empty((P * G, N), dtype=torch.int32, device="cuda")
+    lp = torch.empty((P * G, N), device="cuda")
+    call = lambda: sapo.sapo_rollout_generate(small, prompts, G, N, 1.0, 5, workspace=ws, out_tokens=tok, out_logprobs=lp)
+    sapo.sapo_rollout_generate(small, prompts[:2].contiguous(), G, N, 1.0, 5)
+    call()
+    want = tok.clone(), lp.clone()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call()
+    for _ in range(3):
+        tok.zero_(); lp.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(tok, want[0]) and float((lp - want[1]).abs().max()) <= 2e-5
+        call()                                      # the program's own eager call between two replays
+        torch.cuda.synchronize()
+        assert torch.equal(tok, want[0])
