@@ -71,7 +71,7 @@ def per_launch_work(shape, plan, kernel, launches):
     if kernel == "k_decode_layers":     # every layer of a decode step in one launch: the layers' matrices + the cached K/V
         kv = 2 * shape.kv_dim * 2 * L * S * sum(Lp + t for t in range(1, N))
         return "hbm", (2.0 * shape.matmul_params_per_layer() * L * dec_steps + kv) / launches
-    if kernel == "k_gemm_big_decode":   # gate/up and down projections of a decode layer on the token-parallel kernel
+    if kernel == "k_gemm_rows":   # gate/up and down projections of a decode layer with 65 .. 256 rows
         return "hbm", 2.0 * ffn_params * L * dec_steps / launches
     if kernel == "k_lmhead_sample":     # LM head of one decode step: the whole [V, d] matrix
         return "hbm", 2.0 * V * d

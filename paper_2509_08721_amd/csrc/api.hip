@@ -76,7 +76,7 @@ void prof_events(int kid, hipEvent_t* e0, hipEvent_t* e1) {
 static const char* const kKernelNames[KID_COUNT] = {
     "k_embed", "k_rmsnorm", "k_gemm", "k_rope_append", "k_attention", "k_swiglu", "k_sample_rows", "k_score_rows",
     "misc", "k_gemm_big", "k_lmhead_score", "k_lmhead_score_merge", "k_gemm_skinny", "k_lmhead_sample",
-    "k_lmhead_sample_merge", "k_decode_attention", "k_flash_attention", "k_gemm_big_decode", "k_decode_layers", "k_decode_attention_shared", "k_small"};
+    "k_lmhead_sample_merge", "k_decode_attention", "k_flash_attention", "k_gemm_rows", "k_decode_layers", "k_decode_attention_shared", "k_small"};
 
 extern "C" int sapo_profile_kernel_count(void) { return KID_COUNT; }
 extern "C" const char* sapo_profile_kernel_name(int i) { return (i >= 0 && i < KID_COUNT) ? kKernelNames[i] : ""; }
@@ -347,13 +347,13 @@ static int create_impl(sapo_weights* w, const void* const* t, hipStream_t st) {
     HIP_CK(copy(lw.attn_norm, lt[0], d * 4));
     HIP_CK(copy(lw.ffn_norm, lt[5], d * 4));
     if (w->mfma) {
-      HIP_CK(m_pack_weight(lt[1], (int)q, (int)d, lw.wqkv, 0, 1, w->pack_range, st));
-      HIP_CK(m_pack_weight(lt[2], (int)kv, (int)d, lw.wqkv, (int)(q / 32), 1, w->pack_range, st));
-      HIP_CK(m_pack_weight(lt[3], (int)kv, (int)d, lw.wqkv, (int)((q + kv) / 32), 1, w->pack_range, st));
-      HIP_CK(m_pack_weight(lt[4], (int)d, (int)q, lw.wo, 0, 1, w->pack_range, st));
-      HIP_CK(m_pack_weight(lt[6], (int)F, (int)d, lw.wgu, 0, 2, w->pack_range, st));
-      HIP_CK(m_pack_weight(lt[7], (int)F, (int)d, lw.wgu, 1, 2, w->pack_range, st));
-      HIP_CK(m_pack_weight(lt[8], (int)d, (int)F, lw.wdown, 0, 1, w->pack_range, st));
+      HIP_CK(m_pack_weight(lt[1], (int)q, (int)d, lw.wqkv, 0, 0, w->pack_range, st));
+      HIP_CK(m_pack_weight(lt[2], (int)kv, (int)d, lw.wqkv, (int)(q / 32), 0, w->pack_range, st));
+      HIP_CK(m_pack_weight(lt[3], (int)kv, (int)d, lw.wqkv, (int)((q + kv) / 32), 0, w->pack_range, st));
+      HIP_CK(m_pack_weight(lt[4], (int)d, (int)q, lw.wo, 0, 0, w->pack_range, st));
+      HIP_CK(m_pack_weight(lt[6], (int)F, (int)d, lw.wgu, 0, 1, w->pack_range, st));
+      HIP_CK(m_pack_weight(lt[7], (int)F, (int)d, lw.wgu, 0, 2, w->pack_range, st));
+      HIP_CK(m_pack_weight(lt[8], (int)d, (int)F, lw.wdown, 0, 0, w->pack_range, st));
       if ((rc = dev_alloc(w, (q + 2 * kv) * d * e, &lw.wqkv16))) return rc;
       if ((rc = dev_alloc(w, d * q * e, &lw.wo16))) return rc;
       if ((rc = dev_alloc(w, 2 * F * d * e, &lw.wgu16))) return rc;
@@ -380,7 +380,7 @@ static int create_impl(sapo_weights* w, const void* const* t, hipStream_t st) {
   HIP_CK(copy(w->final_norm, tail[0], d * 4));
   if (w->mfma) {
     if ((rc = dev_alloc(w, V * d * e, &w->lm_head))) return rc;
-    HIP_CK(m_pack_weight(c.tied_embeddings ? t[0] : tail[1], (int)V, (int)d, w->lm_head, 0, 1, w->pack_range, st));
+    HIP_CK(m_pack_weight(c.tied_embeddings ? t[0] : tail[1], (int)V, (int)d, w->lm_head, 0, 0, w->pack_range, st));
     if ((rc = dev_alloc(w, V * d * e, &w->lm_head16))) return rc;
     HIP_CK(d_pack_weight16(c.tied_embeddings ? t[0] : tail[1], (int)V, (int)d, w->lm_head16, 0, 1, st));
   } else if (c.tied_embeddings) {
@@ -624,21 +624,12 @@ struct DecodeBufs {
   void* xb;         // X16 [s_pad, d]: input of the gate/up projection
   float* ssq_a;     // [d/16][s_pad] sums of squares behind xa
   float* ssq_b;     // [d/16][s_pad] sums of squares behind xb
-  // more than 64 sequences: the FFN runs on the token-parallel GEMM, the down projection split over K
-  int down_splits;  // 0: not used
-  float* partial;   // [down_splits][S, d]
+  // 65 .. 256 sequences: the FFN runs on the kernels of kernels_rows.hip
+  bool rows;
+  float* partial;   // parts of the down projection
   // up to 64 sequences: the layers of a step run as one persistent kernel (decode_persist.hip)
   bool persistent;
 };
-
-// Splits of the down projection's K: a multiple of 8 (one residue class per XCD) that brings the grid to about
-// 200 workgroups and leaves every split at least 4 stages of 32 k.
-static int pick_down_splits(int d, int F) {
-  const int tiles = d / 128, nst = F / 32;
-  int s = 8;
-  while (tiles * (s + 8) <= 224 && nst / (s + 8) >= 4) s += 8;
-  return nst >= s ? s : 0;
-}
 
 static void carve_decode(Arena& A, const sapo_weights* w, int S, DecodeBufs& db) {
   const size_t d = w->cfg.d_model;
@@ -647,17 +638,13 @@ static void carve_decode(Arena& A, const sapo_weights* w, int S, DecodeBufs& db)
   db.xb = A.take_bytes((size_t)db.s_pad * d * 2);
   db.ssq_a = A.take<float>((d / 16) * db.s_pad);
   db.ssq_b = A.take<float>((d / 16) * db.s_pad);
-  db.down_splits = 0;
-  db.partial = nullptr;
+  db.rows = S > 64 && S <= 256;
+  db.partial = db.rows ? A.take<float>(r_down_partial_floats(S, (int)d)) : nullptr;
   // opt-in: measured slower than one kernel per phase on the 0.5B-class decoder
   const char* persist = getenv("SAPO_PERSIST");
   db.persistent = (persist && persist[0] == '1') && w->persist_tbl != nullptr &&
                   d_decode_layers_supported(S, (int)d, w->cfg.n_q_heads * w->cfg.head_dim, w->cfg.n_kv_heads * w->cfg.head_dim,
                                             w->cfg.d_ff, w->cfg.head_dim, w->cfg.n_kv_heads);
-  if (S > 64 && S <= 256 && d % 128 == 0 && (2 * w->cfg.d_ff) % 128 == 0 && w->cfg.d_ff % 32 == 0) {
-    db.down_splits = pick_down_splits((int)d, w->cfg.d_ff);
-    if (db.down_splits > 0) db.partial = A.take<float>((size_t)db.down_splits * S * d);
-  }
 }
 
 // On entry b.h holds the residual rows, db.xa their X16 form for layer 0's attention norm and
@@ -685,8 +672,10 @@ static int run_layers_decode16(const sapo_weights* w, const FwdBufs& b, const De
   // Which launch carries the prefetch of which weights: attention, which leaves most compute units idle, gate/up's;
   // gate/up (152 .. 304 workgroups) down's; down the next layer's QKV and O.  In QKV and O, 3 us each with hardly any
   // bytes of their own, any prefetch lengthened the launch by more than it saved (50.2 against 46.8 ms per call).  With
-  // more than 64 rows gate/up's and down's weights are not prefetched: attention fills the chip there, and the
-  // token-parallel GEMM waits for its stages rather than for HBM (1.5B, 256 rows: 71.9 against 69.3 ms per call).
+  // more than 64 rows only QKV's weights are prefetched: attention fills the chip there, and gate/up's in its launch took
+  // the step from 928 to 995 us at 96 rows, 1106 to 1127 at 192 (0.5B), 2162 to 2269 at 256 (1.5B); down's in gate/up's
+  // changed nothing (930, 1135, 2191).
+  const int down_parts = db.rows ? r_down_parts(d) : d / 16;
   for (int l = 0; l < c.n_layers; ++l) {
     const LayerWeights& lw = w->layers[l];
     const KVCache kvc = layer_cache(w, cb, l);
@@ -694,7 +683,7 @@ static int run_layers_decode16(const sapo_weights* w, const FwdBufs& b, const De
     a.n_rows = S; a.s_pad = db.s_pad; a.eps = c.rms_eps; a.norm_dim = d;
     // QKV projection of the attention-normed residual
     a.Wp = (const uint4*)lw.wqkv16; a.Xp = (const uint4*)db.xa; a.N = nqkv; a.K = d;
-    a.ssq_in = db.ssq_a; a.ssq_parts = (l == 0) ? 1 : db.down_splits > 0 ? (d + 1023) / 1024 : d / 16;
+    a.ssq_in = db.ssq_a; a.ssq_parts = (l == 0) ? 1 : down_parts;
     a.out_f32 = b.qkv; a.ldc = nqkv; a.bias = lw.bqkv;
     HIP_CK(d_gemm_skinny(a, SKM_STORE, st));
     ShareArgs sh_l;
@@ -706,22 +695,13 @@ static int run_layers_decode16(const sapo_weights* w, const FwdBufs& b, const De
     o.n_rows = S; o.s_pad = db.s_pad;
     o.Wp = (const uint4*)lw.wo16; o.Xp = (const uint4*)b.attn; o.N = d; o.K = q;
     o.h = b.h; o.gain_next = lw.ffn_norm; o.xp_out = (uint4*)db.xb; o.ssq_out = db.ssq_b;
-    HIP_CK(d_gemm_skinny(o, SKM_RESID, st));
+    HIP_CK(d_gemm_skinny(o, db.rows ? SKM_RESID_X32 : SKM_RESID, st));
     const float* gain_after = (l + 1 < c.n_layers) ? w->layers[l + 1].attn_norm : w->final_norm;
-    if (db.down_splits > 0) {
-      // many sequences: the register-direct GEMMs re-read the token operand once per workgroup and are
-      // ingest-bound here; the FFN goes through the LDS-staged token-parallel GEMM instead (256-token tiles),
-      // the down projection split over K with its partial sums added, in split order, by a row kernel
-      HIP_CK(m_rmsnorm_x32(b.h, lw.ffn_norm, c.rms_eps, b.a, S, d, nullptr, st));
-      BigEpi ge{BIG_SWIGLU, nullptr, 0, (f16*)b.act};
-      ge.decode = true;
-      HIP_CK(m_gemm_big(b.a, lw.wgu, S, 2 * F, d, ge, st));
-      BigEpi pe{BIG_STORE_F32, db.partial, d, nullptr};
-      pe.splits = db.down_splits; pe.split_stride = (size_t)S * d; pe.decode = true;
-      if (l + 1 < c.n_layers) pe.pf = d_prefetch_skinny(w->layers[l + 1].wqkv16, S, SKM_STORE, nqkv, d);
-      HIP_CK(m_gemm_big(b.act, lw.wdown, S, d, F, pe, st));
-      HIP_CK(d_resid_finish_x16(db.partial, db.down_splits, (size_t)S * d, b.h, gain_after, S, d, db.s_pad, db.xa, db.ssq_a,
-                                st));
+    if (db.rows) {
+      HIP_CK(r_gate_up(db.xb, lw.wgu, db.ssq_b, d_skinny_units(S, SKM_RESID_X32, d, q), db.s_pad, S, F, d, c.rms_eps, b.act, st));
+      Prefetch next;
+      if (l + 1 < c.n_layers) next = d_prefetch_skinny(w->layers[l + 1].wqkv16, S, SKM_STORE, nqkv, d);
+      HIP_CK(r_down(b.act, lw.wdown, S, d, F, db.partial, b.h, gain_after, db.s_pad, db.xa, db.ssq_a, next, st));
       continue;
     }
     // gate / up projections + SwiGLU
@@ -932,7 +912,7 @@ static int rollout_impl(const sapo_weights* w, const int32_t* prompts, const int
     }
   }
   auto parts_after_layers = [&](const RolloutPlan::Level& lv) {
-    return c.n_layers == 0 ? 1 : (w->mfma && lv.dec.down_splits > 0) ? (d + 1023) / 1024 : d / 16;
+    return c.n_layers == 0 ? 1 : d / 16;
   };
 
   SampleParams sp;

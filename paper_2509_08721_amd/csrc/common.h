@@ -233,7 +233,7 @@ struct SampleParams {
 enum KernelId {
   KID_EMBED = 0, KID_RMSNORM, KID_GEMM_GENERIC, KID_ROPE_APPEND, KID_ATTN_GENERIC, KID_SWIGLU, KID_SAMPLE_ROWS,
   KID_SCORE_ROWS, KID_MISC, KID_GEMM_BIG, KID_LMHEAD_SCORE, KID_LMHEAD_SCORE_MERGE, KID_GEMM_SKINNY,
-  KID_LMHEAD_SAMPLE, KID_LMHEAD_SAMPLE_MERGE, KID_DECODE_ATTN, KID_FLASH_ATTN, KID_GEMM_BIG_DECODE, KID_DECODE_LAYERS,
+  KID_LMHEAD_SAMPLE, KID_LMHEAD_SAMPLE_MERGE, KID_DECODE_ATTN, KID_FLASH_ATTN, KID_GEMM_ROWS, KID_DECODE_LAYERS,
   KID_DECODE_ATTN_SHARED, KID_SMALL, KID_COUNT
 };
 extern bool g_prof_on;
@@ -375,6 +375,8 @@ hipError_t g_gumbel(uint32_t seed_lo, uint32_t seed_hi, uint32_t seq, uint32_t s
 // =======================================================================================
 namespace sapo {
 
+int n_compute_units();   // of the current device
+
 // Weights (fragment order: tiles of KS blocks of 1 KiB) of a later launch that extra workgroups of an earlier one bring into
 // the L2s: the first ks1 blocks of every tile, the tiles of unit u (2^nt_log2 tiles) into the L2 of XCD u % 8.
 struct Prefetch {
@@ -434,6 +436,16 @@ __device__ __forceinline__ void prefetch_role(const Prefetch& pf, int block, int
   asm volatile("" ::"v"(all));   // the loads are wanted for what they leave behind
 }
 
+// uint4 index of the chunk that holds x[tok][k .. k+7] (k a multiple of 8) in X16 order.
+__host__ __device__ __forceinline__ size_t x16_chunk(int tok, int k, int KS) {
+  return ((((size_t)(tok >> 6) * KS + (k >> 5)) * 4 + ((tok >> 4) & 3)) * 64) + (tok & 15) + 16 * ((k >> 3) & 3);
+}
+
+// the same in X32 order (32-token blocks, 16 k)
+__host__ __device__ __forceinline__ size_t x32_chunk(int tok, int k, int KS) {
+  return (((size_t)(tok >> 5) * KS + (k >> 4)) * 64) + (tok & 31) + 32 * ((k >> 3) & 1);
+}
+
 struct BigEpi {
   int mode;            // see enum below
   float* out_f32;      // STORE_F32 / ADD_F32: [M, ldc]
@@ -443,13 +455,6 @@ struct BigEpi {
   // token operand holds x * gain without the row scale; the accumulators are multiplied by
   // rsqrt(sum of the row's ssq parts / norm_dim + eps) before the epilogue proper.
   const float* bias = nullptr;     // STORE_F32, optional: [N] added after the row scale
-  // Split-K (STORE_F32, M <= 256 only): split z of `splits` (a multiple of 8) covers about 1/splits of K and stores
-  // to out_f32 + z * split_stride.
-  int splits = 1;
-  size_t split_stride = 0;
-  bool decode = false;   // a launch of the decode step (weight-streaming-bound)
-  Prefetch pf;           // weights of a later launch to bring into the L2s
-  int main_blocks = 0;   // set by the launcher: the workgroups behind these prefetch
   const float* ssq_in = nullptr;   // [M, ssq_parts rounded up to a multiple of 4]; at most 16 parts
   int ssq_parts = 0;
   bool ssq_halves = false;         // every part as the two 64-feature halves it is the sum of: [M, 2 ssq_parts rounded up to a multiple of 4]
@@ -478,8 +483,8 @@ struct QkvEpi {
 hipError_t m_gemm_qkv_rope(const void* Xp, const void* Wp, int M, int N, int K, const QkvEpi& epi, hipStream_t st);
 
 constexpr int kPackRangeSlots = 512;   // pairs of range counters behind m_pack_weight's `range`
-hipError_t m_pack_weight(const void* src, int n_rows, int K, void* dst, int dst_tile0, int dst_tile_stride, unsigned* range,
-                         hipStream_t st);
+// interleave 0: 32-row tiles from dst_tile0 on; 1, 2: gate, up rows, 16 of each per tile
+hipError_t m_pack_weight(const void* src, int n_rows, int K, void* dst, int dst_tile0, int interleave, unsigned* range, hipStream_t st);
 // Xp: tokens in X32 fragment order (rows padded to a multiple of 32); Wp: weights in W32 order
 // Whether a BIG_ADD_F32 launch of this size leaves its sums of squares in halves.
 bool m_gemm_writes_halves(int M, int N);
@@ -499,8 +504,21 @@ hipError_t m_lmhead_sample_big(const void* Xp, const void* Wp, int n_rows, int V
 // q row-major, out in X32 order
 hipError_t m_flash_attention(const void* q, RowMap rm, KVCache kv, void* out, int n_seq, int n_q_heads, hipStream_t st);
 
+// FFN of a decode step of 65 .. 256 rows (kernels_rows.hip) ------------------------------------
+// Xp: rows x gain in X32 order, ssq: their sums of squares [parts][s_pad], at most 48 parts; Wp: W32 order, 16 gate and 16 up
+// rows per block; act: X32 order over F
+hipError_t r_gate_up(const void* Xp, const void* Wp, const float* ssq, int parts, int s_pad, int M, int F, int K, float eps, void* act,
+                     hipStream_t st);
+// h += X W^T; xp = half(h * gain) in X16 order, ssq: [r_down_parts(d)][s_pad].  Xp in X32 order; pf: weights of a later launch
+// that the product's launch brings into the L2s
+constexpr int kRowSplits = 8;
+int r_down_parts(int d);
+size_t r_down_partial_floats(int M, int d);
+hipError_t r_down(const void* Xp, const void* Wp, int M, int d, int K, float* partial, float* h, const float* gain, int s_pad, void* xp,
+                  float* ssq, const Prefetch& pf, hipStream_t st);
+
 // decode kernels (kernels_decode.hip) -------------------------------------------------------
-enum { SKM_STORE = 0, SKM_RESID = 1, SKM_SWIGLU = 2 };
+enum { SKM_STORE = 0, SKM_RESID = 1, SKM_SWIGLU = 2, SKM_RESID_X32 = 3 };
 struct SkinnyArgs {
   const uint4* Wp;        // weights, W16 fragment order [N/16][K/32][64]
   const uint4* Xp;        // tokens, X16 order [blocks][K/32][4][64]
@@ -524,11 +542,10 @@ struct SkinnyArgs {
 hipError_t d_pack_weight16(const void* src, int n_rows, int K, void* dst, int dst_tile0, int dst_tile_stride,
                            hipStream_t st);
 hipError_t d_gemm_skinny(const SkinnyArgs& a, int mode, hipStream_t st);
+// workgroup columns of a launch: parts of the sums of squares that RESID_X32 leaves
+int d_skinny_units(int n_rows, int mode, int N, int K);
 Prefetch d_prefetch_skinny(const void* w16, int n_rows, int mode, int N, int K);
 hipError_t d_pack_rows_x16(const float* h, const float* gain, int M, int d, void* xp, float* ssq, hipStream_t st);
-// h += sum_z partial[z] (z < splits, each [M, d], split_stride floats apart), then xp and ssq[(d + 1023) / 1024][s_pad]
-hipError_t d_resid_finish_x16(const float* partial, int splits, size_t split_stride, float* h, const float* gain, int M, int d,
-                              int s_pad, void* xp, float* ssq, hipStream_t st);
 // Row m <- the embedding of the token that sequence m (slot_seq[m] when slot_seq is given) emitted at step *step - 1
 hipError_t d_embed_x16(const int32_t* tokens, int tok_stride, const int* step, const void* embed, int M, int d,
                        const float* gain, float* h, void* xp, float* ssq, const int* slot_seq, hipStream_t st);

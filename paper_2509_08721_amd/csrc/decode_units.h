@@ -37,11 +37,6 @@ __device__ __forceinline__ f32x4 mfma16(const Frag16& a, const Frag16& b, f32x4 
 }
 __device__ __forceinline__ float silu_f(float x) { return x / (1.0f + __expf(-x)); }
 
-// uint4 index of the chunk that holds x[tok][k .. k+7] (k a multiple of 8) in X16 order.
-__host__ __device__ __forceinline__ size_t x16_chunk(int tok, int k, int KS) {
-  return ((((size_t)(tok >> 6) * KS + (k >> 5)) * 4 + ((tok >> 4) & 3)) * 64) + (tok & 15) + 16 * ((k >> 3) & 3);
-}
-
 
 struct NoWait { __device__ __forceinline__ void operator()() const {} };
 // The thread's index as a value the compiler must take as new each time: inside a kernel that walks many phases in

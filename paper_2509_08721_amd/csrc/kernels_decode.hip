@@ -39,11 +39,6 @@ __device__ __forceinline__ f32x4 mfma16(const Frag16& a, const Frag16& b, f32x4 
 }
 __device__ __forceinline__ float silu_f(float x) { return x / (1.0f + __expf(-x)); }
 
-// uint4 index of the chunk that holds x[tok][k .. k+7] (k a multiple of 8) in X16 order.
-__host__ __device__ __forceinline__ size_t x16_chunk(int tok, int k, int KS) {
-  return ((((size_t)(tok >> 6) * KS + (k >> 5)) * 4 + ((tok >> 4) & 3)) * 64) + (tok & 15) + 16 * ((k >> 3) & 3);
-}
-
 // ---------------------------------------------------------------------------------------
 // weight packing: row-major bf16 [n_rows, K] -> half, W16 order; 16-row tile t goes to tile slot
 // tile0 + t * tile_stride (stride 2 interleaves gate and up tiles).
@@ -123,6 +118,7 @@ __device__ __forceinline__ void prefetch_behind(const SkinnyArgs& a, int first) 
 //   SWIGLU : tiles come in (gate, up) pairs; act = silu(gate * scale) * (up * scale) -> half, X16 order
 //   RESID  : h[tok][feat] += acc;  xp_out = half(h * gain_next) in X16 order;  ssq_out[tile][tok] =
 //            sum of h^2 over the tile's 16 features
+//   RESID_X32 (more than 64 rows): as RESID, but X32 order, and sums of squares over all tiles of the workgroup
 // ---------------------------------------------------------------------------------------
 template <int NT, int TG, int TS, int R, int MODE>
 // The first arguments are passed one by one (and once more inside the struct): the hardware preloads the first 14 dwords
@@ -132,6 +128,7 @@ template <int NT, int TG, int TS, int R, int MODE>
 __global__ void __launch_bounds__(512) k_skinny16(const uint4* Wp_, const uint4* Xp_, const float* ssq_in_, float* h_,
                                                   const float* gain_next_, int N_, int K_, int n_rows_, int ssq_parts_,
                                                   SkinnyArgs a_rest) {
+  constexpr bool RESID = MODE == SKM_RESID || MODE == SKM_RESID_X32;
   SkinnyArgs a = a_rest;
   a.Wp = Wp_; a.Xp = Xp_; a.ssq_in = ssq_in_; a.h = h_; a.gain_next = gain_next_;
   a.N = N_; a.K = K_; a.n_rows = n_rows_; a.ssq_parts = ssq_parts_;
@@ -165,10 +162,10 @@ __global__ void __launch_bounds__(512) k_skinny16(const uint4* Wp_, const uint4*
 #pragma unroll
     for (int g = 0; g < TG; ++g) acc[t][g] = f32x4{0.f, 0.f, 0.f, 0.f};
   float sq[kSsqPerThread];
-  if (MODE != SKM_RESID) ssq_issue(a.ssq_in, a.ssq_parts, a.s_pad, tb * 64, sq);
+  if (!RESID) ssq_issue(a.ssq_in, a.ssq_parts, a.s_pad, tb * 64, sq);
   // RESID, single chunk: this thread's residual / gain operands are requested up front
   float4 h_old[RS], g_next[RS];
-  if (MODE == SKM_RESID && CH == NT) {
+  if (RESID && CH == NT) {
 #pragma unroll
     for (int i = 0; i < RS; ++i) {
       const int slot = tid + 512 * i;
@@ -212,7 +209,7 @@ __global__ void __launch_bounds__(512) k_skinny16(const uint4* Wp_, const uint4*
       }
     }
   }
-  if (MODE != SKM_RESID) ssq_publish(sq, a.ssq_parts, s_part);
+  if (!RESID) ssq_publish(sq, a.ssq_parts, s_part);
   auto sum8 = [&](int tg, int l) -> float4 {   // tg = (t - chunk start) * TG + g
     float4 s = red[(size_t)tg * 64 + l];
 #pragma unroll
@@ -299,11 +296,25 @@ __global__ void __launch_bounds__(512) k_skinny16(const uint4* Wp_, const uint4*
         } else {
           o[0] = o[1] = o[2] = o[3] = (f16)0.f;
         }
-        *(f16x4*)((f16*)a.xp_out + x16_chunk(tok, f0, a.N >> 5) * 8 + (f0 & 4)) = o;
+        const size_t chunk = MODE == SKM_RESID_X32 ? x32_chunk(tok, f0, a.N >> 4) : x16_chunk(tok, f0, a.N >> 5);
+        *(f16x4*)((f16*)a.xp_out + chunk * 8 + (f0 & 4)) = o;
         q = sum_xor16(q);
         q = sum_xor32(q);
-        if (l < 16) a.ssq_out[(size_t)(tile0 + c0 + t) * a.s_pad + tok] = q;
+        if (l < 16) {
+          if (MODE == SKM_RESID_X32) s_part[((c0 + t) * TG + g) * 16 + l] = q;
+          else a.ssq_out[(size_t)(tile0 + c0 + t) * a.s_pad + tok] = q;
+        }
       }
+    }
+  }
+  if constexpr (MODE == SKM_RESID_X32) {   // one part per unit instead of one per tile
+    static_assert(NT * TG * 16 <= 512, "parts of the unit's tiles");
+    __syncthreads();
+    if (tid < TG * 16) {
+      float q = 0.f;
+#pragma unroll
+      for (int t = 0; t < NT; ++t) q += s_part[t * TG * 16 + tid];
+      a.ssq_out[(size_t)unit * a.s_pad + tb * 64 + tg0 * 16 + tid] = q;
     }
   }
 }
@@ -509,10 +520,11 @@ static int skinny_unit_log2(int n_rows, int mode, int N, int K) {
   if (n_rows <= kFewRows) return mode == SKM_SWIGLU ? 1 : 0;
   if (n_rows <= 64) return mode != SKM_SWIGLU ? 0 : K <= 1024 ? 2 : 1;
   if (mode == SKM_SWIGLU) return tiles % 8 == 0 ? 3 : K <= 1024 ? 2 : 1;
-  if (mode == SKM_RESID && K > 2048) return tiles % 2 == 0 ? 1 : 0;
-  if (tiles % 4 != 0) return mode == SKM_RESID && tiles % 2 == 0 ? 1 : 0;
+  if (mode != SKM_STORE && K > 2048) return tiles % 2 == 0 ? 1 : 0;
+  if (tiles % 4 != 0) return mode != SKM_STORE && tiles % 2 == 0 ? 1 : 0;
   return (tiles / 4) * ((n_rows + 63) / 64) < 192 ? 1 : 2;
 }
+int d_skinny_units(int n_rows, int mode, int N, int K) { return N / 16 >> skinny_unit_log2(n_rows, mode, N, K); }
 // Prefetch of a skinny GEMM's weights by an earlier launch of a step of n_rows rows.
 Prefetch d_prefetch_skinny(const void* w16, int n_rows, int mode, int N, int K) {
   return make_prefetch(w16, K / 32, N / 16, skinny_unit_log2(n_rows, mode, N, K));
@@ -523,8 +535,8 @@ Prefetch d_prefetch_skinny(const void* w16, int n_rows, int mode, int N, int K) 
 // are latency-bound and small workgroups win (1 x 1; the gate/up pairs 4 x 4); with several blocks
 // the re-reads of the token operand dominate and the blocking goes towards square.
 hipError_t d_gemm_skinny(const SkinnyArgs& a, int mode, hipStream_t st) {
-  if (a.K % 32 != 0 || a.N % 16 != 0 || a.n_rows <= 0) return hipErrorInvalidValue;
-  if (mode != SKM_RESID && (a.ssq_in == nullptr || a.ssq_parts < 1 || a.ssq_parts > 8 * kSsqPerThread)) return hipErrorInvalidValue;
+  if (a.K % 32 != 0 || a.N % 16 != 0 || a.n_rows <= 0 || (mode == SKM_RESID_X32 && a.n_rows <= 64)) return hipErrorInvalidValue;
+  if (mode != SKM_RESID && mode != SKM_RESID_X32 && (a.ssq_in == nullptr || a.ssq_parts < 1 || a.ssq_parts > 8 * kSsqPerThread)) return hipErrorInvalidValue;
   const int per_wave = ((a.K >> 5) + 7) / 8;   // k steps per wave
   const int tiles = a.N / 16;
   const bool multi = a.n_rows > 64;
@@ -556,6 +568,11 @@ hipError_t d_gemm_skinny(const SkinnyArgs& a, int mode, hipStream_t st) {
     if (multi && tiles % 4 == 0) return launch_skinny<4, 4, 1, 3, SKM_STORE>(a, st);
     if (tg2) return per_wave <= 4 ? launch_pairs<4, SKM_STORE>(a, groups, st) : launch_pairs<8, SKM_STORE>(a, groups, st);
     return per_wave <= 4 ? launch_singles<4, SKM_STORE>(a, groups, st) : launch_singles<8, SKM_STORE>(a, groups, st);
+  }
+  if (mode == SKM_RESID_X32) {
+    if (few && per_wave <= 8) return launch_skinny<2, 4, 1, 3, SKM_RESID_X32>(a, st);
+    if (per_wave <= 8 && tiles % 4 == 0) return launch_skinny<4, 4, 1, 3, SKM_RESID_X32>(a, st);
+    return tiles % 2 == 0 ? launch_skinny<2, 2, 2, 9, SKM_RESID_X32>(a, st) : hipErrorInvalidValue;
   }
   if (few && per_wave <= 8) return launch_skinny<2, 4, 1, 3, SKM_RESID>(a, st);
   if (multi && per_wave <= 8 && tiles % 4 == 0) return launch_skinny<4, 4, 1, 3, SKM_RESID>(a, st);
@@ -603,50 +620,6 @@ __global__ void __launch_bounds__(128) k_pack_rows_x16(const float* __restrict__
 }
 hipError_t d_pack_rows_x16(const float* h, const float* gain, int M, int d, void* xp, float* ssq, hipStream_t st) {
   return launch(KID_MISC, k_pack_rows_x16, dim3(M), dim3(128), 0, st, h, gain, d, (uint4*)xp, ssq);
-}
-
-// The same after a split-K GEMM: h[row] += sum over the splits of partial[z][row] (added in split order),
-// then xp and the sums of squares of the updated row, one part per 1024 features: ssq[part][s_pad].
-// One workgroup of 128 threads per (row, 1024 features).
-__global__ void __launch_bounds__(128) k_resid_finish_x16(const float* __restrict__ partial, int splits, size_t split_stride,
-                                                          float* __restrict__ h, const float* __restrict__ gain, int d,
-                                                          int s_pad, uint4* __restrict__ xp, float* __restrict__ ssq) {
-  __shared__ float red[2];
-  const int row = blockIdx.x, k = blockIdx.y * 1024 + threadIdx.x * 8;
-  float ss = 0.f;
-  if (k < d) {
-    float v[8];
-    float* hp = h + (size_t)row * d + k;
-    const float4 a = *(const float4*)hp, b = *(const float4*)(hp + 4);
-    v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
-    // eight splits' values in flight at a time (the number of splits is a multiple of 8)
-    for (int z0 = 0; z0 < splits; z0 += 8) {
-      float4 pa[8], pb[8];
-#pragma unroll
-      for (int z = 0; z < 8; ++z) {
-        const float* pp = partial + (size_t)(z0 + z) * split_stride + (size_t)row * d + k;
-        pa[z] = *(const float4*)pp;
-        pb[z] = *(const float4*)(pp + 4);
-      }
-#pragma unroll
-      for (int z = 0; z < 8; ++z) {
-        v[0] += pa[z].x; v[1] += pa[z].y; v[2] += pa[z].z; v[3] += pa[z].w;
-        v[4] += pb[z].x; v[5] += pb[z].y; v[6] += pb[z].z; v[7] += pb[z].w;
-      }
-    }
-    *(float4*)hp = make_float4(v[0], v[1], v[2], v[3]);
-    *(float4*)(hp + 4) = make_float4(v[4], v[5], v[6], v[7]);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) ss += v[e] * v[e];
-    row_to_x16(v, gain, k, row, d >> 5, xp);
-  }
-  ss = block128_sum(ss, red);
-  if (threadIdx.x == 0) ssq[(size_t)blockIdx.y * s_pad + row] = ss;
-}
-hipError_t d_resid_finish_x16(const float* partial, int splits, size_t split_stride, float* h, const float* gain, int M, int d,
-                              int s_pad, void* xp, float* ssq, hipStream_t st) {
-  return launch(KID_MISC, k_resid_finish_x16, dim3(M, (d + 1023) / 1024), dim3(128), 0, st, partial, splits, split_stride, h,
-                gain, d, s_pad, (uint4*)xp, ssq);
 }
 
 // Embedding row of token id `tok` -> h[row] (fp32), X16 half(h * gain), ssq[row].  128 threads.

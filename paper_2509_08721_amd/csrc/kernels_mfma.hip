@@ -8,46 +8,23 @@
 // half keeps 3 more mantissa bits, which is what keeps 28-layer models inside the stated logit and
 // log-prob tolerances (with bf16 activations the rounding points alone put the 1.5B-class model's
 // logits 6e-2 away from the definition).
-#include "common.h"
+#include "tiles.h"
 #include <algorithm>
 #include <type_traits>
 
 namespace sapo {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-union Frag {
-  uint4 u;
-  u32x4 n;
-  bf16x8 v;
-  f16x8 h;
-};
-
-__device__ __forceinline__ f32x16 mfma32(const Frag& a, const Frag& b, f32x16 c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_f16(a.h, b.h, c, 0, 0, 0);
-}
-__device__ __forceinline__ f32x4 mfma16h(const Frag& a, const Frag& b, f32x4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_f16(a.h, b.h, c, 0, 0, 0);
-}
-// x * sigmoid(x) with the hardware reciprocal (1 ulp) instead of an IEEE division: the token-parallel SwiGLU epilogue
-// evaluates 64 of these per thread and tile, where the correctly rounded division alone was a dozen instructions
-// each; the result is rounded to half right after.
-__device__ __forceinline__ float silu_f(float x) { return x * __builtin_amdgcn_rcpf(1.0f + __expf(-x)); }
-
 // ---------------------------------------------------------------------------------------
-// weight packing: row-major bf16 [n_rows, K] -> half, fragment order, 32-row tiles placed at
-// dst_tile0 + t * dst_tile_stride (stride 2 interleaves gate and up tiles).
+// weight packing: row-major bf16 [n_rows, K] -> half, fragment order, 32-row tiles from dst_tile0 on.
+// half 0, 1 instead of -1 (gate, up): 16 rows go into rows 16 half .. 16 half + 15 of each tile, so that an accumulator block of
+// 32 features holds 16 gate features and, two register quads on in the same lane, the up features that belong to them: a
+// kernel may take any number of blocks.
 // ---------------------------------------------------------------------------------------
 // range: kPackRangeSlots (512) pairs of counters, to be summed by the reader.  The first of a pair counts values half
 // cannot hold (|w| > 65504, infinities, NaN: they would be clamped or carried as NaN), the second non-zero values
 // below half's smallest normal number 2^-14 (kept with an absolute error below 3e-8).
 __global__ void k_pack_weight(const bf16* __restrict__ src, int n_rows, int K, uint4* __restrict__ dst, int tile0,
-                              int tile_stride, unsigned* __restrict__ range) {
+                              int half, unsigned* __restrict__ range) {
   const int KS = K >> 4;
   const size_t total = (size_t)(n_rows >> 5) * KS * 64;
   const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -60,7 +37,8 @@ __global__ void k_pack_weight(const bf16* __restrict__ src, int n_rows, int K, u
   v.u = *(const uint4*)(src + (size_t)row * K + k);
 #pragma unroll
   for (int e = 0; e < 8; ++e) o.h[e] = from_f32<f16>((float)v.v[e]);   // bf16 value -> half
-  dst[((size_t)(tile0 + t * tile_stride) * KS + ks) * 64 + lane] = o.u;
+  if (half < 0) dst[((size_t)(tile0 + t) * KS + ks) * 64 + lane] = o.u;
+  else dst[((size_t)(tile0 + (row >> 4)) * KS + ks) * 64 + (lane & 32) + half * 16 + (row & 15)] = o.u;
   if (range) {
     unsigned too_large = 0, tiny = 0;
 #pragma unroll
@@ -80,12 +58,11 @@ __global__ void k_pack_weight(const bf16* __restrict__ src, int n_rows, int K, u
     }
   }
 }
-hipError_t m_pack_weight(const void* src, int n_rows, int K, void* dst, int dst_tile0, int dst_tile_stride,
-                         unsigned* range, hipStream_t st) {
+hipError_t m_pack_weight(const void* src, int n_rows, int K, void* dst, int dst_tile0, int interleave, unsigned* range, hipStream_t st) {
   const size_t total = (size_t)(n_rows / 32) * (K / 16) * 64;
   if (total == 0) return hipSuccess;
   return launch(KID_MISC, k_pack_weight, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, (const bf16*)src, n_rows, K, (uint4*)dst, dst_tile0,
-                                                                  dst_tile_stride, range);
+                                                                  interleave - 1, range);
 }
 
 // =======================================================================================
@@ -110,31 +87,9 @@ hipError_t m_pack_weight(const void* src, int n_rows, int K, void* dst, int dst_
 // register's use.
 // Accumulator layout: acc[fi][tj][4 r + j] = C[tok = wave * 32 TJ + tj*32 + lane%32][feat = fi*32 + 8 r + (lane/32)*4 + j].
 // ---------------------------------------------------------------------------------------
-__host__ __device__ __forceinline__ size_t x32_chunk(int tok, int k, int KS) {
-  return (((size_t)(tok >> 5) * KS + (k >> 4)) * 64) + (tok & 31) + 32 * ((k >> 3) & 1);
-}
-
 constexpr int kRing = 3;                                            // stages of the LDS ring
 constexpr int ring_bytes(int H) { return kRing * 4 * H * 1024; }     // 4 H fragments of 1 KiB per stage
 constexpr int kBigLds = ring_bytes(4);
-
-__device__ __forceinline__ unsigned lds_addr(const void* p) {
-  return (unsigned)(size_t)(const __attribute__((address_space(3))) void*)p;
-}
-// one wave-wide 1 KiB copy global -> LDS: lane l's 16 bytes (at base + off(l)) land at lds + 16 l (no immediate offset: the
-// instruction would add it to the LDS address as well)
-__device__ __forceinline__ void dma16(const void* base, unsigned off, unsigned lds) {
-  asm volatile("s_mov_b32 m0, %0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "memory");
-}
-// one wave-wide 1 KiB load into registers; the value is there after a wait and a landed() that names it
-template <int IMM> __device__ __forceinline__ void reg16(u32x4& d, const void* base, unsigned off) {
-  asm volatile("global_load_dwordx4 %0, %1, %2 offset:%3" : "=v"(d) : "v"(off), "s"(base), "n"(IMM) : "memory");
-}
-__device__ __forceinline__ void landed(u32x4& d) { asm volatile("" : "+v"(d)); }
-template <int N> __device__ __forceinline__ void wait_vmcnt() {
-  __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
-}
-__device__ __forceinline__ void wg_barrier() { asm volatile("s_barrier" ::: "memory"); }
 
 // Block id -> (feature tile bx, token tile by).  Block ids are dealt round-robin to the 8 XCDs, each
 // with its own L2.  With 8 or more token tiles XCD c owns the token tiles 8 y' + c and walks them in
@@ -162,11 +117,10 @@ static int big_grid(int NX, int NY) {
 // The k loop of one tile.  begin() requests the first two stages, run() multiplies all of them; a caller that walks several
 // tiles may call begin() for the next one before it is done with the accumulators, after a barrier (the ring is free
 // once every wave has left run()).
-template <int TJ, int H, int NW = 4>
+template <int TJ, int H>
 struct TileLoop {
-  static constexpr int NF = 4 * H / NW;       // ring copies per wave and stage (4 H fragments, NW waves)
+  static constexpr int NF = H;                // ring copies per wave and stage: the H fragments of a feature block
   static_assert(H == 2 || H == 4, "stage of 32 or 64 k");
-  static_assert(NW == 4 || NW == 8, "a feature block per wave, or half of one");
   u32x4 x[2][H][TJ];
   const char* wbase;          // this wave's fragments of the feature operand
   const char* xbase[TJ];
@@ -184,11 +138,10 @@ struct TileLoop {
       xbase[t] = (const char*)(Xp + ((size_t)tb * KS + ks0) * 64);
     }
   }
-  // ring fragment f of a stage: feature block f / H, 16-k step f % H; wave w copies fragments w NF .. w NF + NF - 1, the H
-  // steps of its feature blocks
+  // ring fragment f of a stage: feature block f / H, 16-k step f % H; wave w copies those of block w
   __device__ __forceinline__ void features(const uint4* Wp, int KS, int fblk0, int ks0, int n_stages, const uint4* smem) {
     const int wave = wave_index(threadIdx.x);
-    wbase = (const char*)(Wp + ((size_t)(fblk0 + wave * 4 / NW) * KS + ks0 + (NW == 8 ? (wave & 1) * NF : 0)) * 64);
+    wbase = (const char*)(Wp + ((size_t)(fblk0 + wave) * KS + ks0) * 64);
     ring = __builtin_amdgcn_readfirstlane(lds_addr(smem)) + (unsigned)(wave * NF * 1024);
     off = (threadIdx.x & 63) * 16;
     nst = n_stages;
@@ -329,29 +282,15 @@ __device__ __forceinline__ void row_scales(const float* __restrict__ ssq, int pa
   }
 }
 
-template <int TJ, int H, int NW>
-__global__ void __launch_bounds__(NW * 64, TJ == 2 ? 2 : 3) k_gemm_big(const uint4* __restrict__ Xp,
+// MODE: the epilogue (BigEpi::mode), each with a register allocation of its own
+template <int TJ, int H, int MODE>
+__global__ void __launch_bounds__(256, TJ == 2 ? 2 : 3) k_gemm_big(const uint4* __restrict__ Xp,
                                                                       const uint4* __restrict__ Wp, int M, int N, int K,
                                                                       BigEpi ep) {
-  constexpr int TM = 32 * NW * TJ;   // tokens per tile
+  constexpr int TM = 128 * TJ;   // tokens per tile
   extern __shared__ uint4 smem[];
-  if ((int)blockIdx.x >= ep.main_blocks) {
-    prefetch_role<NW>(ep.pf, blockIdx.x - ep.main_blocks, (int)gridDim.x - ep.main_blocks);
-    return;
-  }
-  int bx, by, st0 = 0, n_st = K / (16 * H);
-  if (ep.splits > 1) {
-    // split-K (one token tile): XCD c runs the splits c, c + 8, ... of every feature tile, so the K range of
-    // the token operand that a split reads sits in one L2; split z covers stages z nst / s .. (z + 1) nst / s
-    const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3, per = ep.splits >> 3;
-    const int z = (j % per) * 8 + xcd;
-    bx = j / per; by = 0;
-    st0 = (int)((long)z * n_st / ep.splits);
-    n_st = (int)((long)(z + 1) * n_st / ep.splits) - st0;
-    ep.out_f32 += (size_t)z * ep.split_stride;
-  } else if (!big_raster(N >> 7, (M + TM - 1) / TM, bx, by)) {
-    return;
-  }
+  int bx, by;
+  if (!big_raster(N >> 7, (M + TM - 1) / TM, bx, by)) return;
   f32x16 acc[4][TJ];
   const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63;
   const int tok0 = by * TM + wave * (32 * TJ) + (lane & 31);
@@ -359,20 +298,15 @@ __global__ void __launch_bounds__(NW * 64, TJ == 2 ? 2 : 3) k_gemm_big(const uin
 #pragma unroll
   for (int tj = 0; tj < TJ; ++tj) row_scale[tj] = 1.f;
   {
-    TileLoop<TJ, H, NW> loop;
-    loop.tokens(Xp, (M + 31) >> 5, K >> 4, by * (NW * TJ), st0 * H);
-    loop.features(Wp, K >> 4, bx * 4, st0 * H, n_st, smem);
-    if (ep.decode && by * TM + wave * (32 * TJ) >= M) {   // nothing of this wave is stored
-      loop.template begin<false>();
-      loop.template run<false>(smem, acc);
-      return;
-    }
+    TileLoop<TJ, H> loop;
+    loop.tokens(Xp, (M + 31) >> 5, K >> 4, by * (4 * TJ), 0);
+    loop.features(Wp, K >> 4, bx * 4, 0, K / (16 * H), smem);
     loop.begin();
-    if (ep.ssq_in) row_scales<TJ>(ep.ssq_in, ep.ssq_parts, ep.ssq_halves, ep.norm_dim, ep.eps, tok0, M, row_scale);
+    if (MODE != BIG_ADD_F32 && ep.ssq_in) row_scales<TJ>(ep.ssq_in, ep.ssq_parts, ep.ssq_halves, ep.norm_dim, ep.eps, tok0, M, row_scale);
     loop.run(smem, acc);
   }
   const int fcol = bx * 128 + (lane >> 5) * 4;   // + fi * 32 + 8 r: this lane's four features of block (fi, r)
-  if (ep.ssq_in) {
+  if (MODE != BIG_ADD_F32 && ep.ssq_in) {
 #pragma unroll
     for (int tj = 0; tj < TJ; ++tj)
 #pragma unroll
@@ -380,27 +314,26 @@ __global__ void __launch_bounds__(NW * 64, TJ == 2 ? 2 : 3) k_gemm_big(const uin
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[fi][tj][v] *= row_scale[tj];
   }
-  if (ep.mode == BIG_SWIGLU) {
+  if constexpr (MODE == BIG_SWIGLU) {
     const int F = N >> 1;
 #pragma unroll
     for (int tj = 0; tj < TJ; ++tj) {
       const int tok = tok0 + tj * 32;
       if (tok >= M) continue;   // lanes l and l + 32 hold the same token: they leave together
 #pragma unroll
-      for (int pr = 0; pr < 2; ++pr) {
-        // block 2 pr is a gate tile, 2 pr + 1 the matching up tile; act goes out in X32 order over F = N / 2
-        const int f0 = (bx * 2 + pr) * 32 + (lane >> 5) * 4;
+      for (int fi = 0; fi < 4; ++fi) {
+        // a block is 16 gate rows and the 16 matching up rows; act goes out in X32 order over F = N / 2
+        const int f0 = (bx * 4 + fi) * 16 + (lane >> 5) * 4;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
+        for (int r = 0; r < 2; ++r) {
           f16x4 o;
 #pragma unroll
-          for (int j = 0; j < 4; ++j)
-            o[j] = from_f32<f16>(silu_f(acc[2 * pr][tj][4 * r + j]) * acc[2 * pr + 1][tj][4 * r + j]);
+          for (int j = 0; j < 4; ++j) o[j] = from_f32<f16>(silu_f(acc[fi][tj][4 * r + j]) * acc[fi][tj][4 * (r + 2) + j]);
           *(f16x4*)(ep.out_act + x32_chunk(tok, f0 + 8 * r, F >> 4) * 8 + ((lane >> 5) << 2)) = o;
         }
       }
     }
-  } else if (ep.mode == BIG_STORE_F32) {
+  } else if constexpr (MODE == BIG_STORE_F32) {
 #pragma unroll
     for (int fi = 0; fi < 4; ++fi) {
       float4 bb[4];
@@ -420,7 +353,7 @@ __global__ void __launch_bounds__(NW * 64, TJ == 2 ? 2 : 3) k_gemm_big(const uin
       }
     }
   }
-  if (ep.mode == BIG_ADD_F32) {
+  if constexpr (MODE == BIG_ADD_F32) {
     // Residual update.  In the accumulator layout a lane holds one token, so a load or store instruction on the
     // row-major fp32 residual touches 32 cache lines for 1 KiB.  The residual therefore moves in row layout (16 lanes
     // cover 256 contiguous bytes of a row: 8 full lines per instruction) and changes layout through LDS, once on the
@@ -445,13 +378,13 @@ __global__ void __launch_bounds__(NW * 64, TJ == 2 ? 2 : 3) k_gemm_big(const uin
       // the tile's 128 gains wait in LDS behind the four row areas (in registers they would not fit next to the rows)
       float* G = (float*)smem + 4 * 32 * RS + wave * 128;
       if (prod && lane < 32) *(float4*)(G + 4 * lane) = *(const float4*)(ep.gain_next + bx * 128 + 4 * lane);
-      float4 in[8];
+      f32x4 in[8];   // (as HIP's float4, a struct, the array may end up in scratch memory: O 129 -> 175 us)
       auto request = [&](int p) {   // pass p: token block p / 2, feature half p % 2
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
           const int tok = row0 + (p >> 1) * 32 + 4 * i + rt;
-          in[i] = (full || tok < M) ? *(const float4*)(ep.out_f32 + (size_t)tok * ep.ldc + bx * 128 + (p & 1) * 64 + rc)
-                                    : make_float4(0.f, 0.f, 0.f, 0.f);
+          in[i] = (full || tok < M) ? *(const f32x4*)(ep.out_f32 + (size_t)tok * ep.ldc + bx * 128 + (p & 1) * 64 + rc)
+                                    : f32x4{0.f, 0.f, 0.f, 0.f};
         }
       };
       request(0);
@@ -459,7 +392,7 @@ __global__ void __launch_bounds__(NW * 64, TJ == 2 ? 2 : 3) k_gemm_big(const uin
       for (int p = 0; p < NP; ++p) {
         const int tj = p >> 1, fh = p & 1, tok = tok0 + tj * 32;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) *(float4*)(R + (4 * i + rt) * RS + rc) = in[i];
+        for (int i = 0; i < 8; ++i) *(f32x4*)(R + (4 * i + rt) * RS + rc) = in[i];
         wave_sync();
         float ssq = 0.f;
 #pragma unroll
@@ -483,14 +416,14 @@ __global__ void __launch_bounds__(NW * 64, TJ == 2 ? 2 : 3) k_gemm_big(const uin
           }
         ssq_half[tj][fh] = ssq + __shfl_xor(ssq, 32, 64);
         wave_sync();
-        float4 out[8];
+        f32x4 out[8];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) out[i] = *(const float4*)(R + (4 * i + rt) * RS + rc);
+        for (int i = 0; i < 8; ++i) out[i] = *(const f32x4*)(R + (4 * i + rt) * RS + rc);
         if (p + 1 < NP) request(p + 1);
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
           const int t = row0 + tj * 32 + 4 * i + rt;
-          if (full || t < M) *(float4*)(ep.out_f32 + (size_t)t * ep.ldc + bx * 128 + fh * 64 + rc) = out[i];
+          if (full || t < M) *(f32x4*)(ep.out_f32 + (size_t)t * ep.ldc + bx * 128 + fh * 64 + rc) = out[i];
         }
         wave_sync();   // the rows are in registers before the next pass overwrites them
       }
@@ -618,12 +551,14 @@ __global__ void __launch_bounds__(256, 2) k_gemm_mid(const uint4* __restrict__ X
     if (tok >= M) return;
     const int F = N >> 1, f0 = (n0 >> 1) + (lane >> 5) * 4;
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      f16x4 o;
+    for (int b = 0; b < 2; ++b)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) o[j] = from_f32<f16>(silu_f(acc[0][0][4 * r + j]) * acc[1][0][4 * r + j]);
-      *(f16x4*)(ep.out_act + x32_chunk(tok, f0 + 8 * r, F >> 4) * 8 + ((lane >> 5) << 2)) = o;
-    }
+      for (int r = 0; r < 2; ++r) {
+        f16x4 o;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) o[j] = from_f32<f16>(silu_f(acc[b][0][4 * r + j]) * acc[b][0][4 * (r + 2) + j]);
+        *(f16x4*)(ep.out_act + x32_chunk(tok, f0 + 16 * b + 8 * r, F >> 4) * 8 + ((lane >> 5) << 2)) = o;
+      }
     return;
   }
   // BIG_ADD_F32: one pass of k_gemm_big's residual update (32 tokens x 64 features in row layout through LDS)
@@ -833,7 +768,7 @@ __global__ void __launch_bounds__(256, 2) k_gemm_qkv_mid(const uint4* __restrict
   qkv_epilogue<HD, 1, 1>(acc, ep, bx, tok, M, row_scale);
 }
 
-static int n_compute_units() {
+int n_compute_units() {
   static int n_cu = 0;
   if (n_cu == 0) {
     int dev = 0, n = 0;
@@ -935,47 +870,38 @@ static bool big_prefers_small_tiles(int NX, int M) {
   return rounds_small <= rounds_big;
 }
 
-template <int TJ, int H, int NW = 4>
-static hipError_t launch_big(const void* Xp, const void* Wp, int M, int N, int K, BigEpi epi, int grid, hipStream_t st) {
+template <int TJ, int H, int MODE>
+static hipError_t launch_big(const void* Xp, const void* Wp, int M, int N, int K, const BigEpi& epi, hipStream_t st) {
   static bool attr_done = false;
   // the residual update's four row areas and gains lie in the ring's memory
   constexpr int lds = ring_bytes(H) > 4 * (32 * 68 + 128) * 4 ? ring_bytes(H) : 4 * (32 * 68 + 128) * 4;
   if (!attr_done) {
-    const hipError_t e = hipFuncSetAttribute((const void*)k_gemm_big<TJ, H, NW>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    const hipError_t e = hipFuncSetAttribute((const void*)k_gemm_big<TJ, H, MODE>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
     attr_done = true;
   }
-  epi.main_blocks = grid;   // a multiple of 8
-  return launch(epi.decode ? KID_GEMM_BIG_DECODE : KID_GEMM_BIG, k_gemm_big<TJ, H, NW>, dim3(grid + prefetch_blocks(epi.pf, NW)),
-                dim3(NW * 64), lds, st, (const uint4*)Xp, (const uint4*)Wp, M, N, K, epi);
+  return launch(KID_GEMM_BIG, k_gemm_big<TJ, H, MODE>, dim3(big_grid(N / 128, (M + 128 * TJ - 1) / (128 * TJ))), dim3(256), lds, st,
+                (const uint4*)Xp, (const uint4*)Wp, M, N, K, epi);
+}
+template <int TJ, int H>
+static hipError_t launch_big(const void* Xp, const void* Wp, int M, int N, int K, const BigEpi& epi, hipStream_t st) {
+  if (epi.mode == BIG_SWIGLU) return launch_big<TJ, H, BIG_SWIGLU>(Xp, Wp, M, N, K, epi, st);
+  if (epi.mode == BIG_ADD_F32) return launch_big<TJ, H, BIG_ADD_F32>(Xp, Wp, M, N, K, epi, st);
+  return launch_big<TJ, H, BIG_STORE_F32>(Xp, Wp, M, N, K, epi, st);
 }
 hipError_t m_gemm_big(const void* Xp, const void* Wp, int M, int N, int K, BigEpi epi, hipStream_t st) {
   if (M == 0) return hipSuccess;
-  if (N % 128 != 0 || K % (epi.splits > 1 ? 32 : 64) != 0) return hipErrorInvalidValue;
-  if (epi.splits < 1 || (epi.splits > 1 && (epi.splits % 8 != 0 || K / 32 < epi.splits || M > 256 ||
-                                            epi.mode != BIG_STORE_F32 || epi.ssq_in || epi.bias)))
-    return hipErrorInvalidValue;
-  if (epi.gain_next && epi.mode != BIG_ADD_F32) return hipErrorInvalidValue;
-  // a split is a number of 32-k stages; 8 waves as below (1.5B, 256 rows: 18.5 -> 17.6 us)
-  if (epi.splits > 1) return launch_big<1, 2, 8>(Xp, Wp, M, N, K, epi, epi.splits * (N / 128), st);
-  if (epi.decode && M <= 256) {
-    // One token tile or two, weights that come from HBM, at most one workgroup per compute unit: what counts is how much
-    // of the chip asks and how many waves hide a stage's barrier and LDS latency.  128-token tiles when they are no
-    // more than the compute units (0.5B gate/up, 192 rows: 76 workgroups become 152, 16.3 -> 12.9 us); 8 waves of 32
-    // tokens on a 256-token tile otherwise (1.5B at 256 rows: 140 workgroups, 26 -> 23 us with two waves per SIMD).
-    if (N / 128 * ((M + 127) / 128) <= n_compute_units())
-      return launch_big<1, 4>(Xp, Wp, M, N, K, epi, big_grid(N / 128, (M + 127) / 128), st);
-    return launch_big<1, 4, 8>(Xp, Wp, M, N, K, epi, big_grid(N / 128, 1), st);
-  }
-  if (epi.mode != BIG_STORE_F32 && !epi.decode) {
+  if (N % 128 != 0 || K % 64 != 0) return hipErrorInvalidValue;
+  if ((epi.gain_next && epi.mode != BIG_ADD_F32) || (epi.ssq_in && epi.mode == BIG_ADD_F32)) return hipErrorInvalidValue;
+  if (epi.mode != BIG_STORE_F32) {
     const MidPick m = pick_mid(M, N, MID_FFN);
     const uint4 *X = (const uint4*)Xp, *W = (const uint4*)Wp;
     if (m.tile == 1) return m.deep ? launch_ffn_mid<1, 1, 10>(X, W, M, N, K, epi, st) : launch_ffn_mid<1, 1, 5>(X, W, M, N, K, epi, st);
     if (m.tile == 2) return m.deep ? launch_ffn_mid<2, 1, 8>(X, W, M, N, K, epi, st) : launch_ffn_mid<2, 1, 4>(X, W, M, N, K, epi, st);
     if (m.tile == 3) return m.deep ? launch_ffn_mid<2, 2, 6>(X, W, M, N, K, epi, st) : launch_ffn_mid<2, 2, 3>(X, W, M, N, K, epi, st);
   }
-  if (big_prefers_small_tiles(N / 128, M)) return launch_big<1, 4>(Xp, Wp, M, N, K, epi, big_grid(N / 128, (M + 127) / 128), st);
-  return launch_big<2, 4>(Xp, Wp, M, N, K, epi, big_grid(N / 128, (M + 255) / 256), st);
+  if (big_prefers_small_tiles(N / 128, M)) return launch_big<1, 4>(Xp, Wp, M, N, K, epi, st);
+  return launch_big<2, 4>(Xp, Wp, M, N, K, epi, st);
 }
 
 // ---------------------------------------------------------------------------------------
