@@ -315,15 +315,13 @@ __device__ __forceinline__ void attention_unit(const float* __restrict__ qkv, co
     const int pb = pt[min(2 * pp + 1, last_page)];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-      const int r = lane & 15;
-      const int ptok = 8 * (r >> 2) + 4 * t + (r & 3);
-      const f16* kp = kpool + (size_t)(ptok < 16 ? pa : pb) * page_elems + ((size_t)kvh * kPageTokens + (ptok & 15)) * HD;
+      const f16* kp = kpool + (size_t)((lane & 15) < 8 ? pa : pb) * page_elems + (size_t)kvh * kPageTokens * HD;
 #pragma unroll
-      for (int kk = 0; kk < KK; ++kk) kf[t][kk].u = *(const uint4*)(kp + kk * 32 + grp * 8);
+      for (int kk = 0; kk < KK; ++kk) kf[t][kk].u = *(const uint4*)(kp + k_frag_at(t, kk, lane));
     }
-    const f16* vp = vpool + (size_t)(grp < 2 ? pa : pb) * page_elems + (size_t)kvh * HD * kPageTokens + (grp & 1) * 8;
+    const f16* vp = vpool + (size_t)(grp < 2 ? pa : pb) * page_elems + (size_t)kvh * HD * kPageTokens;
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt) vf[dt].u = *(const uint4*)(vp + (size_t)(dt * 16 + (lane & 15)) * kPageTokens);
+    for (int dt = 0; dt < DT; ++dt) vf[dt].u = *(const uint4*)(vp + v_frag_at(dt, lane));
   };
   Frag16 kf[PD][2][KK], vf[PD][DT];
 #pragma unroll
@@ -353,15 +351,15 @@ __device__ __forceinline__ void attention_unit(const float* __restrict__ qkv, co
     for (int i = tid; i < half; i += NW * 64) {
       const size_t x = (size_t)(n_q_heads + kvh) * HD;
       const float2 cs = rope[(size_t)pos * half + i];
-      f16* kp = kpool + (size_t)new_page * page_elems + ((size_t)kvh * kPageTokens + new_slot) * HD;
+      f16* kp = kpool + (size_t)new_page * page_elems + (size_t)kvh * kPageTokens * HD;
       const float a = x_at(x + i), b = x_at(x + i + half);
       const f16 k1 = from_f32<f16>(rot_first(a, b, cs.x, cs.y)), k2 = from_f32<f16>(rot_second(a, b, cs.x, cs.y));
-      kp[i] = k1; kp[i + half] = k2;
+      kp[k_page_at(new_slot, i)] = k1; kp[k_page_at(new_slot, i + half)] = k2;
       knew[i] = k1; knew[i + half] = k2;
     }
     for (int i = tid; i < HD; i += NW * 64) {
       const f16 vv = from_f32<f16>(x_at((size_t)(n_q_heads + hkv + kvh) * HD + i));
-      vpool[(size_t)new_page * page_elems + ((size_t)kvh * HD + i) * kPageTokens + new_slot] = vv;
+      vpool[(size_t)new_page * page_elems + (size_t)kvh * HD * kPageTokens + v_page_at(new_slot, i)] = vv;
       vnew[i] = vv;
     }
   }

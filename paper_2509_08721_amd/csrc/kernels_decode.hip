@@ -950,15 +950,13 @@ __device__ __forceinline__ void attention_prefix_role(const float* __restrict__ 
     const int pa = pt[2 * pp], pb = pt[2 * pp + 1];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-      const int r = lane & 15;
-      const int ptok = 8 * (r >> 2) + 4 * t + (r & 3);
-      const f16* kp = kpool + (size_t)(ptok < 16 ? pa : pb) * page_elems + ((size_t)kvh * kPageTokens + (ptok & 15)) * HD;
+      const f16* kp = kpool + (size_t)((lane & 15) < 8 ? pa : pb) * page_elems + (size_t)kvh * kPageTokens * HD;
 #pragma unroll
-      for (int kk = 0; kk < KK; ++kk) kf[t][kk].u = *(const uint4*)(kp + kk * 32 + grp * 8);
+      for (int kk = 0; kk < KK; ++kk) kf[t][kk].u = *(const uint4*)(kp + k_frag_at(t, kk, lane));
     }
-    const f16* vp = vpool + (size_t)(grp < 2 ? pa : pb) * page_elems + (size_t)kvh * HD * kPageTokens + (grp & 1) * 8;
+    const f16* vp = vpool + (size_t)(grp < 2 ? pa : pb) * page_elems + (size_t)kvh * HD * kPageTokens;
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt) vf[dt].u = *(const uint4*)(vp + (size_t)(dt * 16 + (lane & 15)) * kPageTokens);
+    for (int dt = 0; dt < DT; ++dt) vf[dt].u = *(const uint4*)(vp + v_frag_at(dt, lane));
   };
   Frag16 kf[2][2][KK], vf[2][DT];
 #pragma unroll
@@ -1099,7 +1097,7 @@ __device__ __forceinline__ void attention_prefix_role(const float* __restrict__ 
 template <int HD, int NW, int PD, bool LDS, bool SHARE>
 __global__ void __launch_bounds__(NW * 64) k_decode_attention16(const float* __restrict__ qkv,
                                                                const float2* __restrict__ rope, const int* step_,
-                                                               const int* page_table_, int Lp_, int pages_per_seq_,
+                                                               const int* page_table_, int lp_pages_, int rows_,
                                                                int heads_, int n_main, void* kpool_, RowMap rm,
                                                                KVCache kv, uint4* __restrict__ out, ShareArgs sh, Prefetch pf) {
   if ((int)blockIdx.x >= n_main) {   // uniform over the workgroup
@@ -1107,10 +1105,10 @@ __global__ void __launch_bounds__(NW * 64) k_decode_attention16(const float* __r
     if ((int)blockIdx.x >= first) prefetch_role<NW>(pf, blockIdx.x - first, (int)gridDim.x - first);
     return;
   }
-  const int n_q_heads = heads_ >> 16;
   // what leads from the start of the kernel to its first requests arrives preloaded (see k_skinny16): 14 dwords
-  rm.step = step_; rm.Lp = Lp_;
-  kv.page_table = page_table_; kv.pages_per_seq = pages_per_seq_; kv.n_kv_heads = heads_ & 0xffff; kv.k = kpool_;
+  rm.step = step_; rm.Lp = lp_pages_ & 0xffff;
+  kv.page_table = page_table_; kv.pages_per_seq = lp_pages_ >> 16; kv.n_kv_heads = heads_ & 0xffff; kv.k = kpool_;
+  const int n_q_heads = ((heads_ >> 16) & 0xff) * kv.n_kv_heads;
   constexpr int KK = HD / 32;   // k steps of S^T = K Q^T
   constexpr int DT = HD / 16;   // 16-row tiles of O^T
   constexpr int NFRAG = 2 * KK + DT;                        // 1 KiB fragments of one page pair
@@ -1130,8 +1128,17 @@ __global__ void __launch_bounds__(NW * 64) k_decode_attention16(const float* __r
   const int tid = threadIdx.x, wave = wave_index(tid), lane = tid & 63;
   const int qcol = lane & 15, grp = lane >> 4;
   const int hkv = kv.n_kv_heads, rep = n_q_heads / hkv;
-  const int bid = SHARE ? (int)blockIdx.x - sh.n_prefix : (int)blockIdx.x;
-  const int s = bid / hkv, kvh = bid % hkv;
+  // Siblings read the same prompt pages: the rows of a group (consecutive rows, one KV head) run on one XCD, whose L2 fetches
+  // them once.  Block ids are dealt round-robin to the XCDs.
+  int s, kvh;
+  if constexpr (SHARE) {
+    const int bid = (int)blockIdx.x - sh.n_prefix;
+    s = bid / hkv; kvh = bid % hkv;
+  } else {
+    const int group_log2 = heads_ >> 24, j = (int)blockIdx.x >> 3, g = (j >> group_log2) * 8 + ((int)blockIdx.x & 7), p = g / hkv;
+    s = (p << group_log2) + (j & ((1 << group_log2) - 1)); kvh = g - p * hkv;
+    if (s >= rows_) return;
+  }
   const int pp0 = SHARE ? sh.prefix_pairs : 0;   // first page pair this workgroup covers
   int seq, pos;
   rm.get(s, seq, pos);
@@ -1148,15 +1155,13 @@ __global__ void __launch_bounds__(NW * 64) k_decode_attention16(const float* __r
   auto load_pages = [&](int pa, int pb, Frag16 (&kf)[2][KK], Frag16 (&vf)[DT]) {
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-      const int r = lane & 15;
-      const int ptok = 8 * (r >> 2) + 4 * t + (r & 3);
-      const f16* kp = kpool + (size_t)(ptok < 16 ? pa : pb) * page_elems + ((size_t)kvh * kPageTokens + (ptok & 15)) * HD;
+      const f16* kp = kpool + (size_t)((lane & 15) < 8 ? pa : pb) * page_elems + (size_t)kvh * kPageTokens * HD;
 #pragma unroll
-      for (int kk = 0; kk < KK; ++kk) kf[t][kk].u = *(const uint4*)(kp + kk * 32 + grp * 8);
+      for (int kk = 0; kk < KK; ++kk) kf[t][kk].u = *(const uint4*)(kp + k_frag_at(t, kk, lane));
     }
-    const f16* vp = vpool + (size_t)(grp < 2 ? pa : pb) * page_elems + (size_t)kvh * HD * kPageTokens + (grp & 1) * 8;
+    const f16* vp = vpool + (size_t)(grp < 2 ? pa : pb) * page_elems + (size_t)kvh * HD * kPageTokens;
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt) vf[dt].u = *(const uint4*)(vp + (size_t)(dt * 16 + (lane & 15)) * kPageTokens);
+    for (int dt = 0; dt < DT; ++dt) vf[dt].u = *(const uint4*)(vp + v_frag_at(dt, lane));
   };
   auto load_pair = [&](int pp, Frag16 (&kf)[2][KK], Frag16 (&vf)[DT]) {
     load_pages(pt[2 * pp], pt[min(2 * pp + 1, last_page)], kf, vf);
@@ -1167,15 +1172,13 @@ __global__ void __launch_bounds__(NW * 64) k_decode_attention16(const float* __r
     const unsigned dst = stage0 + (unsigned)j * NFRAG * 1024u;
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-      const int r = lane & 15;
-      const int ptok = 8 * (r >> 2) + 4 * t + (r & 3);
-      const f16* kp = kpool + (size_t)(ptok < 16 ? pa : pb) * page_elems + ((size_t)kvh * kPageTokens + (ptok & 15)) * HD;
+      const f16* kp = kpool + (size_t)((lane & 15) < 8 ? pa : pb) * page_elems + (size_t)kvh * kPageTokens * HD;
 #pragma unroll
-      for (int kk = 0; kk < KK; ++kk) dma16_lds(kp + kk * 32 + grp * 8, dst + (unsigned)(t * KK + kk) * 1024u);
+      for (int kk = 0; kk < KK; ++kk) dma16_lds(kp + k_frag_at(t, kk, lane), dst + (unsigned)(t * KK + kk) * 1024u);
     }
-    const f16* vp = vpool + (size_t)(grp < 2 ? pa : pb) * page_elems + (size_t)kvh * HD * kPageTokens + (grp & 1) * 8;
+    const f16* vp = vpool + (size_t)(grp < 2 ? pa : pb) * page_elems + (size_t)kvh * HD * kPageTokens;
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt) dma16_lds(vp + (size_t)(dt * 16 + (lane & 15)) * kPageTokens, dst + (unsigned)(2 * KK + dt) * 1024u);
+    for (int dt = 0; dt < DT; ++dt) dma16_lds(vp + v_frag_at(dt, lane), dst + (unsigned)(2 * KK + dt) * 1024u);
   };
   auto stage_pair = [&](int pp, int j) { stage_pages(pt[2 * pp], pt[min(2 * pp + 1, last_page)], j); };
   auto read_pair = [&](int j, Frag16 (&kf)[2][KK], Frag16 (&vf)[DT]) {
@@ -1244,14 +1247,14 @@ __global__ void __launch_bounds__(NW * 64) k_decode_attention16(const float* __r
       qs[r * HD + i + half] = from_f32<f16>(live ? rot_second(qx1[n], qx2[n], qcs[n].x, qcs[n].y) : 0.f);
     }
     if (tid < half) {
-      f16* kp = kpool + (size_t)new_page * page_elems + ((size_t)kvh * kPageTokens + new_slot) * HD;
+      f16* kp = kpool + (size_t)new_page * page_elems + (size_t)kvh * kPageTokens * HD;
       const f16 k1 = from_f32<f16>(rot_first(kx1, kx2, kcs.x, kcs.y)), k2 = from_f32<f16>(rot_second(kx1, kx2, kcs.x, kcs.y));
-      kp[tid] = k1; kp[tid + half] = k2;
+      kp[k_page_at(new_slot, tid)] = k1; kp[k_page_at(new_slot, tid + half)] = k2;
       knew[tid] = k1; knew[tid + half] = k2;
     }
     if (tid < HD) {
       const f16 vv = from_f32<f16>(vx);
-      vpool[(size_t)new_page * page_elems + ((size_t)kvh * HD + tid) * kPageTokens + new_slot] = vv;
+      vpool[(size_t)new_page * page_elems + (size_t)kvh * HD * kPageTokens + v_page_at(new_slot, tid)] = vv;
       vnew[tid] = vv;
     }
   };
@@ -1423,6 +1426,11 @@ __global__ void __launch_bounds__(NW * 64) k_decode_attention16(const float* __r
   }
 }
 
+// Rows of one KV head that run on one XCD, as a power of two: the siblings of a prompt, at most 8 (the rows of a larger group
+// would crowd one XCD).  us per step, rows dealt one by one -> in groups: 0.5B, 64 rows, contexts of 1050 795 -> 781, of 240 667 ->
+// 661; 1.5B, 256 rows, contexts of 710 2324 -> 2279.
+static int sibling_group_log2(int G) { return G >= 8 ? 3 : G >= 4 ? 2 : G >= 2 ? 1 : 0; }
+
 template <int HD, int NW, int PD, bool LDS = false, bool SHARE = false>
 static hipError_t launch_decode_attention(const float* qkv, const float2* rope, RowMap rm, KVCache kv, void* out, int S,
                                           int n_q_heads, hipStream_t st, const Prefetch& pf, const ShareArgs& sh = ShareArgs()) {
@@ -1436,11 +1444,15 @@ static hipError_t launch_decode_attention(const float* qkv, const float2* rope, 
     if (e != hipSuccess) return e;
     attr_done = true;
   }
-  const int n_main = (SHARE ? sh.n_prefix : 0) + S * kv.n_kv_heads, n_pf = prefetch_blocks(pf, NW);
+  const int group_log2 = sibling_group_log2(rm.G), group = 1 << group_log2;
+  const int n_main = SHARE ? sh.n_prefix + S * kv.n_kv_heads : ((S + group - 1) / group * kv.n_kv_heads + 7) / 8 * 8 * group;
+  const int n_pf = prefetch_blocks(pf, NW);
   const int blocks = n_pf > 0 ? ((n_main + 7) & ~7) + n_pf : n_main;
+  // fields of the packed arguments (max_seq is at most 3584, 16 query heads per KV head: both checked when the handle is made)
+  if (kv.n_kv_heads > 0xffff || n_q_heads / kv.n_kv_heads > 16 || rm.Lp > 0xffff || kv.pages_per_seq > 0x7fff) return hipErrorInvalidValue;
   return launch(SHARE ? KID_DECODE_ATTN_SHARED : KID_DECODE_ATTN, k_decode_attention16<HD, NW, PD, LDS, SHARE>, dim3(blocks),
-                dim3(NW * 64), smem, st, qkv, rope, rm.step, kv.page_table, rm.Lp, kv.pages_per_seq,
-                kv.n_kv_heads | (n_q_heads << 16), n_main, kv.k, rm, kv, (uint4*)out, sh, pf);
+                dim3(NW * 64), smem, st, qkv, rope, rm.step, kv.page_table, rm.Lp | (kv.pages_per_seq << 16), S,
+                kv.n_kv_heads | (n_q_heads / kv.n_kv_heads << 16) | (group_log2 << 24), n_main, kv.k, rm, kv, (uint4*)out, sh, pf);
 }
 
 hipError_t d_decode_attention(const float* qkv, const float2* rope, RowMap rm, KVCache kv, void* out, int S, int n_q_heads,
@@ -1462,6 +1474,9 @@ hipError_t d_decode_attention(const float* qkv, const float2* rope, RowMap rm, K
   const char* lds_env = getenv("SAPO_ATTN_LDS");
   if (kv.head_dim == 64) {
     if (lds_env && lds_env[0] == '1') return launch_decode_attention<64, 8, 2, true>(qkv, rope, rm, kv, out, S, n_q_heads, st, pf);
+    // more workgroups than compute units: with two page pairs in flight per wave two workgroups fit a unit (0.5B, 192 rows:
+    // a step of 1112 us with three pairs, 1048 with two, 1051 with one, 1060 with four waves of three)
+    if (S * kv.n_kv_heads > n_compute_units()) return launch_decode_attention<64, 8, 2>(qkv, rope, rm, kv, out, S, n_q_heads, st, pf);
     return launch_decode_attention<64, 8, 3>(qkv, rope, rm, kv, out, S, n_q_heads, st, pf);
   }
   if (kv.head_dim == 128) {

@@ -684,19 +684,21 @@ __device__ __forceinline__ void qkv_epilogue(f32x16 (&acc)[NH * (HD / 32)][TJ], 
       if (head >= hq && !keeps[tj]) continue;
       if (head >= hq + hkv) {
         const int vh = head - hq - hkv;
-        f16* vp = vpool + ((size_t)page_of[tj] * hkv + vh) * HD * kPageTokens + pos_of[tj] % kPageTokens;
+        f16* vp = vpool + ((size_t)page_of[tj] * hkv + vh) * HD * kPageTokens;
 #pragma unroll
         for (int b = 0; b < NB; ++b)
 #pragma unroll
           for (int v = 0; v < 16; ++v) {
             const int f = b * 32 + 8 * (v >> 2) + (v & 3) + half_sel * 4;
-            vp[(size_t)f * kPageTokens] = from_f32<f16>(acc[hh * NB + b][tj][v]);
+            vp[v_page_at(pos_of[tj] % kPageTokens, f)] = from_f32<f16>(acc[hh * NB + b][tj][v]);
           }
         continue;
       }
-      // start of the row's head: q row-major, k in its page slot
-      f16* dst = head < hq ? ep.q_out + ((size_t)tok * hq + head) * HD
-                           : kpool + (((size_t)page_of[tj] * hkv + (head - hq)) * kPageTokens + pos_of[tj] % kPageTokens) * HD;
+      // start of the row's head, and the strides of 32 and of 8 dims: q row-major, k in its page (k_page_at)
+      const bool is_q = head < hq;
+      f16* dst = is_q ? ep.q_out + ((size_t)tok * hq + head) * HD
+                      : kpool + ((size_t)page_of[tj] * hkv + (head - hq)) * kPageTokens * HD + k_page_at(pos_of[tj] % kPageTokens, 0);
+      const int s32 = is_q ? 32 : k_page_at(0, 32), s8 = is_q ? 8 : k_page_at(0, 8);
 #pragma unroll
       for (int b = 0; b < NB / 2; ++b) {
         f16x4 o1[4], o2[4];
@@ -715,8 +717,8 @@ __device__ __forceinline__ void qkv_epilogue(f32x16 (&acc)[NH * (HD / 32)][TJ], 
         if (b + 1 < NB / 2) request(b + 1);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          *(f16x4*)(dst + b * 32 + 8 * r + half_sel * 4) = o1[r];
-          *(f16x4*)(dst + b * 32 + 8 * r + half_sel * 4 + HD / 2) = o2[r];
+          *(f16x4*)(dst + b * s32 + r * s8 + half_sel * 4) = o1[r];
+          *(f16x4*)(dst + (b + NB / 2) * s32 + r * s8 + half_sel * 4) = o2[r];
         }
       }
     }
@@ -1224,15 +1226,13 @@ __global__ void __launch_bounds__(256, 2) k_flash_attention(const f16* __restric
     const int pb = pt[min(2 * pp + 1, last_page)];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-      const int r = lane & 15;
-      const int ptok = 8 * (r >> 2) + 4 * t + (r & 3);   // key row r of score tile t
-      const f16* kp = kpool + (size_t)(ptok < 16 ? pa : pb) * page_elems + ((size_t)kvh * kPageTokens + (ptok & 15)) * HD;
+      const f16* kp = kpool + (size_t)((lane & 15) < 8 ? pa : pb) * page_elems + (size_t)kvh * kPageTokens * HD;
 #pragma unroll
-      for (int kk = 0; kk < KK; ++kk) kd[t][kk].u = *(const uint4*)(kp + kk * 32 + grp * 8);
+      for (int kk = 0; kk < KK; ++kk) kd[t][kk].u = *(const uint4*)(kp + k_frag_at(t, kk, lane));
     }
-    const f16* vp = vpool + (size_t)(grp < 2 ? pa : pb) * page_elems + (size_t)kvh * HD * kPageTokens + (grp & 1) * 8;
+    const f16* vp = vpool + (size_t)(grp < 2 ? pa : pb) * page_elems + (size_t)kvh * HD * kPageTokens;
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt) vd[dt].u = *(const uint4*)(vp + (size_t)(dt * 16 + (lane & 15)) * kPageTokens);
+    for (int dt = 0; dt < DT; ++dt) vd[dt].u = *(const uint4*)(vp + v_frag_at(dt, lane));
   };
   fetch(0, kn, vn);
   for (int pp = 0; pp < npairs; ++pp) {

@@ -53,3 +53,24 @@ def test_rows_follow_the_oracle(d, F, S, std):
     ref = oracle_logprobs_for(ma, prompts, 1, toks, seqs)
     assert max(np.max(np.abs(ref[s] - lps[s])) for s in seqs) <= 2e-2
     gw.close()
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+@pytest.mark.parametrize("P,G", [(1, 2), (3, 3), (5, 3), (3, 5), (2, 12), (1, 16), (7, 11)])   # the last one not a multiple of its group, and 77 rows
+def test_rows_dealt_in_groups_of_siblings(hd, P, G):
+    """Decode attention deals rows to the XCDs in groups of 1, 2, 4 or 8: every row is there once, whatever the number of
+    siblings, also where a group holds rows of two prompts."""
+    shape = replace(W.MINI_BF16 if hd == 64 else W.MINI_BF16_HD128, n_layers=1)
+    w = W.make_weights(shape, 12, std=0.05)
+    gw = sapo.sapo_weights_create(shape, w)
+    ma, Lp, N, seed = O.Model(shape, w), 21, 4, 78
+    prompts = np.random.default_rng(P * G).integers(0, shape.vocab, size=(P, Lp)).astype(np.int32)
+    toks, lps = sapo.sapo_rollout_generate(gw, torch.from_numpy(prompts).cuda(), G, N, 1.0, seed)
+    toks, lps = toks.cpu().numpy(), lps.cpu().numpy()
+    seqs = list(range(P * G))
+    eps = max(measured_logit_eps(sapo, gw, ma, np.concatenate([prompts[s // G], toks[s]]), Lp - 1) for s in seqs[::5])
+    n, exact, near, bad = teacher_forced_token_check(ma, prompts, G, toks, 1.0, seed, seqs, delta=1e-3 + 2 * max(eps, 5e-3))
+    assert not bad, bad[:5]
+    ref = oracle_logprobs_for(ma, prompts, G, toks, seqs)
+    assert max(np.max(np.abs(ref[s] - lps[s])) for s in seqs) <= 2e-2
+    gw.close()
