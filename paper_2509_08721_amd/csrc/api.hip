@@ -334,6 +334,15 @@ static int create_impl(sapo_weights* w, const void* const* t, hipStream_t st) {
     if ((rc = dev_alloc(w, 2 * kPackRangeSlots * sizeof(unsigned), (void**)&w->pack_range))) return rc;
     HIP_CK(g_fill_i32((int*)w->pack_range, 0, 2 * kPackRangeSlots, st));
   }
+  std::vector<PackTask> tasks;   // MFMA path
+  auto matrix = [&](const void* src, size_t rows, size_t K, void* dst32, size_t tile32, int half, void* dst16, size_t tile16, int stride16) {
+    tasks.push_back(PackTask{src, (uint4*)dst32, (uint4*)dst16, (int)rows, (int)K, (int)tile32, half, (int)tile16, stride16, 0});
+  };
+  auto gain = [&](float* dst, const void* src) -> hipError_t {
+    if (!w->mfma) return copy(dst, src, d * 4);
+    tasks.push_back(PackTask{src, nullptr, (uint4*)dst, (int)d, 0, 0, 0, 0, 0, 0});
+    return hipSuccess;
+  };
   w->layers.resize(c.n_layers);
   for (int l = 0; l < c.n_layers; ++l) {
     const void* const* lt = t + 1 + 9 * l;
@@ -344,27 +353,20 @@ static int create_impl(sapo_weights* w, const void* const* t, hipStream_t st) {
     if ((rc = dev_alloc(w, d * q * e, &lw.wo))) return rc;
     if ((rc = dev_alloc(w, 2 * F * d * e, &lw.wgu))) return rc;
     if ((rc = dev_alloc(w, d * F * e, &lw.wdown))) return rc;
-    HIP_CK(copy(lw.attn_norm, lt[0], d * 4));
-    HIP_CK(copy(lw.ffn_norm, lt[5], d * 4));
+    HIP_CK(gain(lw.attn_norm, lt[0]));
+    HIP_CK(gain(lw.ffn_norm, lt[5]));
     if (w->mfma) {
-      HIP_CK(m_pack_weight(lt[1], (int)q, (int)d, lw.wqkv, 0, 0, w->pack_range, st));
-      HIP_CK(m_pack_weight(lt[2], (int)kv, (int)d, lw.wqkv, (int)(q / 32), 0, w->pack_range, st));
-      HIP_CK(m_pack_weight(lt[3], (int)kv, (int)d, lw.wqkv, (int)((q + kv) / 32), 0, w->pack_range, st));
-      HIP_CK(m_pack_weight(lt[4], (int)d, (int)q, lw.wo, 0, 0, w->pack_range, st));
-      HIP_CK(m_pack_weight(lt[6], (int)F, (int)d, lw.wgu, 0, 1, w->pack_range, st));
-      HIP_CK(m_pack_weight(lt[7], (int)F, (int)d, lw.wgu, 0, 2, w->pack_range, st));
-      HIP_CK(m_pack_weight(lt[8], (int)d, (int)F, lw.wdown, 0, 0, w->pack_range, st));
       if ((rc = dev_alloc(w, (q + 2 * kv) * d * e, &lw.wqkv16))) return rc;
       if ((rc = dev_alloc(w, d * q * e, &lw.wo16))) return rc;
       if ((rc = dev_alloc(w, 2 * F * d * e, &lw.wgu16))) return rc;
       if ((rc = dev_alloc(w, d * F * e, &lw.wdown16))) return rc;
-      HIP_CK(d_pack_weight16(lt[1], (int)q, (int)d, lw.wqkv16, 0, 1, st));
-      HIP_CK(d_pack_weight16(lt[2], (int)kv, (int)d, lw.wqkv16, (int)(q / 16), 1, st));
-      HIP_CK(d_pack_weight16(lt[3], (int)kv, (int)d, lw.wqkv16, (int)((q + kv) / 16), 1, st));
-      HIP_CK(d_pack_weight16(lt[4], (int)d, (int)q, lw.wo16, 0, 1, st));
-      HIP_CK(d_pack_weight16(lt[6], (int)F, (int)d, lw.wgu16, 0, 2, st));
-      HIP_CK(d_pack_weight16(lt[7], (int)F, (int)d, lw.wgu16, 1, 2, st));
-      HIP_CK(d_pack_weight16(lt[8], (int)d, (int)F, lw.wdown16, 0, 1, st));
+      matrix(lt[1], q, d, lw.wqkv, 0, -1, lw.wqkv16, 0, 1);
+      matrix(lt[2], kv, d, lw.wqkv, q / 32, -1, lw.wqkv16, q / 16, 1);
+      matrix(lt[3], kv, d, lw.wqkv, (q + kv) / 32, -1, lw.wqkv16, (q + kv) / 16, 1);
+      matrix(lt[4], d, q, lw.wo, 0, -1, lw.wo16, 0, 1);
+      matrix(lt[6], F, d, lw.wgu, 0, 0, lw.wgu16, 0, 2);
+      matrix(lt[7], F, d, lw.wgu, 0, 1, lw.wgu16, 1, 2);
+      matrix(lt[8], d, F, lw.wdown, 0, -1, lw.wdown16, 0, 1);
     } else {
       HIP_CK(copy(lw.wqkv, lt[1], q * d * e));
       HIP_CK(copy((char*)lw.wqkv + q * d * e, lt[2], kv * d * e));
@@ -377,12 +379,12 @@ static int create_impl(sapo_weights* w, const void* const* t, hipStream_t st) {
   }
   const void* const* tail = t + 1 + 9 * c.n_layers;
   if ((rc = dev_alloc(w, d * 4, (void**)&w->final_norm))) return rc;
-  HIP_CK(copy(w->final_norm, tail[0], d * 4));
+  HIP_CK(gain(w->final_norm, tail[0]));
   if (w->mfma) {
     if ((rc = dev_alloc(w, V * d * e, &w->lm_head))) return rc;
-    HIP_CK(m_pack_weight(c.tied_embeddings ? t[0] : tail[1], (int)V, (int)d, w->lm_head, 0, 0, w->pack_range, st));
     if ((rc = dev_alloc(w, V * d * e, &w->lm_head16))) return rc;
-    HIP_CK(d_pack_weight16(c.tied_embeddings ? t[0] : tail[1], (int)V, (int)d, w->lm_head16, 0, 1, st));
+    matrix(c.tied_embeddings ? t[0] : tail[1], V, d, w->lm_head, 0, -1, w->lm_head16, 0, 1);
+    HIP_CK(m_pack_weights(tasks.data(), (int)tasks.size(), w->pack_range, st));
   } else if (c.tied_embeddings) {
     w->lm_head = w->embed;
   } else {

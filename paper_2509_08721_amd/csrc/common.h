@@ -496,9 +496,17 @@ struct QkvEpi {
 };
 hipError_t m_gemm_qkv_rope(const void* Xp, const void* Wp, int M, int N, int K, const QkvEpi& epi, hipStream_t st);
 
-constexpr int kPackRangeSlots = 512;   // pairs of range counters behind m_pack_weight's `range`
-// interleave 0: 32-row tiles from dst_tile0 on; 1, 2: gate, up rows, 16 of each per tile
-hipError_t m_pack_weight(const void* src, int n_rows, int K, void* dst, int dst_tile0, int interleave, unsigned* range, hipStream_t st);
+constexpr int kPackRangeSlots = 512;   // pairs of range counters behind m_pack_weights' `range`
+// One matrix [n_rows, K] (n_rows % 32 == 0, K % 64 == 0) into both fragment orders, or (dst32 NULL) n_rows floats into dst16.
+struct PackTask {
+  const void* src;
+  uint4 *dst32, *dst16;
+  int n_rows, K;
+  int tile32, half;       // first 32-row tile; -1, or gate (0) / up (1) rows, 16 of each per tile
+  int tile16, stride16;   // 16-row tile t goes to tile16 + t stride16
+  int first_block;        // set by the launcher
+};
+hipError_t m_pack_weights(const PackTask* tasks, int n, unsigned* range, hipStream_t st);
 // Xp: tokens in X32 fragment order (rows padded to a multiple of 32); Wp: weights in W32 order
 // Whether a BIG_ADD_F32 launch of this size leaves its sums of squares in halves.
 bool m_gemm_writes_halves(int M, int N);
@@ -553,8 +561,6 @@ struct SkinnyArgs {
   int pf_blocks;          // workgroups of pf (set by the launcher)
   float* ssq_out;         // RESID: [N/16][s_pad] sums of h^2 over each 16-feature tile
 };
-hipError_t d_pack_weight16(const void* src, int n_rows, int K, void* dst, int dst_tile0, int dst_tile_stride,
-                           hipStream_t st);
 hipError_t d_gemm_skinny(const SkinnyArgs& a, int mode, hipStream_t st);
 // workgroup columns of a launch: parts of the sums of squares that RESID_X32 leaves
 int d_skinny_units(int n_rows, int mode, int N, int K);

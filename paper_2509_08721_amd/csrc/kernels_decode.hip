@@ -40,34 +40,6 @@ __device__ __forceinline__ f32x4 mfma16(const Frag16& a, const Frag16& b, f32x4 
 __device__ __forceinline__ float silu_f(float x) { return x / (1.0f + __expf(-x)); }
 
 // ---------------------------------------------------------------------------------------
-// weight packing: row-major bf16 [n_rows, K] -> half, W16 order; 16-row tile t goes to tile slot
-// tile0 + t * tile_stride (stride 2 interleaves gate and up tiles).
-// ---------------------------------------------------------------------------------------
-__global__ void k_pack_weight16(const bf16* __restrict__ src, int n_rows, int K, uint4* __restrict__ dst, int tile0,
-                                int tile_stride) {
-  const int KS = K >> 5;
-  const size_t total = (size_t)(n_rows >> 4) * KS * 64;
-  const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= total) return;
-  const int lane = (int)(idx & 63);
-  const int ks = (int)((idx >> 6) % KS);
-  const int t = (int)((idx >> 6) / KS);
-  const int row = t * 16 + (lane & 15), k = ks * 32 + (lane >> 4) * 8;
-  Frag16 v, o;
-  v.u = *(const uint4*)(src + (size_t)row * K + k);
-#pragma unroll
-  for (int e = 0; e < 8; ++e) o.h[e] = from_f32<f16>((float)v.v[e]);   // bf16 value -> half
-  dst[((size_t)(tile0 + t * tile_stride) * KS + ks) * 64 + lane] = o.u;
-}
-hipError_t d_pack_weight16(const void* src, int n_rows, int K, void* dst, int dst_tile0, int dst_tile_stride,
-                           hipStream_t st) {
-  const size_t total = (size_t)(n_rows / 16) * (K / 32) * 64;
-  if (total == 0) return hipSuccess;
-  return launch(KID_MISC, k_pack_weight16, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, (const bf16*)src, n_rows, K, (uint4*)dst, dst_tile0,
-                                                                    dst_tile_stride);
-}
-
-// ---------------------------------------------------------------------------------------
 // Sum of the ssq parts of one token, spread over the 8 waves of a workgroup: thread (grp, tok)
 // loads parts grp, grp + 8, ... early (ssq_issue) and the sums meet in LDS later (ssq_finish).
 // ---------------------------------------------------------------------------------------

@@ -15,54 +15,83 @@
 namespace sapo {
 
 // ---------------------------------------------------------------------------------------
-// weight packing: row-major bf16 [n_rows, K] -> half, fragment order, 32-row tiles from dst_tile0 on.
-// half 0, 1 instead of -1 (gate, up): 16 rows go into rows 16 half .. 16 half + 15 of each tile, so that an accumulator block of
-// 32 features holds 16 gate features and, two register quads on in the same lane, the up features that belong to them: a
-// kernel may take any number of blocks.
-// ---------------------------------------------------------------------------------------
+// Filling a handle: every matrix, row-major bf16 [n_rows, K], goes out as half in both fragment orders (W32 and W16), every
+// gain is copied, in a few launches for the whole model: a launch per tensor and order was 400 launches of a few us each with
+// as much between them (0.5B: 5.2 ms, of which the kernels 1.6; now 1.1).
+// A wave takes 32 rows x 64 k: every value is read once (8 rows x 128 contiguous bytes per request) and stored as the same 16
+// bytes in either order, 128 contiguous bytes per eight rows.
+// half 0, 1 instead of -1 (gate, up): 16 rows go into rows 16 half .. 16 half + 15 of each 32-row tile, so that an accumulator
+// block of 32 features holds 16 gate features and, two register quads on in the same lane, the up features that belong to
+// them: a kernel may take any number of blocks.  16-row tile t goes to tile16 + t stride16.
 // range: kPackRangeSlots (512) pairs of counters, to be summed by the reader.  The first of a pair counts values half
 // cannot hold (|w| > 65504, infinities, NaN: they would be clamped or carried as NaN), the second non-zero values
 // below half's smallest normal number 2^-14 (kept with an absolute error below 3e-8).
-__global__ void k_pack_weight(const bf16* __restrict__ src, int n_rows, int K, uint4* __restrict__ dst, int tile0,
-                              int half, unsigned* __restrict__ range) {
-  const int KS = K >> 4;
-  const size_t total = (size_t)(n_rows >> 5) * KS * 64;
-  const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= total) return;   // total is a multiple of 64: a wave leaves or stays as a whole
-  const int lane = (int)(idx & 63);
-  const int ks = (int)((idx >> 6) % KS);
-  const int t = (int)((idx >> 6) / KS);
-  const int row = t * 32 + (lane & 31), k = ks * 16 + (lane >> 5) * 8;
-  Frag v, o;
-  v.u = *(const uint4*)(src + (size_t)row * K + k);
+// ---------------------------------------------------------------------------------------
+constexpr int kPackTasks = 48;   // tasks of a launch: they travel as kernel arguments (at most 4 KiB)
+struct PackTasks { int n; PackTask t[kPackTasks]; };
+static_assert(sizeof(PackTasks) + 64 <= 4096, "kernel arguments");
+
+__global__ void __launch_bounds__(256) k_pack_weights(PackTasks tasks, unsigned* __restrict__ range) {
+  int ti = 0;
+  for (int end = tasks.n; end - ti > 1;) {
+    const int mid = (ti + end) >> 1;
+    if ((int)blockIdx.x >= tasks.t[mid].first_block) ti = mid; else end = mid;
+  }
+  const PackTask t = tasks.t[ti];
+  const int lane = threadIdx.x & 63, block = (int)blockIdx.x - t.first_block;
+  if (t.dst32 == nullptr) {   // a gain: n_rows floats
+    for (int i = threadIdx.x; i < t.n_rows; i += 256) ((float*)t.dst16)[i] = ((const float*)t.src)[i];
+    return;
+  }
+  const int units_k = t.K >> 6, unit = block * 4 + wave_index(threadIdx.x);
+  if (unit >= (t.n_rows >> 5) * units_k) return;   // a wave leaves as a whole
+  const int r32 = unit / units_k, k0 = (unit - r32 * units_k) * 64, k8 = lane & 7;
+  Frag v[4];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) o.h[e] = from_f32<f16>((float)v.v[e]);   // bf16 value -> half
-  if (half < 0) dst[((size_t)(tile0 + t) * KS + ks) * 64 + lane] = o.u;
-  else dst[((size_t)(tile0 + (row >> 4)) * KS + ks) * 64 + (lane & 32) + half * 16 + (row & 15)] = o.u;
-  if (range) {
-    unsigned too_large = 0, tiny = 0;
+  for (int i = 0; i < 4; ++i) v[i].u = *(const uint4*)((const bf16*)t.src + (size_t)(r32 * 32 + 8 * i + (lane >> 3)) * t.K + k0 + k8 * 8);
+  unsigned too_large = 0, tiny = 0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int row = r32 * 32 + 8 * i + (lane >> 3);
+    Frag o;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const float a = fabsf((float)v.v[e]);
+      const float w = (float)v[i].v[e], a = fabsf(w);   // bf16 value -> half
+      o.h[e] = from_f32<f16>(w);
       too_large += !(a <= 65504.f);
       tiny += (a > 0.f && a < 6.103515625e-05f);
     }
-    // one atomic per wave and counter, only when there is something to add, spread over kPackRangeSlots pairs of
-    // counters (small weights are common: with one pair every wave of a 0.5B model queues on the same address)
-    unsigned packed = (too_large << 16) | tiny;          // at most 8 each per lane
-    for (int off = 32; off > 0; off >>= 1) packed += __shfl_xor(packed, off, 64);   // at most 512 each per wave
-    if (lane == 0) {
-      unsigned* slot = range + 2 * (((unsigned)(idx >> 6) * 2654435761u) >> (32 - 9));
-      if (packed >> 16) atomicAdd(slot, packed >> 16);
-      if (packed & 0xffffu) atomicAdd(slot + 1, packed & 0xffffu);
-    }
+    const size_t ks = (k0 >> 4) + (k8 >> 1);
+    const int tile = t.half < 0 ? row >> 5 : row >> 4, in = t.half < 0 ? row & 31 : t.half * 16 + (row & 15);
+    t.dst32[((size_t)(t.tile32 + tile) * (t.K >> 4) + ks) * 64 + (k8 & 1) * 32 + in] = o.u;
+    t.dst16[((size_t)(t.tile16 + (row >> 4) * t.stride16) * (t.K >> 5) + (k0 >> 5) + (k8 >> 2)) * 64 + (k8 & 3) * 16 + (row & 15)] = o.u;
+  }
+  // one atomic per wave and counter, only when there is something to add, spread over kPackRangeSlots pairs of
+  // counters (small weights are common: with one pair every wave of a 0.5B model queues on the same address)
+  unsigned packed = (too_large << 16) | tiny;          // at most 32 each per lane, 2048 each per wave
+  for (int off = 32; off > 0; off >>= 1) packed += __shfl_xor(packed, off, 64);
+  if (lane == 0) {
+    unsigned* slot = range + 2 * (((unsigned)(unit + blockIdx.x) * 2654435761u) >> (32 - 9));
+    if (packed >> 16) atomicAdd(slot, packed >> 16);
+    if (packed & 0xffffu) atomicAdd(slot + 1, packed & 0xffffu);
   }
 }
-hipError_t m_pack_weight(const void* src, int n_rows, int K, void* dst, int dst_tile0, int interleave, unsigned* range, hipStream_t st) {
-  const size_t total = (size_t)(n_rows / 32) * (K / 16) * 64;
-  if (total == 0) return hipSuccess;
-  return launch(KID_MISC, k_pack_weight, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st, (const bf16*)src, n_rows, K, (uint4*)dst, dst_tile0,
-                                                                  interleave - 1, range);
+hipError_t m_pack_weights(const PackTask* tasks, int n, unsigned* range, hipStream_t st) {
+  for (int i = 0; i < n; ++i)
+    if (tasks[i].dst32 && (tasks[i].n_rows % 32 != 0 || tasks[i].K % 64 != 0)) return hipErrorInvalidValue;
+  for (int i0 = 0; i0 < n; i0 += kPackTasks) {
+    PackTasks a;
+    a.n = n - i0 < kPackTasks ? n - i0 : kPackTasks;
+    int blocks = 0;
+    for (int i = 0; i < a.n; ++i) {
+      a.t[i] = tasks[i0 + i];
+      a.t[i].first_block = blocks;
+      blocks += a.t[i].dst32 ? (a.t[i].n_rows / 32 * (a.t[i].K / 64) + 3) / 4 : 1;
+    }
+    const hipError_t e = launch(KID_MISC, k_pack_weights, dim3(blocks), dim3(256), 0, st, a, range);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 // =======================================================================================

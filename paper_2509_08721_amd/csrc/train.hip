@@ -801,9 +801,41 @@ __global__ void k_bf16_to_f32(const bf16* __restrict__ src, float* __restrict__ 
   const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
   if (i < n) dst[i] = (float)src[i];
 }
-__global__ void k_f32_to_bf16(const float* __restrict__ src, bf16* __restrict__ dst, size_t n) {
-  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) dst[i] = from_f32<bf16>(src[i]);   // round to nearest even
+// Masters into the caller's tensors, a few launches for all of them (a conversion or copy per tensor: 218 launches, 3.4 ms on
+// the 0.5B decoder with the gaps between them, 1.6 ms of kernels; now 0.8).  A block takes kExportBlock values of one tensor.
+constexpr int kExportTasks = 96, kExportBlock = 4096;
+struct ExportTask { const float* src; void* dst; size_t n; unsigned first_block, f32; };
+struct ExportTasks { int n; ExportTask t[kExportTasks]; };
+static_assert(sizeof(ExportTasks) + 64 <= 4096, "kernel arguments");
+__global__ void __launch_bounds__(256) k_export(ExportTasks tasks) {
+  int ti = 0;
+  for (int end = tasks.n; end - ti > 1;) {
+    const int mid = (ti + end) >> 1;
+    if (blockIdx.x >= tasks.t[mid].first_block) ti = mid; else end = mid;
+  }
+  const ExportTask t = tasks.t[ti];
+  const size_t i0 = (size_t)(blockIdx.x - t.first_block) * kExportBlock;
+  const bool aligned = (((uintptr_t)t.src & 15) | ((uintptr_t)t.dst & (t.f32 ? 15 : 7))) == 0;
+  if (aligned && i0 + kExportBlock <= t.n) {
+    float4 v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = *(const float4*)(t.src + i0 + u * 1024 + threadIdx.x * 4);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const size_t i = i0 + u * 1024 + threadIdx.x * 4;
+      if (t.f32) {
+        *(float4*)((float*)t.dst + i) = v[u];
+      } else {
+        typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+        *(bf16x4*)((bf16*)t.dst + i) = bf16x4{(bf16)v[u].x, (bf16)v[u].y, (bf16)v[u].z, (bf16)v[u].w};
+      }
+    }
+    return;
+  }
+  for (size_t i = i0 + threadIdx.x; i < t.n && i < i0 + kExportBlock; i += 256) {
+    if (t.f32) ((float*)t.dst)[i] = t.src[i];
+    else ((bf16*)t.dst)[i] = (bf16)t.src[i];
+  }
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1918,14 +1950,19 @@ extern "C" int sapo_trainer_read(const sapo_trainer* tr, int what, int tensor, f
 extern "C" int sapo_trainer_export(const sapo_trainer* tr, void* const* tensors_out, int n_tensors, void* stream) {
   if (!tr || !tensors_out) return set_error(SAPO_EINVAL, "NULL argument");
   if (n_tensors != tr->n_in) return set_error(SAPO_EINVAL, "n_tensors is %d, expected %d", n_tensors, tr->n_in);
-  hipStream_t st = (hipStream_t)stream;
-  for (int i = 0; i < n_tensors; ++i) {
+  for (int i = 0; i < n_tensors; ++i)
     if (!tensors_out[i]) return set_error(SAPO_EINVAL, "tensor %d is NULL", i);
-    const float* src = tr->theta + tr->off[i];
-    if (tr->cfg.dtype == SAPO_DTYPE_F32 || gain_tensor(tr->cfg, i))
-      T_CK(hipMemcpyAsync(tensors_out[i], src, tr->len[i] * sizeof(float), hipMemcpyDeviceToDevice, st));
-    else
-      T_CK(launch(KID_MISC, k_f32_to_bf16, dim3(blocks256(tr->len[i])), dim3(256), 0, st, src, (bf16*)tensors_out[i], tr->len[i]));
+  for (int i0 = 0; i0 < n_tensors; i0 += kExportTasks) {
+    ExportTasks a;
+    a.n = std::min(kExportTasks, n_tensors - i0);
+    size_t blocks = 0;
+    for (int k = 0; k < a.n; ++k) {
+      const int i = i0 + k;
+      a.t[k] = ExportTask{tr->theta + tr->off[i], tensors_out[i], tr->len[i], (unsigned)blocks,
+                          tr->cfg.dtype == SAPO_DTYPE_F32 || gain_tensor(tr->cfg, i) ? 1u : 0u};
+      blocks += (tr->len[i] + kExportBlock - 1) / kExportBlock;
+    }
+    T_CK(launch(KID_MISC, k_export, dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)stream, a));
   }
   return SAPO_OK;
 }
