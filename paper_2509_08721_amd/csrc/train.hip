@@ -717,15 +717,15 @@ hipError_t x3_sum_parts(const X3Bufs& bufs, int splits, size_t n, float beta, co
   return launch(KID_MISC, k_sum_parts, dim3((unsigned)((n + 1023) / 1024)), dim3(256), 0, st, (const float*)bufs.parts, splits, n, beta,
                 Cin, C);
 }
-// C[M, N] = beta C + op(A) op(B)^T-style product of two operands given row-wise over the same K
+// C[M, N] = beta C + op(A) op(B)^T-style product of two operands given row-wise over the same K; an operand packed earlier
+// (a_packed, b_packed) is used as it is
 hipError_t gemm_x3(const X3Op& A, const X3Op& B, float* C, const float* Cin, int ldc, float beta, const X3Bufs& bufs, hipStream_t st,
-                   const void* b_packed = nullptr, bool split_ok = true) {
+                   const void* b_packed = nullptr, bool split_ok = true, const void* a_packed = nullptr) {
   if (A.K != B.K || A.rows <= 0 || B.rows <= 0 || A.K <= 0) return hipErrorInvalidValue;
   hipError_t e;
-  if ((e = x3_pack(A, bufs.a, bufs.a_cap, bufs.NP, st)) != hipSuccess) return e;
-  // an operand packed earlier (b_packed) is used as it is
+  if (!a_packed && (e = x3_pack(A, bufs.a, bufs.a_cap, bufs.NP, st)) != hipSuccess) return e;
   if (!b_packed && (e = x3_pack(B, bufs.b, bufs.b_cap, bufs.NP, st)) != hipSuccess) return e;
-  const u32x4_t* pa_ = (const u32x4_t*)bufs.a;
+  const u32x4_t* pa_ = (const u32x4_t*)(a_packed ? a_packed : bufs.a);
   const u32x4_t* pb_ = (const u32x4_t*)(b_packed ? b_packed : bufs.b);
   const int KB = x3_steps(A.K, bufs.NP);
   const X3Grid g = x3_grid(bufs.NP, A.rows, B.rows, KB, x3_stage(bufs.NP), split_ok && ldc == B.rows ? bufs.parts_cap : 0);
@@ -1242,6 +1242,49 @@ __global__ void k_swiglu_bwd4(const float* __restrict__ dact, const float* __res
   *(float4*)out = dg;
   *(float4*)(out + F) = du;
 }
+// The same straight into the packed operands of the two products that read it, F % 64 == 0: by rows of tokens (for the d input
+// product) and by rows of features (for the weight gradients, which contract over the tokens).  dgu itself is not stored.
+// Bound by its bytes; 64 tokens x 64 features per workgroup, the tokens' octets for the second order through LDS.
+// Before, dgu was written and read three times in fp32 (by the packing and, between its MFMAs, by the product over
+// the tokens, which then took in twice its operands' bytes: 21 x 301 tokens, one piece, 297 us a layer at 0.37 PFLOP/s).
+template <int NP>
+__global__ void __launch_bounds__(256) k_swiglu_bwd_pack(const float* __restrict__ dact, const float* __restrict__ gu, int M, int F,
+                                                         int KB_rows, uint4* __restrict__ by_rows, int KB_cols,
+                                                         uint4* __restrict__ by_cols) {
+  __shared__ float tile[2][64][65];
+  const int f0 = blockIdx.x * 64, m0 = blockIdx.y * 64;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int r = (threadIdx.x >> 3) + 32 * i, c = (threadIdx.x & 7) * 8, m = m0 + r;
+    float dg[8], du[8];
+    if (m < M) {
+      const float *gp = gu + (size_t)m * 2 * F + f0 + c, *dp = dact + (size_t)m * F + f0 + c;
+      float g[8], u[8], da[8];
+      *(float4*)g = *(const float4*)gp; *(float4*)(g + 4) = *(const float4*)(gp + 4);
+      *(float4*)u = *(const float4*)(gp + F); *(float4*)(u + 4) = *(const float4*)(gp + F + 4);
+      *(float4*)da = *(const float4*)dp; *(float4*)(da + 4) = *(const float4*)(dp + 4);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) swiglu_grad(g[e], u[e], da[e], dg[e], du[e]);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) dg[e] = du[e] = 0.f;
+    }
+    x3_store<NP>(by_rows, KB_rows, m, (f0 + c) >> 3, dg);
+    x3_store<NP>(by_rows, KB_rows, m, (F + f0 + c) >> 3, du);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) { tile[0][r][c + e] = dg[e]; tile[1][r][c + e] = du[e]; }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int item = threadIdx.x + 256 * i, col = item & 63, oct = (item >> 6) & 7, half = item >> 9, k8 = (m0 >> 3) + oct;
+    if (k8 >= KB_cols * 2) continue;
+    float x[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = tile[half][oct * 8 + e][col];
+    x3_store<NP>(by_cols, KB_cols, half * F + f0 + col, k8, x);
+  }
+}
 // dgu from dact: d gate = dact * up * sig(g) (1 + g (1 - sig(g))), d up = dact * silu(g)
 __global__ void k_swiglu_bwd(const float* __restrict__ dact, const float* __restrict__ gu, float* __restrict__ dgu, int F,
                              size_t total) {
@@ -1718,7 +1761,7 @@ struct TrainPlan {
   float* xfc;                                   // the final-normed rows that predict a masked token, gathered
   int* eorder;                                  // a chunk's rows ordered by token (embedding gradient)
   int *mrows, *mpos, *mcount;                   // per micro-batch: those rows' indices (mpos: their (s, t)), their number
-  float *dh, *dx, *dact, *dgu, *dao, *dqkv;     // backward temporaries
+  float *dh, *dx, *dact, *dgu, *dao, *dqkv;     // backward temporaries (dgu: also its packed form by rows of features)
   float *delta, *prob, *dsc, *gpart, *logits, *logp_all, *loss;
   void* sur_ws;
   long long* n_masked;
@@ -1759,7 +1802,7 @@ void make_plan(const sapo_model_config& c, size_t S, size_t T, size_t S_total, c
   p.dh = A.take<float>(M * D.d);
   p.dx = A.take<float>(M * D.d);
   p.dact = A.take<float>(M * D.F);
-  p.dgu = A.take<float>(M * 2 * D.F);
+  p.dgu = A.take<float>(std::max(M * 2 * D.F, x3_pack_bytes(kPieces, 2 * D.F, M) / sizeof(float)));
   p.dao = A.take<float>(M * D.q);
   p.dqkv = A.take<float>(M * D.nqkv);
   p.delta = A.take<float>(S * c.n_q_heads * T);
@@ -2105,15 +2148,27 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
     // down projection
     T_CK(mm_nn(p.dh, d, TH(t0 + 8), F, p.dact, F, Mi, F, d, 0.f));
     T_CK(mm_tn(p.dh, d, a.act, F, GR(t0 + 8), d, F, Mi, 1.f));
-    if (F % 4 == 0 && M <= 65535)
-      T_CK(launch(KID_SWIGLU, k_swiglu_bwd4, dim3((F / 4 + 255) / 256, Mi), dim3(256), 0, st, (const float*)p.dact,
-                  (const float*)a.gu, p.dgu, F));
-    else
-      T_CK(launch(KID_SWIGLU, k_swiglu_bwd, dim3(blocks256(M * D.F)), dim3(256), 0, st, (const float*)p.dact, (const float*)a.gu,
-                p.dgu, F, M * D.F));
-    // gate / up projections
-    T_CK(mm_nn(p.dgu, 2 * F, TH(t0 + 6), d, p.dx, d, Mi, d, 2 * F, 0.f));
-    T_CK(mm_tn(p.dgu, 2 * F, a.xn2, d, GR(t0 + 6), 2 * F, d, Mi, 1.f));
+    const int mb = (Mi + 127) / 128 * 2;   // blocks of 64 tokens that the packed operands hold
+    if (F % 64 == 0 && mb <= 65535) {
+      const int KB_rows = x3_steps(2 * F, pieces), KB_cols = x3_steps(Mi, pieces);
+      auto pack = [&](auto kernel) {
+        return launch(KID_SWIGLU, kernel, dim3(F / 64, mb), dim3(256), 0, st, (const float*)p.dact, (const float*)a.gu, Mi, F, KB_rows,
+                      (uint4*)p.packa, KB_cols, (uint4*)p.dgu);
+      };
+      T_CK(pieces == 3 ? pack(k_swiglu_bwd_pack<3>) : pieces == 2 ? pack(k_swiglu_bwd_pack<2>) : pack(k_swiglu_bwd_pack<1>));
+      // gate / up projections
+      T_CK(gemm_x3(X3Op{nullptr, 0, Mi, 2 * F, false}, X3Op{TH(t0 + 6), d, d, 2 * F, true}, p.dx, p.dx, d, 0.f, xb, st, nullptr, true, p.packa));
+      T_CK(gemm_x3(X3Op{nullptr, 0, 2 * F, Mi, true}, X3Op{a.xn2, d, d, Mi, true}, GR(t0 + 6), GR(t0 + 6), d, 1.f, xb, st, nullptr, true, p.dgu));
+    } else {
+      if (F % 4 == 0 && M <= 65535)
+        T_CK(launch(KID_SWIGLU, k_swiglu_bwd4, dim3((F / 4 + 255) / 256, Mi), dim3(256), 0, st, (const float*)p.dact,
+                    (const float*)a.gu, p.dgu, F));
+      else
+        T_CK(launch(KID_SWIGLU, k_swiglu_bwd, dim3(blocks256(M * D.F)), dim3(256), 0, st, (const float*)p.dact, (const float*)a.gu,
+                    p.dgu, F, M * D.F));
+      T_CK(mm_nn(p.dgu, 2 * F, TH(t0 + 6), d, p.dx, d, Mi, d, 2 * F, 0.f));
+      T_CK(mm_tn(p.dgu, 2 * F, a.xn2, d, GR(t0 + 6), 2 * F, d, Mi, 1.f));
+    }
     T_CK(norm_bwd(p.dx, a.h2, a.r2, t0 + 5, 1));
     // output projection
     T_CK(mm_nn(p.dh, d, TH(t0 + 4), q, p.dao, q, Mi, q, d, 0.f));
