@@ -1370,12 +1370,91 @@ __device__ __forceinline__ void store_acc(float* __restrict__ row, const f32x4_t
   }
 }
 
+// Tiles of 16 positions, head dims in multiples of 64.  What bounded these kernels is the unit that returns loads from the L1:
+// read as rows, four neighbouring lanes of a float4 load are in four rows, and it returned a lane a cycle, 64 instead of 16
+// cycles per request (busy 60 - 69 % of the time, and all of the time that a compute unit had waves; the matrix cores
+// 27 - 33 %), and most tiles were read twice, as rows and by columns.  Now a tile is read once, by columns - lane (r, g)
+// holds chunk 16 j + r (4 dims) of the positions 4 g + u, 256 contiguous bytes per 16 lanes - which is the operand of the
+// products over the positions, and goes through the wave's own LDS (chunks XORed with the row's low bits: free of bank
+// conflicts both ways) for the products over the head dim; the next tile is on its way meanwhile.  Same products in the same
+// order.  The grids deal the longest walks first: causal walks are 1 .. T / 16 tiles long, and with the tile index fastest
+// the compute units had waves 62 % of the time.  Register limits leave two waves a SIMD (a limit for more spills).
+// us per layer, forward / d queries / d keys and values, before and now (with exp_split below):
+//   14 heads of 64,  64 x 384 tokens: 320 / 432 / 704, 245 / 330 / 449;   21 x 301: 77 / 96 / 150, 49 / 69 / 90
+//   12 heads of 128, 64 x 384 tokens: 494 / 705 / 1507, 388 / 657 / 871;   9 x 300: 79 / 101 / 180, 46 / 74 / 86
+// The matrix cores are now busy 52 - 60 % of the time a compute unit has waves ; the rest is
+// mostly the softmax's vector instructions, which a SIMD issues in turn with them.
+template <int HD> struct TileCols {
+  f32x4_t x[4][HD / 64];
+  unsigned off[4];   // bytes from the tile's first position to this lane's chunk of the positions 4 g + u
+  __device__ __forceinline__ void stride(size_t row_stride, int g, int r) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) off[u] = (unsigned)((4 * g + u) * row_stride + 4 * r) * 4u;
+  }
+  // tile_base and n_valid are the same for the wave: a whole tile's requests need no address arithmetic
+  __device__ __forceinline__ void load(const float* __restrict__ tile_base, size_t row_stride, int n_valid, int g, int r) {
+    if (n_valid >= 16) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int j = 0; j < HD / 64; ++j) x[u][j] = *(const f32x4_t*)((const char*)tile_base + off[u] + 256 * j);
+      return;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const float* row = tile_base + (size_t)min(4 * g + u, n_valid - 1) * row_stride;   // rows past the end repeat the last one
+#pragma unroll
+      for (int j = 0; j < HD / 64; ++j) x[u][j] = *(const f32x4_t*)(row + 64 * j + 4 * r);
+    }
+  }
+  // o += sum over the positions of this[position][dim] * p[position], as accumulate_tile
+  __device__ __forceinline__ void accumulate(const f32x4_t& p, f32x4_t (&o)[HD / 16]) const {
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int j = 0; j < HD / 64; ++j)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) o[4 * j + c] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[u][j][c], p[u], o[4 * j + c], 0, 0, 0);
+  }
+  // as rows (load_rows4's layout), through the wave's 16 x HD floats at `area`
+  __device__ __forceinline__ void rows(f32x4_t* area, int g, int r, float4 (&dst)[HD / 16]) const {
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int j = 0; j < HD / 64; ++j) area[(4 * g + u) * (HD / 4) + ((16 * j + r) ^ ((4 * g + u) & 7))] = x[u][j];
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+    for (int w = 0; w < HD / 16; ++w) {
+      const f32x4_t v = area[r * (HD / 4) + ((4 * w + g) ^ (r & 7))];
+      dst[w] = make_float4(v[0], v[1], v[2], v[3]);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");   // the next tile's values are not written before these are read
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  }
+};
+// exp(x) of a difference to a maximum or a log-sum-exp, as 2^(x log2 e): the product is split into its rounded value and what
+// the rounding dropped (an fma, and the part of log2 e behind its leading 24 bits), which enters to first order behind the
+// hardware's 2^y.  Below -200 (and -infinity, a masked score) the result is zero, NaN stays NaN; results under 2^-126 are
+// zero as well, where a probability is to be added to others of a sum of one.  Eight instructions; the library's also reduces
+// the range and scales back, which arguments of this kind do not need.
+__device__ __forceinline__ float exp_split(float x) {
+  constexpr float L = 0x1.715476p+0f, L_low = 0x1.4ae0bep-26f, ln2 = 0x1.62e43p-1f;   // log2 e = 0x1.71547652b82fep+0
+  x = x < -200.f ? -200.f : x;
+  const float y = x * L, e = __builtin_fmaf(x, L_low, __builtin_fmaf(x, L, -y));
+  const float p = __builtin_amdgcn_exp2f(y);
+  return __builtin_fmaf(p, e * ln2, p);
+}
+template <int HD> constexpr int tile_area() { return HD % 64 == 0 ? 16 * HD / 4 : 1; }   // float4s of LDS per wave and operand
+
 template <int HD>
-__global__ void __launch_bounds__(256, HD == 128 ? 3 : 1) k_tattn_fwd(const float* __restrict__ qkv, int T, int hq, int hkv, float scale,
+__global__ void __launch_bounds__(256, HD == 128 ? 2 : 1) k_tattn_fwd(const float* __restrict__ qkv, int T, int hq, int hkv, float scale,
                                                    float* __restrict__ out, float* __restrict__ lse) {
   const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
-  const int h = blockIdx.y, s = blockIdx.z, kvh = h / (hq / hkv);
-  const int q0 = (blockIdx.x * 4 + wave) * 16;
+  const int h = blockIdx.x, s = blockIdx.y, kvh = h / (hq / hkv);
+  const int q0 = (((int)gridDim.z - 1 - (int)blockIdx.z) * 4 + wave) * 16;   // the longest walks first
   if (q0 >= T) return;
   const int qd = hq * HD, kvd = hkv * HD;
   const size_t rl = (size_t)qd + 2 * kvd;
@@ -1391,10 +1470,23 @@ __global__ void __launch_bounds__(256, HD == 128 ? 3 : 1) k_tattn_fwd(const floa
   for (int dt = 0; dt < HD / 16; ++dt) o[dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   float m_run = -INFINITY, l_run = 0.f;
   const int last = min(q0 + 15, T - 1);
+  constexpr bool COLS = HD % 64 == 0;
+  __shared__ f32x4_t area[4][tile_area<HD>()];
+  TileCols<COLS ? HD : 64> kc, vc;
+  if constexpr (COLS) {
+    kc.stride(rl, g, r); vc.stride(rl, g, r);
+    kc.load(kb, rl, min(16, T), g, r);
+    vc.load(vb, rl, min(16, T), g, r);
+  }
   for (int k0 = 0; k0 <= last; k0 += 16) {
-    const int n_valid = min(16, T - k0);
+    const int n_valid = min(16, T - k0), k1 = k0 + 16 <= last ? k0 + 16 : k0;   // the next tile (behind the last one: it again)
     float4 kf[HD / 16];
-    load_rows4<HD>(kb, rl, min(k0 + r, T - 1), g, kf);
+    if constexpr (COLS) {
+      kc.rows(area[wave], g, r, kf);
+      kc.load(kb + (size_t)k1 * rl, rl, min(16, T - k1), g, r);
+    } else {
+      load_rows4<HD>(kb, rl, min(k0 + r, T - 1), g, kf);
+    }
     f32x4_t sc = dot_rows<HD>(kf, qf);   // rows: keys k0 + 4 g + v; column: query qi
     float mx = -INFINITY;
 #pragma unroll
@@ -1403,24 +1495,31 @@ __global__ void __launch_bounds__(256, HD == 128 ? 3 : 1) k_tattn_fwd(const floa
       sc[v] = (key <= qi && key < T) ? sc[v] * scale : -INFINITY;
       mx = fmaxf(mx, sc[v]);
     }
-    mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
-    mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+    mx = max_xor32(max_xor16(mx));
     const float m_new = fmaxf(m_run, mx);        // finite: key 0 is visible to every query
-    const float alpha = expf(m_run - m_new);
     f32x4_t p;
     float ps = 0.f;
 #pragma unroll
-    for (int v = 0; v < 4; ++v) { p[v] = expf(sc[v] - m_new); ps += p[v]; }
-    l_run = l_run * alpha + ps;
+    for (int v = 0; v < 4; ++v) { p[v] = exp_split(sc[v] - m_new); ps += p[v]; }
+    if (__builtin_amdgcn_ballot_w64(m_run != m_new) != 0) {   // the running maximum moved in some lane
+      const float alpha = exp_split(m_run - m_new);
+      asm volatile("");   // a branch, not 16 selects
+      l_run *= alpha;
+#pragma unroll
+      for (int dt = 0; dt < HD / 16; ++dt)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) o[dt][v] *= alpha;
+    }
+    l_run += ps;
     m_run = m_new;
-#pragma unroll
-    for (int dt = 0; dt < HD / 16; ++dt)
-#pragma unroll
-      for (int v = 0; v < 4; ++v) o[dt][v] *= alpha;
-    accumulate_tile<HD>(vb + (size_t)k0 * rl, rl, n_valid, g, r, p, o);
+    if constexpr (COLS) {
+      vc.accumulate(p, o);
+      vc.load(vb + (size_t)k1 * rl, rl, min(16, T - k1), g, r);
+    } else {
+      accumulate_tile<HD>(vb + (size_t)k0 * rl, rl, n_valid, g, r, p, o);
+    }
   }
-  l_run += __shfl_xor(l_run, 16, 64);
-  l_run += __shfl_xor(l_run, 32, 64);
+  l_run = sum_xor32(sum_xor16(l_run));
   if (q0 + r >= T) return;
   const float inv = 1.0f / l_run;
   store_acc<HD>(out + ((size_t)s * T + qi) * qd + (size_t)h * HD, o, g, inv);
@@ -1431,12 +1530,12 @@ __global__ void __launch_bounds__(256, HD == 128 ? 3 : 1) k_tattn_fwd(const floa
 //   p = exp(scale s - lse), dP = V dO^T, dS = scale p (dP - delta), dQ^T += K^T dS.
 // Writes dq into dqkv's query columns and delta[(s Hq + h) T + i].
 template <int HD>
-__global__ void __launch_bounds__(256, HD == 128 ? 3 : 1) k_tattn_bwd_q(const float* __restrict__ qkv, const float* __restrict__ out,
+__global__ void __launch_bounds__(256, 1) k_tattn_bwd_q(const float* __restrict__ qkv, const float* __restrict__ out,
                                                      const float* __restrict__ dout, const float* __restrict__ lse, int T, int hq,
                                                      int hkv, float scale, float* __restrict__ dqkv, float* __restrict__ delta) {
   const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
-  const int h = blockIdx.y, s = blockIdx.z, kvh = h / (hq / hkv);
-  const int q0 = (blockIdx.x * 4 + wave) * 16;
+  const int h = blockIdx.x, s = blockIdx.y, kvh = h / (hq / hkv);
+  const int q0 = (((int)gridDim.z - 1 - (int)blockIdx.z) * 4 + wave) * 16;   // the longest walks first
   if (q0 >= T) return;
   const int qd = hq * HD, kvd = hkv * HD;
   const size_t rl = (size_t)qd + 2 * kvd;
@@ -1453,29 +1552,45 @@ __global__ void __launch_bounds__(256, HD == 128 ? 3 : 1) k_tattn_bwd_q(const fl
 #pragma unroll
   for (int w = 0; w < HD / 16; ++w)
     dl += dof[w].x * of[w].x + dof[w].y * of[w].y + dof[w].z * of[w].z + dof[w].w * of[w].w;
-  dl += __shfl_xor(dl, 16, 64);
-  dl += __shfl_xor(dl, 32, 64);
+  dl = sum_xor32(sum_xor16(dl));
   const size_t stat = ((size_t)s * hq + h) * T + qi;
   const float l = lse[stat];
   f32x4_t dq[HD / 16];
 #pragma unroll
   for (int dt = 0; dt < HD / 16; ++dt) dq[dt] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   const int last = min(q0 + 15, T - 1);
+  constexpr bool COLS = HD % 64 == 0;
+  __shared__ f32x4_t area[4][2][tile_area<HD>()];
+  TileCols<COLS ? HD : 64> kc, kn, vc;
+  if constexpr (COLS) {
+    kn.stride(rl, g, r); vc.stride(rl, g, r);
+    kn.load(kb, rl, min(16, T), g, r);
+    vc.load(vb, rl, min(16, T), g, r);
+  }
   for (int k0 = 0; k0 <= last; k0 += 16) {
-    const int n_valid = min(16, T - k0);
+    const int n_valid = min(16, T - k0), k1 = k0 + 16 <= last ? k0 + 16 : k0;   // the next tile (behind the last one: it again)
     float4 kf[HD / 16], vf[HD / 16];
-    load_rows4<HD>(kb, rl, min(k0 + r, T - 1), g, kf);
-    load_rows4<HD>(vb, rl, min(k0 + r, T - 1), g, vf);
+    if constexpr (COLS) {
+      kc = kn;
+      kc.rows(area[wave][0], g, r, kf);
+      vc.rows(area[wave][1], g, r, vf);
+      kn.load(kb + (size_t)k1 * rl, rl, min(16, T - k1), g, r);
+      vc.load(vb + (size_t)k1 * rl, rl, min(16, T - k1), g, r);
+    } else {
+      load_rows4<HD>(kb, rl, min(k0 + r, T - 1), g, kf);
+      load_rows4<HD>(vb, rl, min(k0 + r, T - 1), g, vf);
+    }
     const f32x4_t sc = dot_rows<HD>(kf, qf);    // rows: keys k0 + 4 g + v; column: query qi
     const f32x4_t dp = dot_rows<HD>(vf, dof);   // dP[key][query] = v_key . dO_query
     f32x4_t ds;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const int key = k0 + 4 * g + v;
-      const float pv = (key <= qi && key < T) ? expf(sc[v] * scale - l) : 0.f;
+      const float pv = (key <= qi && key < T) ? exp_split(sc[v] * scale - l) : 0.f;
       ds[v] = scale * pv * (dp[v] - dl);
     }
-    accumulate_tile<HD>(kb + (size_t)k0 * rl, rl, n_valid, g, r, ds, dq);
+    if constexpr (COLS) kc.accumulate(ds, dq);
+    else accumulate_tile<HD>(kb + (size_t)k0 * rl, rl, n_valid, g, r, ds, dq);
   }
   if (q0 + r >= T) return;
   store_acc<HD>(dqkv + ((size_t)s * T + qi) * rl + (size_t)h * HD, dq, g, 1.0f);
@@ -1483,18 +1598,18 @@ __global__ void __launch_bounds__(256, HD == 128 ? 3 : 1) k_tattn_bwd_q(const fl
 }
 
 // Backward, keys and values: a wave owns 16 keys of one (sequence, KV head) and walks n_heads query heads of the group
-// (part blockIdx.y / hkv of it) and the query tiles from its own on, in that fixed order; n_heads = 1 leaves one partial
+// (part blockIdx.x / hkv of it) and the query tiles from its own on, in that fixed order; n_heads = 1 leaves one partial
 // result per query head, which k_attn_bwd_finish adds in head order (all heads in one wave left the chip a fifth full:
 // 840 waves of up to 7 x 19 dependent tiles at 21 x 301):
 //   p = exp(scale s - lse_q), dV^T += dO^T p, dP = dO V^T, dS = scale p (dP - delta_q), dK^T += Q^T dS.
 template <int HD>
-__global__ void __launch_bounds__(256, HD == 64 ? 4 : 1) k_tattn_bwd_kv(const float* __restrict__ qkv, const float* __restrict__ dout,
+__global__ void __launch_bounds__(256, HD == 64 ? 2 : 1) k_tattn_bwd_kv(const float* __restrict__ qkv, const float* __restrict__ dout,
                                                       const float* __restrict__ lse, const float* __restrict__ delta, int T, int hq,
                                                       int hkv, float scale, int n_heads, float* __restrict__ dkv, size_t row_stride,
                                                       size_t part_stride) {
   const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
-  const int kvh = blockIdx.y % hkv, part = blockIdx.y / hkv, s = blockIdx.z, rep = hq / hkv;
-  const int k0 = (blockIdx.x * 4 + wave) * 16;
+  const int kvh = blockIdx.x % hkv, part = blockIdx.x / hkv, s = blockIdx.y, rep = hq / hkv;
+  const int k0 = (blockIdx.z * 4 + wave) * 16;   // the longest walks first
   if (k0 >= T) return;
   const int qd = hq * HD, kvd = hkv * HD;
   const size_t rl = (size_t)qd + 2 * kvd;
@@ -1509,30 +1624,58 @@ __global__ void __launch_bounds__(256, HD == 64 ? 4 : 1) k_tattn_bwd_kv(const fl
   f32x4_t dk[HD / 16], dv[HD / 16];
 #pragma unroll
   for (int dt = 0; dt < HD / 16; ++dt) { dk[dt] = f32x4_t{0.f, 0.f, 0.f, 0.f}; dv[dt] = dk[dt]; }
+  constexpr bool COLS = HD % 64 == 0;
+  __shared__ f32x4_t area[4][2][tile_area<HD>()];
   for (int hh = 0; hh < n_heads; ++hh) {
     const int h = kvh * rep + part * n_heads + hh;
     const float* qb = base + (size_t)h * HD;
     const float* dob = dout + (size_t)s * T * qd + (size_t)h * HD;
     const float* lse_h = lse + ((size_t)s * hq + h) * T;
     const float* del_h = delta + ((size_t)s * hq + h) * T;
+    TileCols<COLS ? HD : 64> qc, qn, doc, don;
+    if constexpr (COLS) {
+      qn.stride(rl, g, r); don.stride(qd, g, r);
+      qn.load(qb + (size_t)k0 * rl, rl, min(16, T - k0), g, r);
+      don.load(dob + (size_t)k0 * qd, qd, min(16, T - k0), g, r);
+    }
     for (int q0 = k0; q0 < T; q0 += 16) {
-      const int n_valid = min(16, T - q0);
+      const int n_valid = min(16, T - q0), q1 = q0 + 16 < T ? q0 + 16 : q0;   // the next tile (behind the last one: it again)
       float4 qf[HD / 16], dof[HD / 16];
-      load_rows4<HD>(qb, rl, min(q0 + r, T - 1), g, qf);
-      load_rows4<HD>(dob, qd, min(q0 + r, T - 1), g, dof);
+      if constexpr (COLS) {
+        qc = qn; doc = don;
+        qc.rows(area[wave][0], g, r, qf);
+        doc.rows(area[wave][1], g, r, dof);
+        qn.load(qb + (size_t)q1 * rl, rl, min(16, T - q1), g, r);
+        don.load(dob + (size_t)q1 * qd, qd, min(16, T - q1), g, r);
+      } else {
+        load_rows4<HD>(qb, rl, min(q0 + r, T - 1), g, qf);
+        load_rows4<HD>(dob, qd, min(q0 + r, T - 1), g, dof);
+      }
       const f32x4_t sc = dot_rows<HD>(qf, kf);    // rows: queries q0 + 4 g + v; column: key kj
       const f32x4_t dp = dot_rows<HD>(dof, vf);   // dP[query][key]
       f32x4_t pv, ds;
+      float ls[4], de[4];
+      if (n_valid == 16) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) { ls[v] = (lse_h + q0)[4 * g + v]; de[v] = (del_h + q0)[4 * g + v]; }
+      } else {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) { const int qc = min(q0 + 4 * g + v, T - 1); ls[v] = lse_h[qc]; de[v] = del_h[qc]; }
+      }
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int qi = q0 + 4 * g + v;
-        const int qc = min(qi, T - 1);
-        const float pr = (key_ok && qi < T && kj <= qi) ? expf(sc[v] * scale - lse_h[qc]) : 0.f;
+        const float pr = (key_ok && qi < T && kj <= qi) ? exp_split(sc[v] * scale - ls[v]) : 0.f;
         pv[v] = pr;
-        ds[v] = scale * pr * (dp[v] - del_h[qc]);
+        ds[v] = scale * pr * (dp[v] - de[v]);
       }
-      accumulate_tile<HD>(dob + (size_t)q0 * qd, qd, n_valid, g, r, pv, dv);
-      accumulate_tile<HD>(qb + (size_t)q0 * rl, rl, n_valid, g, r, ds, dk);
+      if constexpr (COLS) {
+        doc.accumulate(pv, dv);
+        qc.accumulate(ds, dk);
+      } else {
+        accumulate_tile<HD>(dob + (size_t)q0 * qd, qd, n_valid, g, r, pv, dv);
+        accumulate_tile<HD>(qb + (size_t)q0 * rl, rl, n_valid, g, r, ds, dk);
+      }
     }
   }
   if (!key_ok) return;
@@ -1545,14 +1688,14 @@ template <int HD>
 hipError_t tattn_bwd(const float* qkv, const float* out, const float* dout, const float* lse, int S, int T, int hq, int hkv,
                      float scale, float* dqkv, float* delta, float* parts, hipStream_t st) {
   const unsigned tiles = (unsigned)((T + 63) / 64);
-  hipError_t e = launch(KID_ATTN_GENERIC, k_tattn_bwd_q<HD>, dim3(tiles, hq, S), dim3(256), 0, st, qkv, out, dout, lse, T, hq, hkv,
+  hipError_t e = launch(KID_ATTN_GENERIC, k_tattn_bwd_q<HD>, dim3(hq, S, tiles), dim3(256), 0, st, qkv, out, dout, lse, T, hq, hkv,
                         scale, dqkv, delta);
   if (e != hipSuccess) return e;
   const size_t qd = (size_t)hq * HD, kvd = (size_t)hkv * HD;
   if (parts)   // [query heads of a group][S T][2 kvd]
-    return launch(KID_ATTN_GENERIC, k_tattn_bwd_kv<HD>, dim3(tiles, hq, S), dim3(256), 0, st, qkv, dout, lse, (const float*)delta, T,
+    return launch(KID_ATTN_GENERIC, k_tattn_bwd_kv<HD>, dim3(hq, S, tiles), dim3(256), 0, st, qkv, dout, lse, (const float*)delta, T,
                   hq, hkv, scale, 1, parts, 2 * kvd, (size_t)S * T * 2 * kvd);
-  return launch(KID_ATTN_GENERIC, k_tattn_bwd_kv<HD>, dim3(tiles, hkv, S), dim3(256), 0, st, qkv, dout, lse, (const float*)delta, T,
+  return launch(KID_ATTN_GENERIC, k_tattn_bwd_kv<HD>, dim3(hkv, S, tiles), dim3(256), 0, st, qkv, dout, lse, (const float*)delta, T,
                 hq, hkv, scale, hq / hkv, dqkv + qd, qd + 2 * kvd, (size_t)0);
 }
 // The partial results of k_tattn_bwd_kv added in part order into dqkv's key and value columns, and the rotary embedding's
@@ -2078,7 +2221,7 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
                   hq + hkv, hd, nqkv, 1.0f, total));
     }
     if (fused_attn) {
-      const dim3 ag((unsigned)((T + 63) / 64), hq, (unsigned)S);
+      const dim3 ag(hq, (unsigned)S, (unsigned)((T + 63) / 64));
       hipError_t e = hipErrorInvalidValue;
       if (hd == 16) e = launch(KID_ATTN_GENERIC, k_tattn_fwd<16>, ag, dim3(256), 0, st, (const float*)a.qkv, (int)T, hq, hkv, att_scale, a.ao, a.lse);
       if (hd == 32) e = launch(KID_ATTN_GENERIC, k_tattn_fwd<32>, ag, dim3(256), 0, st, (const float*)a.qkv, (int)T, hq, hkv, att_scale, a.ao, a.lse);

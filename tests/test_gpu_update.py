@@ -517,3 +517,54 @@ def test_update_of_many_rows(sapo, S, T, masked):
     for i, (g, b) in enumerate(zip(read_all(sapo, tr, 1), ref_g)):
         assert float(np.max(np.abs(g - b))) <= 2e-4 * max(float(np.max(np.abs(b))), 1e-3 * gmax) + 1e-7, i
     tr.close()
+
+
+def tiles_shape(head_dim, d_ff):
+    return W.ModelShape(n_layers=2, d_model=64, n_q_heads=4, n_kv_heads=2, head_dim=head_dim, d_ff=d_ff, vocab=160,
+                        rms_eps=1e-6, rope_theta=1e4, tied_embeddings=True, dtype="f32", max_seq=160)
+
+
+# The attention's tiles of 16 positions and blocks of 64 (one short, whole, one over), and the SwiGLU backward's 64 x 64 blocks
+# in rows and columns (widths in multiples of 64 take the kernel that packs; 72 does not).  Tolerances as for the other sizes
+# with the same number of pieces.  `sharp` scales the query projections, so that the scores of a row lie hundreds apart (up to
+# 450 here) and most probabilities are zero: an fp32 score of 450 is good to about 8 of its 2^-24, 2.1e-4, which is the
+# relative error of its probability; it enters the gradients twice, on top of the 2e-4 of the other cases: 7e-4.
+@pytest.mark.parametrize("head_dim,d_ff,S,T,pieces,sharp", [
+    (64, 64, 3, 15, 3, 1), (64, 64, 2, 16, 3, 1), (64, 128, 3, 17, 2, 1), (64, 192, 2, 47, 1, 1), (64, 64, 1, 63, 3, 1),
+    (64, 72, 2, 64, 3, 1), (64, 128, 2, 65, 1, 1), (64, 128, 1, 129, 3, 1), (64, 64, 3, 80, 2, 1),
+    (128, 64, 2, 16, 2, 1), (128, 72, 3, 33, 3, 1), (128, 128, 1, 64, 1, 1), (128, 64, 2, 65, 3, 1), (128, 128, 1, 145, 3, 1),
+    (64, 64, 2, 70, 3, 24), (128, 64, 2, 49, 3, 24)])
+def test_update_at_the_edges_of_tiles(sapo, head_dim, d_ff, S, T, pieces, sharp):
+    import torch
+    from oracle import sapo_update_oracle as U
+    grad_tol, logp_tol = {3: (2e-4, 2e-4), 2: (1e-3, 5e-4), 1: (5e-2, 2e-2)}[pieces]
+    if sharp != 1:
+        grad_tol, logp_tol = 7e-4, 7e-4
+    shape = tiles_shape(head_dim, d_ff)
+    # bf16 operands are good to 2^-9 each, so a log-prob to about 2^-8 of the largest logit (12 with weights of 0.25, times
+    # what the layers before it add): the bound of 2e-2 is for the small weights that it was set for, logits below 1
+    w = W.perturb_norm_gains(W.make_weights(shape, 40 + T, std=0.25 if pieces > 1 else 0.02), T)
+    for lw in w["layers"]:
+        lw["wq"] = (lw["wq"] * sharp).astype(lw["wq"].dtype)
+    rng = np.random.default_rng([head_dim, T])
+    tokens = rng.integers(0, shape.vocab, size=(S, T)).astype(np.int32)
+    mask = np.zeros((S, T), dtype=np.uint8)
+    mask[:, max(1, T - 20):] = 1
+    adv = np.where(np.arange(S) % 2 == 0, 1.25, -0.75).astype(np.float32)
+    params = U.parameter_list(shape, w)
+    _, lp, _ = U.loss_and_gradients(shape, params, tokens, mask, np.zeros((S, T), np.float32), adv)
+    # ratios clear of 1, where the loss of either sign has one branch
+    logp_old = (lp + np.where(rng.random((S, T)) < 0.5, -0.1, 0.1) * (mask != 0)).astype(np.float32)
+    ref_loss, ref_lp, ref_g = U.loss_and_gradients(shape, params, tokens, mask, logp_old, adv)
+    tr = sapo.sapo_trainer_create(shape, w)
+    sapo.sapo_trainer_set_matmul_pieces(tr, pieces)
+    loss, lp_new = sapo.sapo_policy_update(tr, dev(tokens), dev(mask), dev(logp_old), dev(adv))
+    torch.cuda.synchronize()
+    assert np.max(np.abs(lp_new.cpu().numpy() - ref_lp)) < logp_tol
+    gmax = max(float(np.max(np.abs(b))) for b in ref_g)
+    for i, (a, b) in enumerate(zip(read_all(sapo, tr, 1), ref_g)):
+        if pieces == 1:   # bf16 operands: the tensor's norm, as of the other sizes
+            assert np.linalg.norm(a - b) <= grad_tol * max(np.linalg.norm(b), 1e-3 * gmax), (i, np.linalg.norm(a - b))
+        else:
+            assert float(np.max(np.abs(a - b))) <= grad_tol * max(float(np.max(np.abs(b))), 1e-3 * gmax) + 1e-7, i
+    tr.close()
