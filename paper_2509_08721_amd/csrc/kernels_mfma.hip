@@ -651,10 +651,72 @@ __global__ void __launch_bounds__(256, 2) k_gemm_mid(const uint4* __restrict__ X
 // accumulator blocks on.  q goes out as half row-major [M, Hq hd] (flash attention's operand), rotated k and v go to the
 // row's cache page.
 // ---------------------------------------------------------------------------------------
-// The epilogue of a wave's tile of NH heads, the first of them head0.
+// A wave's 64 tokens x 128 features of values, finished, into their V pages.  A lane's accumulators are features of one token,
+// a page holds 8 tokens of a feature side by side: written from the registers that is two bytes per lane in runs of 16
+// bytes, and the few workgroups with values end the launch.  They go through the wave's own LDS ([feature][token]) and leave
+// as 16 bytes per lane wherever 8 slots are all here.  0.5B, 9 x 301 tokens: 31.4 -> 20.7 us per launch (with the values' stores
+// left out 20.1; 64 features at a time, twice the runs, 24.7).
+constexpr int kValueStride = 66;   // halves from a feature to the next: the lanes of a write and of a read are in different banks
+constexpr int kQkvLds = 4 * 128 * kValueStride * (int)sizeof(f16);   // the ring is smaller; two workgroups fit a compute unit
+static_assert(kQkvLds >= kBigLds && 2 * kQkvLds <= 160 * 1024, "ring, then the values of four waves");
+template <int HD>
+__device__ __forceinline__ void store_values(f32x16 (&acc)[4][2], const QkvEpi& ep, int head0, int row0, int M, const int (&pos_of)[2],
+                                             const int (&page_of)[2], const bool (&keeps)[2], f16* area) {
+  constexpr int RS = kValueStride;
+  const int lane = threadIdx.x & 63, half_sel = lane >> 5, n_tok = min(64, M - row0);
+  const int hkv = ep.kv.n_kv_heads;
+#pragma unroll
+  for (int b = 0; b < 4; ++b)
+#pragma unroll
+    for (int tj = 0; tj < 2; ++tj)
+#pragma unroll
+      for (int v = 0; v < 16; ++v)
+        area[(b * 32 + 8 * (v >> 2) + (v & 3) + 4 * half_sel) * RS + tj * 32 + (lane & 31)] = from_f32<f16>(acc[b][tj][v]);
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  // features lane and lane + 64 of the tile: head f / HD, dim f % HD
+  f16* vpool = (f16*)ep.kv.v + (size_t)(head0 - ep.n_q_heads - hkv) * HD * kPageTokens;
+  const int at0 = (lane / HD) * HD * kPageTokens + v_page_at(0, lane % HD);
+  const int at1 = ((lane + 64) / HD) * HD * kPageTokens + v_page_at(0, (lane + 64) % HD);
+  const f16* src0 = area + lane * RS;
+  const f16* src1 = src0 + 64 * RS;
+  const unsigned long long kept[2] = {__builtin_amdgcn_ballot_w64(keeps[0]), __builtin_amdgcn_ballot_w64(keeps[1])};
+  const unsigned long long kept64 = (kept[0] & 0xffffffffull) | (kept[1] << 32);   // bit t: token t stays in the cache
+  // runs of tokens within 8 slots of a page; the lane that looked a token up knows its position and page
+  for (int t = 0; t < n_tok;) {
+    const int from = t & 31, pos = __builtin_amdgcn_readlane(t < 32 ? pos_of[0] : pos_of[1], from);
+    const int page = __builtin_amdgcn_readlane(t < 32 ? page_of[0] : page_of[1], from);
+    const int n = ep.rm.decode ? 1 : min(min(8 - (pos & 7), n_tok - t), ep.rm.T - pos);
+    f16* dst = vpool + (size_t)page * hkv * HD * kPageTokens + v_page_at(pos % kPageTokens, 0);
+    const unsigned stays = (unsigned)(kept64 >> t) & ((1u << n) - 1);
+    if (stays == 0xff) {
+      Frag o0, o1;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) { o0.h[i] = src0[t + i]; o1.h[i] = src1[t + i]; }
+      *(uint4*)(dst + at0) = o0.u;
+      *(uint4*)(dst + at1) = o1.u;
+    } else {
+      for (int i = 0; i < n; ++i)
+        if (stays >> i & 1) { dst[at0 + i] = src0[t + i]; dst[at1 + i] = src1[t + i]; }
+    }
+    t += n;
+  }
+}
+
+// Of two groups of 4 values per lane, lanes l and l + 32 holding the first and the second half of 8: lane l's 8 of `a`, lane
+// l + 32's 8 of `b`
+__device__ __forceinline__ uint4 trade_halves(f16x4 a, f16x4 b) {
+  typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+  const u32x2 x = __builtin_bit_cast(u32x2, a), y = __builtin_bit_cast(u32x2, b);
+  const u32x2 w0 = __builtin_amdgcn_permlane32_swap(x[0], y[0], false, false), w1 = __builtin_amdgcn_permlane32_swap(x[1], y[1], false, false);
+  return make_uint4(w0[0], w1[0], w0[1], w1[1]);
+}
+
+// The epilogue of a wave's tile of NH heads, the first of them head0.  smem: the workgroup's ring (large tiles).
 template <int HD, int NH, int TJ>
 __device__ __forceinline__ void qkv_epilogue(f32x16 (&acc)[NH * (HD / 32)][TJ], const QkvEpi& ep, int head0, int tok0, int M,
-                                             const float (&row_scale)[TJ]) {
+                                             const float (&row_scale)[TJ], uint4* smem = nullptr) {
   constexpr int NB = HD / 32;   // accumulator blocks of a head
   const int lane = threadIdx.x & 63;
   const int hq = ep.n_q_heads, hkv = ep.kv.n_kv_heads;
@@ -691,6 +753,14 @@ __device__ __forceinline__ void qkv_epilogue(f32x16 (&acc)[NH * (HD / 32)][TJ], 
     page_of[tj] = ep.kv.page_table[(size_t)seq * ep.kv.pages_per_seq + pos_of[tj] / kPageTokens];
   }
   const bool rotates = head0 < hq + hkv;   // else the tile is all V
+  if constexpr (TJ == 2) {
+    if (!rotates) {   // the same for the workgroup
+      wg_barrier();   // nobody reads the ring any more
+      store_values<HD>(acc, ep, head0, tok0 - (lane & 31), M, pos_of, page_of, keeps,
+                       (f16*)smem + wave_index(threadIdx.x) * (kQkvLds / 4 / sizeof(f16)));
+      return;
+    }
+  }
 #pragma unroll
   for (int tj = 0; tj < TJ; ++tj) {
     const int tok = tok0 + tj * 32;
@@ -713,21 +783,19 @@ __device__ __forceinline__ void qkv_epilogue(f32x16 (&acc)[NH * (HD / 32)][TJ], 
       if (head >= hq && !keeps[tj]) continue;
       if (head >= hq + hkv) {
         const int vh = head - hq - hkv;
-        f16* vp = vpool + ((size_t)page_of[tj] * hkv + vh) * HD * kPageTokens;
+        // the lane's dims are 4 half_sel + a constant, which moves no carry in v_page_at: constant distances from its first one
+        f16* vp = vpool + ((size_t)page_of[tj] * hkv + vh) * HD * kPageTokens + v_page_at(pos_of[tj] % kPageTokens, 4 * half_sel);
 #pragma unroll
         for (int b = 0; b < NB; ++b)
 #pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            const int f = b * 32 + 8 * (v >> 2) + (v & 3) + half_sel * 4;
-            vp[v_page_at(pos_of[tj] % kPageTokens, f)] = from_f32<f16>(acc[hh * NB + b][tj][v]);
-          }
+          for (int v = 0; v < 16; ++v) vp[v_page_at(0, b * 32 + 8 * (v >> 2) + (v & 3))] = from_f32<f16>(acc[hh * NB + b][tj][v]);
         continue;
       }
-      // start of the row's head, and the strides of 32 and of 8 dims: q row-major, k in its page (k_page_at)
+      // the row's head, q row-major, k in its page (k_page_at), from the lane's 8 dims of each 16 on
       const bool is_q = head < hq;
-      f16* dst = is_q ? ep.q_out + ((size_t)tok * hq + head) * HD
-                      : kpool + ((size_t)page_of[tj] * hkv + (head - hq)) * kPageTokens * HD + k_page_at(pos_of[tj] % kPageTokens, 0);
-      const int s32 = is_q ? 32 : k_page_at(0, 32), s8 = is_q ? 8 : k_page_at(0, 8);
+      f16* dst = is_q ? ep.q_out + ((size_t)tok * hq + head) * HD + half_sel * 8
+                      : kpool + ((size_t)page_of[tj] * hkv + (head - hq)) * kPageTokens * HD +
+                            k_page_at(pos_of[tj] % kPageTokens, half_sel * 8);
 #pragma unroll
       for (int b = 0; b < NB / 2; ++b) {
         f16x4 o1[4], o2[4];
@@ -744,11 +812,17 @@ __device__ __forceinline__ void qkv_epilogue(f32x16 (&acc)[NH * (HD / 32)][TJ], 
           }
         }
         if (b + 1 < NB / 2) request(b + 1);
+        // A lane holds dims 0 .. 3 or 4 .. 7 of every 8; two groups are traded with the lane that holds the others, so that each
+        // stores 16 bytes (8 at a time the rows of q took twice the requests: 64 x 768 tokens at 0.5B 160 -> 149 us per launch).
+        auto store = [&](auto at) {   // at(dim): where a dim lies behind the head's first one
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          *(f16x4*)(dst + b * s32 + r * s8 + half_sel * 4) = o1[r];
-          *(f16x4*)(dst + (b + NB / 2) * s32 + r * s8 + half_sel * 4) = o2[r];
-        }
+          for (int r = 0; r < 4; r += 2) {
+            *(uint4*)(dst + at(b * 32 + r * 8)) = trade_halves(o1[r], o1[r + 1]);
+            *(uint4*)(dst + at((b + NB / 2) * 32 + r * 8)) = trade_halves(o2[r], o2[r + 1]);
+          }
+        };
+        if (is_q) store([](int dim) { return dim; });
+        else store([](int dim) { return k_page_at(0, dim); });
       }
     }
   }
@@ -772,7 +846,7 @@ __global__ void __launch_bounds__(256, 2) k_gemm_qkv_rope(const uint4* __restric
     if (ep.ssq_in) row_scales<TJ>(ep.ssq_in, ep.ssq_parts, ep.ssq_halves, ep.norm_dim, ep.eps, tok0, M, row_scale);
     loop.run(smem, acc);
   }
-  qkv_epilogue<HD, NH, TJ>(acc, ep, bx * NH, tok0, M, row_scale);
+  qkv_epilogue<HD, NH, TJ>(acc, ep, bx * NH, tok0, M, row_scale, smem);
 }
 
 // The same for few tokens: 32 WM tokens x one head per workgroup
@@ -869,17 +943,17 @@ hipError_t m_gemm_qkv_rope(const void* Xp, const void* Wp, int M, int N, int K, 
   }
   static bool attr_done = false;
   if (!attr_done) {
-    hipError_t e = hipFuncSetAttribute((const void*)k_gemm_qkv_rope<64>, hipFuncAttributeMaxDynamicSharedMemorySize, kBigLds);
+    hipError_t e = hipFuncSetAttribute((const void*)k_gemm_qkv_rope<64>, hipFuncAttributeMaxDynamicSharedMemorySize, kQkvLds);
     if (e == hipSuccess)
-      e = hipFuncSetAttribute((const void*)k_gemm_qkv_rope<128>, hipFuncAttributeMaxDynamicSharedMemorySize, kBigLds);
+      e = hipFuncSetAttribute((const void*)k_gemm_qkv_rope<128>, hipFuncAttributeMaxDynamicSharedMemorySize, kQkvLds);
     if (e != hipSuccess) return e;
     attr_done = true;
   }
   const dim3 grid(big_grid(N / 128, (M + 255) / 256));
   if (hd == 64)
-    return launch(KID_GEMM_BIG, k_gemm_qkv_rope<64>, grid, dim3(256), kBigLds, st, (const uint4*)Xp, (const uint4*)Wp, M, N, K,
+    return launch(KID_GEMM_BIG, k_gemm_qkv_rope<64>, grid, dim3(256), kQkvLds, st, (const uint4*)Xp, (const uint4*)Wp, M, N, K,
                   epi);
-  return launch(KID_GEMM_BIG, k_gemm_qkv_rope<128>, grid, dim3(256), kBigLds, st, (const uint4*)Xp, (const uint4*)Wp, M, N, K,
+  return launch(KID_GEMM_BIG, k_gemm_qkv_rope<128>, grid, dim3(256), kQkvLds, st, (const uint4*)Xp, (const uint4*)Wp, M, N, K,
                 epi);
 }
 
@@ -1196,7 +1270,8 @@ hipError_t m_lmhead_sample_big(const void* Xp, const void* Wp, int n_rows, int V
 
 // =======================================================================================
 // Causal GQA attention for prefill and scoring (many positions per sequence), MFMA 16x16x32.
-// grid (64-position blocks, longest first; sequences x KV heads; groups of HPW query heads).
+// grid (sequences x KV heads; groups of HPW query heads; 64-position blocks), the longest walks of all sequences first: with
+// the blocks fastest the compute units had waves 71 % of the time.
 // A wave owns 16 query positions and up to HPW query heads that share the KV head, and walks the
 // keys 0 .. last query position in 32-key page pairs read straight from the paged cache into
 // fragment registers: S^T = K Q^T puts one query column in each lane, so the running max / sum are
@@ -1205,7 +1280,24 @@ hipError_t m_lmhead_sample_big(const void* Xp, const void* Wp, int n_rows, int V
 // consecutive tokens, the unit the token-minor V page delivers in one 16-byte load.  No LDS, no
 // block-level synchronisation; waves never exchange data.  q (row-major [rows, Hq hd]), K, V and the
 // probabilities are IEEE half; the output goes out as half in X32 order (the O projection's operand).
+// What bounds it: a SIMD issues MFMAs, vector instructions and (quarter rate) exponentials one after the other, 8 + ~35 + 8 per
+// head and page pair, and their serial sum is the time.  So what could go went: the exponents' reference follows the maximum
+// only in large steps (cross-lane maximum, rescaling and an exponential less in most pairs), no register copies between
+// the two page pairs in flight, page numbers as scalars, no operand quieting.  us per launch before and now: 64 x 768 tokens,
+// 14 heads of 64 198 -> 115 (of which the order of the blocks and the copies 198 -> 133), 12 heads of 128 322 -> 206; 9 x 301
+// tokens 15.0 -> 8.9.
 // ---------------------------------------------------------------------------------------
+// The largest of a lane's 8 scores, two accumulators of 4, in 4 instructions (fmaxf() quiets the results of MFMAs first, which
+// are not known to be free of signalling NaNs: 11).  The first one is the compiler's and reads both accumulators, so that
+// the wait states behind the MFMAs have passed before the asm, which it knows nothing about; inf: +infinity in a register
+// that it cannot see through.  A NaN score reaches the result through its own exponential whatever is found here.
+__device__ __forceinline__ float max8(const float (&p)[8], float inf) {
+  float m = __builtin_amdgcn_fmed3f(p[3], p[7], inf);
+  asm("v_max3_f32 %0, %0, %1, %2\n\tv_max3_f32 %0, %0, %3, %4\n\tv_max3_f32 %0, %0, %5, %6"
+      : "+v"(m) : "v"(p[0]), "v"(p[1]), "v"(p[2]), "v"(p[4]), "v"(p[5]), "v"(p[6]));
+  return m;
+}
+
 template <int HD, int HPW>
 __global__ void __launch_bounds__(256, 2) k_flash_attention(const f16* __restrict__ q, RowMap rm, KVCache kv,
                                                          f16* __restrict__ out, int n_q_heads) {
@@ -1213,14 +1305,16 @@ __global__ void __launch_bounds__(256, 2) k_flash_attention(const f16* __restric
   const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63;
   const int qcol = lane & 15, grp = lane >> 4;
   const int T = rm.T;
-  const int qb = gridDim.x - 1 - blockIdx.x;
+  const int qb = gridDim.z - 1 - blockIdx.z;   // the longest walks first, over all sequences
   const int hkv = kv.n_kv_heads, rep = n_q_heads / hkv;
-  const int sblk = blockIdx.y / hkv, kvh = blockIdx.y % hkv;
-  const int h0 = blockIdx.z * HPW;
+  const int sblk = blockIdx.x / hkv, kvh = blockIdx.x % hkv;
+  const int h0 = blockIdx.y * HPW;
   const int nh = min(HPW, rep - h0);
   const int q0 = qb * 64 + wave * 16;
   if (q0 >= T) return;
-  const int* pt = kv.page_table + (size_t)(sblk * rm.seq_stride) * kv.pages_per_seq;
+  // read through the constant address space: scalar loads, which do not queue behind the K / V fragments
+  typedef const __attribute__((address_space(4))) int* ConstInts;
+  const ConstInts pt = (ConstInts)(kv.page_table + (size_t)(sblk * rm.seq_stride) * kv.pages_per_seq);
   const size_t row0 = (size_t)sblk * T;
   const int qpos = min(q0 + qcol, T - 1);   // columns past T repeat the last position and are not stored
   const size_t qstride = (size_t)n_q_heads * HD;
@@ -1232,93 +1326,115 @@ __global__ void __launch_bounds__(256, 2) k_flash_attention(const f16* __restric
       for (int kk = 0; kk < KK; ++kk)
         qf[h][kk].u = *(const uint4*)(q + (row0 + qpos) * qstride + (size_t)(kvh * rep + h0 + h) * HD + kk * 32 + grp * 8);
     }
-  float m_run[HPW], l_run[HPW];
+  const float scale2 = 1.4426950408889634f / sqrtf((float)HD);   // scores in units of log2
+  // The exponents' reference m (in log2 units) follows a query's running maximum only once that lies more than kSlack above
+  // it: probabilities of up to 2^kSlack instead of 1, the same relative precision in half and in the fp32 sums.  limit: the
+  // raw score from which on it moves.  Per query, so that a query's result depends on nothing beside it.
+  constexpr float kSlack = 8.f;
+  const float slack_raw = kSlack / scale2;
+  float inf = INFINITY;
+  asm("" : "+s"(inf));
+  float m_ref[HPW], limit[HPW], l_run[HPW];
   f32x4 o[HPW][DT];
 #pragma unroll
   for (int h = 0; h < HPW; ++h) {
-    m_run[h] = -INFINITY; l_run[h] = 0.f;
+    m_ref[h] = -INFINITY; limit[h] = -INFINITY; l_run[h] = 0.f;
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) o[h][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-  const float scale2 = 1.4426950408889634f / sqrtf((float)HD);   // scores in units of log2
   const int q_hi = min(q0 + 15, T - 1);
   const int npairs = q_hi / 32 + 1;
   const int last_page = q_hi / kPageTokens;
-  const f16* kpool = (const f16*)kv.k;
-  const f16* vpool = (const f16*)kv.v;
-  const size_t page_elems = (size_t)hkv * kPageTokens * HD;
+  const size_t page_bytes = (size_t)hkv * kPageTokens * HD * sizeof(f16);
+  const char* kpool = (const char*)kv.k + (size_t)kvh * kPageTokens * HD * sizeof(f16);
+  const char* vpool = (const char*)kv.v + (size_t)kvh * kPageTokens * HD * sizeof(f16);
+  const unsigned k_off = k_frag_at(0, 0, lane) * sizeof(f16), v_off = v_frag_at(0, lane) * sizeof(f16);
+  const bool k_first = (lane & 15) < 8, v_first = grp < 2;
   // K / V fragments of a page pair; the next pair's are requested before the current one is multiplied (a third
   // register set, two pairs ahead, was measured at head dim 64: 238 against 223 us per launch at 64 x 768)
-  Frag kf[2][KK], vf[DT], kn[2][KK], vn[DT];
-  auto fetch = [&](int pp, Frag (&kd)[2][KK], Frag (&vd)[DT]) {
-    const int pa = pt[2 * pp];
-    const int pb = pt[min(2 * pp + 1, last_page)];
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      const f16* kp = kpool + (size_t)((lane & 15) < 8 ? pa : pb) * page_elems + (size_t)kvh * kPageTokens * HD;
-#pragma unroll
-      for (int kk = 0; kk < KK; ++kk) kd[t][kk].u = *(const uint4*)(kp + k_frag_at(t, kk, lane));
-    }
-    const f16* vp = vpool + (size_t)(grp < 2 ? pa : pb) * page_elems + (size_t)kvh * HD * kPageTokens;
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt) vd[dt].u = *(const uint4*)(vp + v_frag_at(dt, lane));
-  };
-  fetch(0, kn, vn);
-  for (int pp = 0; pp < npairs; ++pp) {
+  Frag kf[2][2][KK], vf[2][DT];
+  auto fetch = [&](int pp, auto buf) {
+    constexpr int b = decltype(buf)::value;
+    const size_t pa = (size_t)pt[2 * pp] * page_bytes, pb = (size_t)pt[min(2 * pp + 1, last_page)] * page_bytes;
+    const char* kp = kpool + (k_first ? pa : pb) + k_off;
+    const char* vp = vpool + (v_first ? pa : pb) + v_off;
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
-      for (int kk = 0; kk < KK; ++kk) kf[t][kk] = kn[t][kk];
+      for (int kk = 0; kk < KK; ++kk)
+        kf[b][t][kk].u = *(const uint4*)(kp + (k_frag_at(t, kk, 0) - k_frag_at(0, 0, 0)) * sizeof(f16));
 #pragma unroll
-    for (int dt = 0; dt < DT; ++dt) vf[dt] = vn[dt];
-    if (pp + 1 < npairs) fetch(pp + 1, kn, vn);
-    const bool diag = pp * 32 + 31 > q0;   // some (query, key) of the pair is masked
+    for (int dt = 0; dt < DT; ++dt) vf[b][dt].u = *(const uint4*)(vp + (v_frag_at(dt, 0) - v_frag_at(0, 0)) * sizeof(f16));
+  };
+  // DIAG: the walk's last pair, the only one with masked (query, key)s
+  auto multiply = [&](int pp, auto buf, auto diag) {
+    constexpr int b = decltype(buf)::value;
+    constexpr bool DIAG = decltype(diag)::value;
 #pragma unroll
     for (int h = 0; h < HPW; ++h) {
-      if (h >= nh) continue;
+      if (h >= nh) break;
       f32x4 sc[2];
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
         sc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int kk = 0; kk < KK; ++kk) sc[t] = mfma16h(kf[t][kk], qf[h][kk], sc[t]);
+        for (int kk = 0; kk < KK; ++kk) sc[t] = mfma16h(kf[b][t][kk], qf[h][kk], sc[t]);
       }
       // lane (query qcol, group grp) holds keys pp*32 + 8 grp + e, e = 4 t + j
       float p[8];   // raw scores; the softmax scale enters through the exponent's fma
 #pragma unroll
       for (int e = 0; e < 8; ++e) p[e] = sc[e >> 2][e & 3];
-      if (diag) {
+      if constexpr (DIAG) {
 #pragma unroll
         for (int e = 0; e < 8; ++e)
           if (pp * 32 + 8 * grp + e > qpos) p[e] = -INFINITY;
       }
-      float m_loc = fmaxf(fmaxf(fmaxf(p[0], p[1]), fmaxf(p[2], p[3])), fmaxf(fmaxf(p[4], p[5]), fmaxf(p[6], p[7])));
-      m_loc = max_xor16(m_loc);
-      m_loc = max_xor32(m_loc);
-      const float m_new = fmaxf(m_run[h], m_loc * scale2);   // finite: key 0 is visible to every query
-      const float alpha = __builtin_amdgcn_exp2f(m_run[h] - m_new);   // exp2(-inf) = 0 on the first pair
-      float psum = 0.f;
-      Frag pf;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float pe = __builtin_amdgcn_exp2f(fmaf(p[e], scale2, -m_new));
-        psum += pe;
-        pf.h[e] = (f16)pe;
-      }
-      l_run[h] = l_run[h] * alpha + psum;
-      m_run[h] = m_new;
-      if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {   // the running max moved in some lane
-        // the empty statement keeps this a branch: turned into selects, the 16 multiplies (and 16 selects) would run
-        // for every pair, a quarter of the loop's vector-ALU work
-        asm volatile("");
+      float m_loc = max8(p, inf);
+      if (__builtin_amdgcn_ballot_w64(m_loc > limit[h]) != 0) {   // some query's maximum left the slack
+        asm volatile("");   // a branch: as selects, its 30 instructions would run for every pair
+        m_loc = max_xor32(max_xor16(m_loc));
+        const bool moves = m_loc > limit[h];
+        const float m_new = moves ? m_loc * scale2 : m_ref[h];
+        const float alpha = __builtin_amdgcn_exp2f(m_ref[h] - m_new);   // exp2(-inf) = 0 on the first pair
+        limit[h] = moves ? m_loc + slack_raw : limit[h];
+        m_ref[h] = m_new;
+        l_run[h] *= alpha;
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
           for (int j = 0; j < 4; ++j) o[h][dt][j] *= alpha;
       }
+      float pe[8];
+      Frag pf;
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt) o[h][dt] = mfma16h(vf[dt], pf, o[h][dt]);
+      for (int e = 0; e < 8; ++e) {
+        pe[e] = __builtin_amdgcn_exp2f(fmaf(p[e], scale2, -m_ref[h]));
+        pf.h[e] = (f16)pe[e];
+      }
+      l_run[h] += ((pe[0] + pe[1]) + (pe[2] + pe[3])) + ((pe[4] + pe[5]) + (pe[6] + pe[7]));
+#pragma unroll
+      for (int dt = 0; dt < DT; ++dt) o[h][dt] = mfma16h(vf[b][dt], pf, o[h][dt]);
     }
+  };
+  const std::integral_constant<int, 0> even;
+  const std::integral_constant<int, 1> odd;
+  const std::true_type last;
+  const std::false_type inner;
+  // the requests of the loop sit under no branch: behind one, the compiler would wait for everything in flight
+  fetch(0, even);
+  int pp = 0;
+  for (; pp + 2 < npairs; pp += 2) {
+    fetch(pp + 1, odd);
+    multiply(pp, even, inner);
+    fetch(pp + 2, even);
+    multiply(pp + 1, odd, inner);
+  }
+  if (pp + 1 < npairs) {
+    fetch(pp + 1, odd);
+    multiply(pp, even, inner);
+    multiply(pp + 1, odd, last);
+  } else {
+    multiply(pp, even, last);
   }
   if (q0 + qcol >= T) return;
 #pragma unroll
@@ -1348,7 +1464,7 @@ hipError_t m_flash_attention(const void* q, RowMap rm, KVCache kv, void* out, in
   // SIMD, which hide the softmax arithmetic, pay for the second read of K / V.  With few sequences a wave's walk over the
   // keys is what the launch takes, and fewer heads shorten it: the most that still leave a workgroup for every compute unit.
   auto go = [&](auto kernel, int hpw) {
-    return launch(KID_FLASH_ATTN, kernel, dim3(nqb, n_seq * kv.n_kv_heads, (rep + hpw - 1) / hpw), dim3(256), 0, st, (const f16*)q, rm,
+    return launch(KID_FLASH_ATTN, kernel, dim3(n_seq * kv.n_kv_heads, (rep + hpw - 1) / hpw, nqb), dim3(256), 0, st, (const f16*)q, rm,
                   kv, (f16*)out, n_q_heads);
   };
   auto groups = [&](int hpw) { return (long)nqb * n_seq * kv.n_kv_heads * ((rep + hpw - 1) / hpw); };

@@ -148,3 +148,61 @@ def test_both_tile_heights_of_the_token_parallel_gemm_give_the_same_bits(sapo, m
         os.environ.pop("SAPO_BIG_TILE", None)
     assert np.array_equal(out["128"].view(np.uint32), out["256"].view(np.uint32))
     assert np.max(np.abs(out["256"] - O.score_logprobs(ma, toks, mask))) <= LOGPROB_TOL
+
+
+@pytest.mark.parametrize("shape_name,S,T,sharp", [("MINI_BF16", 1, 31, 24), ("MINI_BF16", 2, 33, 24), ("MINI_BF16", 2, 100, 24),
+                                                  ("MINI_BF16", 70, 65, 24), ("MINI_BF16_HD128", 1, 64, 10),
+                                                  ("MINI_BF16_HD128", 2, 129, 10), ("MINI_BF16_HD128", 140, 50, 10)])
+def test_scoring_with_scores_far_apart(sapo, shape_name, S, T, sharp):
+    """The token-parallel attention's reference exponent follows a query's maximum only in steps of more than 8 (in powers of
+    two): query projections scaled so that the scores of a row spread over 40 and more, at one page pair, one token over,
+    several pairs, and with the head counts per wave that many and few sequences get.  A score of 40 from halves is off
+    by 40 2^-11 = 0.02 at most and a tenth of that on average over the head dim's products; what that does to a
+    log-prob stays under the general tolerance at these weights.  Changing later tokens changes no earlier bit."""
+    shape = getattr(W, shape_name)
+    w = W.perturb_norm_gains(W.make_weights(shape, 77, std=0.05), 77)
+    for lw in w["layers"]:
+        lw["wq"] = W.f32_to_bf16_bits(W.bf16_bits_to_f32(lw["wq"]) * np.float32(sharp))
+    gw = sapo.sapo_weights_create(shape, w)
+    ma = O.Model(shape, w)
+    rng = np.random.default_rng(S * 1000 + T)
+    toks = rng.integers(0, shape.vocab, size=(S, T)).astype(np.int32)
+    mask = np.ones((S, T), dtype=np.uint8)
+    rewards = rng.random(S).astype(np.float32)
+    lp, _ = sapo.sapo_score_logprobs(gw, dev(toks), dev(mask), dev(rewards), 1)
+    lp = lp.cpu().numpy()
+    rows = [0, S - 1]
+    assert np.max(np.abs(lp[rows] - O.score_logprobs(ma, toks[rows], mask[rows]))) <= LOGPROB_TOL
+    later = toks.copy()
+    later[:, T - 3:] = (later[:, T - 3:] + 1 + rng.integers(0, shape.vocab - 1, size=(S, 3))) % shape.vocab
+    lp2, _ = sapo.sapo_score_logprobs(gw, dev(later), dev(mask), dev(rewards), 1)
+    assert np.array_equal(lp2.cpu().numpy()[:, :T - 3], lp[:, :T - 3])
+    gw.close()
+
+
+@pytest.mark.parametrize("kv_heads,head_dim,lens,T", [
+    (2, 64, [7] * 5, 7), (2, 64, [17] * 3, 17), (2, 64, [33] * 9, 33), (2, 64, [61] * 7, 61), (2, 64, [64] * 4, 64), (2, 64, [1, 9, 40], 40),
+    (2, 64, [31, 8, 16, 1, 24, 30], 31), (1, 64, [45] * 6, 45), (1, 128, [19] * 14, 19), (1, 128, [12, 5, 50], 50)])
+def test_value_pages_from_either_qkv_tile(sapo, kv_heads, head_dim, lens, T):
+    """The 256-token QKV tile writes the value pages 8 slots at a time through LDS, the small tiles a token per lane: prompts of
+    one length and of several (slots past a prompt's end stay untouched), aligned to 8 slots or not, several sequences
+    per wave, values and keys in one tile (one KV head of 64), both head dims.  The generated tokens and log-probs, whose
+    attention reads the pages, must agree bit for bit."""
+    import os
+    from dataclasses import replace
+    shape = replace(W.MINI_BF16 if head_dim == 64 else W.MINI_BF16_HD128, n_kv_heads=kv_heads)
+    w = W.perturb_norm_gains(W.make_weights(shape, 55, std=0.05), 55)
+    gw = sapo.sapo_weights_create(shape, w)
+    assert gw.uses_mfma
+    prompts = np.random.default_rng(T).integers(0, shape.vocab, size=(len(lens), T)).astype(np.int32)
+    out = {}
+    try:
+        for tile in (None, "256"):
+            if tile:
+                os.environ["SAPO_BIG_TILE"] = tile
+            toks, lps, _ = sapo.sapo_rollout_generate_ragged(gw, dev(prompts), lens, 2, 6, 1.0, 12)
+            out[tile] = toks.cpu().numpy(), lps.cpu().numpy()
+    finally:
+        os.environ.pop("SAPO_BIG_TILE", None)
+    assert np.array_equal(out[None][0], out["256"][0]) and np.array_equal(out[None][1], out["256"][1])
+    gw.close()
