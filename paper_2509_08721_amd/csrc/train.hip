@@ -1027,6 +1027,7 @@ __global__ void k_probs_from_lse(float* __restrict__ sc, const float* __restrict
   sc[idx] = (j <= i) ? expf(sc[idx] * scale - lse[r]) : 0.f;
 }
 
+__device__ __forceinline__ float swiglu(float g, float u) { return g / (1.0f + expf(-g)) * u; }
 // act = silu(gate) * up from gu[M, 2F] (gate columns first).  Workgroup (x, y): columns of row y, four per thread where F
 // allows it.
 __global__ void k_swiglu_fwd4(const float* __restrict__ gu, float* __restrict__ act, int F) {
@@ -1035,17 +1036,40 @@ __global__ void k_swiglu_fwd4(const float* __restrict__ gu, float* __restrict__ 
   const float* row = gu + (size_t)blockIdx.y * 2 * F + f;
   const float4 g = *(const float4*)row, u = *(const float4*)(row + F);
   float4 o;
-  o.x = g.x / (1.0f + expf(-g.x)) * u.x; o.y = g.y / (1.0f + expf(-g.y)) * u.y;
-  o.z = g.z / (1.0f + expf(-g.z)) * u.z; o.w = g.w / (1.0f + expf(-g.w)) * u.w;
+  o.x = swiglu(g.x, u.x); o.y = swiglu(g.y, u.y); o.z = swiglu(g.z, u.z); o.w = swiglu(g.w, u.w);
   *(float4*)(act + (size_t)blockIdx.y * F + f) = o;
+}
+// The same straight into the packed operand of the down projection, F % 64 == 0: act itself is not stored (the backward pass
+// makes its other packed form again, k_swiglu_bwd_pack).  64 tokens x 64 features per workgroup, bound by its bytes.  us a
+// layer of the 0.5B decoder for act and its packing before, and now: 64 x 384 tokens, three pieces 265 + 230, 329 (5.1 TB/s);
+// 21 x 301 tokens, one piece 61 + 39, 52 (5.9 TB/s).
+template <int NP>
+__global__ void __launch_bounds__(256) k_swiglu_fwd_pack(const float* __restrict__ gu, int M, int F, int KB, uint4* __restrict__ dst) {
+  const int f0 = blockIdx.x * 64, m0 = blockIdx.y * 64;
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int c = (threadIdx.x & 7) * 8, m = m0 + (threadIdx.x >> 3) + 32 * i;
+    float x[8];
+    if (m < M) {
+      const float* gp = gu + (size_t)m * 2 * F + f0 + c;
+      float g[8], u[8];
+      *(float4*)g = *(const float4*)gp; *(float4*)(g + 4) = *(const float4*)(gp + 4);
+      *(float4*)u = *(const float4*)(gp + F); *(float4*)(u + 4) = *(const float4*)(gp + F + 4);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x[e] = swiglu(g[e], u[e]);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x[e] = 0.f;
+    }
+    x3_store<NP>(dst, KB, m, (f0 + c) >> 3, x);
+  }
 }
 __global__ void k_swiglu_fwd(const float* __restrict__ gu, float* __restrict__ act, int F, size_t total) {
   const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
   if (idx >= total) return;
   const size_t m = idx / F;
   const int f = (int)(idx % F);
-  const float g = gu[m * 2 * F + f], u = gu[m * 2 * F + F + f];
-  act[idx] = g / (1.0f + expf(-g)) * u;
+  act[idx] = swiglu(gu[m * 2 * F + f], gu[m * 2 * F + F + f]);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1243,20 +1267,23 @@ __global__ void k_swiglu_bwd4(const float* __restrict__ dact, const float* __res
   *(float4*)(out + F) = du;
 }
 // The same straight into the packed operands of the two products that read it, F % 64 == 0: by rows of tokens (for the d input
-// product) and by rows of features (for the weight gradients, which contract over the tokens).  dgu itself is not stored.
+// product) and by rows of features (for the weight gradients, which contract over the tokens); act, which the down
+// projection's weight gradient contracts over the tokens, by rows of features as well.  Neither is stored in fp32.
 // Bound by its bytes; 64 tokens x 64 features per workgroup, the tokens' octets for the second order through LDS.
 // Before, dgu was written and read three times in fp32 (by the packing and, between its MFMAs, by the product over
 // the tokens, which then took in twice its operands' bytes: 21 x 301 tokens, one piece, 297 us a layer at 0.37 PFLOP/s).
+// act's packed form makes the pass longer (64 x 384 tokens, three pieces 826 -> 971 us a layer; 21 x 301, one piece 116 ->
+// 122) and the down projection's weight gradient shorter (1137 -> 775, 112 -> 47).
 template <int NP>
 __global__ void __launch_bounds__(256) k_swiglu_bwd_pack(const float* __restrict__ dact, const float* __restrict__ gu, int M, int F,
                                                          int KB_rows, uint4* __restrict__ by_rows, int KB_cols,
-                                                         uint4* __restrict__ by_cols) {
-  __shared__ float tile[2][64][65];
+                                                         uint4* __restrict__ by_cols, uint4* __restrict__ act_by_cols) {
+  __shared__ float tile[3][64][65];
   const int f0 = blockIdx.x * 64, m0 = blockIdx.y * 64;
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     const int r = (threadIdx.x >> 3) + 32 * i, c = (threadIdx.x & 7) * 8, m = m0 + r;
-    float dg[8], du[8];
+    float dg[8], du[8], act[8];
     if (m < M) {
       const float *gp = gu + (size_t)m * 2 * F + f0 + c, *dp = dact + (size_t)m * F + f0 + c;
       float g[8], u[8], da[8];
@@ -1264,25 +1291,28 @@ __global__ void __launch_bounds__(256) k_swiglu_bwd_pack(const float* __restrict
       *(float4*)u = *(const float4*)(gp + F); *(float4*)(u + 4) = *(const float4*)(gp + F + 4);
       *(float4*)da = *(const float4*)dp; *(float4*)(da + 4) = *(const float4*)(dp + 4);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) swiglu_grad(g[e], u[e], da[e], dg[e], du[e]);
+      for (int e = 0; e < 8; ++e) {
+        swiglu_grad(g[e], u[e], da[e], dg[e], du[e]);
+        act[e] = swiglu(g[e], u[e]);   // the forward's value to the bit
+      }
     } else {
 #pragma unroll
-      for (int e = 0; e < 8; ++e) dg[e] = du[e] = 0.f;
+      for (int e = 0; e < 8; ++e) dg[e] = du[e] = act[e] = 0.f;
     }
     x3_store<NP>(by_rows, KB_rows, m, (f0 + c) >> 3, dg);
     x3_store<NP>(by_rows, KB_rows, m, (F + f0 + c) >> 3, du);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) { tile[0][r][c + e] = dg[e]; tile[1][r][c + e] = du[e]; }
+    for (int e = 0; e < 8; ++e) { tile[0][r][c + e] = dg[e]; tile[1][r][c + e] = du[e]; tile[2][r][c + e] = act[e]; }
   }
   __syncthreads();
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int item = threadIdx.x + 256 * i, col = item & 63, oct = (item >> 6) & 7, half = item >> 9, k8 = (m0 >> 3) + oct;
+  for (int i = 0; i < 6; ++i) {
+    const int item = threadIdx.x + 256 * i, col = item & 63, oct = (item >> 6) & 7, which = item >> 9, k8 = (m0 >> 3) + oct;
     if (k8 >= KB_cols * 2) continue;
     float x[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) x[e] = tile[half][oct * 8 + e][col];
-    x3_store<NP>(by_cols, KB_cols, half * F + f0 + col, k8, x);
+    for (int e = 0; e < 8; ++e) x[e] = tile[which][oct * 8 + e][col];
+    x3_store<NP>(which < 2 ? by_cols : act_by_cols, KB_cols, (which == 1 ? F : 0) + f0 + col, k8, x);
   }
 }
 // dgu from dact: d gate = dact * up * sig(g) (1 + g (1 - sig(g))), d up = dact * silu(g)
@@ -1900,6 +1930,8 @@ struct LayerActs {
 };
 struct TrainPlan {
   std::vector<LayerActs> layer;
+  bool packed_ffn;                              // the SwiGLU passes write packed operands (act of a layer is not kept)
+  char* act_cols;                               // act of the layer at hand by rows of features
   float *h_last, *rf, *xf;                      // final residual rows, their rstd, final-normed rows
   float* xfc;                                   // the final-normed rows that predict a masked token, gathered
   int* eorder;                                  // a chunk's rows ordered by token (embedding gradient)
@@ -1919,6 +1951,7 @@ void make_plan(const sapo_model_config& c, size_t S, size_t T, size_t S_total, c
   const Dims D(c);
   const size_t M = S * T;
   Arena A{base, 0};
+  p.packed_ffn = D.F % 64 == 0 && (M + 127) / 128 * 2 <= 65535;
   p.layer.resize(D.L);
   for (int l = 0; l < D.L; ++l) {
     LayerActs& a = p.layer[l];
@@ -1932,7 +1965,7 @@ void make_plan(const sapo_model_config& c, size_t S, size_t T, size_t S_total, c
     a.r2 = A.take<float>(M);
     a.xn2 = A.take<float>(M * D.d);
     a.gu = A.take<float>(M * 2 * D.F);
-    a.act = A.take<float>(M * D.F);
+    a.act = A.take<float>(p.packed_ffn ? 0 : M * D.F);
   }
   p.h_last = A.take<float>(M * D.d);
   p.rf = A.take<float>(M);
@@ -1946,6 +1979,7 @@ void make_plan(const sapo_model_config& c, size_t S, size_t T, size_t S_total, c
   p.dx = A.take<float>(M * D.d);
   p.dact = A.take<float>(M * D.F);
   p.dgu = A.take<float>(std::max(M * 2 * D.F, x3_pack_bytes(kPieces, 2 * D.F, M) / sizeof(float)));
+  p.act_cols = A.take<char>(p.packed_ffn ? x3_pack_bytes(kPieces, D.F, M) : 0);
   p.dao = A.take<float>(M * D.q);
   p.dqkv = A.take<float>(M * D.nqkv);
   p.delta = A.take<float>(S * c.n_q_heads * T);
@@ -1965,7 +1999,7 @@ void make_plan(const sapo_model_config& c, size_t S, size_t T, size_t S_total, c
     const size_t R = p.chunk, twoF = 2 * D.F;
     const size_t a_shapes[][2] = {{M, D.d}, {M, D.q}, {M, D.F}, {M, twoF}, {M, D.nqkv}, {D.d, M}, {twoF, M}, {D.nqkv, M},
                                   {R, D.d}, {R, D.V}, {D.V, R}};
-    const size_t b_shapes[][2] = {{D.nqkv, D.d}, {D.d, D.q}, {twoF, D.d}, {D.d, D.F}, {D.F, D.d}, {D.F, M}, {D.d, twoF},
+    const size_t b_shapes[][2] = {{D.nqkv, D.d}, {D.d, D.q}, {twoF, D.d}, {D.d, D.F}, {D.F, D.d}, {D.d, twoF},
                                   {D.d, M}, {D.q, D.d}, {D.q, M}, {D.d, D.nqkv}, {D.d, R}};
     p.packa_cap = p.packb_cap = 0;
     for (auto& sh : a_shapes) p.packa_cap = std::max(p.packa_cap, x3_pack_bytes(kPieces, sh[0], sh[1]));
@@ -2206,6 +2240,7 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
     return gemm_x3_tn(A_, lda, B_, ldb, C, Mg, Ng, Kg, beta, xb, st);   // C = beta C + A^T B
   };
 
+  const int blocks64 = (Mi + 127) / 128 * 2;   // blocks of 64 tokens that a packed operand by rows of tokens holds
   // ---- forward, every activation kept
   float* h = p.layer[0].h;
   T_CK(launch(KID_EMBED, k_embed_rows, dim3(Mi), dim3(256), 0, st, tokens, (const float*)TH(0), h, d, V));
@@ -2237,11 +2272,19 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
     T_CK(mm_nt(a.ao, q, TH(t0 + 4), q, a.h2, d, Mi, d, q, 1.f, a.h));
     T_CK(rmsnorm_fwd(a.h2, TH(t0 + 5), c.rms_eps, Mi, d, a.xn2, a.r2, st));
     T_CK(mm_nt(a.xn2, d, TH(t0 + 6), d, a.gu, 2 * F, Mi, 2 * F, d, 0.f));   // w_gate, w_up are adjacent
+    float* h_next = (l + 1 < D.L) ? p.layer[l + 1].h : p.h_last;
+    if (p.packed_ffn) {
+      auto pack = [&](auto kernel) {
+        return launch(KID_SWIGLU, kernel, dim3(F / 64, blocks64), dim3(256), 0, st, (const float*)a.gu, Mi, F, x3_steps(F, pieces), (uint4*)p.packa);
+      };
+      T_CK(pieces == 3 ? pack(k_swiglu_fwd_pack<3>) : pieces == 2 ? pack(k_swiglu_fwd_pack<2>) : pack(k_swiglu_fwd_pack<1>));
+      T_CK(gemm_x3(X3Op{nullptr, 0, Mi, F, false}, X3Op{TH(t0 + 8), F, d, F, false}, h_next, a.h2, d, 1.f, xb, st, nullptr, pieces == 3, p.packa));
+      continue;
+    }
     if (F % 4 == 0 && M <= 65535)
       T_CK(launch(KID_SWIGLU, k_swiglu_fwd4, dim3((F / 4 + 255) / 256, Mi), dim3(256), 0, st, (const float*)a.gu, a.act, F));
     else
       T_CK(launch(KID_SWIGLU, k_swiglu_fwd, dim3(blocks256(M * D.F)), dim3(256), 0, st, (const float*)a.gu, a.act, F, M * D.F));
-    float* h_next = (l + 1 < D.L) ? p.layer[l + 1].h : p.h_last;
     T_CK(mm_nt(a.act, F, TH(t0 + 8), F, h_next, d, Mi, d, F, 1.f, a.h2));
   }
   T_CK(rmsnorm_fwd(p.h_last, TH(t_final), c.rms_eps, Mi, d, p.xf, p.rf, st));
@@ -2290,19 +2333,19 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
     const int t0 = 1 + 9 * l;
     // down projection
     T_CK(mm_nn(p.dh, d, TH(t0 + 8), F, p.dact, F, Mi, F, d, 0.f));
-    T_CK(mm_tn(p.dh, d, a.act, F, GR(t0 + 8), d, F, Mi, 1.f));
-    const int mb = (Mi + 127) / 128 * 2;   // blocks of 64 tokens that the packed operands hold
-    if (F % 64 == 0 && mb <= 65535) {
+    if (p.packed_ffn) {
       const int KB_rows = x3_steps(2 * F, pieces), KB_cols = x3_steps(Mi, pieces);
       auto pack = [&](auto kernel) {
-        return launch(KID_SWIGLU, kernel, dim3(F / 64, mb), dim3(256), 0, st, (const float*)p.dact, (const float*)a.gu, Mi, F, KB_rows,
-                      (uint4*)p.packa, KB_cols, (uint4*)p.dgu);
+        return launch(KID_SWIGLU, kernel, dim3(F / 64, blocks64), dim3(256), 0, st, (const float*)p.dact, (const float*)a.gu, Mi, F, KB_rows,
+                      (uint4*)p.packa, KB_cols, (uint4*)p.dgu, (uint4*)p.act_cols);
       };
       T_CK(pieces == 3 ? pack(k_swiglu_bwd_pack<3>) : pieces == 2 ? pack(k_swiglu_bwd_pack<2>) : pack(k_swiglu_bwd_pack<1>));
-      // gate / up projections
+      // gate / up projections, then the down projection's weights
       T_CK(gemm_x3(X3Op{nullptr, 0, Mi, 2 * F, false}, X3Op{TH(t0 + 6), d, d, 2 * F, true}, p.dx, p.dx, d, 0.f, xb, st, nullptr, true, p.packa));
       T_CK(gemm_x3(X3Op{nullptr, 0, 2 * F, Mi, true}, X3Op{a.xn2, d, d, Mi, true}, GR(t0 + 6), GR(t0 + 6), d, 1.f, xb, st, nullptr, true, p.dgu));
+      T_CK(gemm_x3(X3Op{p.dh, d, d, Mi, true}, X3Op{nullptr, 0, F, Mi, true}, GR(t0 + 8), GR(t0 + 8), F, 1.f, xb, st, p.act_cols));
     } else {
+      T_CK(mm_tn(p.dh, d, a.act, F, GR(t0 + 8), d, F, Mi, 1.f));
       if (F % 4 == 0 && M <= 65535)
         T_CK(launch(KID_SWIGLU, k_swiglu_bwd4, dim3((F / 4 + 255) / 256, Mi), dim3(256), 0, st, (const float*)p.dact,
                     (const float*)a.gu, p.dgu, F));
