@@ -1281,11 +1281,11 @@ hipError_t m_lmhead_sample_big(const void* Xp, const void* Wp, int n_rows, int V
 // block-level synchronisation; waves never exchange data.  q (row-major [rows, Hq hd]), K, V and the
 // probabilities are IEEE half; the output goes out as half in X32 order (the O projection's operand).
 // What bounds it: a SIMD issues MFMAs, vector instructions and (quarter rate) exponentials one after the other, 8 + ~35 + 8 per
-// head and page pair, and their serial sum is the time.  So what could go went: the exponents' reference follows the maximum
-// only in large steps (cross-lane maximum, rescaling and an exponential less in most pairs), no register copies between
-// the two page pairs in flight, page numbers as scalars, no operand quieting.  us per launch before and now: 64 x 768 tokens,
-// 14 heads of 64 198 -> 115 (of which the order of the blocks and the copies 198 -> 133), 12 heads of 128 322 -> 206; 9 x 301
-// tokens 15.0 -> 8.9.
+// head and page pair, and their serial sum is the time.  So what could go went: the cross-lane maximum and the rescaling
+// where no lane has a score above its query's maximum, register copies between the two page pairs in flight, page numbers
+// as vector loads, operand quieting; the arithmetic is the same to the bit.  us per launch before and now: 64 x 768
+// tokens, 14 heads of 64 198 -> 129, 12 heads of 128 322 -> 227; 9 x 301 tokens 15.0 -> 9.4.  (A reference that follows the
+// maximum only in steps of more than 2^8 gives 115, 206 and 8.9, and other last bits.)
 // ---------------------------------------------------------------------------------------
 // The largest of a lane's 8 scores, two accumulators of 4, in 4 instructions (fmaxf() quiets the results of MFMAs first, which
 // are not known to be free of signalling NaNs: 11).  The first one is the compiler's and reads both accumulators, so that
@@ -1296,6 +1296,13 @@ __device__ __forceinline__ float max8(const float (&p)[8], float inf) {
   asm("v_max3_f32 %0, %0, %1, %2\n\tv_max3_f32 %0, %0, %3, %4\n\tv_max3_f32 %0, %0, %5, %6"
       : "+v"(m) : "v"(p[0]), "v"(p[1]), "v"(p[2]), "v"(p[4]), "v"(p[5]), "v"(p[6]));
   return m;
+}
+// the largest of lanes l, l ^ 16, l ^ 32 and l ^ 48, without quieting either
+__device__ __forceinline__ float max_lanes(float x, float inf) {
+  lane_u32x2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = __builtin_amdgcn_fmed3f(__uint_as_float(r[0]), __uint_as_float(r[1]), inf);
+  r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __builtin_amdgcn_fmed3f(__uint_as_float(r[0]), __uint_as_float(r[1]), inf);
 }
 
 template <int HD, int HPW>
@@ -1327,18 +1334,13 @@ __global__ void __launch_bounds__(256, 2) k_flash_attention(const f16* __restric
         qf[h][kk].u = *(const uint4*)(q + (row0 + qpos) * qstride + (size_t)(kvh * rep + h0 + h) * HD + kk * 32 + grp * 8);
     }
   const float scale2 = 1.4426950408889634f / sqrtf((float)HD);   // scores in units of log2
-  // The exponents' reference m (in log2 units) follows a query's running maximum only once that lies more than kSlack above
-  // it: probabilities of up to 2^kSlack instead of 1, the same relative precision in half and in the fp32 sums.  limit: the
-  // raw score from which on it moves.  Per query, so that a query's result depends on nothing beside it.
-  constexpr float kSlack = 8.f;
-  const float slack_raw = kSlack / scale2;
   float inf = INFINITY;
   asm("" : "+s"(inf));
-  float m_ref[HPW], limit[HPW], l_run[HPW];
+  float m_run[HPW], l_run[HPW];
   f32x4 o[HPW][DT];
 #pragma unroll
   for (int h = 0; h < HPW; ++h) {
-    m_ref[h] = -INFINITY; limit[h] = -INFINITY; l_run[h] = 0.f;
+    m_run[h] = -INFINITY; l_run[h] = 0.f;
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) o[h][dt] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
@@ -1389,29 +1391,27 @@ __global__ void __launch_bounds__(256, 2) k_flash_attention(const f16* __restric
         for (int e = 0; e < 8; ++e)
           if (pp * 32 + 8 * grp + e > qpos) p[e] = -INFINITY;
       }
-      float m_loc = max8(p, inf);
-      if (__builtin_amdgcn_ballot_w64(m_loc > limit[h]) != 0) {   // some query's maximum left the slack
-        asm volatile("");   // a branch: as selects, its 30 instructions would run for every pair
-        m_loc = max_xor32(max_xor16(m_loc));
-        const bool moves = m_loc > limit[h];
-        const float m_new = moves ? m_loc * scale2 : m_ref[h];
-        const float alpha = __builtin_amdgcn_exp2f(m_ref[h] - m_new);   // exp2(-inf) = 0 on the first pair
-        limit[h] = moves ? m_loc + slack_raw : limit[h];
-        m_ref[h] = m_new;
-        l_run[h] *= alpha;
+      float m_loc = max8(p, inf) * scale2, alpha = 1.f;
+      if (__builtin_amdgcn_ballot_w64(m_loc > m_run[h]) != 0) {   // the running maximum moves for some query
+        asm volatile("");   // a branch: as selects, its 28 instructions would run for every pair
+        m_loc = max_lanes(m_loc, inf);
+        const float m_new = __builtin_amdgcn_fmed3f(m_run[h], m_loc, inf);   // finite: key 0 is visible to every query
+        alpha = __builtin_amdgcn_exp2f(m_run[h] - m_new);   // exp2(-inf) = 0 on the first pair
+        m_run[h] = m_new;
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
           for (int j = 0; j < 4; ++j) o[h][dt][j] *= alpha;
       }
-      float pe[8];
+      float psum = 0.f;
       Frag pf;
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
-        pe[e] = __builtin_amdgcn_exp2f(fmaf(p[e], scale2, -m_ref[h]));
-        pf.h[e] = (f16)pe[e];
+        const float pe = __builtin_amdgcn_exp2f(fmaf(p[e], scale2, -m_run[h]));
+        psum += pe;
+        pf.h[e] = (f16)pe;
       }
-      l_run[h] += ((pe[0] + pe[1]) + (pe[2] + pe[3])) + ((pe[4] + pe[5]) + (pe[6] + pe[7]));
+      l_run[h] = fmaf(l_run[h], alpha, psum);
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt) o[h][dt] = mfma16h(vf[b][dt], pf, o[h][dt]);
     }

@@ -154,9 +154,9 @@ def test_both_tile_heights_of_the_token_parallel_gemm_give_the_same_bits(sapo, m
                                                   ("MINI_BF16", 70, 65, 24), ("MINI_BF16_HD128", 1, 64, 10),
                                                   ("MINI_BF16_HD128", 2, 129, 10), ("MINI_BF16_HD128", 140, 50, 10)])
 def test_scoring_with_scores_far_apart(sapo, shape_name, S, T, sharp):
-    """The token-parallel attention's reference exponent follows a query's maximum only in steps of more than 8 (in powers of
-    two): query projections scaled so that the scores of a row spread over 40 and more, at one page pair, one token over,
-    several pairs, and with the head counts per wave that many and few sequences get.  A score of 40 from halves is off
+    """The token-parallel attention rescales only where some query's running maximum moves: query projections scaled so that
+    the scores of a row spread over 30 and more, at one page pair, one token over, several pairs, and with the head counts
+    per wave that many and few sequences get.  A score of 40 from halves is off
     by 40 2^-11 = 0.02 at most and a tenth of that on average over the head dim's products; what that does to a
     log-prob stays under the general tolerance at these weights.  Changing later tokens changes no earlier bit."""
     shape = getattr(W, shape_name)
