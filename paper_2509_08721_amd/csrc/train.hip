@@ -941,8 +941,10 @@ __global__ void __launch_bounds__(256) k_rmsnorm_bwd_rows(const float* __restric
     *(float4*)(part + (size_t)blockIdx.x * d + 4 * e) = s;
   }
 }
-// dgain += the partial sums: 16 columns per workgroup, 16 threads per column take parts k, k + 16, ...; added in that order
-__global__ void __launch_bounds__(256) k_gain_sum(const float* __restrict__ part, int n_part, int d, float* __restrict__ dgain) {
+// dgain = (accumulate: dgain +) the partial sums: 16 columns per workgroup, 16 threads per column take parts k, k + 16, ...;
+// added in that order
+__global__ void __launch_bounds__(256) k_gain_sum(const float* __restrict__ part, int n_part, int d, int accumulate,
+                                                  float* __restrict__ dgain) {
   __shared__ float red[16][17];
   const int c = threadIdx.x & 15, k = threadIdx.x >> 4, i = blockIdx.x * 16 + c;
   float s = 0.f;
@@ -954,7 +956,7 @@ __global__ void __launch_bounds__(256) k_gain_sum(const float* __restrict__ part
   __syncthreads();
   if (k == 0 && i < d) {
     for (int j = 1; j < 16; ++j) s += red[j][c];
-    dgain[i] += s;   // the gradient buffer starts at zero; micro-batches add up
+    dgain[i] = accumulate ? dgain[i] + s : s;
   }
 }
 
@@ -1240,13 +1242,13 @@ __global__ void __launch_bounds__(256) k_colsum_partial(const float* __restrict_
   for (int m = m0; m < m1; ++m) s += x[(size_t)m * N + i];
   part[(size_t)blockIdx.y * N + i] = s;
 }
-__global__ void __launch_bounds__(256) k_gain_grad_finish(const float* __restrict__ part, int n_part, int d,
+__global__ void __launch_bounds__(256) k_gain_grad_finish(const float* __restrict__ part, int n_part, int d, int accumulate,
                                                           float* __restrict__ dgain) {
   const int i = blockIdx.x * 256 + threadIdx.x;
   if (i >= d) return;
   float s = 0.f;
   for (int p = 0; p < n_part; ++p) s += part[(size_t)p * d + i];
-  dgain[i] += s;   // the gradient buffer starts at zero; micro-batches add up
+  dgain[i] = accumulate ? dgain[i] + s : s;
 }
 
 __device__ __forceinline__ void swiglu_grad(float g, float u, float da, float& dg, float& du) {
@@ -1409,8 +1411,8 @@ __device__ __forceinline__ void store_acc(float* __restrict__ row, const f32x4_t
 // conflicts both ways) for the products over the head dim; the next tile is on its way meanwhile.  Same products in the same
 // order.  The grids deal the longest walks first: causal walks are 1 .. T / 16 tiles long, and with the tile index fastest
 // the compute units had waves 62 % of the time.  Register limits leave two waves a SIMD (a limit for more spills).
-// us per layer, forward / d queries / d keys and values, before and now (with exp_split below):
-//   14 heads of 64,  64 x 384 tokens: 320 / 432 / 704, 245 / 330 / 449;   21 x 301: 77 / 96 / 150, 49 / 69 / 90
+// us per layer, forward / d queries / d keys and values, before and now (the backward kernels with exp_split below):
+//   14 heads of 64,  64 x 384 tokens: 320 / 432 / 704, 238 / 326 / 437;   21 x 301: 77 / 96 / 150, 52 / 70 / 90
 //   12 heads of 128, 64 x 384 tokens: 494 / 705 / 1507, 388 / 657 / 871;   9 x 300: 79 / 101 / 180, 46 / 74 / 86
 // The matrix cores are now busy 52 - 60 % of the time a compute unit has waves ; the rest is
 // mostly the softmax's vector instructions, which a SIMD issues in turn with them.
@@ -1530,17 +1532,17 @@ __global__ void __launch_bounds__(256, HD == 128 ? 2 : 1) k_tattn_fwd(const floa
     f32x4_t p;
     float ps = 0.f;
 #pragma unroll
-    for (int v = 0; v < 4; ++v) { p[v] = exp_split(sc[v] - m_new); ps += p[v]; }
+    for (int v = 0; v < 4; ++v) { p[v] = expf(sc[v] - m_new); ps += p[v]; }
+    float alpha = 1.f;
     if (__builtin_amdgcn_ballot_w64(m_run != m_new) != 0) {   // the running maximum moved in some lane
-      const float alpha = exp_split(m_run - m_new);
       asm volatile("");   // a branch, not 16 selects
-      l_run *= alpha;
+      alpha = expf(m_run - m_new);
 #pragma unroll
       for (int dt = 0; dt < HD / 16; ++dt)
 #pragma unroll
         for (int v = 0; v < 4; ++v) o[dt][v] *= alpha;
     }
-    l_run += ps;
+    l_run = fmaf(l_run, alpha, ps);
     m_run = m_new;
     if constexpr (COLS) {
       vc.accumulate(p, o);
@@ -2187,12 +2189,13 @@ extern "C" int sapo_trainer_export(const sapo_trainer* tr, void* const* tensors_
   return SAPO_OK;
 }
 
-// Forward, LM head and backward over one micro-batch of S_ sequences: gradients are added to tr->grad, the
-// log-probs go to logp_new [S_, T_].  p.n_masked holds the count of masked tokens of the whole training set and
+// Forward, LM head and backward over one micro-batch of S_ sequences: gradients are written to tr->grad by the first one of
+// an update (first) and added by the others (zeroing the buffer and adding to the zeros moved 6 GB at 0.5B: 21 x 301 tokens,
+// one piece, 43.0 -> 42.0 ms), the log-probs go to logp_new [S_, T_].  p.n_masked holds the count of masked tokens of the whole training set and
 // the LM head is packed (p.head_nt, p.head_t).
 static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* tokens, const uint8_t* completion_mask,
                        const float* logp_old, const float* advantages, int S_, int T_, float eps_low, float eps_high,
-                       float* logp_new, const int* rows, int n_rows, hipStream_t st) {
+                       float* logp_new, const int* rows, int n_rows, bool first, hipStream_t st) {
   const sapo_model_config& c = tr->cfg;
   const Dims D(c);
   const size_t S = S_, T = T_, M = S * T;
@@ -2201,6 +2204,7 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
   const int Mi = (int)M;
   auto TH = [&](int tensor) { return tr->theta + tr->off[tensor]; };
   auto GR = [&](int tensor) { return tr->grad + tr->off[tensor]; };
+  const float keep = first ? 0.f : 1.f;   // of the gradients there
   const int t_final = 1 + 9 * D.L, t_head = c.tied_embeddings ? 0 : t_final + 1;
   const int rep = hq / hkv;
   const float att_scale = 1.0f / sqrtf((float)hd);
@@ -2294,6 +2298,9 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
   // p.dh, scattered to p.dx afterwards) and d head
   T_CK(g_fill_f32(logp_new, 0.f, M, st));
   T_CK(g_fill_f32(p.dx, 0.f, M * D.d, st));
+  // the embedding's gradient is added up row by row, by the head's rows first where the two are one tensor
+  if (first && t_head != 0) T_CK(g_fill_f32(GR(0), 0.f, D.V * D.d, st));
+  if (first && n_rows == 0) T_CK(g_fill_f32(GR(t_head), 0.f, D.V * D.d, st));
   if (n_rows > 0) {
     T_CK(launch(KID_MISC, k_move_rows, dim3(n_rows), dim3(256), 0, st, (const float*)p.xf, rows, d, 0, p.xfc));
     for (size_t r0 = 0; r0 < (size_t)n_rows; r0 += p.chunk) {
@@ -2302,7 +2309,7 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
       T_CK(launch(KID_SCORE_ROWS, k_logp_dlogits, dim3(R), dim3(kLogpThreads), 0, st, p.logits, V, rows + r0, (int)T, tokens, completion_mask,
                   logp_old, advantages, eps_low, eps_high, (const long long*)p.n_masked, logp_new));
       T_CK(mm_nn(p.logits, V, TH(t_head), d, p.dh + r0 * D.d, d, R, d, V, 0.f, p.head_t));
-      T_CK(mm_tn(p.logits, V, p.xfc + r0 * D.d, d, GR(t_head), V, d, R, 1.f));
+      T_CK(mm_tn(p.logits, V, p.xfc + r0 * D.d, d, GR(t_head), V, d, R, r0 == 0 ? keep : 1.f));
     }
     T_CK(launch(KID_MISC, k_move_rows, dim3(n_rows), dim3(256), 0, st, (const float*)p.dh, rows, d, 1, p.dx));
   }
@@ -2316,12 +2323,12 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
                       (const float*)TH(gain_tensor_idx), Mi, d, p.dh, accumulate, p.gpart);
       });
       if (e != hipSuccess) return e;
-      return launch(KID_MISC, k_gain_sum, dim3((d + 15) / 16), dim3(256), 0, st, (const float*)p.gpart, n_part, d, GR(gain_tensor_idx));
+      return launch(KID_MISC, k_gain_sum, dim3((d + 15) / 16), dim3(256), 0, st, (const float*)p.gpart, n_part, d, !first, GR(gain_tensor_idx));
     }
     hipError_t e = launch(KID_MISC, k_gain_grad_partial, dim3((d + 255) / 256, n_gpart), dim3(256), 0, st, dxn, hin, rstd, Mi, d,
                           p.gpart);
     if (e != hipSuccess) return e;
-    e = launch(KID_MISC, k_gain_grad_finish, dim3((d + 255) / 256), dim3(256), 0, st, (const float*)p.gpart, n_gpart, d,
+    e = launch(KID_MISC, k_gain_grad_finish, dim3((d + 255) / 256), dim3(256), 0, st, (const float*)p.gpart, n_gpart, d, !first,
                GR(gain_tensor_idx));
     if (e != hipSuccess) return e;
     return launch(KID_RMSNORM, k_rmsnorm_bwd, dim3(Mi), dim3(256), 0, st, dxn, hin, rstd, (const float*)TH(gain_tensor_idx), d,
@@ -2342,10 +2349,10 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
       T_CK(pieces == 3 ? pack(k_swiglu_bwd_pack<3>) : pieces == 2 ? pack(k_swiglu_bwd_pack<2>) : pack(k_swiglu_bwd_pack<1>));
       // gate / up projections, then the down projection's weights
       T_CK(gemm_x3(X3Op{nullptr, 0, Mi, 2 * F, false}, X3Op{TH(t0 + 6), d, d, 2 * F, true}, p.dx, p.dx, d, 0.f, xb, st, nullptr, true, p.packa));
-      T_CK(gemm_x3(X3Op{nullptr, 0, 2 * F, Mi, true}, X3Op{a.xn2, d, d, Mi, true}, GR(t0 + 6), GR(t0 + 6), d, 1.f, xb, st, nullptr, true, p.dgu));
-      T_CK(gemm_x3(X3Op{p.dh, d, d, Mi, true}, X3Op{nullptr, 0, F, Mi, true}, GR(t0 + 8), GR(t0 + 8), F, 1.f, xb, st, p.act_cols));
+      T_CK(gemm_x3(X3Op{nullptr, 0, 2 * F, Mi, true}, X3Op{a.xn2, d, d, Mi, true}, GR(t0 + 6), GR(t0 + 6), d, keep, xb, st, nullptr, true, p.dgu));
+      T_CK(gemm_x3(X3Op{p.dh, d, d, Mi, true}, X3Op{nullptr, 0, F, Mi, true}, GR(t0 + 8), GR(t0 + 8), F, keep, xb, st, p.act_cols));
     } else {
-      T_CK(mm_tn(p.dh, d, a.act, F, GR(t0 + 8), d, F, Mi, 1.f));
+      T_CK(mm_tn(p.dh, d, a.act, F, GR(t0 + 8), d, F, Mi, keep));
       if (F % 4 == 0 && M <= 65535)
         T_CK(launch(KID_SWIGLU, k_swiglu_bwd4, dim3((F / 4 + 255) / 256, Mi), dim3(256), 0, st, (const float*)p.dact,
                     (const float*)a.gu, p.dgu, F));
@@ -2353,12 +2360,12 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
         T_CK(launch(KID_SWIGLU, k_swiglu_bwd, dim3(blocks256(M * D.F)), dim3(256), 0, st, (const float*)p.dact, (const float*)a.gu,
                     p.dgu, F, M * D.F));
       T_CK(mm_nn(p.dgu, 2 * F, TH(t0 + 6), d, p.dx, d, Mi, d, 2 * F, 0.f));
-      T_CK(mm_tn(p.dgu, 2 * F, a.xn2, d, GR(t0 + 6), 2 * F, d, Mi, 1.f));
+      T_CK(mm_tn(p.dgu, 2 * F, a.xn2, d, GR(t0 + 6), 2 * F, d, Mi, keep));
     }
     T_CK(norm_bwd(p.dx, a.h2, a.r2, t0 + 5, 1));
     // output projection
     T_CK(mm_nn(p.dh, d, TH(t0 + 4), q, p.dao, q, Mi, q, d, 0.f));
-    T_CK(mm_tn(p.dh, d, a.ao, q, GR(t0 + 4), d, q, Mi, 1.f));
+    T_CK(mm_tn(p.dh, d, a.ao, q, GR(t0 + 4), d, q, Mi, keep));
     // attention and the rotary embedding; dgu is free here and takes the partial dk / dv
     float* kv_parts = fused_attn && rep > 1 && 2 * D.F >= 2 * D.q ? p.dgu : nullptr;
     if (fused_attn) {
@@ -2407,11 +2414,11 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
       T_CK(launch(KID_MISC, k_colsum_partial, dim3((nqkv + 255) / 256, n_gpart), dim3(256), 0, st, (const float*)p.dqkv, Mi, nqkv,
                   p.gpart));
       T_CK(launch(KID_MISC, k_gain_grad_finish, dim3((nqkv + 255) / 256), dim3(256), 0, st, (const float*)p.gpart, n_gpart, nqkv,
-                  GR(tr->n_in + l)));
+                  !first, GR(tr->n_in + l)));
     }
     // query / key / value projections
     T_CK(mm_nn(p.dqkv, nqkv, TH(t0 + 1), d, p.dx, d, Mi, d, nqkv, 0.f));
-    T_CK(mm_tn(p.dqkv, nqkv, a.xn, d, GR(t0 + 1), nqkv, d, Mi, 1.f));
+    T_CK(mm_tn(p.dqkv, nqkv, a.xn, d, GR(t0 + 1), nqkv, d, Mi, keep));
     T_CK(norm_bwd(p.dx, a.h, a.r1, t0, 1));
   }
   T_CK(launch(KID_EMBED, k_embed_order, dim3((Mi + kEmbedChunk - 1) / kEmbedChunk), dim3(1024), 0, st, tokens, Mi, V, p.eorder));
@@ -2464,7 +2471,6 @@ extern "C" int sapo_policy_update(sapo_trainer* tr, const int32_t* tokens, const
   hipStream_t st = (hipStream_t)stream;
   const int t_head = c.tied_embeddings ? 0 : 1 + 9 * c.n_layers + 1;
   const int d = (int)D.d, V = (int)D.V;
-  T_CK(g_fill_f32(tr->grad, 0.f, tr->n_params, st));
   T_CK(launch(KID_MISC, k_count_mask, dim3(1), dim3(256), 0, st, completion_mask, M, p.n_masked));
   T_CK(x3_pack(X3Op{tr->theta + tr->off[t_head], d, V, d, false}, p.head_nt, p.head_cap, tr->pieces, st));   // rows = vocabulary
   T_CK(x3_pack(X3Op{tr->theta + tr->off[t_head], d, d, V, true}, p.head_t, p.head_t_cap, tr->pieces, st));    // rows = d
@@ -2485,7 +2491,7 @@ extern "C" int sapo_policy_update(sapo_trainer* tr, const int32_t* tokens, const
     const int n = (int)(S - s0 < S_mb ? S - s0 : S_mb);
     if (n_rows[i] < 0 || (size_t)n_rows[i] > (size_t)n * T) return set_error(SAPO_EHIP, "row count read back from the device is out of range");
     const int rc = update_rows(tr, p, tokens + s0 * T, completion_mask + s0 * T, logp_old + s0 * T, advantages + s0, n, T_,
-                               eps_low, eps_high, p.logp_all + s0 * T, p.mrows + s0 * T, n_rows[i], st);
+                               eps_low, eps_high, p.logp_all + s0 * T, p.mrows + s0 * T, n_rows[i], i == 0, st);
     if (rc != SAPO_OK) return rc;
   }
   // ---- the loss (the surrogate of sapo_clipped_surrogate on the log-probs just computed)

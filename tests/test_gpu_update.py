@@ -568,3 +568,33 @@ def test_update_at_the_edges_of_tiles(sapo, head_dim, d_ff, S, T, pieces, sharp)
         else:
             assert float(np.max(np.abs(a - b))) <= grad_tol * max(float(np.max(np.abs(b))), 1e-3 * gmax) + 1e-7, i
     tr.close()
+
+
+@pytest.mark.parametrize("name", ["tiny", "ragged_untied"])
+@pytest.mark.parametrize("empty", [(), (0,), (0, 1, 2)])
+@pytest.mark.parametrize("one_at_a_time", [False, True])
+def test_gradients_do_not_see_the_update_before(sapo, name, empty, one_at_a_time):
+    """The first micro-batch writes the gradient buffer, the others add to it: after an update on other data (at a learning
+    rate that moves nothing) the gradients are those of a new trainer, bit for bit - tied and untied embeddings, in one
+    go and a sequence at a time, with the first or every sequence without a masked token."""
+    import torch
+    shape = SHAPES[name]
+    S, T = 3, 20
+    w, params, tokens, mask, logp_old, adv = make_case(shape, 77, S, T, 9)
+    mask2 = mask.copy()
+    for s in empty:
+        mask2[s] = 0
+    grads = []
+    for used in (False, True):
+        tr = sapo.sapo_trainer_create(shape, w, lr=1e-30)
+        ws = None
+        if one_at_a_time:
+            ws = torch.empty(sapo.sapo_trainer_workspace_bytes_for(tr, S, T, 1) + 256, dtype=torch.uint8, device="cuda")
+        if used:
+            sapo.sapo_policy_update(tr, dev(tokens[::-1].copy()), dev(mask), dev(logp_old), dev(adv), workspace=ws)
+        sapo.sapo_policy_update(tr, dev(tokens), dev(mask2), dev(logp_old), dev(adv), workspace=ws)
+        grads.append([g + 0.0 for g in read_all(sapo, tr, 1)])
+        tr.close()
+    for a, b in zip(*grads):
+        assert np.array_equal(a, b)
+    assert any(np.any(a != 0.0) for a in grads[0]) == (len(empty) < S)
