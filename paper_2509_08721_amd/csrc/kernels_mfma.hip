@@ -1180,29 +1180,30 @@ hipError_t m_lmhead_score(const void* Xp, const void* Wp, int max_rows, const in
 
 // ---------------------------------------------------------------------------------------
 // LM head for decode with many sequences (or a K too large for the 64-token kernel): the scoring
-// GEMM's main loop with the sampler's epilogue, one (256 sequences x 128 vocabulary ids) tile per
+// GEMM's main loop with the sampler's epilogue, one (256 or 128 sequences x 128 vocabulary ids) tile per
 // workgroup.  A lane turns its quads of consecutive vocabulary ids into perturbed scores (one Philox
-// block per quad) and reduces, for each of its 4 sequences, (max, sum exp) and the best perturbed
+// block per quad) and reduces, for each of its sequences, (max, sum exp) and the best perturbed
 // score.  partials: [V / 128][n_rows][5].
 // ---------------------------------------------------------------------------------------
 int m_lmhead_sample_big_groups(int V) { return V >> 7; }
 
-__global__ void __launch_bounds__(256, 2) k_lmhead_sample_big(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp,
-                                                              int n_rows, int V, int K, SampleParams sp,
-                                                              float* __restrict__ partials) {
-  constexpr int TJ = 2, H = 4;
+template <int TJ>
+__global__ void __launch_bounds__(256, TJ == 2 ? 2 : 3) k_lmhead_sample_big(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp,
+                                                                            int n_rows, int V, int K, SampleParams sp,
+                                                                            float* __restrict__ partials) {
+  constexpr int H = 4, TM = 128 * TJ, RW = 32 * TJ;   // rows of a tile and of a wave
   extern __shared__ uint4 smem[];
   int ft, by;
-  if (!big_raster(V >> 7, (n_rows + 255) >> 8, ft, by)) return;
+  if (!big_raster(V >> 7, (n_rows + TM - 1) / TM, ft, by)) return;
   const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63;
   f32x16 acc[4][TJ];
   {
     TileLoop<TJ, H> loop;
-    loop.tokens(Xp, (n_rows + 31) >> 5, K >> 4, by * 8, 0);
+    loop.tokens(Xp, (n_rows + 31) >> 5, K >> 4, by * (TM / 32), 0);
     loop.features(Wp, K >> 4, ft * 4, 0, K / (16 * H), smem);
-    if (by * 256 + wave * 64 >= n_rows) {   // no row of this wave exists
-      loop.begin<false>();
-      loop.run<false>(smem, acc);
+    if (by * TM + wave * RW >= n_rows) {   // no row of this wave exists
+      loop.template begin<false>();
+      loop.template run<false>(smem, acc);
       return;
     }
     loop.begin();
@@ -1214,8 +1215,8 @@ __global__ void __launch_bounds__(256, 2) k_lmhead_sample_big(const uint4* __res
   const float inv_t = noisy ? 1.0f / sp.temperature : 1.0f;
 #pragma unroll
   for (int tj = 0; tj < TJ; ++tj) {
-    const int row = by * 256 + wave * 64 + tj * 32 + (lane & 31);
-    if (by * 256 + wave * 64 + tj * 32 >= n_rows) break;   // a whole block past the end
+    const int row = by * TM + wave * RW + tj * 32 + (lane & 31);
+    if (by * TM + wave * RW + tj * 32 >= n_rows) break;   // a whole block past the end
     const int seq = (sp.slot_seq && row < n_rows) ? sp.slot_seq[row] : row;   // the noise is keyed on the sequence
     LseAcc lse;
     BestAcc best;
@@ -1258,14 +1259,21 @@ __global__ void __launch_bounds__(256, 2) k_lmhead_sample_big(const uint4* __res
 hipError_t m_lmhead_sample_big(const void* Xp, const void* Wp, int n_rows, int V, int K, SampleParams sp, float* partials,
                                hipStream_t st) {
   if (n_rows <= 0 || V % 128 != 0 || K % 64 != 0) return hipErrorInvalidValue;
-  static bool attr_done = false;
-  if (!attr_done) {
-    hipError_t e = hipFuncSetAttribute((const void*)k_lmhead_sample_big, hipFuncAttributeMaxDynamicSharedMemorySize, kBigLds);
-    if (e != hipSuccess) return e;
-    attr_done = true;
-  }
-  return launch(KID_LMHEAD_SAMPLE, k_lmhead_sample_big, dim3(big_grid(V >> 7, (n_rows + 255) / 256)), dim3(256),
-                kBigLds, st, (const uint4*)Xp, (const uint4*)Wp, n_rows, V, K, sp, partials);
+  auto go = [&](auto kernel, int rows, bool& attr_done) {
+    if (!attr_done) {
+      const hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kBigLds);
+      if (e != hipSuccess) return e;
+      attr_done = true;
+    }
+    return launch(KID_LMHEAD_SAMPLE, kernel, dim3(big_grid(V >> 7, (n_rows + rows - 1) / rows)), dim3(256), kBigLds, st, (const uint4*)Xp,
+                  (const uint4*)Wp, n_rows, V, K, sp, partials);
+  };
+  static bool done_128 = false, done_256 = false;
+  // Up to 128 rows as 32 per wave: in the tile of 256 half the waves, always the same SIMDs', would have no row.
+  // us per step, 0.5B: 72 rows 909 -> 898, 128 957 -> 938; 1.5B: 16 rows 1196 -> 1193,
+  // 64 1624 -> 1609, 128 1699 -> 1683; the same bits.
+  if (n_rows <= 128) return go(k_lmhead_sample_big<1>, 128, done_128);
+  return go(k_lmhead_sample_big<2>, 256, done_256);
 }
 
 // =======================================================================================
