@@ -1411,7 +1411,7 @@ __device__ __forceinline__ void store_acc(float* __restrict__ row, const f32x4_t
 // conflicts both ways) for the products over the head dim; the next tile is on its way meanwhile.  Same products in the same
 // order.  The grids deal the longest walks first: causal walks are 1 .. T / 16 tiles long, and with the tile index fastest
 // the compute units had waves 62 % of the time.  Register limits leave two waves a SIMD (a limit for more spills).
-// us per layer, forward / d queries / d keys and values, before and now (the backward kernels with exp_split below):
+// us per layer, forward / d queries / d keys and values, before and now:
 //   14 heads of 64,  64 x 384 tokens: 320 / 432 / 704, 238 / 326 / 437;   21 x 301: 77 / 96 / 150, 52 / 70 / 90
 //   12 heads of 128, 64 x 384 tokens: 494 / 705 / 1507, 388 / 657 / 871;   9 x 300: 79 / 101 / 180, 46 / 74 / 86
 // The matrix cores are now busy 52 - 60 % of the time a compute unit has waves ; the rest is
@@ -1467,18 +1467,6 @@ template <int HD> struct TileCols {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   }
 };
-// exp(x) of a difference to a maximum or a log-sum-exp, as 2^(x log2 e): the product is split into its rounded value and what
-// the rounding dropped (an fma, and the part of log2 e behind its leading 24 bits), which enters to first order behind the
-// hardware's 2^y.  Below -200 (and -infinity, a masked score) the result is zero, NaN stays NaN; results under 2^-126 are
-// zero as well, where a probability is to be added to others of a sum of one.  Eight instructions; the library's also reduces
-// the range and scales back, which arguments of this kind do not need.
-__device__ __forceinline__ float exp_split(float x) {
-  constexpr float L = 0x1.715476p+0f, L_low = 0x1.4ae0bep-26f, ln2 = 0x1.62e43p-1f;   // log2 e = 0x1.71547652b82fep+0
-  x = x < -200.f ? -200.f : x;
-  const float y = x * L, e = __builtin_fmaf(x, L_low, __builtin_fmaf(x, L, -y));
-  const float p = __builtin_amdgcn_exp2f(y);
-  return __builtin_fmaf(p, e * ln2, p);
-}
 template <int HD> constexpr int tile_area() { return HD % 64 == 0 ? 16 * HD / 4 : 1; }   // float4s of LDS per wave and operand
 
 template <int HD>
@@ -1618,7 +1606,7 @@ __global__ void __launch_bounds__(256, 1) k_tattn_bwd_q(const float* __restrict_
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
       const int key = k0 + 4 * g + v;
-      const float pv = (key <= qi && key < T) ? exp_split(sc[v] * scale - l) : 0.f;
+      const float pv = (key <= qi && key < T) ? expf(sc[v] * scale - l) : 0.f;
       ds[v] = scale * pv * (dp[v] - dl);
     }
     if constexpr (COLS) kc.accumulate(ds, dq);
@@ -1697,7 +1685,7 @@ __global__ void __launch_bounds__(256, HD == 64 ? 2 : 1) k_tattn_bwd_kv(const fl
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int qi = q0 + 4 * g + v;
-        const float pr = (key_ok && qi < T && kj <= qi) ? exp_split(sc[v] * scale - ls[v]) : 0.f;
+        const float pr = (key_ok && qi < T && kj <= qi) ? expf(sc[v] * scale - ls[v]) : 0.f;
         pv[v] = pr;
         ds[v] = scale * pr * (dp[v] - de[v]);
       }

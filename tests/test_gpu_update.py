@@ -598,3 +598,31 @@ def test_gradients_do_not_see_the_update_before(sapo, name, empty, one_at_a_time
     for a, b in zip(*grads):
         assert np.array_equal(a, b)
     assert any(np.any(a != 0.0) for a in grads[0]) == (len(empty) < S)
+
+
+@pytest.mark.parametrize("head_dim,sharp", [(32, 43.17), (64, 14.51), (128, 10.40)])
+def test_gradients_through_probabilities_below_the_normal_range(sapo, head_dim, sharp):
+    """Backward attention keeps probabilities under 2^-126.  Position 1 is seen by one other query, with exp(-92) = 1e-40, and
+    leaves no other trace in the loss: the gradient of its token's embedding (untied) is that probability times the
+    advantage, 1e35 here.  An fp32 score of 92 is good to a few 92 2^-24 = 5.5e-6 and a probability of 1e-40 to 2^-149 =
+    1.4e-45 of it, 1.4e-5: 1e-3 leaves room for both and is far from the zero that a flushed probability gives."""
+    import torch
+    from oracle import sapo_update_oracle as U
+    shape = W.ModelShape(n_layers=1, d_model=64, n_q_heads=2, n_kv_heads=1, head_dim=head_dim, d_ff=64, vocab=160, rms_eps=1e-6,
+                         rope_theta=1e4, tied_embeddings=False, dtype="f32", max_seq=16)
+    w = W.make_weights(shape, 0, std=0.25)
+    w["layers"][0]["wq"] = (w["layers"][0]["wq"] * np.float32(sharp)).astype(np.float32)
+    tokens, mask = np.array([[3, 57, 90, 120]], np.int32), np.array([[0, 0, 0, 1]], np.uint8)
+    adv = np.array([1e35], np.float32)
+    params = U.parameter_list(shape, w)
+    _, lp, _ = U.loss_and_gradients(shape, params, tokens, mask, np.zeros((1, 4), np.float32), adv)
+    logp_old = (lp - 0.05 * mask).astype(np.float32)
+    _, _, ref_g = U.loss_and_gradients(shape, params, tokens, mask, logp_old, adv)
+    want = ref_g[0][57]
+    assert 1e-43 < np.linalg.norm(want) / np.linalg.norm(ref_g[0]) < 1e-37
+    tr = sapo.sapo_trainer_create(shape, w)
+    sapo.sapo_policy_update(tr, dev(tokens), dev(mask), dev(logp_old), dev(adv))
+    torch.cuda.synchronize()
+    got = read_all(sapo, tr, 1)[0][57]
+    assert np.linalg.norm(got - want) <= 1e-3 * np.linalg.norm(want), (np.linalg.norm(got), np.linalg.norm(want))
+    tr.close()
