@@ -700,7 +700,8 @@ static int run_layers_decode16(const sapo_weights* w, const FwdBufs& b, const De
     HIP_CK(d_gemm_skinny(o, db.rows ? SKM_RESID_X32 : SKM_RESID, st));
     const float* gain_after = (l + 1 < c.n_layers) ? w->layers[l + 1].attn_norm : w->final_norm;
     if (db.rows) {
-      HIP_CK(r_gate_up(db.xb, lw.wgu, db.ssq_b, d_skinny_units(S, SKM_RESID_X32, d, q), db.s_pad, S, F, d, c.rms_eps, b.act, st));
+      HIP_CK(r_gate_up(db.xb, lw.wgu, db.ssq_b, d_skinny_units(S, SKM_RESID_X32, d, q), db.s_pad, S, F, d, c.rms_eps,
+                       b.h, lw.ffn_norm, b.act, st));
       Prefetch next;
       if (l + 1 < c.n_layers) next = d_prefetch_skinny(w->layers[l + 1].wqkv16, S, SKM_STORE, nqkv, d);
       HIP_CK(r_down(b.act, lw.wdown, S, d, F, db.partial, b.h, gain_after, db.s_pad, db.xa, db.ssq_a, next, st));

@@ -527,10 +527,11 @@ hipError_t m_lmhead_sample_big(const void* Xp, const void* Wp, int n_rows, int V
 hipError_t m_flash_attention(const void* q, RowMap rm, KVCache kv, void* out, int n_seq, int n_q_heads, hipStream_t st);
 
 // FFN of a decode step of 65 .. 256 rows (kernels_rows.hip) ------------------------------------
-// Xp: rows x gain in X32 order, ssq: their sums of squares [parts][s_pad], at most 48 parts; Wp: W32 order, 16 gate and 16 up
-// rows per block; act: X32 order over F
-hipError_t r_gate_up(const void* Xp, const void* Wp, const float* ssq, int parts, int s_pad, int M, int F, int K, float eps, void* act,
-                     hipStream_t st);
+// Xp: rows x gain in X32 order, ssq: their sums of squares [parts][s_pad] (an infinite part: a value was clamped), h, gain:
+// what Xp was made of, read for the rows that half does not hold as they lie; Wp: W32 order, 16 gate and 16 up rows per block;
+// act: X32 order over F
+hipError_t r_gate_up(const void* Xp, const void* Wp, const float* ssq, int parts, int s_pad, int M, int F, int K, float eps, const float* h,
+                     const float* gain, void* act, hipStream_t st);
 // h += X W^T; xp = half(h * gain) in X16 order, ssq: [r_down_parts(d)][s_pad].  Xp in X32 order; pf: weights of a later launch
 // that the product's launch brings into the L2s
 constexpr int kRowSplits = 8;

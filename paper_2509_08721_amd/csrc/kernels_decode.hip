@@ -90,7 +90,8 @@ __device__ __forceinline__ void prefetch_behind(const SkinnyArgs& a, int first) 
 //   SWIGLU : tiles come in (gate, up) pairs; act = silu(gate * scale) * (up * scale) -> half, X16 order
 //   RESID  : h[tok][feat] += acc;  xp_out = half(h * gain_next) in X16 order;  ssq_out[tile][tok] =
 //            sum of h^2 over the tile's 16 features
-//   RESID_X32 (more than 64 rows): as RESID, but X32 order, and sums of squares over all tiles of the workgroup
+//   RESID_X32 (more than 64 rows): as RESID, but X32 order, and sums of squares over all tiles of the workgroup,
+//            infinite where some h * gain of theirs is beyond half's range and was clamped
 // ---------------------------------------------------------------------------------------
 template <int NT, int TG, int TS, int R, int MODE>
 // The first arguments are passed one by one (and once more inside the struct): the hardware preloads the first 14 dwords
@@ -265,6 +266,9 @@ __global__ void __launch_bounds__(512) k_skinny16(const uint4* Wp_, const uint4*
           o[0] = from_f32<f16>(s.x * gn.x); o[1] = from_f32<f16>(s.y * gn.y);
           o[2] = from_f32<f16>(s.z * gn.z); o[3] = from_f32<f16>(s.w * gn.w);
           q = sum_squares4(s);
+          if (MODE == SKM_RESID_X32 &&
+              !(fmaxf(fmaxf(fabsf(s.x * gn.x), fabsf(s.y * gn.y)), fmaxf(fabsf(s.z * gn.z), fabsf(s.w * gn.w))) <= 65504.f))
+            q = INFINITY;
         } else {
           o[0] = o[1] = o[2] = o[3] = (f16)0.f;
         }

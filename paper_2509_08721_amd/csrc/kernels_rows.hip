@@ -138,7 +138,7 @@ struct RowsLoop {
 };
 
 // Sum of a row's sums of squares, parts [parts][s_pad]: lanes l and l + 32 hold the same row and ask for every other part each,
-// the first 2 NL of them in front of the k loop; they are added behind it, with what is left (rows wider than 1536).
+// the first 2 NL of them in front of the k loop; they are added behind it, with what is left (more than 48 parts).
 template <int NL> struct RowParts {
   float v[NL];
   __device__ __forceinline__ void request(const float* __restrict__ ssq, int parts, int s_pad, int row) {
@@ -156,12 +156,44 @@ template <int NL> struct RowParts {
   }
 };
 
+// The product of a wave whose rows do not all fit half as they lie: the rows that do not (`refit`, per lane) from the residual,
+// normalised first, their scale then 1; the others as before to the bit (same values, same order).  Straight from global
+// memory: this is there for correctness.
+template <int NB>
+__device__ __forceinline__ void refit_rows(const float* __restrict__ h_row, const float* __restrict__ gain, float eps, bool refit,
+                                           const uint4* __restrict__ Wp, int fblk0, int n_fblk, int K, f32x16 (&acc)[NB], float& scale) {
+  const int lane = threadIdx.x & 63, KS = K >> 4;
+  float sum = 0.f;
+#pragma clang loop unroll(disable)
+  for (int k = (lane >> 5) * 4; k < K; k += 8) sum += sum_squares4(*(const float4*)(h_row + k));
+  const float row_scale = rsqrtf(sum_xor32(sum) / (float)K + eps);
+#pragma unroll
+  for (int f = 0; f < NB; ++f)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[f][v] = 0.f;
+#pragma clang loop unroll(disable)
+  for (int ks = 0; ks < KS; ++ks) {
+    const int k = ks * 16 + (lane >> 5) * 8;
+    Frag x;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x.h[e] = from_f32<f16>((refit ? h_row[k + e] * row_scale : h_row[k + e]) * gain[k + e]);
+#pragma unroll
+    for (int f = 0; f < NB; ++f) {
+      Frag w;
+      w.u = Wp[((size_t)min(fblk0 + f, n_fblk - 1) * KS + ks) * 64 + lane];
+      acc[f] = mfma32(w, x, acc[f]);
+    }
+  }
+  scale = refit ? 1.f : scale;
+}
+
 // act = silu(gate) * up, half, in X32 order over F = 16 n_fblk.  A 32-feature block of the weights holds 16 gate rows
 // and the 16 matching up rows: accumulator entries 4 r + j and 4 (r + 2) + j of a lane are a pair.
 template <int NB, int NL>
 __global__ void __launch_bounds__(256, 2) k_rows_gate_up(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp,
                                                          const float* __restrict__ ssq, int M, int n_fblk, int K, int parts, int s_pad,
-                                                         float eps, f16* __restrict__ act) {
+                                                         float eps, f16* __restrict__ act, const float* __restrict__ h,
+                                                         const float* __restrict__ gain) {
   extern __shared__ uint4 smem[];
   const int n_tblk = (M + 31) >> 5, token_tiles = (n_tblk + 3) >> 2;
   // the token tiles of a feature tile run on one XCD at the same time: its weights come from HBM once
@@ -178,7 +210,14 @@ __global__ void __launch_bounds__(256, 2) k_rows_gate_up(const uint4* __restrict
     loop.run(smem, acc);
   }
   if (tblk >= n_tblk) return;
-  const float scale = rsqrtf(rp.sum(ssq, parts, s_pad, min(tok, M - 1)) / (float)K + eps);
+  // Xp holds half(h * gain), scaled here: what half cannot hold of a row as it lies, it may hold of the normalised row.  That
+  // is, if a value was clamped (an infinite part), or if the row is so small that half's spacing below 2^-14 counts: at a
+  // root mean square of 2^-10, 2^-25 is an eighth of the rounding of a value of that size.
+  const float mean = rp.sum(ssq, parts, s_pad, min(tok, M - 1)) / (float)K;
+  float scale = rsqrtf(mean + eps);
+  const bool refit = mean < 0x1p-20f || mean == INFINITY;
+  if (__builtin_expect(__builtin_amdgcn_ballot_w64(refit) != 0, 0))
+    refit_rows<NB>(h + (size_t)min(tok, M - 1) * K, gain, eps, refit, Wp, bx * NB, n_fblk, K, acc, scale);
   if (tok >= M) return;
   const int F = n_fblk * 16;
 #pragma unroll
@@ -291,12 +330,12 @@ static hipError_t launch_rows(Kernel kernel, bool& attr_done, int grid, hipStrea
   return launch(KID_GEMM_ROWS, kernel, dim3(grid), dim3(256), RowsLoop<NB>::kBytes, st, args...);
 }
 template <int NB, int NL>
-static hipError_t gate_up(const void* Xp, const void* Wp, const float* ssq, int parts, int s_pad, int M, int n_fblk, int K, float eps, void* act,
-                          hipStream_t st) {
+static hipError_t gate_up(const void* Xp, const void* Wp, const float* ssq, int parts, int s_pad, int M, int n_fblk, int K, float eps,
+                          const float* h, const float* gain, void* act, hipStream_t st) {
   static bool attr_done = false;
   const int grid = ((n_fblk + NB - 1) / NB + 7) / 8 * 8 * ((M + 127) / 128);
   return launch_rows<NB>(k_rows_gate_up<NB, NL>, attr_done, grid, st, (const uint4*)Xp, (const uint4*)Wp, ssq, M, n_fblk, K, parts, s_pad, eps,
-                         (f16*)act);
+                         (f16*)act, h, gain);
 }
 template <int NB>
 static hipError_t down(const void* Xp, const void* Wp, int M, int n_fblk, int K, float* partial, const Prefetch& pf, hipStream_t st) {
@@ -306,17 +345,17 @@ static hipError_t down(const void* Xp, const void* Wp, int M, int n_fblk, int K,
                          (float4*)partial, grid, pf);
 }
 
-hipError_t r_gate_up(const void* Xp, const void* Wp, const float* ssq, int parts, int s_pad, int M, int F, int K, float eps, void* act,
-                     hipStream_t st) {
+hipError_t r_gate_up(const void* Xp, const void* Wp, const float* ssq, int parts, int s_pad, int M, int F, int K, float eps, const float* h,
+                     const float* gain, void* act, hipStream_t st) {
   if (M <= 0 || M > s_pad || F % 32 != 0 || K % 64 != 0 || parts < 1) return hipErrorInvalidValue;
   const int n_fblk = F / 16;
   auto go = [&](auto nl) {
     constexpr int NL = decltype(nl)::value;
     switch (pick_blocks(n_fblk, (M + 127) / 128)) {
-      case 2: return gate_up<2, NL>(Xp, Wp, ssq, parts, s_pad, M, n_fblk, K, eps, act, st);
-      case 3: return gate_up<3, NL>(Xp, Wp, ssq, parts, s_pad, M, n_fblk, K, eps, act, st);
-      case 4: return gate_up<4, NL>(Xp, Wp, ssq, parts, s_pad, M, n_fblk, K, eps, act, st);
-      default: return gate_up<5, NL>(Xp, Wp, ssq, parts, s_pad, M, n_fblk, K, eps, act, st);
+      case 2: return gate_up<2, NL>(Xp, Wp, ssq, parts, s_pad, M, n_fblk, K, eps, h, gain, act, st);
+      case 3: return gate_up<3, NL>(Xp, Wp, ssq, parts, s_pad, M, n_fblk, K, eps, h, gain, act, st);
+      case 4: return gate_up<4, NL>(Xp, Wp, ssq, parts, s_pad, M, n_fblk, K, eps, h, gain, act, st);
+      default: return gate_up<5, NL>(Xp, Wp, ssq, parts, s_pad, M, n_fblk, K, eps, h, gain, act, st);
     }
   };
   return parts <= 28 ? go(std::integral_constant<int, 14>()) : go(std::integral_constant<int, 24>());

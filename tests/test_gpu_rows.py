@@ -74,3 +74,35 @@ def test_rows_dealt_in_groups_of_siblings(hd, P, G):
     ref = oracle_logprobs_for(ma, prompts, G, toks, seqs)
     assert max(np.max(np.abs(ref[s] - lps[s])) for s in seqs) <= 2e-2
     gw.close()
+
+
+@pytest.mark.parametrize("d,F,S", [(256, 320, 66), (128, 4160, 129), (128, 8256, 200), (1664, 192, 100)])   # 2, 3, 5 feature blocks; 52 parts
+def test_rows_that_half_cannot_hold_before_their_norm(d, F, S):
+    """The FFN of 65 .. 256 rows reads half(residual x gain) and scales behind the product.  Rows whose product is beyond half's
+    range, and rows far below its normal range, get what their normalised values give, next to ordinary rows in the same
+    wave: embeddings of three sizes (peaks of 32000, 4 and 1e-6; ffn gains of 8), no attention output, an FFN whose output
+    outweighs the residual.  Step 0 comes from the prompt's pass, which clamps as documented: steps 1 on are compared.
+    Halves are good to 2^-11 of the largest of the values that meet in a logit: the general tolerance."""
+    shape = replace(W.MINI_BF16, n_layers=1, d_model=d, d_ff=F, tied_embeddings=False, rms_eps=1e-15)
+    rng = np.random.default_rng(S)
+    w = W.perturb_norm_gains(W.make_weights(shape, 13, std=0.05 * (128 / d) ** 0.5), 13)
+    lw = w["layers"][0]
+    lw["wo"] = np.zeros_like(lw["wo"])
+    lw["ffn_norm"] = (8.0 * lw["ffn_norm"]).astype(np.float32)
+    lw["w_down"] = W.f32_to_bf16_bits(W.bf16_bits_to_f32(lw["w_down"]) * np.float32(250.0 / (F / 256) ** 0.5))
+    size = np.array([32000.0, 4.0, 1e-6], np.float32)[rng.integers(0, 3, shape.vocab)]
+    e = W.bf16_bits_to_f32(w["embed"])
+    w["embed"] = W.f32_to_bf16_bits((e / np.abs(e).max() * size[:, None]).astype(np.float32))
+    gw = sapo.sapo_weights_create(shape, w)
+    assert gw.uses_mfma
+    ma, Lp, N, seed = O.Model(shape, w), 5, 6, 79
+    prompts = rng.integers(0, shape.vocab, size=(S, Lp)).astype(np.int32)
+    toks, lps = sapo.sapo_rollout_generate(gw, torch.from_numpy(prompts).cuda(), 1, N, 1.0, seed)
+    toks, lps = toks.cpu().numpy(), lps.cpu().numpy()
+    seqs = list(range(0, S, 3))
+    assert len({float(size[toks[s, t]]) for s in seqs for t in range(N - 1)}) == 3
+    n, exact, near, bad = teacher_forced_token_check(ma, prompts, 1, toks, 1.0, seed, seqs, steps=range(1, N), delta=2e-2)
+    assert not bad, bad[:5]
+    ref = oracle_logprobs_for(ma, prompts, 1, toks, seqs)
+    assert max(np.max(np.abs(ref[s] - lps[s])[1:]) for s in seqs) <= 2e-2
+    gw.close()
