@@ -773,9 +773,15 @@ struct RolloutPlan {
   int n_levels;
   size_t bytes;
 };
-// Rows per step a batch is compacted to: at 64 rows and below the weight-streaming kernels run, up to 256 the
-// token-parallel FFN with one token tile (see run_layers_decode16)
+// Rows per step a batch is compacted to: at 64 rows and below the weight-streaming kernels run, up to 256 the FFN of
+// kernels_rows.hip (see run_layers_decode16)
 static const int kCompactSlots[2] = {256, 64};
+
+// Can decode steps of so many rows run?  The weight-streaming GEMMs add at most kMaxSsqParts parts of a row's sum of squares, and
+// every 16 features of the projection before them leave one, unless the FFN is that of 65 .. 256 rows.
+static bool decode_rows_run(const sapo_weights* w, int rows) {
+  return !w->mfma || w->cfg.n_layers == 0 || w->cfg.d_model / 16 <= kMaxSsqParts || (rows > 64 && rows <= 256);
+}
 
 static void plan_rollout(const sapo_weights* w, int P, int Lp, int G, int N, char* base, RolloutPlan& pl) {
   const sapo_model_config& c = w->cfg;
@@ -811,7 +817,7 @@ static void plan_rollout(const sapo_weights* w, int P, int Lp, int G, int N, cha
   pl.level[0].partials = pl.partials; pl.level[0].slot_seq = nullptr;
   if (w->mfma) {
     for (int slots : kCompactSlots) {
-      if (slots >= pl.S) continue;
+      if (slots >= pl.S || !decode_rows_run(w, slots)) continue;
       RolloutPlan::Level& lv = pl.level[pl.n_levels++];
       lv.slots = slots;
       carve_decode(A, w, slots, lv.dec);
@@ -881,6 +887,8 @@ static int rollout_impl(const sapo_weights* w, const int32_t* prompts, const int
   if (stop_token >= w->cfg.vocab) return fail(SAPO_EINVAL, "stop token %d is outside the vocabulary", stop_token);
   if (!(temperature >= 0.f)) return fail(SAPO_EINVAL, "temperature must be >= 0");
   if (((uintptr_t)workspace & 255) != 0) return fail(SAPO_EINVAL, "workspace must be 256-byte aligned");
+  if (max_new > 1 && !decode_rows_run(w, P * G))
+    return fail(SAPO_ESHAPE, "d_model %d > %d decodes with 65 .. 256 sequences only, not %d", w->cfg.d_model, 16 * kMaxSsqParts, P * G);
   RolloutPlan pl;
   plan_rollout(w, P, Lp, G, max_new, (char*)workspace, pl);
   if (workspace_bytes < pl.bytes) return fail(SAPO_EWORKSPACE, "workspace %zu < required %zu", workspace_bytes, pl.bytes);

@@ -541,6 +541,7 @@ hipError_t r_down(const void* Xp, const void* Wp, int M, int d, int K, float* pa
                   float* ssq, const Prefetch& pf, hipStream_t st);
 
 // decode kernels (kernels_decode.hip) -------------------------------------------------------
+constexpr int kMaxSsqParts = 96;   // parts of a row's sum of squares that d_gemm_skinny and d_lmhead_sample add up
 enum { SKM_STORE = 0, SKM_RESID = 1, SKM_SWIGLU = 2, SKM_RESID_X32 = 3 };
 struct SkinnyArgs {
   const uint4* Wp;        // weights, W16 fragment order [N/16][K/32][64]

@@ -43,7 +43,7 @@ __device__ __forceinline__ float silu_f(float x) { return x / (1.0f + __expf(-x)
 // Sum of the ssq parts of one token, spread over the 8 waves of a workgroup: thread (grp, tok)
 // loads parts grp, grp + 8, ... early (ssq_issue) and the sums meet in LDS later (ssq_finish).
 // ---------------------------------------------------------------------------------------
-constexpr int kSsqPerThread = 12;   // up to 96 parts
+constexpr int kSsqPerThread = kMaxSsqParts / 8;
 
 // ssq is not null and parts >= 1.  Every thread asks for all kSsqPerThread values, a part past the end being the last
 // part again (dropped in ssq_publish): with a request under a branch each, the compiler waited for the first one on
@@ -512,7 +512,7 @@ Prefetch d_prefetch_skinny(const void* w16, int n_rows, int mode, int N, int K) 
 // the re-reads of the token operand dominate and the blocking goes towards square.
 hipError_t d_gemm_skinny(const SkinnyArgs& a, int mode, hipStream_t st) {
   if (a.K % 32 != 0 || a.N % 16 != 0 || a.n_rows <= 0 || (mode == SKM_RESID_X32 && a.n_rows <= 64)) return hipErrorInvalidValue;
-  if (mode != SKM_RESID && mode != SKM_RESID_X32 && (a.ssq_in == nullptr || a.ssq_parts < 1 || a.ssq_parts > 8 * kSsqPerThread)) return hipErrorInvalidValue;
+  if (mode != SKM_RESID && mode != SKM_RESID_X32 && (a.ssq_in == nullptr || a.ssq_parts < 1 || a.ssq_parts > kMaxSsqParts)) return hipErrorInvalidValue;
   const int per_wave = ((a.K >> 5) + 7) / 8;   // k steps per wave
   const int tiles = a.N / 16;
   const bool multi = a.n_rows > 64;
@@ -861,7 +861,7 @@ bool d_lmhead_sample_supported(int K, int n_rows) { return n_rows <= 64 && K % 3
 hipError_t d_lmhead_sample(const void* Wp, const void* Xp, int K, int V, const float* ssq, int ssq_parts, bool ssq_quarters, int s_pad,
                            float eps, int n_rows, SampleParams sp, float* partials, const void* embed,
                            const float* gain_first, float* h, void* xp_first, float* ssq_first, hipStream_t st) {
-  if (!d_lmhead_sample_supported(K, n_rows) || V % 16 != 0 || ssq == nullptr || ssq_parts < 1 || ssq_parts > 8 * kSsqPerThread)
+  if (!d_lmhead_sample_supported(K, n_rows) || V % 16 != 0 || ssq == nullptr || ssq_parts < 1 || ssq_parts > kMaxSsqParts)
     return hipErrorInvalidValue;
   const int KS = K / 32, n_tiles = V / 16;
   int n_wg = 256;

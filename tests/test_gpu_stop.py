@@ -210,3 +210,39 @@ def test_stop_token_bad_arguments():
     for bad in (-1, wl.shape.vocab):
         with pytest.raises(sapo.SapoError):
             sapo.sapo_rollout_generate_stop(gw, prompts, wl.group, 4, 1.0, 1, bad)
+
+
+def test_models_too_wide_for_the_small_batches():
+    """d_model 1664 leaves 104 sums of squares per row, more than the kernels of up to 64 rows (and of more than 256) add up:
+    a call of 65 .. 256 sequences goes on with all its rows when fewer than 64 are left running, where it used to end in
+    an error; other calls are refused before they write anything, unless they take no decode step."""
+    from dataclasses import replace
+    shape, P, G, Lp, N, stop, seed = replace(W.MINI_BF16, n_layers=2, d_model=1664, d_ff=128), 10, 8, 9, 70, 77, 5
+    w = W.boost_token(W.perturb_norm_gains(W.make_weights(shape, 7, std=0.02), 7), shape, stop, 6)
+    gw = sapo.sapo_weights_create(shape, w)
+    assert gw.uses_mfma
+    prompts_np = np.random.default_rng(1).integers(0, shape.vocab, size=(P, Lp)).astype(np.int32)
+    prompts = torch.from_numpy(prompts_np).cuda()
+    st = torch.cuda.Stream()
+    for stream in (None, st):
+        with torch.cuda.stream(stream or torch.cuda.current_stream()):
+            plain, plp = sapo.sapo_rollout_generate(gw, prompts, G, N, 1.0, seed, stream=stream)
+            tok, lp, ln = sapo.sapo_rollout_generate_stop(gw, prompts, G, N, 1.0, seed, stop, stream=stream)
+            torch.cuda.synchronize()
+        stats = sapo.sapo_rollout_last_stats(gw)
+        assert stats["compactions"] == 0 and stats["rows"] == P * G
+        plain, plp, tok, lp, ln = (x.cpu().numpy() for x in (plain, plp, tok, lp, ln))
+        assert (ln <= 32).sum() > P * G - 64 and (ln == N).any()     # at the first look fewer than 64 are left, and some stay
+        for s in range(P * G):
+            k = int(ln[s])
+            assert np.array_equal(tok[s, :k], plain[s, :k]) and np.array_equal(lp[s, :k], plp[s, :k])
+            assert (tok[s, k:] == stop).all() and not lp[s, k:].any()
+    for few, g in ((8, 8), (1, 300)):        # 64 and 300 sequences
+        out = torch.full((few * g, 2), -7, dtype=torch.int32, device="cuda"), torch.full((few * g, 2), -7.0, device="cuda")
+        with pytest.raises(sapo.SapoError, match="d_model"):
+            sapo.sapo_rollout_generate(gw, prompts[:few].contiguous(), g, 2, 1.0, seed, out_tokens=out[0], out_logprobs=out[1])
+        torch.cuda.synchronize()
+        assert (out[0] == -7).all() and (out[1] == -7).all()
+        one, _ = sapo.sapo_rollout_generate(gw, prompts[:few].contiguous(), g, 1, 1.0, seed)
+        assert one.shape == (few * g, 1) and (one.cpu().numpy() >= 0).all()
+    gw.close()
