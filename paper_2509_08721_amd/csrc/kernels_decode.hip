@@ -490,15 +490,23 @@ static hipError_t launch_few_r(const SkinnyArgs& a, hipStream_t st) {
   return launch_few<FR, 20, MODE>(a, st);
 }
 
+// Blocking (feature tiles x token groups) of a STORE or RESID launch with several token blocks.  With 4 x 4 a narrow output leaves
+// compute units idle (1.5B QKV at 256 rows: 128 workgroups of 393 KB); two tiles per workgroup double the workgroups at
+// 295 KB each.  K above 2048 or a number of tiles that is no multiple of 4: 2 x 2 where the output is a residual.
+enum WideTile { WIDE_1X1, WIDE_2X2, WIDE_2X4, WIDE_4X4 };
+static WideTile wide_tile(int n_rows, int mode, int N, int K) {
+  const int tiles = N / 16;
+  if (tiles % 4 == 0 && (mode == SKM_STORE || K <= 2048)) return tiles / 4 * ((n_rows + 63) / 64) < 192 ? WIDE_2X4 : WIDE_4X4;
+  return mode != SKM_STORE && tiles % 2 == 0 ? WIDE_2X2 : WIDE_1X1;
+}
 // 16-feature tiles that a workgroup of the launch below reads, as a power of two: what the block numbering calls a unit.
 static int skinny_unit_log2(int n_rows, int mode, int N, int K) {
   const int tiles = N / 16;
   if (n_rows <= kFewRows) return mode == SKM_SWIGLU ? 1 : 0;
   if (n_rows <= 64) return mode != SKM_SWIGLU ? 0 : K <= 1024 ? 2 : 1;
   if (mode == SKM_SWIGLU) return tiles % 8 == 0 ? 3 : K <= 1024 ? 2 : 1;
-  if (mode != SKM_STORE && K > 2048) return tiles % 2 == 0 ? 1 : 0;
-  if (tiles % 4 != 0) return mode != SKM_STORE && tiles % 2 == 0 ? 1 : 0;
-  return (tiles / 4) * ((n_rows + 63) / 64) < 192 ? 1 : 2;
+  const WideTile t = wide_tile(n_rows, mode, N, K);
+  return t == WIDE_4X4 ? 2 : t == WIDE_1X1 ? 0 : 1;
 }
 int d_skinny_units(int n_rows, int mode, int N, int K) { return N / 16 >> skinny_unit_log2(n_rows, mode, N, K); }
 // Prefetch of a skinny GEMM's weights by an earlier launch of a step of n_rows rows.
@@ -533,26 +541,24 @@ hipError_t d_gemm_skinny(const SkinnyArgs& a, int mode, hipStream_t st) {
     if (per_wave <= 4) return launch_groups<4, 4, SKM_SWIGLU>(a, groups, st);
     return launch_groups<2, 6, SKM_SWIGLU>(a, groups, st);
   }
-  // several token blocks and a narrow output: 4 x 4 blocking would leave compute units idle (1.5B QKV at 256 rows:
-  // 128 workgroups of 393 KB); two tiles per workgroup double the workgroups at 295 KB each
-  const bool few = multi && tiles % 4 == 0 && (tiles / 4) * ((a.n_rows + 63) / 64) < 192;
+  const WideTile wide = multi ? wide_tile(a.n_rows, mode, a.N, a.K) : WIDE_1X1;
+  if (mode == SKM_RESID_X32) {
+    if (wide == WIDE_2X4) return launch_skinny<2, 4, 1, 3, SKM_RESID_X32>(a, st);
+    if (wide == WIDE_4X4) return launch_skinny<4, 4, 1, 3, SKM_RESID_X32>(a, st);
+    return wide == WIDE_2X2 ? launch_skinny<2, 2, 2, 9, SKM_RESID_X32>(a, st) : hipErrorInvalidValue;
+  }
   // one token block, more 16-token workgroups than compute units (0.5B QKV: 72 tiles x 4 = 288): some compute
   // units would get two workgroups and ingest twice; 32-token workgroups (144 of them, 86 KB each) keep it one each
   const bool tg2 = !multi && tiles * groups > 256;
   if (mode == SKM_STORE) {
-    if (few) return launch_skinny<2, 4, 1, 3, SKM_STORE>(a, st);
-    if (multi && tiles % 4 == 0) return launch_skinny<4, 4, 1, 3, SKM_STORE>(a, st);
+    if (wide == WIDE_2X4) return launch_skinny<2, 4, 1, 3, SKM_STORE>(a, st);
+    if (wide == WIDE_4X4) return launch_skinny<4, 4, 1, 3, SKM_STORE>(a, st);
     if (tg2) return per_wave <= 4 ? launch_pairs<4, SKM_STORE>(a, groups, st) : launch_pairs<8, SKM_STORE>(a, groups, st);
     return per_wave <= 4 ? launch_singles<4, SKM_STORE>(a, groups, st) : launch_singles<8, SKM_STORE>(a, groups, st);
   }
-  if (mode == SKM_RESID_X32) {
-    if (few && per_wave <= 8) return launch_skinny<2, 4, 1, 3, SKM_RESID_X32>(a, st);
-    if (per_wave <= 8 && tiles % 4 == 0) return launch_skinny<4, 4, 1, 3, SKM_RESID_X32>(a, st);
-    return tiles % 2 == 0 ? launch_skinny<2, 2, 2, 9, SKM_RESID_X32>(a, st) : hipErrorInvalidValue;
-  }
-  if (few && per_wave <= 8) return launch_skinny<2, 4, 1, 3, SKM_RESID>(a, st);
-  if (multi && per_wave <= 8 && tiles % 4 == 0) return launch_skinny<4, 4, 1, 3, SKM_RESID>(a, st);
-  if (multi && tiles % 2 == 0) return launch_skinny<2, 2, 2, 9, SKM_RESID>(a, st);
+  if (wide == WIDE_2X4) return launch_skinny<2, 4, 1, 3, SKM_RESID>(a, st);
+  if (wide == WIDE_4X4) return launch_skinny<4, 4, 1, 3, SKM_RESID>(a, st);
+  if (wide == WIDE_2X2) return launch_skinny<2, 2, 2, 9, SKM_RESID>(a, st);
   if (tg2 && per_wave <= 4) return launch_pairs<4, SKM_RESID>(a, groups, st);
   if (tg2 && per_wave <= 8) return launch_pairs<8, SKM_RESID>(a, groups, st);
   if (per_wave <= 4) return launch_singles<4, SKM_RESID>(a, groups, st);

@@ -1,6 +1,6 @@
 """Decode steps of 65 .. 256 rows against the oracle: row counts at the edges of the 32- and 128-row blocks, widths of the FFN
 and of the model that take each number of feature blocks per workgroup (2 .. 5, with a last tile that is not full), fewer
-stages of K than parts, rows with more sums of squares than are requested ahead."""
+stages of K than parts, rows with more sums of squares than are requested ahead, each tile of the O projection in front."""
 from dataclasses import replace
 
 import numpy as np
@@ -15,7 +15,7 @@ from tests.parity import measured_logit_eps, oracle_logprobs_for, teacher_forced
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("d,F,S,std", [
+@pytest.mark.parametrize("d,F,S,std,heads", [(*c, (4, 2)) for c in [
     (128, 64, 65, 0.05),        # one stage of K for eight parts
     (128, 256, 96, 0.05), (128, 576, 97, 0.05), (256, 320, 128, 0.05), (256, 704, 129, 0.05), (384, 512, 160, 0.05),
     (256, 4160, 192, 0.02),     # gate/up: 260 blocks, 3 per workgroup
@@ -25,9 +25,11 @@ pytestmark = pytest.mark.gpu
     (1664, 128, 131, 0.02),     # 52 blocks, 4; 52 parts of the sums of squares
     (2176, 192, 254, 0.02),     # 68 blocks, 5, the last tile three
     (3200, 64, 70, 0.01),       # two blocks per part of the sums of squares
-])
-def test_rows_follow_the_oracle(d, F, S, std):
-    shape = replace(W.MINI_BF16, n_layers=2, d_model=d, d_ff=F)
+    (3200, 64, 193, 0.01),      # O projection: four tiles x four token groups per workgroup
+]] + [                          # O projection: K of 2304, two workgroups of two token groups per block, each with its sums
+    (256, 320, 65, 0.05, (36, 4)), (640, 192, 150, 0.02, (36, 4)), (128, 64, 256, 0.05, (36, 4))])
+def test_rows_follow_the_oracle(d, F, S, std, heads):
+    shape = replace(W.MINI_BF16, n_layers=2, d_model=d, d_ff=F, n_q_heads=heads[0], n_kv_heads=heads[1])
     w = W.perturb_norm_gains(W.make_weights(shape, 11, std=std), 11)
     gw = sapo.sapo_weights_create(shape, w)
     assert gw.uses_mfma
