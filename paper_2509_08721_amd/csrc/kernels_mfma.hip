@@ -654,8 +654,9 @@ __global__ void __launch_bounds__(256, 2) k_gemm_mid(const uint4* __restrict__ X
 // A wave's 64 tokens x 128 features of values, finished, into their V pages.  A lane's accumulators are features of one token,
 // a page holds 8 tokens of a feature side by side: written from the registers that is two bytes per lane in runs of 16
 // bytes, and the few workgroups with values end the launch.  They go through the wave's own LDS ([feature][token]) and leave
-// as 16 bytes per lane wherever 8 slots are all here.  0.5B, 9 x 301 tokens: 31.4 -> 20.7 us per launch (with the values' stores
-// left out 20.1; 64 features at a time, twice the runs, 24.7).
+// as 16 bytes per lane wherever 8 slots are all here.  0.5B, 9 x 301 tokens: 21.1 us per launch; 31.4 with two bytes per lane
+// (21.6 while a page held 16 tokens of a feature side by side, in runs of 32 bytes), 20.1 with the values' stores left
+// out, 24.7 with 64 features at a time, twice the runs.
 constexpr int kValueStride = 66;   // halves from a feature to the next: the lanes of a write and of a read are in different banks
 constexpr int kQkvLds = 4 * 128 * kValueStride * (int)sizeof(f16);   // the ring is smaller; two workgroups fit a compute unit
 static_assert(kQkvLds >= kBigLds && 2 * kQkvLds <= 160 * 1024, "ring, then the values of four waves");
@@ -941,19 +942,26 @@ hipError_t m_gemm_qkv_rope(const void* Xp, const void* Wp, int M, int N, int K, 
     if (hd == 128 && m.tile == 1) return m.deep ? launch_qkv_mid<128, 1, 7>(X, W, M, N, K, epi, st) : launch_qkv_mid<128, 1, 4>(X, W, M, N, K, epi, st);
     if (hd == 128 && m.tile == 2) return m.deep ? launch_qkv_mid<128, 2, 6>(X, W, M, N, K, epi, st) : launch_qkv_mid<128, 2, 3>(X, W, M, N, K, epi, st);
   }
+  // With few workgroups the dispatcher may still put two on one compute unit, and the launch then takes their time one after the
+  // other: 0.5B, 10 .. 16 token tiles, 20 us in some launches and 27 in most.  With more than half of a unit's LDS each has its
+  // own: 9 x 301 tokens 27.8 -> 21.1 us, 39 x 64 26.6 -> 20.0, 64 x 64 28.5 -> 21.5 (at most 18 workgroups on the fullest
+  // XCD of 32 units).  At 27 on an XCD the raster's empty workgroups, which ask for the LDS too, wait for units: 30.5 -> 38.8.
+  constexpr int kAloneLds = 84 * 1024;
   static bool attr_done = false;
   if (!attr_done) {
-    hipError_t e = hipFuncSetAttribute((const void*)k_gemm_qkv_rope<64>, hipFuncAttributeMaxDynamicSharedMemorySize, kQkvLds);
+    hipError_t e = hipFuncSetAttribute((const void*)k_gemm_qkv_rope<64>, hipFuncAttributeMaxDynamicSharedMemorySize, kAloneLds);
     if (e == hipSuccess)
-      e = hipFuncSetAttribute((const void*)k_gemm_qkv_rope<128>, hipFuncAttributeMaxDynamicSharedMemorySize, kQkvLds);
+      e = hipFuncSetAttribute((const void*)k_gemm_qkv_rope<128>, hipFuncAttributeMaxDynamicSharedMemorySize, kAloneLds);
     if (e != hipSuccess) return e;
     attr_done = true;
   }
-  const dim3 grid(big_grid(N / 128, (M + 255) / 256));
+  const int NX = N / 128, NY = (M + 255) / 256, per_xcd = NY < 8 ? (NX + 7) / 8 * NY : (NY + 7) / 8 * NX;
+  const int lds = per_xcd <= 20 ? kAloneLds : kQkvLds;
+  const dim3 grid(big_grid(NX, NY));
   if (hd == 64)
-    return launch(KID_GEMM_BIG, k_gemm_qkv_rope<64>, grid, dim3(256), kQkvLds, st, (const uint4*)Xp, (const uint4*)Wp, M, N, K,
+    return launch(KID_GEMM_BIG, k_gemm_qkv_rope<64>, grid, dim3(256), lds, st, (const uint4*)Xp, (const uint4*)Wp, M, N, K,
                   epi);
-  return launch(KID_GEMM_BIG, k_gemm_qkv_rope<128>, grid, dim3(256), kQkvLds, st, (const uint4*)Xp, (const uint4*)Wp, M, N, K,
+  return launch(KID_GEMM_BIG, k_gemm_qkv_rope<128>, grid, dim3(256), lds, st, (const uint4*)Xp, (const uint4*)Wp, M, N, K,
                 epi);
 }
 
