@@ -1448,10 +1448,16 @@ __global__ void __launch_bounds__(256, 2) k_flash_attention(const f16* __restric
   if (pp + 1 < npairs) {
     fetch(pp + 1, odd);
     multiply(pp, even, inner);
-    multiply(pp + 1, odd, last);
-  } else {
-    multiply(pp, even, last);
+    // copied, once per walk: a second copy of the masked code spilled registers (head dim 128, two heads)
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk) kf[0][t][kk] = kf[1][t][kk];
+#pragma unroll
+    for (int dt = 0; dt < DT; ++dt) vf[0][dt] = vf[1][dt];
+    ++pp;
   }
+  multiply(pp, even, last);
   if (q0 + qcol >= T) return;
 #pragma unroll
   for (int h = 0; h < HPW; ++h) {

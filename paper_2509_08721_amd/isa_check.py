@@ -87,6 +87,17 @@ def waits_behind_stores(asm_text: str):
     return out
 
 
+def scratch(asm_text: str):
+    """{kernel: bytes of scratch memory per lane} of the kernels that use any (spilled registers, arrays the compiler could
+    not keep in registers)."""
+    out = {}
+    for m in re.finditer(r"^\s*\.amdhsa_kernel (\S+)\n(.*?)^\s*\.end_amdhsa_kernel", asm_text, re.M | re.S):
+        n = int(re.search(r"\.amdhsa_private_segment_fixed_size (\d+)", m.group(2)).group(1))
+        if n:
+            out[m.group(1)] = n
+    return out
+
+
 def assemble(src: str, tmp: str) -> str:
     """The gfx950 assembly of one source of the library."""
     flags = [f for f in B.FLAGS if f not in ("-fPIC",)] + ["--cuda-device-only", "-S"]

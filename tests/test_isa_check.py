@@ -80,3 +80,11 @@ def test_residual_epilogues_of_the_decode_gemms_do_not_wait_behind_their_stores(
     found = isa_check.waits_behind_stores(isa_check.assemble("kernels_decode.hip", str(tmp_path)))
     resid = [fn for fn in found if "k_skinny16" in fn and fn.endswith("ELi1EEEvNS_10SkinnyArgsEi")]
     assert resid == [], resid
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None and not shutil.os.path.exists("/opt/rocm/bin/hipcc"), reason="no hipcc")
+@pytest.mark.parametrize("src", ["kernels_mfma.hip", "kernels_rows.hip", "kernels_decode.hip"])
+def test_matrix_core_kernels_use_no_scratch_memory(tmp_path, src):
+    asm = isa_check.assemble(src, str(tmp_path))
+    assert ".amdhsa_private_segment_fixed_size 0" in asm     # what the scan looks for is there
+    assert isa_check.scratch(asm) == {}
