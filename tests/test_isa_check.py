@@ -1,5 +1,6 @@
 """The check of the generated code for matrix-core instructions under a lane mask (they ignore the mask, so a guard
 whose branch the compiler dropped lets them run on registers that were never loaded)."""
+import re
 import shutil
 
 import pytest
@@ -77,9 +78,10 @@ def test_reports_a_wait_that_covers_a_store():
 
 @pytest.mark.skipif(shutil.which("hipcc") is None and not shutil.os.path.exists("/opt/rocm/bin/hipcc"), reason="no hipcc")
 def test_residual_epilogues_of_the_decode_gemms_do_not_wait_behind_their_stores(tmp_path):
-    found = isa_check.waits_behind_stores(isa_check.assemble("kernels_decode.hip", str(tmp_path)))
-    resid = [fn for fn in found if "k_skinny16" in fn and fn.endswith("ELi1EEEvNS_10SkinnyArgsEi")]
-    assert resid == [], resid
+    asm = isa_check.assemble("kernels_decode.hip", str(tmp_path))
+    resid = set(re.findall(r"^(_ZN4sapo10k_skinny16I(?:Li\d+E){4}Li[13]EEE\w*):", asm, re.M))     # modes RESID and RESID_X32
+    assert len(resid) >= 6, resid
+    assert resid.isdisjoint(isa_check.waits_behind_stores(asm))
 
 
 @pytest.mark.skipif(shutil.which("hipcc") is None and not shutil.os.path.exists("/opt/rocm/bin/hipcc"), reason="no hipcc")
