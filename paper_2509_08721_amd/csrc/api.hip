@@ -624,10 +624,11 @@ struct DecodeBufs {
   int s_pad;        // 64 * token blocks
   void* xa;         // X16 [s_pad, d]: input of the QKV projection (and of the LM head after the last layer)
   void* xb;         // X16 [s_pad, d]: input of the gate/up projection
-  float* ssq_a;     // [d/16][s_pad] sums of squares behind xa
-  float* ssq_b;     // [d/16][s_pad] sums of squares behind xb
+  float* ssq_a;     // [at most d/16][s_pad] sums of squares behind xa
+  float* ssq_b;     // [at most d/16][s_pad] sums of squares behind xb
   // 65 .. 256 sequences: the FFN runs on the kernels of kernels_rows.hip
   bool rows;
+  int parts;        // sums of squares per row that a layer leaves behind xa
   float* partial;   // parts of the down projection
   // up to 64 sequences: the layers of a step run as one persistent kernel (decode_persist.hip)
   bool persistent;
@@ -641,6 +642,7 @@ static void carve_decode(Arena& A, const sapo_weights* w, int S, DecodeBufs& db)
   db.ssq_a = A.take<float>((d / 16) * db.s_pad);
   db.ssq_b = A.take<float>((d / 16) * db.s_pad);
   db.rows = S > 64 && S <= 256;
+  db.parts = db.rows ? r_down_parts((int)d) : (int)d / 16;
   db.partial = db.rows ? A.take<float>(r_down_partial_floats(S, (int)d)) : nullptr;
   // opt-in: measured slower than one kernel per phase on the 0.5B-class decoder
   const char* persist = getenv("SAPO_PERSIST");
@@ -650,8 +652,8 @@ static void carve_decode(Arena& A, const sapo_weights* w, int S, DecodeBufs& db)
 }
 
 // On entry b.h holds the residual rows, db.xa their X16 form for layer 0's attention norm and
-// db.ssq_a their sums of squares in ONE part.  On exit db.xa / db.ssq_a (d/16 parts) feed the
-// final norm, and b.h holds the final residual rows.
+// db.ssq_a their sums of squares in ONE part.  On exit db.xa / db.ssq_a (db.parts parts, where there is a layer)
+// feed the final norm, and b.h holds the final residual rows.
 static int run_layers_decode16(const sapo_weights* w, const FwdBufs& b, const DecodeBufs& db, int S, RowMap rm,
                                const CacheBufs& cb, PersistCtl* pctl, const ShareArgs* share, hipStream_t st) {
   const sapo_model_config& c = w->cfg;
@@ -677,7 +679,6 @@ static int run_layers_decode16(const sapo_weights* w, const FwdBufs& b, const De
   // more than 64 rows only QKV's weights are prefetched: attention fills the chip there, and gate/up's in its launch took
   // the step from 928 to 995 us at 96 rows, 1106 to 1127 at 192 (0.5B), 2162 to 2269 at 256 (1.5B); down's in gate/up's
   // changed nothing (930, 1135, 2191).
-  const int down_parts = db.rows ? r_down_parts(d) : d / 16;
   for (int l = 0; l < c.n_layers; ++l) {
     const LayerWeights& lw = w->layers[l];
     const KVCache kvc = layer_cache(w, cb, l);
@@ -685,7 +686,7 @@ static int run_layers_decode16(const sapo_weights* w, const FwdBufs& b, const De
     a.n_rows = S; a.s_pad = db.s_pad; a.eps = c.rms_eps; a.norm_dim = d;
     // QKV projection of the attention-normed residual
     a.Wp = (const uint4*)lw.wqkv16; a.Xp = (const uint4*)db.xa; a.N = nqkv; a.K = d;
-    a.ssq_in = db.ssq_a; a.ssq_parts = (l == 0) ? 1 : down_parts;
+    a.ssq_in = db.ssq_a; a.ssq_parts = (l == 0) ? 1 : db.parts;
     a.out_f32 = b.qkv; a.ldc = nqkv; a.bias = lw.bqkv;
     HIP_CK(d_gemm_skinny(a, SKM_STORE, st));
     ShareArgs sh_l;
@@ -922,10 +923,6 @@ static int rollout_impl(const sapo_weights* w, const int32_t* prompts, const int
       return SAPO_OK;
     }
   }
-  auto parts_after_layers = [&](const RolloutPlan::Level& lv) {
-    return c.n_layers == 0 ? 1 : d / 16;
-  };
-
   SampleParams sp;
   sp.temperature = temperature;
   sp.seed_lo = (uint32_t)(seed & 0xffffffffu);
@@ -1023,7 +1020,7 @@ static int rollout_impl(const sapo_weights* w, const int32_t* prompts, const int
       // the prompt's pages once per group of siblings: the full batch only (rows = sequences)
       const ShareArgs* sh = (share.prefix_pairs > 0 && lv.slot_seq == nullptr && lv.slots == S) ? &share : nullptr;
       if ((rc2 = run_layers_decode16(w, pl.fwd, lv.dec, lv.slots, rm, pl.cache, pl.pctl, sh, st))) return rc2;
-      if ((rc2 = sample_step(w, pl, lv, pl.fwd.h, parts_after_layers(lv), spl, st))) return rc2;
+      if ((rc2 = sample_step(w, pl, lv, pl.fwd.h, c.n_layers == 0 ? 1 : lv.dec.parts, spl, st))) return rc2;
     } else {
       HIP_CK(g_embed(dt, out_tokens, max_new, pl.step, w->embed, pl.fwd.h, S, d, st));
       if ((rc2 = run_layers(w, pl.fwd, S, rm, pl.cache, Lp + max_new, st))) return rc2;

@@ -52,15 +52,15 @@ struct RowMap {
   __device__ __forceinline__ bool keeps_kv(int m) const { return decode || !lens || (m % T) < lens[m / T]; }
 };
 
-// Paged KV cache of one layer.  K page: [Hkv][16 tokens][hd]; V page: [Hkv][hd][16 tokens]
-// (V is kept token-minor so that a fixed feature's 16 tokens are contiguous).
+// Paged KV cache of one layer.  K and V page: [Hkv] x 16 tokens of hd values, for the shape-generic kernels K as
+// [16 tokens][hd] and V as [hd][16 tokens] (token-minor: a fixed feature's 16 tokens are contiguous).
 // Element type: fp32 for fp32 models; for bf16 models the shape-generic kernels keep bf16 and the
 // MFMA kernels keep IEEE half (same 2 bytes, 3 more mantissa bits: attention involves no weights,
 // so its operands need not share the weights' type; values are clamped to the half range).
 // Inside a page and head the MFMA kernels keep the order in which a wave reads it as operands (k_page_at, v_page_at).
 struct KVCache {
-  void* k;                // [n_pages][Hkv][16][hd]
-  void* v;                // [n_pages][Hkv][hd][16]
+  void* k;                // [n_pages][Hkv] pages
+  void* v;                // [n_pages][Hkv] pages
   const int* page_table;  // [n_cache_seq][pages_per_seq]
   int pages_per_seq;
   int n_kv_heads;
@@ -389,7 +389,7 @@ hipError_t g_gumbel(uint32_t seed_lo, uint32_t seed_hi, uint32_t seq, uint32_t s
 // =======================================================================================
 namespace sapo {
 
-int n_compute_units();   // of the current device
+int n_compute_units();   // of the device that was current at the first call
 
 // Weights (fragment order: tiles of KS blocks of 1 KiB) of a later launch that extra workgroups of an earlier one bring into
 // the L2s: the first ks1 blocks of every tile, the tiles of unit u (2^nt_log2 tiles) into the L2 of XCD u % 8.

@@ -269,7 +269,7 @@ __device__ __forceinline__ void skinny_unit(const SkinnyArgs& a, int unit, int t
 // query column: the running max / sum are per-lane scalars plus two cross-lane shuffles, and the
 // probabilities a lane produces are exactly its operand of O^T = V^T P^T.  Token rows are permuted
 // inside a 32-token page pair so that a lane's 8 probabilities are 8 consecutive tokens, which is
-// what the token-minor V page delivers in one 16-byte load.  Waves take page pairs round-robin, PD
+// what a lane gets from a V page in one 16-byte load (v_page_at).  Waves take page pairs round-robin, PD
 // pairs at a time with all their K/V fragments in flight at once; the first chunk is requested
 // before the query rows are even read (K/V addresses depend on the page table only), so a step
 // pays one memory round trip, not one per dependent stage.  Waves are merged through LDS.

@@ -899,7 +899,7 @@ hipError_t d_lmhead_merge_embed(const float* partials, int n_parts, int row_stri
 // query column: the running max / sum are per-lane scalars plus two cross-lane shuffles, and the
 // probabilities a lane produces are exactly its operand of O^T = V^T P^T.  Token rows are permuted
 // inside a 32-token page pair so that a lane's 8 probabilities are 8 consecutive tokens, which is
-// what the token-minor V page delivers in one 16-byte load.  Waves take page pairs round-robin, PD
+// what a lane gets from a V page in one 16-byte load (v_page_at).  Waves take page pairs round-robin, PD
 // pairs at a time with all their K/V fragments in flight at once; the first chunk is requested
 // before the query rows are even read (K/V addresses depend on the page table only), so a step
 // pays one memory round trip, not one per dependent stage.  Waves are merged through LDS.
@@ -1464,7 +1464,7 @@ hipError_t d_decode_attention(const float* qkv, const float2* rope, RowMap rm, K
   if (kv.head_dim == 128) {
     // more workgroups than compute units: 4-wave workgroups with one page pair in flight per wave leave room for
     // two per compute unit, so the whole grid is resident at once (1.5B, 256 sequences: 24.7 us against 29.8)
-    if (S * kv.n_kv_heads > 256) return launch_decode_attention<128, 4, 1>(qkv, rope, rm, kv, out, S, n_q_heads, st, pf);
+    if (S * kv.n_kv_heads > n_compute_units()) return launch_decode_attention<128, 4, 1>(qkv, rope, rm, kv, out, S, n_q_heads, st, pf);
     return launch_decode_attention<128, 8, 2>(qkv, rope, rm, kv, out, S, n_q_heads, st, pf);
   }
   return hipErrorInvalidValue;

@@ -1293,7 +1293,7 @@ hipError_t m_lmhead_sample_big(const void* Xp, const void* Wp, int n_rows, int V
 // fragment registers: S^T = K Q^T puts one query column in each lane, so the running max / sum are
 // per-lane scalars (plus two shuffles) and the probabilities a lane produces are its operand of
 // O^T = V^T P^T; key rows are permuted inside a pair so that a lane's 8 probabilities are 8
-// consecutive tokens, the unit the token-minor V page delivers in one 16-byte load.  No LDS, no
+// consecutive tokens, what a lane gets from a V page in one 16-byte load (v_page_at).  No LDS, no
 // block-level synchronisation; waves never exchange data.  q (row-major [rows, Hq hd]), K, V and the
 // probabilities are IEEE half; the output goes out as half in X32 order (the O projection's operand).
 // What bounds it: a SIMD issues MFMAs, vector instructions and (quarter rate) exponentials one after the other, 8 + ~35 + 8 per

@@ -1410,12 +1410,12 @@ __device__ __forceinline__ void store_acc(float* __restrict__ row, const f32x4_t
 // products over the positions, and goes through the wave's own LDS (chunks XORed with the row's low bits: free of bank
 // conflicts both ways) for the products over the head dim; the next tile is on its way meanwhile.  Same products in the same
 // order.  The grids deal the longest walks first: causal walks are 1 .. T / 16 tiles long, and with the tile index fastest
-// the compute units had waves 62 % of the time.  Register limits leave two waves a SIMD (a limit for more spills).
+// the compute units had waves 62 % of the time.  Registers leave a SIMD four waves (forward), three (d queries) and two (d keys
+// and values) at head dim 64, and two, one and one at head dim 128; limits for more spill.
 // us per layer, forward / d queries / d keys and values, before and now:
-//   14 heads of 64,  64 x 384 tokens: 320 / 432 / 704, 238 / 326 / 437;   21 x 301: 77 / 96 / 150, 52 / 70 / 90
-//   12 heads of 128, 64 x 384 tokens: 494 / 705 / 1507, 388 / 657 / 871;   9 x 300: 79 / 101 / 180, 46 / 74 / 86
-// The matrix cores are now busy 52 - 60 % of the time a compute unit has waves ; the rest is
-// mostly the softmax's vector instructions, which a SIMD issues in turn with them.
+//   14 heads of 64,  64 x 384 tokens: 329 / 415 / 686, 225 / 317 / 408;   21 x 301: 83 / 106 / 161, 58 / 77 / 100
+//   12 heads of 128, 64 x 384 tokens: 490 / 701 / 1489, 384 / 680 / 905;   9 x 300: 76 / 105 / 183, 45 / 77 / 93
+// What is left is mostly the softmax's vector instructions, which a SIMD issues in turn with the MFMAs.
 template <int HD> struct TileCols {
   f32x4_t x[4][HD / 64];
   unsigned off[4];   // bytes from the tile's first position to this lane's chunk of the positions 4 g + u
