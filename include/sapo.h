@@ -100,7 +100,8 @@ typedef struct sapo_weights sapo_weights; /* opaque, library-owned */
  * +-65504 is clamped to +-65504 (never infinite): the results stay finite but no longer follow the
  * definition; sapo_debug_half_clamped counts such values for a given batch.  The operand of a
  * projection after an RMSNorm is (residual row x gain), normalised after the product, so the clamp
- * is reached when |residual x gain| exceeds 65504, whatever the row's norm.
+ * is reached when |residual x gain| exceeds 65504, whatever the row's norm (the feed-forward part of
+ * decode steps with 65 .. 256 sequences excepted: such a row is normalised first there).
  */
 int sapo_weights_create(const sapo_model_config* cfg, const void* const* tensors, int n_tensors,
                         void* stream, sapo_weights** out);
@@ -145,7 +146,9 @@ size_t sapo_debug_logits_workspace_bytes(const sapo_weights* w, int S, int T, in
  *   out_tokens    dev int32 [P*G, max_new]   generated tokens only
  *   out_logprobs  dev fp32  [P*G, max_new]   log softmax(z)[token] at temperature 1
  *   workspace     dev, >= sapo_rollout_workspace_bytes(w, P, Lp, G, max_new), 256-byte aligned
- * Requires Lp >= 1, Lp + max_new <= cfg.max_seq.
+ * Requires Lp >= 1, Lp + max_new <= cfg.max_seq.  On the matrix-core path a model with d_model > 1536
+ * takes decode steps (max_new > 1) with 65 .. 256 sequences only; other calls return SAPO_ESHAPE before
+ * they write anything.
  * A step whose logits are not numbers (NaN from non-finite weights set behind the library's back, or
  * a decode step that gave up its bounded wait) yields token -1 with log-prob 0 for that row instead
  * of an id; the row's later steps continue from id 0.  A caller that sees -1 discards the row.

@@ -1415,7 +1415,8 @@ __device__ __forceinline__ void store_acc(float* __restrict__ row, const f32x4_t
 // us per layer, forward / d queries / d keys and values, before and now:
 //   14 heads of 64,  64 x 384 tokens: 329 / 415 / 686, 225 / 317 / 408;   21 x 301: 83 / 106 / 161, 58 / 77 / 100
 //   12 heads of 128, 64 x 384 tokens: 490 / 701 / 1489, 384 / 680 / 905;   9 x 300: 76 / 105 / 183, 45 / 77 / 93
-// What is left is mostly the softmax's vector instructions, which a SIMD issues in turn with the MFMAs.
+// Matrix cores busy over a launch, 64 x 384 tokens, heads of 64: 37 / 42 / 33 %, now 51 / 57 / 56 %; the rest is mostly the
+// softmax's vector instructions, which a SIMD issues in turn with the MFMAs.
 template <int HD> struct TileCols {
   f32x4_t x[4][HD / 64];
   unsigned off[4];   // bytes from the tile's first position to this lane's chunk of the positions 4 g + u
