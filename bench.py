@@ -312,11 +312,11 @@ def bench_update(args, wl):
         for name, (ms, cnt) in sorted(prof.items(), key=lambda kv: -kv[1][0]):
             kernels[name] = {"launches": cnt, "total_ms": round(ms, 3), "avg_us": round(ms * 1e3 / cnt, 3)}
         if "k_gemm" in kernels:
-            # The GEMMs multiply fp32 values as three bf16 pieces each: one algorithmic multiply-add is six bf16
-            # MFMA multiply-adds.  `achieved` counts the algorithmic flops (what an fp32 GEMM would count) against
-            # the bf16 MFMA peak, the contraction's own type; `executed_*` counts what the matrix cores ran.
+            # The GEMMs multiply fp32 values as pairs of 16-bit values: one algorithmic multiply-add is three 16-bit MFMA
+            # multiply-adds.  `achieved` counts the algorithmic flops (what an fp32 GEMM would count) against the 16-bit
+            # MFMA peak, the contraction's own type; `executed_*` counts what the matrix cores ran.
             k = kernels["k_gemm"]
-            n_products = {3: 6, 2: 3, 1: 1}[args.pieces]
+            n_products = {3: 3, 2: 3, 1: 1}[args.pieces]
             ach = flops / (k["total_ms"] * 1e-3) / 1e12
             k.update(bound="mfma", work_per_launch=flops / k["launches"], achieved=round(ach, 2), unit="TFLOP/s",
                      frac=round(ach / MFMA_16BIT_PEAK_TFLOPS, 4))
@@ -345,7 +345,7 @@ def bench_update(args, wl):
            "ms_per_step": round(dt * 1e3, 3), "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
            "dtype": {3: "f32", 2: "bf16x2", 1: "bf16"}[args.pieces], "data": "synthetic",
            "config": {"workload": wl.name,
-                      "arithmetic": {3: "fp32 (GEMM products as 6 bf16 x bf16 partial products, fp32 accumulation)",
+                      "arithmetic": {3: "fp32 (GEMM products as 3 half x half partial products of scaled rows, fp32 accumulation)",
                                      2: "fp32 with GEMM operands of 16 significant bits (2 bf16 pieces, 3 partial products), "
                                         "fp32 accumulation",
                                      1: "fp32 with bf16 GEMM operands (1 piece), fp32 accumulation"}[args.pieces],

@@ -373,9 +373,9 @@ size_t sapo_trainer_workspace_bytes_for(const sapo_trainer* tr, int S, int T, in
  *                    (sapo_trainer_workspace_bytes_for gives the size for a chosen number), adding their
  *                    gradients up before the one Adam step: the same update up to the order of fp32
  *                    additions.  SAPO_EWORKSPACE if not even one sequence fits.
- * fp32 values throughout (the large matrix products are formed from bf16 pieces on the matrix cores
- * with the accuracy of fp32 products), every sum in a fixed order (no atomics): the same call on the
- * same state gives the same bits.  How the sums are cut depends on the size of the set (and of the
+ * fp32 values throughout (the large matrix products are formed from half-precision pairs on the matrix
+ * cores with the accuracy of fp32 products), every sum in a fixed order: the same call on the same
+ * state gives the same bits.  How the sums are cut depends on the size of the set (and of the
  * micro-batch): with three pieces (sapo_trainer_set_matmul_pieces) a sequence's log-probs may differ in
  * their last bits between sets of different size, with two and one they do not; gradients may with any.
  * The LM head runs only on the rows that predict a masked token; the host sizes its products from their
@@ -406,11 +406,12 @@ int sapo_trainer_set_qkv_bias(sapo_trainer* tr, int layer, const float* bq, cons
 int sapo_trainer_get_qkv_bias(const sapo_trainer* tr, int layer, float* bq, float* bk, float* bv, void* stream);
 /*
  * Arithmetic of the update's large matrix products (projections and LM head; forward and backward).
- *   pieces = 3 (default): every fp32 operand is the exact sum of three bf16 values and a product is the
- *                sum of the six largest of the nine partial products: the accuracy of an fp32 product.
+ *   pieces = 3 (default): every operand row along the contraction is scaled by a power of two and every
+ *                value kept as the sum of two half-precision values; a product is the sum of the three
+ *                larger of the four partial products: the accuracy of an fp32 product.  (A value below
+ *                2^-17 of the largest of its row is kept to 2^-40 of that largest.)
  *   pieces = 2: every operand is rounded to 16 significant bits (two bf16 values) and a product is the
- *                sum of three partial products: relative error below 2^-16 per product, of either sign,
- *                at half the matrix-core work.
+ *                sum of three partial products: relative error below 2^-16 per product, of either sign.
  *   pieces = 1: operands rounded to bf16 (nearest even), fp32 accumulation: plain mixed precision,
  *                several times faster; gradients then carry the relative error of bf16 operands
  *                (about 2^-8 of a contraction's sum of absolute terms).

@@ -30,7 +30,7 @@ constexpr bool small_offsets_fit(uint64_t d, uint64_t q, uint64_t kv, uint64_t c
 }
 
 // Tile height (TJ blocks of 128 rows) and split of a packed product of the update (k_gemm_x3, k_gemm_x3_tn) with rows x cols
-// outputs and KB steps of 16 along the contraction, in stages of `stage` steps; NP bf16 pieces per value.  A product whose
+// outputs and KB steps of 16 along the contraction, in stages of `stage` steps; three products per value pair (NP 3, 2) or one.  A product whose
 // output tiles fill the workgroups in flight badly (weight gradients: 49 .. 532 tiles; outputs d wide: 672 tiles on 512
 // slots are 1.3 rounds run as 2) is split along the contraction where parts_cap (floats) allows it: each part writes its own
 // product and k_sum_parts adds them in part order.  Taken are the height and number of parts with the least estimated time:
@@ -45,14 +45,14 @@ constexpr int kMaxSplits = 16, kChainSteps = 608;
 struct X3Split { int TJ, parts, per_part; };
 inline X3Split x3_split(int NP, int rows, int cols, int KB, int stage, size_t parts_cap) {
   const int gnx = (cols + 127) / 128, gny = (rows + 127) / 128;
-  const double terms = NP == 3 ? 6.0 : NP == 2 ? 3.0 : 1.0;
+  const double terms = NP == 1 ? 1.0 : 3.0;
   X3Split best{2, 1, (KB + stage - 1) / stage * stage};
   double best_us = 0.0;
   for (int TJ = 2; TJ >= 1; --TJ) {
     const int gty = (gny + TJ - 1) / TJ;
     const long tiles = (long)gnx * gty, slots = TJ == 2 ? 512 : 768;
-    // one 16-k step of a full round (measured: 1.6 PFLOP/s with three pieces, 0.9 with one; 10 % more for the small tile)
-    const double step_us = (TJ == 2 ? 1.0 : 0.825) * 0.336 * terms * (NP == 1 ? 1.8 : NP == 2 ? 1.2 : 1.0);
+    // one 16-k step of a full round (measured: 1.35 PFLOP/s with three products, 0.9 with one; 10 % more for the small tile)
+    const double step_us = (TJ == 2 ? 1.0 : 0.825) * 0.336 * terms * (NP == 1 ? 1.8 : 1.2);
     for (int s = 1; s <= kMaxSplits; ++s) {
       if (s > 1 && (KB / s < 16 || (size_t)s * rows * cols > parts_cap)) break;
       if ((KB + s - 1) / s > kChainSteps && s < kMaxSplits && (size_t)(s + 1) * rows * cols <= parts_cap) continue;

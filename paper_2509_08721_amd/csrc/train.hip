@@ -2,10 +2,10 @@
 // KL term, asymmetric clipping, Adam with its default hyper-parameters): kernels, orchestration, C ABI.
 //
 // Values are fp32 on row-major buffers: master parameters, activations, gradients and the two Adam
-// moments; the large GEMMs form their products from bf16 pieces on the matrix cores at fp32 accuracy
+// moments; the large GEMMs form their products from half-precision pairs on the matrix cores at fp32 accuracy
 // (k_gemm_x3).  One update = forward pass over the whole training set with every layer's activations
 // kept (HBM is large enough: about 80 KB per token and layer for the 0.5B shape), the clipped surrogate,
-// the backward pass, one Adam step.  No atomics: every sum has a fixed order, so an update is
+// the backward pass, one Adam step.  Every sum has a fixed order (atomics take integer maxima only), so an update is
 // reproducible bit for bit.
 #include <math.h>
 #include <stdio.h>
@@ -262,100 +262,162 @@ __global__ void __launch_bounds__(256) k_sgemm_mfma(const float* __restrict__ A,
 }
 
 // ---------------------------------------------------------------------------------------
-// The large GEMMs at fp32 accuracy on the bf16 matrix cores.  An fp32 value is the exact sum of three bf16
-// values (its 24-bit mantissa cut into three 8-bit pieces: hi, mid, lo); a product a b is taken as the six
-// partial products of weight >= 2^-16 (hi hi, hi mid, mid hi, hi lo, lo hi, mid mid), each exact in fp32,
-// the three dropped ones being below 2^-23 of the product: the rounding of an fp32 multiply.  Six
-// v_mfma_f32_32x32x16_bf16 (32 cycles each) do the work of sixteen v_mfma_f32_32x32x2_f32 (64 cycles each).
-// With one piece the same kernels are a plain bf16 GEMM with fp32 accumulation (the value rounded to nearest).
-// With two pieces (the value rounded to bf16, then the exact remainder rounded to bf16: 16 significant bits) the
-// three products hi hi, hi mid, mid hi are taken: what is dropped is below 2^-16 of a product and of either sign,
-// at half the matrix-core work of the six-product form.
+// The large GEMMs at fp32 accuracy on the half-precision matrix cores.  Every row of an operand (a row of op(A), a column of
+// op(B): what one output's contraction runs along) is scaled by a power of two that brings its largest value into
+// [2^14, 2^15), and a scaled value is taken as the sum of two halves: hi, the value rounded to nearest, and lo, the remainder
+// rounded to nearest.  hi + lo is within 2^-23 of a value of at least 2^-17 of its row's largest and within 2^-40 of that
+// largest for smaller ones.  A product is the three partial products hi lo, lo hi, hi hi, each exact in fp32; lo lo, below 2^-22
+// of the product and of either sign, is dropped.  The output is scaled back by an exact power of two.  Three
+// v_mfma_f32_32x32x16_f16 (32 cycles each) do the work of sixteen v_mfma_f32_32x32x2_f32 (64 cycles each).  What this replaces,
+// values cut into three bf16 pieces without scales and six partial products, dropped products up to 2^-21 of one sign,
+// took six, and 6 bytes a value instead of 4: 64 x 384 tokens of the 0.5B decoder 386 -> 259 ms an update, 21 x 301 tokens 109 -> 77,
+// with smaller errors against 64 bits, since the sums take half as many roundings (21 x 301 tokens: gradient 2.7e-5 -> 1.2e-5,
+// log-probs 1.7e-6 -> 1.3e-6).  Of that the products 285 -> 190 ms (1.19 PFLOP/s of executed products, 1.48 in the largest).
+// That is NP = 3, the accuracy of three bf16 pieces.  With NP = 2 a value is rounded to bf16 and the remainder to bf16 (16
+// significant bits, no scales: 5 % less time an update), the same three products; with NP = 1 the same kernels are a plain
+// bf16 GEMM with fp32 accumulation (the value rounded to nearest).
 //
-// Operands are cut once per GEMM by k_pack_x3 into the order a workgroup stages them in: for every block of
-// 128 rows and every 16-k step, [piece][k half][row] entries of 8 bf16 (16 bytes): one contiguous 2 KB x
-// pieces x 2 run per step, and the LDS image needs no rearrangement.  Rows and k are zero-padded to the
-// blocks.  "Rows" are the M side of op(A) or the N side of op(B); k is the contraction.
+// A row's largest value is kept as its bits without the sign, as integers order them (NaN above infinity above all others);
+// whoever writes a tensor leaves the maxima of its rows, and packing it by rows those of its columns for the products
+// that contract over the rows.  Maxima do not depend on the order they are taken in, so atomics leave the same bits.
+//
+// Operands are cut by k_pack_x3 into the order a workgroup stages them in: for every block of 128 rows and every 16-k step,
+// [part][k half][row] entries of 8 values (16 bytes): one contiguous 2 KB x parts x 2 run per step, and the LDS image
+// needs no rearrangement.  Rows and k are zero-padded to the blocks.  "Rows" are the M side of op(A) or the N side of op(B);
+// k is the contraction.
 // ---------------------------------------------------------------------------------------
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef _Float16 halfx8_t __attribute__((ext_vector_type(8)));
 // 16-byte entries as a plain vector type: with HIP's uint4 struct the compiler kept the kernel's prefetch registers
 // in scratch memory (every load waited for at once, then re-read), 2.7x slower
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
-union Frag8 { u32x4_t u; bf16x8_t v; };
+union Frag8 { u32x4_t u; bf16x8_t v; halfx8_t h; };
 
-__device__ __forceinline__ void split3(float x, uint32_t& hi, uint32_t& mid, uint32_t& lo) {   // bf16 bits in the high halves
-  hi = __float_as_uint(x) & 0xFFFF0000u;
-  const float r = x - __uint_as_float(hi);
-  mid = __float_as_uint(r) & 0xFFFF0000u;
-  const float r2 = r - __uint_as_float(mid);
-  lo = __float_as_uint(r2) & 0xFFFF0000u;
+__device__ __forceinline__ uint32_t max_u32_xor16(uint32_t v) {
+  const lane_u32x2 r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  return max((uint32_t)r[0], (uint32_t)r[1]);
 }
-__device__ __forceinline__ uint32_t pack_hi(uint32_t a, uint32_t b) { return (a >> 16) | b; }   // a low half, b high half
+__device__ __forceinline__ uint32_t max_u32_xor32(uint32_t v) {
+  const lane_u32x2 r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  return max((uint32_t)r[0], (uint32_t)r[1]);
+}
+__device__ __forceinline__ uint32_t abs_bits(float x) { return __float_as_uint(x) & 0x7FFFFFFFu; }
+// the wave's largest, in every lane: four steps within 16 lanes by DPP, two between them
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
+  v = max(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, true));    // lane ^ 1
+  v = max(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, true));    // lane ^ 2
+  v = max(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x141, 0xF, 0xF, true));   // mirrored within 8
+  v = max(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x140, 0xF, 0xF, true));   // mirrored within 16
+  return max_u32_xor32(max_u32_xor16(v));
+}
+// Scale of a row whose largest value has the bits mx: 2^-row_exp(mx).  Rows below 2^-112 take the largest scale (their values,
+// multiples of 2^-149, are then multiples of 2^-23); with an infinity or NaN in the row every output of it is one whatever
+// the scale.
+__device__ __forceinline__ int row_exp(uint32_t mx) {
+  const int e = (int)(mx >> 23);
+  return e == 255 ? 0 : max(e, 15) - 141;
+}
+__device__ __forceinline__ float row_scale(uint32_t mx) { return __uint_as_float((uint32_t)(127 - row_exp(mx)) << 23); }
 
-// entry (16 bytes) of (piece, row, k / 8) in a packed operand with KB = padded K / 16 steps
-__device__ __forceinline__ size_t x3_entry(int NP, int KB, int piece, int row, int k8) {
-  return ((((size_t)(row >> 7) * KB + (k8 >> 1)) * NP + piece) * 2 + (k8 & 1)) * 128 + (row & 127);
+// A bound of the products of two rows' values, times f, from their maxima
+__device__ __forceinline__ uint32_t product_bound(uint32_t a, uint32_t b, float f) {
+  if (max(a, b) >= 0x7F800000u) return 0x7F800000u;
+  return __float_as_uint(fminf(__uint_as_float(a) * __uint_as_float(b) * f, 3.4028234e38f));
 }
-template <int NP>
-__device__ __forceinline__ void x3_store(uint4* __restrict__ dst, int KB, int row, int k8, const float (&x)[8]) {
-  uint32_t p[3][8];
+
+__host__ __device__ constexpr int x3_parts(int NP) { return NP == 1 ? 1 : 2; }   // 16-bit values that a value is kept as
+// 8 values (scaled: NP 3) as MFMA fragments
+template <int NP> __device__ __forceinline__ void x3_cut(const float (&x)[8], float scale, Frag8 (&f)[x3_parts(NP)]) {
 #pragma unroll
-  for (int j = 0; j < 8; ++j) split3(x[j], p[0][j], p[1][j], p[2][j]);
-  if constexpr (NP < 3) {   // one or two pieces are roundings to nearest even (of the value, then of what is left), not bit fields
-    auto rne = [](float f) { const uint32_t u = __float_as_uint(f); return (u + 0x7FFFu + ((u >> 16) & 1u)) & 0xFFFF0000u; };
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      p[0][j] = rne(x[j]);
-      p[1][j] = rne(x[j] - __uint_as_float(p[0][j]));
+  for (int e = 0; e < 8; ++e) {
+    if constexpr (NP == 3) {
+      const float y = x[e] * scale;
+      const _Float16 hi = (_Float16)y;   // round to nearest even
+      f[0].h[e] = hi;
+      f[1].h[e] = (_Float16)(y - (float)hi);
+    } else {
+      const __bf16 hi = (__bf16)x[e];
+      f[0].v[e] = hi;
+      if constexpr (NP == 2) f[1].v[e] = (__bf16)(x[e] - (float)hi);
     }
   }
-#pragma unroll
-  for (int pc = 0; pc < NP; ++pc)
-    dst[x3_entry(NP, KB, pc, row, k8)] = make_uint4(pack_hi(p[pc][0], p[pc][1]), pack_hi(p[pc][2], p[pc][3]),
-                                                    pack_hi(p[pc][4], p[pc][5]), pack_hi(p[pc][6], p[pc][7]));
 }
-// src[row * ld + k]: one workgroup per (block of 128 rows, 8 k steps); thread (row, k half) reads 8 consecutive
-// k per step, so a row is read in 64-byte runs and every piece of a step goes out as two 2 KB runs
+
+// entry (16 bytes) of (part, row, k / 8) in a packed operand with KB = padded K / 16 steps
+__device__ __forceinline__ size_t x3_entry(int parts, int KB, int part, int row, int k8) {
+  return ((((size_t)(row >> 7) * KB + (k8 >> 1)) * parts + part) * 2 + (k8 & 1)) * 128 + (row & 127);
+}
+template <int NP>
+__device__ __forceinline__ void x3_store(u32x4_t* __restrict__ dst, int KB, int row, int k8, const float (&x)[8], float scale) {
+  constexpr int PC = x3_parts(NP);
+  Frag8 f[PC];
+  x3_cut<NP>(x, scale, f);
+#pragma unroll
+  for (int pc = 0; pc < PC; ++pc) dst[x3_entry(PC, KB, pc, row, k8)] = f[pc].u;
+}
+// the row's scale (NP 3)
+template <int NP> __device__ __forceinline__ float x3_scale(const uint32_t* __restrict__ mx, int row) {
+  return NP < 3 ? 1.f : row_scale(mx[row]);
+}
+// Largest values of the 8 columns k0 .. k0 + 7 of each lane, over the wave's lanes with the same lane % C, into col_mx
+template <int C> __device__ __forceinline__ void wave_column_max(uint32_t (&cm)[8], uint32_t* __restrict__ col_mx, int k0, int K) {
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    if constexpr (C == 4) cm[e] = max(cm[e], (uint32_t)__builtin_amdgcn_mov_dpp((int)cm[e], 0x124, 0xF, 0xF, true));   // rotated by 4 lanes of 16
+    cm[e] = max_u32_xor32(max_u32_xor16(max(cm[e], (uint32_t)__builtin_amdgcn_mov_dpp((int)cm[e], 0x128, 0xF, 0xF, true))));   // by 8
+  }
+  const int r = (threadIdx.x & 63) / C;   // every such lane has all of them: number r leaves column k0 + r
+  uint32_t v = cm[0];
+#pragma unroll
+  for (int e = 1; e < 8; ++e) v = r == e ? cm[e] : v;
+  if (r < 8 && k0 + r < K) atomicMax(col_mx + k0 + r, v);
+}
+// src[row * ld + k]: one workgroup per (block of 128 rows, 8 k steps), everything a thread reads is in flight at once.  NP 3: a
+// lane holds one octet of k of 8 rows, so that the columns' maxima (into col_mx, if given) are mostly the lane's own; else
+// one row's 8 octets, which every part is written of in longer runs.  row_mx: the rows' maxima (NP 3).
 template <int NP>
 __global__ void __launch_bounds__(256) k_pack_x3(const float* __restrict__ src, int ld, int rows, int K, int /*rows_pad*/, int KB,
-                                                 uint4* __restrict__ dst) {
-  const int row = blockIdx.x * 128 + (threadIdx.x >> 1), kh = threadIdx.x & 1;
-  const float* rp = src + (size_t)row * ld;
+                                                 u32x4_t* __restrict__ dst, const uint32_t* __restrict__ row_mx,
+                                                 uint32_t* __restrict__ col_mx) {
+  const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63;
+  auto row_of = [&](int i) { return (int)blockIdx.x * 128 + (NP == 3 ? (lane >> 2) + 16 * i : (int)(threadIdx.x >> 1)); };
+  auto octet_of = [&](int i) { return (int)blockIdx.y * 16 + (NP == 3 ? wave * 4 + (lane & 3) : 2 * i + (lane & 1)); };
   const bool vec = ((ld & 3) == 0) && ((((uintptr_t)src) & 15) == 0);
-  const int kb0 = blockIdx.y * 8, n = min(KB - kb0, 8);
-  if (vec && n == 8 && (kb0 + 8) * 16 <= K && (int)blockIdx.x * 128 + 128 <= rows) {
-    // everything the thread reads is in flight at once
-    float4 v[8][2];
+  float x[8][8];
+  if (vec && ((int)blockIdx.y + 1) * 128 <= K && ((int)blockIdx.x + 1) * 128 <= rows) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      const float* q = rp + (kb0 + i) * 16 + kh * 8;
-      v[i][0] = *(const float4*)q;
-      v[i][1] = *(const float4*)(q + 4);
+      const float* q = src + (size_t)row_of(i) * ld + octet_of(i) * 8;
+      *(float4*)&x[i][0] = *(const float4*)q;
+      *(float4*)&x[i][4] = *(const float4*)(q + 4);
     }
+  } else {
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      const float x[8] = {v[i][0].x, v[i][0].y, v[i][0].z, v[i][0].w, v[i][1].x, v[i][1].y, v[i][1].z, v[i][1].w};
-      x3_store<NP>(dst, KB, row, (kb0 + i) * 2 + kh, x);
+      const int row = row_of(i), k0 = octet_of(i) * 8;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) x[i][j] = (row < rows && k0 + j < K) ? src[(size_t)row * ld + k0 + j] : 0.f;
     }
-    return;
   }
-  for (int kb = kb0; kb < kb0 + n; ++kb) {
-    const int k0 = kb * 16 + kh * 8;
-    float x[8];
-    if (row < rows && k0 + 8 <= K && vec) {
-      const float4 a = *(const float4*)(rp + k0), b = *(const float4*)(rp + k0 + 4);
-      x[0] = a.x; x[1] = a.y; x[2] = a.z; x[3] = a.w; x[4] = b.x; x[5] = b.y; x[6] = b.z; x[7] = b.w;
-    } else {
 #pragma unroll
-      for (int j = 0; j < 8; ++j) x[j] = (row < rows && k0 + j < K) ? rp[k0 + j] : 0.f;
+  for (int i = 0; i < 8; ++i)
+    if (octet_of(i) < KB * 2) x3_store<NP>(dst, KB, row_of(i), octet_of(i), x[i], x3_scale<NP>(row_mx, min(row_of(i), rows - 1)));
+  if (NP == 3 && col_mx && octet_of(0) < KB * 2) {   // padded steps are a multiple of 4 (8 octets): the whole wave
+    uint32_t cm[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      cm[j] = abs_bits(x[0][j]);
+#pragma unroll
+      for (int i = 1; i < 8; ++i) cm[j] = max(cm[j], abs_bits(x[i][j]));
     }
-    x3_store<NP>(dst, KB, row, kb * 2 + kh, x);
+    wave_column_max<4>(cm, col_mx, octet_of(0) * 8, K);
   }
 }
 // src[k * ld + row] (rows contiguous): 64 rows x 64 k per workgroup through LDS
 template <int NP>
 __global__ void __launch_bounds__(256) k_pack_x3_t(const float* __restrict__ src, int ld, int rows, int K, int rows_pad, int KB,
-                                                   uint4* __restrict__ dst) {
+                                                   u32x4_t* __restrict__ dst, const uint32_t* __restrict__ row_mx,
+                                                   uint32_t* __restrict__ /*col_mx*/) {
   __shared__ float tile[64][65];
   const int r0 = blockIdx.x * 64, k0 = blockIdx.y * 64;
   for (int e = threadIdx.x; e < 64 * 64; e += 256) {
@@ -371,19 +433,86 @@ __global__ void __launch_bounds__(256) k_pack_x3_t(const float* __restrict__ src
     float x[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) x[j] = tile[kq * 8 + j][rr];
-    x3_store<NP>(dst, KB, row, k8, x);
+    x3_store<NP>(dst, KB, row, k8, x, x3_scale<NP>(row_mx, min(row, rows - 1)));
   }
 }
 
+// Where a product leaves the maxima of its output's rows and columns (row null: nowhere).  With `half` > 0 the rows have two
+// maxima, of the columns below `half` and behind, `row_pitch` apart (a tile of both counts for both).
+struct OutMax { uint32_t *row, *col; int half; size_t row_pitch; };
+// Maxima of the rows and columns of a product x[M, N] that was added up from parts, N % 64 == 0: 128 rows x 256 columns per workgroup
+__global__ void __launch_bounds__(256) k_matrix_max(const float* __restrict__ x, int M, int N, OutMax out) {
+  const int c = threadIdx.x & 7, m0 = blockIdx.y * 128 + (threadIdx.x >> 3);
+  uint32_t rm[4] = {0, 0, 0, 0};
+  const int n_first = blockIdx.x * 256;
+  for (int n0 = n_first; n0 < min(N, n_first + 256); n0 += 64) {
+    uint32_t cm[8] = {};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (m0 + 32 * i >= M) continue;
+      float v[8];
+      const float* p = x + (size_t)(m0 + 32 * i) * N + n0 + c * 8;
+      *(float4*)v = *(const float4*)p; *(float4*)(v + 4) = *(const float4*)(p + 4);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        cm[e] = max(cm[e], abs_bits(v[e]));
+        rm[i] = max(rm[i], abs_bits(v[e]));
+      }
+    }
+    wave_column_max<8>(cm, out.col, n0 + c * 8, N);
+  }
+  const bool second = out.half > 0 && n_first + 256 > out.half, first = out.half <= 0 || n_first < out.half;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    rm[i] = max(rm[i], (uint32_t)__builtin_amdgcn_mov_dpp((int)rm[i], 0xB1, 0xF, 0xF, true));    // lane ^ 1
+    rm[i] = max(rm[i], (uint32_t)__builtin_amdgcn_mov_dpp((int)rm[i], 0x4E, 0xF, 0xF, true));    // lane ^ 2
+    rm[i] = max(rm[i], (uint32_t)__builtin_amdgcn_mov_dpp((int)rm[i], 0x141, 0xF, 0xF, true));   // lane ^ 7
+    if (c != 0 || m0 + 32 * i >= M) continue;
+    if (first) atomicMax(out.row + m0 + 32 * i, rm[i]);
+    if (second) atomicMax(out.row + out.row_pitch + m0 + 32 * i, rm[i]);
+  }
+}
+// Maxima of the rows of a few matrices [rows, K], contiguous: a wave per row
+constexpr int kRowMaxTasks = 100;
+struct RowMaxTask { const float* src; uint32_t* out; int rows, K; unsigned first_block; };
+struct RowMaxTasks { int n; RowMaxTask t[kRowMaxTasks]; };
+static_assert(sizeof(RowMaxTasks) + 64 <= 4096, "kernel arguments");
+__global__ void __launch_bounds__(256) k_row_max(RowMaxTasks tasks) {
+  int ti = 0;
+  for (int end = tasks.n; end - ti > 1;) {
+    const int mid = (ti + end) >> 1;
+    if (blockIdx.x >= tasks.t[mid].first_block) ti = mid; else end = mid;
+  }
+  const RowMaxTask t = tasks.t[ti];
+  const int lane = threadIdx.x & 63, row = (int)(blockIdx.x - t.first_block) * 4 + wave_index(threadIdx.x);
+  if (row >= t.rows) return;
+  const float* p = t.src + (size_t)row * t.K;
+  uint32_t mx = 0;
+  if ((t.K & 3) == 0 && ((uintptr_t)t.src & 15) == 0) {
+#pragma unroll 4
+    for (int k = lane * 4; k < t.K; k += 256) {
+      const float4 v = *(const float4*)(p + k);
+      mx = max(max(max(mx, abs_bits(v.x)), max(abs_bits(v.y), abs_bits(v.z))), abs_bits(v.w));
+    }
+  } else {
+    for (int k = lane; k < t.K; k += 64) mx = max(mx, abs_bits(p[k]));
+  }
+  mx = wave_max_u32(mx);
+  if (lane == 0) t.out[row] = mx;
+}
+
 // k steps of 16 per stage of the packed GEMM: what keeps a stage at 32 .. 48 MFMAs per wave
-__host__ __device__ constexpr int x3_stage(int NP) { return NP == 3 ? 1 : NP == 2 ? 2 : 4; }
+__host__ __device__ constexpr int x3_stage(int NP) { return NP == 1 ? 4 : 2; }
 
 __host__ __device__ constexpr int x3_tn_stage(int NP) { return NP == 1 ? 2 : 1; }   // of k_gemm_x3_tn
 
-// The A operand's products go out smallest first: (hi lo), (lo hi), (mid mid), (hi mid), (mid hi), (hi hi); two pieces take
-// the last three, one piece the last.
-template <int NP> __device__ __forceinline__ constexpr int x3_terms() { return NP == 3 ? 6 : NP == 2 ? 3 : 1; }
-__device__ constexpr int kTermA[6] = {0, 2, 1, 0, 1, 0}, kTermB[6] = {2, 0, 1, 1, 0, 0};
+// The products go out smallest first: hi lo, lo hi, hi hi; one piece takes the last.
+template <int NP> __device__ __forceinline__ constexpr int x3_terms() { return NP == 1 ? 1 : 3; }
+__device__ constexpr int kTermA[3] = {0, 1, 0}, kTermB[3] = {1, 0, 0};
+template <int NP> __device__ __forceinline__ f32x16_t x3_mfma(const Frag8& a, const Frag8& b, const f32x16_t& c) {
+  if constexpr (NP == 3) return __builtin_amdgcn_mfma_f32_32x32x16_f16(a.h, b.h, c, 0, 0, 0);
+  else return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.v, b.v, c, 0, 0, 0);
+}
 
 // One wave-wide 1 KiB copy global -> LDS / load into registers (base + lane offset), awaited with x3_wait; issued from inline
 // assembly because the compiler would wait for a copy before any LDS read.
@@ -397,24 +526,115 @@ template <int N> __device__ __forceinline__ void x3_wait() {
   __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
 }
 
-// C tile of a wave: TJ x 4 MFMA tiles; accumulator v of lane l: row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32.  A tile
-// without rows or columns past the end is stored without a comparison per value, rows by scalar base addresses.
-template <int TJ>
+// 16 values per lane, all 64 lanes: the maximum of value v over the 32 lanes of a half wave, in the half's lanes with
+// (lane >> 1) % 16 = v.  A swap leaves each 16 lanes half of the values, then every step keeps the half that a bit of the lane
+// names and gives the other to a lane that differs in it.
+__device__ __forceinline__ float max_of_half_wave(const float (&v16)[16]) {
+  const int lane = threadIdx.x & 63;
+  float v8[8], v4[4], v2[2];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const lane_u32x2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v16[i]), __float_as_uint(v16[i + 8]), false, false);
+    v8[i] = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  }
+  auto moved = [](float x, auto ctrl) __attribute__((always_inline)) {
+    return __uint_as_float((uint32_t)__builtin_amdgcn_mov_dpp((int)__float_as_uint(x), decltype(ctrl)::value, 0xF, 0xF, true));
+  };
+#pragma unroll
+  for (int i = 0; i < 4; ++i)   // lane ^ 15
+    v4[i] = fmaxf(lane & 8 ? v8[i + 4] : v8[i], moved(lane & 8 ? v8[i] : v8[i + 4], std::integral_constant<int, 0x140>()));
+#pragma unroll
+  for (int i = 0; i < 2; ++i)   // lane ^ 7
+    v2[i] = fmaxf(lane & 4 ? v4[i + 2] : v4[i], moved(lane & 4 ? v4[i] : v4[i + 2], std::integral_constant<int, 0x141>()));
+  const float v1 = fmaxf(lane & 2 ? v2[1] : v2[0], moved(lane & 2 ? v2[0] : v2[1], std::integral_constant<int, 0x4E>()));   // lane ^ 2
+  return fmaxf(v1, moved(v1, std::integral_constant<int, 0xB1>()));   // lane ^ 1
+}
+
+// C tile of a wave: TJ x 4 MFMA tiles; accumulator v of lane l: row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32.  With
+// NP 3 the operands' scales are taken out of the sums: amx, bmx are their rows' maxima.
+template <bool full> __device__ __forceinline__ void x3_col_exps(int (&eb)[4], const uint32_t* __restrict__ bmx, int n, int N) {
+#pragma unroll
+  for (int j = 0; j < 4; ++j) eb[j] = row_exp(bmx[full ? n + j * 32 : min(n + j * 32, N - 1)]);
+}
+template <bool full> __device__ __forceinline__ void x3_row_exps(int (&ea)[4], const uint32_t* __restrict__ amx, int m, int M) {   // rows m .. m + 3
+  if constexpr (full) {
+    const u32x4_t a = *(const u32x4_t*)(amx + m);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) ea[u] = row_exp(a[u]);
+  } else {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) ea[u] = row_exp(amx[min(m + u, M - 1)]);
+  }
+}
+// The maxima of the tile's rows and columns: about 400 vector instructions a wave, against 1344 MFMAs of 32 cycles at a
+// contraction over 896.
+template <int TJ, bool full>
+__device__ __forceinline__ void x3_tile_max(const f32x16_t (&acc)[TJ][4], const OutMax& out, int row0, int n0, int M, int N,
+                                            const uint32_t* __restrict__ amx, const uint32_t* __restrict__ bmx) {
+  const int lane = threadIdx.x & 63, m_lane = (lane >> 5) * 4;
+  int eb[4];
+  float col[4] = {0.f, 0.f, 0.f, 0.f};
+  x3_col_exps<full>(eb, bmx, n0 + (lane & 31), N);
+#pragma unroll
+  for (int t = 0; t < TJ; ++t) {
+    float row[16];
+#pragma unroll
+    for (int v4 = 0; v4 < 4; ++v4) {
+      const int m = row0 + t * 32 + 8 * v4 + m_lane;
+      int ea[4];
+      x3_row_exps<full>(ea, amx, m, M);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        float a[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          a[j] = fabsf(ldexpf(acc[t][j][4 * v4 + u], ea[u] + eb[j]));
+          if (!full) a[j] = m + u < M ? a[j] : 0.f;   // rows past the end repeat others
+          col[j] = fmaxf(col[j], a[j]);
+        }
+        row[4 * v4 + u] = fmaxf(fmaxf(a[0], a[1]), fmaxf(a[2], a[3]));
+      }
+      asm volatile("" : "+v"(col[0]), "+v"(col[1]), "+v"(col[2]), "+v"(col[3]));
+      __builtin_amdgcn_sched_barrier(0);   // the accumulators fill half of the registers: nothing of a group is kept for later
+    }
+    const float mx = max_of_half_wave(row);
+    const int v = (lane >> 1) & 15, m = row0 + t * 32 + 8 * (v >> 2) + (v & 3) + m_lane;
+    if ((lane & 1) == 0 && (full || m < M)) {
+      if (out.half <= 0 || n0 < out.half) atomicMax(out.row + m, __float_as_uint(mx));
+      if (out.half > 0 && n0 + 128 > out.half) atomicMax(out.row + out.row_pitch + m, __float_as_uint(mx));
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  }
+#pragma unroll
+  for (int j = 0; j < 4; j += 2) {   // the lower 32 lanes take column block j, the upper ones j + 1
+    const lane_u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(col[j]), __float_as_uint(col[j + 1]), false, false);
+    const int c = n0 + j * 32 + lane;
+    if (full || c < N) atomicMax(out.col + c, __float_as_uint(fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]))));
+  }
+}
+// A tile without rows or columns past the end is stored without a comparison per value, rows by scalar base addresses.
+template <int NP, int TJ>
 __device__ __forceinline__ void x3_store_tile(const f32x16_t (&acc)[TJ][4], float* C, const float* Cin, int ldc, int row0, int n0,
-                                              int M, int N, float beta) {
+                                              int M, int N, float beta, const uint32_t* __restrict__ amx,
+                                              const uint32_t* __restrict__ bmx) {
   const int lane = threadIdx.x & 63;
   auto store = [&](auto full_c, auto beta_c) __attribute__((always_inline)) {
     constexpr bool full = decltype(full_c)::value, add = decltype(beta_c)::value;
     const unsigned off = (unsigned)((lane >> 5) * 4 * ldc + n0 + (lane & 31)) * 4u;   // bytes behind the base of a row pair
     const int m_lane = (lane >> 5) * 4, n = n0 + (lane & 31);
     const ptrdiff_t d_in = (const char*)Cin - (const char*)C;
+    int eb[4];
+    if constexpr (NP == 3) x3_col_exps<full>(eb, bmx, n, N);
 #pragma unroll
     for (int t = 0; t < TJ; ++t)
 #pragma unroll
       for (int v4 = 0; v4 < 4; ++v4) {
+        const int m0 = row0 + t * 32 + 8 * v4;
         char* base[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) base[u] = (char*)(C + (size_t)(row0 + t * 32 + 8 * v4 + u) * ldc);
+        for (int u = 0; u < 4; ++u) base[u] = (char*)(C + (size_t)(m0 + u) * ldc);
+        int ea[4];
+        if constexpr (NP == 3) x3_row_exps<full>(ea, amx, m0 + m_lane, M);
         float old[4][4];
         if constexpr (add) {
 #pragma unroll
@@ -422,15 +642,17 @@ __device__ __forceinline__ void x3_store_tile(const f32x16_t (&acc)[TJ][4], floa
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
               old[u][j] = 0.f;
-              if (full || (row0 + t * 32 + 8 * v4 + u + m_lane < M && n + j * 32 < N)) old[u][j] = *(const float*)(base[u] + d_in + off + j * 128);
+              if (full || (m0 + u + m_lane < M && n + j * 32 < N)) old[u][j] = *(const float*)(base[u] + d_in + off + j * 128);
             }
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u)
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
-            const float r = add ? fmaf(beta, old[u][j], acc[t][j][4 * v4 + u]) : acc[t][j][4 * v4 + u];
-            if (full || (row0 + t * 32 + 8 * v4 + u + m_lane < M && n + j * 32 < N)) *(float*)(base[u] + off + j * 128) = r;
+            float r = acc[t][j][4 * v4 + u];
+            if constexpr (NP == 3) r = ldexpf(r, ea[u] + eb[j]);
+            if constexpr (add) r = fmaf(beta, old[u][j], r);
+            if (full || (m0 + u + m_lane < M && n + j * 32 < N)) *(float*)(base[u] + off + j * 128) = r;
           }
       }
   };
@@ -451,8 +673,9 @@ __device__ __forceinline__ void x3_store_tile(const f32x16_t (&acc)[TJ][4], floa
 template <int NP, int TJ>
 __global__ void __launch_bounds__(256, TJ == 2 ? 2 : 3) k_gemm_x3(const u32x4_t* __restrict__ Ap, const u32x4_t* __restrict__ Bp,
                                                                   float* C, const float* Cin, int ldc, int M, int N, int KB,
-                                                                  float beta, int kb_split, size_t c_split) {
-  constexpr int H = x3_stage(NP), NF = H * NP;     // ring copies per wave and stage; fragments of a column block
+                                                                  float beta, int kb_split, size_t c_split,
+                                                                  const uint32_t* amx, const uint32_t* bmx, OutMax out_mx) {
+  constexpr int PC = x3_parts(NP), H = x3_stage(NP), NF = H * PC;     // ring copies per wave and stage; fragments of a column block
   constexpr int PER = NF + NF * TJ;                // requests per wave and stage
   constexpr int kRing = 3;
   __shared__ u32x4_t ring[kRing * NF * 4 * 64];
@@ -465,8 +688,8 @@ __global__ void __launch_bounds__(256, TJ == 2 ? 2 : 3) k_gemm_x3(const u32x4_t*
   C += (size_t)blockIdx.z * c_split;
   const int row_w = wave * 32 * TJ;                // this wave's rows of the tile
   // a tile's last row block may not exist: it repeats the previous one and is not stored
-  const char* xbase = (const char*)(Ap + ((size_t)min(ty * TJ + (row_w >> 7), n_rb - 1) * KB + t0) * (NP * 256) + (row_w & 127));
-  const char* wbase = (const char*)(Bp + ((size_t)tx * KB + t0) * (NP * 256) + wave * 32);
+  const char* xbase = (const char*)(Ap + ((size_t)min(ty * TJ + (row_w >> 7), n_rb - 1) * KB + t0) * (PC * 256) + (row_w & 127));
+  const char* wbase = (const char*)(Bp + ((size_t)tx * KB + t0) * (PC * 256) + wave * 32);
   const unsigned off = ((lane >> 5) * 128 + (lane & 31)) * 16;
   const unsigned lds0 =
       __builtin_amdgcn_readfirstlane((unsigned)(size_t)(const __attribute__((address_space(3))) void*)ring) + wave * 1024u;
@@ -478,7 +701,7 @@ __global__ void __launch_bounds__(256, TJ == 2 ? 2 : 3) k_gemm_x3(const u32x4_t*
     for (int j = 0; j < 4; ++j)
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[t][j][v] = 0.f;
-  // fragment i = (k step of the stage) * NP + piece: a 4 KiB step of the packed operand
+  // fragment i = (k step of the stage) * PC + part: a 4 KiB step of the packed operand
   auto request_w = [&](int i, int st) { x3_dma(wbase + ((size_t)st * NF + i) * 4096, off, lds0 + ((st % kRing) * NF + i) * 4096u); };
   auto request_x = [&](u32x4_t (&dst)[TJ], int i, int st) {
     const char* b = xbase + ((size_t)st * NF + i) * 4096;
@@ -505,20 +728,20 @@ __global__ void __launch_bounds__(256, TJ == 2 ? 2 : 3) k_gemm_x3(const u32x4_t*
     const u32x4_t* buf = ring + (st % kRing) * (NF * 4 * 64) + lane;
 #pragma unroll
     for (int h = 0; h < H; ++h) {
-      Frag8 b[4][NP];
+      Frag8 b[4][PC];
 #pragma unroll
       for (int j = 0; j < 4; ++j)
 #pragma unroll
-        for (int q = 0; q < NP; ++q) b[j][q].u = buf[((h * NP + q) * 4 + j) * 64];
+        for (int q = 0; q < PC; ++q) b[j][q].u = buf[((h * PC + q) * 4 + j) * 64];
       __builtin_amdgcn_s_setprio(1);
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
 #pragma unroll
-        for (int term = 6 - x3_terms<NP>(); term < 6; ++term)
+        for (int term = 3 - x3_terms<NP>(); term < 3; ++term)
 #pragma unroll
           for (int t = 0; t < TJ; ++t) {
-            Frag8 a; a.u = x[P][h * NP + kTermA[term]][t];
-            acc[t][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.v, b[j][kTermB[term]].v, acc[t][j], 0, 0, 0);
+            Frag8 a; a.u = x[P][h * PC + kTermA[term]][t];
+            acc[t][j] = x3_mfma<NP>(a, b[j][kTermB[term]], acc[t][j]);
           }
         if (h * 4 + j < NF) {   // the next-but-one stage's copies go out between the MFMAs, not in one burst
           __builtin_amdgcn_sched_barrier(0);
@@ -530,7 +753,7 @@ __global__ void __launch_bounds__(256, TJ == 2 ? 2 : 3) k_gemm_x3(const u32x4_t*
       __builtin_amdgcn_sched_barrier(0);
       if (more) {
 #pragma unroll
-        for (int q = 0; q < NP; ++q) request_x(x[P][h * NP + q], h * NP + q, st + 2);
+        for (int q = 0; q < PC; ++q) request_x(x[P][h * PC + q], h * PC + q, st + 2);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
@@ -541,7 +764,13 @@ __global__ void __launch_bounds__(256, TJ == 2 ? 2 : 3) k_gemm_x3(const u32x4_t*
     stage(std::integral_constant<int, 1>(), st + 1);
   }
   if (st < nst) stage(std::integral_constant<int, 0>(), st);
-  x3_store_tile<TJ>(acc, C, Cin, ldc, ty * kGM * TJ + row_w, tx * kGM, M, N, beta);
+  int row0 = ty * kGM * TJ + row_w, n0 = tx * kGM;
+  if (NP == 3 && out_mx.row) {
+    if (row0 + 32 * TJ <= M && n0 + 128 <= N) x3_tile_max<TJ, true>(acc, out_mx, row0, n0, M, N, amx, bmx);
+    else x3_tile_max<TJ, false>(acc, out_mx, row0, n0, M, N, amx, bmx);
+    asm volatile("" : "+s"(amx), "+s"(bmx), "+s"(row0), "+s"(n0));   // what both passes compute is not kept between them: no registers
+  }
+  x3_store_tile<NP, TJ>(acc, C, Cin, ldc, row0, n0, M, N, beta, amx, bmx);
 }
 
 // f(0), f(1), ... f(N - 1) with the index as a compile-time constant
@@ -549,30 +778,6 @@ template <typename F, int... I> __device__ __forceinline__ void each_of(F&& f, s
   (f(std::integral_constant<int, I>()), ...);
 }
 template <int N, typename F> __device__ __forceinline__ void each(F&& f) { each_of(f, std::make_integer_sequence<int, N>()); }
-
-// bf16 pieces of 8 values as MFMA fragments (the cut of x3_store)
-template <int NP> __device__ __forceinline__ void x3_cut(const float (&x)[8], Frag8 (&f)[NP]) {
-  if constexpr (NP == 3) {
-    float r[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) r[e] = x[e];
-#pragma unroll
-    for (int q = 0; q < 3; ++q)
-#pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        f[q].u[w] = __builtin_amdgcn_perm(__float_as_uint(r[2 * w + 1]), __float_as_uint(r[2 * w]), 0x07060302u);   // the high halves
-        r[2 * w] -= __uint_as_float(__float_as_uint(r[2 * w]) & 0xFFFF0000u);
-        r[2 * w + 1] -= __uint_as_float(__float_as_uint(r[2 * w + 1]) & 0xFFFF0000u);
-      }
-  } else {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const __bf16 hi = (__bf16)x[e];   // round to nearest even
-      f[0].v[e] = hi;
-      if constexpr (NP == 2) f[1].v[e] = (__bf16)(x[e] - (float)hi);
-    }
-  }
-}
 
 // C[M, N] = beta C + A^T B with A [K, M] (lda) and B [K, N] (ldb) in fp32 as they lie (weight gradients: K counts tokens):
 // the operands are cut into pieces on the way in.  Packing them first cost a read of 4 and a write and read of 2 NP bytes
@@ -583,9 +788,10 @@ template <int NP> __device__ __forceinline__ void x3_cut(const float (&x)[8], Fr
 template <int NP, int TJ>
 __global__ void __launch_bounds__(256, TJ == 2 ? 2 : 3) k_gemm_x3_tn(const float* __restrict__ A, int lda, const float* __restrict__ B,
                                                                      int ldb, float* C, int ldc, int M, int N, int K, float beta,
-                                                                     int k_split, size_t c_split) {
-  constexpr int H = x3_tn_stage(NP), kTasks = H * (TJ + 1), KS = 16 * H;
-  __shared__ u32x4_t Bs[2][H * NP * 4 * 64];
+                                                                     int k_split, size_t c_split, const uint32_t* __restrict__ amx,
+                                                                     const uint32_t* __restrict__ bmx) {
+  constexpr int PC = x3_parts(NP), H = x3_tn_stage(NP), kTasks = H * (TJ + 1), KS = 16 * H;
+  __shared__ u32x4_t Bs[2][H * PC * 4 * 64];
   const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63, kh = lane >> 5, c = lane & 31;
   int tx, ty;
   if (!raster_tile((N + kGM - 1) / kGM, (M + kGM * TJ - 1) / (kGM * TJ), tx, ty)) return;
@@ -603,6 +809,10 @@ __global__ void __launch_bounds__(256, TJ == 2 ? 2 : 3) k_gemm_x3_tn(const float
 #pragma unroll
   for (int t = 0; t < TJ; ++t) aoff[t] = (unsigned)(kh * 8 * lda + arow[t]) * 4u;
   const unsigned boff = (unsigned)(kh * 8 * ldb + bcol) * 4u;
+  float ascale[TJ];
+#pragma unroll
+  for (int t = 0; t < TJ; ++t) ascale[t] = x3_scale<NP>(amx, (int)arow[t]);
+  const float bscale = x3_scale<NP>(bmx, (int)bcol);
   // Task i of a stage: fragment i % (TJ + 1) of k step i / (TJ + 1); the last fragment is the wave's part of B.
   float raw[kTasks][8];
   auto request = [&](auto ic, int s) __attribute__((always_inline)) {
@@ -614,16 +824,16 @@ __global__ void __launch_bounds__(256, TJ == 2 ? 2 : 3) k_gemm_x3_tn(const float
       else raw[i][e] = *(const float*)((const char*)(B + (k + e) * ldb) + boff);
     }
   };
-  Frag8 a[2][H][TJ][NP];
+  Frag8 a[2][H][TJ][PC];
   auto cut = [&](auto ic, auto pc) __attribute__((always_inline)) {
     constexpr int i = decltype(ic)::value, h = i / (TJ + 1), t = i % (TJ + 1), p = decltype(pc)::value;
     if constexpr (t < TJ) {
-      x3_cut<NP>(raw[i], a[p][h][t]);
+      x3_cut<NP>(raw[i], ascale[t], a[p][h][t]);
     } else {
-      Frag8 b[NP];
-      x3_cut<NP>(raw[i], b);
+      Frag8 b[PC];
+      x3_cut<NP>(raw[i], bscale, b);
 #pragma unroll
-      for (int q = 0; q < NP; ++q) Bs[p][((h * NP + q) * 4 + wave) * 64 + lane] = b[q].u;
+      for (int q = 0; q < PC; ++q) Bs[p][((h * PC + q) * 4 + wave) * 64 + lane] = b[q].u;
     }
   };
   f32x16_t acc[TJ][4];
@@ -639,14 +849,13 @@ __global__ void __launch_bounds__(256, TJ == 2 ? 2 : 3) k_gemm_x3_tn(const float
     const u32x4_t* buf = Bs[P] + lane;
     each<H * 4>([&](auto slot_c) __attribute__((always_inline)) {
       constexpr int slot = decltype(slot_c)::value, h = slot >> 2, j = slot & 3;
-      Frag8 b[NP];
+      Frag8 b[PC];
 #pragma unroll
-      for (int q = 0; q < NP; ++q) b[q].u = buf[((h * NP + q) * 4 + j) * 64];
+      for (int q = 0; q < PC; ++q) b[q].u = buf[((h * PC + q) * 4 + j) * 64];
 #pragma unroll
-      for (int term = 6 - x3_terms<NP>(); term < 6; ++term)
+      for (int term = 3 - x3_terms<NP>(); term < 3; ++term)
 #pragma unroll
-        for (int t = 0; t < TJ; ++t)
-          acc[t][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[P][h][t][kTermA[term]].v, b[kTermB[term]].v, acc[t][j], 0, 0, 0);
+        for (int t = 0; t < TJ; ++t) acc[t][j] = x3_mfma<NP>(a[P][h][t][kTermA[term]], b[kTermB[term]], acc[t][j]);
       if constexpr (slot < kTasks && !last) {
         cut(slot_c, std::integral_constant<int, P ^ 1>());
         request(slot_c, s + 2);
@@ -654,7 +863,7 @@ __global__ void __launch_bounds__(256, TJ == 2 ? 2 : 3) k_gemm_x3_tn(const float
 #pragma unroll
         for (int m = 0; m < x3_terms<NP>() * TJ; ++m) {
           __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x2, NP == 3 ? 48 / (6 * TJ) : 24 / (x3_terms<NP>() * TJ), 0);
+          __builtin_amdgcn_sched_group_barrier(0x2, (NP == 3 ? 48 : 24) / (x3_terms<NP>() * TJ), 0);
         }
       }
       __builtin_amdgcn_sched_barrier(0);
@@ -685,25 +894,30 @@ __global__ void __launch_bounds__(256, TJ == 2 ? 2 : 3) k_gemm_x3_tn(const float
     stage(odd, std::false_type(), s + 1);
   }
   if (s < nst) stage(even, std::true_type(), s);
-  x3_store_tile<TJ>(acc, C, C, ldc, row0, tx * kGM, M, N, beta);
+  x3_store_tile<NP, TJ>(acc, C, C, ldc, row0, tx * kGM, M, N, beta, amx, bmx);
 }
 
-// One operand of a packed GEMM: `rows` x K values at src[row * ld + k], or src[k * ld + row] when `trans`.
-struct X3Op { const float* src; int ld, rows, K; bool trans; };
+// One operand of a packed GEMM: `rows` x K values at src[row * ld + k], or src[k * ld + row] when `trans`; the maxima of its
+// rows, and where packing it by rows leaves those of its columns (both: NP 3 only).
+struct X3Op { const float* src; int ld, rows, K; bool trans; const uint32_t* row_mx; uint32_t* col_mx; };
 inline size_t x3_pack_bytes(int NP, size_t rows, size_t K) {
-  return ((rows + 127) / 128 * 128) * ((K + 63) / 64 * 64) * 2 * NP;
+  return ((rows + 127) / 128 * 128) * ((K + 63) / 64 * 64) * 2 * x3_parts(NP);
 }
-inline int x3_steps(int K, int NP) { const int k = 16 * x3_stage(NP); return (K + k - 1) / k * x3_stage(NP); }   // padded k steps
+inline int x3_steps(int K) { return (K + 63) / 64 * 4; }   // padded k steps: whole stages, whole waves of the packing
 struct X3Bufs { void* a; void* b; size_t a_cap, b_cap; int NP; float* parts; size_t parts_cap; };
 __global__ void k_sum_parts(const float* __restrict__ part, int n_part, size_t n, float beta, const float* in, float* out);
 
+hipError_t matrix_max(const float* x, int M, int N, const OutMax& out, hipStream_t st) {
+  return launch(KID_MISC, k_matrix_max, dim3((N + 255) / 256, (M + 127) / 128), dim3(256), 0, st, x, M, N, out);
+}
 hipError_t x3_pack(const X3Op& op, void* dst, size_t cap, int NP, hipStream_t st) {
   if (x3_pack_bytes(NP, op.rows, op.K) > cap) return hipErrorInvalidValue;
-  const int rows_pad = (op.rows + 127) / 128 * 128, KB = x3_steps(op.K, NP);
+  const int rows_pad = (op.rows + 127) / 128 * 128, KB = x3_steps(op.K);
   const dim3 grid = op.trans ? dim3(rows_pad / 64, (KB * 16 + 63) / 64) : dim3(rows_pad / 128, (KB + 7) / 8);
   auto go = [&](auto kernel) {
-    return launch(KID_MISC, kernel, grid, dim3(256), 0, st, op.src, op.ld, op.rows, op.K, rows_pad, KB, (uint4*)dst);
+    return launch(KID_MISC, kernel, grid, dim3(256), 0, st, op.src, op.ld, op.rows, op.K, rows_pad, KB, (u32x4_t*)dst, op.row_mx, op.col_mx);
   };
+  if (NP == 3 && !op.row_mx) return hipErrorInvalidValue;
   if (op.trans) return NP == 3 ? go(k_pack_x3_t<3>) : NP == 2 ? go(k_pack_x3_t<2>) : go(k_pack_x3_t<1>);
   return NP == 3 ? go(k_pack_x3<3>) : NP == 2 ? go(k_pack_x3<2>) : go(k_pack_x3<1>);
 }
@@ -720,38 +934,43 @@ hipError_t x3_sum_parts(const X3Bufs& bufs, int splits, size_t n, float beta, co
 // C[M, N] = beta C + op(A) op(B)^T-style product of two operands given row-wise over the same K; an operand packed earlier
 // (a_packed, b_packed) is used as it is
 hipError_t gemm_x3(const X3Op& A, const X3Op& B, float* C, const float* Cin, int ldc, float beta, const X3Bufs& bufs, hipStream_t st,
-                   const void* b_packed = nullptr, bool split_ok = true, const void* a_packed = nullptr) {
-  if (A.K != B.K || A.rows <= 0 || B.rows <= 0 || A.K <= 0) return hipErrorInvalidValue;
+                   const void* b_packed = nullptr, bool split_ok = true, const void* a_packed = nullptr,
+                   const OutMax& out_mx = OutMax{}) {
+  if (out_mx.row && beta != 0.f) return hipErrorInvalidValue;   // maxima are those of the product
+  if (A.K != B.K || A.rows <= 0 || B.rows <= 0 || A.K <= 0 || (bufs.NP == 3 && (!A.row_mx || !B.row_mx))) return hipErrorInvalidValue;
   hipError_t e;
   if (!a_packed && (e = x3_pack(A, bufs.a, bufs.a_cap, bufs.NP, st)) != hipSuccess) return e;
   if (!b_packed && (e = x3_pack(B, bufs.b, bufs.b_cap, bufs.NP, st)) != hipSuccess) return e;
   const u32x4_t* pa_ = (const u32x4_t*)(a_packed ? a_packed : bufs.a);
   const u32x4_t* pb_ = (const u32x4_t*)(b_packed ? b_packed : bufs.b);
-  const int KB = x3_steps(A.K, bufs.NP);
+  const int KB = x3_steps(A.K);
   const X3Grid g = x3_grid(bufs.NP, A.rows, B.rows, KB, x3_stage(bufs.NP), split_ok && ldc == B.rows ? bufs.parts_cap : 0);
   float* out = g.splits > 1 ? bufs.parts : C;
   const size_t c_split = g.splits > 1 ? (size_t)A.rows * B.rows : 0;
   const float b_ = g.splits > 1 ? 0.f : beta;
   auto go = [&](auto kernel) {
-    return launch(KID_GEMM_GENERIC, kernel, g.grid, dim3(256), 0, st, pa_, pb_, out, Cin, ldc, A.rows, B.rows, KB, b_, g.per_split, c_split);
+    return launch(KID_GEMM_GENERIC, kernel, g.grid, dim3(256), 0, st, pa_, pb_, out, Cin, ldc, A.rows, B.rows, KB, b_, g.per_split, c_split,
+                  A.row_mx, B.row_mx, g.splits > 1 ? OutMax{} : out_mx);
   };
   if (bufs.NP == 3) e = g.TJ == 2 ? go(k_gemm_x3<3, 2>) : go(k_gemm_x3<3, 1>);
   else if (bufs.NP == 2) e = g.TJ == 2 ? go(k_gemm_x3<2, 2>) : go(k_gemm_x3<2, 1>);
   else e = g.TJ == 2 ? go(k_gemm_x3<1, 2>) : go(k_gemm_x3<1, 1>);
   if (e != hipSuccess || g.splits == 1) return e;
-  return x3_sum_parts(bufs, g.splits, (size_t)A.rows * B.rows, beta, Cin, C, st);
+  e = x3_sum_parts(bufs, g.splits, (size_t)A.rows * B.rows, beta, Cin, C, st);
+  return e != hipSuccess || !out_mx.row ? e : matrix_max(C, A.rows, B.rows, out_mx, st);
 }
 // C[M, N] = beta C + A^T B, A [K, M] and B [K, N] in fp32
 hipError_t gemm_x3_tn(const float* A, int lda, const float* B, int ldb, float* C, int M, int N, int K, float beta,
-                      const X3Bufs& bufs, hipStream_t st) {
-  if (M <= 0 || N <= 0 || K <= 0) return hipErrorInvalidValue;
+                      const X3Bufs& bufs, hipStream_t st, const uint32_t* amx, const uint32_t* bmx) {   // maxima of their columns
+  if (M <= 0 || N <= 0 || K <= 0 || (bufs.NP == 3 && (!amx || !bmx))) return hipErrorInvalidValue;
   const int KB = (K + 15) / 16;
   const X3Grid g = x3_grid(bufs.NP, M, N, KB, x3_tn_stage(bufs.NP), bufs.parts_cap);
   float* out = g.splits > 1 ? bufs.parts : C;
   const size_t c_split = g.splits > 1 ? (size_t)M * N : 0;
   const float b_ = g.splits > 1 ? 0.f : beta;
   auto go = [&](auto kernel) {
-    return launch(KID_GEMM_GENERIC, kernel, g.grid, dim3(256), 0, st, A, lda, B, ldb, out, N, M, N, K, b_, g.per_split * 16, c_split);
+    return launch(KID_GEMM_GENERIC, kernel, g.grid, dim3(256), 0, st, A, lda, B, ldb, out, N, M, N, K, b_, g.per_split * 16, c_split,
+                  amx, bmx);
   };
   hipError_t e;
   if (bufs.NP == 3) e = g.TJ == 2 ? go(k_gemm_x3_tn<3, 2>) : go(k_gemm_x3_tn<3, 1>);
@@ -861,7 +1080,8 @@ inline bool norm_rows_vectorised(int d) { return d % 4 == 0 && d <= 256 * kNormM
 // that rows of any width see the same rounding: with bf16 operands a last bit of rstd decides roundings downstream.
 template <int NV>
 __global__ void __launch_bounds__(256) k_rmsnorm_fwd_rows(const float* __restrict__ h, const float* __restrict__ gain, float eps,
-                                                          int M, int d, float* __restrict__ xn, float* __restrict__ rstd) {
+                                                          int M, int d, float* __restrict__ xn, float* __restrict__ rstd,
+                                                          uint32_t* __restrict__ row_mx) {
   const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63;
   const size_t m = (size_t)blockIdx.x * 4 + wave;
   if (m >= (size_t)M) return;
@@ -875,11 +1095,19 @@ __global__ void __launch_bounds__(256) k_rmsnorm_fwd_rows(const float* __restric
 #pragma unroll
   for (int c = 0; c < 4; ++c) ss[c] = wave_reduce_sum(ss[c]);
   const float r = 1.0f / sqrtf((ss[0] + ss[1] + ss[2] + ss[3]) / (float)d + eps);
-  if (lane == 0) rstd[m] = r;
 #pragma unroll
   for (int i = 0; i < 4 * NV; ++i) {
     const int f = lane + 64 * i;
-    if (f < d) xn[m * d + f] = x[i] * r * gain[f];
+    x[i] = x[i] * r * (f < d ? gain[f] : 0.f);
+    if (f < d) xn[m * d + f] = x[i];
+  }
+  if (lane == 0) rstd[m] = r;
+  if (row_mx) {
+    uint32_t mx = 0;
+#pragma unroll
+    for (int i = 0; i < 4 * NV; ++i) mx = max(mx, abs_bits(x[i]));
+    mx = wave_max_u32(mx);
+    if (lane == 0) row_mx[m] = mx;
   }
 }
 // Backward of the norm and the gain's gradient in one pass over dxn and h (in two they took 209 us per norm at 24576 rows
@@ -890,7 +1118,8 @@ constexpr int kNormRows = 32;
 template <int NV>
 __global__ void __launch_bounds__(256) k_rmsnorm_bwd_rows(const float* __restrict__ dxn, const float* __restrict__ h,
                                                           const float* __restrict__ rstd, const float* __restrict__ gain, int M,
-                                                          int d, float* __restrict__ dh, int accumulate, float* __restrict__ part) {
+                                                          int d, float* __restrict__ dh, int accumulate, float* __restrict__ part,
+                                                          uint32_t* __restrict__ row_mx) {
   __shared__ float4 red[4][NV * 64];
   const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63;
   float4 g[NV], dg[NV];
@@ -920,15 +1149,22 @@ __global__ void __launch_bounds__(256) k_rmsnorm_bwd_rows(const float* __restric
       dot = fmaf(x[i].x * g[i].x, y[i].x, fmaf(x[i].y * g[i].y, y[i].y, fmaf(x[i].z * g[i].z, y[i].z, fmaf(x[i].w * g[i].w, y[i].w, dot))));
     dot = wave_reduce_sum(dot);
     const float r = rstd[m], c = r * r * r * dot / (float)d;
+    uint32_t mx = 0;
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
       const int f = 4 * (lane + 64 * i);
       dg[i].x = fmaf(x[i].x * y[i].x, r, dg[i].x); dg[i].y = fmaf(x[i].y * y[i].y, r, dg[i].y);
       dg[i].z = fmaf(x[i].z * y[i].z, r, dg[i].z); dg[i].w = fmaf(x[i].w * y[i].w, r, dg[i].w);
-      if (f < d)
-        *(float4*)(dh + (size_t)m * d + f) =
-            make_float4(o[i].x + (r * g[i].x * x[i].x - c * y[i].x), o[i].y + (r * g[i].y * x[i].y - c * y[i].y),
-                        o[i].z + (r * g[i].z * x[i].z - c * y[i].z), o[i].w + (r * g[i].w * x[i].w - c * y[i].w));
+      if (f < d) {
+        const float4 v = make_float4(o[i].x + (r * g[i].x * x[i].x - c * y[i].x), o[i].y + (r * g[i].y * x[i].y - c * y[i].y),
+                                     o[i].z + (r * g[i].z * x[i].z - c * y[i].z), o[i].w + (r * g[i].w * x[i].w - c * y[i].w));
+        *(float4*)(dh + (size_t)m * d + f) = v;
+        mx = max(max(max(mx, abs_bits(v.x)), max(abs_bits(v.y), abs_bits(v.z))), abs_bits(v.w));
+      }
+    }
+    if (row_mx) {
+      mx = wave_max_u32(mx);
+      if (lane == 0) row_mx[m] = mx;
     }
   }
 #pragma unroll
@@ -978,11 +1214,20 @@ template <typename F> hipError_t with_norm_width(int d, F&& f) {   // f(number o
   if (d <= 1024) return f(std::integral_constant<int, 4>());
   return f(std::integral_constant<int, kNormMaxV>());
 }
-hipError_t rmsnorm_fwd(const float* h, const float* gain, float eps, int M, int d, float* xn, float* rstd, hipStream_t st) {
-  if (!norm_rows_vectorised(d))
-    return launch(KID_RMSNORM, k_rmsnorm_fwd, dim3(M), dim3(256), 0, st, h, gain, eps, d, xn, rstd);
+hipError_t row_max(const float* x, int rows, int K, uint32_t* out, hipStream_t st) {   // of a matrix whose writer does not leave them
+  RowMaxTasks t;
+  t.n = 1;
+  t.t[0] = RowMaxTask{x, out, rows, K, 0};
+  return launch(KID_MISC, k_row_max, dim3((rows + 3) / 4), dim3(256), 0, st, t);
+}
+hipError_t rmsnorm_fwd(const float* h, const float* gain, float eps, int M, int d, float* xn, float* rstd, uint32_t* row_mx, hipStream_t st) {
+  if (!norm_rows_vectorised(d)) {
+    const hipError_t e = launch(KID_RMSNORM, k_rmsnorm_fwd, dim3(M), dim3(256), 0, st, h, gain, eps, d, xn, rstd);
+    return e != hipSuccess || !row_mx ? e : row_max(xn, M, d, row_mx, st);
+  }
   return with_norm_width(d, [&](auto nv) {
-    return launch(KID_RMSNORM, k_rmsnorm_fwd_rows<decltype(nv)::value>, dim3((M + 3) / 4), dim3(256), 0, st, h, gain, eps, M, d, xn, rstd);
+    return launch(KID_RMSNORM, k_rmsnorm_fwd_rows<decltype(nv)::value>, dim3((M + 3) / 4), dim3(256), 0, st, h, gain, eps, M, d, xn, rstd,
+                  row_mx);
   });
 }
 
@@ -1043,14 +1288,22 @@ __global__ void k_swiglu_fwd4(const float* __restrict__ gu, float* __restrict__ 
 }
 // The same straight into the packed operand of the down projection, F % 64 == 0: act itself is not stored (the backward pass
 // makes its other packed form again, k_swiglu_bwd_pack).  64 tokens x 64 features per workgroup, bound by its bytes.  us a
-// layer of the 0.5B decoder for act and its packing before, and now: 64 x 384 tokens, three pieces 265 + 230, 329 (5.1 TB/s);
-// 21 x 301 tokens, one piece 61 + 39, 52 (5.9 TB/s).
+// layer of the 0.5B decoder for act and its packing before, and now: 21 x 301 tokens, one piece 61 + 39, 52 (5.9 TB/s).
 template <int NP>
-__global__ void __launch_bounds__(256) k_swiglu_fwd_pack(const float* __restrict__ gu, int M, int F, int KB, uint4* __restrict__ dst) {
+__global__ void __launch_bounds__(256) k_swiglu_fwd_pack(const float* __restrict__ gu, int M, int F, int KB, u32x4_t* __restrict__ dst,
+                                                         const uint32_t* __restrict__ gate_mx, const uint32_t* __restrict__ up_mx,
+                                                         uint32_t* __restrict__ row_mx) {
   const int f0 = blockIdx.x * 64, m0 = blockIdx.y * 64;
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     const int c = (threadIdx.x & 7) * 8, m = m0 + (threadIdx.x >> 3) + 32 * i;
+    uint32_t mx = 0;   // |silu(g)| <= |g|
+    if constexpr (NP == 3) {
+      if (m < M) {
+        mx = product_bound(gate_mx[m], up_mx[m], 1.f);
+        if (f0 + c == 0) row_mx[m] = mx;
+      }
+    }
     float x[8];
     if (m < M) {
       const float* gp = gu + (size_t)m * 2 * F + f0 + c;
@@ -1063,7 +1316,7 @@ __global__ void __launch_bounds__(256) k_swiglu_fwd_pack(const float* __restrict
 #pragma unroll
       for (int e = 0; e < 8; ++e) x[e] = 0.f;
     }
-    x3_store<NP>(dst, KB, m, (f0 + c) >> 3, x);
+    x3_store<NP>(dst, KB, m, (f0 + c) >> 3, x, row_scale(mx));
   }
 }
 __global__ void k_swiglu_fwd(const float* __restrict__ gu, float* __restrict__ act, int F, size_t total) {
@@ -1102,15 +1355,17 @@ __global__ void __launch_bounds__(kLogpThreads) k_logp_dlogits(float* __restrict
                                                                const int32_t* __restrict__ tokens, const uint8_t* __restrict__ mask,
                                                                const float* __restrict__ logp_old, const float* __restrict__ adv,
                                                                float eps_low, float eps_high, const long long* __restrict__ n_masked,
-                                                               float* __restrict__ logp_new) {
+                                                               float* __restrict__ logp_new, uint32_t* __restrict__ row_mx) {
   constexpr int NT = kLogpThreads;
   __shared__ float red_m[NT / 64], red_l[NT / 64];
+  __shared__ uint32_t red_x[NT / 64];
   const int r = rows[blockIdx.x];
   const int t = r % T;
   float* z = logits + (size_t)blockIdx.x * V;
   const int V4 = (V & 3) == 0 ? V >> 2 : 0;   // rows of whole float4s (the buffer is aligned), else value by value
   if (t == T - 1 || !mask[r + 1]) {   // not in a well-formed list; uniform over the workgroup
     for (int v = threadIdx.x; v < V; v += NT) z[v] = 0.f;
+    if (threadIdx.x == 0) row_mx[blockIdx.x] = 0;
     return;
   }
   float m = -INFINITY, l = 0.f;
@@ -1153,7 +1408,12 @@ __global__ void __launch_bounds__(kLogpThreads) k_logp_dlogits(float* __restrict
   const float w = surrogate_dlogp(a, rho, active, *n_masked);
   __syncthreads();   // every thread has read z[target]
   if (threadIdx.x == 0) logp_new[r + 1] = lp;
-  auto grad = [&](float x, int v) { return w == 0.f ? 0.f : w * ((v == target ? 1.f : 0.f) - expf(x - lse)); };
+  uint32_t gmax = 0;
+  auto grad = [&](float x, int v) {
+    const float g = w == 0.f ? 0.f : w * ((v == target ? 1.f : 0.f) - expf(x - lse));
+    gmax = max(gmax, abs_bits(g));
+    return g;
+  };
   if (V4) {
     for (int v0 = threadIdx.x; v0 < V4; v0 += 4 * NT) {
       float4 x[4];
@@ -1168,15 +1428,26 @@ __global__ void __launch_bounds__(kLogpThreads) k_logp_dlogits(float* __restrict
   } else {
     for (int v = threadIdx.x; v < V; v += NT) z[v] = grad(z[v], v);
   }
+  gmax = wave_max_u32(gmax);
+  if ((threadIdx.x & 63) == 0) red_x[threadIdx.x >> 6] = gmax;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int w_ = 1; w_ < NT / 64; ++w_) gmax = max(gmax, red_x[w_]);
+    row_mx[blockIdx.x] = gmax;
+  }
 }
 
-// dst[k] = src[rows[k]] (gather) or dst[rows[k]] = src[k] (scatter): rows of d floats, one workgroup per listed row
+// dst[k] = src[rows[k]] (gather; dst_mx[k] = src_mx[rows[k]] with it) or dst[rows[k]] = src[k] (scatter): rows of d floats, one
+// workgroup per listed row
 __global__ void __launch_bounds__(256) k_move_rows(const float* __restrict__ src, const int* __restrict__ rows, int d, int scatter,
-                                                   float* __restrict__ dst) {
+                                                   float* __restrict__ dst, const uint32_t* __restrict__ src_mx,
+                                                   uint32_t* __restrict__ dst_mx) {
   const size_t k = blockIdx.x, r = (size_t)rows[blockIdx.x];
   const float* a = src + (scatter ? k : r) * d;
   float* b = dst + (scatter ? r : k) * d;
   for (int i = threadIdx.x; i < d; i += 256) b[i] = a[i];
+  if (src_mx && threadIdx.x == 0) dst_mx[k] = src_mx[r];
 }
 // out = beta in + sum over the parts, in part order (in may be out)
 __global__ void k_sum_parts(const float* __restrict__ part, int n_part, size_t n, float beta, const float* in, float* out) {
@@ -1268,18 +1539,25 @@ __global__ void k_swiglu_bwd4(const float* __restrict__ dact, const float* __res
   *(float4*)out = dg;
   *(float4*)(out + F) = du;
 }
+// Scales of the packed SwiGLU operands come from bounds (NP 3): |silu(g)| <= |g| and |silu'(g)| <= 1.1 give the largest
+// |act| and |d gate|, |d up| of a row or column from the maxima of gate, up and d act there, which the products that make
+// them leave.  A bound is a few bits above the largest value, of the 17 that a value may lie below it at full precision.
+// (Exact maxima by a pass over the same inputs beforehand: 225 + 300 us a layer at 64 x 384 tokens of the 0.5B decoder.)
+constexpr float kSiluSlope = 1.1f;
+struct SwigluMax { const uint32_t *gate_r, *up_r, *dact_r, *gu_c, *dact_c; uint32_t *dgu_r, *dgu_c, *act_c; };   // in; out: the bounds
 // The same straight into the packed operands of the two products that read it, F % 64 == 0: by rows of tokens (for the d input
 // product) and by rows of features (for the weight gradients, which contract over the tokens); act, which the down
 // projection's weight gradient contracts over the tokens, by rows of features as well.  Neither is stored in fp32.
 // Bound by its bytes; 64 tokens x 64 features per workgroup, the tokens' octets for the second order through LDS.
 // Before, dgu was written and read three times in fp32 (by the packing and, between its MFMAs, by the product over
 // the tokens, which then took in twice its operands' bytes: 21 x 301 tokens, one piece, 297 us a layer at 0.37 PFLOP/s).
-// act's packed form makes the pass longer (64 x 384 tokens, three pieces 826 -> 971 us a layer; 21 x 301, one piece 116 ->
-// 122) and the down projection's weight gradient shorter (1137 -> 775, 112 -> 47).
+// act's packed form makes the pass longer (21 x 301 tokens, one piece 116 -> 122 us a layer) and the down projection's weight
+// gradient shorter (112 -> 47).
 template <int NP>
 __global__ void __launch_bounds__(256) k_swiglu_bwd_pack(const float* __restrict__ dact, const float* __restrict__ gu, int M, int F,
-                                                         int KB_rows, uint4* __restrict__ by_rows, int KB_cols,
-                                                         uint4* __restrict__ by_cols, uint4* __restrict__ act_by_cols) {
+                                                         int KB_rows, u32x4_t* __restrict__ by_rows, int KB_cols,
+                                                         u32x4_t* __restrict__ by_cols, u32x4_t* __restrict__ act_by_cols,
+                                                         SwigluMax mx) {
   __shared__ float tile[3][64][65];
   const int f0 = blockIdx.x * 64, m0 = blockIdx.y * 64;
 #pragma unroll
@@ -1301,8 +1579,16 @@ __global__ void __launch_bounds__(256) k_swiglu_bwd_pack(const float* __restrict
 #pragma unroll
       for (int e = 0; e < 8; ++e) dg[e] = du[e] = act[e] = 0.f;
     }
-    x3_store<NP>(by_rows, KB_rows, m, (f0 + c) >> 3, dg);
-    x3_store<NP>(by_rows, KB_rows, m, (F + f0 + c) >> 3, du);
+    float scale = 1.f;
+    if constexpr (NP == 3) {
+      if (m < M) {
+        const uint32_t b = max(product_bound(mx.dact_r[m], mx.up_r[m], kSiluSlope), product_bound(mx.dact_r[m], mx.gate_r[m], 1.f));
+        scale = row_scale(b);
+        if (f0 + c == 0) mx.dgu_r[m] = b;
+      }
+    }
+    x3_store<NP>(by_rows, KB_rows, m, (f0 + c) >> 3, dg, scale);
+    x3_store<NP>(by_rows, KB_rows, m, (F + f0 + c) >> 3, du, scale);
 #pragma unroll
     for (int e = 0; e < 8; ++e) { tile[0][r][c + e] = dg[e]; tile[1][r][c + e] = du[e]; tile[2][r][c + e] = act[e]; }
   }
@@ -1314,7 +1600,15 @@ __global__ void __launch_bounds__(256) k_swiglu_bwd_pack(const float* __restrict
     float x[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) x[e] = tile[which][oct * 8 + e][col];
-    x3_store<NP>(which < 2 ? by_cols : act_by_cols, KB_cols, (which == 1 ? F : 0) + f0 + col, k8, x);
+    const int f = f0 + col;
+    float scale = 1.f;
+    if constexpr (NP == 3) {
+      const uint32_t g = mx.gu_c[f], u = mx.gu_c[F + f];
+      const uint32_t b = which == 0 ? product_bound(mx.dact_c[f], u, kSiluSlope) : which == 1 ? product_bound(mx.dact_c[f], g, 1.f) : product_bound(g, u, 1.f);
+      scale = row_scale(b);
+      if (m0 == 0 && oct == 0) (which < 2 ? mx.dgu_c : mx.act_c)[(which == 1 ? F : 0) + f] = b;
+    }
+    x3_store<NP>(which < 2 ? by_cols : act_by_cols, KB_cols, (which == 1 ? F : 0) + f, k8, x, scale);
   }
 }
 // dgu from dact: d gate = dact * up * sig(g) (1 + g (1 - sig(g))), d up = dact * silu(g)
@@ -1352,12 +1646,14 @@ __device__ __forceinline__ float f4c(const float4& v, int c) { return c == 0 ? v
 // acc (rows = positions of `a`, 4 g + v; column = position of `b`, lane % 16) += a b^T over the head dim
 template <int HD>
 __device__ __forceinline__ f32x4_t dot_rows(const float4 (&a)[HD / 16], const float4 (&b)[HD / 16]) {
-  f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+  // Four chains: a quarter of the roundings at the sum's full size (the scores' rounding is most of the gradients' error where
+  // they lie hundreds apart; 16 sets with scores to 450: error against 64 bits 4.1e-4 -> 2.9e-4 of a tensor's largest entry)
+  f32x4_t acc[4] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
   for (int w = 0; w < HD / 16; ++w)
 #pragma unroll
-    for (int c = 0; c < 4; ++c) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(f4c(a[w], c), f4c(b[w], c), acc, 0, 0, 0);
-  return acc;
+    for (int c = 0; c < 4; ++c) acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(f4c(a[w], c), f4c(b[w], c), acc[c], 0, 0, 0);
+  return (acc[0] + acc[1]) + (acc[2] + acc[3]);
 }
 // o (head dims x the 16 columns of lane % 16) += sum over the tile's positions 4 g + u of src[position][dim] * p[u];
 // src rows start at `tile_base` (pointer to position 0 of the tile, this head's dims).  Which head dim an
@@ -1472,7 +1768,7 @@ template <int HD> constexpr int tile_area() { return HD % 64 == 0 ? 16 * HD / 4 
 
 template <int HD>
 __global__ void __launch_bounds__(256, HD == 128 ? 2 : 1) k_tattn_fwd(const float* __restrict__ qkv, int T, int hq, int hkv, float scale,
-                                                   float* __restrict__ out, float* __restrict__ lse) {
+                                                   float* __restrict__ out, float* __restrict__ lse, uint32_t* __restrict__ row_mx) {
   const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
   const int h = blockIdx.x, s = blockIdx.y, kvh = h / (hq / hkv);
   const int q0 = (((int)gridDim.z - 1 - (int)blockIdx.z) * 4 + wave) * 16;   // the longest walks first
@@ -1541,17 +1837,28 @@ __global__ void __launch_bounds__(256, HD == 128 ? 2 : 1) k_tattn_fwd(const floa
     }
   }
   l_run = sum_xor32(sum_xor16(l_run));
-  if (q0 + r >= T) return;
   const float inv = 1.0f / l_run;
+  uint32_t mx = 0;
+  if (row_mx) {
+#pragma unroll
+    for (int dt = 0; dt < HD / 16; ++dt)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) mx = max(mx, abs_bits(o[dt][v] * inv));
+    mx = max_u32_xor32(max_u32_xor16(mx));
+  }
+  if (q0 + r >= T) return;
   store_acc<HD>(out + ((size_t)s * T + qi) * qd + (size_t)h * HD, o, g, inv);
-  if (g == 0) lse[((size_t)s * hq + h) * T + qi] = m_run + logf(l_run);
+  if (g == 0) {
+    lse[((size_t)s * hq + h) * T + qi] = m_run + logf(l_run);
+    if (row_mx) atomicMax(row_mx + (size_t)s * T + qi, mx);   // the row's heads
+  }
 }
 
 // Backward, queries: a wave owns 16 queries of one (sequence, head).  delta = dO . O; per key tile
 //   p = exp(scale s - lse), dP = V dO^T, dS = scale p (dP - delta), dQ^T += K^T dS.
 // Writes dq into dqkv's query columns and delta[(s Hq + h) T + i].
 template <int HD>
-__global__ void __launch_bounds__(256, 1) k_tattn_bwd_q(const float* __restrict__ qkv, const float* __restrict__ out,
+__global__ void __launch_bounds__(256, HD == 64 ? 3 : 1) k_tattn_bwd_q(const float* __restrict__ qkv, const float* __restrict__ out,
                                                      const float* __restrict__ dout, const float* __restrict__ lse, int T, int hq,
                                                      int hkv, float scale, float* __restrict__ dqkv, float* __restrict__ delta) {
   const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
@@ -1723,7 +2030,9 @@ hipError_t tattn_bwd(const float* qkv, const float* out, const float* dout, cons
 // transpose on the query and key columns.  One workgroup per row; a thread takes 4 rotation pairs or 4 value columns.
 __global__ void __launch_bounds__(256) k_attn_bwd_finish(float* __restrict__ dqkv, const float* __restrict__ parts, int n_parts,
                                                          size_t part_stride, const float2* __restrict__ rope, int T, int hq, int hkv,
-                                                         int hd) {
+                                                         int hd, uint32_t* __restrict__ row_mx) {
+  uint32_t mx = 0;
+  auto seen = [&](const float4& v) { mx = max(max(max(mx, abs_bits(v.x)), max(abs_bits(v.y), abs_bits(v.z))), abs_bits(v.w)); };
   const size_t m = blockIdx.x;
   const int half = hd >> 1, qd = hq * hd, kvd = hkv * hd, quads = half >> 2;
   float* row = dqkv + m * (size_t)(qd + 2 * kvd);
@@ -1740,7 +2049,9 @@ __global__ void __launch_bounds__(256) k_attn_bwd_finish(float* __restrict__ dqk
   for (int e = threadIdx.x; e < n_all; e += 256) {
     if (e >= n_rot) {
       const int c = kvd + 4 * (e - n_rot);
-      *(float4*)(row + qd + c) = sum(c);
+      const float4 v = sum(c);
+      *(float4*)(row + qd + c) = v;
+      seen(v);
       continue;
     }
     const int head = e / quads, i = 4 * (e % quads);
@@ -1750,9 +2061,16 @@ __global__ void __launch_bounds__(256) k_attn_bwd_finish(float* __restrict__ dqk
     else { a = sum((head - hq) * hd + i); b = sum((head - hq) * hd + i + half); }
     const float4* cs = (const float4*)(rope + (m % T) * half + i);
     const float4 c01 = cs[0], c23 = cs[1];   // (cos, sin) of four pairs
-    *(float4*)p = make_float4(a.x * c01.x + b.x * c01.y, a.y * c01.z + b.y * c01.w, a.z * c23.x + b.z * c23.y, a.w * c23.z + b.w * c23.w);
-    *(float4*)(p + half) =
-        make_float4(b.x * c01.x - a.x * c01.y, b.y * c01.z - a.y * c01.w, b.z * c23.x - a.z * c23.y, b.w * c23.z - a.w * c23.w);
+    const float4 lo = make_float4(a.x * c01.x + b.x * c01.y, a.y * c01.z + b.y * c01.w, a.z * c23.x + b.z * c23.y, a.w * c23.z + b.w * c23.w);
+    const float4 hi = make_float4(b.x * c01.x - a.x * c01.y, b.y * c01.z - a.y * c01.w, b.z * c23.x - a.z * c23.y, b.w * c23.z - a.w * c23.w);
+    *(float4*)p = lo;
+    *(float4*)(p + half) = hi;
+    seen(lo);
+    seen(hi);
+  }
+  if (row_mx) {
+    mx = wave_max_u32(mx);
+    if ((threadIdx.x & 63) == 0) atomicMax(row_mx + m, mx);
   }
 }
 
@@ -1847,7 +2165,7 @@ struct sapo_trainer {
   sapo_model_config cfg;
   sapo_adam_config opt;
   int t = 0;                      // Adam steps taken
-  int pieces = 3;                 // bf16 pieces per value in the large GEMMs: 3 (fp32 accuracy), 2 or 1 (bf16 operands)
+  int pieces = 3;                 // of the large GEMMs (NP there): 3 (fp32 accuracy), 2 (16 significant bits), 1 (bf16 operands)
   bool use_bias = false;          // the model has biases on its query / key / value projections (set_qkv_bias)
   int n_in = 0;                   // tensors of the input list; tensor n_in + l is layer l's bias vector
   int device = 0;
@@ -1908,7 +2226,7 @@ struct Arena {
 // head's d-input product: 238 tiles, contraction over the vocabulary) are split over the contraction into up to
 // kMaxSplits parts that are added in part order; the buffer holds 8 parts of the largest layer matrix.
 inline size_t split_parts_floats(const Dims& D) { return (size_t)8 * std::max((size_t)2 * D.F * D.d, (size_t)192 * 128 * 128); }
-constexpr int kPieces = 3;   // most bf16 pieces per fp32 value in the packed GEMMs (3: fp32 accuracy; buffers are sized for it)
+constexpr int kPieces = 3;   // the packed operands' buffers are sized for any
 
 // the fused attention kernels need float4 rows: head dim 16 / 32 / 64 / 128 and row lengths that are multiples of 4
 inline bool fused_attention(const sapo_model_config& c) {
@@ -1919,7 +2237,19 @@ inline bool fused_attention(const sapo_model_config& c) {
 struct LayerActs {
   float *h, *r1, *xn, *qkv, *lse, *ao, *h2, *r2, *xn2, *gu, *act;
 };
+// Maxima (bits) of the rows and columns of the products' operands: see k_gemm_x3
+struct LayerMax {
+  uint32_t *wqkv_r, *wo_r, *wgu_r, *wd_r;                   // weights by rows: written once per update
+  uint32_t *wqkv_c, *wo_c, *wgu_c, *wd_c;                   // from here on taken by atomics, zeroed before a micro-batch
+  uint32_t *xn_c, *ao_r, *ao_c, *xn2_c, *gu_r, *gu_c, *act_r, *act_c, *dh1_c, *dact_r, *dact_c, *dgu_r,
+      *dgu_c, *dh2_c, *dqkv_r, *dqkv_c;                     // gu_r: gate's, then up's (M apart)
+};
 struct TrainPlan {
+  std::vector<LayerMax> mx;
+  uint32_t *xn_r, *dh_r, *dl_r, *xfc_r;            // by rows, written anew for every layer or chunk
+  uint32_t *head_r, *head_c, *xfc_c, *dl_c;
+  uint32_t* mx_zero;                                        // the atomics' ones, mx_zero_n of them (head_c is on its own)
+  size_t mx_zero_n;
   std::vector<LayerActs> layer;
   bool packed_ffn;                              // the SwiGLU passes write packed operands (act of a layer is not kept)
   char* act_cols;                               // act of the layer at hand by rows of features
@@ -2002,6 +2332,25 @@ void make_plan(const sapo_model_config& c, size_t S, size_t T, size_t S_total, c
     p.head_nt = A.take<char>(p.head_cap);
     p.head_t = A.take<char>(p.head_t_cap);
   }
+  p.mx.resize(D.L);
+  for (auto& m : p.mx) {
+    m.wqkv_r = A.take<uint32_t>(D.nqkv); m.wo_r = A.take<uint32_t>(D.d); m.wgu_r = A.take<uint32_t>(2 * D.F); m.wd_r = A.take<uint32_t>(D.d);
+  }
+  for (uint32_t** r : {&p.xn_r, &p.dh_r, &p.dl_r, &p.xfc_r}) *r = A.take<uint32_t>(M);
+  p.head_r = A.take<uint32_t>(D.V);
+  p.head_c = A.take<uint32_t>(D.d);
+  p.mx_zero = A.take<uint32_t>(1);
+  const size_t zero0 = A.off;
+  for (auto& m : p.mx) {
+    m.wqkv_c = A.take<uint32_t>(D.d); m.wo_c = A.take<uint32_t>(D.q); m.wgu_c = A.take<uint32_t>(D.d); m.wd_c = A.take<uint32_t>(D.F);
+    m.xn_c = A.take<uint32_t>(D.d); m.ao_r = A.take<uint32_t>(M); m.ao_c = A.take<uint32_t>(D.q); m.xn2_c = A.take<uint32_t>(D.d);
+    m.gu_r = A.take<uint32_t>(2 * M); m.gu_c = A.take<uint32_t>(2 * D.F); m.dact_r = A.take<uint32_t>(M); m.dact_c = A.take<uint32_t>(D.F);
+    m.act_r = A.take<uint32_t>(M); m.act_c = A.take<uint32_t>(D.F); m.dh1_c = A.take<uint32_t>(D.d); m.dgu_r = A.take<uint32_t>(M);
+    m.dgu_c = A.take<uint32_t>(2 * D.F); m.dh2_c = A.take<uint32_t>(D.d); m.dqkv_r = A.take<uint32_t>(M); m.dqkv_c = A.take<uint32_t>(D.nqkv);
+  }
+  p.xfc_c = A.take<uint32_t>(D.d);
+  p.dl_c = A.take<uint32_t>(D.V);
+  p.mx_zero_n = (A.off - zero0) / sizeof(uint32_t) + 1;
   p.sur_ws = A.take<char>(g_surrogate_workspace_bytes());
   p.bytes = (A.off + 255) & ~(size_t)255;
 }
@@ -2217,21 +2566,28 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
   b_scores.causal = 1; b_dp.causal = 1; b_pv.causal = 2; b_dq.causal = 2; b_dk.causal = 3; b_dv.causal = 3;
 
   // The projections and the LM head run on the packed bf16-piece GEMM; forms as in sgemm<TA, TB>.
-  const int pieces = tr->pieces;
-  const X3Bufs xb{p.packa, p.packb, p.packa_cap, p.packb_cap, pieces, p.kparts, split_parts_floats(D)};
-  auto mm_nt = [&](const float* X, int ldx, const float* W, int ldw, float* C, int ldc, int M_, int N_, int K_, float beta,
-                   const float* Cin = nullptr, const void* w_packed = nullptr) {   // C = beta Cin + X W^T
-    // Forward products are split over K with three pieces only: the order of additions must not depend on the batch's size
-    // where operands are rounded to bf16 (a last bit decides roundings downstream, about 1e-2 of a log-prob after 24 layers).
-    return gemm_x3(X3Op{X, ldx, M_, K_, false}, X3Op{W, ldw, N_, K_, false}, C, Cin, ldc, beta, xb, st, w_packed, pieces == 3);
+  const int NP = tr->pieces;
+  const X3Bufs xb{p.packa, p.packb, p.packa_cap, p.packb_cap, NP, p.kparts, split_parts_floats(D)};
+  // Forward products are split over K with three pieces only: with two and one a sequence's log-probs do not depend on the
+  // batch around it (where operands are rounded to bf16 a last bit decides roundings downstream, about 1e-2 of a log-prob
+  // after 24 layers).
+  const bool split_fwd = NP == 3;
+  struct Mat { const float* x; int ld; uint32_t *row_mx, *col_mx; };   // a matrix by rows, with its maxima
+  auto mm_nt = [&](const Mat& X, const Mat& W, float* C, int ldc, int M_, int N_, int K_, float beta,
+                   const float* Cin = nullptr, const void* w_packed = nullptr, const OutMax& out_mx = OutMax{}) {   // C = beta Cin + X W^T
+    return gemm_x3(X3Op{X.x, X.ld, M_, K_, false, X.row_mx, X.col_mx}, X3Op{W.x, W.ld, N_, K_, false, W.row_mx, W.col_mx}, C, Cin, ldc,
+                   beta, xb, st, w_packed, split_fwd, nullptr, out_mx);
   };
-  auto mm_nn = [&](const float* A_, int lda, const float* B_, int ldb, float* C, int ldc, int M_, int N_, int K_, float beta,
-                   const void* b_packed = nullptr) {   // C = beta C + A B
-    return gemm_x3(X3Op{A_, lda, M_, K_, false}, X3Op{B_, ldb, N_, K_, true}, C, C, ldc, beta, xb, st, b_packed);
+  auto mm_nn = [&](const Mat& A_, const Mat& B_, float* C, int ldc, int M_, int N_, int K_, float beta,
+                   const void* b_packed = nullptr, const OutMax& out_mx = OutMax{}) {   // C = beta C + A B
+    return gemm_x3(X3Op{A_.x, A_.ld, M_, K_, false, A_.row_mx, A_.col_mx}, X3Op{B_.x, B_.ld, N_, K_, true, B_.col_mx, nullptr}, C, C, ldc,
+                   beta, xb, st, b_packed, true, nullptr, out_mx);
   };
-  auto mm_tn = [&](const float* A_, int lda, const float* B_, int ldb, float* C, int Mg, int Ng, int Kg, float beta) {
-    return gemm_x3_tn(A_, lda, B_, ldb, C, Mg, Ng, Kg, beta, xb, st);   // C = beta C + A^T B
+  auto mm_tn = [&](const Mat& A_, const Mat& B_, float* C, int Mg, int Ng, int Kg, float beta) {   // C = beta C + A^T B
+    return gemm_x3_tn(A_.x, A_.ld, B_.x, B_.ld, C, Mg, Ng, Kg, beta, xb, st, A_.col_mx, B_.col_mx);
   };
+  auto rows_max = [&](const float* x, int K_, uint32_t* out) { return NP == 3 ? row_max(x, Mi, K_, out, st) : hipSuccess; };
+  if (NP == 3) T_CK(g_fill_f32((float*)p.mx_zero, 0.f, p.mx_zero_n, st));
 
   const int blocks64 = (Mi + 127) / 128 * 2;   // blocks of 64 tokens that a packed operand by rows of tokens holds
   // ---- forward, every activation kept
@@ -2239,9 +2595,10 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
   T_CK(launch(KID_EMBED, k_embed_rows, dim3(Mi), dim3(256), 0, st, tokens, (const float*)TH(0), h, d, V));
   for (int l = 0; l < D.L; ++l) {
     const LayerActs& a = p.layer[l];
+    const LayerMax& mx = p.mx[l];
     const int t0 = 1 + 9 * l;   // attn_norm, wq, wk, wv, wo, ffn_norm, w_gate, w_up, w_down
-    T_CK(rmsnorm_fwd(a.h, TH(t0), c.rms_eps, Mi, d, a.xn, a.r1, st));
-    T_CK(mm_nt(a.xn, d, TH(t0 + 1), d, a.qkv, nqkv, Mi, nqkv, d, 0.f));   // wq, wk, wv are adjacent
+    T_CK(rmsnorm_fwd(a.h, TH(t0), c.rms_eps, Mi, d, a.xn, a.r1, NP == 3 ? p.xn_r : nullptr, st));
+    T_CK(mm_nt(Mat{a.xn, d, p.xn_r, mx.xn_c}, Mat{TH(t0 + 1), d, mx.wqkv_r, mx.wqkv_c}, a.qkv, nqkv, Mi, nqkv, d, 0.f));   // wq, wk, wv are adjacent
     if (tr->use_bias) T_CK(g_add_row_bias(a.qkv, TH(tr->n_in + l), Mi, nqkv, st));
     {
       const size_t total = M * (size_t)(hq + hkv) * (hd / 2);
@@ -2250,37 +2607,43 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
     }
     if (fused_attn) {
       const dim3 ag(hq, (unsigned)S, (unsigned)((T + 63) / 64));
+      uint32_t* const ao_r = NP == 3 ? mx.ao_r : nullptr;
       hipError_t e = hipErrorInvalidValue;
-      if (hd == 16) e = launch(KID_ATTN_GENERIC, k_tattn_fwd<16>, ag, dim3(256), 0, st, (const float*)a.qkv, (int)T, hq, hkv, att_scale, a.ao, a.lse);
-      if (hd == 32) e = launch(KID_ATTN_GENERIC, k_tattn_fwd<32>, ag, dim3(256), 0, st, (const float*)a.qkv, (int)T, hq, hkv, att_scale, a.ao, a.lse);
-      if (hd == 64) e = launch(KID_ATTN_GENERIC, k_tattn_fwd<64>, ag, dim3(256), 0, st, (const float*)a.qkv, (int)T, hq, hkv, att_scale, a.ao, a.lse);
-      if (hd == 128) e = launch(KID_ATTN_GENERIC, k_tattn_fwd<128>, ag, dim3(256), 0, st, (const float*)a.qkv, (int)T, hq, hkv, att_scale, a.ao, a.lse);
+      if (hd == 16) e = launch(KID_ATTN_GENERIC, k_tattn_fwd<16>, ag, dim3(256), 0, st, (const float*)a.qkv, (int)T, hq, hkv, att_scale, a.ao, a.lse, ao_r);
+      if (hd == 32) e = launch(KID_ATTN_GENERIC, k_tattn_fwd<32>, ag, dim3(256), 0, st, (const float*)a.qkv, (int)T, hq, hkv, att_scale, a.ao, a.lse, ao_r);
+      if (hd == 64) e = launch(KID_ATTN_GENERIC, k_tattn_fwd<64>, ag, dim3(256), 0, st, (const float*)a.qkv, (int)T, hq, hkv, att_scale, a.ao, a.lse, ao_r);
+      if (hd == 128) e = launch(KID_ATTN_GENERIC, k_tattn_fwd<128>, ag, dim3(256), 0, st, (const float*)a.qkv, (int)T, hq, hkv, att_scale, a.ao, a.lse, ao_r);
       T_CK(e);
     } else {
       T_CK((sgemm<0, 1>(a.qkv, nqkv, a.qkv + q, nqkv, p.prob, (int)T, (int)T, (int)T, hd, 0.f, st, b_scores)));
       T_CK(launch(KID_ATTN_GENERIC, k_softmax_causal, dim3((unsigned)(S * hq * T)), dim3(64), 0, st, p.prob, a.lse, (int)T,
                   att_scale));
       T_CK((sgemm<0, 0>(p.prob, (int)T, a.qkv + q + kv, nqkv, a.ao, q, (int)T, hd, (int)T, 0.f, st, b_pv)));
+      T_CK(rows_max(a.ao, q, mx.ao_r));
     }
-    T_CK(mm_nt(a.ao, q, TH(t0 + 4), q, a.h2, d, Mi, d, q, 1.f, a.h));
-    T_CK(rmsnorm_fwd(a.h2, TH(t0 + 5), c.rms_eps, Mi, d, a.xn2, a.r2, st));
-    T_CK(mm_nt(a.xn2, d, TH(t0 + 6), d, a.gu, 2 * F, Mi, 2 * F, d, 0.f));   // w_gate, w_up are adjacent
+    T_CK(mm_nt(Mat{a.ao, q, mx.ao_r, mx.ao_c}, Mat{TH(t0 + 4), q, mx.wo_r, mx.wo_c}, a.h2, d, Mi, d, q, 1.f, a.h));
+    T_CK(rmsnorm_fwd(a.h2, TH(t0 + 5), c.rms_eps, Mi, d, a.xn2, a.r2, NP == 3 ? p.xn_r : nullptr, st));
+    T_CK(mm_nt(Mat{a.xn2, d, p.xn_r, mx.xn2_c}, Mat{TH(t0 + 6), d, mx.wgu_r, mx.wgu_c}, a.gu, 2 * F, Mi, 2 * F, d, 0.f, nullptr,
+               nullptr, NP == 3 && p.packed_ffn ? OutMax{mx.gu_r, mx.gu_c, F, M} : OutMax{}));   // w_gate, w_up are adjacent
     float* h_next = (l + 1 < D.L) ? p.layer[l + 1].h : p.h_last;
     if (p.packed_ffn) {
       auto pack = [&](auto kernel) {
-        return launch(KID_SWIGLU, kernel, dim3(F / 64, blocks64), dim3(256), 0, st, (const float*)a.gu, Mi, F, x3_steps(F, pieces), (uint4*)p.packa);
+        return launch(KID_SWIGLU, kernel, dim3(F / 64, blocks64), dim3(256), 0, st, (const float*)a.gu, Mi, F, x3_steps(F), (u32x4_t*)p.packa,
+                      (const uint32_t*)mx.gu_r, (const uint32_t*)(mx.gu_r + M), mx.act_r);
       };
-      T_CK(pieces == 3 ? pack(k_swiglu_fwd_pack<3>) : pieces == 2 ? pack(k_swiglu_fwd_pack<2>) : pack(k_swiglu_fwd_pack<1>));
-      T_CK(gemm_x3(X3Op{nullptr, 0, Mi, F, false}, X3Op{TH(t0 + 8), F, d, F, false}, h_next, a.h2, d, 1.f, xb, st, nullptr, pieces == 3, p.packa));
+      T_CK(NP == 3 ? pack(k_swiglu_fwd_pack<3>) : NP == 2 ? pack(k_swiglu_fwd_pack<2>) : pack(k_swiglu_fwd_pack<1>));
+      T_CK(gemm_x3(X3Op{nullptr, 0, Mi, F, false, mx.act_r, nullptr}, X3Op{TH(t0 + 8), F, d, F, false, mx.wd_r, mx.wd_c}, h_next, a.h2, d, 1.f,
+                   xb, st, nullptr, split_fwd, p.packa));
       continue;
     }
     if (F % 4 == 0 && M <= 65535)
       T_CK(launch(KID_SWIGLU, k_swiglu_fwd4, dim3((F / 4 + 255) / 256, Mi), dim3(256), 0, st, (const float*)a.gu, a.act, F));
     else
       T_CK(launch(KID_SWIGLU, k_swiglu_fwd, dim3(blocks256(M * D.F)), dim3(256), 0, st, (const float*)a.gu, a.act, F, M * D.F));
-    T_CK(mm_nt(a.act, F, TH(t0 + 8), F, h_next, d, Mi, d, F, 1.f, a.h2));
+    T_CK(rows_max(a.act, F, mx.act_r));
+    T_CK(mm_nt(Mat{a.act, F, mx.act_r, mx.act_c}, Mat{TH(t0 + 8), F, mx.wd_r, mx.wd_c}, h_next, d, Mi, d, F, 1.f, a.h2));
   }
-  T_CK(rmsnorm_fwd(p.h_last, TH(t_final), c.rms_eps, Mi, d, p.xf, p.rf, st));
+  T_CK(rmsnorm_fwd(p.h_last, TH(t_final), c.rms_eps, Mi, d, p.xf, p.rf, NP == 3 ? p.xn_r : nullptr, st));
 
   // ---- LM head, over the rows that predict a masked token only (the others have no log-prob to report and a zero
   // d logits row): their final-normed rows gathered, then chunks of them: logits, log-probs, d logits, d rows (into
@@ -2291,16 +2654,19 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
   if (first && t_head != 0) T_CK(g_fill_f32(GR(0), 0.f, D.V * D.d, st));
   if (first && n_rows == 0) T_CK(g_fill_f32(GR(t_head), 0.f, D.V * D.d, st));
   if (n_rows > 0) {
-    T_CK(launch(KID_MISC, k_move_rows, dim3(n_rows), dim3(256), 0, st, (const float*)p.xf, rows, d, 0, p.xfc));
+    T_CK(launch(KID_MISC, k_move_rows, dim3(n_rows), dim3(256), 0, st, (const float*)p.xf, rows, d, 0, p.xfc, (const uint32_t*)p.xn_r,
+                p.xfc_r));
     for (size_t r0 = 0; r0 < (size_t)n_rows; r0 += p.chunk) {
       const int R = (int)(((size_t)n_rows - r0 < p.chunk) ? (size_t)n_rows - r0 : p.chunk);
-      T_CK(mm_nt(p.xfc + r0 * D.d, d, TH(t_head), d, p.logits, V, R, V, d, 0.f, nullptr, p.head_nt));
+      const Mat xfc{p.xfc + r0 * D.d, d, p.xfc_r + r0, p.xfc_c}, logits{p.logits, V, p.dl_r, p.dl_c}, head{TH(t_head), d, p.head_r, p.head_c};
+      T_CK(mm_nt(xfc, head, p.logits, V, R, V, d, 0.f, nullptr, p.head_nt));
       T_CK(launch(KID_SCORE_ROWS, k_logp_dlogits, dim3(R), dim3(kLogpThreads), 0, st, p.logits, V, rows + r0, (int)T, tokens, completion_mask,
-                  logp_old, advantages, eps_low, eps_high, (const long long*)p.n_masked, logp_new));
-      T_CK(mm_nn(p.logits, V, TH(t_head), d, p.dh + r0 * D.d, d, R, d, V, 0.f, p.head_t));
-      T_CK(mm_tn(p.logits, V, p.xfc + r0 * D.d, d, GR(t_head), V, d, R, r0 == 0 ? keep : 1.f));
+                  logp_old, advantages, eps_low, eps_high, (const long long*)p.n_masked, logp_new, p.dl_r));
+      T_CK(mm_nn(logits, head, p.dh + r0 * D.d, d, R, d, V, 0.f, p.head_t));
+      T_CK(mm_tn(logits, xfc, GR(t_head), V, d, R, r0 == 0 ? keep : 1.f));
     }
-    T_CK(launch(KID_MISC, k_move_rows, dim3(n_rows), dim3(256), 0, st, (const float*)p.dh, rows, d, 1, p.dx));
+    T_CK(launch(KID_MISC, k_move_rows, dim3(n_rows), dim3(256), 0, st, (const float*)p.dh, rows, d, 1, p.dx, (const uint32_t*)nullptr,
+                (uint32_t*)nullptr));
   }
   // ---- backward through the layers
   const int n_gpart = (Mi + 255) / 256;
@@ -2309,7 +2675,7 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
       const int n_part = (Mi + kNormRows - 1) / kNormRows;
       const hipError_t e = with_norm_width(d, [&](auto nv) {
         return launch(KID_RMSNORM, k_rmsnorm_bwd_rows<decltype(nv)::value>, dim3(n_part), dim3(256), 0, st, dxn, hin, rstd,
-                      (const float*)TH(gain_tensor_idx), Mi, d, p.dh, accumulate, p.gpart);
+                      (const float*)TH(gain_tensor_idx), Mi, d, p.dh, accumulate, p.gpart, NP == 3 ? p.dh_r : nullptr);
       });
       if (e != hipSuccess) return e;
       return launch(KID_MISC, k_gain_sum, dim3((d + 15) / 16), dim3(256), 0, st, (const float*)p.gpart, n_part, d, !first, GR(gain_tensor_idx));
@@ -2320,41 +2686,51 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
     e = launch(KID_MISC, k_gain_grad_finish, dim3((d + 255) / 256), dim3(256), 0, st, (const float*)p.gpart, n_gpart, d, !first,
                GR(gain_tensor_idx));
     if (e != hipSuccess) return e;
-    return launch(KID_RMSNORM, k_rmsnorm_bwd, dim3(Mi), dim3(256), 0, st, dxn, hin, rstd, (const float*)TH(gain_tensor_idx), d,
-                  p.dh, accumulate);
+    e = launch(KID_RMSNORM, k_rmsnorm_bwd, dim3(Mi), dim3(256), 0, st, dxn, hin, rstd, (const float*)TH(gain_tensor_idx), d,
+               p.dh, accumulate);
+    return e != hipSuccess ? e : rows_max(p.dh, d, p.dh_r);
   };
   T_CK(norm_bwd(p.dx, p.h_last, p.rf, t_final, 0));
   for (int l = D.L - 1; l >= 0; --l) {
     const LayerActs& a = p.layer[l];
     const int t0 = 1 + 9 * l;
+    const LayerMax& mx = p.mx[l];
     // down projection
-    T_CK(mm_nn(p.dh, d, TH(t0 + 8), F, p.dact, F, Mi, F, d, 0.f));
+    const Mat dh1{p.dh, d, p.dh_r, mx.dh1_c}, dh2{p.dh, d, p.dh_r, mx.dh2_c};   // the residual gradient before and after the FFN's norm
+    T_CK(mm_nn(dh1, Mat{TH(t0 + 8), F, mx.wd_r, mx.wd_c}, p.dact, F, Mi, F, d, 0.f, nullptr,
+               NP == 3 && p.packed_ffn ? OutMax{mx.dact_r, mx.dact_c, 0, 0} : OutMax{}));
     if (p.packed_ffn) {
-      const int KB_rows = x3_steps(2 * F, pieces), KB_cols = x3_steps(Mi, pieces);
+      const int KB_rows = x3_steps(2 * F), KB_cols = x3_steps(Mi);
       auto pack = [&](auto kernel) {
         return launch(KID_SWIGLU, kernel, dim3(F / 64, blocks64), dim3(256), 0, st, (const float*)p.dact, (const float*)a.gu, Mi, F, KB_rows,
-                      (uint4*)p.packa, KB_cols, (uint4*)p.dgu, (uint4*)p.act_cols);
+                      (u32x4_t*)p.packa, KB_cols, (u32x4_t*)p.dgu, (u32x4_t*)p.act_cols,
+                      SwigluMax{mx.gu_r, mx.gu_r + M, mx.dact_r, mx.gu_c, mx.dact_c, mx.dgu_r, mx.dgu_c, mx.act_c});
       };
-      T_CK(pieces == 3 ? pack(k_swiglu_bwd_pack<3>) : pieces == 2 ? pack(k_swiglu_bwd_pack<2>) : pack(k_swiglu_bwd_pack<1>));
+      T_CK(NP == 3 ? pack(k_swiglu_bwd_pack<3>) : NP == 2 ? pack(k_swiglu_bwd_pack<2>) : pack(k_swiglu_bwd_pack<1>));
       // gate / up projections, then the down projection's weights
-      T_CK(gemm_x3(X3Op{nullptr, 0, Mi, 2 * F, false}, X3Op{TH(t0 + 6), d, d, 2 * F, true}, p.dx, p.dx, d, 0.f, xb, st, nullptr, true, p.packa));
-      T_CK(gemm_x3(X3Op{nullptr, 0, 2 * F, Mi, true}, X3Op{a.xn2, d, d, Mi, true}, GR(t0 + 6), GR(t0 + 6), d, keep, xb, st, nullptr, true, p.dgu));
-      T_CK(gemm_x3(X3Op{p.dh, d, d, Mi, true}, X3Op{nullptr, 0, F, Mi, true}, GR(t0 + 8), GR(t0 + 8), F, keep, xb, st, p.act_cols));
+      T_CK(gemm_x3(X3Op{nullptr, 0, Mi, 2 * F, false, mx.dgu_r, nullptr}, X3Op{TH(t0 + 6), d, d, 2 * F, true, mx.wgu_c, nullptr}, p.dx, p.dx, d,
+                   0.f, xb, st, nullptr, true, p.packa));
+      T_CK(gemm_x3(X3Op{nullptr, 0, 2 * F, Mi, true, mx.dgu_c, nullptr}, X3Op{a.xn2, d, d, Mi, true, mx.xn2_c, nullptr}, GR(t0 + 6), GR(t0 + 6), d,
+                   keep, xb, st, nullptr, true, p.dgu));
+      T_CK(gemm_x3(X3Op{p.dh, d, d, Mi, true, mx.dh1_c, nullptr}, X3Op{nullptr, 0, F, Mi, true, mx.act_c, nullptr}, GR(t0 + 8), GR(t0 + 8), F, keep,
+                   xb, st, p.act_cols));
     } else {
-      T_CK(mm_tn(p.dh, d, a.act, F, GR(t0 + 8), d, F, Mi, keep));
+      T_CK(mm_tn(dh1, Mat{a.act, F, mx.act_r, mx.act_c}, GR(t0 + 8), d, F, Mi, keep));
       if (F % 4 == 0 && M <= 65535)
         T_CK(launch(KID_SWIGLU, k_swiglu_bwd4, dim3((F / 4 + 255) / 256, Mi), dim3(256), 0, st, (const float*)p.dact,
                     (const float*)a.gu, p.dgu, F));
       else
         T_CK(launch(KID_SWIGLU, k_swiglu_bwd, dim3(blocks256(M * D.F)), dim3(256), 0, st, (const float*)p.dact, (const float*)a.gu,
                     p.dgu, F, M * D.F));
-      T_CK(mm_nn(p.dgu, 2 * F, TH(t0 + 6), d, p.dx, d, Mi, d, 2 * F, 0.f));
-      T_CK(mm_tn(p.dgu, 2 * F, a.xn2, d, GR(t0 + 6), 2 * F, d, Mi, keep));
+      T_CK(rows_max(p.dgu, 2 * F, mx.dgu_r));
+      const Mat dgu{p.dgu, 2 * F, mx.dgu_r, mx.dgu_c};
+      T_CK(mm_nn(dgu, Mat{TH(t0 + 6), d, mx.wgu_r, mx.wgu_c}, p.dx, d, Mi, d, 2 * F, 0.f));
+      T_CK(mm_tn(dgu, Mat{a.xn2, d, nullptr, mx.xn2_c}, GR(t0 + 6), 2 * F, d, Mi, keep));
     }
     T_CK(norm_bwd(p.dx, a.h2, a.r2, t0 + 5, 1));
     // output projection
-    T_CK(mm_nn(p.dh, d, TH(t0 + 4), q, p.dao, q, Mi, q, d, 0.f));
-    T_CK(mm_tn(p.dh, d, a.ao, q, GR(t0 + 4), d, q, Mi, keep));
+    T_CK(mm_nn(dh2, Mat{TH(t0 + 4), q, mx.wo_r, mx.wo_c}, p.dao, q, Mi, q, d, 0.f));
+    T_CK(mm_tn(dh2, Mat{a.ao, q, mx.ao_r, mx.ao_c}, GR(t0 + 4), d, q, Mi, keep));
     // attention and the rotary embedding; dgu is free here and takes the partial dk / dv
     float* kv_parts = fused_attn && rep > 1 && 2 * D.F >= 2 * D.q ? p.dgu : nullptr;
     if (fused_attn) {
@@ -2393,11 +2769,12 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
     }
     if (kv_parts) {
       T_CK(launch(KID_ROPE_APPEND, k_attn_bwd_finish, dim3(Mi), dim3(256), 0, st, p.dqkv, (const float*)kv_parts, rep,
-                  M * 2 * D.kv, (const float2*)tr->rope, (int)T, hq, hkv, hd));
+                  M * 2 * D.kv, (const float2*)tr->rope, (int)T, hq, hkv, hd, NP == 3 ? mx.dqkv_r : nullptr));
     } else {
       const size_t total = M * (size_t)(hq + hkv) * (hd / 2);
       T_CK(launch(KID_ROPE_APPEND, k_rope, dim3(blocks256(total)), dim3(256), 0, st, p.dqkv, (const float2*)tr->rope, (int)T,
                   hq + hkv, hd, nqkv, -1.0f, total));
+      T_CK(rows_max(p.dqkv, nqkv, mx.dqkv_r));
     }
     if (tr->use_bias) {   // the biases enter before the rotary embedding: their gradient is the column sum of dqkv here
       T_CK(launch(KID_MISC, k_colsum_partial, dim3((nqkv + 255) / 256, n_gpart), dim3(256), 0, st, (const float*)p.dqkv, Mi, nqkv,
@@ -2406,8 +2783,9 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
                   !first, GR(tr->n_in + l)));
     }
     // query / key / value projections
-    T_CK(mm_nn(p.dqkv, nqkv, TH(t0 + 1), d, p.dx, d, Mi, d, nqkv, 0.f));
-    T_CK(mm_tn(p.dqkv, nqkv, a.xn, d, GR(t0 + 1), nqkv, d, Mi, keep));
+    const Mat dqkv{p.dqkv, nqkv, mx.dqkv_r, mx.dqkv_c};
+    T_CK(mm_nn(dqkv, Mat{TH(t0 + 1), d, mx.wqkv_r, mx.wqkv_c}, p.dx, d, Mi, d, nqkv, 0.f));
+    T_CK(mm_tn(dqkv, Mat{a.xn, d, nullptr, mx.xn_c}, GR(t0 + 1), nqkv, d, Mi, keep));
     T_CK(norm_bwd(p.dx, a.h, a.r1, t0, 1));
   }
   T_CK(launch(KID_EMBED, k_embed_order, dim3((Mi + kEmbedChunk - 1) / kEmbedChunk), dim3(1024), 0, st, tokens, Mi, V, p.eorder));
@@ -2461,8 +2839,36 @@ extern "C" int sapo_policy_update(sapo_trainer* tr, const int32_t* tokens, const
   const int t_head = c.tied_embeddings ? 0 : 1 + 9 * c.n_layers + 1;
   const int d = (int)D.d, V = (int)D.V;
   T_CK(launch(KID_MISC, k_count_mask, dim3(1), dim3(256), 0, st, completion_mask, M, p.n_masked));
-  T_CK(x3_pack(X3Op{tr->theta + tr->off[t_head], d, V, d, false}, p.head_nt, p.head_cap, tr->pieces, st));   // rows = vocabulary
-  T_CK(x3_pack(X3Op{tr->theta + tr->off[t_head], d, d, V, true}, p.head_t, p.head_t_cap, tr->pieces, st));    // rows = d
+  const int NP = tr->pieces;
+  const float* head = tr->theta + tr->off[t_head];
+  if (NP == 3) {   // maxima of the weights' rows
+    RowMaxTasks t;
+    t.n = 0;
+    unsigned blocks = 0;
+    auto flush = [&]() {
+      const hipError_t e = launch(KID_MISC, k_row_max, dim3(blocks), dim3(256), 0, st, t);
+      t.n = 0;
+      blocks = 0;
+      return e;
+    };
+    auto add = [&](const float* src, size_t rows, size_t K, uint32_t* out) -> hipError_t {
+      t.t[t.n++] = RowMaxTask{src, out, (int)rows, (int)K, blocks};
+      blocks += (unsigned)((rows + 3) / 4);
+      return t.n == kRowMaxTasks ? flush() : hipSuccess;
+    };
+    T_CK(add(head, D.V, D.d, p.head_r));
+    for (int l = 0; l < D.L; ++l) {
+      auto w = [&](int k) { return tr->theta + tr->off[1 + 9 * l + k]; };
+      T_CK(add(w(1), D.nqkv, D.d, p.mx[l].wqkv_r));
+      T_CK(add(w(4), D.d, D.q, p.mx[l].wo_r));
+      T_CK(add(w(6), 2 * D.F, D.d, p.mx[l].wgu_r));
+      T_CK(add(w(8), D.d, D.F, p.mx[l].wd_r));
+    }
+    if (t.n > 0) T_CK(flush());
+    T_CK(g_fill_f32((float*)p.head_c, 0.f, D.d, st));
+  }
+  T_CK(x3_pack(X3Op{head, d, V, d, false, p.head_r, p.head_c}, p.head_nt, p.head_cap, NP, st));        // rows = vocabulary
+  T_CK(x3_pack(X3Op{head, d, d, V, true, p.head_c, nullptr}, p.head_t, p.head_t_cap, NP, st));       // rows = d
   // The rows that predict a masked token, per micro-batch (indices within it, ascending), and how many there are:
   // the host needs the numbers to size the LM head's GEMMs, so the call waits here once, before the forward passes
   // are enqueued, for these small kernels (and for whatever the stream held before).

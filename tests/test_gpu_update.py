@@ -626,3 +626,58 @@ def test_gradients_through_probabilities_below_the_normal_range(sapo, head_dim, 
     got = read_all(sapo, tr, 1)[0][57]
     assert np.linalg.norm(got - want) <= 1e-3 * np.linalg.norm(want), (np.linalg.norm(got), np.linalg.norm(want))
     tr.close()
+
+
+@pytest.mark.parametrize("d_model,d_ff,S,T,bits,scale", [
+    (64, 192, 2, 70, 6, 1.0), (64, 64, 2, 129, 0, 1e30), (96, 72, 3, 33, 6, 1e-25), (512, 192, 2, 24, 0, 1e-30), (512, 128, 3, 50, 6, 1e12)])
+def test_update_of_operands_of_very_different_sizes(sapo, d_model, d_ff, S, T, bits, scale):
+    """Three pieces: every row of a product's operands has a scale of its own.  Gradients of any size (advantages of 1e-30 ..
+    1e30), and normalised rows whose values lie 2^(2 bits) apart, the weights behind them the other way round, are as
+    accurate as others (a value within 2^-17 of its row's largest keeps its bits).  d_model 512: products that are split,
+    whose maxima a pass over the output takes; d_ff 192, 72: a row's two maxima in one tile, rows packed without the fused pass."""
+    import torch
+    from oracle import sapo_update_oracle as U
+    shape = W.ModelShape(n_layers=2, d_model=d_model, n_q_heads=2, n_kv_heads=1, head_dim=64, d_ff=d_ff, vocab=160, rms_eps=1e-6,
+                         rope_theta=1e4, tied_embeddings=False, dtype="f32", max_seq=160)
+    w = W.perturb_norm_gains(W.make_weights(shape, 9 + T, std=0.25 * (64 / d_model) ** 0.5), T)
+    rng = np.random.default_rng([d_model, d_ff, T])
+    powers = lambda: (2.0 ** rng.integers(-bits, bits + 1, size=d_model)).astype(np.float32)
+    for lw in w["layers"]:
+        for gain, behind in (("attn_norm", ("wq", "wk", "wv")), ("ffn_norm", ("w_gate", "w_up"))):
+            u = powers()
+            lw[gain] = lw[gain] * u
+            for k in behind:
+                lw[k] = lw[k] / u
+    u = powers()
+    w["final_norm"], w["lm_head"] = w["final_norm"] * u, w["lm_head"] / u
+    tokens = rng.integers(0, shape.vocab, size=(S, T)).astype(np.int32)
+    mask = np.zeros((S, T), dtype=np.uint8)
+    mask[:, max(1, T - 20):] = 1
+    adv = np.where(np.arange(S) % 2 == 0, 1.25, -0.75).astype(np.float32)
+    params = U.parameter_list(shape, w)
+    _, lp, _ = U.loss_and_gradients(shape, params, tokens, mask, np.zeros((S, T), np.float32), adv)
+    logp_old = (lp + np.where(rng.random((S, T)) < 0.5, -0.1, 0.1) * (mask != 0)).astype(np.float32)
+    _, ref_lp, ref_g = U.loss_and_gradients(shape, params, tokens, mask, logp_old, adv)   # linear in the advantages
+    tr = sapo.sapo_trainer_create(shape, w)
+    _, lp_new = sapo.sapo_policy_update(tr, dev(tokens), dev(mask), dev(logp_old), dev((adv * np.float32(scale)).astype(np.float32)))
+    torch.cuda.synchronize()
+    assert np.max(np.abs(lp_new.cpu().numpy() - ref_lp)) < 2e-4
+    ref_g = [np.asarray(b) * float(np.float32(scale)) for b in ref_g]
+    for i, (a, b) in enumerate(zip(read_all(sapo, tr, 1), ref_g)):
+        assert np.linalg.norm(a.astype(np.float64) - b) <= 2e-4 * np.linalg.norm(b), i
+    tr.close()
+
+
+def test_update_keeps_what_is_not_finite(sapo):
+    """An infinite weight's products are infinite or NaN, whatever their row's scale: nothing of them looks like a number."""
+    import torch
+    shape = SHAPES["tiny"]
+    w, params, tokens, mask, logp_old, adv = make_case(shape, 78, 3, 20, 9)
+    for bad in (np.inf, np.nan):
+        w["layers"][0]["w_down"][5, 7] = bad
+        tr = sapo.sapo_trainer_create(shape, w)
+        loss, lp = sapo.sapo_policy_update(tr, dev(tokens), dev(mask), dev(logp_old), dev(adv))
+        torch.cuda.synchronize()
+        assert not np.any(np.isfinite(lp.cpu().numpy()[mask != 0]))
+        assert not np.any(np.isfinite(read_all(sapo, tr, 1)[0]).all(axis=1)[np.unique(tokens)])
+        tr.close()
