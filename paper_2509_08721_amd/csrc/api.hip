@@ -270,7 +270,8 @@ static int upload_persist_table(sapo_weights* w) {
 // streams the model through one compute unit (about 80 GB/s) and pays its barriers (about 5 us per layer); the
 // shape-generic path pays its 11 launches per layer, about 5 us each.  The line is drawn where the former is at most half
 // of the latter with one round of workgroups, so that a batch of two rounds (512 sequences) is still no slower; larger
-// batches are decided call by call (small_pays).  Tiny configuration: 18 us per step (the estimate says 19) against 135.
+// batches are decided call by call (small_pays).  Tiny configuration: 12 us per step (the estimate, fitted when it was 18,
+// says 19) against 135.
 static bool small_eligible(const sapo_weights* w) {
   const sapo_model_config& c = w->cfg;
   if (w->mfma || force_generic() || c.n_layers == 0) return false;

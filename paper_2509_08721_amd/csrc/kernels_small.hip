@@ -2,8 +2,8 @@
 //
 // The shape-generic kernels run one operation of one layer per launch; on a decoder whose matrices are a few hundred KB
 // every one of those launches is a few microseconds of latency around a fraction of a microsecond of work (the tiny
-// configuration: 23 launches per decode step, 135 us; here 18 us).  Its rollout call, 8 sequences of 16 + 16 tokens, went
-// from 2230 to 305 us, scoring 8 x 256 tokens from 360 to 65 us.  Sequences do not
+// configuration: 23 launches per decode step, 135 us; here 12 us).  Its rollout call, 8 sequences of 16 + 16 tokens, went
+// from 2230 to 220 us, scoring 8 x 256 tokens from 360 to 65 us.  Sequences do not
 // depend on each other, so here a workgroup of 8 waves takes one sequence through all layers, positions and steps: the
 // activations stay in LDS, a workgroup barrier takes the place of a launch, the weights come out of the L2 again for
 // every step.
@@ -14,8 +14,13 @@
 //                    scoring: two tiles 77 us in one launch, 51 us in three).
 //   k_small_decode   one workgroup per sequence: LM head, sampler, embedding and layers of one position, step after step.
 // Offsets are 32-bit: small_rows_fit (host; the limits are in ranges.h) says for which calls they are enough.
-// What bounds them: a workgroup streams the model through one compute unit per step (about 80 GB/s), five barriers per
-// layer.  small_eligible (api.hip) says for which models that is still cheaper than the launches.
+// What bounds them: a workgroup takes its weights in at 32 bytes a cycle (layers of the tiny decoder: 11.5 of a step's 27
+// thousand cycles), and a phase is a chain of dependent instructions between barriers, five per layer.  small_eligible
+// (api.hip) says for which models that is still cheaper than the launches.  Per step of the tiny decoder, thousands of
+// cycles, before and now: attention 6.3 -> 4.0 a layer (its keys, values and the norms' gains in LDS), other phases of a layer
+// 10.2 -> 6.2 (a first pass outside the loop does not wait for the next phase's weights; sums scattered over the lanes, one
+// lane's epilogue per feature), LM head 5.1 -> 2.4 (in LDS), sampler 4.4 -> 3.5 (outputs written during the next attention);
+// about a third of it all because LDS areas start at multiples of 16 bytes now.
 //
 // Decode (one row): a product is spread over groups of 16 lanes (lane i takes the k = 4 i .. 4 i + 3 of every 64);
 // groups take output features round-robin, so a group's weight request is 256 contiguous bytes and a wave's the rows of
@@ -107,11 +112,13 @@ template <typename T> struct Quad;
 template <> struct Quad<float> {
   f32x4 u;
   __device__ __forceinline__ void load(gptr<float> p) { u = *(gptr<f32x4>)p; }
+  __device__ __forceinline__ void load(const float* lds) { u = *(const f32x4*)lds; }
   __device__ __forceinline__ float4 f() const { return make_float4(u[0], u[1], u[2], u[3]); }
 };
 template <> struct Quad<bf16> {
   u32x2 u;
   __device__ __forceinline__ void load(gptr<bf16> p) { u = *(gptr<u32x2>)p; }
+  __device__ __forceinline__ void load(const bf16* lds) { u = *(const u32x2*)lds; }
   __device__ __forceinline__ float4 f() const {
     return make_float4(__uint_as_float(u[0] << 16), __uint_as_float(u[0] & 0xffff0000u), __uint_as_float(u[1] << 16),
                        __uint_as_float(u[1] & 0xffff0000u));
@@ -131,56 +138,96 @@ __device__ __forceinline__ int fresh_thread() {
   asm volatile("" : "+v"(t));
   return t;
 }
-// The weights of a group's first NF features, KC chunks of 64 k: requested a phase ahead of their use, since they
+// Features of a pass: group g's feature j is first_feature(n0, j, N) + g, n0 the pass's first.  The last groups of features
+// that N does not fill begin early, so that no request needs a bound of its own; what is computed twice is kept once
+// (own_feature).  N below kGroups: groups past the end repeat the last feature.
+__device__ __forceinline__ int first_feature(int n0, int j, int N) { return max(0, min(n0 + j * kGroups, N - kGroups)); }
+__device__ __forceinline__ bool own_feature(int n0, int j, int N, int g) { return g < N && first_feature(n0, j, N) + g >= n0 + j * kGroups; }
+// Sums of NF (2, 4, 8, 16) values over the 16 lanes of a group, in the order of sum16; a lane gets value scatter_index (the
+// lane's highest bits, the highest first)
+template <int NF> __device__ __forceinline__ int scatter_index(int ln) { return ln / (16 / NF); }
+template <int NF> __device__ __forceinline__ bool scatter_writer(int ln) { return (ln & (16 / NF - 1)) == 0; }   // one lane per value
+template <int NF> __device__ __forceinline__ float scatter16(const float (&in)[NF], int ln) {
+  static_assert(NF == 2 || NF == 4 || NF == 8 || NF == 16, "halves");
+  float a[16];
+#pragma unroll
+  for (int i = 0; i < NF; ++i) a[i] = in[i];
+  auto step = [&](auto ctrl_c, auto n_c, int bit) __attribute__((always_inline)) {
+    constexpr int ctrl = decltype(ctrl_c)::value, n = decltype(n_c)::value;
+    if constexpr (n >= 2) {
+#pragma unroll
+      for (int i = 0; i < n / 2; ++i) a[i] = (ln & bit ? a[i + n / 2] : a[i]) + dpp<ctrl>(ln & bit ? a[i] : a[i + n / 2]);
+    } else {
+      a[0] += dpp<ctrl>(a[0]);
+    }
+  };
+  step(std::integral_constant<int, kMirror>(), std::integral_constant<int, NF>(), 8);
+  step(std::integral_constant<int, kHalfMirror>(), std::integral_constant<int, NF / 2>(), 4);
+  step(std::integral_constant<int, kXor2>(), std::integral_constant<int, NF / 4>(), 2);
+  step(std::integral_constant<int, kXor1>(), std::integral_constant<int, NF / 8>(), 1);
+  return a[0];
+}
+// The weights of a group's features of one pass, KC chunks of 64 k: requested a phase ahead of their use, since they
 // depend on nothing the step computes.
 template <typename T, int NF, int KC> struct WeightAhead {
   Quad<T> w[KC][NF];
-  __device__ __forceinline__ void request(gptr<T> W, int N, int K) {
+  template <class P> __device__ __forceinline__ void request(P W, int N, int K, int n0 = 0) {   // P: where W lies, global memory or LDS
     const int ft = fresh_thread(), g = ft >> 4, ln = ft & 15;
+    const unsigned row = (unsigned)min(g, N - 1) * K;
 #pragma unroll
-    for (int c = 0; c < KC; ++c)
+    for (int c = 0; c < KC; ++c) {
+      const int k = c * 64 + ln * 4;
+      const unsigned at = row + (k < K ? k : 0);
 #pragma unroll
-      for (int j = 0; j < NF; ++j) {
-        const int k = c * 64 + ln * 4;
-        w[c][j].load(W + (unsigned)min(g + j * kGroups, N - 1) * K + (k < K ? k : 0));
-      }
+      for (int j = 0; j < NF; ++j) w[c][j].load(W + (unsigned)first_feature(n0, j, N) * K + at);
+    }
   }
 };
-// y[n] = sum_k W[n][k] x[k] for one row; x(k) gives x[k .. k + 3]; out(n, y) runs in every lane of the group.  NF
-// features per group and pass, so that many weight requests are in flight; the first pass takes what `ahead` holds.
-template <typename T, int NF, int KC, class X, class Out>
-__device__ __forceinline__ void row_product(const WeightAhead<T, NF, KC>& ahead, gptr<T> W, int N, int K, X x,
-                                            Out out) {
+// y[n] = sum_k W[n][k] x[k] for one row; x(k) gives x[k .. k + 3]; out(n, y) runs in one lane per feature.  NF
+// features per group and pass, so that many weight requests are in flight; the first pass takes what `ahead` holds.  It
+// stands in front of the loop: in a loop that also requests, the compiler has every use wait for whatever was requested
+// last - the next phase's weights, a memory round trip in each phase.
+template <typename T, int NF, int KC, class P, class X, class Out>
+__device__ __forceinline__ void row_product(const WeightAhead<T, NF, KC>& ahead, P W, int N, int K, X x, Out out) {
   const int ft = fresh_thread(), g = ft >> 4, ln = ft & 15;
-  for (int n0 = g; n0 < N; n0 += kGroups * NF) {
-    float acc[NF];
-#pragma unroll
-    for (int j = 0; j < NF; ++j) acc[j] = 0.f;
-    const bool first = n0 == g;
-    if (first) {
-#pragma unroll
-      for (int c = 0; c < KC; ++c) {
-        const int k = c * 64 + ln * 4;
-        if (k < K) {
-          const float4 xv = x(k);
-#pragma unroll
-          for (int j = 0; j < NF; ++j) acc[j] = fma4(ahead.w[c][j].f(), xv, acc[j]);
-        }
-      }
-    }
-    for (int k = (first ? KC * 64 : 0) + ln * 4; k < K; k += 64) {
+  const unsigned row = (unsigned)min(g, N - 1) * K;
+  auto rest_of_k = [&](float (&acc)[NF], int n0, int k_first) __attribute__((always_inline)) {
+#pragma unroll 1
+    for (int k = k_first + ln * 4; k < K; k += 64) {
       Quad<T> w[NF];
 #pragma unroll
-      for (int j = 0; j < NF; ++j) w[j].load(W + (unsigned)min(n0 + j * kGroups, N - 1) * K + k);
+      for (int j = 0; j < NF; ++j) w[j].load(W + (unsigned)first_feature(n0, j, N) * K + row + k);
       const float4 xv = x(k);
 #pragma unroll
       for (int j = 0; j < NF; ++j) acc[j] = fma4(w[j].f(), xv, acc[j]);
     }
+  };
+  auto emit = [&](const float (&acc)[NF], int n0) __attribute__((always_inline)) {
+    const float y = scatter16<NF>(acc, ln);
+    const int j = scatter_index<NF>(ln);
+    if (scatter_writer<NF>(ln) && own_feature(n0, j, N, g)) out(first_feature(n0, j, N) + g, y);
+  };
+  float acc[NF];
 #pragma unroll
-    for (int j = 0; j < NF; ++j) {
-      const float y = sum16(acc[j]);
-      if (n0 + j * kGroups < N) out(n0 + j * kGroups, y);
+  for (int j = 0; j < NF; ++j) acc[j] = 0.f;
+#pragma unroll
+  for (int c = 0; c < KC; ++c) {
+    const int k = c * 64 + ln * 4;
+    if (k < K) {
+      const float4 xv = x(k);
+#pragma unroll
+      for (int j = 0; j < NF; ++j) acc[j] = fma4(ahead.w[c][j].f(), xv, acc[j]);
     }
+  }
+  if (K > KC * 64) rest_of_k(acc, 0, KC * 64);
+  emit(acc, 0);
+#pragma unroll 1
+  for (int n0 = kGroups * NF; n0 < N; n0 += kGroups * NF) {
+    float more[NF];
+#pragma unroll
+    for (int j = 0; j < NF; ++j) more[j] = 0.f;
+    rest_of_k(more, n0, 0);
+    emit(more, n0);
   }
 }
 
@@ -189,32 +236,40 @@ template <typename T, int NF, class X>
 __device__ __forceinline__ void gate_up(const WeightAhead<T, NF, 1>& ag, const WeightAhead<T, NF, 1>& au, gptr<T> W,
                                         int F, int K, X x, float* act) {
   const int ft = fresh_thread(), g = ft >> 4, ln = ft & 15;
-  for (int n0 = g; n0 < F; n0 += kGroups * NF) {
-    float yg[NF], yu[NF];
-#pragma unroll
-    for (int j = 0; j < NF; ++j) { yg[j] = 0.f; yu[j] = 0.f; }
-    const bool first = n0 == g;
-    if (first && ln * 4 < K) {
-      const float4 xv = x(ln * 4);
-#pragma unroll
-      for (int j = 0; j < NF; ++j) { yg[j] = fma4(ag.w[0][j].f(), xv, yg[j]); yu[j] = fma4(au.w[0][j].f(), xv, yu[j]); }
-    }
-    for (int k = (first ? 64 : 0) + ln * 4; k < K; k += 64) {
+  const gptr<T> Wu = W + (unsigned)F * K;
+  const unsigned row = (unsigned)min(g, F - 1) * K;
+  auto rest_of_k = [&](float (&yg)[8], float (&yu)[8], int n0, int k_first) __attribute__((always_inline)) {
+#pragma unroll 1
+    for (int k = k_first + ln * 4; k < K; k += 64) {
       Quad<T> w0[NF], w1[NF];
 #pragma unroll
       for (int j = 0; j < NF; ++j) {
-        const int n = min(n0 + j * kGroups, F - 1);
-        w0[j].load(W + (unsigned)n * K + k); w1[j].load(W + (unsigned)(F + n) * K + k);
+        const unsigned at = (unsigned)first_feature(n0, j, F) * K;
+        w0[j].load(W + at + row + k); w1[j].load(Wu + at + row + k);
       }
       const float4 xv = x(k);
 #pragma unroll
       for (int j = 0; j < NF; ++j) { yg[j] = fma4(w0[j].f(), xv, yg[j]); yu[j] = fma4(w1[j].f(), xv, yu[j]); }
     }
+  };
+  auto emit = [&](const float (&yg)[8], const float (&yu)[8], int n0) __attribute__((always_inline)) {
+    const float a = scatter16<8>(yg, ln), b = scatter16<8>(yu, ln);
+    const int j = scatter_index<8>(ln);
+    if (scatter_writer<8>(ln) && j < NF && own_feature(n0, j, F, g)) act[first_feature(n0, j, F) + g] = rounded<T>(a / (1.0f + expf(-a)) * b);
+  };
+  float yg[8] = {}, yu[8] = {};   // NF of them
+  if (ln * 4 < K) {
+    const float4 xv = x(ln * 4);
 #pragma unroll
-    for (int j = 0; j < NF; ++j) {
-      const float a = sum16(yg[j]), b = sum16(yu[j]);
-      if (n0 + j * kGroups < F) act[n0 + j * kGroups] = rounded<T>(a / (1.0f + expf(-a)) * b);
-    }
+    for (int j = 0; j < NF; ++j) { yg[j] = fma4(ag.w[0][j].f(), xv, yg[j]); yu[j] = fma4(au.w[0][j].f(), xv, yu[j]); }
+  }
+  if (K > 64) rest_of_k(yg, yu, 0, 64);
+  emit(yg, yu, 0);
+#pragma unroll 1
+  for (int n0 = kGroups * NF; n0 < F; n0 += kGroups * NF) {
+    float mg[8] = {}, mu[8] = {};
+    rest_of_k(mg, mu, n0, 0);
+    emit(mg, mu, n0);
   }
 }
 
@@ -262,7 +317,9 @@ __device__ __forceinline__ void tile_product(gptr<T> W, int N, int K, const floa
 __device__ __forceinline__ float rms_scale(const float* h, int d, float eps) {   // by every wave for itself
   float ss = 0.f;
   for (int i = threadIdx.x & 63; i < d; i += 64) ss += h[i] * h[i];
-  return 1.0f / sqrtf(wave_sum(ss) / (float)d + eps);
+  // one step of Newton's on the hardware's reciprocal root: to the last bit or two like 1 / sqrtf, a tenth of its instructions
+  const float x = fmaf(wave_sum(ss), 1.0f / (float)d, eps), r = __builtin_amdgcn_rsqf(x);
+  return r * fmaf(-0.5f * x * r, r, 1.5f);
 }
 // a wave's own LDS stores before its own LDS loads
 __device__ __forceinline__ void wave_sync() {
@@ -376,6 +433,54 @@ __device__ __forceinline__ void head_attention(const SmallModel& m, gptr<T> kb, 
   }
 }
 
+// The same with the sequence's keys and values in LDS (rows k + n stride, v + n stride; position ctx - 1: kn, vn), head dims
+// 16, 32, 64; the same sums in the same order.
+template <typename T, int HD>
+__device__ __forceinline__ void lds_attention(const T* k, const T* v, int stride, int ctx, const float* qs, const T* kn, const T* vn,
+                                              float* sc, float* out) {
+  constexpr int QP = HD / 4, PARTS = 64 / QP;   // lanes per position; positions of a step
+  const int lane = fresh_thread() & 63, iq = lane % QP, part = lane / QP;
+  const float scale = 1.0f / sqrtf((float)HD);
+  auto quad = [](const T* p) { Quad<T> q; q.load(p); return q.f(); };
+  float mx = -INFINITY;
+  for (int n = lane; n < ctx; n += 64) {
+    const T* kp = n < ctx - 1 ? k + n * stride : kn;
+    float acc = 0.f;
+#pragma unroll 4
+    for (int i = 0; i < HD; i += 4) acc = fma4(quad(kp + i), *(const float4*)(qs + i), acc);
+    acc *= scale;
+    sc[n] = acc;
+    mx = fmaxf(mx, acc);
+  }
+  mx = wave_max(mx);
+  float sum = 0.f;
+  for (int n = lane; n < ctx; n += 64) {
+    const float p = expf(sc[n] - mx);
+    sc[n] = p;
+    sum += p;
+  }
+  sum = wave_sum(sum);
+  wave_sync();
+  const float inv = 1.0f / sum;
+  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+  auto add = [&](const T* vp, int n) {
+    const float4 f = quad(vp + 4 * iq);
+    const float p = sc[n];
+    acc.x = fmaf(p, f.x, acc.x); acc.y = fmaf(p, f.y, acc.y); acc.z = fmaf(p, f.z, acc.z); acc.w = fmaf(p, f.w, acc.w);
+  };
+#pragma unroll 4
+  for (int n = part; n < ctx - 1; n += PARTS) add(v + n * stride, n);
+  if (part == 0) add(vn, ctx - 1);
+  auto over_parts = [](float x) {
+    if constexpr (QP <= 4) x += dpp<kRor4>(x);
+    if constexpr (QP <= 8) x += dpp<kRor8>(x);
+    return sum_xor32(sum_xor16(x));
+  };
+  acc.x = over_parts(acc.x); acc.y = over_parts(acc.y); acc.z = over_parts(acc.z); acc.w = over_parts(acc.w);
+  if (part == 0)
+    *(float4*)(out + 4 * iq) = make_float4(rounded<T>(acc.x * inv), rounded<T>(acc.y * inv), rounded<T>(acc.z * inv), rounded<T>(acc.w * inv));
+}
+
 // Causal attention of the 16 rows of a tile (positions t0 .. t0 + 15) for one query head by one wave, head dim 16 KK, on
 // the fp32 matrix cores: 16 positions at a time, S^T = K Q^T (positions x rows, so that a lane owns one row's statistics),
 // online softmax, O^T = V^T P^T with the lane's own probabilities as operand.  Positions past the tile's last row are
@@ -454,7 +559,7 @@ __device__ __forceinline__ void tile_attention(gptr<T> kb, gptr<T> vb, unsigned 
 
 template <typename T>
 __global__ void __launch_bounds__(kThreads) k_small_prefill(SmallModel m, SmallPrefill a) {
-  extern __shared__ float smem[];
+  extern __shared__ __align__(16) float smem[];   // behind 8 bytes more than a multiple of 16, every 16-byte access would be split
   const int d = m.d, q = m.hq * m.hd, kvd = m.hkv * m.hd, nq = q + 2 * kvd, F = m.F, half = m.hd / 2;
   const int sa = max(d, q);
   float* h = smem;                      // [16][d]
@@ -609,16 +714,26 @@ __global__ void __launch_bounds__(kThreads) k_small_prefill(SmallModel m, SmallP
   }
 }
 
-template <typename T>
+// RES: the norms' gains and the sequence's keys and values stay in LDS for the whole call (where everything fits and the head
+// dim is 16, 32 or 64).  What it is for: read from memory, every phase's gains and keys were requested last and waited for
+// first, behind the weights requested ahead.
+template <typename T, bool RES>
 __global__ void __launch_bounds__(kThreads) k_small_decode(SmallModel m, SmallDecode a) {
-  extern __shared__ float smem[];
+  extern __shared__ __align__(16) float smem[];   // behind 8 bytes more than a multiple of 16, every 16-byte access would be split
   const int d = m.d, q = m.hq * m.hd, kvd = m.hkv * m.hd, nq = q + 2 * kvd, F = m.F, half = m.hd / 2, V = m.V;
   float* h = smem;                       // [d]
   float* u = h + d;                      // [max(nq, F)] q / k / v, then the SwiGLU product
   float* at = u + max(nq, F);            // [q] attention output
-  float* hw = at + q;                    // [waves][2 hd] the wave's rotated query and key
-  float* noise = hw + kWaves * 2 * m.hd; // [V] the step's Gumbel noise
-  float* sc = noise + V;                 // [max(V, waves x ctx)] logits, then scores
+  constexpr int HW = RES ? 3 : 2;        // vectors of a wave: its rotated query and key (RES: and value)
+  float* hw = at + q;                    // [waves][HW hd]
+  float* noise = hw + kWaves * HW * m.hd; // [V] the step's Gumbel noise
+  const int v4 = RES ? (V + 3) & ~3 : V;
+  float* sc = noise + v4;                // [max(V, waves x ctx)] logits, then scores
+  // RES: [2 L + 1][d] gains; [L][2][ctx_max] rows of kv_row keys or values, 16 bytes apart from a multiple of the banks
+  float* gains = sc + ((max(V, kWaves * a.ctx_max) + 3) & ~3);
+  T* kv_lds = (T*)(gains + (2 * m.L + 1) * d);
+  const int kv_row = kvd + 16 / (int)sizeof(T);
+  T* lm_lds = kv_lds + 2 * m.L * a.ctx_max * kv_row;   // a.lm_resident: [V][d], 16-byte aligned (as every area in front)
   __shared__ float s_m[kWaves], s_l[kWaves], s_y[kWaves], s_z[kWaves];
   __shared__ int s_id[kWaves], s_tok, s_end;
   const int tid = threadIdx.x, wave = wave_index(tid), lane = tid & 63;
@@ -628,6 +743,34 @@ __global__ void __launch_bounds__(kThreads) k_small_decode(SmallModel m, SmallDe
   const unsigned own0 = (unsigned)a.P * a.Lp + (unsigned)s * a.N;   // cache row of the sequence's first generated token
   for (int i = tid; i < d; i += kThreads) h[i] = a.h_last[(unsigned)p * d + i];
   if (tid == 0) s_end = 0;
+  if constexpr (RES) {
+    for (int l = 0; l < m.L; ++l) {
+      const LayerPtrs w = layer_ptrs(m, l);
+      for (int i = tid; i < d; i += kThreads) {
+        gains[2 * l * d + i] = w.attn_norm[i];
+        gains[(2 * l + 1) * d + i] = w.ffn_norm[i];
+      }
+      for (int i = tid; i < len * (kvd / 4); i += kThreads) {
+        const int n = i / (kvd / 4), c = 4 * (i - n * (kvd / 4));
+        const unsigned o = ((unsigned)p * a.Lp + n) * kvd + c;
+#pragma unroll
+        for (int which = 0; which < 2; ++which) {
+          Quad<T> x;
+          x.load((gptr<T>)kv_base<T>(m, l, which) + o);
+          *(decltype(x.u)*)(kv_lds + (unsigned)(2 * l + which) * a.ctx_max * kv_row + n * kv_row + c) = x.u;
+        }
+      }
+    }
+    for (int i = tid; i < d; i += kThreads) gains[2 * m.L * d + i] = m.final_norm[i];
+    if (a.lm_resident) {
+#pragma unroll 8
+      for (int i = tid; i < V * d / 4; i += kThreads) {
+        Quad<T> x;
+        x.load(global<T>(m.lm_head) + 4 * (unsigned)i);
+        *(decltype(x.u)*)(lm_lds + 4 * i) = x.u;
+      }
+    }
+  }
   __syncthreads();
   // The noise of a step does not depend on the logits: the waves without a query head draw it during the last layer's
   // attention of that step (all waves, if every wave has one).
@@ -642,9 +785,12 @@ __global__ void __launch_bounds__(kThreads) k_small_decode(SmallModel m, SmallDe
         if (4 * b + j < V) noise[4 * b + j] = g[j];
     }
   };
-  auto normed = [&](gptr<float> gain, float scl) {
+  auto normed = [&](gptr<float> gain, int which, float scl) {   // norm `which`: 2 l, 2 l + 1, 2 L
     return [=](int k) {
-      const float4 hv = *(const float4*)(h + k), gv = load4(gain + k);
+      float4 gv;
+      if constexpr (RES) gv = *(const float4*)(gains + which * d + k);
+      else gv = load4(gain + k);
+      const float4 hv = *(const float4*)(h + k);
       return make_float4(rounded<T>(hv.x * scl * gv.x), rounded<T>(hv.y * scl * gv.y), rounded<T>(hv.z * scl * gv.z),
                          rounded<T>(hv.w * scl * gv.w));
     };
@@ -653,13 +799,38 @@ __global__ void __launch_bounds__(kThreads) k_small_decode(SmallModel m, SmallDe
   WeightAhead<T, 4, 1> w_qkv;
   w_qkv.request(global<T>(layer_ptrs(m, 0).wqkv), nq, d);
   draw_noise(0, 0);
+  static_assert(kWaves == 8, "one wave's result per lane of a half row");
+  auto best_of_waves = [&] {
+    BestAcc b;
+    b.y = s_y[lane & 7]; b.z = s_z[lane & 7]; b.id = s_id[lane & 7];
+    return best_half_row(b);
+  };
+  // The outputs of step `at` from the waves' results, which stand until the next logits: by one wave, while the others are in
+  // the next step's first attention.
+  auto write_outputs = [&](int at) {
+    if (wave != kWaves - 1) return;
+    const BestAcc b = best_of_waves();
+    Lse lse{s_m[lane & 7], s_l[lane & 7]};
+    lse = lse_merge(lse, Lse{dpp<kHalfMirror>(lse.m), dpp<kHalfMirror>(lse.l)});
+    lse = lse_merge(lse, Lse{dpp<kXor2>(lse.m), dpp<kXor2>(lse.l)});
+    lse = lse_merge(lse, Lse{dpp<kXor1>(lse.m), dpp<kXor1>(lse.l)});
+    if (lane == 0) {
+      const bool good = (unsigned)b.id < (unsigned)V;
+      a.out_tokens[(unsigned)s * a.N + at] = good ? b.id : -1;
+      a.out_logprobs[(unsigned)s * a.N + at] = good ? b.z - (lse.m + logf(lse.l)) : 0.f;
+    }
+  };
   int t = 0;
   for (;;) {
     // ---- the token of step t: logits, log-sum-exp, Gumbel-max
     {
-      WeightAhead<T, 8, 1> w_lm;
-      w_lm.request(lm, V, d);
-      row_product<T>(w_lm, lm, V, d, normed(global<float>(m.final_norm), rms_scale(h, d, m.eps)), [&](int n, float y) { sc[n] = y; });
+      auto logits = [&](auto W) __attribute__((always_inline)) {
+        WeightAhead<T, 16, 1> w_lm;
+        w_lm.request(W, V, d);
+        row_product<T>(w_lm, W, V, d, normed(global<float>(m.final_norm), 2 * m.L, rms_scale(h, d, m.eps)), [&](int n, float y) { sc[n] = y; });
+      };
+      if (RES && a.lm_resident) logits((const T*)lm_lds);
+      else logits(lm);
       __syncthreads();
       // every wave: the maximum of its logits, then the sum of exponentials around it, and its best perturbed score
       float mx = -INFINITY;
@@ -678,21 +849,9 @@ __global__ void __launch_bounds__(kThreads) k_small_decode(SmallModel m, SmallDe
       if (lane == 0) { s_m[wave] = mx; s_l[wave] = sum; s_y[wave] = best.y; s_z[wave] = best.z; s_id[wave] = best.id; }
       __syncthreads();
       if (wave == 0) {
-        static_assert(kWaves == 8, "one wave's result per lane of a half row");
-        const int w = lane & 7;
-        const Lse z{s_m[w], s_l[w]};
-        best.y = s_y[w]; best.z = s_z[w]; best.id = s_id[w];
-        best = best_half_row(best);
-        Lse lse = z;
-        lse = lse_merge(lse, Lse{dpp<kHalfMirror>(lse.m), dpp<kHalfMirror>(lse.l)});
-        lse = lse_merge(lse, Lse{dpp<kXor2>(lse.m), dpp<kXor2>(lse.l)});
-        lse = lse_merge(lse, Lse{dpp<kXor1>(lse.m), dpp<kXor1>(lse.l)});
+        best = best_of_waves();
         if (lane == 0) {
-          int tk = best.id;
-          float lp = best.z - (lse.m + logf(lse.l));
-          if ((unsigned)tk >= (unsigned)V) { tk = -1; lp = 0.f; }   // no score beat the initial one: the logits are not numbers
-          a.out_tokens[(unsigned)s * a.N + t] = tk;
-          a.out_logprobs[(unsigned)s * a.N + t] = lp;
+          const int tk = (unsigned)best.id < (unsigned)V ? best.id : -1;   // -1: no score beat the initial one: the logits are not numbers
           s_end = a.stop_token >= 0 && tk == a.stop_token;
           s_tok = tk < 0 ? 0 : tk;
         }
@@ -710,14 +869,49 @@ __global__ void __launch_bounds__(kThreads) k_small_decode(SmallModel m, SmallDe
       const gptr_mut<T> kb = kv_base<T>(m, l, 0), vb = kv_base<T>(m, l, 1);
       WeightAhead<T, 2, 1> w_o;
       w_o.request(global<T>(w.wo), d, q);
-      row_product<T>(w_qkv, global<T>(w.wqkv), nq, d, normed(w.attn_norm, rms_scale(h, d, m.eps)),
+      row_product<T>(w_qkv, global<T>(w.wqkv), nq, d, normed(w.attn_norm, 2 * l, rms_scale(h, d, m.eps)),
                   [&](int n, float y) { u[n] = w.bqkv ? y + w.bqkv[n] : y; });
       __syncthreads();
       if (l == m.L - 1) draw_noise(t, first_idle);
+      if (l == 0) write_outputs(t - 1);
+      WeightAhead<T, 6, 1> w_g, w_u;
+      auto request_gate_up = [&] {
+        w_g.request(global<T>(w.wgu), F, d);
+        w_u.request(global<T>(w.wgu) + (unsigned)F * d, F, d);
+      };
+      if constexpr (RES) {
+        request_gate_up();   // nothing of the attention waits behind them
+        for (int head = wave; head < m.hq; head += kWaves) {
+          const int kvh = head / rep;
+          float* qs = hw + wave * HW * m.hd;
+          T *kn = (T*)(qs + m.hd), *vn = (T*)(qs + 2 * m.hd);
+          T *kl = kv_lds + (unsigned)(2 * l) * a.ctx_max * kv_row + kvh * m.hd, *vl = kl + (unsigned)a.ctx_max * kv_row;
+          for (int e = fresh_thread() & 63; e < half; e += 64) {
+            const float q1 = u[head * m.hd + e], q2 = u[head * m.hd + e + half];
+            const float k1 = u[q + kvh * m.hd + e], k2 = u[q + kvh * m.hd + e + half];
+            qs[e] = rounded<T>(q1 * cs_pos.x - q2 * cs_pos.y); qs[e + half] = rounded<T>(q2 * cs_pos.x + q1 * cs_pos.y);
+            const T r1 = from_f32<T>(k1 * cs_pos.x - k2 * cs_pos.y), r2 = from_f32<T>(k2 * cs_pos.x + k1 * cs_pos.y);
+            const T w1 = from_f32<T>(u[q + kvd + kvh * m.hd + e]), w2 = from_f32<T>(u[q + kvd + kvh * m.hd + e + half]);
+            kn[e] = r1; kn[e + half] = r2;
+            vn[e] = w1; vn[e + half] = w2;
+            if (head == kvh * rep) {   // read from the next step on
+              kl[pos * kv_row + e] = r1; kl[pos * kv_row + e + half] = r2;
+              vl[pos * kv_row + e] = w1; vl[pos * kv_row + e + half] = w2;
+            }
+          }
+          wave_sync();
+          float *scw = sc + (unsigned)wave * a.ctx_max, *out = at + head * m.hd;
+          if (m.hd == 16) lds_attention<T, 16>(kl, vl, kv_row, ctx, qs, kn, vn, scw, out);
+          else if (m.hd == 32) lds_attention<T, 32>(kl, vl, kv_row, ctx, qs, kn, vn, scw, out);
+          else lds_attention<T, 64>(kl, vl, kv_row, ctx, qs, kn, vn, scw, out);
+          wave_sync();
+        }
+        __syncthreads();
+      } else {
       // a wave per query head: it rotates its query and, for itself, the new key
       for (int head = wave; head < m.hq; head += kWaves) {
         const int kvh = head / rep;
-        float* qs = hw + wave * 2 * m.hd;
+        float* qs = hw + wave * HW * m.hd;
         float* kn = qs + m.hd;
         float* vn = u + q + kvd + kvh * m.hd;
         for (int e = lane; e < half; e += 64) {
@@ -738,29 +932,29 @@ __global__ void __launch_bounds__(kThreads) k_small_decode(SmallModel m, SmallDe
                           vn, sc + (unsigned)wave * a.ctx_max, at + head * m.hd);
         wave_sync();
       }
-      WeightAhead<T, 6, 1> w_g, w_u;
-      w_g.request(global<T>(w.wgu), F, d);
-      w_u.request(global<T>(w.wgu) + (unsigned)F * d, F, d);
+      request_gate_up();
       __syncthreads();
+      }
       row_product<T>(w_o, global<T>(w.wo), d, q, [&](int k) { return *(const float4*)(at + k); }, [&](int n, float y) {
-        if ((tid & 15) == 0) h[n] += y;
+        h[n] += y;
       });
       WeightAhead<T, 2, 3> w_d;
       w_d.request(global<T>(w.wdown), d, F);
       __syncthreads();
       {
         // a group's gate and up features side by side: the product is taken in the lane
-        const auto x = normed(w.ffn_norm, rms_scale(h, d, m.eps));
+        const auto x = normed(w.ffn_norm, 2 * l + 1, rms_scale(h, d, m.eps));
         gate_up<T>(w_g, w_u, global<T>(w.wgu), F, d, x, u);
       }
       w_qkv.request(global<T>(layer_ptrs(m, l + 1 < m.L ? l + 1 : 0).wqkv), nq, d);   // after the last layer: the next step's first
       __syncthreads();
       row_product<T>(w_d, global<T>(w.wdown), d, F, [&](int k) { return *(const float4*)(u + k); }, [&](int n, float y) {
-        if ((tid & 15) == 0) h[n] += y;
+        h[n] += y;
       });
       __syncthreads();
     }
   }
+  write_outputs(t);
   // an ended sequence's row goes on as padding
   for (int i = t + 1 + tid; i < a.N; i += kThreads) {
     a.out_tokens[(unsigned)s * a.N + i] = a.stop_token;
@@ -775,17 +969,23 @@ size_t prefill_lds(const SmallModel& m, int T) {
   if (u < 16 + kWaves * 32) u = 16 + kWaves * 32;
   return (kRows * d + kRows * (d > q ? d : q) + u + (size_t)kWaves * T) * sizeof(float);
 }
-size_t decode_lds(const SmallModel& m, int ctx_max) {
-  const size_t d = m.d, q = (size_t)m.hq * m.hd, nq = q + 2 * (size_t)m.hkv * m.hd, F = m.F, V = m.V;
+size_t decode_lds(const SmallModel& m, int ctx_max, bool res, size_t elt) {
+  const size_t d = m.d, q = (size_t)m.hq * m.hd, kvd = (size_t)m.hkv * m.hd, nq = q + 2 * kvd, F = m.F, V = m.V;
   const size_t sc = (size_t)kWaves * ctx_max;
-  return (d + (nq > F ? nq : F) + q + kWaves * 2 * (size_t)m.hd + V + (V > sc ? V : sc)) * sizeof(float);
+  if (!res) return (d + (nq > F ? nq : F) + q + kWaves * 2 * (size_t)m.hd + V + (V > sc ? V : sc)) * sizeof(float);
+  const auto four = [](size_t n) { return (n + 3) & ~(size_t)3; };
+  return (d + (nq > F ? nq : F) + q + kWaves * 3 * (size_t)m.hd + four(V) + four(V > sc ? V : sc) + (2 * (size_t)m.L + 1) * d) * sizeof(float) +
+         2 * (size_t)m.L * ctx_max * (kvd * elt + 16);
 }
 constexpr size_t kLdsLimit = 150 * 1024;
+constexpr size_t kDecodeLds = 159 * 1024;   // a workgroup has its compute unit to itself
 
 template <typename T> hipError_t set_lds() {
   hipError_t e = hipFuncSetAttribute((const void*)k_small_prefill<T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsLimit);
   if (e != hipSuccess) return e;
-  return hipFuncSetAttribute((const void*)k_small_decode<T>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsLimit);
+  e = hipFuncSetAttribute((const void*)k_small_decode<T, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kDecodeLds);
+  if (e != hipSuccess) return e;
+  return hipFuncSetAttribute((const void*)k_small_decode<T, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsLimit);
 }
 hipError_t set_lds_once(int dtype) {
   static bool done[2] = {false, false};
@@ -802,7 +1002,7 @@ bool small_rows_fit(const SmallModel& m, size_t cache_rows, size_t prompt_rows, 
   return small_offsets_fit(m.d, (uint64_t)m.hq * m.hd, (uint64_t)m.hkv * m.hd, cache_rows, prompt_rows, io_elems);
 }
 bool small_prefill_fits(const SmallModel& m, int T) { return prefill_lds(m, T) <= kLdsLimit; }
-bool small_decode_fits(const SmallModel& m, int ctx_max) { return decode_lds(m, ctx_max) <= kLdsLimit; }
+bool small_decode_fits(const SmallModel& m, int ctx_max) { return decode_lds(m, ctx_max, false, 4) <= kLdsLimit; }
 
 hipError_t small_prefill(int dtype, const SmallModel& m, const SmallPrefill& args, int n_seq, hipStream_t st) {
   if (n_seq <= 0 || args.T <= 0 || !small_prefill_fits(m, args.T)) return hipErrorInvalidValue;
@@ -821,13 +1021,20 @@ hipError_t small_prefill(int dtype, const SmallModel& m, const SmallPrefill& arg
   }
   return hipSuccess;
 }
-hipError_t small_decode(int dtype, const SmallModel& m, const SmallDecode& a, int S, hipStream_t st) {
-  if (S <= 0 || !small_decode_fits(m, a.ctx_max)) return hipErrorInvalidValue;
+hipError_t small_decode(int dtype, const SmallModel& m, const SmallDecode& args, int S, hipStream_t st) {
+  if (S <= 0 || !small_decode_fits(m, args.ctx_max)) return hipErrorInvalidValue;
+  SmallDecode a = args;
   const hipError_t e = set_lds_once(dtype);
   if (e != hipSuccess) return e;
-  const size_t lds = decode_lds(m, a.ctx_max);
-  if (dtype == SAPO_DTYPE_F32) return launch(KID_SMALL, k_small_decode<float>, dim3(S), dim3(kThreads), lds, st, m, a);
-  return launch(KID_SMALL, k_small_decode<bf16>, dim3(S), dim3(kThreads), lds, st, m, a);
+  const size_t elt = dtype == SAPO_DTYPE_F32 ? 4 : 2;
+  const bool res = (m.hd == 16 || m.hd == 32 || m.hd == 64) && decode_lds(m, a.ctx_max, true, elt) <= kDecodeLds;
+  size_t lds = decode_lds(m, a.ctx_max, res, elt);
+  const size_t head = (size_t)m.V * m.d * elt;   // the LM head too, where it fits behind the rest
+  a.lm_resident = res && head <= kDecodeLds - lds;
+  if (a.lm_resident) lds += head;
+  auto go = [&](auto kernel) { return launch(KID_SMALL, kernel, dim3(S), dim3(kThreads), lds, st, m, a); };
+  if (dtype == SAPO_DTYPE_F32) return res ? go(k_small_decode<float, true>) : go(k_small_decode<float, false>);
+  return res ? go(k_small_decode<bf16, true>) : go(k_small_decode<bf16, false>);
 }
 
 }  // namespace sapo

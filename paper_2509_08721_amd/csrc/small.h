@@ -45,6 +45,7 @@ struct SmallDecode {
   int32_t* out_tokens;     // [S, N]
   float* out_logprobs;
   int32_t* out_lengths;    // optional [S]
+  bool lm_resident = false;   // set by the launcher: the LM head is kept in LDS
 };
 bool small_rows_fit(const SmallModel& m, size_t cache_rows, size_t prompt_rows, size_t io_elems);
 bool small_prefill_fits(const SmallModel& m, int T);

@@ -76,6 +76,32 @@ def test_small_rollouts(name, P, G, Lp, N):
         assert st < 0 or torch.equal(a[2], b[2])
 
 
+@pytest.mark.parametrize("P,G,Lp,N", [(2, 2, 18, 9), (1, 3, 30, 45), (2, 1, 380, 21)])
+def test_small_rollouts_by_what_fits_in_lds(P, G, Lp, N):
+    """A sequence's keys and values and the LM head in LDS (contexts of 27), the keys and values alone (75), neither (401)."""
+    shape = replace(W.TINY, max_seq=512)
+    small, generic = handles(shape, 21)
+    prompts = torch.from_numpy(np.random.default_rng(Lp).integers(0, shape.vocab, (P, Lp)).astype(np.int32)).cuda()
+    assert kernels_of(lambda: sapo.sapo_rollout_generate(small, prompts, G, N, 1.0, 8)) == {"k_small"}
+    a = sapo.sapo_rollout_generate(small, prompts, G, N, 1.0, 8)
+    b = sapo.sapo_rollout_generate(generic, prompts, G, N, 1.0, 8)
+    assert torch.equal(a[0], b[0]) and float((a[1] - b[1]).abs().max()) <= 2e-5
+
+
+@pytest.mark.parametrize("hd", [12, 16, 32, 64])
+def test_small_bf16_rollouts_are_scored_alike(hd):
+    """bf16: a rollout's log-probs are those that scoring gives its tokens (roundings to bf16 may fall either way)."""
+    shape = replace(W.TINY, dtype="bf16", head_dim=hd, d_model=64 if hd != 12 else 48)
+    small, _ = handles(shape, 22)
+    prompts = torch.from_numpy(np.random.default_rng(hd).integers(0, shape.vocab, (2, 13)).astype(np.int32)).cuda()
+    tok, lp = sapo.sapo_rollout_generate(small, prompts, 3, 30, 1.0, 9)
+    seqs = torch.cat([prompts.repeat_interleave(3, 0), tok], 1).contiguous()
+    mask = torch.zeros_like(seqs, dtype=torch.uint8)
+    mask[:, 13:] = 1
+    ref = sapo.sapo_score_logprobs(small, seqs, mask, torch.zeros(6, device="cuda"), 3)[0][:, 13:]
+    assert float((ref - lp).abs().max()) <= 2e-2
+
+
 def test_small_bf16_follows_the_generic_kernels():
     shape = replace(W.TINY, dtype="bf16")
     small, generic = handles(shape, 13)
