@@ -492,12 +492,34 @@ static hipError_t launch_few_r(const SkinnyArgs& a, hipStream_t st) {
 
 // Blocking (feature tiles x token groups) of a STORE or RESID launch with several token blocks.  With 4 x 4 a narrow output leaves
 // compute units idle (1.5B QKV at 256 rows: 128 workgroups of 393 KB); two tiles per workgroup double the workgroups at
-// 295 KB each.  K above 2048 or a number of tiles that is no multiple of 4: 2 x 2 where the output is a residual.
-enum WideTile { WIDE_1X1, WIDE_2X2, WIDE_2X4, WIDE_4X4 };
+// 295 KB each.  Of these as few token groups as still give every workgroup a compute unit of its own: each takes in less.
+// us per step with 4 groups, 2 and 1, 0.5B: O projection 72 rows (56, 112, 224 workgroups) 909, 886, 870; 192 rows (84, 168, 336)
+// 1012, 993, 1005; 256 rows (112, 224, 448) 1076, 1056, 1072; QKV 72 rows (72, 144, 288) 909, 892, 900; 192 rows (108, 216)
+// 1012, 997; 256 rows (144, 288) 1076, 1082.  1.5B: O 96 rows (96, 192, 384) 1598, 1555, 1584; 192 rows (144, 288) 1924, 1961; QKV
+// 96 rows (128, 256, 512) 1598, 1557, 1613; 192 rows (192, 384) 1924, 1946.
+// K above 2048 or a number of tiles that is no multiple of 4: 2 x 2 where the output is a residual.
+enum WideTile { WIDE_1X1, WIDE_2X1, WIDE_2X2, WIDE_2X4, WIDE_4X4 };
 static WideTile wide_tile(int n_rows, int mode, int N, int K) {
-  const int tiles = N / 16;
-  if (tiles % 4 == 0 && (mode == SKM_STORE || K <= 2048)) return tiles / 4 * ((n_rows + 63) / 64) < 192 ? WIDE_2X4 : WIDE_4X4;
+  const int tiles = N / 16, blocks = (n_rows + 63) / 64, cu = n_compute_units();
+  if (tiles % 4 == 0 && (mode == SKM_STORE || K <= 2048)) {
+    if (tiles / 4 * blocks >= 192) return WIDE_4X4;
+    const int by_two = tiles / 2 * blocks;
+    return 4 * by_two <= cu ? WIDE_2X1 : 2 * by_two <= cu ? WIDE_2X2 : WIDE_2X4;
+  }
   return mode != SKM_STORE && tiles % 2 == 0 ? WIDE_2X2 : WIDE_1X1;
+}
+// Its launch.  R: with K up to 1024 all of a wave's k steps in one round.
+template <int MODE>
+static hipError_t launch_wide(WideTile wide, const SkinnyArgs& a, int per_wave, hipStream_t st) {
+  switch (wide) {
+    case WIDE_2X1: return per_wave <= 4 ? launch_skinny<2, 1, 4, 4, MODE>(a, st) : launch_skinny<2, 1, 4, 3, MODE>(a, st);
+    case WIDE_2X2:
+      return per_wave <= 4 ? launch_skinny<2, 2, 2, 4, MODE>(a, st) : per_wave <= 8 ? launch_skinny<2, 2, 2, 3, MODE>(a, st)
+                                                                                     : launch_skinny<2, 2, 2, 9, MODE>(a, st);
+    case WIDE_2X4: return launch_skinny<2, 4, 1, 3, MODE>(a, st);
+    case WIDE_4X4: return launch_skinny<4, 4, 1, 3, MODE>(a, st);
+    default: return hipErrorInvalidValue;
+  }
 }
 // 16-feature tiles that a workgroup of the launch below reads, as a power of two: what the block numbering calls a unit.
 static int skinny_unit_log2(int n_rows, int mode, int N, int K) {
@@ -542,23 +564,16 @@ hipError_t d_gemm_skinny(const SkinnyArgs& a, int mode, hipStream_t st) {
     return launch_groups<2, 6, SKM_SWIGLU>(a, groups, st);
   }
   const WideTile wide = multi ? wide_tile(a.n_rows, mode, a.N, a.K) : WIDE_1X1;
-  if (mode == SKM_RESID_X32) {
-    if (wide == WIDE_2X4) return launch_skinny<2, 4, 1, 3, SKM_RESID_X32>(a, st);
-    if (wide == WIDE_4X4) return launch_skinny<4, 4, 1, 3, SKM_RESID_X32>(a, st);
-    return wide == WIDE_2X2 ? launch_skinny<2, 2, 2, 9, SKM_RESID_X32>(a, st) : hipErrorInvalidValue;
-  }
+  if (mode == SKM_RESID_X32) return launch_wide<SKM_RESID_X32>(wide, a, per_wave, st);
   // one token block, more 16-token workgroups than compute units (0.5B QKV: 72 tiles x 4 = 288): some compute
   // units would get two workgroups and ingest twice; 32-token workgroups (144 of them, 86 KB each) keep it one each
   const bool tg2 = !multi && tiles * groups > 256;
   if (mode == SKM_STORE) {
-    if (wide == WIDE_2X4) return launch_skinny<2, 4, 1, 3, SKM_STORE>(a, st);
-    if (wide == WIDE_4X4) return launch_skinny<4, 4, 1, 3, SKM_STORE>(a, st);
+    if (wide != WIDE_1X1) return launch_wide<SKM_STORE>(wide, a, per_wave, st);
     if (tg2) return per_wave <= 4 ? launch_pairs<4, SKM_STORE>(a, groups, st) : launch_pairs<8, SKM_STORE>(a, groups, st);
     return per_wave <= 4 ? launch_singles<4, SKM_STORE>(a, groups, st) : launch_singles<8, SKM_STORE>(a, groups, st);
   }
-  if (wide == WIDE_2X4) return launch_skinny<2, 4, 1, 3, SKM_RESID>(a, st);
-  if (wide == WIDE_4X4) return launch_skinny<4, 4, 1, 3, SKM_RESID>(a, st);
-  if (wide == WIDE_2X2) return launch_skinny<2, 2, 2, 9, SKM_RESID>(a, st);
+  if (wide != WIDE_1X1) return launch_wide<SKM_RESID>(wide, a, per_wave, st);
   if (tg2 && per_wave <= 4) return launch_pairs<4, SKM_RESID>(a, groups, st);
   if (tg2 && per_wave <= 8) return launch_pairs<8, SKM_RESID>(a, groups, st);
   if (per_wave <= 4) return launch_singles<4, SKM_RESID>(a, groups, st);

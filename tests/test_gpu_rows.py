@@ -25,6 +25,7 @@ pytestmark = pytest.mark.gpu
     (1664, 128, 131, 0.02),     # 52 blocks, 4; 52 parts of the sums of squares
     (2176, 192, 254, 0.02),     # 68 blocks, 5, the last tile three
     (3200, 64, 70, 0.01),       # two blocks per part of the sums of squares
+    (1280, 128, 100, 0.02),     # O projection: two tiles x two token groups; QKV: two x one, K in two rounds
     (3200, 64, 193, 0.01),      # O projection: four tiles x four token groups per workgroup
 ]] + [                          # O projection: K of 2304, two workgroups of two token groups per block, each with its sums
     (256, 320, 65, 0.05, (36, 4)), (640, 192, 150, 0.02, (36, 4)), (128, 64, 256, 0.05, (36, 4))])
