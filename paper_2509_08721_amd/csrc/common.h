@@ -398,10 +398,15 @@ struct Prefetch {
   int KS = 0, n_tiles = 0, nt_log2 = 0, ks1 = 0;   // ks1 = 0: nothing
 };
 constexpr int kPrefetchKb = 18;   // blocks of 1 KiB that a prefetching wave has in flight
+// In the gate/up launch of at most 16 rows half of that: its own workgroups take in 57 KB, and one that prefetched 144 KB was
+// the last to end.  us per step with 18 and 9, 0.5B: 1 row 588, 570; 16 rows 602, 585; 1.5B: 1126, 1110; 1196, 1167.  With 12 or 7
+// within 3 of 9.  Elsewhere 18: gate/up of 32 rows 614, 621; attention 1 row 588, 606 (its few workgroups' dependent loads wait
+// longer behind more requests); down 64 rows 658, 677.
+constexpr int kPrefetchKbFew = 9;
 // workgroups of `waves` waves for it, a multiple of 8
-inline int prefetch_blocks(const Prefetch& pf, int waves) {
+inline int prefetch_blocks(const Prefetch& pf, int waves, int per_wave = kPrefetchKb) {
   const long kb = (long)pf.ks1 * pf.n_tiles;
-  return (int)((kb + waves * kPrefetchKb - 1) / (waves * kPrefetchKb) + 7) / 8 * 8;
+  return (int)((kb + waves * per_wave - 1) / (waves * per_wave) + 7) / 8 * 8;
 }
 // All of a weight matrix, or the leading blocks of every tile where it is more than the L2s hold next to everything else
 // (32 MB: 1.5B gate/up, 55 MB, of which half: 73.9 ms per call of 64 rows against 76.6 with all and 74.6 with none).
@@ -422,20 +427,20 @@ typedef unsigned int prefetch_u32x4 __attribute__((ext_vector_type(4)));
 // whose workgroups will read the weights (block ids are dealt round-robin): XCD x prefetches the tiles of the units
 // x, x + 8, ... of the consumer.  0.5B, 64 rows: gate/up 8.8 -> 6.8 us, down 7.4 -> 6.3, attention (which carries
 // gate/up's 17 MB on the compute units it leaves idle) 5.8 -> 7.0; on the wrong XCD the gain is lost.
-// A wave asks for kPrefetchKb blocks of 1 KiB at once and waits for them once: with 8 in flight and several rounds the
+// A wave asks for KB blocks of 1 KiB at once and waits for them once: with 8 in flight and several rounds the
 // launch that carries them got longer by what the consumer gained.
 // ---------------------------------------------------------------------------------------
-template <int NW>   // waves of a workgroup
+template <int NW, int KB = kPrefetchKb>   // waves of a workgroup
 __device__ __forceinline__ void prefetch_role(const Prefetch& pf, int block, int n_blocks) {
   const int xcd = block & 7, wv = (block >> 3) * NW + wave_index(threadIdx.x), nw = (n_blocks >> 3) * NW;   // waves per XCD
   const uint4* base = pf.p + (threadIdx.x & 63);
   prefetch_u32x4 all = {0, 0, 0, 0};
   const int n_units = pf.n_tiles >> pf.nt_log2, mine = ((n_units - xcd + 7) >> 3) << pf.nt_log2;   // tiles of this XCD
   const int span = pf.ks1, total = mine * span, nt1 = (1 << pf.nt_log2) - 1;
-  for (int k = wv; k < total; k += nw * kPrefetchKb) {
-    prefetch_u32x4 v[kPrefetchKb];
+  for (int k = wv; k < total; k += nw * KB) {
+    prefetch_u32x4 v[KB];
 #pragma unroll
-    for (int r = 0; r < kPrefetchKb; ++r) {
+    for (int r = 0; r < KB; ++r) {
       const int kk = k + r * nw;
       if (kk < total) {
         const int m = kk / span, tile = ((((m >> pf.nt_log2) << 3) + xcd) << pf.nt_log2) + (m & nt1);
@@ -445,7 +450,7 @@ __device__ __forceinline__ void prefetch_role(const Prefetch& pf, int block, int
       }
     }
 #pragma unroll
-    for (int r = 0; r < kPrefetchKb; ++r) all |= v[r];
+    for (int r = 0; r < KB; ++r) all |= v[r];
   }
   asm volatile("" ::"v"(all));   // the loads are wanted for what they leave behind
 }

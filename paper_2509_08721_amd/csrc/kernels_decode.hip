@@ -69,11 +69,12 @@ __device__ __forceinline__ float ssq_scale(const float* s_part, int tok_local, i
   return 1.0f / sqrtf(s / (float)norm_dim + eps);
 }
 
+template <int KB = kPrefetchKb>
 __device__ __forceinline__ void prefetch_behind(const SkinnyArgs& a, int first) {
   const int block = (int)blockIdx.x - first;
   if (block < 0) return;
-  if (block < a.pf_blocks) prefetch_role<8>(a.pf, block, a.pf_blocks);
-  else prefetch_role<8>(a.pf2, block - a.pf_blocks, (int)gridDim.x - first - a.pf_blocks);
+  if (block < a.pf_blocks) prefetch_role<8, KB>(a.pf, block, a.pf_blocks);
+  else prefetch_role<8, KB>(a.pf2, block - a.pf_blocks, (int)gridDim.x - first - a.pf_blocks);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -385,7 +386,7 @@ __global__ void __launch_bounds__(512) k_skinny_few(const uint4* Wp_, const uint
   const int unit = (j / PT) * 8 + (blockIdx.x & 7);
   if (unit >= n_units) {
     const int first = (n_units + 7) / 8 * 8 * PT;
-    prefetch_behind(a_rest, first);
+    prefetch_behind<MODE == SKM_SWIGLU ? kPrefetchKbFew : kPrefetchKb>(a_rest, first);
     return;
   }
   const int row = lane & 15, kg = lane >> 4;
@@ -477,7 +478,7 @@ __global__ void __launch_bounds__(512) k_skinny_few(const uint4* Wp_, const uint
 
 template <int FR, int R, int MODE>
 static hipError_t launch_few(SkinnyArgs a, hipStream_t st) {
-  a.pf_blocks = prefetch_blocks(a.pf, 8);
+  a.pf_blocks = prefetch_blocks(a.pf, 8, MODE == SKM_SWIGLU ? kPrefetchKbFew : kPrefetchKb);
   const int units = a.N / (MODE == SKM_SWIGLU ? 32 : 16);
   return launch(KID_GEMM_SKINNY, k_skinny_few<FR, R, MODE>, dim3((units + 7) / 8 * 8 * (16 / FR) + a.pf_blocks + prefetch_blocks(a.pf2, 8)), dim3(512), 0, st, a.Wp, a.Xp,
                 a.ssq_in, a.h, a.gain_next, a.N, a.K, a.n_rows, a.ssq_parts, a);
