@@ -9,6 +9,7 @@
 // log-prob tolerances (with bf16 activations the rounding points alone put the 1.5B-class model's
 // logits 6e-2 away from the definition).
 #include "tiles.h"
+#include "ranges.h"
 #include <algorithm>
 #include <type_traits>
 
@@ -120,28 +121,8 @@ constexpr int kRing = 3;                                            // stages of
 constexpr int ring_bytes(int H) { return kRing * 4 * H * 1024; }     // 4 H fragments of 1 KiB per stage
 constexpr int kBigLds = ring_bytes(4);
 
-// Block id -> (feature tile bx, token tile by).  Block ids are dealt round-robin to the 8 XCDs, each
-// with its own L2.  With 8 or more token tiles XCD c owns the token tiles 8 y' + c and walks them in
-// supertiles of 8 token tiles x 8 feature tiles (feature tiles fastest), the 64 workgroups it runs at
-// a time.  With fewer token tiles XCD c owns the feature tiles 8 x' + c instead and walks each one's
-// token tiles back to back, so every weight tile is fetched into one L2 only.
-__device__ __forceinline__ bool big_raster(int NX, int NY, int& bx, int& by) {
-  const int b = blockIdx.x, xcd = b & 7, j = b >> 3;
-  if (NY < 8) {
-    by = j % NY;
-    bx = (j / NY) * 8 + xcd;
-    return bx < NX;
-  }
-  const int NXs = (NX + 7) >> 3;
-  const int sti = j >> 6, w = j & 63;
-  bx = (sti % NXs) * 8 + (w & 7);
-  by = ((sti / NXs) * 8 + (w >> 3)) * 8 + xcd;
-  return bx < NX && by < NY;
-}
-static int big_grid(int NX, int NY) {
-  if (NY < 8) return 8 * NY * ((NX + 7) / 8);
-  return 8 * ((NX + 7) / 8) * ((((NY + 7) / 8) + 7) / 8) * 64;
-}
+__device__ __forceinline__ bool big_raster(int NX, int NY, int& bx, int& by) { return tile_of_block(blockIdx.x, NX, NY, bx, by); }
+static int big_grid(int NX, int NY) { return tile_blocks(NX, NY); }
 
 // The k loop of one tile.  begin() requests the first two stages, run() multiplies all of them; a caller that walks several
 // tiles may call begin() for the next one before it is done with the accumulators, after a barrier (the ring is free
@@ -955,7 +936,7 @@ hipError_t m_gemm_qkv_rope(const void* Xp, const void* Wp, int M, int N, int K, 
     if (e != hipSuccess) return e;
     attr_done = true;
   }
-  const int NX = N / 128, NY = (M + 255) / 256, per_xcd = NY < 8 ? (NX + 7) / 8 * NY : (NY + 7) / 8 * NX;
+  const int NX = N / 128, NY = (M + 255) / 256, per_xcd = (NX * NY + 7) / 8;
   const int lds = per_xcd <= 20 ? kAloneLds : kQkvLds;
   const dim3 grid(big_grid(NX, NY));
   if (hd == 64)
@@ -1086,8 +1067,7 @@ __global__ void __launch_bounds__(256, 2) k_lmhead_score(const uint4* __restrict
   const int n_ft = V >> 7;
   const int n_groups = (n_ft + group - 1) / group;
   int bx, by;
-  if (!big_raster(n_groups, (max_rows + 255) >> 8, bx, by)) return;
-  if (by * 256 >= n_rows) return;
+  if (!big_raster(n_groups, (n_rows + 255) >> 8, bx, by)) return;
   const int ft_begin = bx * group, ft_end = min(n_ft, ft_begin + group);
   const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63;
   const int row0 = by * 256 + wave * 64 + (lane & 31);

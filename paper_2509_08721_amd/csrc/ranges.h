@@ -21,6 +21,24 @@ struct StageRows {
   constexpr int row(int i) const { return k_first + i > k_begin ? k_first + i : k_begin; }   // first stage: row i, clamped
 };
 
+// Block id -> (feature tile bx, token tile by) of the token-parallel products.  Block ids are dealt round-robin to the 8 XCDs, each
+// with its own L2.  XCD c takes the c-th eighth of the tiles in this order: panels of 8 token tiles, in a panel blocks of 8
+// feature tiles, in a block feature tiles fastest.  The 64 workgroups an XCD runs at a time then share 8 token tiles and 8
+// feature tiles, and every XCD has as many tiles as the others.  Whole token tiles dealt to the XCDs (what this replaces) leave
+// them unequal: 11 token tiles are two for three XCDs and one for five.  Scoring calls, us before and now, 0.5B: 9 x 301
+// tokens (11 token tiles) 4542 -> 4024, 24 x 200 (19) 6414 -> 5653, 17 x 700 (47) 11715 -> 10949, 64 x 768 (192) within 0.2 %; 1.5B: 9 x 301
+// 12258 -> 10277, 24 x 200 17066 -> 14602.  With the token tiles fastest in a panel 64 x 768 takes 1.4 % longer.
+constexpr int tile_blocks(int NX, int NY) { return (NX * NY + 7) / 8 * 8; }   // blocks of the launch
+constexpr bool tile_of_block(int id, int NX, int NY, int& bx, int& by) {
+  const int n = NX * NY, per = (n + 7) >> 3, j = id >> 3, t = (id & 7) * per + j;
+  if (j >= per || t >= n) return false;
+  const int panel = t / (8 * NX), w = t - panel * 8 * NX, rows = NY - panel * 8 < 8 ? NY - panel * 8 : 8;
+  const int block = w / (8 * rows), v = w - block * 8 * rows, cols = NX - block * 8 < 8 ? NX - block * 8 : 8, y = v / cols;
+  bx = block * 8 + v - y * cols;
+  by = panel * 8 + y;
+  return true;
+}
+
 // The small-decoder kernels index with 32 bits: K and V of a layer (cache_rows of kv values) and the call's tokens and
 // outputs (io_elems of 4 bytes) stay below 2^31 bytes, the rows a long prompt keeps between launches (prompt_rows of d
 // residual values, and of q query values) below 2^32 elements.

@@ -54,6 +54,32 @@ int main() {
 """)
 
 
+def test_every_tile_has_one_block_and_the_xcds_share_alike(tmp_path):
+    """Tiles of the token-parallel products over the blocks of a launch, and over a launch made for more token tiles than there
+    are (the scorer's): each tile once, no XCD (id % 8) with more than an eighth, rounded up."""
+    run(tmp_path, r"""
+int main() {
+  int bad = 0;
+  for (int NX : {1, 2, 7, 8, 9, 16, 36, 75, 76, 149, 1187})
+    for (int NY = 0; NY <= 70; NY += NY < 20 ? 1 : 7)
+      for (int more : {0, 5}) {
+        std::vector<int> seen(NX * NY, 0);
+        int per[8] = {};
+        for (int id = 0; id < tile_blocks(NX, NY + more); ++id) {
+          int bx = -1, by = -1;
+          if (!tile_of_block(id, NX, NY, bx, by)) continue;
+          if (bx < 0 || bx >= NX || by < 0 || by >= NY) { ++bad; printf("%d x %d block %d: %d %d\n", NX, NY, id, bx, by); continue; }
+          ++seen[by * NX + bx];
+          ++per[id & 7];
+        }
+        for (int s : seen) bad += s != 1;
+        for (int p : per) bad += p > (NX * NY + 7) / 8;
+      }
+  return bad != 0;
+}
+""")
+
+
 def test_buffers_that_share_a_byte_are_seen(tmp_path):
     """Which buffers the surrogate may not write while it reads them."""
     run(tmp_path, r"""
