@@ -1044,31 +1044,27 @@ hipError_t m_rmsnorm_x32(const float* h, const float* gain, float eps, void* out
 // Rastered like the GEMM over (256-row tiles) x (groups of 128-feature tiles): a workgroup
 // walks the tiles of its group for its 256 rows keeping a running (max, sum exp) per row, and the
 // one lane that sees a row's target id writes the target logit.  A second kernel merges the groups
-// in a fixed order.  partials: [n_groups][max_rows][2], then ztarget [max_rows].
+// in a fixed order.  partials: ztarget [max_rows], then [n_groups][n_rows][2]; the groups as ScoreGroups cuts them.
 // ---------------------------------------------------------------------------------------
-// 128-feature tiles of a group: 16, fewer when that leaves compute units idle (about half of max_rows are scored; with one
-// 256-row tile 16 would be 75 workgroups, 223 us whatever the number of rows)
-static int score_group(int max_rows, int V) {
-  int g = 16;
-  while (g > 1 && (long)((V / 128 + g - 1) / g) * ((max_rows / 2 + 255) / 256) < 512) g >>= 1;
-  return g;
+static int score_slots() { return 2 * n_compute_units(); }   // workgroups in flight
+size_t m_lmhead_score_partial_floats(int max_rows, int V) {
+  return (size_t)max_rows + 2 * (size_t)ScoreMost(V >> 7, max_rows, score_slots()).pairs;
 }
-static int score_groups(int max_rows, int V) { const int g = score_group(max_rows, V); return (V / 128 + g - 1) / g; }
-size_t m_lmhead_score_partial_floats(int max_rows, int V) { return (size_t)max_rows * (2 * score_groups(max_rows, V) + 1); }
 
 __global__ void __launch_bounds__(256, 2) k_lmhead_score(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp,
                                                          int max_rows, const int* __restrict__ n_rows_dev, int V, int K,
                                                          const int* __restrict__ row_seq_pos,
-                                                         const int32_t* __restrict__ tokens, int T, int group,
+                                                         const int32_t* __restrict__ tokens, int T, int slots,
                                                          float* __restrict__ partials) {
   constexpr int TJ = 2, H = 4;
   extern __shared__ uint4 smem[];
   const int n_rows = *n_rows_dev;
   const int n_ft = V >> 7;
-  const int n_groups = (n_ft + group - 1) / group;
+  const int row_tiles = (n_rows + 255) >> 8;
+  const ScoreGroups g(n_ft, row_tiles, slots);
   int bx, by;
-  if (!big_raster(n_groups, (n_rows + 255) >> 8, bx, by)) return;
-  const int ft_begin = bx * group, ft_end = min(n_ft, ft_begin + group);
+  if (!big_raster(g.groups, row_tiles, bx, by)) return;
+  const int ft_begin = bx * g.tiles, ft_end = min(n_ft, ft_begin + g.tiles);
   const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63;
   const int row0 = by * 256 + wave * 64 + (lane & 31);
   LseAcc lse[TJ];
@@ -1080,7 +1076,7 @@ __global__ void __launch_bounds__(256, 2) k_lmhead_score(const uint4* __restrict
     target[tj] = -1;
     if (row < n_rows) target[tj] = tokens[(size_t)row_seq_pos[2 * row] * T + row_seq_pos[2 * row + 1]];
   }
-  float* ztarget = partials + (size_t)max_rows * 2 * n_groups;
+  float* ztarget = partials;
   TileLoop<TJ, H> loop;
   loop.tokens(Xp, (n_rows + 31) >> 5, K >> 4, by * 8, 0);
   loop.features(Wp, K >> 4, ft_begin * 4, 0, K / (16 * H), smem);
@@ -1122,27 +1118,29 @@ __global__ void __launch_bounds__(256, 2) k_lmhead_score(const uint4* __restrict
     lse[tj].merge(__shfl_xor(lse[tj].m, 32, 64), __shfl_xor(lse[tj].l, 32, 64));
     const int row = row0 + tj * 32;
     if (lane < 32 && row < n_rows) {
-      float* p = partials + ((size_t)bx * max_rows + row) * 2;
+      float* p = partials + max_rows + ((size_t)bx * n_rows + row) * 2;
       p[0] = lse[tj].m; p[1] = lse[tj].l;
     }
   }
 }
 
 // A wave per row: lane l merges the groups l, l + 64, ... in order, then the lanes pairwise.
-__global__ void __launch_bounds__(256) k_lmhead_score_merge(const float* __restrict__ partials, int max_rows, int n_groups,
+__global__ void __launch_bounds__(256) k_lmhead_score_merge(const float* __restrict__ partials, int max_rows, int V, int slots,
                                                             const int* __restrict__ n_rows_dev, const int* __restrict__ row_seq_pos,
                                                             int T, float* __restrict__ out_logprobs) {
   const int row = blockIdx.x * 4 + wave_index(threadIdx.x), lane = threadIdx.x & 63;
-  if (row >= *n_rows_dev) return;
+  const int n_rows = *n_rows_dev;
+  if (row >= n_rows) return;
+  const int n_groups = ScoreGroups(V >> 7, (n_rows + 255) >> 8, slots).groups;
   LseAcc a; a.init();
   for (int s = lane; s < n_groups; s += 64) {
-    const float* p = partials + ((size_t)s * max_rows + row) * 2;
+    const float* p = partials + max_rows + ((size_t)s * n_rows + row) * 2;
     a.merge(p[0], p[1]);
   }
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) a.merge(__shfl_xor(a.m, o, 64), __shfl_xor(a.l, o, 64));
   if (lane != 0) return;
-  const float zt = partials[(size_t)max_rows * 2 * n_groups + row];
+  const float zt = partials[row];
   out_logprobs[(size_t)row_seq_pos[2 * row] * T + row_seq_pos[2 * row + 1]] = zt - (a.m + logf(a.l));
 }
 
@@ -1157,13 +1155,13 @@ hipError_t m_lmhead_score(const void* Xp, const void* Wp, int max_rows, const in
     if (e != hipSuccess) return e;
     attr_done = true;
   }
-  const int group = score_group(max_rows, V), n_groups = score_groups(max_rows, V);
-  const hipError_t e = launch(KID_LMHEAD_SCORE, k_lmhead_score, dim3(big_grid(n_groups, (max_rows + 255) / 256)), dim3(256),
-                              kBigLds, st, (const uint4*)Xp, (const uint4*)Wp, max_rows, n_rows_dev, V, K, row_seq_pos, tokens,
-                              T, group, partials);
+  const int slots = score_slots();
+  const unsigned blocks = (unsigned)((ScoreMost(V >> 7, max_rows, slots).blocks + 7) / 8 * 8);
+  const hipError_t e = launch(KID_LMHEAD_SCORE, k_lmhead_score, dim3(blocks), dim3(256), kBigLds, st, (const uint4*)Xp,
+                              (const uint4*)Wp, max_rows, n_rows_dev, V, K, row_seq_pos, tokens, T, slots, partials);
   if (e != hipSuccess) return e;
   return launch(KID_LMHEAD_SCORE_MERGE, k_lmhead_score_merge, dim3((max_rows + 3) / 4), dim3(256), 0, st, partials,
-                max_rows, n_groups, n_rows_dev, row_seq_pos, T, out_logprobs);
+                max_rows, V, slots, n_rows_dev, row_seq_pos, T, out_logprobs);
 }
 
 // ---------------------------------------------------------------------------------------

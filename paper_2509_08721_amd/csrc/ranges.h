@@ -39,6 +39,35 @@ constexpr bool tile_of_block(int id, int NX, int NY, int& bx, int& by) {
   return true;
 }
 
+// Groups that the LM-head scorer cuts the n_ft 128-feature tiles of the vocabulary into, each walked by one workgroup per row
+// tile: as few as fill whole rounds of the `slots` workgroups in flight, of at most 32 tiles each.  The number of row tiles is
+// that of the rows that are scored, which the device counts.  us per call before (groups of 16 tiles, halved while half of the
+// call's positions gave fewer than 512 workgroups) and now: 0.5B, 24 x 200 tokens 5653, 5378; 9 x 301 4024, 3921 (the scorer 496 us with
+// the row tiles dealt to the XCDs, now 312); 64 x 768 46.2 ms both; 1.5B, 24 x 200 14602, 14192.
+struct ScoreGroups {
+  int groups, tiles;   // their number, and the tiles of one (the last one may have fewer)
+  constexpr ScoreGroups(int n_ft, int row_tiles, int slots) : groups(0), tiles(1) {
+    if (row_tiles <= 0 || n_ft <= 0) return;
+    const int least = (n_ft + 31) / 32;
+    const int rounds = (least * row_tiles + slots - 1) / slots, fill = slots * rounds / row_tiles;   // fill >= least
+    const int most = fill < n_ft ? fill : n_ft;
+    tiles = (n_ft + most - 1) / most;
+    groups = (n_ft + tiles - 1) / tiles;
+  }
+};
+// Largest number of workgroups of a call that scores up to max_rows rows, and of (group, row) pairs, row tiles of 256
+struct ScoreMost {
+  long blocks, pairs;
+  constexpr ScoreMost(int n_ft, int max_rows, int slots) : blocks(0), pairs(0) {
+    for (int t = 1; t <= (max_rows + 255) / 256; ++t) {
+      const ScoreGroups g(n_ft, t, slots);
+      const long rows = (long)t * 256 < max_rows ? (long)t * 256 : max_rows, b = (long)g.groups * t, p = g.groups * rows;
+      if (b > blocks) blocks = b;
+      if (p > pairs) pairs = p;
+    }
+  }
+};
+
 // The small-decoder kernels index with 32 bits: K and V of a layer (cache_rows of kv values) and the call's tokens and
 // outputs (io_elems of 4 bytes) stay below 2^31 bytes, the rows a long prompt keeps between launches (prompt_rows of d
 // residual values, and of q query values) below 2^32 elements.
