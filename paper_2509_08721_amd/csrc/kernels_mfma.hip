@@ -867,7 +867,8 @@ int n_compute_units() {
 }
 // Tiles for few tokens.  A workgroup's time is what it has to take in, so the tile is the one whose fullest compute unit
 // takes in least: workgroups per unit x (tokens + features) of a tile; the large tiles' fetch (two stages ahead) counts
-// half as much again.  deep: one workgroup per unit, the whole LDS as its ring; otherwise two share it.
+// half as much again, and a little more: two tiles of 64 x 128 on a unit are faster than one of 128 x 128 (scoring calls, us, 0.5B: 301
+// tokens 1660 -> 1540, 2709 4024 -> 3767, 3600 4982 -> 4709; 1.5B: 128 tokens 2817 -> 2653, 1800 7570 -> 7156).  deep: one workgroup per unit, the whole LDS as its ring; otherwise two share it.
 enum { MID_FFN, MID_QKV64, MID_QKV128 };
 struct MidPick { int tile; bool deep; };   // tile: 0 = none of them, 1 = 32, 2 = 64 tokens x one wave's features, 3 = 64 x 128
 static MidPick pick_mid(int M, int N, int what) {
@@ -876,7 +877,7 @@ static MidPick pick_mid(int M, int N, int what) {
   auto load = [&](int tm, int tn, double weight) { return (double)((groups(tm, tn) + cu - 1) / cu) * (tm + tn) * weight; };
   MidPick best{0, true};
   if (getenv("SAPO_BIG_TILE")) return best;   // one of the large tiles is forced (measurement, tests)
-  double least = std::min(load(256, 128, 1.5), what == MID_FFN ? load(128, 128, 1.5) : 1e30);
+  double least = std::min(load(256, 128, 1.55), what == MID_FFN ? load(128, 128, 1.55) : 1e30);
   const int tm[4] = {0, 32, 64, 64}, tn[4] = {0, nb, nb, 128};
   for (int t = 1; t <= (what == MID_FFN ? 3 : 2); ++t) {
     const long g = groups(tm[t], tn[t]);
@@ -958,8 +959,11 @@ static bool big_prefers_small_tiles(int NX, int M) {
   const int forced = e ? atoi(e) : 0;
   if (forced == 128) return true;
   if (forced == 256) return false;
-  if (NX > 16) return false;   // wide outputs have rounds enough: the smaller tile only adds operand traffic per flop
   const long big = (long)NX * ((M + 255) / 256), small = (long)NX * ((M + 127) / 128);
+  // wide outputs: what the fullest compute unit multiplies, the smaller tile's operand traffic counted as 8 %.  Scoring calls, us
+  // with 256- and 128-token tiles of gate/up, 0.5B: 1600 tokens 2859, 2668; 1800 3060, 2983; 2250 3228, 3232 (6 and 12 half tiles: equal);
+  // 3600 4992, 4924; 4800 5531, 5592; 6000 6599, 6500; 1.5B: 2709 10304, 10461; 4800 14370, 14729.
+  if (NX > 16) return (small + n_cu - 1) / n_cu * 128 * 1.08 < (double)((big + n_cu - 1) / n_cu * 256);
   const long rounds_big = (big + 2 * n_cu - 1) / (2 * n_cu), rounds_small = (small + 3 * n_cu - 1) / (3 * n_cu);
   return rounds_small <= rounds_big;
 }
