@@ -809,20 +809,22 @@ __device__ __forceinline__ void qkv_epilogue(f32x16 (&acc)[NH * (HD / 32)][TJ], 
     }
   }
 }
-template <int HD>
-__global__ void __launch_bounds__(256, 2) k_gemm_qkv_rope(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, int M,
-                                                          int N, int K, QkvEpi ep) {
-  constexpr int TJ = 2, H = 4, NH = 128 / HD;   // heads of a tile
+template <int HD, int TJ>
+__global__ void __launch_bounds__(256, TJ == 2 ? 2 : 3) k_gemm_qkv_rope(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, int M,
+                                                                        int N, int K, QkvEpi ep) {
+  constexpr int H = 4, NH = 128 / HD, TM = 128 * TJ;   // heads and tokens of a tile
   extern __shared__ uint4 smem[];
   int bx, by;
-  if (!big_raster(N >> 7, (M + 255) >> 8, bx, by)) return;
+  if (!big_raster(N >> 7, (M + TM - 1) / TM, bx, by)) return;
   f32x16 acc[4][TJ];
   const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63;
-  const int tok0 = by * 256 + wave * 64 + (lane & 31);
-  float row_scale[TJ] = {1.f, 1.f};
+  const int tok0 = by * TM + wave * (32 * TJ) + (lane & 31);
+  float row_scale[TJ];
+#pragma unroll
+  for (int tj = 0; tj < TJ; ++tj) row_scale[tj] = 1.f;
   {
     TileLoop<TJ, H> loop;
-    loop.tokens(Xp, (M + 31) >> 5, K >> 4, by * 8, 0);
+    loop.tokens(Xp, (M + 31) >> 5, K >> 4, by * (4 * TJ), 0);
     loop.features(Wp, K >> 4, bx * 4, 0, K / (16 * H), smem);
     loop.begin();
     if (ep.ssq_in) row_scales<TJ>(ep.ssq_in, ep.ssq_parts, ep.ssq_halves, ep.norm_dim, ep.eps, tok0, M, row_scale);
@@ -865,10 +867,18 @@ int n_compute_units() {
   }
   return n_cu;
 }
+// SAPO_BIG_TILE=128 / 256 in the environment forces one of the large tiles (measurement, tests); read per call, so that a test
+// can switch it
+static int forced_tile() {
+  const char* e = getenv("SAPO_BIG_TILE");
+  const int t = e ? atoi(e) : 0;
+  return t == 128 || t == 256 ? t : 0;
+}
 // Tiles for few tokens.  A workgroup's time is what it has to take in, so the tile is the one whose fullest compute unit
 // takes in least: workgroups per unit x (tokens + features) of a tile; the large tiles' fetch (two stages ahead) counts
 // half as much again, and a little more: two tiles of 64 x 128 on a unit are faster than one of 128 x 128 (scoring calls, us, 0.5B: 301
-// tokens 1660 -> 1540, 2709 4024 -> 3767, 3600 4982 -> 4709; 1.5B: 128 tokens 2817 -> 2653, 1800 7570 -> 7156).  deep: one workgroup per unit, the whole LDS as its ring; otherwise two share it.
+// tokens 1660 -> 1540, 2709 4024 -> 3767, 3600 4982 -> 4709; 1.5B: 128 tokens 2817 -> 2653, 1800 7570 -> 7156).  deep:
+// one workgroup per unit, the whole LDS as its ring; otherwise two share it.
 enum { MID_FFN, MID_QKV64, MID_QKV128 };
 struct MidPick { int tile; bool deep; };   // tile: 0 = none of them, 1 = 32, 2 = 64 tokens x one wave's features, 3 = 64 x 128
 static MidPick pick_mid(int M, int N, int what) {
@@ -876,7 +886,7 @@ static MidPick pick_mid(int M, int N, int what) {
   auto groups = [&](int tm, int tn) { return (long)((M + tm - 1) / tm) * ((N + tn - 1) / tn); };
   auto load = [&](int tm, int tn, double weight) { return (double)((groups(tm, tn) + cu - 1) / cu) * (tm + tn) * weight; };
   MidPick best{0, true};
-  if (getenv("SAPO_BIG_TILE")) return best;   // one of the large tiles is forced (measurement, tests)
+  if (forced_tile() != 0) return best;
   double least = std::min(load(256, 128, 1.55), what == MID_FFN ? load(128, 128, 1.55) : 1e30);
   const int tm[4] = {0, 32, 64, 64}, tn[4] = {0, nb, nb, 128};
   for (int t = 1; t <= (what == MID_FFN ? 3 : 2); ++t) {
@@ -910,6 +920,14 @@ static hipError_t launch_qkv_mid(const uint4* X, const uint4* W, int M, int N, i
   return launch_mid(k_gemm_qkv_mid<HD, WM, D>, MidLoop<WM, 1, HD / 32, D>::kBytes, attr_done, big_grid(N / HD, (M + 32 * WM - 1) / (32 * WM)),
                     X, W, M, N, K, epi, st);
 }
+// 128-token instead of 256-token tiles by what the fullest compute unit multiplies, the smaller tile's operand traffic counted as
+// 8 %.  Scoring calls, us with 256- and 128-token tiles of gate/up, 0.5B: 1600 tokens 2859, 2668; 1800 3060, 2983; 2250 3228, 3232 (6
+// and 12 half tiles: equal); 3600 4992, 4924; 4800 5531, 5592; 6000 6599, 6500; 1.5B: 2709 10304, 10461; 4800 14370, 14729.  Of QKV,
+// 0.5B: 1800 tokens 3031, 2914; 2250 3266, 3146; 2709 3761, 3665; 8000 8134, 8081; 1.5B, 4800 14547, 14411.
+static bool half_tiles_leave_less(int NX, int M) {
+  const long cu = n_compute_units(), big = (long)NX * ((M + 255) / 256), small = (long)NX * ((M + 127) / 128);
+  return (double)((small + cu - 1) / cu * 128) * 1.08 < (double)((big + cu - 1) / cu * 256);
+}
 bool m_gemm_writes_halves(int M, int N) { return pick_mid(M, N, MID_FFN).tile != 0; }
 hipError_t m_gemm_qkv_rope(const void* Xp, const void* Wp, int M, int N, int K, const QkvEpi& epi, hipStream_t st) {
   if (M == 0) return hipSuccess;
@@ -931,39 +949,36 @@ hipError_t m_gemm_qkv_rope(const void* Xp, const void* Wp, int M, int N, int K, 
   constexpr int kAloneLds = 84 * 1024;
   static bool attr_done = false;
   if (!attr_done) {
-    hipError_t e = hipFuncSetAttribute((const void*)k_gemm_qkv_rope<64>, hipFuncAttributeMaxDynamicSharedMemorySize, kAloneLds);
+    hipError_t e = hipFuncSetAttribute((const void*)k_gemm_qkv_rope<64, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, kAloneLds);
     if (e == hipSuccess)
-      e = hipFuncSetAttribute((const void*)k_gemm_qkv_rope<128>, hipFuncAttributeMaxDynamicSharedMemorySize, kAloneLds);
+      e = hipFuncSetAttribute((const void*)k_gemm_qkv_rope<128, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, kAloneLds);
+    if (e == hipSuccess) e = hipFuncSetAttribute((const void*)k_gemm_qkv_rope<64, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, kBigLds);
+    if (e == hipSuccess) e = hipFuncSetAttribute((const void*)k_gemm_qkv_rope<128, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, kBigLds);
     if (e != hipSuccess) return e;
     attr_done = true;
   }
   const int NX = N / 128, NY = (M + 255) / 256, per_xcd = (NX * NY + 7) / 8;
+  auto go = [&](auto kernel, int ny, int lds) {
+    return launch(KID_GEMM_BIG, kernel, dim3(big_grid(NX, ny)), dim3(256), lds, st, (const uint4*)Xp, (const uint4*)Wp, M, N, K, epi);
+  };
+  if (forced_tile() != 0 ? forced_tile() == 128 : half_tiles_leave_less(NX, M)) {
+    const int ny = (M + 127) / 128;
+    return hd == 64 ? go(k_gemm_qkv_rope<64, 1>, ny, kBigLds) : go(k_gemm_qkv_rope<128, 1>, ny, kBigLds);
+  }
   const int lds = per_xcd <= 20 ? kAloneLds : kQkvLds;
-  const dim3 grid(big_grid(NX, NY));
-  if (hd == 64)
-    return launch(KID_GEMM_BIG, k_gemm_qkv_rope<64>, grid, dim3(256), lds, st, (const uint4*)Xp, (const uint4*)Wp, M, N, K,
-                  epi);
-  return launch(KID_GEMM_BIG, k_gemm_qkv_rope<128>, grid, dim3(256), lds, st, (const uint4*)Xp, (const uint4*)Wp, M, N, K,
-                epi);
+  return hd == 64 ? go(k_gemm_qkv_rope<64, 2>, NY, lds) : go(k_gemm_qkv_rope<128, 2>, NY, lds);
 }
 
 // 128-token tiles (three workgroups per compute unit) instead of 256-token tiles (two): for narrow outputs whose
 // 256-token tiles fill their last round of resident workgroups badly, when the half-size tiles need no more rounds
 // (64 x 384 tokens x 896 features: 672 tiles in 2 rounds of 512 become 1344 in 2 rounds of 768; O projection 86 ->
 // 70 us, the prompt's small launches 70 -> 58 us.  With one round more - 64 x 768: 4 against 3 - the down projection
-// lost 14 %, so that case keeps the large tile).  SAPO_BIG_TILE=128 / 256 in the environment forces one or the
-// other (measurement).
+// lost 14 %, so that case keeps the large tile).
 static bool big_prefers_small_tiles(int NX, int M) {
   const int n_cu = n_compute_units();
-  const char* e = getenv("SAPO_BIG_TILE");   // read per call, so that a test can switch it
-  const int forced = e ? atoi(e) : 0;
-  if (forced == 128) return true;
-  if (forced == 256) return false;
+  if (forced_tile() != 0) return forced_tile() == 128;
+  if (NX > 16) return half_tiles_leave_less(NX, M);
   const long big = (long)NX * ((M + 255) / 256), small = (long)NX * ((M + 127) / 128);
-  // wide outputs: what the fullest compute unit multiplies, the smaller tile's operand traffic counted as 8 %.  Scoring calls, us
-  // with 256- and 128-token tiles of gate/up, 0.5B: 1600 tokens 2859, 2668; 1800 3060, 2983; 2250 3228, 3232 (6 and 12 half tiles: equal);
-  // 3600 4992, 4924; 4800 5531, 5592; 6000 6599, 6500; 1.5B: 2709 10304, 10461; 4800 14370, 14729.
-  if (NX > 16) return (small + n_cu - 1) / n_cu * 128 * 1.08 < (double)((big + n_cu - 1) / n_cu * 256);
   const long rounds_big = (big + 2 * n_cu - 1) / (2 * n_cu), rounds_small = (small + 3 * n_cu - 1) / (3 * n_cu);
   return rounds_small <= rounds_big;
 }

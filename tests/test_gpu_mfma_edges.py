@@ -206,3 +206,26 @@ def test_value_pages_from_either_qkv_tile(sapo, kv_heads, head_dim, lens, T):
         os.environ.pop("SAPO_BIG_TILE", None)
     assert np.array_equal(out[None][0], out["256"][0]) and np.array_equal(out[None][1], out["256"][1])
     gw.close()
+
+
+@pytest.mark.parametrize("kv_heads,head_dim,lens,T", [(2, 64, [31, 8, 16, 1, 24, 30], 31), (1, 64, [45] * 6, 45), (2, 128, [12, 5, 50], 50),
+                                                      (2, 64, [129, 64], 129)])
+def test_pages_from_the_qkv_tile_of_128_tokens(sapo, kv_heads, head_dim, lens, T):
+    """QKV in 128-token tiles (values a token per lane) and in 256-token tiles: prompts that end inside a tile, at and one over
+    its edge, keys and values in one tile, both head dims.  What is generated from the pages agrees bit for bit."""
+    import os
+    from dataclasses import replace
+    shape = replace(W.MINI_BF16 if head_dim == 64 else W.MINI_BF16_HD128, n_kv_heads=kv_heads)
+    w = W.perturb_norm_gains(W.make_weights(shape, 56, std=0.05), 56)
+    gw = sapo.sapo_weights_create(shape, w)
+    prompts = np.random.default_rng(T).integers(0, shape.vocab, size=(len(lens), T)).astype(np.int32)
+    out = []
+    try:
+        for tile in ("128", "256"):
+            os.environ["SAPO_BIG_TILE"] = tile
+            toks, lps, _ = sapo.sapo_rollout_generate_ragged(gw, dev(prompts), lens, 2, 6, 1.0, 12)
+            out.append((toks.cpu().numpy(), lps.cpu().numpy()))
+    finally:
+        os.environ.pop("SAPO_BIG_TILE", None)
+    assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
+    gw.close()
