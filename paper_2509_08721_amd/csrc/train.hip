@@ -1643,17 +1643,22 @@ __device__ __forceinline__ void load_rows4(const float* __restrict__ base, size_
 }
 __device__ __forceinline__ float f4c(const float4& v, int c) { return c == 0 ? v.x : c == 1 ? v.y : c == 2 ? v.z : v.w; }
 
-// acc (rows = positions of `a`, 4 g + v; column = position of `b`, lane % 16) += a b^T over the head dim
-template <int HD>
+// Rows = positions of `a`, 4 g + v; column = position of `b`, lane % 16: a b^T over the head dim, in CH chains.  Four chains have a
+// quarter of the roundings at the sum's full size (the scores' rounding is most of the gradients' error where they lie hundreds
+// apart; 16 sets with scores to 450: error against 64 bits 4.1e-4 -> 2.9e-4 of a tensor's largest entry).  With one and two pieces,
+// whose operands' rounding is far larger and turns another last bit into another rounding downstream, one chain.
+template <int HD, int CH>
 __device__ __forceinline__ f32x4_t dot_rows(const float4 (&a)[HD / 16], const float4 (&b)[HD / 16]) {
-  // Four chains: a quarter of the roundings at the sum's full size (the scores' rounding is most of the gradients' error where
-  // they lie hundreds apart; 16 sets with scores to 450: error against 64 bits 4.1e-4 -> 2.9e-4 of a tensor's largest entry)
-  f32x4_t acc[4] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+  f32x4_t acc[CH];
+#pragma unroll
+  for (int i = 0; i < CH; ++i) acc[i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int w = 0; w < HD / 16; ++w)
 #pragma unroll
-    for (int c = 0; c < 4; ++c) acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(f4c(a[w], c), f4c(b[w], c), acc[c], 0, 0, 0);
-  return (acc[0] + acc[1]) + (acc[2] + acc[3]);
+    for (int c = 0; c < 4; ++c)
+      acc[c % CH] = __builtin_amdgcn_mfma_f32_16x16x4f32(f4c(a[w], c), f4c(b[w], c), acc[c % CH], 0, 0, 0);
+  if constexpr (CH == 4) return (acc[0] + acc[1]) + (acc[2] + acc[3]);
+  return acc[0];
 }
 // o (head dims x the 16 columns of lane % 16) += sum over the tile's positions 4 g + u of src[position][dim] * p[u];
 // src rows start at `tile_base` (pointer to position 0 of the tile, this head's dims).  Which head dim an
@@ -1766,7 +1771,7 @@ template <int HD> struct TileCols {
 };
 template <int HD> constexpr int tile_area() { return HD % 64 == 0 ? 16 * HD / 4 : 1; }   // float4s of LDS per wave and operand
 
-template <int HD>
+template <int HD, int CH>
 __global__ void __launch_bounds__(256, HD == 128 ? 2 : 1) k_tattn_fwd(const float* __restrict__ qkv, int T, int hq, int hkv, float scale,
                                                    float* __restrict__ out, float* __restrict__ lse, uint32_t* __restrict__ row_mx) {
   const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
@@ -1804,7 +1809,7 @@ __global__ void __launch_bounds__(256, HD == 128 ? 2 : 1) k_tattn_fwd(const floa
     } else {
       load_rows4<HD>(kb, rl, min(k0 + r, T - 1), g, kf);
     }
-    f32x4_t sc = dot_rows<HD>(kf, qf);   // rows: keys k0 + 4 g + v; column: query qi
+    f32x4_t sc = dot_rows<HD, CH>(kf, qf);   // rows: keys k0 + 4 g + v; column: query qi
     float mx = -INFINITY;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
@@ -1857,7 +1862,7 @@ __global__ void __launch_bounds__(256, HD == 128 ? 2 : 1) k_tattn_fwd(const floa
 // Backward, queries: a wave owns 16 queries of one (sequence, head).  delta = dO . O; per key tile
 //   p = exp(scale s - lse), dP = V dO^T, dS = scale p (dP - delta), dQ^T += K^T dS.
 // Writes dq into dqkv's query columns and delta[(s Hq + h) T + i].
-template <int HD>
+template <int HD, int CH>
 __global__ void __launch_bounds__(256, HD == 64 ? 3 : 1) k_tattn_bwd_q(const float* __restrict__ qkv, const float* __restrict__ out,
                                                      const float* __restrict__ dout, const float* __restrict__ lse, int T, int hq,
                                                      int hkv, float scale, float* __restrict__ dqkv, float* __restrict__ delta) {
@@ -1908,8 +1913,8 @@ __global__ void __launch_bounds__(256, HD == 64 ? 3 : 1) k_tattn_bwd_q(const flo
       load_rows4<HD>(kb, rl, min(k0 + r, T - 1), g, kf);
       load_rows4<HD>(vb, rl, min(k0 + r, T - 1), g, vf);
     }
-    const f32x4_t sc = dot_rows<HD>(kf, qf);    // rows: keys k0 + 4 g + v; column: query qi
-    const f32x4_t dp = dot_rows<HD>(vf, dof);   // dP[key][query] = v_key . dO_query
+    const f32x4_t sc = dot_rows<HD, CH>(kf, qf);    // rows: keys k0 + 4 g + v; column: query qi
+    const f32x4_t dp = dot_rows<HD, CH>(vf, dof);   // dP[key][query] = v_key . dO_query
     f32x4_t ds;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
@@ -1930,7 +1935,7 @@ __global__ void __launch_bounds__(256, HD == 64 ? 3 : 1) k_tattn_bwd_q(const flo
 // result per query head, which k_attn_bwd_finish adds in head order (all heads in one wave left the chip a fifth full:
 // 840 waves of up to 7 x 19 dependent tiles at 21 x 301):
 //   p = exp(scale s - lse_q), dV^T += dO^T p, dP = dO V^T, dS = scale p (dP - delta_q), dK^T += Q^T dS.
-template <int HD>
+template <int HD, int CH>
 __global__ void __launch_bounds__(256, HD == 64 ? 2 : 1) k_tattn_bwd_kv(const float* __restrict__ qkv, const float* __restrict__ dout,
                                                       const float* __restrict__ lse, const float* __restrict__ delta, int T, int hq,
                                                       int hkv, float scale, int n_heads, float* __restrict__ dkv, size_t row_stride,
@@ -1979,8 +1984,8 @@ __global__ void __launch_bounds__(256, HD == 64 ? 2 : 1) k_tattn_bwd_kv(const fl
         load_rows4<HD>(qb, rl, min(q0 + r, T - 1), g, qf);
         load_rows4<HD>(dob, qd, min(q0 + r, T - 1), g, dof);
       }
-      const f32x4_t sc = dot_rows<HD>(qf, kf);    // rows: queries q0 + 4 g + v; column: key kj
-      const f32x4_t dp = dot_rows<HD>(dof, vf);   // dP[query][key]
+      const f32x4_t sc = dot_rows<HD, CH>(qf, kf);    // rows: queries q0 + 4 g + v; column: key kj
+      const f32x4_t dp = dot_rows<HD, CH>(dof, vf);   // dP[query][key]
       f32x4_t pv, ds;
       float ls[4], de[4];
       if (n_valid == 16) {
@@ -2012,18 +2017,18 @@ __global__ void __launch_bounds__(256, HD == 64 ? 2 : 1) k_tattn_bwd_kv(const fl
   store_acc<HD>(krow + kvd, dv, g, 1.0f);
 }
 
-template <int HD>
+template <int HD, int CH>
 hipError_t tattn_bwd(const float* qkv, const float* out, const float* dout, const float* lse, int S, int T, int hq, int hkv,
                      float scale, float* dqkv, float* delta, float* parts, hipStream_t st) {
   const unsigned tiles = (unsigned)((T + 63) / 64);
-  hipError_t e = launch(KID_ATTN_GENERIC, k_tattn_bwd_q<HD>, dim3(hq, S, tiles), dim3(256), 0, st, qkv, out, dout, lse, T, hq, hkv,
+  hipError_t e = launch(KID_ATTN_GENERIC, k_tattn_bwd_q<HD, CH>, dim3(hq, S, tiles), dim3(256), 0, st, qkv, out, dout, lse, T, hq, hkv,
                         scale, dqkv, delta);
   if (e != hipSuccess) return e;
   const size_t qd = (size_t)hq * HD, kvd = (size_t)hkv * HD;
   if (parts)   // [query heads of a group][S T][2 kvd]
-    return launch(KID_ATTN_GENERIC, k_tattn_bwd_kv<HD>, dim3(hq, S, tiles), dim3(256), 0, st, qkv, dout, lse, (const float*)delta, T,
+    return launch(KID_ATTN_GENERIC, k_tattn_bwd_kv<HD, CH>, dim3(hq, S, tiles), dim3(256), 0, st, qkv, dout, lse, (const float*)delta, T,
                   hq, hkv, scale, 1, parts, 2 * kvd, (size_t)S * T * 2 * kvd);
-  return launch(KID_ATTN_GENERIC, k_tattn_bwd_kv<HD>, dim3(hkv, S, tiles), dim3(256), 0, st, qkv, dout, lse, (const float*)delta, T,
+  return launch(KID_ATTN_GENERIC, k_tattn_bwd_kv<HD, CH>, dim3(hkv, S, tiles), dim3(256), 0, st, qkv, dout, lse, (const float*)delta, T,
                 hq, hkv, scale, hq / hkv, dqkv + qd, qd + 2 * kvd, (size_t)0);
 }
 // The partial results of k_tattn_bwd_kv added in part order into dqkv's key and value columns, and the rotary embedding's
@@ -2608,11 +2613,14 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
     if (fused_attn) {
       const dim3 ag(hq, (unsigned)S, (unsigned)((T + 63) / 64));
       uint32_t* const ao_r = NP == 3 ? mx.ao_r : nullptr;
+      auto fwd = [&](auto kernel) {
+        return launch(KID_ATTN_GENERIC, kernel, ag, dim3(256), 0, st, (const float*)a.qkv, (int)T, hq, hkv, att_scale, a.ao, a.lse, ao_r);
+      };
       hipError_t e = hipErrorInvalidValue;
-      if (hd == 16) e = launch(KID_ATTN_GENERIC, k_tattn_fwd<16>, ag, dim3(256), 0, st, (const float*)a.qkv, (int)T, hq, hkv, att_scale, a.ao, a.lse, ao_r);
-      if (hd == 32) e = launch(KID_ATTN_GENERIC, k_tattn_fwd<32>, ag, dim3(256), 0, st, (const float*)a.qkv, (int)T, hq, hkv, att_scale, a.ao, a.lse, ao_r);
-      if (hd == 64) e = launch(KID_ATTN_GENERIC, k_tattn_fwd<64>, ag, dim3(256), 0, st, (const float*)a.qkv, (int)T, hq, hkv, att_scale, a.ao, a.lse, ao_r);
-      if (hd == 128) e = launch(KID_ATTN_GENERIC, k_tattn_fwd<128>, ag, dim3(256), 0, st, (const float*)a.qkv, (int)T, hq, hkv, att_scale, a.ao, a.lse, ao_r);
+      if (hd == 16) e = NP == 3 ? fwd(k_tattn_fwd<16, 4>) : fwd(k_tattn_fwd<16, 1>);
+      if (hd == 32) e = NP == 3 ? fwd(k_tattn_fwd<32, 4>) : fwd(k_tattn_fwd<32, 1>);
+      if (hd == 64) e = NP == 3 ? fwd(k_tattn_fwd<64, 4>) : fwd(k_tattn_fwd<64, 1>);
+      if (hd == 128) e = NP == 3 ? fwd(k_tattn_fwd<128, 4>) : fwd(k_tattn_fwd<128, 1>);
       T_CK(e);
     } else {
       T_CK((sgemm<0, 1>(a.qkv, nqkv, a.qkv + q, nqkv, p.prob, (int)T, (int)T, (int)T, hd, 0.f, st, b_scores)));
@@ -2735,10 +2743,11 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
     float* kv_parts = fused_attn && rep > 1 && 2 * D.F >= 2 * D.q ? p.dgu : nullptr;
     if (fused_attn) {
       hipError_t e = hipErrorInvalidValue;
-      if (hd == 16) e = tattn_bwd<16>(a.qkv, a.ao, p.dao, a.lse, S_, T_, hq, hkv, att_scale, p.dqkv, p.delta, kv_parts, st);
-      if (hd == 32) e = tattn_bwd<32>(a.qkv, a.ao, p.dao, a.lse, S_, T_, hq, hkv, att_scale, p.dqkv, p.delta, kv_parts, st);
-      if (hd == 64) e = tattn_bwd<64>(a.qkv, a.ao, p.dao, a.lse, S_, T_, hq, hkv, att_scale, p.dqkv, p.delta, kv_parts, st);
-      if (hd == 128) e = tattn_bwd<128>(a.qkv, a.ao, p.dao, a.lse, S_, T_, hq, hkv, att_scale, p.dqkv, p.delta, kv_parts, st);
+      auto bwd = [&](auto f) { return f(a.qkv, a.ao, p.dao, a.lse, S_, T_, hq, hkv, att_scale, p.dqkv, p.delta, kv_parts, st); };
+      if (hd == 16) e = NP == 3 ? bwd(tattn_bwd<16, 4>) : bwd(tattn_bwd<16, 1>);
+      if (hd == 32) e = NP == 3 ? bwd(tattn_bwd<32, 4>) : bwd(tattn_bwd<32, 1>);
+      if (hd == 64) e = NP == 3 ? bwd(tattn_bwd<64, 4>) : bwd(tattn_bwd<64, 1>);
+      if (hd == 128) e = NP == 3 ? bwd(tattn_bwd<128, 4>) : bwd(tattn_bwd<128, 1>);
       T_CK(e);
     } else {
       T_CK((sgemm<0, 1>(a.qkv, nqkv, a.qkv + q, nqkv, p.prob, (int)T, (int)T, (int)T, hd, 0.f, st, b_scores)));
