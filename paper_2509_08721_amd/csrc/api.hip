@@ -121,6 +121,8 @@ struct LayerWeights {
   void* wdown16 = nullptr;
 };
 
+static constexpr int kCompactLevels = 4;   // smaller batches a rollout with a stop token can go on with (kCompactSlots)
+
 struct sapo_weights {
   sapo_model_config cfg;
   int elt;                       // bytes per weight element
@@ -148,9 +150,9 @@ struct sapo_weights {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
   };
-  // [0]: every sequence has its row; [1], [2]: the smaller batches a call with a stop token falls back to once
+  // [0]: every sequence has its row; [1] ..: the smaller batches a call with a stop token falls back to once
   // enough sequences have ended (kCompactSlots)
-  mutable DecodeGraph dgraph[3];
+  mutable DecodeGraph dgraph[1 + kCompactLevels];
   // the last rollout call on this handle: decode steps enqueued, compactions, rows per step at the end,
   // ended sequences at the last look
   mutable int last_stats[4] = {0, 0, 0, 0};
@@ -771,13 +773,16 @@ struct RolloutPlan {
     float* partials = nullptr;
     int* slot_seq = nullptr;
   };
-  Level level[3];
+  Level level[1 + kCompactLevels];
   int n_levels;
   size_t bytes;
 };
 // Rows per step a batch is compacted to: at 64 rows and below the weight-streaming kernels run, up to 256 the FFN of
-// kernels_rows.hip (see run_layers_decode16)
-static const int kCompactSlots[2] = {256, 64};
+// kernels_rows.hip (see run_layers_decode16), whose workgroups take 128 rows.  us per step of the 0.5B decoder: 256 rows 1064,
+// 192 993, 128 902, 72 855, 64 680.  A level costs a captured step (1.5 ms), so there is none where it saves less than that in
+// the 32 steps between two looks.  ms per call of 120 tokens with levels 256, 64 only and now: 224 sequences, 158 of them running
+// at the end, 127.2, 121.2; 136 sequences, 100 running, 118, 113.
+static const int kCompactSlots[kCompactLevels] = {256, 192, 128, 64};
 
 // Can decode steps of so many rows run?  The weight-streaming GEMMs add at most kMaxSsqParts parts of a row's sum of squares, and
 // every 16 features of the projection before them leave one, unless the FFN is that of 65 .. 256 rows.

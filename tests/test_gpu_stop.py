@@ -99,7 +99,8 @@ def test_stop_token_mfma_rows_are_prefixes_of_the_plain_call(P, G, Lp, N):
 
 
 @pytest.mark.parametrize("P,N,boost,ragged,levels", [(12, 120, 3, False, [64]), (12, 120, 3, True, [64]),
-                                                     (40, 130, 6, False, [256, 64])])
+                                                     (40, 130, 6, False, [256, 64]), (20, 130, 4, False, [128, 64]),
+                                                     (32, 130, 4, True, [192, 128]), (36, 130, 3, False, [256, 192, 128])])
 def test_ended_sequences_leave_the_batch(P, N, boost, ragged, levels):
     """More than 64 sequences on the MFMA path, a stop token whose logit swings widely (lengths from a few tokens
     to max_new): once the running sequences fit 256 / 64 rows the step goes on with that many rows.  Every row
