@@ -810,8 +810,8 @@ __device__ __forceinline__ void qkv_epilogue(f32x16 (&acc)[NH * (HD / 32)][TJ], 
   }
 }
 template <int HD, int TJ>
-__global__ void __launch_bounds__(256, TJ == 2 ? 2 : 3) k_gemm_qkv_rope(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, int M,
-                                                                        int N, int K, QkvEpi ep) {
+__global__ void __launch_bounds__(256, 2) k_gemm_qkv_rope(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, int M,
+                                                          int N, int K, QkvEpi ep) {
   constexpr int H = 4, NH = 128 / HD, TM = 128 * TJ;   // heads and tokens of a tile
   extern __shared__ uint4 smem[];
   int bx, by;
