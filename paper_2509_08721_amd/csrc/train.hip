@@ -319,12 +319,6 @@ __device__ __forceinline__ int row_exp(uint32_t mx) {
 }
 __device__ __forceinline__ float row_scale(uint32_t mx) { return __uint_as_float((uint32_t)(127 - row_exp(mx)) << 23); }
 
-// A bound of the products of two rows' values, times f, from their maxima
-__device__ __forceinline__ uint32_t product_bound(uint32_t a, uint32_t b, float f) {
-  if (max(a, b) >= 0x7F800000u) return 0x7F800000u;
-  return __float_as_uint(fminf(__uint_as_float(a) * __uint_as_float(b) * f, 3.4028234e38f));
-}
-
 __host__ __device__ constexpr int x3_parts(int NP) { return NP == 1 ? 1 : 2; }   // 16-bit values that a value is kept as
 // 8 values (scaled: NP 3) as MFMA fragments
 template <int NP> __device__ __forceinline__ void x3_cut(const float (&x)[8], float scale, Frag8 (&f)[x3_parts(NP)]) {
@@ -437,41 +431,6 @@ __global__ void __launch_bounds__(256) k_pack_x3_t(const float* __restrict__ src
   }
 }
 
-// Where a product leaves the maxima of its output's rows and columns (row null: nowhere).  With `half` > 0 the rows have two
-// maxima, of the columns below `half` and behind, `row_pitch` apart (a tile of both counts for both).
-struct OutMax { uint32_t *row, *col; int half; size_t row_pitch; };
-// Maxima of the rows and columns of a product x[M, N] that was added up from parts, N % 64 == 0: 128 rows x 256 columns per workgroup
-__global__ void __launch_bounds__(256) k_matrix_max(const float* __restrict__ x, int M, int N, OutMax out) {
-  const int c = threadIdx.x & 7, m0 = blockIdx.y * 128 + (threadIdx.x >> 3);
-  uint32_t rm[4] = {0, 0, 0, 0};
-  const int n_first = blockIdx.x * 256;
-  for (int n0 = n_first; n0 < min(N, n_first + 256); n0 += 64) {
-    uint32_t cm[8] = {};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      if (m0 + 32 * i >= M) continue;
-      float v[8];
-      const float* p = x + (size_t)(m0 + 32 * i) * N + n0 + c * 8;
-      *(float4*)v = *(const float4*)p; *(float4*)(v + 4) = *(const float4*)(p + 4);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        cm[e] = max(cm[e], abs_bits(v[e]));
-        rm[i] = max(rm[i], abs_bits(v[e]));
-      }
-    }
-    wave_column_max<8>(cm, out.col, n0 + c * 8, N);
-  }
-  const bool second = out.half > 0 && n_first + 256 > out.half, first = out.half <= 0 || n_first < out.half;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    rm[i] = max(rm[i], (uint32_t)__builtin_amdgcn_mov_dpp((int)rm[i], 0xB1, 0xF, 0xF, true));    // lane ^ 1
-    rm[i] = max(rm[i], (uint32_t)__builtin_amdgcn_mov_dpp((int)rm[i], 0x4E, 0xF, 0xF, true));    // lane ^ 2
-    rm[i] = max(rm[i], (uint32_t)__builtin_amdgcn_mov_dpp((int)rm[i], 0x141, 0xF, 0xF, true));   // lane ^ 7
-    if (c != 0 || m0 + 32 * i >= M) continue;
-    if (first) atomicMax(out.row + m0 + 32 * i, rm[i]);
-    if (second) atomicMax(out.row + out.row_pitch + m0 + 32 * i, rm[i]);
-  }
-}
 // Maxima of the rows of a few matrices [rows, K], contiguous: a wave per row
 constexpr int kRowMaxTasks = 100;
 struct RowMaxTask { const float* src; uint32_t* out; int rows, K; unsigned first_block; };
@@ -526,30 +485,6 @@ template <int N> __device__ __forceinline__ void x3_wait() {
   __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (15 << 8) | ((N >> 4) << 14));
 }
 
-// 16 values per lane, all 64 lanes: the maximum of value v over the 32 lanes of a half wave, in the half's lanes with
-// (lane >> 1) % 16 = v.  A swap leaves each 16 lanes half of the values, then every step keeps the half that a bit of the lane
-// names and gives the other to a lane that differs in it.
-__device__ __forceinline__ float max_of_half_wave(const float (&v16)[16]) {
-  const int lane = threadIdx.x & 63;
-  float v8[8], v4[4], v2[2];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const lane_u32x2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v16[i]), __float_as_uint(v16[i + 8]), false, false);
-    v8[i] = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-  }
-  auto moved = [](float x, auto ctrl) __attribute__((always_inline)) {
-    return __uint_as_float((uint32_t)__builtin_amdgcn_mov_dpp((int)__float_as_uint(x), decltype(ctrl)::value, 0xF, 0xF, true));
-  };
-#pragma unroll
-  for (int i = 0; i < 4; ++i)   // lane ^ 15
-    v4[i] = fmaxf(lane & 8 ? v8[i + 4] : v8[i], moved(lane & 8 ? v8[i] : v8[i + 4], std::integral_constant<int, 0x140>()));
-#pragma unroll
-  for (int i = 0; i < 2; ++i)   // lane ^ 7
-    v2[i] = fmaxf(lane & 4 ? v4[i + 2] : v4[i], moved(lane & 4 ? v4[i] : v4[i + 2], std::integral_constant<int, 0x141>()));
-  const float v1 = fmaxf(lane & 2 ? v2[1] : v2[0], moved(lane & 2 ? v2[0] : v2[1], std::integral_constant<int, 0x4E>()));   // lane ^ 2
-  return fmaxf(v1, moved(v1, std::integral_constant<int, 0xB1>()));   // lane ^ 1
-}
-
 // C tile of a wave: TJ x 4 MFMA tiles; accumulator v of lane l: row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32.  With
 // NP 3 the operands' scales are taken out of the sums: amx, bmx are their rows' maxima.
 template <bool full> __device__ __forceinline__ void x3_col_exps(int (&eb)[4], const uint32_t* __restrict__ bmx, int n, int N) {
@@ -564,52 +499,6 @@ template <bool full> __device__ __forceinline__ void x3_row_exps(int (&ea)[4], c
   } else {
 #pragma unroll
     for (int u = 0; u < 4; ++u) ea[u] = row_exp(amx[min(m + u, M - 1)]);
-  }
-}
-// The maxima of the tile's rows and columns: about 400 vector instructions a wave, against 1344 MFMAs of 32 cycles at a
-// contraction over 896.
-template <int TJ, bool full>
-__device__ __forceinline__ void x3_tile_max(const f32x16_t (&acc)[TJ][4], const OutMax& out, int row0, int n0, int M, int N,
-                                            const uint32_t* __restrict__ amx, const uint32_t* __restrict__ bmx) {
-  const int lane = threadIdx.x & 63, m_lane = (lane >> 5) * 4;
-  int eb[4];
-  float col[4] = {0.f, 0.f, 0.f, 0.f};
-  x3_col_exps<full>(eb, bmx, n0 + (lane & 31), N);
-#pragma unroll
-  for (int t = 0; t < TJ; ++t) {
-    float row[16];
-#pragma unroll
-    for (int v4 = 0; v4 < 4; ++v4) {
-      const int m = row0 + t * 32 + 8 * v4 + m_lane;
-      int ea[4];
-      x3_row_exps<full>(ea, amx, m, M);
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        float a[4];
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          a[j] = fabsf(ldexpf(acc[t][j][4 * v4 + u], ea[u] + eb[j]));
-          if (!full) a[j] = m + u < M ? a[j] : 0.f;   // rows past the end repeat others
-          col[j] = fmaxf(col[j], a[j]);
-        }
-        row[4 * v4 + u] = fmaxf(fmaxf(a[0], a[1]), fmaxf(a[2], a[3]));
-      }
-      asm volatile("" : "+v"(col[0]), "+v"(col[1]), "+v"(col[2]), "+v"(col[3]));
-      __builtin_amdgcn_sched_barrier(0);   // the accumulators fill half of the registers: nothing of a group is kept for later
-    }
-    const float mx = max_of_half_wave(row);
-    const int v = (lane >> 1) & 15, m = row0 + t * 32 + 8 * (v >> 2) + (v & 3) + m_lane;
-    if ((lane & 1) == 0 && (full || m < M)) {
-      if (out.half <= 0 || n0 < out.half) atomicMax(out.row + m, __float_as_uint(mx));
-      if (out.half > 0 && n0 + 128 > out.half) atomicMax(out.row + out.row_pitch + m, __float_as_uint(mx));
-    }
-    __builtin_amdgcn_sched_barrier(0);
-  }
-#pragma unroll
-  for (int j = 0; j < 4; j += 2) {   // the lower 32 lanes take column block j, the upper ones j + 1
-    const lane_u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(col[j]), __float_as_uint(col[j + 1]), false, false);
-    const int c = n0 + j * 32 + lane;
-    if (full || c < N) atomicMax(out.col + c, __float_as_uint(fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]))));
   }
 }
 // A tile without rows or columns past the end is stored without a comparison per value, rows by scalar base addresses.
@@ -674,7 +563,7 @@ template <int NP, int TJ>
 __global__ void __launch_bounds__(256, TJ == 2 ? 2 : 3) k_gemm_x3(const u32x4_t* __restrict__ Ap, const u32x4_t* __restrict__ Bp,
                                                                   float* C, const float* Cin, int ldc, int M, int N, int KB,
                                                                   float beta, int kb_split, size_t c_split,
-                                                                  const uint32_t* amx, const uint32_t* bmx, OutMax out_mx) {
+                                                                  const uint32_t* __restrict__ amx, const uint32_t* __restrict__ bmx) {
   constexpr int PC = x3_parts(NP), H = x3_stage(NP), NF = H * PC;     // ring copies per wave and stage; fragments of a column block
   constexpr int PER = NF + NF * TJ;                // requests per wave and stage
   constexpr int kRing = 3;
@@ -764,13 +653,7 @@ __global__ void __launch_bounds__(256, TJ == 2 ? 2 : 3) k_gemm_x3(const u32x4_t*
     stage(std::integral_constant<int, 1>(), st + 1);
   }
   if (st < nst) stage(std::integral_constant<int, 0>(), st);
-  int row0 = ty * kGM * TJ + row_w, n0 = tx * kGM;
-  if (NP == 3 && out_mx.row) {
-    if (row0 + 32 * TJ <= M && n0 + 128 <= N) x3_tile_max<TJ, true>(acc, out_mx, row0, n0, M, N, amx, bmx);
-    else x3_tile_max<TJ, false>(acc, out_mx, row0, n0, M, N, amx, bmx);
-    asm volatile("" : "+s"(amx), "+s"(bmx), "+s"(row0), "+s"(n0));   // what both passes compute is not kept between them: no registers
-  }
-  x3_store_tile<NP, TJ>(acc, C, Cin, ldc, row0, n0, M, N, beta, amx, bmx);
+  x3_store_tile<NP, TJ>(acc, C, Cin, ldc, ty * kGM * TJ + row_w, tx * kGM, M, N, beta, amx, bmx);
 }
 
 // f(0), f(1), ... f(N - 1) with the index as a compile-time constant
@@ -907,9 +790,6 @@ inline int x3_steps(int K) { return (K + 63) / 64 * 4; }   // padded k steps: wh
 struct X3Bufs { void* a; void* b; size_t a_cap, b_cap; int NP; float* parts; size_t parts_cap; };
 __global__ void k_sum_parts(const float* __restrict__ part, int n_part, size_t n, float beta, const float* in, float* out);
 
-hipError_t matrix_max(const float* x, int M, int N, const OutMax& out, hipStream_t st) {
-  return launch(KID_MISC, k_matrix_max, dim3((N + 255) / 256, (M + 127) / 128), dim3(256), 0, st, x, M, N, out);
-}
 hipError_t x3_pack(const X3Op& op, void* dst, size_t cap, int NP, hipStream_t st) {
   if (x3_pack_bytes(NP, op.rows, op.K) > cap) return hipErrorInvalidValue;
   const int rows_pad = (op.rows + 127) / 128 * 128, KB = x3_steps(op.K);
@@ -934,9 +814,7 @@ hipError_t x3_sum_parts(const X3Bufs& bufs, int splits, size_t n, float beta, co
 // C[M, N] = beta C + op(A) op(B)^T-style product of two operands given row-wise over the same K; an operand packed earlier
 // (a_packed, b_packed) is used as it is
 hipError_t gemm_x3(const X3Op& A, const X3Op& B, float* C, const float* Cin, int ldc, float beta, const X3Bufs& bufs, hipStream_t st,
-                   const void* b_packed = nullptr, bool split_ok = true, const void* a_packed = nullptr,
-                   const OutMax& out_mx = OutMax{}) {
-  if (out_mx.row && beta != 0.f) return hipErrorInvalidValue;   // maxima are those of the product
+                   const void* b_packed = nullptr, bool split_ok = true, const void* a_packed = nullptr) {
   if (A.K != B.K || A.rows <= 0 || B.rows <= 0 || A.K <= 0 || (bufs.NP == 3 && (!A.row_mx || !B.row_mx))) return hipErrorInvalidValue;
   hipError_t e;
   if (!a_packed && (e = x3_pack(A, bufs.a, bufs.a_cap, bufs.NP, st)) != hipSuccess) return e;
@@ -950,14 +828,13 @@ hipError_t gemm_x3(const X3Op& A, const X3Op& B, float* C, const float* Cin, int
   const float b_ = g.splits > 1 ? 0.f : beta;
   auto go = [&](auto kernel) {
     return launch(KID_GEMM_GENERIC, kernel, g.grid, dim3(256), 0, st, pa_, pb_, out, Cin, ldc, A.rows, B.rows, KB, b_, g.per_split, c_split,
-                  A.row_mx, B.row_mx, g.splits > 1 ? OutMax{} : out_mx);
+                  A.row_mx, B.row_mx);
   };
   if (bufs.NP == 3) e = g.TJ == 2 ? go(k_gemm_x3<3, 2>) : go(k_gemm_x3<3, 1>);
   else if (bufs.NP == 2) e = g.TJ == 2 ? go(k_gemm_x3<2, 2>) : go(k_gemm_x3<2, 1>);
   else e = g.TJ == 2 ? go(k_gemm_x3<1, 2>) : go(k_gemm_x3<1, 1>);
   if (e != hipSuccess || g.splits == 1) return e;
-  e = x3_sum_parts(bufs, g.splits, (size_t)A.rows * B.rows, beta, Cin, C, st);
-  return e != hipSuccess || !out_mx.row ? e : matrix_max(C, A.rows, B.rows, out_mx, st);
+  return x3_sum_parts(bufs, g.splits, (size_t)A.rows * B.rows, beta, Cin, C, st);
 }
 // C[M, N] = beta C + A^T B, A [K, M] and B [K, N] in fp32
 hipError_t gemm_x3_tn(const float* A, int lda, const float* B, int ldb, float* C, int M, int N, int K, float beta,
@@ -1291,19 +1168,12 @@ __global__ void k_swiglu_fwd4(const float* __restrict__ gu, float* __restrict__ 
 // layer of the 0.5B decoder for act and its packing before, and now: 21 x 301 tokens, one piece 61 + 39, 52 (5.9 TB/s).
 template <int NP>
 __global__ void __launch_bounds__(256) k_swiglu_fwd_pack(const float* __restrict__ gu, int M, int F, int KB, u32x4_t* __restrict__ dst,
-                                                         const uint32_t* __restrict__ gate_mx, const uint32_t* __restrict__ up_mx,
-                                                         uint32_t* __restrict__ row_mx) {
+                                                         uint32_t* /*row_mx*/) {
+  static_assert(NP < 3, "three pieces: k_swiglu_fwd_pack_rows");
   const int f0 = blockIdx.x * 64, m0 = blockIdx.y * 64;
 #pragma unroll
   for (int i = 0; i < 2; ++i) {
     const int c = (threadIdx.x & 7) * 8, m = m0 + (threadIdx.x >> 3) + 32 * i;
-    uint32_t mx = 0;   // |silu(g)| <= |g|
-    if constexpr (NP == 3) {
-      if (m < M) {
-        mx = product_bound(gate_mx[m], up_mx[m], 1.f);
-        if (f0 + c == 0) row_mx[m] = mx;
-      }
-    }
     float x[8];
     if (m < M) {
       const float* gp = gu + (size_t)m * 2 * F + f0 + c;
@@ -1316,7 +1186,45 @@ __global__ void __launch_bounds__(256) k_swiglu_fwd_pack(const float* __restrict
 #pragma unroll
       for (int e = 0; e < 8; ++e) x[e] = 0.f;
     }
-    x3_store<NP>(dst, KB, m, (f0 + c) >> 3, x, row_scale(mx));
+    x3_store<NP>(dst, KB, m, (f0 + c) >> 3, x, 1.f);
+  }
+}
+// The same with three pieces, whose scales come from the rows' maxima: 8 tokens x all features per workgroup, which reads its rows
+// twice, for the maxima and to pack; the second time they come from the memory-side cache.  A bound from gate's and up's maxima
+// would need no first pass, but silu makes it as loose as gates are negative (2^20 with gates around -16).
+__global__ void __launch_bounds__(512) k_swiglu_fwd_pack_rows(const float* __restrict__ gu, int M, int F, int KB, u32x4_t* __restrict__ dst,
+                                                              uint32_t* __restrict__ row_mx) {
+  __shared__ uint32_t red[8][8];
+  const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63, r = lane & 7, m = blockIdx.x * 8 + r, c0 = (wave * 8 + (lane >> 3)) * 8;
+  const float* row = gu + (size_t)min(m, M - 1) * 2 * F;
+  auto act = [&](int f, float (&x)[8]) __attribute__((always_inline)) {
+    float g[8], u[8];
+    *(float4*)g = *(const float4*)(row + f); *(float4*)(g + 4) = *(const float4*)(row + f + 4);
+    *(float4*)u = *(const float4*)(row + F + f); *(float4*)(u + 4) = *(const float4*)(row + F + f + 4);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = m < M ? swiglu(g[e], u[e]) : 0.f;
+  };
+  uint32_t mx = 0;
+#pragma unroll 2
+  for (int f = c0; f < F; f += 512) {
+    float x[8];
+    act(f, x);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) mx = max(mx, abs_bits(x[e]));
+  }
+  mx = max(mx, (uint32_t)__builtin_amdgcn_mov_dpp((int)mx, 0x128, 0xF, 0xF, true));   // rotated by 8 lanes of 16
+  mx = max_u32_xor32(max_u32_xor16(mx));
+  if (lane < 8) red[wave][lane] = mx;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < 8; ++w) mx = max(mx, red[w][r]);
+  if (threadIdx.x < 8 && m < M) row_mx[m] = mx;
+  const float scale = row_scale(mx);
+#pragma unroll 2
+  for (int f = c0; f < F; f += 512) {
+    float x[8];
+    act(f, x);
+    x3_store<3>(dst, KB, m, f >> 3, x, scale);
   }
 }
 __global__ void k_swiglu_fwd(const float* __restrict__ gu, float* __restrict__ act, int F, size_t total) {
@@ -1539,12 +1447,42 @@ __global__ void k_swiglu_bwd4(const float* __restrict__ dact, const float* __res
   *(float4*)out = dg;
   *(float4*)(out + F) = du;
 }
-// Scales of the packed SwiGLU operands come from bounds (NP 3): |silu(g)| <= |g| and |silu'(g)| <= 1.1 give the largest
-// |act| and |d gate|, |d up| of a row or column from the maxima of gate, up and d act there, which the products that make
-// them leave.  A bound is a few bits above the largest value, of the 17 that a value may lie below it at full precision.
-// (Exact maxima by a pass over the same inputs beforehand: 225 + 300 us a layer at 64 x 384 tokens of the 0.5B decoder.)
-constexpr float kSiluSlope = 1.1f;
-struct SwigluMax { const uint32_t *gate_r, *up_r, *dact_r, *gu_c, *dact_c; uint32_t *dgu_r, *dgu_c, *act_c; };   // in; out: the bounds
+// Maxima of d gate and d up by rows of tokens (of both) and by rows of features, and of act by rows of features, F % 64 == 0: the
+// scales of k_swiglu_bwd_pack with three pieces, before it, since a column's is known when all rows are.  256 tokens x 64 features per
+// workgroup, bound by its bytes.
+struct SwigluMax { uint32_t *dgu_r, *dgu_c, *act_c; };
+__global__ void __launch_bounds__(256) k_swiglu_bwd_max(const float* __restrict__ dact, const float* __restrict__ gu, int M, int F, SwigluMax mx) {
+  const int c = (threadIdx.x & 7) * 8, f = blockIdx.x * 64 + c;
+  uint32_t cg[8] = {}, cu[8] = {}, ca[8] = {};
+#pragma unroll 2
+  for (int i = 0; i < 8; ++i) {
+    const int m = blockIdx.y * 256 + 32 * i + (threadIdx.x >> 3);
+    uint32_t rm = 0;
+    if (m < M) {
+      const float *gp = gu + (size_t)m * 2 * F + f, *dp = dact + (size_t)m * F + f;
+      float g[8], u[8], da[8];
+      *(float4*)g = *(const float4*)gp; *(float4*)(g + 4) = *(const float4*)(gp + 4);
+      *(float4*)u = *(const float4*)(gp + F); *(float4*)(u + 4) = *(const float4*)(gp + F + 4);
+      *(float4*)da = *(const float4*)dp; *(float4*)(da + 4) = *(const float4*)(dp + 4);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        float dg, du;
+        swiglu_grad(g[e], u[e], da[e], dg, du);
+        cg[e] = max(cg[e], abs_bits(dg));
+        cu[e] = max(cu[e], abs_bits(du));
+        ca[e] = max(ca[e], abs_bits(swiglu(g[e], u[e])));
+        rm = max(max(rm, abs_bits(dg)), abs_bits(du));
+      }
+    }
+    rm = max(rm, (uint32_t)__builtin_amdgcn_mov_dpp((int)rm, 0xB1, 0xF, 0xF, true));    // lane ^ 1
+    rm = max(rm, (uint32_t)__builtin_amdgcn_mov_dpp((int)rm, 0x4E, 0xF, 0xF, true));    // lane ^ 2
+    rm = max(rm, (uint32_t)__builtin_amdgcn_mov_dpp((int)rm, 0x141, 0xF, 0xF, true));   // lane ^ 7
+    if (c == 0 && m < M) atomicMax(mx.dgu_r + m, rm);
+  }
+  wave_column_max<8>(cg, mx.dgu_c, f, F);
+  wave_column_max<8>(cu, mx.dgu_c + F, f, F);
+  wave_column_max<8>(ca, mx.act_c, f, F);
+}
 // The same straight into the packed operands of the two products that read it, F % 64 == 0: by rows of tokens (for the d input
 // product) and by rows of features (for the weight gradients, which contract over the tokens); act, which the down
 // projection's weight gradient contracts over the tokens, by rows of features as well.  Neither is stored in fp32.
@@ -1579,14 +1517,7 @@ __global__ void __launch_bounds__(256) k_swiglu_bwd_pack(const float* __restrict
 #pragma unroll
       for (int e = 0; e < 8; ++e) dg[e] = du[e] = act[e] = 0.f;
     }
-    float scale = 1.f;
-    if constexpr (NP == 3) {
-      if (m < M) {
-        const uint32_t b = max(product_bound(mx.dact_r[m], mx.up_r[m], kSiluSlope), product_bound(mx.dact_r[m], mx.gate_r[m], 1.f));
-        scale = row_scale(b);
-        if (f0 + c == 0) mx.dgu_r[m] = b;
-      }
-    }
+    const float scale = x3_scale<NP>(mx.dgu_r, min(m, M - 1));
     x3_store<NP>(by_rows, KB_rows, m, (f0 + c) >> 3, dg, scale);
     x3_store<NP>(by_rows, KB_rows, m, (F + f0 + c) >> 3, du, scale);
 #pragma unroll
@@ -1601,14 +1532,8 @@ __global__ void __launch_bounds__(256) k_swiglu_bwd_pack(const float* __restrict
 #pragma unroll
     for (int e = 0; e < 8; ++e) x[e] = tile[which][oct * 8 + e][col];
     const int f = f0 + col;
-    float scale = 1.f;
-    if constexpr (NP == 3) {
-      const uint32_t g = mx.gu_c[f], u = mx.gu_c[F + f];
-      const uint32_t b = which == 0 ? product_bound(mx.dact_c[f], u, kSiluSlope) : which == 1 ? product_bound(mx.dact_c[f], g, 1.f) : product_bound(g, u, 1.f);
-      scale = row_scale(b);
-      if (m0 == 0 && oct == 0) (which < 2 ? mx.dgu_c : mx.act_c)[(which == 1 ? F : 0) + f] = b;
-    }
-    x3_store<NP>(which < 2 ? by_cols : act_by_cols, KB_cols, (which == 1 ? F : 0) + f, k8, x, scale);
+    const int row = (which == 1 ? F : 0) + f;
+    x3_store<NP>(which < 2 ? by_cols : act_by_cols, KB_cols, row, k8, x, x3_scale<NP>(which < 2 ? mx.dgu_c : mx.act_c, row));
   }
 }
 // dgu from dact: d gate = dact * up * sig(g) (1 + g (1 - sig(g))), d up = dact * silu(g)
@@ -2246,8 +2171,7 @@ struct LayerActs {
 struct LayerMax {
   uint32_t *wqkv_r, *wo_r, *wgu_r, *wd_r;                   // weights by rows: written once per update
   uint32_t *wqkv_c, *wo_c, *wgu_c, *wd_c;                   // from here on taken by atomics, zeroed before a micro-batch
-  uint32_t *xn_c, *ao_r, *ao_c, *xn2_c, *gu_r, *gu_c, *act_r, *act_c, *dh1_c, *dact_r, *dact_c, *dgu_r,
-      *dgu_c, *dh2_c, *dqkv_r, *dqkv_c;                     // gu_r: gate's, then up's (M apart)
+  uint32_t *xn_c, *ao_r, *ao_c, *xn2_c, *act_r, *act_c, *dh1_c, *dgu_r, *dgu_c, *dh2_c, *dqkv_r, *dqkv_c;
 };
 struct TrainPlan {
   std::vector<LayerMax> mx;
@@ -2349,7 +2273,6 @@ void make_plan(const sapo_model_config& c, size_t S, size_t T, size_t S_total, c
   for (auto& m : p.mx) {
     m.wqkv_c = A.take<uint32_t>(D.d); m.wo_c = A.take<uint32_t>(D.q); m.wgu_c = A.take<uint32_t>(D.d); m.wd_c = A.take<uint32_t>(D.F);
     m.xn_c = A.take<uint32_t>(D.d); m.ao_r = A.take<uint32_t>(M); m.ao_c = A.take<uint32_t>(D.q); m.xn2_c = A.take<uint32_t>(D.d);
-    m.gu_r = A.take<uint32_t>(2 * M); m.gu_c = A.take<uint32_t>(2 * D.F); m.dact_r = A.take<uint32_t>(M); m.dact_c = A.take<uint32_t>(D.F);
     m.act_r = A.take<uint32_t>(M); m.act_c = A.take<uint32_t>(D.F); m.dh1_c = A.take<uint32_t>(D.d); m.dgu_r = A.take<uint32_t>(M);
     m.dgu_c = A.take<uint32_t>(2 * D.F); m.dh2_c = A.take<uint32_t>(D.d); m.dqkv_r = A.take<uint32_t>(M); m.dqkv_c = A.take<uint32_t>(D.nqkv);
   }
@@ -2579,14 +2502,14 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
   const bool split_fwd = NP == 3;
   struct Mat { const float* x; int ld; uint32_t *row_mx, *col_mx; };   // a matrix by rows, with its maxima
   auto mm_nt = [&](const Mat& X, const Mat& W, float* C, int ldc, int M_, int N_, int K_, float beta,
-                   const float* Cin = nullptr, const void* w_packed = nullptr, const OutMax& out_mx = OutMax{}) {   // C = beta Cin + X W^T
+                   const float* Cin = nullptr, const void* w_packed = nullptr) {   // C = beta Cin + X W^T
     return gemm_x3(X3Op{X.x, X.ld, M_, K_, false, X.row_mx, X.col_mx}, X3Op{W.x, W.ld, N_, K_, false, W.row_mx, W.col_mx}, C, Cin, ldc,
-                   beta, xb, st, w_packed, split_fwd, nullptr, out_mx);
+                   beta, xb, st, w_packed, split_fwd);
   };
   auto mm_nn = [&](const Mat& A_, const Mat& B_, float* C, int ldc, int M_, int N_, int K_, float beta,
-                   const void* b_packed = nullptr, const OutMax& out_mx = OutMax{}) {   // C = beta C + A B
+                   const void* b_packed = nullptr) {   // C = beta C + A B
     return gemm_x3(X3Op{A_.x, A_.ld, M_, K_, false, A_.row_mx, A_.col_mx}, X3Op{B_.x, B_.ld, N_, K_, true, B_.col_mx, nullptr}, C, C, ldc,
-                   beta, xb, st, b_packed, true, nullptr, out_mx);
+                   beta, xb, st, b_packed);
   };
   auto mm_tn = [&](const Mat& A_, const Mat& B_, float* C, int Mg, int Ng, int Kg, float beta) {   // C = beta C + A^T B
     return gemm_x3_tn(A_.x, A_.ld, B_.x, B_.ld, C, Mg, Ng, Kg, beta, xb, st, A_.col_mx, B_.col_mx);
@@ -2631,15 +2554,15 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
     }
     T_CK(mm_nt(Mat{a.ao, q, mx.ao_r, mx.ao_c}, Mat{TH(t0 + 4), q, mx.wo_r, mx.wo_c}, a.h2, d, Mi, d, q, 1.f, a.h));
     T_CK(rmsnorm_fwd(a.h2, TH(t0 + 5), c.rms_eps, Mi, d, a.xn2, a.r2, NP == 3 ? p.xn_r : nullptr, st));
-    T_CK(mm_nt(Mat{a.xn2, d, p.xn_r, mx.xn2_c}, Mat{TH(t0 + 6), d, mx.wgu_r, mx.wgu_c}, a.gu, 2 * F, Mi, 2 * F, d, 0.f, nullptr,
-               nullptr, NP == 3 && p.packed_ffn ? OutMax{mx.gu_r, mx.gu_c, F, M} : OutMax{}));   // w_gate, w_up are adjacent
+    T_CK(mm_nt(Mat{a.xn2, d, p.xn_r, mx.xn2_c}, Mat{TH(t0 + 6), d, mx.wgu_r, mx.wgu_c}, a.gu, 2 * F, Mi, 2 * F, d, 0.f));   // w_gate, w_up are adjacent
     float* h_next = (l + 1 < D.L) ? p.layer[l + 1].h : p.h_last;
     if (p.packed_ffn) {
-      auto pack = [&](auto kernel) {
-        return launch(KID_SWIGLU, kernel, dim3(F / 64, blocks64), dim3(256), 0, st, (const float*)a.gu, Mi, F, x3_steps(F), (u32x4_t*)p.packa,
-                      (const uint32_t*)mx.gu_r, (const uint32_t*)(mx.gu_r + M), mx.act_r);
+      auto pack = [&](auto kernel, dim3 grid, int threads) {
+        return launch(KID_SWIGLU, kernel, grid, dim3(threads), 0, st, (const float*)a.gu, Mi, F, x3_steps(F), (u32x4_t*)p.packa, mx.act_r);
       };
-      T_CK(NP == 3 ? pack(k_swiglu_fwd_pack<3>) : NP == 2 ? pack(k_swiglu_fwd_pack<2>) : pack(k_swiglu_fwd_pack<1>));
+      const dim3 tiles(F / 64, blocks64);
+      T_CK(NP == 3 ? pack(k_swiglu_fwd_pack_rows, dim3(blocks64 * 8), 512)
+                   : NP == 2 ? pack(k_swiglu_fwd_pack<2>, tiles, 256) : pack(k_swiglu_fwd_pack<1>, tiles, 256));
       T_CK(gemm_x3(X3Op{nullptr, 0, Mi, F, false, mx.act_r, nullptr}, X3Op{TH(t0 + 8), F, d, F, false, mx.wd_r, mx.wd_c}, h_next, a.h2, d, 1.f,
                    xb, st, nullptr, split_fwd, p.packa));
       continue;
@@ -2705,15 +2628,17 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
     const LayerMax& mx = p.mx[l];
     // down projection
     const Mat dh1{p.dh, d, p.dh_r, mx.dh1_c}, dh2{p.dh, d, p.dh_r, mx.dh2_c};   // the residual gradient before and after the FFN's norm
-    T_CK(mm_nn(dh1, Mat{TH(t0 + 8), F, mx.wd_r, mx.wd_c}, p.dact, F, Mi, F, d, 0.f, nullptr,
-               NP == 3 && p.packed_ffn ? OutMax{mx.dact_r, mx.dact_c, 0, 0} : OutMax{}));
+    T_CK(mm_nn(dh1, Mat{TH(t0 + 8), F, mx.wd_r, mx.wd_c}, p.dact, F, Mi, F, d, 0.f));
     if (p.packed_ffn) {
       const int KB_rows = x3_steps(2 * F), KB_cols = x3_steps(Mi);
+      const SwigluMax maxima{mx.dgu_r, mx.dgu_c, mx.act_c};
       auto pack = [&](auto kernel) {
         return launch(KID_SWIGLU, kernel, dim3(F / 64, blocks64), dim3(256), 0, st, (const float*)p.dact, (const float*)a.gu, Mi, F, KB_rows,
-                      (u32x4_t*)p.packa, KB_cols, (u32x4_t*)p.dgu, (u32x4_t*)p.act_cols,
-                      SwigluMax{mx.gu_r, mx.gu_r + M, mx.dact_r, mx.gu_c, mx.dact_c, mx.dgu_r, mx.dgu_c, mx.act_c});
+                      (u32x4_t*)p.packa, KB_cols, (u32x4_t*)p.dgu, (u32x4_t*)p.act_cols, maxima);
       };
+      if (NP == 3)
+        T_CK(launch(KID_SWIGLU, k_swiglu_bwd_max, dim3(F / 64, (Mi + 255) / 256), dim3(256), 0, st, (const float*)p.dact, (const float*)a.gu, Mi, F,
+                    maxima));
       T_CK(NP == 3 ? pack(k_swiglu_bwd_pack<3>) : NP == 2 ? pack(k_swiglu_bwd_pack<2>) : pack(k_swiglu_bwd_pack<1>));
       // gate / up projections, then the down projection's weights
       T_CK(gemm_x3(X3Op{nullptr, 0, Mi, 2 * F, false, mx.dgu_r, nullptr}, X3Op{TH(t0 + 6), d, d, 2 * F, true, mx.wgu_c, nullptr}, p.dx, p.dx, d,
