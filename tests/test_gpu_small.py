@@ -102,6 +102,26 @@ def test_small_bf16_rollouts_are_scored_alike(hd):
     assert float((ref - lp).abs().max()) <= 2e-2
 
 
+def test_small_norm_of_rows_whose_squares_overflow():
+    """Residuals of 1e20: their sum of squares is infinite, its inverse root 0 and the normalised row 0, as in the generic kernels, so
+    the logits behind such a token are all 0 (untied head)."""
+    shape = replace(W.TINY, tied_embeddings=False)
+    w = W.make_weights(shape, 23, std=0.05)
+    w["embed"][3:6] *= 1e21
+    small = sapo.sapo_weights_create(shape, w)
+    os.environ["SAPO_FORCE_GENERIC"] = "1"
+    try:
+        generic = sapo.sapo_weights_create(shape, w)
+    finally:
+        del os.environ["SAPO_FORCE_GENERIC"]
+    tok = torch.tensor([[9, 3, 17, 4, 4, 30, 5, 11]], dtype=torch.int32, device="cuda")
+    a, b = (sapo.sapo_score_logprobs(h, tok, torch.ones_like(tok, dtype=torch.uint8), torch.zeros(1, device="cuda"), 1)[0][0] for h in (small, generic))
+    assert float((a - b).abs().max()) <= 2e-5 and float((a[[2, 4, 5, 7]] + np.log(shape.vocab)).abs().max()) <= 2e-5
+    for prompt in (tok, tok[:, :5].contiguous()):
+        a, b = (sapo.sapo_rollout_generate(h, prompt, 2, 6, 1.0, 4) for h in (small, generic))
+        assert torch.equal(a[0], b[0]) and float((a[1] - b[1]).abs().max()) <= 2e-5
+
+
 def test_small_bf16_follows_the_generic_kernels():
     shape = replace(W.TINY, dtype="bf16")
     small, generic = handles(shape, 13)
