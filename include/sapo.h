@@ -216,9 +216,8 @@ int sapo_rollout_generate_ragged(const sapo_weights* w, const int32_t* prompts, 
  *                                       (r - mean) / (population std + 1e-6); exactly 0 for a
  *                                       group whose rewards are all equal
  * Requires S % G == 0, T <= cfg.max_seq.
- * The same call gives the same bits.  A sequence's logits do not depend on how many others are scored
- * with it; the sum of their exponentials is cut by the number of tokens in the call, so its log-probs may
- * differ in the last bits between calls of different size.
+ * The same call gives the same bits, and on the matrix-core path a sequence's log-probs do not depend on
+ * what else is scored with it, nor on which of its other positions are.
  */
 int sapo_score_logprobs(const sapo_weights* w, const int32_t* tokens,
                         const uint8_t* completion_mask, const float* rewards, int S, int T, int G,

@@ -1061,13 +1061,14 @@ hipError_t m_rmsnorm_x32(const float* h, const float* gain, float eps, void* out
 // ---------------------------------------------------------------------------------------
 // LM head for scoring: log-softmax + target gather without materialising logits.
 // Rastered like the GEMM over (256-row tiles) x (groups of 128-feature tiles): a workgroup
-// walks the tiles of its group for its 256 rows keeping a running (max, sum exp) per row, and the
-// one lane that sees a row's target id writes the target logit.  A second kernel merges the groups
-// in a fixed order.  partials: ztarget [max_rows], then [n_groups][n_rows][2]; the groups as ScoreGroups cuts them.
+// walks the tiles of its group for its 256 rows keeping a (max, sum exp) per row and block of tiles, and the
+// one lane that sees a row's target id writes the target logit.  A second kernel merges the blocks
+// in a fixed order.  partials: ztarget [max_rows], from the next even number on [blocks][n_rows][2]; blocks and groups as in ranges.h.
 // ---------------------------------------------------------------------------------------
 static int score_slots() { return 2 * n_compute_units(); }   // workgroups in flight
+__host__ __device__ constexpr size_t score_pairs_at(int max_rows) { return ((size_t)max_rows + 1) & ~(size_t)1; }
 size_t m_lmhead_score_partial_floats(int max_rows, int V) {
-  return (size_t)max_rows + 2 * (size_t)ScoreMost(V >> 7, max_rows, score_slots()).pairs;
+  return score_pairs_at(max_rows) + 2 * (size_t)ScoreBlocks(V >> 7).n * max_rows;
 }
 
 __global__ void __launch_bounds__(256, 2) k_lmhead_score(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp,
@@ -1080,10 +1081,13 @@ __global__ void __launch_bounds__(256, 2) k_lmhead_score(const uint4* __restrict
   const int n_rows = *n_rows_dev;
   const int n_ft = V >> 7;
   const int row_tiles = (n_rows + 255) >> 8;
-  const ScoreGroups g(n_ft, row_tiles, slots);
+  const ScoreBlocks blocks(n_ft);
+  const ScoreGroups g(blocks, row_tiles, slots);
   int bx, by;
   if (!big_raster(g.groups, row_tiles, bx, by)) return;
-  const int ft_begin = bx * g.tiles, ft_end = min(n_ft, ft_begin + g.tiles);
+  int block = bx * g.blocks;
+  const int ft_begin = block * blocks.tiles, ft_end = min(n_ft, ft_begin + g.blocks * blocks.tiles);
+  int block_end = min(ft_end, ft_begin + blocks.tiles);
   const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63;
   const int row0 = by * 256 + wave * 64 + (lane & 31);
   LseAcc lse[TJ];
@@ -1130,35 +1134,45 @@ __global__ void __launch_bounds__(256, 2) k_lmhead_score(const uint4* __restrict
         }
       }
     }
-  }
-  // merge the two lane halves
+    if (ft + 1 == block_end) {   // merge the two lane halves
 #pragma unroll
-  for (int tj = 0; tj < TJ; ++tj) {
-    lse[tj].merge(__shfl_xor(lse[tj].m, 32, 64), __shfl_xor(lse[tj].l, 32, 64));
-    const int row = row0 + tj * 32;
-    if (lane < 32 && row < n_rows) {
-      float* p = partials + max_rows + ((size_t)bx * n_rows + row) * 2;
-      p[0] = lse[tj].m; p[1] = lse[tj].l;
+      for (int tj = 0; tj < TJ; ++tj) {
+        lse[tj].merge(__shfl_xor(lse[tj].m, 32, 64), __shfl_xor(lse[tj].l, 32, 64));
+        const int row = row0 + tj * 32;
+        if (lane < 32 && row < n_rows) {
+          float* p = partials + score_pairs_at(max_rows) + ((size_t)block * n_rows + row) * 2;
+          p[0] = lse[tj].m; p[1] = lse[tj].l;
+        }
+        lse[tj].init();
+      }
+      ++block;
+      block_end = min(ft_end, block_end + blocks.tiles);
     }
   }
 }
 
-// A wave per row: lane l merges the groups l, l + 64, ... in order, then the lanes pairwise.
-__global__ void __launch_bounds__(256) k_lmhead_score_merge(const float* __restrict__ partials, int max_rows, int V, int slots,
+// 16 rows per workgroup: thread (row, part) merges the blocks part, part + 16, ... in order, then the parts pairwise.
+__global__ void __launch_bounds__(256) k_lmhead_score_merge(const float* __restrict__ partials, int max_rows, int V,
                                                             const int* __restrict__ n_rows_dev, const int* __restrict__ row_seq_pos,
                                                             int T, float* __restrict__ out_logprobs) {
-  const int row = blockIdx.x * 4 + wave_index(threadIdx.x), lane = threadIdx.x & 63;
-  const int n_rows = *n_rows_dev;
-  if (row >= n_rows) return;
-  const int n_groups = ScoreGroups(V >> 7, (n_rows + 255) >> 8, slots).groups;
+  __shared__ float s_m[4][16], s_l[4][16];
+  const int n_rows = *n_rows_dev, wave = wave_index(threadIdx.x), lane = threadIdx.x & 63;
+  if ((int)blockIdx.x * 16 >= n_rows) return;
+  const int row = min((int)blockIdx.x * 16 + (lane & 15), n_rows - 1), n_blocks = ScoreBlocks(V >> 7).n;
+  const float2* p = (const float2*)(partials + score_pairs_at(max_rows)) + row;
   LseAcc a; a.init();
-  for (int s = lane; s < n_groups; s += 64) {
-    const float* p = partials + max_rows + ((size_t)s * n_rows + row) * 2;
-    a.merge(p[0], p[1]);
+#pragma unroll 4
+  for (int s = threadIdx.x >> 4; s < n_blocks; s += 16) {
+    const float2 ml = p[(size_t)s * n_rows];
+    a.merge(ml.x, ml.y);
   }
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) a.merge(__shfl_xor(a.m, o, 64), __shfl_xor(a.l, o, 64));
-  if (lane != 0) return;
+  for (int o = 32; o >= 16; o >>= 1) a.merge(__shfl_xor(a.m, o, 64), __shfl_xor(a.l, o, 64));
+  if (lane < 16) { s_m[wave][lane] = a.m; s_l[wave][lane] = a.l; }
+  __syncthreads();
+  if (threadIdx.x >= 16 || (int)blockIdx.x * 16 + lane >= n_rows) return;
+#pragma unroll
+  for (int w = 1; w < 4; ++w) a.merge(s_m[w][lane], s_l[w][lane]);
   const float zt = partials[row];
   out_logprobs[(size_t)row_seq_pos[2 * row] * T + row_seq_pos[2 * row + 1]] = zt - (a.m + logf(a.l));
 }
@@ -1175,12 +1189,12 @@ hipError_t m_lmhead_score(const void* Xp, const void* Wp, int max_rows, const in
     attr_done = true;
   }
   const int slots = score_slots();
-  const unsigned blocks = (unsigned)((ScoreMost(V >> 7, max_rows, slots).blocks + 7) / 8 * 8);
+  const unsigned blocks = (unsigned)((score_most_workgroups(ScoreBlocks(V >> 7), max_rows, slots) + 7) / 8 * 8);
   const hipError_t e = launch(KID_LMHEAD_SCORE, k_lmhead_score, dim3(blocks), dim3(256), kBigLds, st, (const uint4*)Xp,
                               (const uint4*)Wp, max_rows, n_rows_dev, V, K, row_seq_pos, tokens, T, slots, partials);
   if (e != hipSuccess) return e;
-  return launch(KID_LMHEAD_SCORE_MERGE, k_lmhead_score_merge, dim3((max_rows + 3) / 4), dim3(256), 0, st, partials,
-                max_rows, V, slots, n_rows_dev, row_seq_pos, T, out_logprobs);
+  return launch(KID_LMHEAD_SCORE_MERGE, k_lmhead_score_merge, dim3((max_rows + 15) / 16), dim3(256), 0, st, partials,
+                max_rows, V, n_rows_dev, row_seq_pos, T, out_logprobs);
 }
 
 // ---------------------------------------------------------------------------------------

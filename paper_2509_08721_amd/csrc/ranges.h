@@ -39,34 +39,42 @@ constexpr bool tile_of_block(int id, int NX, int NY, int& bx, int& by) {
   return true;
 }
 
-// Groups that the LM-head scorer cuts the n_ft 128-feature tiles of the vocabulary into, each walked by one workgroup per row
-// tile: as few as fill whole rounds of the `slots` workgroups in flight, of at most 32 tiles each.  The number of row tiles is
-// that of the rows that are scored, which the device counts.  us per call before (groups of 16 tiles, halved while half of the
-// call's positions gave fewer than 512 workgroups) and now: 0.5B, 24 x 200 tokens 5653, 5378; 9 x 301 4024, 3921 (the scorer 496 us with
-// the row tiles dealt to the XCDs, now 312); 64 x 768 46.2 ms both; 1.5B, 24 x 200 14602, 14192.
+// The LM-head scorer's log-sum-exp is added up over blocks of ScoreBlocks::tiles 128-feature tiles of the vocabulary, then over the
+// blocks, in an order that depends on the vocabulary alone: a row's log-prob has the same bits whatever else is scored.  Blocks
+// are as small as needed for one row tile to fill the chip (at most kMaxScoreBlocks); with the groups themselves as the unit (what
+// this replaces) a sequence's last bits changed with other sequences' masks.
+constexpr int kMaxScoreBlocks = 512;
+struct ScoreBlocks {
+  int n, tiles;   // their number, and the tiles of one (the last one may have fewer)
+  constexpr explicit ScoreBlocks(int n_ft) : n(0), tiles((n_ft + kMaxScoreBlocks - 1) / kMaxScoreBlocks) {
+    if (n_ft > 0) n = (n_ft + tiles - 1) / tiles;
+  }
+};
+// Groups of blocks, each walked by one workgroup per row tile: as few as fill whole rounds of the `slots` workgroups in flight, of
+// at most 32 tiles (one block where that is more).  The number of row tiles is that of the rows that are scored, which the device
+// counts.  us per call with groups of 16 tiles, halved while half of the call's positions gave fewer than 512 workgroups, and with
+// these: 0.5B, 24 x 200 tokens 5653, 5378; 9 x 301 4024, 3921 (the scorer 496 us with the row tiles dealt to the XCDs, now 312);
+// 64 x 768 46.2 ms both; 1.5B, 24 x 200 14602, 14192.
 struct ScoreGroups {
-  int groups, tiles;   // their number, and the tiles of one (the last one may have fewer)
-  constexpr ScoreGroups(int n_ft, int row_tiles, int slots) : groups(0), tiles(1) {
-    if (row_tiles <= 0 || n_ft <= 0) return;
-    const int least = (n_ft + 31) / 32;
+  int groups, blocks;   // their number, and the blocks of one (the last one may have fewer)
+  constexpr ScoreGroups(const ScoreBlocks& b, int row_tiles, int slots) : groups(0), blocks(1) {
+    if (row_tiles <= 0 || b.n <= 0) return;
+    const int longest = b.tiles < 32 ? 32 / b.tiles : 1, least = (b.n + longest - 1) / longest;
     const int rounds = (least * row_tiles + slots - 1) / slots, fill = slots * rounds / row_tiles;   // fill >= least
-    const int most = fill < n_ft ? fill : n_ft;
-    tiles = (n_ft + most - 1) / most;
-    groups = (n_ft + tiles - 1) / tiles;
+    const int most = fill < b.n ? fill : b.n;
+    blocks = (b.n + most - 1) / most;
+    groups = (b.n + blocks - 1) / blocks;
   }
 };
-// Largest number of workgroups of a call that scores up to max_rows rows, and of (group, row) pairs, row tiles of 256
-struct ScoreMost {
-  long blocks, pairs;
-  constexpr ScoreMost(int n_ft, int max_rows, int slots) : blocks(0), pairs(0) {
-    for (int t = 1; t <= (max_rows + 255) / 256; ++t) {
-      const ScoreGroups g(n_ft, t, slots);
-      const long rows = (long)t * 256 < max_rows ? (long)t * 256 : max_rows, b = (long)g.groups * t, p = g.groups * rows;
-      if (b > blocks) blocks = b;
-      if (p > pairs) pairs = p;
-    }
+// Largest number of workgroups of a call that scores up to max_rows rows
+constexpr long score_most_workgroups(const ScoreBlocks& b, int max_rows, int slots) {
+  long most = 0;
+  for (int t = 1; t <= (max_rows + 255) / 256; ++t) {
+    const long n = (long)ScoreGroups(b, t, slots).groups * t;
+    if (n > most) most = n;
   }
-};
+  return most;
+}
 
 // The small-decoder kernels index with 32 bits: K and V of a layer (cache_rows of kv values) and the call's tokens and
 // outputs (io_elems of 4 bytes) stay below 2^31 bytes, the rows a long prompt keeps between launches (prompt_rows of d

@@ -2,8 +2,8 @@
 
 SAPO_BIG_TILE=256 forces the 256-token tiles (checked against the oracle in test_gpu_mfma.py and test_gpu_full.py); by
 default calls of few tokens run on k_gemm_mid / k_gemm_qkv_mid, which keep every output's chain of MFMAs.  The query heads
-per wave of the attention and the vocabulary groups of the scorer follow the number of sequences, not that switch: a call
-of few sequences is compared with the same sequences in a larger one for those.
+per wave of the attention follow the number of sequences, and the vocabulary groups of the scorer the number of scored rows, not
+that switch: a call of few sequences is compared with the same sequences in a larger one for those.
 """
 import os
 from dataclasses import replace
@@ -50,7 +50,7 @@ def test_scores_are_bit_identical_to_the_large_tiles(model, S, T):
 
 
 # two layers each: attention waves of 1, 2 and 4 heads at head dim 64 (1, 8 and 16 sequences of 300), 1 and 2 heads at 128;
-# scorer groups of 2, 4 and 16 vocabulary tiles
+# scorer groups of several sizes
 @pytest.mark.parametrize("shape", [replace(W.HALF_B, n_layers=2), replace(W.ONE_HALF_B, n_layers=2)], ids=["hd64", "hd128"])
 def test_a_sequence_scores_the_same_alone_and_among_others(shape):
     gw = sapo.sapo_weights_create(shape, W.make_weights(shape, 43))
@@ -67,8 +67,29 @@ def test_a_sequence_scores_the_same_alone_and_among_others(shape):
         few = tokens[:n].contiguous()
         assert torch.equal(sapo.sapo_debug_logits(gw, few, positions), logits)      # layers and attention: every bit
         a, _ = sapo.sapo_score_logprobs(gw, few, mask[:n].contiguous(), rewards[:n].contiguous(), 1)
-        # the log-sum-exp is added up in other groups: a few units in the last place of a value below 16
-        assert float((a - lp[:n]).abs().max()) <= 4 * 2.0 ** -20
+        assert torch.equal(a, lp[:n])
         again, _ = sapo.sapo_score_logprobs(gw, few, mask[:n].contiguous(), rewards[:n].contiguous(), 1)
         assert torch.equal(a, again)
+    gw.close()
+
+
+@pytest.mark.parametrize("shape", [replace(W.HALF_B, n_layers=1), replace(W.MINI_BF16, max_seq=1024)], ids=["vocabulary of 151936", "mini"])
+def test_log_probs_keep_their_bits_whatever_else_is_scored(shape):
+    """The scorer's workgroups follow the number of rows that the masks name; a sequence's log-probs are the same bits with other
+    sequences' masks empty, sparse or full, with fewer sequences, and at positions its own mask adds none to."""
+    gw = sapo.sapo_weights_create(shape, W.make_weights(shape, 45))
+    rng = np.random.default_rng(46)
+    S, T = 14, 301
+    tokens = torch.from_numpy(rng.integers(0, shape.vocab, size=(S, T)).astype(np.int32)).cuda()
+    rewards = torch.zeros(S, device="cuda")
+    full = torch.ones((S, T), dtype=torch.uint8, device="cuda")
+    want, _ = sapo.sapo_score_logprobs(gw, tokens, full, rewards, 1)
+    for share in (0.0, 0.05, 0.3, 0.8):
+        mask = torch.from_numpy((rng.random((S, T)) < share).astype(np.uint8)).cuda()
+        mask[0] = 1
+        lp, _ = sapo.sapo_score_logprobs(gw, tokens, mask, rewards, 1)
+        assert torch.equal(lp, torch.where(mask != 0, want, torch.zeros_like(want))), share
+    for n in (1, 3, 9):
+        lp, _ = sapo.sapo_score_logprobs(gw, tokens[:n].contiguous(), full[:n].contiguous(), rewards[:n].contiguous(), 1)
+        assert torch.equal(lp, want[:n]), n
     gw.close()

@@ -80,23 +80,25 @@ int main() {
 """)
 
 
-def test_scorer_groups_cover_the_vocabulary_within_their_buffer(tmp_path):
-    """Every feature tile lies in one group, no group is empty or longer than 32 tiles, and the launch and the buffer made for
-    max_rows hold what any smaller number of rows asks for."""
+def test_scorer_blocks_and_groups_cover_the_vocabulary(tmp_path):
+    """Every feature tile lies in one block and every block in one group, none is empty, a group has at most 32 tiles, there are no
+    more blocks than kMaxScoreBlocks, and the launch made for max_rows holds what any smaller number of rows asks for."""
     run(tmp_path, r"""
 int main() {
   int bad = 0;
-  for (int n_ft : {1, 2, 8, 31, 32, 33, 64, 400, 1187, 2000})
+  for (int n_ft : {1, 2, 8, 31, 32, 33, 64, 400, 511, 512, 513, 1187, 2000})
     for (int slots : {512, 304})
       for (int max_rows : {1, 255, 256, 257, 2709, 49152}) {
-        const ScoreMost most(n_ft, max_rows, slots);
+        const ScoreBlocks b(n_ft);
+        bad += b.n < 1 || b.n > kMaxScoreBlocks || b.n * b.tiles < n_ft || (b.n - 1) * b.tiles >= n_ft;
+        const long most = score_most_workgroups(b, max_rows, slots);
         for (int rows = 0; rows <= max_rows; rows += rows < 600 ? 1 : 509) {
           const int t = (rows + 255) / 256;
-          const ScoreGroups g(n_ft, t, slots);
+          const ScoreGroups g(b, t, slots);
           if (rows == 0) { bad += g.groups != 0; continue; }
-          bad += g.tiles < 1 || g.tiles > 32 || g.groups * g.tiles < n_ft || (g.groups - 1) * g.tiles >= n_ft;
-          bad += (long)g.groups * t > most.blocks || (long)g.groups * rows > most.pairs;
-          if (bad) { printf("%d tiles, %d slots, %d of %d rows: %d groups of %d\n", n_ft, slots, rows, max_rows, g.groups, g.tiles); return 1; }
+          bad += g.blocks < 1 || g.blocks * b.tiles > 32 || g.groups * g.blocks < b.n || (g.groups - 1) * g.blocks >= b.n;
+          bad += (long)g.groups * t > most;
+          if (bad) { printf("%d tiles, %d slots, %d of %d rows: %d groups of %d\n", n_ft, slots, rows, max_rows, g.groups, g.blocks); return 1; }
         }
       }
   return 0;
