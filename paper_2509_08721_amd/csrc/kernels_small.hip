@@ -1031,7 +1031,10 @@ hipError_t small_decode(int dtype, const SmallModel& m, const SmallDecode& args,
   const hipError_t e = set_lds_once(dtype);
   if (e != hipSuccess) return e;
   const size_t elt = dtype == SAPO_DTYPE_F32 ? 4 : 2;
-  const bool res = (m.hd == 16 || m.hd == 32 || m.hd == 64) && decode_lds(m, a.ctx_max, true, elt) <= kDecodeLds;
+  // One token per sequence: no step's attention follows and the head is read once, so nothing is worth a copy into LDS.  us a call of
+  // the tiny decoder with the copies and without, 64 x 8 sequences of 16 + 1 tokens 49.7, 44.8;
+  // 128 + 1 112, 101; with two tokens they pay (16 + 2 72, before there were any 81).
+  const bool res = a.N > 1 && (m.hd == 16 || m.hd == 32 || m.hd == 64) && decode_lds(m, a.ctx_max, true, elt) <= kDecodeLds;
   size_t lds = decode_lds(m, a.ctx_max, res, elt);
   const size_t head = (size_t)m.V * m.d * elt;   // the LM head too, where it fits behind the rest
   a.lm_resident = res && head <= kDecodeLds - lds;
