@@ -366,37 +366,76 @@ template <int C> __device__ __forceinline__ void wave_column_max(uint32_t (&cm)[
   for (int e = 1; e < 8; ++e) v = r == e ? cm[e] : v;
   if (r < 8 && k0 + r < K) atomicMax(col_mx + k0 + r, v);
 }
-// src[row * ld + k]: one workgroup per (block of 128 rows, 8 k steps), everything a thread reads is in flight at once.  NP 3: a
-// lane holds one octet of k of 8 rows, so that the columns' maxima (into col_mx, if given) are mostly the lane's own; else
-// one row's 8 octets, which every part is written of in longer runs.  row_mx: the rows' maxima (NP 3).
+// src[row * ld + k]: one workgroup per (block of 128 rows, 8 k steps), everything a thread reads is in flight at once.  One and two
+// pieces: thread (row, k half) takes 8 octets of its row, which every part is written of in longer runs (7 x 141 tokens of the 0.5B
+// decoder, one piece: 7.6 us a launch on average, 8.8 in the order below).
 template <int NP>
 __global__ void __launch_bounds__(256) k_pack_x3(const float* __restrict__ src, int ld, int rows, int K, int /*rows_pad*/, int KB,
-                                                 u32x4_t* __restrict__ dst, const uint32_t* __restrict__ row_mx,
-                                                 uint32_t* __restrict__ col_mx) {
-  const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63;
-  auto row_of = [&](int i) { return (int)blockIdx.x * 128 + (NP == 3 ? (lane >> 2) + 16 * i : (int)(threadIdx.x >> 1)); };
-  auto octet_of = [&](int i) { return (int)blockIdx.y * 16 + (NP == 3 ? wave * 4 + (lane & 3) : 2 * i + (lane & 1)); };
+                                                 u32x4_t* __restrict__ dst, const uint32_t* /*row_mx*/, uint32_t* /*col_mx*/) {
+  static_assert(NP < 3, "three pieces: k_pack_x3_max");
+  const int row = blockIdx.x * 128 + (threadIdx.x >> 1), kh = threadIdx.x & 1;
+  const float* rp = src + (size_t)row * ld;
+  const bool vec = ((ld & 3) == 0) && ((((uintptr_t)src) & 15) == 0);
+  const int kb0 = blockIdx.y * 8, n = min(KB - kb0, 8);
+  if (vec && (kb0 + 8) * 16 <= K && (int)blockIdx.x * 128 + 128 <= rows) {
+    float x[8][8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const float* q = rp + (kb0 + i) * 16 + kh * 8;
+      *(float4*)&x[i][0] = *(const float4*)q;
+      *(float4*)&x[i][4] = *(const float4*)(q + 4);
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) x3_store<NP>(dst, KB, row, (kb0 + i) * 2 + kh, x[i], 1.f);
+    return;
+  }
+  for (int kb = kb0; kb < kb0 + n; ++kb) {
+    const int k0 = kb * 16 + kh * 8;
+    float x[8];
+    if (row < rows && k0 + 8 <= K && vec) {
+      *(float4*)&x[0] = *(const float4*)(rp + k0);
+      *(float4*)&x[4] = *(const float4*)(rp + k0 + 4);
+    } else {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) x[j] = (row < rows && k0 + j < K) ? rp[k0 + j] : 0.f;
+    }
+    x3_store<NP>(dst, KB, row, kb * 2 + kh, x, 1.f);
+  }
+}
+// Three pieces, scaled by the rows' maxima row_mx: a lane holds one octet of k of 8 rows, so that the columns' maxima (into col_mx, if
+// given) are mostly the lane's own.
+__global__ void __launch_bounds__(256) k_pack_x3_max(const float* __restrict__ src, int ld, int rows, int K, int /*rows_pad*/, int KB,
+                                                     u32x4_t* __restrict__ dst, const uint32_t* __restrict__ row_mx,
+                                                     uint32_t* __restrict__ col_mx) {
+  const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63, octet = (int)blockIdx.y * 16 + wave * 4 + (lane & 3), k0 = octet * 8;
+  auto row_of = [&](int i) { return (int)blockIdx.x * 128 + (lane >> 2) + 16 * i; };
   const bool vec = ((ld & 3) == 0) && ((((uintptr_t)src) & 15) == 0);
   float x[8][8];
   if (vec && ((int)blockIdx.y + 1) * 128 <= K && ((int)blockIdx.x + 1) * 128 <= rows) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      const float* q = src + (size_t)row_of(i) * ld + octet_of(i) * 8;
+      const float* q = src + (size_t)row_of(i) * ld + k0;
       *(float4*)&x[i][0] = *(const float4*)q;
       *(float4*)&x[i][4] = *(const float4*)(q + 4);
     }
   } else {
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      const int row = row_of(i), k0 = octet_of(i) * 8;
+      const int row = row_of(i);
+      const float* q = src + (size_t)row * ld + k0;
+      if (vec && row < rows && k0 + 8 <= K) {
+        *(float4*)&x[i][0] = *(const float4*)q;
+        *(float4*)&x[i][4] = *(const float4*)(q + 4);
+      } else {
 #pragma unroll
-      for (int j = 0; j < 8; ++j) x[i][j] = (row < rows && k0 + j < K) ? src[(size_t)row * ld + k0 + j] : 0.f;
+        for (int j = 0; j < 8; ++j) x[i][j] = (row < rows && k0 + j < K) ? q[j] : 0.f;
+      }
     }
   }
+  if (octet >= KB * 2) return;   // padded steps are a multiple of 4 (8 octets): the whole wave
 #pragma unroll
-  for (int i = 0; i < 8; ++i)
-    if (octet_of(i) < KB * 2) x3_store<NP>(dst, KB, row_of(i), octet_of(i), x[i], x3_scale<NP>(row_mx, min(row_of(i), rows - 1)));
-  if (NP == 3 && col_mx && octet_of(0) < KB * 2) {   // padded steps are a multiple of 4 (8 octets): the whole wave
+  for (int i = 0; i < 8; ++i) x3_store<3>(dst, KB, row_of(i), octet, x[i], row_scale(row_mx[min(row_of(i), rows - 1)]));
+  if (col_mx) {
     uint32_t cm[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
@@ -404,7 +443,7 @@ __global__ void __launch_bounds__(256) k_pack_x3(const float* __restrict__ src, 
 #pragma unroll
       for (int i = 1; i < 8; ++i) cm[j] = max(cm[j], abs_bits(x[i][j]));
     }
-    wave_column_max<4>(cm, col_mx, octet_of(0) * 8, K);
+    wave_column_max<4>(cm, col_mx, k0, K);
   }
 }
 // src[k * ld + row] (rows contiguous): 64 rows x 64 k per workgroup through LDS
@@ -799,7 +838,7 @@ hipError_t x3_pack(const X3Op& op, void* dst, size_t cap, int NP, hipStream_t st
   };
   if (NP == 3 && !op.row_mx) return hipErrorInvalidValue;
   if (op.trans) return NP == 3 ? go(k_pack_x3_t<3>) : NP == 2 ? go(k_pack_x3_t<2>) : go(k_pack_x3_t<1>);
-  return NP == 3 ? go(k_pack_x3<3>) : NP == 2 ? go(k_pack_x3<2>) : go(k_pack_x3<1>);
+  return NP == 3 ? go(k_pack_x3_max) : NP == 2 ? go(k_pack_x3<2>) : go(k_pack_x3<1>);
 }
 // Tile, grid and split of a product with `rows` x `cols` outputs and KB k steps in stages of `stage` (x3_split in ranges.h).
 struct X3Grid { int TJ, splits, per_split; dim3 grid; };
@@ -955,7 +994,7 @@ inline bool norm_rows_vectorised(int d) { return d % 4 == 0 && d <= 256 * kNormM
 // xn = h * rstd * gain, rstd = 1 / sqrt(mean(h^2) + eps).  Here a lane takes the values lane, lane + 64, ...: the squares are
 // added as the workgroup-per-row kernel below adds them (four chains of every fourth block of 64, reduced one by one), so
 // that rows of any width see the same rounding: with bf16 operands a last bit of rstd decides roundings downstream.
-template <int NV>
+template <int NV, bool MX>   // MX: the rows' maxima as well
 __global__ void __launch_bounds__(256) k_rmsnorm_fwd_rows(const float* __restrict__ h, const float* __restrict__ gain, float eps,
                                                           int M, int d, float* __restrict__ xn, float* __restrict__ rstd,
                                                           uint32_t* __restrict__ row_mx) {
@@ -975,11 +1014,11 @@ __global__ void __launch_bounds__(256) k_rmsnorm_fwd_rows(const float* __restric
 #pragma unroll
   for (int i = 0; i < 4 * NV; ++i) {
     const int f = lane + 64 * i;
-    x[i] = x[i] * r * (f < d ? gain[f] : 0.f);
-    if (f < d) xn[m * d + f] = x[i];
+    if constexpr (MX) x[i] = x[i] * r * (f < d ? gain[f] : 0.f);
+    if (f < d) xn[m * d + f] = MX ? x[i] : x[i] * r * gain[f];
   }
   if (lane == 0) rstd[m] = r;
-  if (row_mx) {
+  if constexpr (MX) {
     uint32_t mx = 0;
 #pragma unroll
     for (int i = 0; i < 4 * NV; ++i) mx = max(mx, abs_bits(x[i]));
@@ -992,7 +1031,7 @@ __global__ void __launch_bounds__(256) k_rmsnorm_fwd_rows(const float* __restric
 //   dh (+)= rstd * gain * dxn - rstd^3 * h * mean_j(dxn_j gain_j h_j),   part[block] = sum over the block's rows of
 // dxn h rstd (kNormRows rows, each wave's in order, the four waves' sums in wave order)
 constexpr int kNormRows = 32;
-template <int NV>
+template <int NV, bool MX>   // MX: the rows' maxima as well
 __global__ void __launch_bounds__(256) k_rmsnorm_bwd_rows(const float* __restrict__ dxn, const float* __restrict__ h,
                                                           const float* __restrict__ rstd, const float* __restrict__ gain, int M,
                                                           int d, float* __restrict__ dh, int accumulate, float* __restrict__ part,
@@ -1036,10 +1075,10 @@ __global__ void __launch_bounds__(256) k_rmsnorm_bwd_rows(const float* __restric
         const float4 v = make_float4(o[i].x + (r * g[i].x * x[i].x - c * y[i].x), o[i].y + (r * g[i].y * x[i].y - c * y[i].y),
                                      o[i].z + (r * g[i].z * x[i].z - c * y[i].z), o[i].w + (r * g[i].w * x[i].w - c * y[i].w));
         *(float4*)(dh + (size_t)m * d + f) = v;
-        mx = max(max(max(mx, abs_bits(v.x)), max(abs_bits(v.y), abs_bits(v.z))), abs_bits(v.w));
+        if constexpr (MX) mx = max(max(max(mx, abs_bits(v.x)), max(abs_bits(v.y), abs_bits(v.z))), abs_bits(v.w));
       }
     }
-    if (row_mx) {
+    if constexpr (MX) {
       mx = wave_max_u32(mx);
       if (lane == 0) row_mx[m] = mx;
     }
@@ -1103,8 +1142,9 @@ hipError_t rmsnorm_fwd(const float* h, const float* gain, float eps, int M, int 
     return e != hipSuccess || !row_mx ? e : row_max(xn, M, d, row_mx, st);
   }
   return with_norm_width(d, [&](auto nv) {
-    return launch(KID_RMSNORM, k_rmsnorm_fwd_rows<decltype(nv)::value>, dim3((M + 3) / 4), dim3(256), 0, st, h, gain, eps, M, d, xn, rstd,
-                  row_mx);
+    constexpr int NV = decltype(nv)::value;
+    return launch(KID_RMSNORM, row_mx ? k_rmsnorm_fwd_rows<NV, true> : k_rmsnorm_fwd_rows<NV, false>, dim3((M + 3) / 4), dim3(256), 0, st, h,
+                  gain, eps, M, d, xn, rstd, row_mx);
   });
 }
 
@@ -2605,8 +2645,9 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
     if (norm_rows_vectorised(d)) {
       const int n_part = (Mi + kNormRows - 1) / kNormRows;
       const hipError_t e = with_norm_width(d, [&](auto nv) {
-        return launch(KID_RMSNORM, k_rmsnorm_bwd_rows<decltype(nv)::value>, dim3(n_part), dim3(256), 0, st, dxn, hin, rstd,
-                      (const float*)TH(gain_tensor_idx), Mi, d, p.dh, accumulate, p.gpart, NP == 3 ? p.dh_r : nullptr);
+        constexpr int NV = decltype(nv)::value;
+        return launch(KID_RMSNORM, NP == 3 ? k_rmsnorm_bwd_rows<NV, true> : k_rmsnorm_bwd_rows<NV, false>, dim3(n_part), dim3(256), 0, st, dxn,
+                      hin, rstd, (const float*)TH(gain_tensor_idx), Mi, d, p.dh, accumulate, p.gpart, p.dh_r);
       });
       if (e != hipSuccess) return e;
       return launch(KID_MISC, k_gain_sum, dim3((d + 15) / 16), dim3(256), 0, st, (const float*)p.gpart, n_part, d, !first, GR(gain_tensor_idx));
