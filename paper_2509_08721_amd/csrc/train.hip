@@ -1229,13 +1229,18 @@ __global__ void __launch_bounds__(256) k_swiglu_fwd_pack(const float* __restrict
     x3_store<NP>(dst, KB, m, (f0 + c) >> 3, x, 1.f);
   }
 }
-// The same with three pieces, whose scales come from the rows' maxima: 8 tokens x all features per workgroup, which reads its rows
-// twice, for the maxima and to pack; the second time they come from the memory-side cache.  A bound from gate's and up's maxima
-// would need no first pass, but silu makes it as loose as gates are negative (2^20 with gates around -16).
+// The same with three pieces, whose scales come from the rows' maxima: 4 tokens x all features per workgroup, whose threads keep their
+// NI octets of act in registers between the maxima and the packing (NI 0: rows too wide for that are read twice).  A bound from
+// gate's and up's maxima would need no row at once, but silu makes it as loose as gates are negative (2^20 with gates around -16).
+// us a layer of the 0.5B decoder with rows read twice (8 tokens per workgroup) and now: 64 x 384 tokens 482, 338; 21 x 301 143, 90; 7 x
+// 141 30, 12.5.
+constexpr int kActRows = 4, kActStep = 512 / kActRows * 8;   // rows of a workgroup; features of its threads' one octet each
+template <int NI>
 __global__ void __launch_bounds__(512) k_swiglu_fwd_pack_rows(const float* __restrict__ gu, int M, int F, int KB, u32x4_t* __restrict__ dst,
                                                               uint32_t* __restrict__ row_mx) {
-  __shared__ uint32_t red[8][8];
-  const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63, r = lane & 7, m = blockIdx.x * 8 + r, c0 = (wave * 8 + (lane >> 3)) * 8;
+  constexpr int R = kActRows;
+  __shared__ uint32_t red[8][R];
+  const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63, r = lane % R, m = blockIdx.x * R + r, c0 = (wave * (64 / R) + lane / R) * 8;
   const float* row = gu + (size_t)min(m, M - 1) * 2 * F;
   auto act = [&](int f, float (&x)[8]) __attribute__((always_inline)) {
     float g[8], u[8];
@@ -1244,27 +1249,36 @@ __global__ void __launch_bounds__(512) k_swiglu_fwd_pack_rows(const float* __res
 #pragma unroll
     for (int e = 0; e < 8; ++e) x[e] = m < M ? swiglu(g[e], u[e]) : 0.f;
   };
+  float kept[NI ? NI : 1][8];
   uint32_t mx = 0;
-#pragma unroll 2
-  for (int f = c0; f < F; f += 512) {
-    float x[8];
-    act(f, x);
+  auto seen = [&](const float (&x)[8]) __attribute__((always_inline)) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) mx = max(mx, abs_bits(x[e]));
+  };
+  if constexpr (NI > 0) {
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+      if (c0 + i * kActStep < F) { act(c0 + i * kActStep, kept[i]); seen(kept[i]); }
+  } else {
+#pragma unroll 2
+    for (int f = c0; f < F; f += kActStep) { act(f, kept[0]); seen(kept[0]); }
   }
-  mx = max(mx, (uint32_t)__builtin_amdgcn_mov_dpp((int)mx, 0x128, 0xF, 0xF, true));   // rotated by 8 lanes of 16
+  mx = max(mx, (uint32_t)__builtin_amdgcn_mov_dpp((int)mx, 0x124, 0xF, 0xF, true));   // rotated by 4 lanes of 16
+  mx = max(mx, (uint32_t)__builtin_amdgcn_mov_dpp((int)mx, 0x128, 0xF, 0xF, true));   // by 8
   mx = max_u32_xor32(max_u32_xor16(mx));
-  if (lane < 8) red[wave][lane] = mx;
+  if (lane < R) red[wave][lane] = mx;
   __syncthreads();
 #pragma unroll
   for (int w = 0; w < 8; ++w) mx = max(mx, red[w][r]);
-  if (threadIdx.x < 8 && m < M) row_mx[m] = mx;
+  if (threadIdx.x < R && m < M) row_mx[m] = mx;
   const float scale = row_scale(mx);
+  if constexpr (NI > 0) {
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+      if (c0 + i * kActStep < F) x3_store<3>(dst, KB, m, (c0 + i * kActStep) >> 3, kept[i], scale);
+  } else {
 #pragma unroll 2
-  for (int f = c0; f < F; f += 512) {
-    float x[8];
-    act(f, x);
-    x3_store<3>(dst, KB, m, f >> 3, x, scale);
+    for (int f = c0; f < F; f += kActStep) { act(f, kept[0]); x3_store<3>(dst, KB, m, f >> 3, kept[0], scale); }
   }
 }
 __global__ void k_swiglu_fwd(const float* __restrict__ gu, float* __restrict__ act, int F, size_t total) {
@@ -1489,12 +1503,13 @@ __global__ void k_swiglu_bwd4(const float* __restrict__ dact, const float* __res
 }
 // Maxima of d gate and d up by rows of tokens (of both) and by rows of features, and of act by rows of features, F % 64 == 0: the
 // scales of k_swiglu_bwd_pack with three pieces, before it, since a column's is known when all rows are.  256 tokens x 64 features per
-// workgroup, bound by its bytes.
+// workgroup, bound by its bytes: 64 x 384 tokens of the 0.5B decoder 310 us a layer (4.6 TB/s; two blocks of rows in flight instead of four
+// 317), 21 x 301 86, 7 x 141 18.
 struct SwigluMax { uint32_t *dgu_r, *dgu_c, *act_c; };
 __global__ void __launch_bounds__(256) k_swiglu_bwd_max(const float* __restrict__ dact, const float* __restrict__ gu, int M, int F, SwigluMax mx) {
   const int c = (threadIdx.x & 7) * 8, f = blockIdx.x * 64 + c;
   uint32_t cg[8] = {}, cu[8] = {}, ca[8] = {};
-#pragma unroll 2
+#pragma unroll 4
   for (int i = 0; i < 8; ++i) {
     const int m = blockIdx.y * 256 + 32 * i + (threadIdx.x >> 3);
     uint32_t rm = 0;
@@ -2601,8 +2616,13 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
         return launch(KID_SWIGLU, kernel, grid, dim3(threads), 0, st, (const float*)a.gu, Mi, F, x3_steps(F), (u32x4_t*)p.packa, mx.act_r);
       };
       const dim3 tiles(F / 64, blocks64);
-      T_CK(NP == 3 ? pack(k_swiglu_fwd_pack_rows, dim3(blocks64 * 8), 512)
-                   : NP == 2 ? pack(k_swiglu_fwd_pack<2>, tiles, 256) : pack(k_swiglu_fwd_pack<1>, tiles, 256));
+      if (NP == 3) {
+        const dim3 rows_grid(blocks64 * (64 / kActRows));
+        T_CK(F <= 5 * kActStep ? pack(k_swiglu_fwd_pack_rows<5>, rows_grid, 512) : F <= 9 * kActStep ? pack(k_swiglu_fwd_pack_rows<9>, rows_grid, 512)
+                                                                                             : pack(k_swiglu_fwd_pack_rows<0>, rows_grid, 512));
+      } else {
+        T_CK(NP == 2 ? pack(k_swiglu_fwd_pack<2>, tiles, 256) : pack(k_swiglu_fwd_pack<1>, tiles, 256));
+      }
       T_CK(gemm_x3(X3Op{nullptr, 0, Mi, F, false, mx.act_r, nullptr}, X3Op{TH(t0 + 8), F, d, F, false, mx.wd_r, mx.wd_c}, h_next, a.h2, d, 1.f,
                    xb, st, nullptr, split_fwd, p.packa));
       continue;
