@@ -286,9 +286,12 @@ static bool small_eligible(const sapo_weights* w) {
 // Is a rollout call cheaper on the small path?  256 workgroups run at once, so a step there costs rounds of 256
 // sequences, while the generic path's launches are shared by the whole batch and only its work grows.  Estimates in us,
 // fitted to 280 comparisons of the two paths on seven decoders (1 .. 8 layers, d 32 .. 128, vocabulary 256 .. 6000), 64 ..
-// 16384 sequences, contexts of 4 .. 270 tokens; above 512 sequences they name the faster path in all but 13, and in 12 of
-// those the two are within 15 % of each other.  Both sides at 2 layers, d 64, vocabulary 512 (us per step, contexts of
-// 28): small 109 / 217 / 433 / 868 at 1536 / 3072 / 6144 / 12288 sequences, generic 218 / 254 / 314 / 447.  Scoring stays
+// 16384 sequences, contexts of 4 .. 270 tokens, when a step of the small path took half as much again: above 512 sequences they then
+// named the faster path in all but 13, and in 12 of those the two were within 15 % of each other.  Both sides now (us per
+// step, contexts of 30, at 1536 / 3072 / 6144 / 12288 sequences): 2 layers, d 64, vocabulary 512, small 68 / 138 / 273 / 545, generic 210 /
+// 250 / 308 / 448; 4 layers, d 128, vocabulary 2048, 313 / 626 / 1253 / 2501 and 675 / 811 / 1091 / 1602; 1 layer, d 64, vocabulary 6000, 142 /
+// 286 / 572 / 1143 and 153 / 202 / 294 / 529.  Of these twelve the estimates give three to the generic path that the small one
+// would take 7, 11 and 23 % less for (the first decoder at 6144, the second at 3072, the third at 1536).  Scoring stays
 // on the small path whatever the batch: its tiles of 16 rows cost 0.2 .. 0.6 of the generic kernels at every size measured
 // (up to 262144 tokens).
 static bool small_pays(const sapo_model_config& c, int P, int Lp, int G, int N) {

@@ -923,7 +923,9 @@ static hipError_t launch_qkv_mid(const uint4* X, const uint4* W, int M, int N, i
 // 128-token instead of 256-token tiles by what the fullest compute unit multiplies, the smaller tile's operand traffic counted as
 // 8 %.  Scoring calls, us with 256- and 128-token tiles of gate/up, 0.5B: 1600 tokens 2859, 2668; 1800 3060, 2983; 2250 3228, 3232 (6
 // and 12 half tiles: equal); 3600 4992, 4924; 4800 5531, 5592; 6000 6599, 6500; 1.5B: 2709 10304, 10461; 4800 14370, 14729.  Of QKV,
-// 0.5B: 1800 tokens 3031, 2914; 2250 3266, 3146; 2709 3761, 3665; 8000 8134, 8081; 1.5B, 4800 14547, 14411.
+// 0.5B: 1800 tokens 2950, 2792; 2250 3228, 3100; 2709 3738, 3628; 8100 7897, 7896; 1.5B, 4800 14566, 14389; where the rule keeps 256-token
+// tiles, 0.5B: 12000 11060, 11123; 3600 4332, 4270; 6000 6379, 6334; 1.5B: 2709 9952, 9955; 3600 12117, 12021 (two half tiles on a unit
+// take up to 1.4 % less of a call than one whole one here; the line is the one for both products).
 static bool half_tiles_leave_less(int NX, int M) {
   const long cu = n_compute_units(), big = (long)NX * ((M + 255) / 256), small = (long)NX * ((M + 127) / 128);
   return (double)((small + cu - 1) / cu * 128) * 1.08 < (double)((big + cu - 1) / cu * 256);
@@ -944,8 +946,8 @@ hipError_t m_gemm_qkv_rope(const void* Xp, const void* Wp, int M, int N, int K, 
   }
   // With few workgroups the dispatcher may still put two on one compute unit, and the launch then takes their time one after the
   // other: 0.5B, 10 .. 16 token tiles, 20 us in some launches and 27 in most.  With more than half of a unit's LDS each has its
-  // own: 9 x 301 tokens 27.8 -> 21.1 us, 39 x 64 26.6 -> 20.0, 64 x 64 28.5 -> 21.5 (at most 18 workgroups on the fullest
-  // XCD of 32 units).  At 27 on an XCD the raster's empty workgroups, which ask for the LDS too, wait for units: 30.5 -> 38.8.
+  // own: 39 x 64 tokens 26.6 -> 20.0, 64 x 64 28.5 -> 21.5 (at most 18 workgroups on the fullest XCD of 32 units).  At 27 on an XCD it
+  // took 38.8 instead of 30.5, with a raster whose empty workgroups asked for the LDS too.
   constexpr int kAloneLds = 84 * 1024;
   static bool attr_done = false;
   if (!attr_done) {

@@ -3,7 +3,7 @@
 // The shape-generic kernels run one operation of one layer per launch; on a decoder whose matrices are a few hundred KB
 // every one of those launches is a few microseconds of latency around a fraction of a microsecond of work (the tiny
 // configuration: 23 launches per decode step, 135 us; here 12 us).  Its rollout call, 8 sequences of 16 + 16 tokens, went
-// from 2230 to 220 us, scoring 8 x 256 tokens from 360 to 65 us.  Sequences do not
+// from 2230 to 209 us, scoring 8 x 256 tokens from 360 to 65 us.  Sequences do not
 // depend on each other, so here a workgroup of 8 waves takes one sequence through all layers, positions and steps: the
 // activations stay in LDS, a workgroup barrier takes the place of a launch, the weights come out of the L2 again for
 // every step.

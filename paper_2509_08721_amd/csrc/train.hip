@@ -2548,7 +2548,7 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
   b_dv = b_dk; b_dv.b1 = Tq;
   b_scores.causal = 1; b_dp.causal = 1; b_pv.causal = 2; b_dq.causal = 2; b_dk.causal = 3; b_dv.causal = 3;
 
-  // The projections and the LM head run on the packed bf16-piece GEMM; forms as in sgemm<TA, TB>.
+  // The projections and the LM head run on the packed GEMM (k_gemm_x3); forms as in sgemm<TA, TB>.
   const int NP = tr->pieces;
   const X3Bufs xb{p.packa, p.packb, p.packa_cap, p.packb_cap, NP, p.kparts, split_parts_floats(D)};
   // Forward products are split over K with three pieces only: with two and one a sequence's log-probs do not depend on the

@@ -30,9 +30,9 @@ FAMILIES = {
     "k_decode_attention": (("k_decode_attention16",), ("kernels_decode.hip", "common.h")),
     "k_lmhead_sample": (("k_lmhead_sample16", "k_lmhead_sample_big"), ("kernels_decode.hip", "kernels_mfma.hip", "common.h")),
     "k_gemm_rows": (("k_rows_gate_up", "k_rows_down"), ("kernels_rows.hip", "tiles.h", "common.h")),
-    "k_gemm_big": (("k_gemm_big", "k_gemm_qkv_rope", "k_gemm_mid", "k_gemm_qkv_mid"), ("kernels_mfma.hip", "tiles.h", "common.h")),
+    "k_gemm_big": (("k_gemm_big", "k_gemm_qkv_rope", "k_gemm_mid", "k_gemm_qkv_mid"), ("kernels_mfma.hip", "tiles.h", "ranges.h", "common.h")),
     "k_flash_attention": (("k_flash_attention",), ("kernels_mfma.hip", "tiles.h", "common.h")),
-    "k_lmhead_score": (("k_lmhead_score(", "k_lmhead_score<", "k_lmhead_score"), ("kernels_mfma.hip", "tiles.h", "common.h")),
+    "k_lmhead_score": (("k_lmhead_score(", "k_lmhead_score<", "k_lmhead_score"), ("kernels_mfma.hip", "tiles.h", "ranges.h", "common.h")),
 }
 
 
