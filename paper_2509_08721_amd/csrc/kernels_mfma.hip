@@ -1063,15 +1063,17 @@ hipError_t m_rmsnorm_x32(const float* h, const float* gain, float eps, void* out
 // ---------------------------------------------------------------------------------------
 // LM head for scoring: log-softmax + target gather without materialising logits.
 // Rastered like the GEMM over (256-row tiles) x (groups of 128-feature tiles): a workgroup
-// walks the tiles of its group for its 256 rows keeping a (max, sum exp) per row and block of tiles, and the
-// one lane that sees a row's target id writes the target logit.  A second kernel merges the blocks
-// in a fixed order.  partials: ztarget [max_rows], from the next even number on [blocks][n_rows][2]; blocks and groups as in ranges.h.
+// walks the tiles of its group for its 256 rows, leaves every tile's (max, sum exp) of every row, and the
+// one lane that sees a row's target id writes the target logit.  A second kernel merges a row's tiles
+// in one order, so that a log-prob has the same bits whatever else is scored: groups follow the number of scored rows, and with a
+// (max, sum exp) per group a sequence's last bits changed with other sequences' masks.  32768 rows, vocabulary of 151936: 7.74 ms
+// and 62 us for the merge; with groups as the unit, whose running maxima cost 4 more exponentials per lane and tile, 7.71 and 14.  2678
+// rows: 507 and 8 us; 506 and 4.  (Blocks of two or three tiles as the unit: 3 .. 5 % longer, groups of whole blocks fill rounds worse.)
+// partials: ztarget [max_rows], from the next even number on [tiles][n_rows][2].
 // ---------------------------------------------------------------------------------------
 static int score_slots() { return 2 * n_compute_units(); }   // workgroups in flight
 __host__ __device__ constexpr size_t score_pairs_at(int max_rows) { return ((size_t)max_rows + 1) & ~(size_t)1; }
-size_t m_lmhead_score_partial_floats(int max_rows, int V) {
-  return score_pairs_at(max_rows) + 2 * (size_t)ScoreBlocks(V >> 7).n * max_rows;
-}
+size_t m_lmhead_score_partial_floats(int max_rows, int V) { return score_pairs_at(max_rows) + 2 * (size_t)(V >> 7) * max_rows; }
 
 __global__ void __launch_bounds__(256, 2) k_lmhead_score(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp,
                                                          int max_rows, const int* __restrict__ n_rows_dev, int V, int K,
@@ -1083,24 +1085,21 @@ __global__ void __launch_bounds__(256, 2) k_lmhead_score(const uint4* __restrict
   const int n_rows = *n_rows_dev;
   const int n_ft = V >> 7;
   const int row_tiles = (n_rows + 255) >> 8;
-  const ScoreBlocks blocks(n_ft);
-  const ScoreGroups g(blocks, row_tiles, slots);
+  const ScoreGroups g(n_ft, row_tiles, slots);
   int bx, by;
   if (!big_raster(g.groups, row_tiles, bx, by)) return;
-  int block = bx * g.blocks;
-  const int ft_begin = block * blocks.tiles, ft_end = min(n_ft, ft_begin + g.blocks * blocks.tiles);
-  int block_end = min(ft_end, ft_begin + blocks.tiles);
+  const int ft_begin = bx * g.tiles, ft_end = min(n_ft, ft_begin + g.tiles);
   const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63;
   const int row0 = by * 256 + wave * 64 + (lane & 31);
-  LseAcc lse[TJ];
   int target[TJ];
 #pragma unroll
   for (int tj = 0; tj < TJ; ++tj) {
-    lse[tj].init();
     const int row = row0 + tj * 32;
     target[tj] = -1;
     if (row < n_rows) target[tj] = tokens[(size_t)row_seq_pos[2 * row] * T + row_seq_pos[2 * row + 1]];
   }
+  float2* const pairs = (float2*)(partials + score_pairs_at(max_rows));
+  const int own_row = by * 256 + wave * 64 + lane;   // lane 32 and up: the row of tj 1
   float* ztarget = partials;
   TileLoop<TJ, H> loop;
   loop.tokens(Xp, (n_rows + 31) >> 5, K >> 4, by * 8, 0);
@@ -1114,20 +1113,22 @@ __global__ void __launch_bounds__(256, 2) k_lmhead_score(const uint4* __restrict
       loop.features(Wp, K >> 4, (ft + 1) * 4, 0, K / (16 * H), smem);
       loop.begin();
     }
+    float m[TJ], l[TJ];
 #pragma unroll
     for (int tj = 0; tj < TJ; ++tj) {
+      float mt = acc[0][tj][0];
+#pragma unroll
+      for (int fi = 0; fi < 4; ++fi)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) mt = fmaxf(mt, acc[fi][tj][v]);
+      mt = max_xor32(mt);
+      float su[4];
 #pragma unroll
       for (int fi = 0; fi < 4; ++fi) {
         const int f0 = ft * 128 + fi * 32 + (lane >> 5) * 4;
-        float mt = acc[fi][tj][0];
+        su[fi] = 0.f;
 #pragma unroll
-        for (int v = 1; v < 16; ++v) mt = fmaxf(mt, acc[fi][tj][v]);
-        const float mn = fmaxf(lse[tj].m, mt);
-        float su = 0.f;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) su += __expf(acc[fi][tj][v] - mn);
-        lse[tj].l = lse[tj].l * __expf(lse[tj].m - mn) + su;
-        lse[tj].m = mn;
+        for (int v = 0; v < 16; ++v) su[fi] += __expf(acc[fi][tj][v] - mt);
         const int dt = target[tj] - f0;   // target among this lane's 4 x 4 features?
         if (dt >= 0 && dt < 32 && (dt & 4) == 0) {
 #pragma unroll
@@ -1135,46 +1136,47 @@ __global__ void __launch_bounds__(256, 2) k_lmhead_score(const uint4* __restrict
             if (dt == 8 * (v >> 2) + (v & 3)) ztarget[row0 + tj * 32] = acc[fi][tj][v];
         }
       }
+      m[tj] = mt;
+      l[tj] = sum_xor32((su[0] + su[1]) + (su[2] + su[3]));   // in both halves of the wave
     }
-    if (ft + 1 == block_end) {   // merge the two lane halves
-#pragma unroll
-      for (int tj = 0; tj < TJ; ++tj) {
-        lse[tj].merge(__shfl_xor(lse[tj].m, 32, 64), __shfl_xor(lse[tj].l, 32, 64));
-        const int row = row0 + tj * 32;
-        if (lane < 32 && row < n_rows) {
-          float* p = partials + score_pairs_at(max_rows) + ((size_t)block * n_rows + row) * 2;
-          p[0] = lse[tj].m; p[1] = lse[tj].l;
-        }
-        lse[tj].init();
-      }
-      ++block;
-      block_end = min(ft_end, block_end + blocks.tiles);
-    }
+    if (own_row < n_rows) pairs[(size_t)ft * n_rows + own_row] = make_float2(lane < 32 ? m[0] : m[1], lane < 32 ? l[0] : l[1]);
   }
 }
 
-// 16 rows per workgroup: thread (row, part) merges the blocks part, part + 16, ... in order, then the parts pairwise.
-__global__ void __launch_bounds__(256) k_lmhead_score_merge(const float* __restrict__ partials, int max_rows, int V,
-                                                            const int* __restrict__ n_rows_dev, const int* __restrict__ row_seq_pos,
-                                                            int T, float* __restrict__ out_logprobs) {
-  __shared__ float s_m[4][16], s_l[4][16];
+// 16 rows per workgroup: thread (row, part) merges the tiles part, part + 64, ... in order, then the parts pairwise (16 parts: 10 us
+// instead of 5 with few rows).
+constexpr int kMergeThreads = 1024;
+__global__ void __launch_bounds__(kMergeThreads) k_lmhead_score_merge(const float* __restrict__ partials, int max_rows, int V,
+                                                                      const int* __restrict__ n_rows_dev, const int* __restrict__ row_seq_pos,
+                                                                      int T, float* __restrict__ out_logprobs) {
+  constexpr int kParts = kMergeThreads / 16;
+  __shared__ float2 s_ml[kMergeThreads / 64][16];
   const int n_rows = *n_rows_dev, wave = wave_index(threadIdx.x), lane = threadIdx.x & 63;
   if ((int)blockIdx.x * 16 >= n_rows) return;
-  const int row = min((int)blockIdx.x * 16 + (lane & 15), n_rows - 1), n_blocks = ScoreBlocks(V >> 7).n;
+  const int row = min((int)blockIdx.x * 16 + (lane & 15), n_rows - 1), n_tiles = V >> 7;
   const float2* p = (const float2*)(partials + score_pairs_at(max_rows)) + row;
   LseAcc a; a.init();
+  auto over_parts = [&] {   // of the wave's four
+#pragma unroll
+    for (int o = 32; o >= 16; o >>= 1) a.merge(__shfl_xor(a.m, o, 64), __shfl_xor(a.l, o, 64));
+  };
 #pragma unroll 4
-  for (int s = threadIdx.x >> 4; s < n_blocks; s += 16) {
+  for (int s = threadIdx.x >> 4; s < n_tiles; s += kParts) {
     const float2 ml = p[(size_t)s * n_rows];
     a.merge(ml.x, ml.y);
   }
-#pragma unroll
-  for (int o = 32; o >= 16; o >>= 1) a.merge(__shfl_xor(a.m, o, 64), __shfl_xor(a.l, o, 64));
-  if (lane < 16) { s_m[wave][lane] = a.m; s_l[wave][lane] = a.l; }
+  over_parts();
+  if (lane < 16) s_ml[wave][lane] = make_float2(a.m, a.l);
   __syncthreads();
-  if (threadIdx.x >= 16 || (int)blockIdx.x * 16 + lane >= n_rows) return;
+  if (wave != 0) return;
+  a.init();
 #pragma unroll
-  for (int w = 1; w < 4; ++w) a.merge(s_m[w][lane], s_l[w][lane]);
+  for (int w = 0; w < 4; ++w) {
+    const float2 ml = s_ml[(lane >> 4) * 4 + w][lane & 15];
+    a.merge(ml.x, ml.y);
+  }
+  over_parts();
+  if (lane >= 16 || (int)blockIdx.x * 16 + lane >= n_rows) return;
   const float zt = partials[row];
   out_logprobs[(size_t)row_seq_pos[2 * row] * T + row_seq_pos[2 * row + 1]] = zt - (a.m + logf(a.l));
 }
@@ -1191,11 +1193,11 @@ hipError_t m_lmhead_score(const void* Xp, const void* Wp, int max_rows, const in
     attr_done = true;
   }
   const int slots = score_slots();
-  const unsigned blocks = (unsigned)((score_most_workgroups(ScoreBlocks(V >> 7), max_rows, slots) + 7) / 8 * 8);
+  const unsigned blocks = (unsigned)((score_most_workgroups(V >> 7, max_rows, slots) + 7) / 8 * 8);
   const hipError_t e = launch(KID_LMHEAD_SCORE, k_lmhead_score, dim3(blocks), dim3(256), kBigLds, st, (const uint4*)Xp,
                               (const uint4*)Wp, max_rows, n_rows_dev, V, K, row_seq_pos, tokens, T, slots, partials);
   if (e != hipSuccess) return e;
-  return launch(KID_LMHEAD_SCORE_MERGE, k_lmhead_score_merge, dim3((max_rows + 15) / 16), dim3(256), 0, st, partials,
+  return launch(KID_LMHEAD_SCORE_MERGE, k_lmhead_score_merge, dim3((max_rows + 15) / 16), dim3(kMergeThreads), 0, st, partials,
                 max_rows, V, n_rows_dev, row_seq_pos, T, out_logprobs);
 }
 

@@ -29,48 +29,53 @@ struct StageRows {
 // tokens (11 token tiles) 4542 -> 4024, 24 x 200 (19) 6414 -> 5653, 17 x 700 (47) 11715 -> 10949, 64 x 768 (192) within 0.2 %; 1.5B: 9 x 301
 // 12258 -> 10277, 24 x 200 17066 -> 14602.  With the token tiles fastest in a panel 64 x 768 takes 1.4 % longer.
 constexpr int tile_blocks(int NX, int NY) { return (NX * NY + 7) / 8 * 8; }   // blocks of the launch
+// a / b for 0 <= a < 2^20, b > 0 from an approximation r of 1 / b within 2^-22 of it: (a + 1/2) / b lies 1 / (2 b) or more from the next
+// integers, and what is computed within 2^-21 (a + 1/2) / b of it.
+constexpr int quotient_by(int a, float r) { return (int)(((float)a + 0.5f) * r); }
+// On the GPU by the hardware's reciprocal: the compiler's division takes some 200 cycles, three of them 0.3 us of every launch (a scoring
+// call of 24 tokens, 6 layers of d_model 1024: 279 us with whole token tiles dealt to the XCDs, 286 with those, 277 with these).
+constexpr int quotient(int a, int b) {
+#ifdef __HIP_DEVICE_COMPILE__
+  if (a < 1 << 20) return quotient_by(a, __builtin_amdgcn_rcpf((float)b));
+#endif
+  return a / b;
+}
 constexpr bool tile_of_block(int id, int NX, int NY, int& bx, int& by) {
   const int n = NX * NY, per = (n + 7) >> 3, j = id >> 3, t = (id & 7) * per + j;
   if (j >= per || t >= n) return false;
-  const int panel = t / (8 * NX), w = t - panel * 8 * NX, rows = NY - panel * 8 < 8 ? NY - panel * 8 : 8;
-  const int block = w / (8 * rows), v = w - block * 8 * rows, cols = NX - block * 8 < 8 ? NX - block * 8 : 8, y = v / cols;
+  bx = t;
+  by = 0;
+  if (NY == 1) return true;
+  const int panel = NY <= 8 ? 0 : quotient(t, 8 * NX), w = t - panel * 8 * NX, rows = NY - panel * 8 < 8 ? NY - panel * 8 : 8;
+  const int block = rows == 8 ? w >> 6 : quotient(w, 8 * rows), v = w - block * 8 * rows, cols = NX - block * 8 < 8 ? NX - block * 8 : 8;
+  const int y = cols == 8 ? v >> 3 : quotient(v, cols);
   bx = block * 8 + v - y * cols;
   by = panel * 8 + y;
   return true;
 }
 
-// The LM-head scorer's log-sum-exp is added up over blocks of ScoreBlocks::tiles 128-feature tiles of the vocabulary, then over the
-// blocks, in an order that depends on the vocabulary alone: a row's log-prob has the same bits whatever else is scored.  Blocks
-// are as small as needed for one row tile to fill the chip (at most kMaxScoreBlocks); with the groups themselves as the unit (what
-// this replaces) a sequence's last bits changed with other sequences' masks.
-constexpr int kMaxScoreBlocks = 512;
-struct ScoreBlocks {
-  int n, tiles;   // their number, and the tiles of one (the last one may have fewer)
-  constexpr explicit ScoreBlocks(int n_ft) : n(0), tiles((n_ft + kMaxScoreBlocks - 1) / kMaxScoreBlocks) {
-    if (n_ft > 0) n = (n_ft + tiles - 1) / tiles;
-  }
-};
-// Groups of blocks, each walked by one workgroup per row tile: as few as fill whole rounds of the `slots` workgroups in flight, of
-// at most 32 tiles (one block where that is more).  The number of row tiles is that of the rows that are scored, which the device
-// counts.  us per call with groups of 16 tiles, halved while half of the call's positions gave fewer than 512 workgroups, and with
-// these: 0.5B, 24 x 200 tokens 5653, 5378; 9 x 301 4024, 3921 (the scorer 496 us with the row tiles dealt to the XCDs, now 312);
-// 64 x 768 46.2 ms both; 1.5B, 24 x 200 14602, 14192.
+// Groups that the LM-head scorer cuts the n_ft 128-feature tiles of the vocabulary into, each walked by one workgroup per row
+// tile: as few as fill whole rounds of the `slots` workgroups in flight, of at most 32 tiles each.  The number of row tiles is
+// that of the rows that are scored, which the device counts; what a row's log-prob is added up from does not depend on it
+// (k_lmhead_score).  us per call with groups of 16 tiles, halved while half of the
+// call's positions gave fewer than 512 workgroups, and with these: 0.5B, 24 x 200 tokens 5653, 5378; 9 x 301 4024, 3921 (the scorer 496 us
+// with the row tiles dealt to the XCDs, now 312); 64 x 768 46.2 ms both; 1.5B, 24 x 200 14602, 14192.
 struct ScoreGroups {
-  int groups, blocks;   // their number, and the blocks of one (the last one may have fewer)
-  constexpr ScoreGroups(const ScoreBlocks& b, int row_tiles, int slots) : groups(0), blocks(1) {
-    if (row_tiles <= 0 || b.n <= 0) return;
-    const int longest = b.tiles < 32 ? 32 / b.tiles : 1, least = (b.n + longest - 1) / longest;
-    const int rounds = (least * row_tiles + slots - 1) / slots, fill = slots * rounds / row_tiles;   // fill >= least
-    const int most = fill < b.n ? fill : b.n;
-    blocks = (b.n + most - 1) / most;
-    groups = (b.n + blocks - 1) / blocks;
+  int groups, tiles;   // their number, and the tiles of one (the last one may have fewer)
+  constexpr ScoreGroups(int n_ft, int row_tiles, int slots) : groups(0), tiles(1) {
+    if (row_tiles <= 0 || n_ft <= 0) return;
+    const int least = (n_ft + 31) / 32;
+    const int rounds = quotient(least * row_tiles + slots - 1, slots), fill = quotient(slots * rounds, row_tiles);   // fill >= least
+    const int most = fill < n_ft ? fill : n_ft;
+    tiles = quotient(n_ft + most - 1, most);
+    groups = quotient(n_ft + tiles - 1, tiles);
   }
 };
 // Largest number of workgroups of a call that scores up to max_rows rows
-constexpr long score_most_workgroups(const ScoreBlocks& b, int max_rows, int slots) {
+constexpr long score_most_workgroups(int n_ft, int max_rows, int slots) {
   long most = 0;
   for (int t = 1; t <= (max_rows + 255) / 256; ++t) {
-    const long n = (long)ScoreGroups(b, t, slots).groups * t;
+    const long n = (long)ScoreGroups(n_ft, t, slots).groups * t;
     if (n > most) most = n;
   }
   return most;

@@ -80,25 +80,41 @@ int main() {
 """)
 
 
-def test_scorer_blocks_and_groups_cover_the_vocabulary(tmp_path):
-    """Every feature tile lies in one block and every block in one group, none is empty, a group has at most 32 tiles, there are no
-    more blocks than kMaxScoreBlocks, and the launch made for max_rows holds what any smaller number of rows asks for."""
+def test_quotients_by_an_approximate_reciprocal_are_exact(tmp_path):
+    """Around every multiple of b up to 2^20, with reciprocals as far off as quotient_by allows."""
     run(tmp_path, r"""
 int main() {
   int bad = 0;
-  for (int n_ft : {1, 2, 8, 31, 32, 33, 64, 400, 511, 512, 513, 1187, 2000})
+  for (int b = 1; b <= 12000; b += b < 600 ? 1 : 61)
+    for (double off : {-1.0, 0.0, 1.0}) {
+      const float r = (float)((1.0 / b) * (1.0 + off * 1.8e-7));   // and a rounding: within 2^-22
+      for (int q = 0; q * b < 1 << 20; q += 1 + q / 97)
+        for (int a : {q * b - 1, q * b, q * b + b / 2})
+          if (a >= 0 && a < 1 << 20 && quotient_by(a, r) != a / b) { if (!bad) printf("%d / %d\n", a, b); ++bad; }
+      if (quotient_by((1 << 20) - 1, r) != ((1 << 20) - 1) / b) ++bad;
+    }
+  return bad != 0;
+}
+""")
+
+
+def test_scorer_groups_cover_the_vocabulary_within_their_launch(tmp_path):
+    """Every feature tile lies in one group, no group is empty or longer than 32 tiles, and the launch made for
+    max_rows holds what any smaller number of rows asks for."""
+    run(tmp_path, r"""
+int main() {
+  int bad = 0;
+  for (int n_ft : {1, 2, 8, 31, 32, 33, 64, 400, 1187, 2000})
     for (int slots : {512, 304})
       for (int max_rows : {1, 255, 256, 257, 2709, 49152}) {
-        const ScoreBlocks b(n_ft);
-        bad += b.n < 1 || b.n > kMaxScoreBlocks || b.n * b.tiles < n_ft || (b.n - 1) * b.tiles >= n_ft;
-        const long most = score_most_workgroups(b, max_rows, slots);
+        const long most = score_most_workgroups(n_ft, max_rows, slots);
         for (int rows = 0; rows <= max_rows; rows += rows < 600 ? 1 : 509) {
           const int t = (rows + 255) / 256;
-          const ScoreGroups g(b, t, slots);
+          const ScoreGroups g(n_ft, t, slots);
           if (rows == 0) { bad += g.groups != 0; continue; }
-          bad += g.blocks < 1 || g.blocks * b.tiles > 32 || g.groups * g.blocks < b.n || (g.groups - 1) * g.blocks >= b.n;
+          bad += g.tiles < 1 || g.tiles > 32 || g.groups * g.tiles < n_ft || (g.groups - 1) * g.tiles >= n_ft;
           bad += (long)g.groups * t > most;
-          if (bad) { printf("%d tiles, %d slots, %d of %d rows: %d groups of %d\n", n_ft, slots, rows, max_rows, g.groups, g.blocks); return 1; }
+          if (bad) { printf("%d tiles, %d slots, %d of %d rows: %d groups of %d\n", n_ft, slots, rows, max_rows, g.groups, g.tiles); return 1; }
         }
       }
   return 0;
