@@ -418,19 +418,22 @@ __global__ void __launch_bounds__(256) k_pack_x3_max(const float* __restrict__ s
       *(float4*)&x[i][0] = *(const float4*)q;
       *(float4*)&x[i][4] = *(const float4*)(q + 4);
     }
+  } else if (vec && (K & 3) == 0) {   // outside: the last row, the last four k, taken out again; no branch between the loads
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const float4 v = *(const float4*)(src + (size_t)min(row_of(i), rows - 1) * ld + min(k0 + 4 * h, K - 4));
+        *(float4*)&x[i][4 * h] = row_of(i) < rows && k0 + 4 * h < K ? v : make_float4(0.f, 0.f, 0.f, 0.f);
+      }
   } else {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int row = row_of(i);
-      const float* q = src + (size_t)row * ld + k0;
-      if (vec && row < rows && k0 + 8 <= K) {
-        *(float4*)&x[i][0] = *(const float4*)q;
-        *(float4*)&x[i][4] = *(const float4*)(q + 4);
-      } else {
+    for (int i = 0; i < 8; ++i)
 #pragma unroll
-        for (int j = 0; j < 8; ++j) x[i][j] = (row < rows && k0 + j < K) ? q[j] : 0.f;
+      for (int j = 0; j < 8; ++j) {
+        const float v = src[(size_t)min(row_of(i), rows - 1) * ld + min(k0 + j, K - 1)];
+        x[i][j] = row_of(i) < rows && k0 + j < K ? v : 0.f;
       }
-    }
   }
   if (octet >= KB * 2) return;   // padded steps are a multiple of 4 (8 octets): the whole wave
 #pragma unroll
@@ -1194,14 +1197,22 @@ __global__ void k_probs_from_lse(float* __restrict__ sc, const float* __restrict
 __device__ __forceinline__ float swiglu(float g, float u) { return g / (1.0f + expf(-g)) * u; }
 // act = silu(gate) * up from gu[M, 2F] (gate columns first).  Workgroup (x, y): columns of row y, four per thread where F
 // allows it.
-__global__ void k_swiglu_fwd4(const float* __restrict__ gu, float* __restrict__ act, int F) {
+// row_mx, if given: the row's maximum.
+__device__ __forceinline__ uint32_t abs_bits4(const float4& v) { return max(max(abs_bits(v.x), abs_bits(v.y)), max(abs_bits(v.z), abs_bits(v.w))); }
+__global__ void k_swiglu_fwd4(const float* __restrict__ gu, float* __restrict__ act, int F, uint32_t* __restrict__ row_mx) {
   const int f = (blockIdx.x * 256 + threadIdx.x) * 4;
-  if (f >= F) return;
-  const float* row = gu + (size_t)blockIdx.y * 2 * F + f;
-  const float4 g = *(const float4*)row, u = *(const float4*)(row + F);
-  float4 o;
-  o.x = swiglu(g.x, u.x); o.y = swiglu(g.y, u.y); o.z = swiglu(g.z, u.z); o.w = swiglu(g.w, u.w);
-  *(float4*)(act + (size_t)blockIdx.y * F + f) = o;
+  uint32_t mx = 0;
+  if (f < F) {
+    const float* row = gu + (size_t)blockIdx.y * 2 * F + f;
+    const float4 g = *(const float4*)row, u = *(const float4*)(row + F);
+    float4 o;
+    o.x = swiglu(g.x, u.x); o.y = swiglu(g.y, u.y); o.z = swiglu(g.z, u.z); o.w = swiglu(g.w, u.w);
+    *(float4*)(act + (size_t)blockIdx.y * F + f) = o;
+    mx = abs_bits4(o);
+  }
+  if (!row_mx) return;
+  mx = wave_max_u32(mx);
+  if ((threadIdx.x & 63) == 0) atomicMax(row_mx + blockIdx.y, mx);
 }
 // The same straight into the packed operand of the down projection, F % 64 == 0: act itself is not stored (the backward pass
 // makes its other packed form again, k_swiglu_bwd_pack).  64 tokens x 64 features per workgroup, bound by its bytes.  us a
@@ -1489,17 +1500,24 @@ __device__ __forceinline__ void swiglu_grad(float g, float u, float da, float& d
   dg = da * u * sg * (1.0f + g * (1.0f - sg));
   du = da * g * sg;
 }
-__global__ void k_swiglu_bwd4(const float* __restrict__ dact, const float* __restrict__ gu, float* __restrict__ dgu, int F) {
+__global__ void k_swiglu_bwd4(const float* __restrict__ dact, const float* __restrict__ gu, float* __restrict__ dgu, int F,
+                              uint32_t* __restrict__ row_mx) {
   const int f = (blockIdx.x * 256 + threadIdx.x) * 4;
-  if (f >= F) return;
-  const float* row = gu + (size_t)blockIdx.y * 2 * F + f;
-  float* out = dgu + (size_t)blockIdx.y * 2 * F + f;
-  const float4 g = *(const float4*)row, u = *(const float4*)(row + F), da = *(const float4*)(dact + (size_t)blockIdx.y * F + f);
-  float4 dg, du;
-  swiglu_grad(g.x, u.x, da.x, dg.x, du.x); swiglu_grad(g.y, u.y, da.y, dg.y, du.y);
-  swiglu_grad(g.z, u.z, da.z, dg.z, du.z); swiglu_grad(g.w, u.w, da.w, dg.w, du.w);
-  *(float4*)out = dg;
-  *(float4*)(out + F) = du;
+  uint32_t mx = 0;
+  if (f < F) {
+    const float* row = gu + (size_t)blockIdx.y * 2 * F + f;
+    float* out = dgu + (size_t)blockIdx.y * 2 * F + f;
+    const float4 g = *(const float4*)row, u = *(const float4*)(row + F), da = *(const float4*)(dact + (size_t)blockIdx.y * F + f);
+    float4 dg, du;
+    swiglu_grad(g.x, u.x, da.x, dg.x, du.x); swiglu_grad(g.y, u.y, da.y, dg.y, du.y);
+    swiglu_grad(g.z, u.z, da.z, dg.z, du.z); swiglu_grad(g.w, u.w, da.w, dg.w, du.w);
+    *(float4*)out = dg;
+    *(float4*)(out + F) = du;
+    mx = max(abs_bits4(dg), abs_bits4(du));
+  }
+  if (!row_mx) return;
+  mx = wave_max_u32(mx);
+  if ((threadIdx.x & 63) == 0) atomicMax(row_mx + blockIdx.y, mx);
 }
 // Maxima of d gate and d up by rows of tokens (of both) and by rows of features, and of act by rows of features, F % 64 == 0: the
 // scales of k_swiglu_bwd_pack with three pieces, before it, since a column's is known when all rows are.  256 tokens x 64 features per
@@ -2232,7 +2250,7 @@ struct TrainPlan {
   std::vector<LayerMax> mx;
   uint32_t *xn_r, *dh_r, *dl_r, *xfc_r;            // by rows, written anew for every layer or chunk
   uint32_t *head_r, *head_c, *xfc_c, *dl_c;
-  uint32_t* mx_zero;                                        // the atomics' ones, mx_zero_n of them (head_c is on its own)
+  uint32_t* mx_zero;                                        // the atomics' ones, mx_zero_n of them (head_c lies in front of them: zeroed once per update)
   size_t mx_zero_n;
   std::vector<LayerActs> layer;
   bool packed_ffn;                              // the SwiGLU passes write packed operands (act of a layer is not kept)
@@ -2570,7 +2588,7 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
     return gemm_x3_tn(A_.x, A_.ld, B_.x, B_.ld, C, Mg, Ng, Kg, beta, xb, st, A_.col_mx, B_.col_mx);
   };
   auto rows_max = [&](const float* x, int K_, uint32_t* out) { return NP == 3 ? row_max(x, Mi, K_, out, st) : hipSuccess; };
-  if (NP == 3) T_CK(g_fill_f32((float*)p.mx_zero, 0.f, p.mx_zero_n, st));
+  if (NP == 3 && !first) T_CK(g_fill_f32((float*)p.mx_zero, 0.f, p.mx_zero_n, st));   // the first micro-batch: with head_c
 
   const int blocks64 = (Mi + 127) / 128 * 2;   // blocks of 64 tokens that a packed operand by rows of tokens holds
   // ---- forward, every activation kept
@@ -2627,11 +2645,13 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
                    xb, st, nullptr, split_fwd, p.packa));
       continue;
     }
-    if (F % 4 == 0 && M <= 65535)
-      T_CK(launch(KID_SWIGLU, k_swiglu_fwd4, dim3((F / 4 + 255) / 256, Mi), dim3(256), 0, st, (const float*)a.gu, a.act, F));
-    else
+    if (F % 4 == 0 && M <= 65535) {
+      T_CK(launch(KID_SWIGLU, k_swiglu_fwd4, dim3((F / 4 + 255) / 256, Mi), dim3(256), 0, st, (const float*)a.gu, a.act, F,
+                  NP == 3 ? mx.act_r : nullptr));
+    } else {
       T_CK(launch(KID_SWIGLU, k_swiglu_fwd, dim3(blocks256(M * D.F)), dim3(256), 0, st, (const float*)a.gu, a.act, F, M * D.F));
-    T_CK(rows_max(a.act, F, mx.act_r));
+      T_CK(rows_max(a.act, F, mx.act_r));
+    }
     T_CK(mm_nt(Mat{a.act, F, mx.act_r, mx.act_c}, Mat{TH(t0 + 8), F, mx.wd_r, mx.wd_c}, h_next, d, Mi, d, F, 1.f, a.h2));
   }
   T_CK(rmsnorm_fwd(p.h_last, TH(t_final), c.rms_eps, Mi, d, p.xf, p.rf, NP == 3 ? p.xn_r : nullptr, st));
@@ -2710,13 +2730,14 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
                    xb, st, p.act_cols));
     } else {
       T_CK(mm_tn(dh1, Mat{a.act, F, mx.act_r, mx.act_c}, GR(t0 + 8), d, F, Mi, keep));
-      if (F % 4 == 0 && M <= 65535)
+      if (F % 4 == 0 && M <= 65535) {
         T_CK(launch(KID_SWIGLU, k_swiglu_bwd4, dim3((F / 4 + 255) / 256, Mi), dim3(256), 0, st, (const float*)p.dact,
-                    (const float*)a.gu, p.dgu, F));
-      else
+                    (const float*)a.gu, p.dgu, F, NP == 3 ? mx.dgu_r : nullptr));
+      } else {
         T_CK(launch(KID_SWIGLU, k_swiglu_bwd, dim3(blocks256(M * D.F)), dim3(256), 0, st, (const float*)p.dact, (const float*)a.gu,
                     p.dgu, F, M * D.F));
-      T_CK(rows_max(p.dgu, 2 * F, mx.dgu_r));
+        T_CK(rows_max(p.dgu, 2 * F, mx.dgu_r));
+      }
       const Mat dgu{p.dgu, 2 * F, mx.dgu_r, mx.dgu_c};
       T_CK(mm_nn(dgu, Mat{TH(t0 + 6), d, mx.wgu_r, mx.wgu_c}, p.dx, d, Mi, d, 2 * F, 0.f));
       T_CK(mm_tn(dgu, Mat{a.xn2, d, nullptr, mx.xn2_c}, GR(t0 + 6), 2 * F, d, Mi, keep));
@@ -2860,7 +2881,7 @@ extern "C" int sapo_policy_update(sapo_trainer* tr, const int32_t* tokens, const
       T_CK(add(w(8), D.d, D.F, p.mx[l].wd_r));
     }
     if (t.n > 0) T_CK(flush());
-    T_CK(g_fill_f32((float*)p.head_c, 0.f, D.d, st));
+    T_CK(g_fill_f32((float*)p.head_c, 0.f, (size_t)(p.mx_zero - p.head_c) + p.mx_zero_n, st));
   }
   T_CK(x3_pack(X3Op{head, d, V, d, false, p.head_r, p.head_c}, p.head_nt, p.head_cap, NP, st));        // rows = vocabulary
   T_CK(x3_pack(X3Op{head, d, d, V, true, p.head_c, nullptr}, p.head_t, p.head_t_cap, NP, st));       // rows = d
