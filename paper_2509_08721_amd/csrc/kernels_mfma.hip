@@ -121,7 +121,12 @@ constexpr int kRing = 3;                                            // stages of
 constexpr int ring_bytes(int H) { return kRing * 4 * H * 1024; }     // 4 H fragments of 1 KiB per stage
 constexpr int kBigLds = ring_bytes(4);
 
-__device__ __forceinline__ bool big_raster(int NX, int NY, int& bx, int& by) { return tile_of_block(blockIdx.x, NX, NY, bx, by); }
+__device__ __forceinline__ bool big_raster(int NX, int NY, int& bx, int& by) {
+  const bool any = tile_of_block(blockIdx.x, NX, NY, bx, by);
+  bx = __builtin_amdgcn_readfirstlane(bx);   // the quotients come out of vector registers: addresses would stay there
+  by = __builtin_amdgcn_readfirstlane(by);
+  return any;
+}
 static int big_grid(int NX, int NY) { return tile_blocks(NX, NY); }
 
 // The k loop of one tile.  begin() requests the first two stages, run() multiplies all of them; a caller that walks several

@@ -4,6 +4,12 @@
 #include <cstddef>
 #include <cstdint>
 
+#ifdef __HIP__
+#define SAPO_HD __host__ __device__
+#else
+#define SAPO_HD
+#endif
+
 namespace sapo {
 
 // Contraction of k_gemm_x3_tn over token rows [k_begin, k_end) in nst stages of ks rows.  The last stage ends at k_end, so
@@ -29,26 +35,34 @@ struct StageRows {
 // tokens (11 token tiles) 4542 -> 4024, 24 x 200 (19) 6414 -> 5653, 17 x 700 (47) 11715 -> 10949, 64 x 768 (192) within 0.2 %; 1.5B: 9 x 301
 // 12258 -> 10277, 24 x 200 17066 -> 14602.  With the token tiles fastest in a panel 64 x 768 takes 1.4 % longer.
 constexpr int tile_blocks(int NX, int NY) { return (NX * NY + 7) / 8 * 8; }   // blocks of the launch
-// a / b for 0 <= a < 2^20, b > 0 from an approximation r of 1 / b within 2^-22 of it: (a + 1/2) / b lies 1 / (2 b) or more from the next
-// integers, and what is computed within 2^-21 (a + 1/2) / b of it.
+// a / b for 0 <= a < 2^20, 0 < b < 2^19, from an approximation r of 1 / b within 2^-22 of it: (a + 1/2) / b lies 1 / (2 b) or more from the
+// next integers, and what is computed within 2^-21 (a + 1/2) / b of it.
 constexpr int quotient_by(int a, float r) { return (int)(((float)a + 0.5f) * r); }
-// On the GPU by the hardware's reciprocal: the compiler's division takes some 200 cycles, three of them 0.3 us of every launch (a scoring
-// call of 24 tokens, 6 layers of d_model 1024: 279 us with whole token tiles dealt to the XCDs, 286 with those, 277 with these).
-constexpr int quotient(int a, int b) {
-#ifdef __HIP_DEVICE_COMPILE__
-  if (a < 1 << 20) return quotient_by(a, __builtin_amdgcn_rcpf((float)b));
-#endif
-  return a / b;
+// The same for 0 <= a < 2^31 - 2^19: what the approximation leaves is between -2^20 and 2^20.
+constexpr int large_quotient_by(int a, int b, float r) {
+  const int q = (int)((float)a * r), rest = a - q * b, more = quotient_by(rest < 0 ? -1 - rest : rest, r);
+  return rest < 0 ? q - 1 - more : q + more;
 }
-constexpr bool tile_of_block(int id, int NX, int NY, int& bx, int& by) {
+SAPO_HD inline float reciprocal(int b) {
+#ifdef __HIP_DEVICE_COMPILE__
+  return __builtin_amdgcn_rcpf((float)b);
+#else
+  return 1.0f / (float)b;
+#endif
+}
+SAPO_HD inline int quotient(int a, int b) { return quotient_by(a, reciprocal(b)); }
+// What a workgroup executes before its first request counts: us per scoring call of 24 tokens, 6 layers of d_model 1024, with three of
+// the compiler's divisions 286, with these quotients and no branch around the panels 284, as it is 263; 2709 tokens within 0.7 %.
+SAPO_HD inline bool tile_of_block(int id, int NX, int NY, int& bx, int& by) {
   const int n = NX * NY, per = (n + 7) >> 3, j = id >> 3, t = (id & 7) * per + j;
   if (j >= per || t >= n) return false;
-  bx = t;
-  by = 0;
-  if (NY == 1) return true;
-  const int panel = NY <= 8 ? 0 : quotient(t, 8 * NX), w = t - panel * 8 * NX, rows = NY - panel * 8 < 8 ? NY - panel * 8 : 8;
-  const int block = rows == 8 ? w >> 6 : quotient(w, 8 * rows), v = w - block * 8 * rows, cols = NX - block * 8 < 8 ? NX - block * 8 : 8;
-  const int y = cols == 8 ? v >> 3 : quotient(v, cols);
+  int panel = 0, w = t, rows = NY;
+  if (NY > 8) {
+    panel = large_quotient_by(t, 8 * NX, reciprocal(8 * NX));
+    w -= panel * 8 * NX;
+    rows = NY - panel * 8 < 8 ? NY - panel * 8 : 8;
+  }
+  const int block = quotient(w, 8 * rows), v = w - block * 8 * rows, cols = NX - block * 8 < 8 ? NX - block * 8 : 8, y = quotient(v, cols);
   bx = block * 8 + v - y * cols;
   by = panel * 8 + y;
   return true;
@@ -62,7 +76,7 @@ constexpr bool tile_of_block(int id, int NX, int NY, int& bx, int& by) {
 // with the row tiles dealt to the XCDs, now 312); 64 x 768 46.2 ms both; 1.5B, 24 x 200 14602, 14192.
 struct ScoreGroups {
   int groups, tiles;   // their number, and the tiles of one (the last one may have fewer)
-  constexpr ScoreGroups(int n_ft, int row_tiles, int slots) : groups(0), tiles(1) {
+  SAPO_HD ScoreGroups(int n_ft, int row_tiles, int slots) : groups(0), tiles(1) {
     if (row_tiles <= 0 || n_ft <= 0) return;
     const int least = (n_ft + 31) / 32;
     const int rounds = quotient(least * row_tiles + slots - 1, slots), fill = quotient(slots * rounds, row_tiles);   // fill >= least
@@ -72,7 +86,7 @@ struct ScoreGroups {
   }
 };
 // Largest number of workgroups of a call that scores up to max_rows rows
-constexpr long score_most_workgroups(int n_ft, int max_rows, int slots) {
+inline long score_most_workgroups(int n_ft, int max_rows, int slots) {
   long most = 0;
   for (int t = 1; t <= (max_rows + 255) / 256; ++t) {
     const long n = (long)ScoreGroups(n_ft, t, slots).groups * t;

@@ -81,7 +81,7 @@ int main() {
 
 
 def test_quotients_by_an_approximate_reciprocal_are_exact(tmp_path):
-    """Around every multiple of b up to 2^20, with reciprocals as far off as quotient_by allows."""
+    """Around multiples of b up to 2^20, and up to 2^31 - 2^19 for the large ones, with reciprocals as far off as quotient_by allows."""
     run(tmp_path, r"""
 int main() {
   int bad = 0;
@@ -91,7 +91,10 @@ int main() {
       for (int q = 0; q * b < 1 << 20; q += 1 + q / 97)
         for (int a : {q * b - 1, q * b, q * b + b / 2})
           if (a >= 0 && a < 1 << 20 && quotient_by(a, r) != a / b) { if (!bad) printf("%d / %d\n", a, b); ++bad; }
-      if (quotient_by((1 << 20) - 1, r) != ((1 << 20) - 1) / b) ++bad;
+      const long most = (1L << 31) - (1L << 19);
+      for (long q = 0; q * b < most; q += 1 + q / 61)
+        for (long a : {q * b - 1, q * b, q * b + b / 2, most - 1 - q})
+          if (a >= 0 && a < most && large_quotient_by((int)a, b, r) != a / b) { if (!bad) printf("%ld / %d\n", a, b); ++bad; }
     }
   return bad != 0;
 }
