@@ -1167,7 +1167,7 @@ struct ScorePlan {
   int* src_rows;    // [chunk_seqs * T]
   void* x;          // [chunk_seqs * T, d] final-norm output of the gathered rows (T)
   float* logits;    // [row_chunk, V] (shape-generic kernels)
-  float* partials;  // fused LM-head partials (MFMA kernels)
+  float* partials;  // fused LM-head partials (MFMA kernels): over the layers' buffers, which are done with by then
   float* gain_t;    // [d] final-norm gains divided by the temperature (scoring at a temperature)
   size_t bytes;
 };
@@ -1188,10 +1188,16 @@ static void plan_score(const sapo_weights* w, int S, int T, int chunk_seqs, size
   pl.rows = A.take<int>(2 * R);
   pl.src_rows = A.take<int>(R);
   carve_cache(A, w, chunk_seqs, pl.pages_per_seq, (size_t)chunk_seqs * pl.pages_per_seq, pl.cache);
+  const size_t fwd_at = A.off = (A.off + 255) & ~(size_t)255;   // where pl.fwd.h begins
   carve_fwd(A, w, M, pl.fwd);
+  pl.partials = nullptr;
+  if (w->mfma) {   // 9.5 KB a token at a vocabulary of 151936, where the layers' buffers are 24 (0.5B) to 42 (1.5B)
+    const size_t need = m_lmhead_score_partial_floats((int)M, c.vocab) * sizeof(float), have = A.off - fwd_at;
+    if (need > have) A.off = fwd_at + need;
+    pl.partials = pl.fwd.h;
+  }
   pl.x = A.take_bytes((R + 63) / 64 * 64 * c.d_model * w->elt);
   pl.logits = w->mfma ? nullptr : A.take<float>((size_t)pl.row_chunk * c.vocab);
-  pl.partials = w->mfma ? A.take<float>(m_lmhead_score_partial_floats((int)M, c.vocab)) : nullptr;
   pl.gain_t = A.take<float>(c.d_model);
   pl.bytes = (A.off + 255) & ~(size_t)255;
 }

@@ -73,7 +73,10 @@ def test_a_sequence_scores_the_same_alone_and_among_others(shape):
     gw.close()
 
 
-@pytest.mark.parametrize("shape", [replace(W.HALF_B, n_layers=1), replace(W.MINI_BF16, max_seq=1024)], ids=["vocabulary of 151936", "mini"])
+# the last one's (max, sum of exponentials) pairs take more than the layers' buffers, where they lie
+@pytest.mark.parametrize("shape", [replace(W.HALF_B, n_layers=1), replace(W.MINI_BF16, max_seq=1024),
+                                   replace(W.MINI_BF16, n_layers=1, vocab=131072, max_seq=1024)],
+                         ids=["vocabulary of 151936", "mini", "mini with a vocabulary of 131072"])
 def test_log_probs_keep_their_bits_whatever_else_is_scored(shape):
     """The scorer's workgroups follow the number of rows that the masks name; a sequence's log-probs are the same bits with other
     sequences' masks empty, sparse or full, with fewer sequences, and at positions its own mask adds none to."""
@@ -92,4 +95,16 @@ def test_log_probs_keep_their_bits_whatever_else_is_scored(shape):
     for n in (1, 3, 9):
         lp, _ = sapo.sapo_score_logprobs(gw, tokens[:n].contiguous(), full[:n].contiguous(), rewards[:n].contiguous(), 1)
         assert torch.equal(lp, want[:n]), n
+    gw.close()
+
+
+def test_workspace_of_scoring_has_no_room_of_its_own_for_the_scorer():
+    """A call's workspace is what its layers need, the rows to score and their final norms: a (max, sum of exponentials) per row
+    and 128 entries of the vocabulary, 467 MB here, lies where the layers' buffers were."""
+    shape = replace(W.HALF_B, n_layers=1)
+    gw = sapo.sapo_weights_create(shape, W.make_weights(shape, 47))
+    S, T = 64, 768
+    d, q, kv, F = shape.d_model, shape.q_dim, shape.kv_dim, shape.d_ff
+    layers = 4 * d + 2 * d + 4 * (q + 2 * kv) + 2 * q + 2 * q + 2 * F + 4 * (d // 64 + 3)   # bytes per token
+    assert sapo.sapo_score_workspace_bytes(gw, S, T) <= S * T * (layers + 2 * 2 * kv * shape.n_layers + 2 * d + 12) + (1 << 20)
     gw.close()
