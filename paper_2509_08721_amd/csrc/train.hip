@@ -270,11 +270,11 @@ __global__ void __launch_bounds__(256) k_sgemm_mfma(const float* __restrict__ A,
 // of the product and of either sign, is dropped.  The output is scaled back by an exact power of two.  Three
 // v_mfma_f32_32x32x16_f16 (32 cycles each) do the work of sixteen v_mfma_f32_32x32x2_f32 (64 cycles each).  What this replaces,
 // values cut into three bf16 pieces without scales and six partial products, dropped products up to 2^-21 of one sign,
-// took six, and 6 bytes a value instead of 4: 64 x 384 tokens of the 0.5B decoder 386 -> 259 ms an update, 21 x 301 tokens 109 -> 77,
-// with smaller errors against 64 bits, since the sums take half as many roundings (21 x 301 tokens: gradient 2.7e-5 -> 1.2e-5,
-// log-probs 1.7e-6 -> 1.3e-6).  Of that the products 285 -> 190 ms (1.19 PFLOP/s of executed products, 1.48 in the largest).
+// took six, and 6 bytes a value instead of 4: 64 x 384 tokens of the 0.5B decoder 385 -> 264 ms an update, the products 287 -> 170
+// (1.17 PFLOP/s executed, 1.48 in the largest), with smaller errors against 64 bits, since the sums take half as many roundings (64 x
+// 384 tokens: gradient 1.5e-5 -> 8.5e-6, log-probs 1.36e-6 -> 1.24e-6; 3 x 65: 2.9e-6 -> 2.3e-6, 1.06e-6 -> 1.00e-6).
 // That is NP = 3, the accuracy of three bf16 pieces.  With NP = 2 a value is rounded to bf16 and the remainder to bf16 (16
-// significant bits, no scales: 5 % less time an update), the same three products; with NP = 1 the same kernels are a plain
+// significant bits, no scales: 7 % less time an update), the same three products; with NP = 1 the same kernels are a plain
 // bf16 GEMM with fp32 accumulation (the value rounded to nearest).
 //
 // A row's largest value is kept as its bits without the sign, as integers order them (NaN above infinity above all others);
