@@ -580,7 +580,12 @@ static int run_layers_generic(const sapo_weights* w, const FwdBufs& b, int M, Ro
 }
 
 // MFMA, many rows (prefill and scoring)
-static int run_layers_big(const sapo_weights* w, const FwdBufs& b, int M, RowMap rm, const CacheBufs& cb, hipStream_t st) {
+// scored: packed rows of a scoring pass.  Behind the last layer's attention only the rows that predict a scored token are
+// multiplied; they end up side by side in scored->h.
+struct ScoredRows { const int *src_rows, *count; float* h; };
+// M rows of n_seq sequences, or (rows) at most M
+static int run_layers_big(const sapo_weights* w, const FwdBufs& b, int M, int n_seq, RowMap rm, const CacheBufs& cb, const int* rows,
+                          const ScoredRows* scored, hipStream_t st) {
   const sapo_model_config& c = w->cfg;
   const int d = c.d_model, q = c.n_q_heads * c.head_dim, kv = c.n_kv_heads * c.head_dim, F = c.d_ff;
   for (int l = 0; l < c.n_layers; ++l) {
@@ -591,10 +596,11 @@ static int run_layers_big(const sapo_weights* w, const FwdBufs& b, int M, RowMap
     const int parts = d / 128;
     const bool fold = parts <= 16;
     QkvEpi qkv_ep;
+    qkv_ep.rows = rm.packed ? rm.first + n_seq : nullptr;
     qkv_ep.bias = lw.bqkv; qkv_ep.rope = w->rope; qkv_ep.rm = rm; qkv_ep.kv = kvc; qkv_ep.q_out = (f16*)b.q;
     qkv_ep.n_q_heads = c.n_q_heads;
     if (l == 0 || !fold) {
-      HIP_CK(m_rmsnorm_x32(b.h, lw.attn_norm, c.rms_eps, b.a, M, d, nullptr, st));
+      HIP_CK(m_rmsnorm_x32(b.h, lw.attn_norm, c.rms_eps, b.a, M, d, nullptr, st, rows));
     } else {
       qkv_ep.ssq_in = b.ssq; qkv_ep.ssq_parts = parts; qkv_ep.ssq_halves = m_gemm_writes_halves(M, d); qkv_ep.norm_dim = (float)d; qkv_ep.eps = c.rms_eps;
     }
@@ -602,20 +608,28 @@ static int run_layers_big(const sapo_weights* w, const FwdBufs& b, int M, RowMap
     if (clamped) HIP_CK(g_count_half_at_limit(b.a, M, d, 1, clamped, st));
     HIP_CK(m_gemm_qkv_rope(b.a, lw.wqkv, M, q + 2 * kv, d, qkv_ep, st));
     if (clamped) HIP_CK(g_count_half_at_limit(b.q, M, q, 0, clamped, st));
-    HIP_CK(m_flash_attention(b.q, rm, kvc, b.attn, M / rm.T, c.n_q_heads, st));
+    HIP_CK(m_flash_attention(b.q, rm, kvc, b.attn, n_seq, c.n_q_heads, st));
     if (clamped) HIP_CK(g_count_half_at_limit(b.attn, M, q, 1, clamped, st));
-    BigEpi o_ep{BIG_ADD_F32, b.h, d, nullptr};
+    float* h = b.h;
+    const void* attn = b.attn;
+    if (scored && l + 1 == c.n_layers) {
+      HIP_CK(m_gather_rows_x32(scored->src_rows, scored->count, M, b.h, d, b.attn, q, scored->h, b.act, st));
+      h = scored->h; attn = b.act; rows = scored->count;
+    }
+    BigEpi o_ep{BIG_ADD_F32, h, d, nullptr};
     BigEpi gu_ep{BIG_SWIGLU, nullptr, 0, (f16*)b.act};
+    o_ep.rows = gu_ep.rows = rows;
     if (fold) {
       o_ep.gain_next = lw.ffn_norm; o_ep.xn_out = (f16*)b.a; o_ep.ssq_out = b.ssq;
       gu_ep.ssq_in = b.ssq; gu_ep.ssq_parts = parts; gu_ep.ssq_halves = m_gemm_writes_halves(M, d); gu_ep.norm_dim = (float)d; gu_ep.eps = c.rms_eps;
     }
-    HIP_CK(m_gemm_big(b.attn, lw.wo, M, d, q, o_ep, st));
-    if (!fold) HIP_CK(m_rmsnorm_x32(b.h, lw.ffn_norm, c.rms_eps, b.a, M, d, nullptr, st));
+    HIP_CK(m_gemm_big(attn, lw.wo, M, d, q, o_ep, st));
+    if (!fold) HIP_CK(m_rmsnorm_x32(h, lw.ffn_norm, c.rms_eps, b.a, M, d, nullptr, st, rows));
     if (clamped) HIP_CK(g_count_half_at_limit(b.a, M, d, 1, clamped, st));
     HIP_CK(m_gemm_big(b.a, lw.wgu, M, 2 * F, d, gu_ep, st));
     if (clamped) HIP_CK(g_count_half_at_limit(b.act, M, F, 1, clamped, st));
-    BigEpi down_ep{BIG_ADD_F32, b.h, d, nullptr};
+    BigEpi down_ep{BIG_ADD_F32, h, d, nullptr};
+    down_ep.rows = rows;
     if (fold && l + 1 < c.n_layers) {
       down_ep.gain_next = w->layers[l + 1].attn_norm; down_ep.xn_out = (f16*)b.a; down_ep.ssq_out = b.ssq;
     }
@@ -740,7 +754,7 @@ static int run_layers_decode16(const sapo_weights* w, const FwdBufs& b, const De
 static int run_layers(const sapo_weights* w, const FwdBufs& b, int M, RowMap rm, const CacheBufs& cb, int max_ctx,
                       hipStream_t st) {
   if (!w->mfma) return run_layers_generic(w, b, M, rm, cb, max_ctx, st);
-  return run_layers_big(w, b, M, rm, cb, st);
+  return run_layers_big(w, b, M, M / rm.T, rm, cb, nullptr, nullptr, st);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -755,6 +769,7 @@ struct RolloutPlan {
   int* step;        // device step counter
   int* stop;        // device: {stop token or -1, sequences ended, length of each sequence (0 = running)}
   int* lens;        // device [P]: prompt lengths (calls with prompts of different lengths)
+  int* first;       // device [P + 1]: packed rows (RowMap)
   int own_pages;    // pages of its own per sequence
   int* last_rows;   // [P]
   PersistCtl* pctl; // exchange counters of the persistent decode kernel (MFMA path)
@@ -807,6 +822,7 @@ static void plan_rollout(const sapo_weights* w, int P, int Lp, int G, int N, cha
   pl.step = A.take<int>(64);
   pl.stop = A.take<int>((size_t)pl.S + 2);
   pl.lens = A.take<int>(P);
+  pl.first = A.take<int>(P + 1);
   pl.last_rows = A.take<int>(P);
   pl.pctl = w->mfma ? (PersistCtl*)A.take_bytes(d_decode_layers_ctl_bytes()) : nullptr;
   pl.attn_pre = w->mfma ? A.take<float>((size_t)pl.S * c.n_q_heads * (c.head_dim + 4)) : nullptr;
@@ -999,12 +1015,24 @@ static int rollout_impl(const sapo_weights* w, const int32_t* prompts, const int
   {
     const int M = P * Lp;
     RowMap rm{0, Lp, G, 0, nullptr, ragged ? pl.lens : nullptr, G};
-    HIP_CK(g_embed(dt, prompts, 1, nullptr, w->embed, pl.fwd.h, M, d, st));
-    if ((rc = run_layers(w, pl.fwd, M, rm, pl.cache, Lp, st))) return rc;
+    int there = 0;   // positions of the prompts
+    for (int p = 0; p < P; ++p) there += ragged ? lens_host[p] : Lp;
+    // Prompts that end before Lp go without their padding, side by side (the fp32 q / k / v rows, which do not exist here, leave
+    // their place to the rows' positions).
+    const bool packed = w->mfma && c.n_layers > 0 && M >= 1024 && there <= M - M / 16;
+    if (packed) {
+      rm.packed = (const int2*)pl.fwd.qkv; rm.first = pl.first;
+      HIP_CK(g_packed_prompts(pl.lens, P, G, pl.cache.page_table, pl.pages_per_seq, pl.first, (int2*)pl.fwd.qkv, st));
+      HIP_CK(g_embed_packed(prompts, Lp, P, pl.first, w->embed, pl.fwd.h, d, st));
+      if ((rc = run_layers_big(w, pl.fwd, there, P, rm, pl.cache, nullptr, nullptr, st))) return rc;
+    } else {
+      HIP_CK(g_embed(dt, prompts, 1, nullptr, w->embed, pl.fwd.h, M, d, st));
+      if ((rc = run_layers(w, pl.fwd, M, rm, pl.cache, Lp, st))) return rc;
+    }
     if (ragged) {
       for (int l = 0; l < c.n_layers; ++l)
         HIP_CK(g_copy_partial_page_ragged(dt, layer_cache(w, pl.cache, l), P, G, pl.lens, st));
-      HIP_CK(g_gather_last_rows_ragged(pl.fwd.h, pl.h_last, S, G, Lp, pl.lens, d, st));
+      HIP_CK(g_gather_last_rows_ragged(pl.fwd.h, pl.h_last, S, G, Lp, pl.lens, packed ? pl.first : nullptr, d, st));
     } else {
       if (Lp % kPageTokens != 0)
         for (int l = 0; l < c.n_layers; ++l)
@@ -1165,6 +1193,7 @@ struct ScorePlan {
   int* count;       // device: number of rows to score in the current chunk
   int* rows;        // [chunk_seqs * T, 2] (s, t)
   int* src_rows;    // [chunk_seqs * T]
+  int* first;       // [chunk_seqs + 1] packed rows: a sequence's first one; their number
   void* x;          // [chunk_seqs * T, d] final-norm output of the gathered rows (T)
   float* logits;    // [row_chunk, V] (shape-generic kernels)
   float* partials;  // fused LM-head partials (MFMA kernels): over the layers' buffers, which are done with by then
@@ -1187,6 +1216,7 @@ static void plan_score(const sapo_weights* w, int S, int T, int chunk_seqs, size
   pl.count = A.take<int>(64);
   pl.rows = A.take<int>(2 * R);
   pl.src_rows = A.take<int>(R);
+  pl.first = w->mfma ? A.take<int>(chunk_seqs + 1) : nullptr;
   carve_cache(A, w, chunk_seqs, pl.pages_per_seq, (size_t)chunk_seqs * pl.pages_per_seq, pl.cache);
   const size_t fwd_at = A.off = (A.off + 255) & ~(size_t)255;   // where pl.fwd.h begins
   carve_fwd(A, w, M, pl.fwd);
@@ -1238,6 +1268,19 @@ static int score_chunk_seqs(const sapo_weights* w, int S, int T) {
     if (best < 0.0 || total < best * (1.0 - 1e-9)) { best = total; best_cs = cs; }
   }
   return best_cs;
+}
+
+// Does a scoring pass of M positions leave out those that no log-prob depends on?  The line is where a call that has none to leave
+// out is no slower for it: its launches begin with a load of the number of rows (0.2 us), and three more prepare them, against
+// the last layer's projections of unscored rows, which it saves.  us per call without and with, every answer up to the row's end, 0.5B:
+// 1204 positions 2410, 2453; 2048 2879, 2967; 2709 3797, 3776; 49152 45644, 45660; 1.5B: 7200 21186, 21151.  Answers that end
+// a sixth of the row early on average (211 of 301 positions scored at most): 2709 3580, 2893; 1.5B 9740, 7584; a third of 768: 49152 42872, 32161.
+constexpr int kPackedRows = 2560;
+static bool score_packs_rows(const sapo_weights* w, int M) {
+  const sapo_model_config& c = w->cfg;
+  const int q = c.n_q_heads * c.head_dim;
+  // the scored rows' residual takes the place of the q / k / v rows, their attention output that of the FFN's activations
+  return w->mfma && c.n_layers > 0 && M >= kPackedRows && c.d_model <= q + 2 * c.n_kv_heads * c.head_dim && q <= c.d_ff;
 }
 
 static int check_score_args(const sapo_weights* w, int S, int T) {
@@ -1310,6 +1353,19 @@ static int score_impl(const sapo_weights* w, const int32_t* tokens, const uint8_
   for (int s0 = 0; s0 < S; s0 += pl.chunk_seqs) {
     const int ns = (S - s0 < pl.chunk_seqs) ? S - s0 : pl.chunk_seqs;
     const int M = ns * T;
+    if (score_packs_rows(w, M)) {
+      // the fp32 q / k / v rows, which do not exist on this path, leave their place to the rows' positions and then to the scored rows
+      RowMap rm{0, T, 1, 0, nullptr, nullptr, 1};
+      rm.packed = (const int2*)pl.fwd.qkv; rm.first = pl.first;
+      const ScoredRows scored{pl.src_rows, pl.count, pl.fwd.qkv};
+      HIP_CK(g_packed_rows(completion_mask, T, s0, ns, pl.cache.page_table, pl.pages_per_seq, (int2*)pl.x, pl.first, (int2*)pl.fwd.qkv,
+                           pl.rows, pl.src_rows, pl.count, st));
+      HIP_CK(g_embed_packed(tokens + (size_t)s0 * T, T, ns, pl.first, w->embed, pl.fwd.h, c.d_model, st));
+      if ((rc = run_layers_big(w, pl.fwd, M, ns, rm, pl.cache, pl.first + ns, &scored, st))) return rc;
+      HIP_CK(m_rmsnorm_x32(scored.h, final_gain, c.rms_eps, pl.x, M, c.d_model, nullptr, st, pl.count));
+      HIP_CK(m_lmhead_score(pl.x, w->lm_head, M, pl.count, c.vocab, c.d_model, pl.rows, tokens, T, pl.partials, out_logprobs, st));
+      continue;
+    }
     if ((rc = forward_chunk(w, pl, tokens, s0, ns, st))) return rc;
     HIP_CK(g_masked_rows(completion_mask, T, s0, ns, pl.rows, pl.src_rows, pl.count, st));
     if (w->mfma) {

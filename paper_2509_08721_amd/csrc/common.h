@@ -39,6 +39,11 @@ struct RowMap {
   // decode mode, optional, device: the sequence behind each row once ended sequences have been taken out of
   // the batch (row m of the step's activations belongs to sequence slot_seq[m]); NULL: row m is sequence m
   const int* slot_seq = nullptr;
+  // block mode, optional, device (g_packed_rows): only the positions that a result depends on, side by side.  Row m lies on page
+  // packed[m].x of the cache at position packed[m].y of its sequence; sequence s begins at row first[s], and first[number of
+  // sequences] is how many rows there are.  NULL: every sequence has T rows
+  const int2* packed = nullptr;
+  const int* first = nullptr;
   __device__ __forceinline__ void get(int m, int& seq, int& pos) const {
     if (decode) {
       seq = slot_seq ? slot_seq[m] : m;
@@ -49,7 +54,7 @@ struct RowMap {
     }
   }
   // does row m leave K/V in the cache?
-  __device__ __forceinline__ bool keeps_kv(int m) const { return decode || !lens || (m % T) < lens[m / T]; }
+  __device__ __forceinline__ bool keeps_kv(int m) const { return decode || packed || !lens || (m % T) < lens[m / T]; }
 };
 
 // Paged KV cache of one layer.  K and V page: [Hkv] x 16 tokens of hd values, for the shape-generic kernels K as
@@ -373,6 +378,14 @@ struct RolloutBegin {
 };
 hipError_t g_rollout_begin(const RolloutBegin& a, hipStream_t st);
 hipError_t g_incr(int* p, hipStream_t st);
+// RowMap::first [ns + 1] and ::packed [ns T] for the positions of sequences s0 .. that a scored one depends on, and what
+// g_masked_rows leaves (src_rows: packed rows); lens [ns]: scratch
+hipError_t g_packed_rows(const uint8_t* mask, int T, int s0, int ns, const int* page_table, int pages_per_seq, int2* lens, int* first,
+                         int2* packed, int* rows, int* src_rows, int* count, hipStream_t st);
+// ... for prompts of lens[p] tokens, whose pages the first of G siblings' rows of the table name
+hipError_t g_packed_prompts(const int* lens, int P, int G, const int* page_table, int pages_per_seq, int* first, int2* packed,
+                            hipStream_t st);
+hipError_t g_embed_packed(const int32_t* tokens, int T, int ns, const int* first, const void* embed, float* h, int d, hipStream_t st);
 hipError_t g_masked_rows(const uint8_t* mask, int T, int s0, int ns, int* rows /*[ns*T,2]*/, int* src_rows /*[ns*T]*/,
                          int* count, hipStream_t st);
 hipError_t g_rows_from_positions(const int* positions, int n, int T, int* src_rows, hipStream_t st);
@@ -483,6 +496,7 @@ struct BigEpi {
   const float* gain_next = nullptr;   // [N]
   f16* xn_out = nullptr;
   float* ssq_out = nullptr;           // [M, N / 128 rounded up to a multiple of 4], or halves (m_gemm_writes_halves)
+  const int* rows = nullptr;          // optional, device: how many rows there are, at most M
 };
 enum { BIG_STORE_F32 = 0, BIG_ADD_F32 = 1, BIG_SWIGLU = 2 };
 
@@ -498,6 +512,7 @@ struct QkvEpi {
   KVCache kv;
   f16* q_out = nullptr;            // [M, Hq hd] rotated queries, half
   int n_q_heads = 0;
+  const int* rows = nullptr;       // as in BigEpi
 };
 hipError_t m_gemm_qkv_rope(const void* Xp, const void* Wp, int M, int N, int K, const QkvEpi& epi, hipStream_t st);
 
@@ -517,10 +532,13 @@ hipError_t m_pack_weights(const PackTask* tasks, int n, unsigned* range, hipStre
 bool m_gemm_writes_halves(int M, int N);
 hipError_t m_gemm_big(const void* Xp, const void* Wp, int M, int N, int K, BigEpi epi, hipStream_t st);
 hipError_t m_rmsnorm_x32(const float* h, const float* gain, float eps, void* out, int M, int d, const int* row_index,
-                         hipStream_t st);
+                         hipStream_t st, const int* rows = nullptr /* as in BigEpi */);
 hipError_t m_lmhead_score(const void* Xp, const void* Wp, int max_rows, const int* n_rows_dev, int V, int K,
                           const int* row_seq_pos, const int32_t* tokens, int T, float* partials, float* out_logprobs,
                           hipStream_t st);
+// rows src_rows[0 .. *n_rows - 1] (at most M) of a residual [., d] and of an operand in X32 order over q, side by side
+hipError_t m_gather_rows_x32(const int* src_rows, const int* n_rows, int M, const float* h, int d, const void* x, int q, float* h_out,
+                             void* x_out, hipStream_t st);
 size_t m_lmhead_score_partial_floats(int max_rows, int V);
 // Fused LM head + sampler for any number of sequences and any K: Xp = final-normed rows in X32 order.
 // partials: [m_lmhead_sample_big_groups(V)][n_rows][5].
@@ -656,7 +674,8 @@ hipError_t d_decode_layers(PersistArgs args, int head_dim, hipStream_t st);
 
 hipError_t g_gather_last_rows(const float* h, float* out, int S, int G, int Lp, int d, hipStream_t st);
 // with per-prompt lengths (device): row p * Lp + lens[p] - 1
-hipError_t g_gather_last_rows_ragged(const float* h, float* out, int S, int G, int Lp, const int* lens, int d,
+// first: RowMap::first where the rows are packed, or NULL
+hipError_t g_gather_last_rows_ragged(const float* h, float* out, int S, int G, int Lp, const int* lens, const int* first, int d,
                                      hipStream_t st);
 
 }  // namespace sapo

@@ -889,6 +889,111 @@ hipError_t g_masked_rows(const uint8_t* mask, int T, int s0, int ns, int* rows, 
   return launch(KID_MISC, k_masked_rows, dim3(1), dim3(1024), 0, st, mask, T, s0, ns, rows, src_rows, count);
 }
 
+// ---------------------------------------------------------------------------------------
+// The rows of a scoring pass that a log-prob depends on.  Attention is causal, so a sequence's positions from its last scored
+// token on change none: answers that end before their row does need no forward pass over the padding.  Of sequence s0 + s the
+// positions in front of its last scored token go on (none: 0 of them), side by side with the other sequences'; the scored
+// positions are listed in the same pass (as k_masked_rows does).
+// ---------------------------------------------------------------------------------------
+__global__ void __launch_bounds__(256) k_packed_lens(const uint8_t* __restrict__ mask, int T, int s0, int2* __restrict__ lens) {
+  __shared__ int2 part[4];
+  const uint8_t* m = mask + (size_t)(s0 + blockIdx.x) * T;
+  int last = 0, n = 0;
+  for (int t = threadIdx.x; t < T; t += 256) {
+    const bool on = t >= 1 && m[t] != 0;
+    last = on ? t : last;
+    n += on;
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) { last = max(last, __shfl_xor(last, o, 64)); n += __shfl_xor(n, o, 64); }
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = make_int2(last, n);
+  __syncthreads();
+  if (threadIdx.x == 0)
+    lens[blockIdx.x] = make_int2(max(max(part[0].x, part[1].x), max(part[2].x, part[3].x)), (part[0].y + part[1].y) + (part[2].y + part[3].y));
+}
+__global__ void __launch_bounds__(256) k_packed_rows(const uint8_t* __restrict__ mask, int T, int s0, int ns, const int2* __restrict__ lens,
+                                                     const int* __restrict__ page_table, int pages_per_seq, int* __restrict__ first,
+                                                     int2* __restrict__ packed, int* __restrict__ rows, int* __restrict__ src_rows,
+                                                     int* __restrict__ count) {
+  __shared__ int2 part[4];
+  const int s = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int row0 = 0, out0 = 0;   // rows and scored positions of the sequences in front
+  for (int i = threadIdx.x; i < s; i += 256) {
+    const int2 l = lens[i];
+    row0 += l.x; out0 += l.y;
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) { row0 += __shfl_xor(row0, o, 64); out0 += __shfl_xor(out0, o, 64); }
+  if (lane == 0) part[wave] = make_int2(row0, out0);
+  __syncthreads();
+  row0 = (part[0].x + part[1].x) + (part[2].x + part[3].x);
+  out0 = (part[0].y + part[1].y) + (part[2].y + part[3].y);
+  const int2 own = lens[s];
+  if (threadIdx.x == 0) {
+    first[s] = row0;
+    if (s == ns - 1) { first[ns] = row0 + own.x; *count = out0 + own.y; }
+  }
+  const int* pt = page_table + (size_t)s * pages_per_seq;
+  const uint8_t* m = mask + (size_t)(s0 + s) * T;
+  for (int t0 = 0; t0 <= own.x; t0 += 256) {
+    const int t = t0 + threadIdx.x;
+    if (t < own.x) packed[row0 + t] = make_int2(pt[t / kPageTokens], t);
+    const bool on = t >= 1 && t <= own.x && m[t] != 0;
+    const unsigned long long all = __ballot(on);
+    __syncthreads();   // part is read
+    if (lane == 0) part[wave].x = __popcll(all);
+    __syncthreads();
+    int o = out0 + __popcll(all & ((1ull << lane) - 1ull));
+    for (int w = 0; w < wave; ++w) o += part[w].x;
+    if (on) {
+      rows[2 * o] = s0 + s; rows[2 * o + 1] = t;
+      src_rows[o] = row0 + t - 1;
+    }
+    out0 += (part[0].x + part[1].x) + (part[2].x + part[3].x);
+  }
+}
+hipError_t g_packed_rows(const uint8_t* mask, int T, int s0, int ns, const int* page_table, int pages_per_seq, int2* lens, int* first,
+                         int2* packed, int* rows, int* src_rows, int* count, hipStream_t st) {
+  const hipError_t e = launch(KID_MISC, k_packed_lens, dim3(ns), dim3(256), 0, st, mask, T, s0, lens);
+  if (e != hipSuccess) return e;
+  return launch(KID_MISC, k_packed_rows, dim3(ns), dim3(256), 0, st, mask, T, s0, ns, (const int2*)lens, page_table, pages_per_seq, first,
+                packed, rows, src_rows, count);
+}
+// the same for prompts: all of a prompt's positions count
+__global__ void __launch_bounds__(256) k_packed_prompts(const int* __restrict__ lens, int P, int G, const int* __restrict__ page_table,
+                                                        int pages_per_seq, int* __restrict__ first, int2* __restrict__ packed) {
+  __shared__ int part[4];
+  const int p = blockIdx.x, n = lens[p];
+  int row0 = 0;
+  for (int i = threadIdx.x; i < p; i += 256) row0 += lens[i];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) row0 += __shfl_xor(row0, o, 64);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = row0;
+  __syncthreads();
+  row0 = (part[0] + part[1]) + (part[2] + part[3]);
+  if (threadIdx.x == 0) {
+    first[p] = row0;
+    if (p == P - 1) first[P] = row0 + n;
+  }
+  const int* pt = page_table + (size_t)p * G * pages_per_seq;
+  for (int t = threadIdx.x; t < n; t += 256) packed[row0 + t] = make_int2(pt[t / kPageTokens], t);
+}
+hipError_t g_packed_prompts(const int* lens, int P, int G, const int* page_table, int pages_per_seq, int* first, int2* packed,
+                            hipStream_t st) {
+  return launch(KID_MISC, k_packed_prompts, dim3(P), dim3(256), 0, st, lens, P, G, page_table, pages_per_seq, first, packed);
+}
+// a workgroup per sequence and four positions: the packed rows of h <- their tokens' embeddings
+__global__ void __launch_bounds__(256) k_embed_packed(const int32_t* __restrict__ tokens, int T, const int* __restrict__ first,
+                                                      const bf16* __restrict__ embed, float* __restrict__ h, int d) {
+  const int s = blockIdx.y, t = blockIdx.x * 4 + (threadIdx.x >> 6), row0 = first[s];
+  if (t >= first[s + 1] - row0) return;
+  const bf16* e = embed + (size_t)tokens[(size_t)s * T + t] * d;
+  for (int i = threadIdx.x & 63; i < d; i += 64) h[(size_t)(row0 + t) * d + i] = to_f32(e[i]);
+}
+hipError_t g_embed_packed(const int32_t* tokens, int T, int ns, const int* first, const void* embed, float* h, int d, hipStream_t st) {
+  return launch(KID_EMBED, k_embed_packed, dim3((T + 3) / 4, ns), dim3(256), 0, st, tokens, T, first, (const bf16*)embed, h, d);
+}
+
 // src_rows for a list of (s, t) positions: row s * T + t (debug logits).
 __global__ void k_rows_from_positions(const int* positions, int n, int T, int* src_rows) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -909,17 +1014,17 @@ hipError_t g_last_rows(int* rows, int P, int Lp, hipStream_t st) {
 
 // out[s, :] = h[(s / G) * Lp + Lp - 1, :]: the last prompt position's residual, once per sibling.
 __global__ void k_gather_last_rows(const float* __restrict__ h, float* __restrict__ out, int G, int Lp, int d,
-                                   const int* __restrict__ lens) {
-  const int s = blockIdx.x;
-  const float* src = h + ((size_t)(s / G) * Lp + (lens ? lens[s / G] : Lp) - 1) * d;
+                                   const int* __restrict__ lens, const int* __restrict__ first) {
+  const int s = blockIdx.x, p = s / G;
+  const float* src = h + ((first ? (size_t)first[p] : (size_t)p * Lp) + (lens ? lens[p] : Lp) - 1) * d;
   for (int i = threadIdx.x; i < d; i += blockDim.x) out[(size_t)s * d + i] = src[i];
 }
 hipError_t g_gather_last_rows(const float* h, float* out, int S, int G, int Lp, int d, hipStream_t st) {
-  return launch(KID_MISC, k_gather_last_rows, dim3(S), dim3(256), 0, st, h, out, G, Lp, d, (const int*)nullptr);
+  return launch(KID_MISC, k_gather_last_rows, dim3(S), dim3(256), 0, st, h, out, G, Lp, d, (const int*)nullptr, (const int*)nullptr);
 }
-hipError_t g_gather_last_rows_ragged(const float* h, float* out, int S, int G, int Lp, const int* lens, int d,
+hipError_t g_gather_last_rows_ragged(const float* h, float* out, int S, int G, int Lp, const int* lens, const int* first, int d,
                                      hipStream_t st) {
-  return launch(KID_MISC, k_gather_last_rows, dim3(S), dim3(256), 0, st, h, out, G, Lp, d, lens);
+  return launch(KID_MISC, k_gather_last_rows, dim3(S), dim3(256), 0, st, h, out, G, Lp, d, lens, first);
 }
 
 __global__ void k_gumbel(uint32_t seed_lo, uint32_t seed_hi, uint32_t seq, uint32_t step, uint32_t v0, int n, float* out) {

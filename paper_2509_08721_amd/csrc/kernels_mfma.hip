@@ -121,6 +121,14 @@ constexpr int kRing = 3;                                            // stages of
 constexpr int ring_bytes(int H) { return kRing * 4 * H * 1024; }     // 4 H fragments of 1 KiB per stage
 constexpr int kBigLds = ring_bytes(4);
 
+// Rows of a launch for at most M (PK: as many as `rows`, on the device, says): a scalar load, the same for every lane.  A template
+// parameter of the kernels, because what they execute before their first requests counts: with a test of the pointer a scoring call of
+// 301 tokens took 1.465 ms instead of 1.444.
+template <bool PK> __device__ __forceinline__ int rows_there(const int* rows, int M) {
+  typedef const __attribute__((address_space(4))) int* ConstInt;
+  if constexpr (PK) return min(M, *(ConstInt)(uintptr_t)rows);
+  return M;
+}
 __device__ __forceinline__ bool big_raster(int NX, int NY, int& bx, int& by) {
   const bool any = tile_of_block(blockIdx.x, NX, NY, bx, by);
   bx = __builtin_amdgcn_readfirstlane(bx);   // the quotients come out of vector registers: addresses would stay there
@@ -298,13 +306,14 @@ __device__ __forceinline__ void row_scales(const float* __restrict__ ssq, int pa
 }
 
 // MODE: the epilogue (BigEpi::mode), each with a register allocation of its own
-template <int TJ, int H, int MODE>
+template <int TJ, int H, int MODE, bool PK>
 __global__ void __launch_bounds__(256, TJ == 2 ? 2 : 3) k_gemm_big(const uint4* __restrict__ Xp,
-                                                                      const uint4* __restrict__ Wp, int M, int N, int K,
+                                                                      const uint4* __restrict__ Wp, const int* rows, int M, int N, int K,
                                                                       BigEpi ep) {
   constexpr int TM = 128 * TJ;   // tokens per tile
   extern __shared__ uint4 smem[];
   int bx, by;
+  M = rows_there<PK>(rows, M);
   if (!big_raster(N >> 7, (M + TM - 1) / TM, bx, by)) return;
   f32x16 acc[4][TJ];
   const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63;
@@ -532,11 +541,12 @@ struct MidLoop {
 };
 
 // BIG_SWIGLU and BIG_ADD_F32 on tiles of 32 WM tokens x 64 WN features
-template <int WM, int WN, int D>
-__global__ void __launch_bounds__(256, 2) k_gemm_mid(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, int M, int N, int K,
-                                                  BigEpi ep) {
+template <int WM, int WN, int D, bool PK>
+__global__ void __launch_bounds__(256, 2) k_gemm_mid(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, const int* rows, int M, int N,
+                                                     int K, BigEpi ep) {
   extern __shared__ uint4 smem[];
   int bx, by;
+  M = rows_there<PK>(rows, M);
   if (!big_raster(N / (64 * WN), (M + 32 * WM - 1) / (32 * WM), bx, by)) return;
   const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63;
   const bool live = wave < WM * WN;
@@ -670,11 +680,13 @@ __device__ __forceinline__ void store_values(f32x16 (&acc)[4][2], const QkvEpi& 
   const f16* src1 = src0 + 64 * RS;
   const unsigned long long kept[2] = {__builtin_amdgcn_ballot_w64(keeps[0]), __builtin_amdgcn_ballot_w64(keeps[1])};
   const unsigned long long kept64 = (kept[0] & 0xffffffffull) | (kept[1] << 32);   // bit t: token t stays in the cache
+  const unsigned long long first64 = (__builtin_amdgcn_ballot_w64(pos_of[0] == 0) & 0xffffffffull) | (__builtin_amdgcn_ballot_w64(pos_of[1] == 0) << 32);
   // runs of tokens within 8 slots of a page; the lane that looked a token up knows its position and page
   for (int t = 0; t < n_tok;) {
     const int from = t & 31, pos = __builtin_amdgcn_readlane(t < 32 ? pos_of[0] : pos_of[1], from);
     const int page = __builtin_amdgcn_readlane(t < 32 ? page_of[0] : page_of[1], from);
-    const int n = ep.rm.decode ? 1 : min(min(8 - (pos & 7), n_tok - t), ep.rm.T - pos);
+    const unsigned long long next = t < 63 ? first64 >> (t + 1) : 0;   // bit i: token t + 1 + i is a sequence's first
+    const int n = ep.rm.decode ? 1 : min(min(8 - (pos & 7), n_tok - t), next ? __builtin_ctzll(next) + 1 : 8);
     f16* dst = vpool + (size_t)page * hkv * HD * kPageTokens + v_page_at(pos % kPageTokens, 0);
     const unsigned stays = (unsigned)(kept64 >> t) & ((1u << n) - 1);
     if (stays == 0xff) {
@@ -700,8 +712,9 @@ __device__ __forceinline__ uint4 trade_halves(f16x4 a, f16x4 b) {
   return make_uint4(w0[0], w1[0], w0[1], w1[1]);
 }
 
-// The epilogue of a wave's tile of NH heads, the first of them head0.  smem: the workgroup's ring (large tiles).
-template <int HD, int NH, int TJ>
+// The epilogue of a wave's tile of NH heads, the first of them head0.  smem: the workgroup's ring (large tiles).  PK: packed rows (a
+// kernel of its own: with both cases in one, the rotary pairs' loads waited for the page lookup, 1.2 us a layer).
+template <int HD, int NH, int TJ, bool PK>
 __device__ __forceinline__ void qkv_epilogue(f32x16 (&acc)[NH * (HD / 32)][TJ], const QkvEpi& ep, int head0, int tok0, int M,
                                              const float (&row_scale)[TJ], uint4* smem = nullptr) {
   constexpr int NB = HD / 32;   // accumulator blocks of a head
@@ -734,10 +747,16 @@ __device__ __forceinline__ void qkv_epilogue(f32x16 (&acc)[NH * (HD / 32)][TJ], 
 #pragma unroll
   for (int tj = 0; tj < TJ; ++tj) {
     const int tokc = min(tok0 + tj * 32, M - 1);
-    int seq;
-    ep.rm.get(tokc, seq, pos_of[tj]);
     keeps[tj] = ep.rm.keeps_kv(tokc);
-    page_of[tj] = ep.kv.page_table[(size_t)seq * ep.kv.pages_per_seq + pos_of[tj] / kPageTokens];
+    if constexpr (PK) {
+      const int2 at = ep.rm.packed[tokc];
+      page_of[tj] = at.x;
+      pos_of[tj] = at.y;
+    } else {
+      int seq;
+      ep.rm.get(tokc, seq, pos_of[tj]);
+      page_of[tj] = ep.kv.page_table[(size_t)seq * ep.kv.pages_per_seq + pos_of[tj] / kPageTokens];
+    }
   }
   const bool rotates = head0 < hq + hkv;   // else the tile is all V
   if constexpr (TJ == 2) {
@@ -814,12 +833,13 @@ __device__ __forceinline__ void qkv_epilogue(f32x16 (&acc)[NH * (HD / 32)][TJ], 
     }
   }
 }
-template <int HD, int TJ>
-__global__ void __launch_bounds__(256, 2) k_gemm_qkv_rope(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, int M,
+template <int HD, int TJ, bool PK>
+__global__ void __launch_bounds__(256, 2) k_gemm_qkv_rope(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, const int* rows, int M,
                                                           int N, int K, QkvEpi ep) {
   constexpr int H = 4, NH = 128 / HD, TM = 128 * TJ;   // heads and tokens of a tile
   extern __shared__ uint4 smem[];
   int bx, by;
+  M = rows_there<PK>(rows, M);
   if (!big_raster(N >> 7, (M + TM - 1) / TM, bx, by)) return;
   f32x16 acc[4][TJ];
   const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63;
@@ -835,16 +855,17 @@ __global__ void __launch_bounds__(256, 2) k_gemm_qkv_rope(const uint4* __restric
     if (ep.ssq_in) row_scales<TJ>(ep.ssq_in, ep.ssq_parts, ep.ssq_halves, ep.norm_dim, ep.eps, tok0, M, row_scale);
     loop.run(smem, acc);
   }
-  qkv_epilogue<HD, NH, TJ>(acc, ep, bx * NH, tok0, M, row_scale, smem);
+  qkv_epilogue<HD, NH, TJ, PK>(acc, ep, bx * NH, tok0, M, row_scale, smem);
 }
 
 // The same for few tokens: 32 WM tokens x one head per workgroup
-template <int HD, int WM, int D>
-__global__ void __launch_bounds__(256, 2) k_gemm_qkv_mid(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, int M, int N, int K,
-                                                      QkvEpi ep) {
+template <int HD, int WM, int D, bool PK>
+__global__ void __launch_bounds__(256, 2) k_gemm_qkv_mid(const uint4* __restrict__ Xp, const uint4* __restrict__ Wp, const int* rows, int M, int N,
+                                                         int K, QkvEpi ep) {
   constexpr int NB = HD / 32;
   extern __shared__ uint4 smem[];
   int bx, by;
+  M = rows_there<PK>(rows, M);
   if (!big_raster(N / HD, (M + 32 * WM - 1) / (32 * WM), bx, by)) return;
   const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63;
   const bool live = wave < WM;
@@ -859,7 +880,7 @@ __global__ void __launch_bounds__(256, 2) k_gemm_qkv_mid(const uint4* __restrict
     return;
   }
   loop.run(smem, wm, 0, acc);
-  qkv_epilogue<HD, 1, 1>(acc, ep, bx, tok, M, row_scale);
+  qkv_epilogue<HD, 1, 1, PK>(acc, ep, bx, tok, M, row_scale);
 }
 
 int n_compute_units() {
@@ -910,20 +931,22 @@ static hipError_t launch_mid(Kernel kernel, int lds, bool& attr_done, int grid, 
     if (e != hipSuccess) return e;
     attr_done = true;
   }
-  return launch(KID_GEMM_BIG, kernel, dim3(grid), dim3(256), lds, st, X, W, M, N, K, epi);
+  return launch(KID_GEMM_BIG, kernel, dim3(grid), dim3(256), lds, st, X, W, epi.rows, M, N, K, epi);
 }
 template <int WM, int WN, int D>
 static hipError_t launch_ffn_mid(const uint4* X, const uint4* W, int M, int N, int K, const BigEpi& epi, hipStream_t st) {
-  static bool attr_done = false;
+  static bool attr_done[2] = {false, false};
   static_assert(MidLoop<WM, WN, 2, D>::kBytes >= WM * WN * 32 * 68 * 4, "the residual update's row areas lie in the ring");
-  return launch_mid(k_gemm_mid<WM, WN, D>, MidLoop<WM, WN, 2, D>::kBytes, attr_done, big_grid(N / (64 * WN), (M + 32 * WM - 1) / (32 * WM)),
+  const bool pk = epi.rows != nullptr;
+  return launch_mid(pk ? k_gemm_mid<WM, WN, D, true> : k_gemm_mid<WM, WN, D, false>, MidLoop<WM, WN, 2, D>::kBytes, attr_done[pk], big_grid(N / (64 * WN), (M + 32 * WM - 1) / (32 * WM)),
                     X, W, M, N, K, epi, st);
 }
 template <int HD, int WM, int D>
 static hipError_t launch_qkv_mid(const uint4* X, const uint4* W, int M, int N, int K, const QkvEpi& epi, hipStream_t st) {
-  static bool attr_done = false;
-  return launch_mid(k_gemm_qkv_mid<HD, WM, D>, MidLoop<WM, 1, HD / 32, D>::kBytes, attr_done, big_grid(N / HD, (M + 32 * WM - 1) / (32 * WM)),
-                    X, W, M, N, K, epi, st);
+  static bool attr_done[2] = {false, false};
+  const bool pk = epi.rm.packed != nullptr;
+  return launch_mid(pk ? k_gemm_qkv_mid<HD, WM, D, true> : k_gemm_qkv_mid<HD, WM, D, false>, MidLoop<WM, 1, HD / 32, D>::kBytes,
+                    attr_done[pk], big_grid(N / HD, (M + 32 * WM - 1) / (32 * WM)), X, W, M, N, K, epi, st);
 }
 // 128-token instead of 256-token tiles by what the fullest compute unit multiplies, the smaller tile's operand traffic counted as
 // 8 %.  Scoring calls, us with 256- and 128-token tiles of gate/up, 0.5B: 1600 tokens 2859, 2668; 1800 3060, 2983; 2250 3228, 3232 (6
@@ -956,24 +979,33 @@ hipError_t m_gemm_qkv_rope(const void* Xp, const void* Wp, int M, int N, int K, 
   constexpr int kAloneLds = 84 * 1024;
   static bool attr_done = false;
   if (!attr_done) {
-    hipError_t e = hipFuncSetAttribute((const void*)k_gemm_qkv_rope<64, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, kAloneLds);
-    if (e == hipSuccess)
-      e = hipFuncSetAttribute((const void*)k_gemm_qkv_rope<128, 2>, hipFuncAttributeMaxDynamicSharedMemorySize, kAloneLds);
-    if (e == hipSuccess) e = hipFuncSetAttribute((const void*)k_gemm_qkv_rope<64, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, kBigLds);
-    if (e == hipSuccess) e = hipFuncSetAttribute((const void*)k_gemm_qkv_rope<128, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, kBigLds);
+    const auto with_lds = [](auto kernel, int lds) { return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds); };
+    const auto both = [&](auto pk) {
+      constexpr bool PK = decltype(pk)::value;
+      hipError_t e = with_lds(k_gemm_qkv_rope<64, 2, PK>, kAloneLds);
+      if (e == hipSuccess) e = with_lds(k_gemm_qkv_rope<128, 2, PK>, kAloneLds);
+      if (e == hipSuccess) e = with_lds(k_gemm_qkv_rope<64, 1, PK>, kBigLds);
+      return e == hipSuccess ? with_lds(k_gemm_qkv_rope<128, 1, PK>, kBigLds) : e;
+    };
+    hipError_t e = both(std::false_type());
+    if (e == hipSuccess) e = both(std::true_type());
     if (e != hipSuccess) return e;
     attr_done = true;
   }
   const int NX = N / 128, NY = (M + 255) / 256, per_xcd = (NX * NY + 7) / 8;
   auto go = [&](auto kernel, int ny, int lds) {
-    return launch(KID_GEMM_BIG, kernel, dim3(big_grid(NX, ny)), dim3(256), lds, st, (const uint4*)Xp, (const uint4*)Wp, M, N, K, epi);
+    return launch(KID_GEMM_BIG, kernel, dim3(big_grid(NX, ny)), dim3(256), lds, st, (const uint4*)Xp, (const uint4*)Wp, epi.rows, M, N, K, epi);
   };
-  if (forced_tile() != 0 ? forced_tile() == 128 : half_tiles_leave_less(NX, M)) {
-    const int ny = (M + 127) / 128;
-    return hd == 64 ? go(k_gemm_qkv_rope<64, 1>, ny, kBigLds) : go(k_gemm_qkv_rope<128, 1>, ny, kBigLds);
-  }
-  const int lds = per_xcd <= 20 ? kAloneLds : kQkvLds;
-  return hd == 64 ? go(k_gemm_qkv_rope<64, 2>, NY, lds) : go(k_gemm_qkv_rope<128, 2>, NY, lds);
+  const auto pick = [&](auto pk) {
+    constexpr bool PK = decltype(pk)::value;
+    if (forced_tile() != 0 ? forced_tile() == 128 : half_tiles_leave_less(NX, M)) {
+      const int ny = (M + 127) / 128;
+      return hd == 64 ? go(k_gemm_qkv_rope<64, 1, PK>, ny, kBigLds) : go(k_gemm_qkv_rope<128, 1, PK>, ny, kBigLds);
+    }
+    const int lds = per_xcd <= 20 ? kAloneLds : kQkvLds;
+    return hd == 64 ? go(k_gemm_qkv_rope<64, 2, PK>, NY, lds) : go(k_gemm_qkv_rope<128, 2, PK>, NY, lds);
+  };
+  return epi.rm.packed ? pick(std::true_type()) : pick(std::false_type());
 }
 
 // 128-token tiles (three workgroups per compute unit) instead of 256-token tiles (two): for narrow outputs whose
@@ -992,16 +1024,18 @@ static bool big_prefers_small_tiles(int NX, int M) {
 
 template <int TJ, int H, int MODE>
 static hipError_t launch_big(const void* Xp, const void* Wp, int M, int N, int K, const BigEpi& epi, hipStream_t st) {
-  static bool attr_done = false;
+  static bool attr_done[2] = {false, false};
+  const bool pk = epi.rows != nullptr;
+  const auto kernel = pk ? k_gemm_big<TJ, H, MODE, true> : k_gemm_big<TJ, H, MODE, false>;
   // the residual update's four row areas and gains lie in the ring's memory
   constexpr int lds = ring_bytes(H) > 4 * (32 * 68 + 128) * 4 ? ring_bytes(H) : 4 * (32 * 68 + 128) * 4;
-  if (!attr_done) {
-    const hipError_t e = hipFuncSetAttribute((const void*)k_gemm_big<TJ, H, MODE>, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+  if (!attr_done[pk]) {
+    const hipError_t e = hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
-    attr_done = true;
+    attr_done[pk] = true;
   }
-  return launch(KID_GEMM_BIG, k_gemm_big<TJ, H, MODE>, dim3(big_grid(N / 128, (M + 128 * TJ - 1) / (128 * TJ))), dim3(256), lds, st,
-                (const uint4*)Xp, (const uint4*)Wp, M, N, K, epi);
+  return launch(KID_GEMM_BIG, kernel, dim3(big_grid(N / 128, (M + 128 * TJ - 1) / (128 * TJ))), dim3(256), lds, st,
+                (const uint4*)Xp, (const uint4*)Wp, epi.rows, M, N, K, epi);
 }
 template <int TJ, int H>
 static hipError_t launch_big(const void* Xp, const void* Wp, int M, int N, int K, const BigEpi& epi, hipStream_t st) {
@@ -1029,9 +1063,11 @@ hipError_t m_gemm_big(const void* Xp, const void* Wp, int M, int N, int K, BigEp
 // r = row_index ? row_index[i] : i; negative r (padding) gives zeros.  One workgroup per row.
 // ---------------------------------------------------------------------------------------
 __global__ void __launch_bounds__(128) k_rmsnorm_x32(const float* __restrict__ h, const float* __restrict__ gain, float eps,
-                                                     uint4* __restrict__ out, int d, const int* __restrict__ row_index) {
+                                                     uint4* __restrict__ out, int d, const int* __restrict__ row_index,
+                                                     const int* rows) {
   __shared__ float red[2];
   const int i = blockIdx.x;
+  if (rows && i >= rows_there<true>(rows, gridDim.x)) return;
   const int r = row_index ? row_index[i] : i;
   const int KS = d >> 4;
   if (r < 0) {
@@ -1060,9 +1096,24 @@ __global__ void __launch_bounds__(128) k_rmsnorm_x32(const float* __restrict__ h
   }
 }
 hipError_t m_rmsnorm_x32(const float* h, const float* gain, float eps, void* out, int M, int d, const int* row_index,
-                         hipStream_t st) {
+                         hipStream_t st, const int* rows) {
   if (M == 0) return hipSuccess;
-  return launch(KID_RMSNORM, k_rmsnorm_x32, dim3(M), dim3(128), 0, st, h, gain, eps, (uint4*)out, d, row_index);
+  return launch(KID_RMSNORM, k_rmsnorm_x32, dim3(M), dim3(128), 0, st, h, gain, eps, (uint4*)out, d, row_index, rows);
+}
+
+__global__ void __launch_bounds__(256) k_gather_rows_x32(const int* __restrict__ src_rows, const int* __restrict__ n_rows,
+                                                         const float* __restrict__ h, int d, const uint4* __restrict__ x, int q,
+                                                         float* __restrict__ h_out, uint4* __restrict__ x_out) {
+  const int i = blockIdx.x;
+  if (i >= rows_there<true>(n_rows, gridDim.x)) return;
+  const int r = src_rows[i];
+  for (int k = threadIdx.x * 4; k < d; k += 1024) *(float4*)(h_out + (size_t)i * d + k) = *(const float4*)(h + (size_t)r * d + k);
+  for (int k = threadIdx.x * 8; k < q; k += 2048) x_out[x32_chunk(i, k, q >> 4)] = x[x32_chunk(r, k, q >> 4)];
+}
+hipError_t m_gather_rows_x32(const int* src_rows, const int* n_rows, int M, const float* h, int d, const void* x, int q, float* h_out,
+                             void* x_out, hipStream_t st) {
+  if (M == 0) return hipSuccess;
+  return launch(KID_MISC, k_gather_rows_x32, dim3(M), dim3(256), 0, st, src_rows, n_rows, h, d, (const uint4*)x, q, h_out, (uint4*)x_out);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1341,24 +1392,25 @@ __device__ __forceinline__ float max_lanes(float x, float inf) {
   return __builtin_amdgcn_fmed3f(__uint_as_float(r[0]), __uint_as_float(r[1]), inf);
 }
 
-template <int HD, int HPW>
+template <int HD, int HPW, bool PK>   // PK: packed rows
 __global__ void __launch_bounds__(256, 2) k_flash_attention(const f16* __restrict__ q, RowMap rm, KVCache kv,
                                                          f16* __restrict__ out, int n_q_heads) {
   constexpr int KK = HD / 32, DT = HD / 16;
   const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63;
   const int qcol = lane & 15, grp = lane >> 4;
-  const int T = rm.T;
   const int qb = gridDim.z - 1 - blockIdx.z;   // the longest walks first, over all sequences
   const int hkv = kv.n_kv_heads, rep = n_q_heads / hkv;
   const int sblk = blockIdx.x / hkv, kvh = blockIdx.x % hkv;
+  // read through the constant address space: scalar loads, which do not queue behind the K / V fragments
+  typedef const __attribute__((address_space(4))) int* ConstInts;
+  const ConstInts first = (ConstInts)rm.first;
+  const size_t row0 = PK ? (size_t)first[sblk] : (size_t)sblk * rm.T;
+  const int T = PK ? first[sblk + 1] - (int)row0 : rm.T;   // rows of the sequence
   const int h0 = blockIdx.y * HPW;
   const int nh = min(HPW, rep - h0);
   const int q0 = qb * 64 + wave * 16;
   if (q0 >= T) return;
-  // read through the constant address space: scalar loads, which do not queue behind the K / V fragments
-  typedef const __attribute__((address_space(4))) int* ConstInts;
   const ConstInts pt = (ConstInts)(kv.page_table + (size_t)(sblk * rm.seq_stride) * kv.pages_per_seq);
-  const size_t row0 = (size_t)sblk * T;
   const int qpos = min(q0 + qcol, T - 1);   // columns past T repeat the last position and are not stored
   const size_t qstride = (size_t)n_q_heads * HD;
   Frag qf[HPW][KK];
@@ -1511,16 +1563,20 @@ hipError_t m_flash_attention(const void* q, RowMap rm, KVCache kv, void* out, in
   };
   auto groups = [&](int hpw) { return (long)nqb * n_seq * kv.n_kv_heads * ((rep + hpw - 1) / hpw); };
   const long cu = n_compute_units();
-  if (kv.head_dim == 64) {
-    if (groups(4) >= cu) return go(k_flash_attention<64, 4>, 4);
-    if (groups(2) >= cu) return go(k_flash_attention<64, 2>, 2);
-    return go(k_flash_attention<64, 1>, 1);
-  }
-  if (kv.head_dim == 128) {
-    if (groups(2) >= cu) return go(k_flash_attention<128, 2>, 2);
-    return go(k_flash_attention<128, 1>, 1);
-  }
-  return hipErrorInvalidValue;
+  const auto pick = [&](auto pk) {
+    constexpr bool PK = decltype(pk)::value;
+    if (kv.head_dim == 64) {
+      if (groups(4) >= cu) return go(k_flash_attention<64, 4, PK>, 4);
+      if (groups(2) >= cu) return go(k_flash_attention<64, 2, PK>, 2);
+      return go(k_flash_attention<64, 1, PK>, 1);
+    }
+    if (kv.head_dim == 128) {
+      if (groups(2) >= cu) return go(k_flash_attention<128, 2, PK>, 2);
+      return go(k_flash_attention<128, 1, PK>, 1);
+    }
+    return hipErrorInvalidValue;
+  };
+  return rm.packed ? pick(std::true_type()) : pick(std::false_type());
 }
 
 }  // namespace sapo

@@ -1,0 +1,100 @@
+"""Scoring passes and prompts whose padding is left out: every row keeps the bits it has without.
+
+A scoring pass of at least 2560 positions runs only the positions that a scored token depends on, side by side, and behind the
+last layer's attention only the rows that predict a scored token; smaller passes (checked against the oracle in test_gpu_mfma.py
+and test_gpu_full.py) run all of them.  A row's log-prob has the same bits whatever else is scored, so the two are compared
+sequence by sequence, bit for bit.  Prompts of different lengths are left out of the same way from 1024 positions on.
+"""
+from dataclasses import replace
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2509_08721_amd import sapo
+from paper_2509_08721_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = {
+    "hd64": replace(W.MINI_BF16, d_model=384, d_ff=576, n_layers=3, max_seq=1024),
+    "hd128": replace(W.MINI_BF16_HD128, max_seq=1024),
+}
+
+
+@pytest.fixture(scope="module", params=sorted(SHAPES))
+def model(request):
+    shape = SHAPES[request.param]
+    gw = sapo.sapo_weights_create(shape, W.perturb_norm_gains(W.make_weights(shape, 41, std=0.05), 41))
+    assert gw.uses_mfma
+    return shape, gw
+
+
+def masks(S, T, kind, rng):
+    m = np.zeros((S, T), np.uint8)
+    if kind == "ends":          # answers that end anywhere, the row's first and last token included
+        for s in range(S):
+            last = int(rng.integers(0, T)) if s > 1 else (0, T - 1)[s]
+            m[s, int(rng.integers(0, last + 1)):last + 1] = 1
+    elif kind == "holes":       # scattered tokens, whole rows without any
+        m = (rng.random((S, T)) < rng.random((S, 1)) ** 4).astype(np.uint8)
+        m[::3] = 0
+    elif kind == "one":         # a single scored token in the whole call
+        m[S // 2, T // 2] = 1
+    elif kind == "full":
+        m[:] = 255              # any value but zero counts
+    return m
+
+
+# (sequences, tokens each): page and tile edges; the smallest pass that packs; (900, 150): two passes of the call
+@pytest.mark.parametrize("S,T,kind", [(10, 256, "ends"), (20, 129, "holes"), (9, 301, "ends"), (40, 65, "ends"), (16, 161, "full"),
+                                      (16, 161, "one"), (16, 161, "none"), (5, 1000, "ends"), (900, 150, "ends")])
+def test_scores_keep_their_bits_without_the_padding(model, S, T, kind):
+    shape, gw = model
+    rng = np.random.default_rng(S * 1000 + T)
+    tokens = torch.from_numpy(rng.integers(0, shape.vocab, size=(S, T)).astype(np.int32)).cuda()
+    mask = torch.from_numpy(masks(S, T, kind, rng)).cuda()
+    rewards = torch.from_numpy(rng.random(S).astype(np.float32)).cuda()
+    assert S * T >= 2560
+    for temperature in (1.0, 0.7):
+        lp, adv = sapo.sapo_score_logprobs_at(gw, tokens, mask, rewards, 1, temperature)
+        n = 2559 // T
+        ref = [sapo.sapo_score_logprobs_at(gw, tokens[s:s + n].contiguous(), mask[s:s + n].contiguous(), rewards[s:s + n].contiguous(), 1,
+                                           temperature)[0] for s in range(0, S, n)]
+        lp = lp.cpu().numpy()
+        assert np.array_equal(lp, torch.cat(ref).cpu().numpy())
+        on = mask.cpu().numpy() != 0
+        on[:, 0] = False
+        assert np.all(lp[~on] == 0.0) and np.all(lp[on] < 0.0)
+
+
+# the workspace of a call before does not show: the same bits from memory full of NaN patterns
+def test_scores_do_not_depend_on_what_the_workspace_holds(model):
+    shape, gw = model
+    S, T = 12, 257
+    rng = np.random.default_rng(7)
+    tokens = torch.from_numpy(rng.integers(0, shape.vocab, size=(S, T)).astype(np.int32)).cuda()
+    mask = torch.from_numpy(masks(S, T, "ends", rng)).cuda()
+    rewards = torch.zeros(S, device="cuda")
+    ws = torch.zeros(sapo.sapo_score_workspace_bytes(gw, S, T) + 256, dtype=torch.uint8, device="cuda")
+    a = sapo.sapo_score_logprobs(gw, tokens, mask, rewards, 1, workspace=ws)[0].cpu().numpy()
+    ws.fill_(255)
+    b = sapo.sapo_score_logprobs(gw, tokens, mask, rewards, 1, workspace=ws)[0].cpu().numpy()
+    assert np.array_equal(a, b) and np.isfinite(a).all()
+
+
+# P prompts of up to Lp tokens, packed (P Lp >= 1024), against the same prompts two at a time (not packed)
+@pytest.mark.parametrize("P,Lp,G", [(9, 120, 4), (5, 257, 3), (40, 33, 1)])
+def test_rollouts_keep_their_bits_without_the_prompts_padding(model, P, Lp, G):
+    shape, gw = model
+    rng = np.random.default_rng(P * 100 + Lp)
+    lens = [int(x) for x in rng.integers(1, Lp + 1, size=P)]
+    lens[0], lens[1] = 1, Lp
+    prompts = torch.from_numpy(rng.integers(0, shape.vocab, size=(P, Lp)).astype(np.int32)).cuda()
+    assert P * Lp >= 1024 and sum(lens) <= P * Lp * 15 // 16
+    _, lp, _ = sapo.sapo_rollout_generate_ragged(gw, prompts, lens, G, 1, 0.0, 5)
+    for p in range(0, P, 2):
+        e = min(P, p + 2)
+        _, ref, _ = sapo.sapo_rollout_generate_ragged(gw, prompts[p:e].contiguous(), lens[p:e], G, 1, 0.0, 5)
+        # greedy, one token: the log-prob of the largest logit, from the prompt's last position
+        assert np.abs(lp[p * G:e * G].cpu().numpy() - ref.cpu().numpy()).max() <= 1e-5
