@@ -952,9 +952,12 @@ __global__ void __launch_bounds__(256) k_packed_rows(const uint8_t* __restrict__
     out0 += (part[0].x + part[1].x) + (part[2].x + part[3].x);
   }
 }
+hipError_t g_packed_lens(const uint8_t* mask, int T, int s0, int ns, int2* lens, hipStream_t st) {
+  return launch(KID_MISC, k_packed_lens, dim3(ns), dim3(256), 0, st, mask, T, s0, lens);
+}
 hipError_t g_packed_rows(const uint8_t* mask, int T, int s0, int ns, const int* page_table, int pages_per_seq, int2* lens, int* first,
                          int2* packed, int* rows, int* src_rows, int* count, hipStream_t st) {
-  const hipError_t e = launch(KID_MISC, k_packed_lens, dim3(ns), dim3(256), 0, st, mask, T, s0, lens);
+  const hipError_t e = g_packed_lens(mask, T, s0, ns, lens, st);
   if (e != hipSuccess) return e;
   return launch(KID_MISC, k_packed_rows, dim3(ns), dim3(256), 0, st, mask, T, s0, ns, (const int2*)lens, page_table, pages_per_seq, first,
                 packed, rows, src_rows, count);

@@ -1151,17 +1151,17 @@ hipError_t rmsnorm_fwd(const float* h, const float* gain, float eps, int M, int 
   });
 }
 
-// Rotary embedding in place on the query and key heads of qkv[M, (Hq + 2 Hkv) hd]; position = row % T.
+// Rotary embedding in place on the query and key heads of qkv[M, (Hq + 2 Hkv) hd]; position = pos[row], or row % T without it.
 // dir = +1 rotates by the angle, -1 by its negative (the transpose: what the backward pass applies).
-__global__ void k_rope(float* __restrict__ qkv, const float2* __restrict__ rope, int T, int n_rot_heads, int hd, int row_len,
-                       float dir, size_t total) {
+__global__ void k_rope(float* __restrict__ qkv, const float2* __restrict__ rope, int T, const int* __restrict__ pos, int n_rot_heads,
+                       int hd, int row_len, float dir, size_t total) {
   const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
   if (idx >= total) return;
   const int half = hd >> 1;
   const int i = (int)(idx % half);
   const int head = (int)((idx / half) % n_rot_heads);
   const size_t m = idx / ((size_t)half * n_rot_heads);
-  const float2 cs = rope[(size_t)(m % T) * half + i];
+  const float2 cs = rope[(pos ? (size_t)pos[m] : m % T) * half + i];
   float* p = qkv + m * row_len + (size_t)head * hd + i;
   const float x1 = p[0], x2 = p[half], s = cs.y * dir;
   p[0] = x1 * cs.x - x2 * s;
@@ -1319,7 +1319,7 @@ __global__ void __launch_bounds__(256) k_count_mask(const uint8_t* __restrict__ 
     *out = t;
   }
 }
-// Row k of `logits` belongs to row r = rows[k] of the batch (position r % T of sequence r / T), which predicts the
+// Row k of `logits` belongs to token r = rows[k] of the batch (position r % T of sequence r / T), which predicts the
 // masked token at r + 1 (the list holds exactly those rows).  In place: logits -> d loss / d logits.
 // Two passes over the row, each in float4s: log-sum-exp on a running maximum, then the gradient (the second pass finds the
 // row in the caches).  In three passes of single floats by 256 threads: 2.65 ms per chunk of 4352 x 151936 logits.
@@ -1630,9 +1630,17 @@ __global__ void k_swiglu_bwd(const float* __restrict__ dact, const float* __rest
 //  * (head dim x positions) products over the 16 positions of the tile (P V, dS K, ...): the B operand of MFMA u
 //    is the lane's own accumulator entry u of the tile just computed (position 4 g + u), the A operand is the
 //    matching row of V / K / Q / dO, read as scalars (lanes along the head dim).
-// qkv[M, q + 2 kv] holds rotated q, k and v; out[M, q]; lse[(s Hq + h) T + i].
+// qkv[M, q + 2 kv] holds rotated q, k and v; out[M, q]; lse[(s Hq + h) T + i].  A sequence is T rows; with `first` it is the rows
+// first[s] .. first[s + 1] - 1 (at most T).
 // ---------------------------------------------------------------------------------------
 typedef float f32x4_t __attribute__((ext_vector_type(4)));
+
+struct SeqRows { size_t row0; int n; };
+__device__ __forceinline__ SeqRows seq_rows(const int* __restrict__ first, int s, int T) {
+  if (!first) return SeqRows{(size_t)s * T, T};
+  const int a = first[s];
+  return SeqRows{(size_t)a, first[s + 1] - a};
+}
 
 template <int HD>
 __device__ __forceinline__ void load_rows4(const float* __restrict__ base, size_t row_stride, int row, int g, float4 (&dst)[HD / 16]) {
@@ -1770,15 +1778,18 @@ template <int HD> struct TileCols {
 template <int HD> constexpr int tile_area() { return HD % 64 == 0 ? 16 * HD / 4 : 1; }   // float4s of LDS per wave and operand
 
 template <int HD, int CH>
-__global__ void __launch_bounds__(256, HD == 128 ? 2 : 1) k_tattn_fwd(const float* __restrict__ qkv, int T, int hq, int hkv, float scale,
+__global__ void __launch_bounds__(256, HD == 128 ? 2 : 1) k_tattn_fwd(const float* __restrict__ qkv, int T_max, const int* __restrict__ first, int hq, int hkv, float scale,
                                                    float* __restrict__ out, float* __restrict__ lse, uint32_t* __restrict__ row_mx) {
   const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
   const int h = blockIdx.x, s = blockIdx.y, kvh = h / (hq / hkv);
   const int q0 = (((int)gridDim.z - 1 - (int)blockIdx.z) * 4 + wave) * 16;   // the longest walks first
+  const SeqRows seq = seq_rows(first, s, T_max);
+  const size_t row0 = seq.row0;
+  const int T = seq.n;
   if (q0 >= T) return;
   const int qd = hq * HD, kvd = hkv * HD;
   const size_t rl = (size_t)qd + 2 * kvd;
-  const float* base = qkv + (size_t)s * T * rl;
+  const float* base = qkv + row0 * rl;
   const float* qb = base + (size_t)h * HD;
   const float* kb = base + qd + (size_t)kvh * HD;
   const float* vb = kb + kvd;
@@ -1850,10 +1861,10 @@ __global__ void __launch_bounds__(256, HD == 128 ? 2 : 1) k_tattn_fwd(const floa
     mx = max_u32_xor32(max_u32_xor16(mx));
   }
   if (q0 + r >= T) return;
-  store_acc<HD>(out + ((size_t)s * T + qi) * qd + (size_t)h * HD, o, g, inv);
+  store_acc<HD>(out + (row0 + qi) * qd + (size_t)h * HD, o, g, inv);
   if (g == 0) {
-    lse[((size_t)s * hq + h) * T + qi] = m_run + logf(l_run);
-    if (row_mx) atomicMax(row_mx + (size_t)s * T + qi, mx);   // the row's heads
+    lse[((size_t)s * hq + h) * T_max + qi] = m_run + logf(l_run);
+    if (row_mx) atomicMax(row_mx + row0 + qi, mx);   // the row's heads
   }
 }
 
@@ -1862,29 +1873,32 @@ __global__ void __launch_bounds__(256, HD == 128 ? 2 : 1) k_tattn_fwd(const floa
 // Writes dq into dqkv's query columns and delta[(s Hq + h) T + i].
 template <int HD, int CH>
 __global__ void __launch_bounds__(256, HD == 64 ? 3 : 1) k_tattn_bwd_q(const float* __restrict__ qkv, const float* __restrict__ out,
-                                                     const float* __restrict__ dout, const float* __restrict__ lse, int T, int hq,
-                                                     int hkv, float scale, float* __restrict__ dqkv, float* __restrict__ delta) {
+                                                     const float* __restrict__ dout, const float* __restrict__ lse, int T_max,
+                                                     const int* __restrict__ first, int hq, int hkv, float scale, float* __restrict__ dqkv, float* __restrict__ delta) {
   const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
   const int h = blockIdx.x, s = blockIdx.y, kvh = h / (hq / hkv);
   const int q0 = (((int)gridDim.z - 1 - (int)blockIdx.z) * 4 + wave) * 16;   // the longest walks first
+  const SeqRows seq = seq_rows(first, s, T_max);
+  const size_t row0 = seq.row0;
+  const int T = seq.n;
   if (q0 >= T) return;
   const int qd = hq * HD, kvd = hkv * HD;
   const size_t rl = (size_t)qd + 2 * kvd;
-  const float* base = qkv + (size_t)s * T * rl;
+  const float* base = qkv + row0 * rl;
   const float* qb = base + (size_t)h * HD;
   const float* kb = base + qd + (size_t)kvh * HD;
   const float* vb = kb + kvd;
   const int qi = min(q0 + r, T - 1);
   float4 qf[HD / 16], dof[HD / 16], of[HD / 16];
   load_rows4<HD>(qb, rl, qi, g, qf);
-  load_rows4<HD>(dout + (size_t)s * T * qd + (size_t)h * HD, qd, qi, g, dof);
-  load_rows4<HD>(out + (size_t)s * T * qd + (size_t)h * HD, qd, qi, g, of);
+  load_rows4<HD>(dout + row0 * qd + (size_t)h * HD, qd, qi, g, dof);
+  load_rows4<HD>(out + row0 * qd + (size_t)h * HD, qd, qi, g, of);
   float dl = 0.f;
 #pragma unroll
   for (int w = 0; w < HD / 16; ++w)
     dl += dof[w].x * of[w].x + dof[w].y * of[w].y + dof[w].z * of[w].z + dof[w].w * of[w].w;
   dl = sum_xor32(sum_xor16(dl));
-  const size_t stat = ((size_t)s * hq + h) * T + qi;
+  const size_t stat = ((size_t)s * hq + h) * T_max + qi;
   const float l = lse[stat];
   f32x4_t dq[HD / 16];
 #pragma unroll
@@ -1924,7 +1938,7 @@ __global__ void __launch_bounds__(256, HD == 64 ? 3 : 1) k_tattn_bwd_q(const flo
     else accumulate_tile<HD>(kb + (size_t)k0 * rl, rl, n_valid, g, r, ds, dq);
   }
   if (q0 + r >= T) return;
-  store_acc<HD>(dqkv + ((size_t)s * T + qi) * rl + (size_t)h * HD, dq, g, 1.0f);
+  store_acc<HD>(dqkv + (row0 + qi) * rl + (size_t)h * HD, dq, g, 1.0f);
   if (g == 0) delta[stat] = dl;
 }
 
@@ -1935,16 +1949,19 @@ __global__ void __launch_bounds__(256, HD == 64 ? 3 : 1) k_tattn_bwd_q(const flo
 //   p = exp(scale s - lse_q), dV^T += dO^T p, dP = dO V^T, dS = scale p (dP - delta_q), dK^T += Q^T dS.
 template <int HD, int CH>
 __global__ void __launch_bounds__(256, HD == 64 ? 2 : 1) k_tattn_bwd_kv(const float* __restrict__ qkv, const float* __restrict__ dout,
-                                                      const float* __restrict__ lse, const float* __restrict__ delta, int T, int hq,
-                                                      int hkv, float scale, int n_heads, float* __restrict__ dkv, size_t row_stride,
+                                                      const float* __restrict__ lse, const float* __restrict__ delta, int T_max,
+                                                      const int* __restrict__ first, int hq, int hkv, float scale, int n_heads, float* __restrict__ dkv, size_t row_stride,
                                                       size_t part_stride) {
   const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
   const int kvh = blockIdx.x % hkv, part = blockIdx.x / hkv, s = blockIdx.y, rep = hq / hkv;
   const int k0 = (blockIdx.z * 4 + wave) * 16;   // the longest walks first
+  const SeqRows seq = seq_rows(first, s, T_max);
+  const size_t row0 = seq.row0;
+  const int T = seq.n;
   if (k0 >= T) return;
   const int qd = hq * HD, kvd = hkv * HD;
   const size_t rl = (size_t)qd + 2 * kvd;
-  const float* base = qkv + (size_t)s * T * rl;
+  const float* base = qkv + row0 * rl;
   const float* kb = base + qd + (size_t)kvh * HD;
   const float* vb = kb + kvd;
   const int kj = min(k0 + r, T - 1);
@@ -1960,9 +1977,9 @@ __global__ void __launch_bounds__(256, HD == 64 ? 2 : 1) k_tattn_bwd_kv(const fl
   for (int hh = 0; hh < n_heads; ++hh) {
     const int h = kvh * rep + part * n_heads + hh;
     const float* qb = base + (size_t)h * HD;
-    const float* dob = dout + (size_t)s * T * qd + (size_t)h * HD;
-    const float* lse_h = lse + ((size_t)s * hq + h) * T;
-    const float* del_h = delta + ((size_t)s * hq + h) * T;
+    const float* dob = dout + row0 * qd + (size_t)h * HD;
+    const float* lse_h = lse + ((size_t)s * hq + h) * T_max;
+    const float* del_h = delta + ((size_t)s * hq + h) * T_max;
     TileCols<COLS ? HD : 64> qc, qn, doc, don;
     if constexpr (COLS) {
       qn.stride(rl, g, r); don.stride(qd, g, r);
@@ -2010,34 +2027,35 @@ __global__ void __launch_bounds__(256, HD == 64 ? 2 : 1) k_tattn_bwd_kv(const fl
     }
   }
   if (!key_ok) return;
-  float* krow = dkv + part * part_stride + ((size_t)s * T + kj) * row_stride + (size_t)kvh * HD;
+  float* krow = dkv + part * part_stride + (row0 + kj) * row_stride + (size_t)kvh * HD;
   store_acc<HD>(krow, dk, g, 1.0f);
   store_acc<HD>(krow + kvd, dv, g, 1.0f);
 }
 
 template <int HD, int CH>
-hipError_t tattn_bwd(const float* qkv, const float* out, const float* dout, const float* lse, int S, int T, int hq, int hkv,
-                     float scale, float* dqkv, float* delta, float* parts, hipStream_t st) {
+hipError_t tattn_bwd(const float* qkv, const float* out, const float* dout, const float* lse, int S, int T, const int* first, size_t M,
+                     int hq, int hkv, float scale, float* dqkv, float* delta, float* parts, hipStream_t st) {
   const unsigned tiles = (unsigned)((T + 63) / 64);
-  hipError_t e = launch(KID_ATTN_GENERIC, k_tattn_bwd_q<HD, CH>, dim3(hq, S, tiles), dim3(256), 0, st, qkv, out, dout, lse, T, hq, hkv,
-                        scale, dqkv, delta);
+  hipError_t e = launch(KID_ATTN_GENERIC, k_tattn_bwd_q<HD, CH>, dim3(hq, S, tiles), dim3(256), 0, st, qkv, out, dout, lse, T, first, hq,
+                        hkv, scale, dqkv, delta);
   if (e != hipSuccess) return e;
   const size_t qd = (size_t)hq * HD, kvd = (size_t)hkv * HD;
-  if (parts)   // [query heads of a group][S T][2 kvd]
+  if (parts)   // [query heads of a group][M rows][2 kvd]
     return launch(KID_ATTN_GENERIC, k_tattn_bwd_kv<HD, CH>, dim3(hq, S, tiles), dim3(256), 0, st, qkv, dout, lse, (const float*)delta, T,
-                  hq, hkv, scale, 1, parts, 2 * kvd, (size_t)S * T * 2 * kvd);
+                  first, hq, hkv, scale, 1, parts, 2 * kvd, M * 2 * kvd);
   return launch(KID_ATTN_GENERIC, k_tattn_bwd_kv<HD, CH>, dim3(hkv, S, tiles), dim3(256), 0, st, qkv, dout, lse, (const float*)delta, T,
-                hq, hkv, scale, hq / hkv, dqkv + qd, qd + 2 * kvd, (size_t)0);
+                first, hq, hkv, scale, hq / hkv, dqkv + qd, qd + 2 * kvd, (size_t)0);
 }
 // The partial results of k_tattn_bwd_kv added in part order into dqkv's key and value columns, and the rotary embedding's
 // transpose on the query and key columns.  One workgroup per row; a thread takes 4 rotation pairs or 4 value columns.
 __global__ void __launch_bounds__(256) k_attn_bwd_finish(float* __restrict__ dqkv, const float* __restrict__ parts, int n_parts,
-                                                         size_t part_stride, const float2* __restrict__ rope, int T, int hq, int hkv,
-                                                         int hd, uint32_t* __restrict__ row_mx) {
+                                                         size_t part_stride, const float2* __restrict__ rope, int T, const int* __restrict__ pos,
+                                                         int hq, int hkv, int hd, uint32_t* __restrict__ row_mx) {
   uint32_t mx = 0;
   auto seen = [&](const float4& v) { mx = max(max(max(mx, abs_bits(v.x)), max(abs_bits(v.y), abs_bits(v.z))), abs_bits(v.w)); };
   const size_t m = blockIdx.x;
   const int half = hd >> 1, qd = hq * hd, kvd = hkv * hd, quads = half >> 2;
+  const size_t at = pos ? (size_t)pos[m] : m % T;   // the row's position
   float* row = dqkv + m * (size_t)(qd + 2 * kvd);
   const float* prow = parts + m * (size_t)(2 * kvd);
   auto sum = [&](int c) {   // column c of [dk | dv]
@@ -2062,7 +2080,7 @@ __global__ void __launch_bounds__(256) k_attn_bwd_finish(float* __restrict__ dqk
     float4 a, b;
     if (head < hq) { a = *(const float4*)p; b = *(const float4*)(p + half); }
     else { a = sum((head - hq) * hd + i); b = sum((head - hq) * hd + i + half); }
-    const float4* cs = (const float4*)(rope + (m % T) * half + i);
+    const float4* cs = (const float4*)(rope + at * half + i);
     const float4 c01 = cs[0], c23 = cs[1];   // (cos, sin) of four pairs
     const float4 lo = make_float4(a.x * c01.x + b.x * c01.y, a.y * c01.z + b.y * c01.w, a.z * c23.x + b.z * c23.y, a.w * c23.z + b.w * c23.w);
     const float4 hi = make_float4(b.x * c01.x - a.x * c01.y, b.y * c01.z - a.y * c01.w, b.z * c23.x - a.z * c23.y, b.w * c23.z - a.w * c23.w);
@@ -2258,7 +2276,8 @@ struct TrainPlan {
   float *h_last, *rf, *xf;                      // final residual rows, their rstd, final-normed rows
   float* xfc;                                   // the final-normed rows that predict a masked token, gathered
   int* eorder;                                  // a chunk's rows ordered by token (embedding gradient)
-  int *mrows, *mpos, *mcount;                   // per micro-batch: those rows' indices (mpos: their (s, t)), their number
+  int *mrows, *mpos, *mcount;                   // per micro-batch: those rows' indices (mpos: scratch, see PackedUpdate), their number
+  int* first;                                   // packed rows: a sequence's first one
   float *dh, *dx, *dact, *dgu, *dao, *dqkv;     // backward temporaries (dgu: also its packed form by rows of features)
   float *delta, *prob, *dsc, *gpart, *logits, *logp_all, *loss;
   void* sur_ws;
@@ -2297,7 +2316,8 @@ void make_plan(const sapo_model_config& c, size_t S, size_t T, size_t S_total, c
   p.mrows = A.take<int>(S_total * T);
   p.eorder = A.take<int>(M);
   p.mpos = A.take<int>(2 * M);
-  p.mcount = A.take<int>((S_total + S - 1) / S);
+  p.mcount = A.take<int>(2 * ((S_total + S - 1) / S));
+  p.first = A.take<int>(S + 1);
   p.dh = A.take<float>(M * D.d);
   p.dx = A.take<float>(M * D.d);
   p.dact = A.take<float>(M * D.F);
@@ -2532,12 +2552,77 @@ extern "C" int sapo_trainer_export(const sapo_trainer* tr, void* const* tensors_
 // an update (first) and added by the others (zeroing the buffer and adding to the zeros moved 6 GB at 0.5B: 21 x 301 tokens,
 // one piece, 43.0 -> 42.0 ms), the log-probs go to logp_new [S_, T_].  p.n_masked holds the count of masked tokens of the whole training set and
 // the LM head is packed (p.head_nt, p.head_t).
+// The rows of a micro-batch that the loss depends on.  Attention is causal and a row's gradient is zero behind its sequence's last
+// masked token, so what lies behind it (answers that end before their row does) needs neither pass.  Sequence s goes on with
+// lens[s].x positions, side by side with the others': row first[s] + t is token tokens[first[s] + t] at position t; rows: those that
+// predict a masked token, token_rows: the same as indices into [S, T].
+struct PackedUpdate {
+  int2* lens = nullptr;
+  int *first = nullptr, *pos = nullptr, *tokens = nullptr, *rows = nullptr, *token_rows = nullptr;
+  // in buffers that are free until the backward pass through the layers (token_rows) or the embedding's gradient (lens)
+  void init(const TrainPlan& p, int S, int n_rows) {
+    lens = (int2*)p.eorder; first = p.first; pos = p.mpos; tokens = p.mpos + n_rows; rows = p.mrows; token_rows = (int*)p.dh_r;
+  }
+};
+__global__ void __launch_bounds__(256) k_packed_update(const uint8_t* __restrict__ mask, const int32_t* __restrict__ tokens, int T, int S,
+                                                       const int2* __restrict__ lens, int* __restrict__ first, int* __restrict__ pos,
+                                                       int* __restrict__ row_tokens, int* __restrict__ rows, int* __restrict__ token_rows) {
+  __shared__ int2 part[4];
+  const int s = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int row0 = 0, out0 = 0;   // rows and listed ones of the sequences in front
+  for (int i = threadIdx.x; i < s; i += 256) { row0 += lens[i].x; out0 += lens[i].y; }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) { row0 += __shfl_xor(row0, o, 64); out0 += __shfl_xor(out0, o, 64); }
+  if (lane == 0) part[wave] = make_int2(row0, out0);
+  __syncthreads();
+  row0 = (part[0].x + part[1].x) + (part[2].x + part[3].x);
+  out0 = (part[0].y + part[1].y) + (part[2].y + part[3].y);
+  const int n = lens[s].x;
+  if (threadIdx.x == 0) {
+    first[s] = row0;
+    if (s == S - 1) first[S] = row0 + n;
+  }
+  for (int t0 = 0; t0 <= n; t0 += 256) {
+    const int t = t0 + threadIdx.x;
+    if (t < n) { pos[row0 + t] = t; row_tokens[row0 + t] = tokens[(size_t)s * T + t]; }
+    const bool on = t >= 1 && t <= n && mask[(size_t)s * T + t] != 0;
+    const unsigned long long all = __ballot(on);
+    __syncthreads();   // part is read
+    if (lane == 0) part[wave].x = __popcll(all);
+    __syncthreads();
+    int o = out0 + __popcll(all & ((1ull << lane) - 1ull));
+    for (int w = 0; w < wave; ++w) o += part[w].x;
+    if (on) { rows[o] = row0 + t - 1; token_rows[o] = s * T + t - 1; }
+    out0 += (part[0].x + part[1].x) + (part[2].x + part[3].x);
+  }
+}
+__global__ void __launch_bounds__(256) k_packed_count(const int2* __restrict__ lens, int S, int* __restrict__ count) {
+  __shared__ int part[4];
+  int n = 0;
+  for (int i = threadIdx.x; i < S; i += 256) n += lens[i].x;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o, 64);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = n;
+  __syncthreads();
+  if (threadIdx.x == 0) *count = (part[0] + part[1]) + (part[2] + part[3]);
+}
+
 static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* tokens, const uint8_t* completion_mask,
                        const float* logp_old, const float* advantages, int S_, int T_, float eps_low, float eps_high,
-                       float* logp_new, const int* rows, int n_rows, bool first, hipStream_t st) {
+                       float* logp_new, const int* rows, int n_rows, int n_packed, bool first, hipStream_t st) {
   const sapo_model_config& c = tr->cfg;
   const Dims D(c);
-  const size_t S = S_, T = T_, M = S * T;
+  const size_t S = S_, T = T_, M = n_packed > 0 ? (size_t)n_packed : S * T;
+  PackedUpdate pk;
+  if (n_packed > 0) {
+    pk.init(p, S_, n_packed);
+    T_CK(g_packed_lens(completion_mask, T_, 0, S_, pk.lens, st));
+    T_CK(launch(KID_MISC, k_packed_update, dim3(S_), dim3(256), 0, st, completion_mask, tokens, T_, S_, (const int2*)pk.lens, pk.first, pk.pos,
+                pk.tokens, pk.rows, pk.token_rows));
+    rows = pk.rows;
+  }
+  const int32_t* row_tokens = n_packed > 0 ? pk.tokens : tokens;   // of each row
+  const int* token_rows = n_packed > 0 ? pk.token_rows : rows;     // the listed rows as tokens of the batch
   const int d = (int)D.d, q = (int)D.q, kv = (int)D.kv, nqkv = (int)D.nqkv, F = (int)D.F, V = (int)D.V;
   const int hq = c.n_q_heads, hkv = c.n_kv_heads, hd = c.head_dim;
   const int Mi = (int)M;
@@ -2593,7 +2678,7 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
   const int blocks64 = (Mi + 127) / 128 * 2;   // blocks of 64 tokens that a packed operand by rows of tokens holds
   // ---- forward, every activation kept
   float* h = p.layer[0].h;
-  T_CK(launch(KID_EMBED, k_embed_rows, dim3(Mi), dim3(256), 0, st, tokens, (const float*)TH(0), h, d, V));
+  T_CK(launch(KID_EMBED, k_embed_rows, dim3(Mi), dim3(256), 0, st, row_tokens, (const float*)TH(0), h, d, V));
   for (int l = 0; l < D.L; ++l) {
     const LayerActs& a = p.layer[l];
     const LayerMax& mx = p.mx[l];
@@ -2604,13 +2689,14 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
     {
       const size_t total = M * (size_t)(hq + hkv) * (hd / 2);
       T_CK(launch(KID_ROPE_APPEND, k_rope, dim3(blocks256(total)), dim3(256), 0, st, a.qkv, (const float2*)tr->rope, (int)T,
-                  hq + hkv, hd, nqkv, 1.0f, total));
+                  (const int*)pk.pos, hq + hkv, hd, nqkv, 1.0f, total));
     }
     if (fused_attn) {
       const dim3 ag(hq, (unsigned)S, (unsigned)((T + 63) / 64));
       uint32_t* const ao_r = NP == 3 ? mx.ao_r : nullptr;
       auto fwd = [&](auto kernel) {
-        return launch(KID_ATTN_GENERIC, kernel, ag, dim3(256), 0, st, (const float*)a.qkv, (int)T, hq, hkv, att_scale, a.ao, a.lse, ao_r);
+        return launch(KID_ATTN_GENERIC, kernel, ag, dim3(256), 0, st, (const float*)a.qkv, (int)T, (const int*)pk.first, hq, hkv, att_scale, a.ao,
+                      a.lse, ao_r);
       };
       hipError_t e = hipErrorInvalidValue;
       if (hd == 16) e = NP == 3 ? fwd(k_tattn_fwd<16, 4>) : fwd(k_tattn_fwd<16, 1>);
@@ -2659,7 +2745,7 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
   // ---- LM head, over the rows that predict a masked token only (the others have no log-prob to report and a zero
   // d logits row): their final-normed rows gathered, then chunks of them: logits, log-probs, d logits, d rows (into
   // p.dh, scattered to p.dx afterwards) and d head
-  T_CK(g_fill_f32(logp_new, 0.f, M, st));
+  T_CK(g_fill_f32(logp_new, 0.f, S * T, st));
   T_CK(g_fill_f32(p.dx, 0.f, M * D.d, st));
   // the embedding's gradient is added up row by row, by the head's rows first where the two are one tensor
   if (first && t_head != 0) T_CK(g_fill_f32(GR(0), 0.f, D.V * D.d, st));
@@ -2671,7 +2757,7 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
       const int R = (int)(((size_t)n_rows - r0 < p.chunk) ? (size_t)n_rows - r0 : p.chunk);
       const Mat xfc{p.xfc + r0 * D.d, d, p.xfc_r + r0, p.xfc_c}, logits{p.logits, V, p.dl_r, p.dl_c}, head{TH(t_head), d, p.head_r, p.head_c};
       T_CK(mm_nt(xfc, head, p.logits, V, R, V, d, 0.f, nullptr, p.head_nt));
-      T_CK(launch(KID_SCORE_ROWS, k_logp_dlogits, dim3(R), dim3(kLogpThreads), 0, st, p.logits, V, rows + r0, (int)T, tokens, completion_mask,
+      T_CK(launch(KID_SCORE_ROWS, k_logp_dlogits, dim3(R), dim3(kLogpThreads), 0, st, p.logits, V, token_rows + r0, (int)T, tokens, completion_mask,
                   logp_old, advantages, eps_low, eps_high, (const long long*)p.n_masked, logp_new, p.dl_r));
       T_CK(mm_nn(logits, head, p.dh + r0 * D.d, d, R, d, V, 0.f, p.head_t));
       T_CK(mm_tn(logits, xfc, GR(t_head), V, d, R, r0 == 0 ? keep : 1.f));
@@ -2750,7 +2836,7 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
     float* kv_parts = fused_attn && rep > 1 && 2 * D.F >= 2 * D.q ? p.dgu : nullptr;
     if (fused_attn) {
       hipError_t e = hipErrorInvalidValue;
-      auto bwd = [&](auto f) { return f(a.qkv, a.ao, p.dao, a.lse, S_, T_, hq, hkv, att_scale, p.dqkv, p.delta, kv_parts, st); };
+      auto bwd = [&](auto f) { return f(a.qkv, a.ao, p.dao, a.lse, S_, T_, pk.first, M, hq, hkv, att_scale, p.dqkv, p.delta, kv_parts, st); };
       if (hd == 16) e = NP == 3 ? bwd(tattn_bwd<16, 4>) : bwd(tattn_bwd<16, 1>);
       if (hd == 32) e = NP == 3 ? bwd(tattn_bwd<32, 4>) : bwd(tattn_bwd<32, 1>);
       if (hd == 64) e = NP == 3 ? bwd(tattn_bwd<64, 4>) : bwd(tattn_bwd<64, 1>);
@@ -2785,11 +2871,11 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
     }
     if (kv_parts) {
       T_CK(launch(KID_ROPE_APPEND, k_attn_bwd_finish, dim3(Mi), dim3(256), 0, st, p.dqkv, (const float*)kv_parts, rep,
-                  M * 2 * D.kv, (const float2*)tr->rope, (int)T, hq, hkv, hd, NP == 3 ? mx.dqkv_r : nullptr));
+                  M * 2 * D.kv, (const float2*)tr->rope, (int)T, (const int*)pk.pos, hq, hkv, hd, NP == 3 ? mx.dqkv_r : nullptr));
     } else {
       const size_t total = M * (size_t)(hq + hkv) * (hd / 2);
       T_CK(launch(KID_ROPE_APPEND, k_rope, dim3(blocks256(total)), dim3(256), 0, st, p.dqkv, (const float2*)tr->rope, (int)T,
-                  hq + hkv, hd, nqkv, -1.0f, total));
+                  (const int*)pk.pos, hq + hkv, hd, nqkv, -1.0f, total));
       T_CK(rows_max(p.dqkv, nqkv, mx.dqkv_r));
     }
     if (tr->use_bias) {   // the biases enter before the rotary embedding: their gradient is the column sum of dqkv here
@@ -2804,10 +2890,10 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
     T_CK(mm_tn(dqkv, Mat{a.xn, d, nullptr, mx.xn_c}, GR(t0 + 1), nqkv, d, Mi, keep));
     T_CK(norm_bwd(p.dx, a.h, a.r1, t0, 1));
   }
-  T_CK(launch(KID_EMBED, k_embed_order, dim3((Mi + kEmbedChunk - 1) / kEmbedChunk), dim3(1024), 0, st, tokens, Mi, V, p.eorder));
+  T_CK(launch(KID_EMBED, k_embed_order, dim3((Mi + kEmbedChunk - 1) / kEmbedChunk), dim3(1024), 0, st, row_tokens, Mi, V, p.eorder));
   for (int m0 = 0; m0 < Mi; m0 += kEmbedChunk) {
     const int n = std::min(kEmbedChunk, Mi - m0);
-    T_CK(launch(KID_EMBED, k_embed_add, dim3(n, (d + 255) / 256), dim3(64), 0, st, tokens + m0, (const int*)(p.eorder + m0), n,
+    T_CK(launch(KID_EMBED, k_embed_add, dim3(n, (d + 255) / 256), dim3(64), 0, st, row_tokens + m0, (const int*)(p.eorder + m0), n,
                 (const float*)(p.dh + (size_t)m0 * D.d), d, V, GR(0)));
   }
 
@@ -2889,20 +2975,26 @@ extern "C" int sapo_policy_update(sapo_trainer* tr, const int32_t* tokens, const
   // the host needs the numbers to size the LM head's GEMMs, so the call waits here once, before the forward passes
   // are enqueued, for these small kernels (and for whatever the stream held before).
   const size_t n_mb = (S + S_mb - 1) / S_mb;
-  std::vector<int> n_rows(n_mb, 0);
+  std::vector<int> counts(2 * n_mb, 0);
+  const int *n_rows = counts.data(), *n_needed = n_rows + n_mb;
   for (size_t i = 0; i < n_mb; ++i) {
     const size_t s0 = i * S_mb;
     const int n = (int)(S - s0 < S_mb ? S - s0 : S_mb);
     T_CK(g_masked_rows(completion_mask + s0 * T, T_, 0, n, p.mpos, p.mrows + s0 * T, p.mcount + i, st));
+    T_CK(g_packed_lens(completion_mask + s0 * T, T_, 0, n, (int2*)p.eorder, st));
+    T_CK(launch(KID_MISC, k_packed_count, dim3(1), dim3(256), 0, st, (const int2*)p.eorder, n, p.mcount + n_mb + i));
   }
-  T_CK(hipMemcpyAsync(n_rows.data(), p.mcount, n_mb * sizeof(int), hipMemcpyDeviceToHost, st));
+  T_CK(hipMemcpyAsync(counts.data(), p.mcount, 2 * n_mb * sizeof(int), hipMemcpyDeviceToHost, st));
   T_CK(hipStreamSynchronize(st));
   for (size_t i = 0; i < n_mb; ++i) {
     const size_t s0 = i * S_mb;
     const int n = (int)(S - s0 < S_mb ? S - s0 : S_mb);
-    if (n_rows[i] < 0 || (size_t)n_rows[i] > (size_t)n * T) return set_error(SAPO_EHIP, "row count read back from the device is out of range");
+    if (n_rows[i] < 0 || (size_t)n_rows[i] > (size_t)n * T || n_needed[i] < 0 || (size_t)n_needed[i] > (size_t)n * T)
+      return set_error(SAPO_EHIP, "row count read back from the device is out of range");
+    // without the rows that nothing depends on, where they are a sixteenth or more (with fewer, and with none at all: all rows as they lie)
+    const bool packs = fused_attention(c) && n_needed[i] > 0 && (size_t)n_needed[i] + (size_t)n * T / 16 <= (size_t)n * T;
     const int rc = update_rows(tr, p, tokens + s0 * T, completion_mask + s0 * T, logp_old + s0 * T, advantages + s0, n, T_,
-                               eps_low, eps_high, p.logp_all + s0 * T, p.mrows + s0 * T, n_rows[i], i == 0, st);
+                               eps_low, eps_high, p.logp_all + s0 * T, p.mrows + s0 * T, n_rows[i], packs ? n_needed[i] : 0, i == 0, st);
     if (rc != SAPO_OK) return rc;
   }
   // ---- the loss (the surrogate of sapo_clipped_surrogate on the log-probs just computed)

@@ -1,0 +1,94 @@
+"""Updates on answers that end before their row does: what lies behind a sequence's last masked token goes through neither pass.
+
+Loss, log-probs and every gradient against the float64 reference (the bounds of test_gpu_update.py), with the whole set at once and in
+micro-batches (some of them without a masked token, which run all rows as they lie), and the same bits whatever the padding holds.
+"""
+import numpy as np
+import pytest
+import torch
+
+from paper_2509_08721_amd import workloads as W
+from tests.test_gpu_update import SHAPES, dev, read_all, sapo  # noqa: F401  (sapo: the fixture)
+
+pytestmark = pytest.mark.gpu
+
+
+def case(shape, seed, S, T, kind):
+    from oracle import sapo_update_oracle as U
+    w = W.perturb_norm_gains(W.make_weights(shape, seed, std=0.25), seed)
+    rng = np.random.default_rng([seed, S, T])
+    tokens = rng.integers(0, shape.vocab, size=(S, T)).astype(np.int32)
+    mask = np.zeros((S, T), np.uint8)
+    for s in range(S):
+        last = (int(rng.integers(1, T)), 1, T // 2, T - 1)[min(s, 3)] if s < 4 else int(rng.integers(0, T))
+        mask[s, max(0, last - int(rng.integers(0, T))):last + 1] = 1
+    if kind == "holes":
+        mask &= rng.random((S, T)) < 0.3
+        mask[0, 1] = 1
+    if kind == "gaps":          # sequences (with one or two to a micro-batch: micro-batches) without a masked token; one masked at 0 only
+        mask[2:4] = 0
+        mask[S - 1] = 0
+        mask[S - 1, 0] = 1
+    adv = rng.standard_normal(S).astype(np.float32)
+    params = U.parameter_list(shape, w)
+    _, lp, _ = U.loss_and_gradients(shape, params, tokens, mask, np.zeros((S, T), np.float32), adv)
+    u = rng.uniform(-0.4, 0.4, size=lp.shape)
+    u[(np.abs(np.exp(-u) - 1.28) < 0.02) | (np.abs(np.exp(-u) - 0.8) < 0.02)] = 0.0   # clear of the clip bounds
+    return w, params, tokens, mask, (lp + u * (mask != 0)).astype(np.float32), adv
+
+
+@pytest.mark.parametrize("name,S,T", [("tiny", 7, 32), ("ragged_untied", 5, 13), ("hd128", 5, 70), ("tiny_long", 4, 300), ("hd24", 4, 40)])
+@pytest.mark.parametrize("kind", ["ends", "holes", "gaps"])
+@pytest.mark.parametrize("s_micro", [None, 2])
+def test_update_without_the_padding(sapo, name, S, T, kind, s_micro):  # noqa: F811
+    from oracle import sapo_update_oracle as U
+    shape = SHAPES[name]
+    w, params, tokens, mask, logp_old, adv = case(shape, 900 + len(name), S, T, kind)
+    ref_loss, ref_lp, ref_g = U.loss_and_gradients(shape, params, tokens, mask, logp_old, adv)
+    gmax = max(float(np.max(np.abs(x))) for x in ref_g)
+    bits = None
+    for padding in (0, 1):
+        t = tokens.copy()
+        for s in range(S):
+            on = np.flatnonzero(mask[s])
+            end = int(on[-1]) + 1 if len(on) else 0
+            if padding:
+                t[s, end:] = (t[s, end:] + 1 + np.arange(T - end)) % shape.vocab
+        tr = sapo.sapo_trainer_create(shape, w)
+        ws = None
+        if s_micro:
+            ws = torch.empty(sapo.sapo_trainer_workspace_bytes_for(tr, S, T, s_micro) + 256, dtype=torch.uint8, device="cuda").fill_(255)
+        loss, lp = sapo.sapo_policy_update(tr, dev(t), dev(mask), dev(logp_old), dev(adv), workspace=ws)
+        torch.cuda.synchronize()
+        loss, lp, g = float(loss.cpu()[0]), lp.cpu().numpy(), read_all(sapo, tr, 1)
+        tr.close()
+        if bits is None:
+            assert np.max(np.abs(lp - ref_lp)) < 2e-4 and abs(loss - ref_loss) < 1e-4 * max(1.0, abs(ref_loss))
+            for a, b in zip(g, ref_g):
+                assert float(np.max(np.abs(a - b))) <= 2e-4 * max(float(np.max(np.abs(b))), 1e-3 * gmax) + 1e-7
+            bits = (loss, lp, g)
+        elif name != "hd24" and kind != "gaps":   # those run rows that nothing depends on, at head dims without the fused attention
+            assert loss == bits[0] and np.array_equal(lp, bits[1]) and all(np.array_equal(a, b) for a, b in zip(g, bits[2]))
+
+
+# operands of one and two pieces: a sequence's log-probs have the same bits with and without other sequences' padding
+@pytest.mark.parametrize("pieces", [1, 2])
+def test_log_probs_keep_their_bits(sapo, pieces):  # noqa: F811
+    shape = W.MINI_BF16
+    S, T = 6, 150
+    w = W.make_weights(shape, 5, std=0.05)
+    rng = np.random.default_rng(6)
+    tokens = rng.integers(0, shape.vocab, size=(S, T)).astype(np.int32)
+    ends = np.zeros((S, T), np.uint8)
+    for s in range(S):
+        ends[s, 3:int(rng.integers(10, T // 2))] = 1
+    full = np.ones((S, T), np.uint8)
+    old, adv = np.zeros((S, T), np.float32), np.zeros(S, np.float32)
+    out = []
+    for mask in (ends, full):
+        tr = sapo.sapo_trainer_create(shape, w)
+        sapo.sapo_trainer_set_matmul_pieces(tr, pieces)
+        _, lp = sapo.sapo_policy_update(tr, dev(tokens), dev(mask), dev(old), dev(adv))
+        out.append(lp.cpu().numpy())
+        tr.close()
+    assert np.array_equal(out[0], np.where(ends != 0, out[1], np.float32(0)))
