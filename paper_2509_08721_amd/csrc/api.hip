@@ -580,12 +580,17 @@ static int run_layers_generic(const sapo_weights* w, const FwdBufs& b, int M, Ro
 }
 
 // MFMA, many rows (prefill and scoring)
-// scored: packed rows of a scoring pass.  Behind the last layer's attention only the rows that predict a scored token are
-// multiplied; they end up side by side in scored->h.
-struct ScoredRows { const int *src_rows, *count; float* h; };
+// The rows whose final state is wanted: n of them, or (count, on the device) at most n.  Behind the last layer's attention only
+// these are multiplied, from src_rows[i] on; they end up side by side in h, which takes the place of the fp32 q / k / v rows (they do not
+// exist on this path), and their attention output that of the FFN's activations.
+struct WantedRows { const int *src_rows, *count; int n; float* h; };
+static bool can_narrow(const sapo_model_config& c) {
+  const int q = c.n_q_heads * c.head_dim;
+  return c.n_layers > 0 && c.d_model <= q + 2 * c.n_kv_heads * c.head_dim && q <= c.d_ff;
+}
 // M rows of n_seq sequences, or (rows) at most M
 static int run_layers_big(const sapo_weights* w, const FwdBufs& b, int M, int n_seq, RowMap rm, const CacheBufs& cb, const int* rows,
-                          const ScoredRows* scored, hipStream_t st) {
+                          const WantedRows* wanted, hipStream_t st) {
   const sapo_model_config& c = w->cfg;
   const int d = c.d_model, q = c.n_q_heads * c.head_dim, kv = c.n_kv_heads * c.head_dim, F = c.d_ff;
   for (int l = 0; l < c.n_layers; ++l) {
@@ -612,9 +617,9 @@ static int run_layers_big(const sapo_weights* w, const FwdBufs& b, int M, int n_
     if (clamped) HIP_CK(g_count_half_at_limit(b.attn, M, q, 1, clamped, st));
     float* h = b.h;
     const void* attn = b.attn;
-    if (scored && l + 1 == c.n_layers) {
-      HIP_CK(m_gather_rows_x32(scored->src_rows, scored->count, M, b.h, d, b.attn, q, scored->h, b.act, st));
-      h = scored->h; attn = b.act; rows = scored->count;
+    if (wanted && l + 1 == c.n_layers) {
+      M = wanted->n; rows = wanted->count; h = wanted->h; attn = b.act;
+      HIP_CK(m_gather_rows_x32(wanted->src_rows, rows, M, b.h, d, b.attn, q, h, b.act, st));
     }
     BigEpi o_ep{BIG_ADD_F32, h, d, nullptr};
     BigEpi gu_ep{BIG_SWIGLU, nullptr, 0, (f16*)b.act};
@@ -1019,26 +1024,33 @@ static int rollout_impl(const sapo_weights* w, const int32_t* prompts, const int
     for (int p = 0; p < P; ++p) there += ragged ? lens_host[p] : Lp;
     // Prompts that end before Lp go without their padding, side by side (the fp32 q / k / v rows, which do not exist here, leave
     // their place to the rows' positions).
-    const bool packed = w->mfma && c.n_layers > 0 && M >= 1024 && there <= M - M / 16;
+    const bool packed = w->mfma && M >= 1024 && there <= M - M / 16;
     if (packed) {
       rm.packed = (const int2*)pl.fwd.qkv; rm.first = pl.first;
       HIP_CK(g_packed_prompts(pl.lens, P, G, pl.cache.page_table, pl.pages_per_seq, pl.first, (int2*)pl.fwd.qkv, st));
       HIP_CK(g_embed_packed(prompts, Lp, P, pl.first, w->embed, pl.fwd.h, d, st));
-      if ((rc = run_layers_big(w, pl.fwd, there, P, rm, pl.cache, nullptr, nullptr, st))) return rc;
     } else {
       HIP_CK(g_embed(dt, prompts, 1, nullptr, w->embed, pl.fwd.h, M, d, st));
-      if ((rc = run_layers(w, pl.fwd, M, rm, pl.cache, Lp, st))) return rc;
     }
+    // Of the last layer's output only the prompts' last rows are wanted.  us of a call of two tokens with all rows and with those, 0.5B:
+    // 33 positions 1976, 1988; 128 1866, 1872; 1024 2466, 2455; 16000 14112, 13736; 1.5B: 8192 23396, 22872.
+    const bool narrow = w->mfma && M >= 512 && can_narrow(c);
+    const WantedRows last{pl.last_rows, nullptr, P, pl.fwd.qkv};
+    if (narrow) HIP_CK(g_last_rows(pl.last_rows, P, Lp, ragged ? pl.lens : nullptr, packed ? pl.first : nullptr, st));
+    if (w->mfma) rc = run_layers_big(w, pl.fwd, packed ? there : M, P, rm, pl.cache, nullptr, narrow ? &last : nullptr, st);
+    else rc = run_layers_generic(w, pl.fwd, M, rm, pl.cache, Lp, st);
+    if (rc) return rc;
     if (ragged) {
       for (int l = 0; l < c.n_layers; ++l)
         HIP_CK(g_copy_partial_page_ragged(dt, layer_cache(w, pl.cache, l), P, G, pl.lens, st));
-      HIP_CK(g_gather_last_rows_ragged(pl.fwd.h, pl.h_last, S, G, Lp, pl.lens, packed ? pl.first : nullptr, d, st));
+      if (!narrow) HIP_CK(g_gather_last_rows_ragged(pl.fwd.h, pl.h_last, S, G, Lp, pl.lens, packed ? pl.first : nullptr, d, st));
     } else {
       if (Lp % kPageTokens != 0)
         for (int l = 0; l < c.n_layers; ++l)
           HIP_CK(g_copy_partial_page(dt, layer_cache(w, pl.cache, l), P, G, pl.full_prompt_pages, st));
-      HIP_CK(g_gather_last_rows(pl.fwd.h, pl.h_last, S, G, Lp, d, st));
+      if (!narrow) HIP_CK(g_gather_last_rows(pl.fwd.h, pl.h_last, S, G, Lp, d, st));
     }
+    if (narrow) HIP_CK(g_gather_last_rows(last.h, pl.h_last, S, G, 1, d, st));
     if (pl.fused_lm) HIP_CK(d_pack_rows_x16(pl.h_last, w->final_norm, S, d, pl.dec.xa, pl.dec.ssq_a, st));
     if ((rc = sample_step(w, pl, pl.level[0], pl.h_last, 1, sp, st))) return rc;
   }
@@ -1277,10 +1289,7 @@ static int score_chunk_seqs(const sapo_weights* w, int S, int T) {
 // a sixth of the row early on average (211 of 301 positions scored at most): 2709 3580, 2893; 1.5B 9740, 7584; a third of 768: 49152 42872, 32161.
 constexpr int kPackedRows = 2560;
 static bool score_packs_rows(const sapo_weights* w, int M) {
-  const sapo_model_config& c = w->cfg;
-  const int q = c.n_q_heads * c.head_dim;
-  // the scored rows' residual takes the place of the q / k / v rows, their attention output that of the FFN's activations
-  return w->mfma && c.n_layers > 0 && M >= kPackedRows && c.d_model <= q + 2 * c.n_kv_heads * c.head_dim && q <= c.d_ff;
+  return w->mfma && M >= kPackedRows && can_narrow(w->cfg);
 }
 
 static int check_score_args(const sapo_weights* w, int S, int T) {
@@ -1354,10 +1363,10 @@ static int score_impl(const sapo_weights* w, const int32_t* tokens, const uint8_
     const int ns = (S - s0 < pl.chunk_seqs) ? S - s0 : pl.chunk_seqs;
     const int M = ns * T;
     if (score_packs_rows(w, M)) {
-      // the fp32 q / k / v rows, which do not exist on this path, leave their place to the rows' positions and then to the scored rows
+      // (the rows' positions lie where the scored rows will)
       RowMap rm{0, T, 1, 0, nullptr, nullptr, 1};
       rm.packed = (const int2*)pl.fwd.qkv; rm.first = pl.first;
-      const ScoredRows scored{pl.src_rows, pl.count, pl.fwd.qkv};
+      const WantedRows scored{pl.src_rows, pl.count, M, pl.fwd.qkv};
       HIP_CK(g_packed_rows(completion_mask, T, s0, ns, pl.cache.page_table, pl.pages_per_seq, (int2*)pl.x, pl.first, (int2*)pl.fwd.qkv,
                            pl.rows, pl.src_rows, pl.count, st));
       HIP_CK(g_embed_packed(tokens + (size_t)s0 * T, T, ns, pl.first, w->embed, pl.fwd.h, c.d_model, st));

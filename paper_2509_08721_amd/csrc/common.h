@@ -390,7 +390,8 @@ hipError_t g_embed_packed(const int32_t* tokens, int T, int ns, const int* first
 hipError_t g_masked_rows(const uint8_t* mask, int T, int s0, int ns, int* rows /*[ns*T,2]*/, int* src_rows /*[ns*T]*/,
                          int* count, hipStream_t st);
 hipError_t g_rows_from_positions(const int* positions, int n, int T, int* src_rows, hipStream_t st);
-hipError_t g_last_rows(int* rows, int P, int Lp, hipStream_t st);
+// rows[p]: the row of prompt p's last position (lens, first: as in RowMap, or NULL)
+hipError_t g_last_rows(int* rows, int P, int Lp, const int* lens, const int* first, hipStream_t st);
 hipError_t g_gumbel(uint32_t seed_lo, uint32_t seed_hi, uint32_t seq, uint32_t step, uint32_t v0, int n, float* out,
                     hipStream_t st);
 
@@ -537,7 +538,7 @@ hipError_t m_rmsnorm_x32(const float* h, const float* gain, float eps, void* out
 hipError_t m_lmhead_score(const void* Xp, const void* Wp, int max_rows, const int* n_rows_dev, int V, int K,
                           const int* row_seq_pos, const int32_t* tokens, int T, float* partials, float* out_logprobs,
                           hipStream_t st);
-// rows src_rows[0 .. *n_rows - 1] (at most M) of a residual [., d] and of an operand in X32 order over q, side by side
+// rows src_rows[0 .. M - 1] (n_rows: *n_rows of them, at most M) of a residual [., d] and of an operand in X32 order over q, side by side
 hipError_t m_gather_rows_x32(const int* src_rows, const int* n_rows, int M, const float* h, int d, const void* x, int q, float* h_out,
                              void* x_out, hipStream_t st);
 size_t m_lmhead_score_partial_floats(int max_rows, int V);

@@ -1006,13 +1006,13 @@ hipError_t g_rows_from_positions(const int* positions, int n, int T, int* src_ro
   return launch(KID_MISC, k_rows_from_positions, dim3((n + 255) / 256), dim3(256), 0, st, positions, n, T, src_rows);
 }
 
-// rows[p] = index of the last prompt position of prompt p in a [P, Lp] block.
-__global__ void k_last_rows(int* rows, int P, int Lp) {
+// rows[p] = index of the last prompt position of prompt p in a [P, Lp] block, or among packed rows.
+__global__ void k_last_rows(int* rows, int P, int Lp, const int* __restrict__ lens, const int* __restrict__ first) {
   const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p < P) rows[p] = p * Lp + Lp - 1;
+  if (p < P) rows[p] = (first ? first[p] : p * Lp) + (lens ? lens[p] : Lp) - 1;
 }
-hipError_t g_last_rows(int* rows, int P, int Lp, hipStream_t st) {
-  return launch(KID_MISC, k_last_rows, dim3((P + 255) / 256), dim3(256), 0, st, rows, P, Lp);
+hipError_t g_last_rows(int* rows, int P, int Lp, const int* lens, const int* first, hipStream_t st) {
+  return launch(KID_MISC, k_last_rows, dim3((P + 255) / 256), dim3(256), 0, st, rows, P, Lp, lens, first);
 }
 
 // out[s, :] = h[(s / G) * Lp + Lp - 1, :]: the last prompt position's residual, once per sibling.

@@ -1105,7 +1105,7 @@ __global__ void __launch_bounds__(256) k_gather_rows_x32(const int* __restrict__
                                                          const float* __restrict__ h, int d, const uint4* __restrict__ x, int q,
                                                          float* __restrict__ h_out, uint4* __restrict__ x_out) {
   const int i = blockIdx.x;
-  if (i >= rows_there<true>(n_rows, gridDim.x)) return;
+  if (n_rows && i >= rows_there<true>(n_rows, gridDim.x)) return;
   const int r = src_rows[i];
   for (int k = threadIdx.x * 4; k < d; k += 1024) *(float4*)(h_out + (size_t)i * d + k) = *(const float4*)(h + (size_t)r * d + k);
   for (int k = threadIdx.x * 8; k < q; k += 2048) x_out[x32_chunk(i, k, q >> 4)] = x[x32_chunk(r, k, q >> 4)];

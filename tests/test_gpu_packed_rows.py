@@ -83,18 +83,19 @@ def test_scores_do_not_depend_on_what_the_workspace_holds(model):
     assert np.array_equal(a, b) and np.isfinite(a).all()
 
 
-# P prompts of up to Lp tokens, packed (P Lp >= 1024), against the same prompts two at a time (not packed)
-@pytest.mark.parametrize("P,Lp,G", [(9, 120, 4), (5, 257, 3), (40, 33, 1)])
-def test_rollouts_keep_their_bits_without_the_prompts_padding(model, P, Lp, G):
+# P prompts of up to Lp tokens, packed where they are shorter (P Lp >= 1024) and with the last layer for their last rows only
+# (P Lp >= 512), against the same prompts one at a time, which run neither
+@pytest.mark.parametrize("P,Lp,G,full", [(9, 120, 4, False), (5, 257, 3, False), (40, 33, 1, False), (5, 120, 2, True), (3, 257, 3, True),
+                                         (17, 31, 1, True), (33, 32, 1, True)])
+def test_rollouts_keep_their_bits_without_the_prompts_padding(model, P, Lp, G, full):
     shape, gw = model
     rng = np.random.default_rng(P * 100 + Lp)
-    lens = [int(x) for x in rng.integers(1, Lp + 1, size=P)]
-    lens[0], lens[1] = 1, Lp
+    lens = [Lp] * P if full else [1, Lp] + [int(x) for x in rng.integers(1, Lp + 1, size=P - 2)]
     prompts = torch.from_numpy(rng.integers(0, shape.vocab, size=(P, Lp)).astype(np.int32)).cuda()
-    assert P * Lp >= 1024 and sum(lens) <= P * Lp * 15 // 16
-    _, lp, _ = sapo.sapo_rollout_generate_ragged(gw, prompts, lens, G, 1, 0.0, 5)
-    for p in range(0, P, 2):
-        e = min(P, p + 2)
-        _, ref, _ = sapo.sapo_rollout_generate_ragged(gw, prompts[p:e].contiguous(), lens[p:e], G, 1, 0.0, 5)
-        # greedy, one token: the log-prob of the largest logit, from the prompt's last position
-        assert np.abs(lp[p * G:e * G].cpu().numpy() - ref.cpu().numpy()).max() <= 1e-5
+    assert P * Lp >= (512 if full else 1024) and Lp < 512 and (full or sum(lens) <= P * Lp * 15 // 16)
+    tok, lp, _ = sapo.sapo_rollout_generate_ragged(gw, prompts, lens, G, 3, 0.0, 5)
+    for p in range(P):
+        t, ref, _ = sapo.sapo_rollout_generate_ragged(gw, prompts[p:p + 1].contiguous(), lens[p:p + 1], G, 3, 0.0, 5)
+        # greedy tokens; log-probs up to the order in which the parts of a log-sum-exp of at most 1024 entries are merged
+        assert torch.equal(tok[p * G:(p + 1) * G], t)
+        assert np.abs(lp[p * G:(p + 1) * G].cpu().numpy() - ref.cpu().numpy()).max() <= 1e-5
