@@ -111,6 +111,12 @@ template <> __device__ __forceinline__ f16 from_f32<f16>(float x) { return (f16)
 // makes the guard a real branch.
 __device__ __forceinline__ int wave_index(int thread_index) { return __builtin_amdgcn_readfirstlane(thread_index >> 6); }
 
+// One value at an address that is the same for all lanes and that nothing writes while the kernel runs, through the scalar cache.
+// (The compiler takes the vector path, and its wait for everything asked for before, once the kernel has stores in sight.)
+__device__ __forceinline__ int load_uniform(const int* p) {
+  return *(const __attribute__((address_space(4))) int*)(unsigned long long)p;
+}
+
 // The values of lanes l and l ^ 16 (l ^ 32) combined in every lane, through gfx950's lane-swap instructions
 // (v_permlane16_swap / v_permlane32_swap: one vector-ALU instruction, no trip through LDS as the generic shuffle
 // takes).  Both lanes of a pair combine (lower lane's value, upper lane's value) in that order.
@@ -130,6 +136,10 @@ __device__ __forceinline__ float sum_xor16(float x) {
 __device__ __forceinline__ float sum_xor32(float x) {
   const lane_u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+// Lane q's value of every group of 4 lanes, in all four of them.
+template <int Q> __device__ __forceinline__ float dpp_quad(float x) {
+  return __uint_as_float(__builtin_amdgcn_mov_dpp(__float_as_uint(x), Q * 0x55, 0xf, 0xf, true));
 }
 
 __device__ __forceinline__ float wave_reduce_max(float v) {

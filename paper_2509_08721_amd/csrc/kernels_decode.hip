@@ -16,6 +16,8 @@
 // half(h * gain) in X16 order plus per-tile sums of squares of h, and the GEMM that consumes it
 // multiplies its accumulators by rsqrt(mean(h^2) + eps) (the scale is per token, so it commutes
 // with the contraction).
+#include <climits>
+
 #include "common.h"
 #include "coherent.h"
 
@@ -41,25 +43,27 @@ __device__ __forceinline__ float silu_f(float x) { return x / (1.0f + __expf(-x)
 
 // ---------------------------------------------------------------------------------------
 // Sum of the ssq parts of one token, spread over the 8 waves of a workgroup: thread (grp, tok)
-// loads parts grp, grp + 8, ... early (ssq_issue) and the sums meet in LDS later (ssq_finish).
+// loads parts grp, grp + 8, ... early (ssq_issue) and the sums meet in LDS later (ssq_publish, ssq_scale).
 // ---------------------------------------------------------------------------------------
 constexpr int kSsqPerThread = kMaxSsqParts / 8;
 
-// ssq is not null and parts >= 1.  Every thread asks for all kSsqPerThread values, a part past the end being the last
-// part again (dropped in ssq_publish): with a request under a branch each, the compiler waited for the first one on
-// the spot - a memory round trip in front of the kernel's weight requests.
+// ssq is not null and parts >= 1.  Every thread asks for all kSsqPerThread values, the bound of the buffer descriptor
+// answering for a part past the end with zero: with a request under a branch each, the compiler waited for the first
+// one on the spot - a memory round trip in front of the kernel's weight requests.
 __device__ __forceinline__ void ssq_issue(const float* __restrict__ ssq, int parts, int stride, int tok0,
                                           float (&sq)[kSsqPerThread]) {
-  const int tok = threadIdx.x & 63, grp = threadIdx.x >> 6;
+  const int tok = threadIdx.x & 63, grp = wave_index(threadIdx.x);
+  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void*)ssq, 0, parts * stride * 4, 0x00020000);
 #pragma unroll
-  for (int i = 0; i < kSsqPerThread; ++i) sq[i] = ssq[(size_t)min(grp + 8 * i, parts - 1) * stride + tok0 + tok];
+  for (int i = 0; i < kSsqPerThread; ++i)
+    sq[i] = __uint_as_float(
+        __builtin_amdgcn_raw_buffer_load_b32(r, (unsigned)((grp + 8 * i) * stride + tok0 + tok) * 4u, 0, 0));
 }
 // s_part: LDS [8][64].  Call before a __syncthreads(); ssq_scale() after it.
-__device__ __forceinline__ void ssq_publish(const float (&sq)[kSsqPerThread], int parts, float* s_part) {
-  const int grp = threadIdx.x >> 6;
+__device__ __forceinline__ void ssq_publish(const float (&sq)[kSsqPerThread], float* s_part) {
   float s = 0.f;
 #pragma unroll
-  for (int i = 0; i < kSsqPerThread; ++i) s += (grp + 8 * i < parts) ? sq[i] : 0.f;
+  for (int i = 0; i < kSsqPerThread; ++i) s += sq[i];
   s_part[threadIdx.x] = s;
 }
 __device__ __forceinline__ float ssq_scale(const float* s_part, int tok_local, int norm_dim, float eps) {
@@ -80,7 +84,7 @@ __device__ __forceinline__ void prefetch_behind(const SkinnyArgs& a, int first) 
 // ---------------------------------------------------------------------------------------
 // Skinny GEMM.  512 threads = 8 waves per workgroup.
 // A workgroup owns NT 16-feature tiles x TG 16-token groups over the whole K; wave w takes the
-// k steps w, w + 8, ... (R of them per round, all loads of a round in flight at once), and the
+// k steps w, w + 8, ... (the requests of R of them in flight), and the
 // 8 partial results are summed through LDS in wave order, so results never depend on timing.
 // Small per-workgroup operands matter more than the number of workgroups: a compute unit ingests
 // roughly 100 GB/s, so a 64-token block is split into 4 / TG workgroups per tile, which re-read
@@ -94,6 +98,13 @@ __device__ __forceinline__ void prefetch_behind(const SkinnyArgs& a, int first) 
 //   RESID_X32 (more than 64 rows): as RESID, but X32 order, and sums of squares over all tiles of the workgroup,
 //            infinite where some h * gain of theirs is beyond half's range and was clamped
 // ---------------------------------------------------------------------------------------
+// Bound of the operands' buffer descriptors: a lane offset with this bit set fetches nothing and arrives as zero.  A k step past the
+// end is asked for that way, not left out under a branch: the number of requests in flight is then the same on every path,
+// and a wave multiplies what has arrived instead of waiting, in front of its first product, for all of it.  The
+// registers of a step that has been multiplied take the request for the step R rounds on at once.  0.5B, us per step
+// of 32, 48 and 64 rows 619, 642, 665 -> 607, 621, 657; 128 and 256 rows 924, 1122 -> 919, 1111; 1.5B, 128 rows 1775 -> 1752.
+constexpr unsigned kSkinnyRecords = 0x40000000u;
+
 template <int NT, int TG, int TS, int R, int MODE>
 // The first arguments are passed one by one (and once more inside the struct): the hardware preloads the first 14 dwords
 // of a kernel's arguments into scalar registers when it starts a wave (-amdgpu-kernarg-preload-count), but not the
@@ -157,33 +168,37 @@ __global__ void __launch_bounds__(512) k_skinny16(const uint4* Wp_, const uint4*
     }
   }
 
-  const uint4* wbase = a.Wp + (size_t)tile0 * KS * 64 + lane;
-  const uint4* xbase = a.Xp + ((size_t)tb * KS * 4 + tg0) * 64 + lane;
-  for (int k0 = wave; k0 < KS; k0 += 8 * R) {
-    Frag16 wf[R][NT], xf[R][TG];
+  const __amdgpu_buffer_rsrc_t wr =
+      __builtin_amdgcn_make_buffer_rsrc((void*)(a.Wp + (size_t)tile0 * KS * 64), 0, kSkinnyRecords, 0x00020000);
+  const __amdgpu_buffer_rsrc_t xr =
+      __builtin_amdgcn_make_buffer_rsrc((void*)(a.Xp + ((size_t)tb * KS * 4 + tg0) * 64), 0, kSkinnyRecords, 0x00020000);
+  Frag16 wf[R][NT], xf[R][TG];
+  auto request = [&](int i, int ks) {
+    const unsigned off = lane * 16u | (ks < KS ? 0u : kSkinnyRecords);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) wf[i][t].n = __builtin_amdgcn_raw_buffer_load_b128(wr, off, (t * KS + ks) * 1024, 2);
+#pragma unroll
+    for (int g = 0; g < TG; ++g) xf[i][g].n = __builtin_amdgcn_raw_buffer_load_b128(xr, off + g * 1024u, ks * 4096, 0);
+  };
+  auto multiply = [&](int i) {
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int g = 0; g < TG; ++g) acc[t][g] = mfma16(wf[i][t], xf[i][g], acc[t][g]);
+  };
+#pragma unroll
+  for (int i = 0; i < R; ++i) request(i, wave + 8 * i);
+  if (!RESID) ssq_publish(sq, s_part);   // while the weights are on their way
+  int k0 = wave;
+  for (; k0 + 8 * R < KS; k0 += 8 * R) {
 #pragma unroll
     for (int i = 0; i < R; ++i) {
-      const int ks = k0 + 8 * i;
-      if (ks < KS) {
-#pragma unroll
-        for (int t = 0; t < NT; ++t)
-          wf[i][t].n = __builtin_nontemporal_load((const u32x4*)(wbase + ((size_t)t * KS + ks) * 64));
-#pragma unroll
-        for (int g = 0; g < TG; ++g) xf[i][g].u = xbase[(size_t)(ks * 4 + g) * 64];
-      }
-    }
-#pragma unroll
-    for (int i = 0; i < R; ++i) {
-      const int ks = k0 + 8 * i;
-      if (ks < KS) {
-#pragma unroll
-        for (int t = 0; t < NT; ++t)
-#pragma unroll
-          for (int g = 0; g < TG; ++g) acc[t][g] = mfma16(wf[i][t], xf[i][g], acc[t][g]);
-      }
+      multiply(i);
+      request(i, k0 + 8 * (R + i));
     }
   }
-  if (!RESID) ssq_publish(sq, a.ssq_parts, s_part);
+#pragma unroll
+  for (int i = 0; i < R; ++i) multiply(i);
   auto sum8 = [&](int tg, int l) -> float4 {   // tg = (t - chunk start) * TG + g
     float4 s = red[(size_t)tg * 64 + l];
 #pragma unroll
@@ -347,21 +362,48 @@ static hipError_t launch_pairs(const SkinnyArgs& a, int groups, hipStream_t st) 
 // gate/up pair of tiles, or FR = 16 or 8 of a tile's 16 features, and lanes whose row of either operand does not
 // exist are turned away by the buffer bounds instead of fetching.  0.5B decoder, one row: gate/up 9.8 -> 7.8 us, down
 // 7.8 -> 6.7 us per launch with the weights cold, 5.5 and 5.0 us when they were prefetched.
+// What follows the last product is a chain that nothing hides, so it is cut over four waves, one feature per thread (one wave with
+// four features per thread: 0.5 to 1 us of a launch whose weights lie in the L2), and the rows' sums of squares are
+// added up while the weights are on their way.  us per step, 0.5B, 1 and 16 rows 577, 590 -> 570, 578; 1.5B, 8 rows 1137 -> 1102.
 // ssq_out is left per group of 4 features ([tile][4][16 rows], in the same N / 16 x 64 floats): a tile's features may lie
 // in several workgroups.  The consumer adds the four in the order in which k_skinny16's producer adds them.
 // ---------------------------------------------------------------------------------------
-constexpr unsigned kFewRecords = 0x40000000u;   // bound of the buffer descriptors: a lane offset with this bit set fetches nothing
 
 // Sums of squares for at most 16 rows: thread (wave, lane) asks for parts wave, wave + 8, ...; lane = group of 4 features
-// x row.  parts == 1 (rows that come from an embedding gather): one value per row.
-__device__ __forceinline__ void ssq_publish_few(const float (&sq)[kSsqPerThread], int parts, float* s_part) {
-  const int grp = wave_index(threadIdx.x), lane = threadIdx.x & 63;
+// x row.  parts == 1 (rows that come from an embedding gather): one value per row.  What does not exist arrives as zero.
+__device__ __forceinline__ void ssq_issue_few(const float* __restrict__ ssq, int parts, float (&sq)[kSsqPerThread]) {
+  const int wave = wave_index(threadIdx.x), lane = threadIdx.x & 63;
+  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void*)ssq, 0, parts > 1 ? parts * 256 : 64, 0x00020000);
+#pragma unroll
+  for (int i = 0; i < kSsqPerThread; ++i)
+    sq[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, (unsigned)(wave + 8 * i) * 256u + lane * 4u, 0, 0));
+}
+// The four groups of a part are added as (0 + 1) + (2 + 3), then the wave's parts in their order: four parts at a time
+// come together in one register, lane group q holding the sum of part q, and go round to all lanes again.
+__device__ __forceinline__ void ssq_publish_few(const float (&sq)[kSsqPerThread], float* s_part) {
+  static_assert(kSsqPerThread % 4 == 0, "four parts at a time");
+  const auto swap16 = [](float a, float b, float& x, float& y) {   // odd rows of a against even rows of b
+    const lane_u32x2 r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    x = __uint_as_float(r[0]); y = __uint_as_float(r[1]);
+  };
+  const auto swap32 = [](float a, float b, float& x, float& y) {   // upper half of a against lower half of b
+    const lane_u32x2 r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    x = __uint_as_float(r[0]); y = __uint_as_float(r[1]);
+  };
   float s = 0.f;
 #pragma unroll
-  for (int i = 0; i < kSsqPerThread; ++i) {
-    float v = (parts > 1 || lane < 16) ? sq[i] : 0.f;
-    v = sum_xor32(sum_xor16(v));
-    s += (grp + 8 * i < parts) ? v : 0.f;
+  for (int i = 0; i < kSsqPerThread; i += 4) {
+    float x, y, p01, p23, v[4];
+    swap16(sq[i], sq[i + 1], x, y);
+    p01 = x + y;
+    swap16(sq[i + 2], sq[i + 3], x, y);
+    p23 = x + y;
+    swap32(p01, p23, x, y);
+    const float all = x + y;   // lane group q: part i + q
+    swap16(all, all, x, y);    // groups 0 0 2 2 and 1 1 3 3
+    swap32(x, x, v[0], v[2]);
+    swap32(y, y, v[1], v[3]);
+    s += v[0]; s += v[1]; s += v[2]; s += v[3];
   }
   s_part[threadIdx.x] = s;
 }
@@ -377,6 +419,7 @@ __global__ void __launch_bounds__(512) k_skinny_few(const uint4* Wp_, const uint
   static_assert(FR == 16 || (FR == 8 && MODE != SKM_SWIGLU), "whole tiles, or halves of them");
   constexpr int PT = 16 / FR;                       // workgroups per tile (SWIGLU: tile pair)
   constexpr int NA = MODE == SKM_SWIGLU ? 2 : 1;    // weight fragments per k step
+  constexpr int EW = FR / 4;                        // waves of the epilogue: one per 4 features
   __shared__ float4 red[8 * NA * 64];
   __shared__ float s_part[512];
   const int tid = threadIdx.x, wave = wave_index(tid), lane = tid & 63;
@@ -391,87 +434,80 @@ __global__ void __launch_bounds__(512) k_skinny_few(const uint4* Wp_, const uint
   }
   const int row = lane & 15, kg = lane >> 4;
   float sq[kSsqPerThread];
-  if (MODE != SKM_RESID) {
-#pragma unroll
-    for (int i = 0; i < kSsqPerThread; ++i) sq[i] = a.ssq_in[min(wave + 8 * i, a.ssq_parts - 1) * 64 + lane];
-  }
-  // epilogue coordinates of a lane of wave 0: row of the batch, first of its 4 features
-  const int tok = row, f0 = unit * 16 + part * FR + kg * 4;
-  const bool live = tok < a.n_rows && kg * 4 < FR;
-  float4 h_old = make_float4(0.f, 0.f, 0.f, 0.f), g_next = h_old;
-  if (MODE == SKM_RESID && wave == 0) {
-    // clamped, so that the requests sit under no lane mask
-    h_old = *(const float4*)(a.h + (size_t)min(tok, a.n_rows - 1) * a.N + min(f0, a.N - 4));
-    g_next = *(const float4*)(a.gain_next + min(f0, a.N - 4));
+  if (MODE != SKM_RESID) ssq_issue_few(a.ssq_in, a.ssq_parts, sq);
+  // epilogue coordinates of a thread of the first EW waves: row of the batch, its one feature; the 4 features of a group
+  // lie in neighbouring lanes
+  const int tok = lane >> 2, f = unit * 16 + part * FR + wave * 4 + (lane & 3);
+  const bool live = tok < a.n_rows;
+  float h_old = 0.f, g_next = 0.f;
+  if (MODE == SKM_RESID && wave < EW) {
+    h_old = a.h[(size_t)min(tok, a.n_rows - 1) * a.N + f];   // clamped, so that the request sits under no lane mask
+    g_next = a.gain_next[f];
   }
   unsigned woff[NA];
-  woff[0] = row < FR ? (unsigned)(kg * 16 + part * FR + row) * 16u : kFewRecords;
+  woff[0] = row < FR ? (unsigned)(kg * 16 + part * FR + row) * 16u : kSkinnyRecords;
   if (NA == 2) woff[NA - 1] = (unsigned)KS * 1024u + lane * 16u;   // the up tile lies behind its gate tile
-  const unsigned xoff = row < a.n_rows ? lane * 16u : kFewRecords;
+  const unsigned xoff = row < a.n_rows ? lane * 16u : kSkinnyRecords;
   const __amdgpu_buffer_rsrc_t wr = __builtin_amdgcn_make_buffer_rsrc(
-      (void*)(a.Wp + (size_t)unit * (MODE == SKM_SWIGLU ? 2 : 1) * KS * 64), 0, kFewRecords, 0x00020000);
-  const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc((void*)a.Xp, 0, kFewRecords, 0x00020000);
+      (void*)(a.Wp + (size_t)unit * (MODE == SKM_SWIGLU ? 2 : 1) * KS * 64), 0, kSkinnyRecords, 0x00020000);
+  const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc((void*)a.Xp, 0, kSkinnyRecords, 0x00020000);
   f32x4 acc[NA];
 #pragma unroll
   for (int t = 0; t < NA; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-  for (int k0 = wave; k0 < KS; k0 += 8 * R) {
-    Frag16 wf[R][NA], xf[R];
+  Frag16 wf[R][NA], xf[R];
+  auto request = [&](int i, int ks) {
+    const unsigned gone = ks < KS ? 0u : kSkinnyRecords;
+#pragma unroll
+    for (int t = 0; t < NA; ++t) wf[i][t].n = __builtin_amdgcn_raw_buffer_load_b128(wr, woff[t] | gone, ks * 1024, 2);
+    xf[i].n = __builtin_amdgcn_raw_buffer_load_b128(xr, xoff | gone, ks * 4096, 0);
+  };
+  auto multiply = [&](int i) {
+#pragma unroll
+    for (int t = 0; t < NA; ++t) acc[t] = mfma16(wf[i][t], xf[i], acc[t]);
+  };
+#pragma unroll
+  for (int i = 0; i < R; ++i) request(i, wave + 8 * i);
+  float bias = 0.f;
+  if (MODE == SKM_STORE && a.bias && wave < EW) bias = a.bias[f];
+  if (MODE != SKM_RESID) ssq_publish_few(sq, s_part);   // requested first, here first
+  __builtin_amdgcn_sched_barrier(0);   // nothing that waits for the weights moves up
+  int k0 = wave;
+  for (; k0 + 8 * R < KS; k0 += 8 * R) {
 #pragma unroll
     for (int i = 0; i < R; ++i) {
-      // a k step past the end: the last one's weights again, against tokens that are not fetched (zero)
-      const int ks = min(k0 + 8 * i, KS - 1);
-#pragma unroll
-      for (int t = 0; t < NA; ++t) wf[i][t].n = __builtin_amdgcn_raw_buffer_load_b128(wr, woff[t], ks * 1024, 2);
-      xf[i].n = __builtin_amdgcn_raw_buffer_load_b128(xr, xoff | (k0 + 8 * i < KS ? 0u : kFewRecords), ks * 4096, 0);
+      multiply(i);
+      request(i, k0 + 8 * (R + i));
     }
-#pragma unroll
-    for (int i = 0; i < R; ++i)
-#pragma unroll
-      for (int t = 0; t < NA; ++t) acc[t] = mfma16(wf[i][t], xf[i], acc[t]);
   }
 #pragma unroll
-  for (int t = 0; t < NA; ++t) red[(wave * NA + t) * 64 + lane] = make_float4(acc[t][0], acc[t][1], acc[t][2], acc[t][3]);
-  if (MODE != SKM_RESID) ssq_publish_few(sq, a.ssq_parts, s_part);
-  __syncthreads();
-  if (wave != 0) return;
-  auto sum8 = [&](int t, int l) -> float4 {
-    float4 s = red[t * 64 + l];
+  for (int i = 0; i < R; ++i) multiply(i);
 #pragma unroll
-    for (int w = 1; w < 8; ++w) {
-      const float4 p = red[(w * NA + t) * 64 + l];
-      s.x += p.x; s.y += p.y; s.z += p.z; s.w += p.w;
-    }
+  for (int t = 0; t < NA; ++t) red[(wave * NA + t) * 64 + lane] = make_float4(acc[t][0], acc[t][1], acc[t][2], acc[t][3]);
+  __syncthreads();
+  if (wave >= EW) return;
+  auto sum8 = [&](int t) -> float {
+    const float* r = (const float*)red + t * 256 + tid;
+    float s = r[0];
+#pragma unroll
+    for (int w = 1; w < 8; ++w) s += r[w * NA * 256];
     return s;
   };
-  float4 s = sum8(0, lane);
+  float s = sum8(0);
   if (MODE == SKM_SWIGLU) {
-    const float4 us = sum8(NA - 1, lane);
-    const float sc = ssq_scale(s_part, tok, a.norm_dim, a.eps);
-    if (live) {
-      f16x4 o;
-      o[0] = from_f32<f16>(silu_f(s.x * sc) * (us.x * sc)); o[1] = from_f32<f16>(silu_f(s.y * sc) * (us.y * sc));
-      o[2] = from_f32<f16>(silu_f(s.z * sc) * (us.z * sc)); o[3] = from_f32<f16>(silu_f(s.w * sc) * (us.w * sc));
-      *(f16x4*)((f16*)a.xp_out + x16_chunk(tok, f0, a.N >> 6) * 8 + (f0 & 4)) = o;
-    }
+    const float us = sum8(NA - 1), sc = ssq_scale(s_part, tok, a.norm_dim, a.eps);
+    if (live) ((f16*)a.xp_out)[x16_chunk(tok, f, a.N >> 6) * 8 + (f & 7)] = from_f32<f16>(silu_f(s * sc) * (us * sc));
   } else if (MODE == SKM_STORE) {
-    const float sc = ssq_scale(s_part, tok, a.norm_dim, a.eps);
-    if (live) {
-      float4 o = make_float4(s.x * sc, s.y * sc, s.z * sc, s.w * sc);
-      if (a.bias) {
-        const float4 bb = *(const float4*)(a.bias + f0);
-        o.x += bb.x; o.y += bb.y; o.z += bb.z; o.w += bb.w;
-      }
-      *(float4*)(a.out_f32 + (size_t)tok * a.ldc + f0) = o;
-    }
+#pragma clang fp contract(off)   // rounded before the bias is added, as with more rows
+    float o = s * ssq_scale(s_part, tok, a.norm_dim, a.eps);
+    if (a.bias) o += bias;
+    if (live) a.out_f32[(size_t)tok * a.ldc + f] = o;
   } else {
-    s.x += h_old.x; s.y += h_old.y; s.z += h_old.z; s.w += h_old.w;
-    f16x4 o;
-    o[0] = from_f32<f16>(s.x * g_next.x); o[1] = from_f32<f16>(s.y * g_next.y);
-    o[2] = from_f32<f16>(s.z * g_next.z); o[3] = from_f32<f16>(s.w * g_next.w);
+    s += h_old;
+    const float4 all = make_float4(dpp_quad<0>(s), dpp_quad<1>(s), dpp_quad<2>(s), dpp_quad<3>(s));
     if (live) {
-      *(float4*)(a.h + (size_t)tok * a.N + f0) = s;
-      *(f16x4*)((f16*)a.xp_out + x16_chunk(tok, f0, a.N >> 5) * 8 + (f0 & 4)) = o;
-      a.ssq_out[unit * 64 + (part * (FR / 4) + kg) * 16 + tok] = sum_squares4(s);
+      a.h[(size_t)tok * a.N + f] = s;
+      ((f16*)a.xp_out)[x16_chunk(tok, f, a.N >> 5) * 8 + (f & 7)] = from_f32<f16>(s * g_next);
+      if ((lane & 3) == 0) a.ssq_out[unit * 64 + (part * EW + wave) * 16 + tok] = sum_squares4(all);
     }
   }
 }
@@ -702,7 +738,8 @@ __global__ void __launch_bounds__(512) k_lmhead_sample16(const uint4* __restrict
     for (int i = 0; i < U; ++i) cur[i].n = __builtin_nontemporal_load((const u32x4*)(wb + (size_t)i * 64));
   }
   float sq[kSsqPerThread];
-  ssq_issue(ssq, ssq_parts, s_pad, 0, sq);
+  if (ssq_quarters) ssq_issue_few(ssq, ssq_parts, sq);
+  else ssq_issue(ssq, ssq_parts, s_pad, 0, sq);
   // the sampling parameters too (behind the copy below they would be read through the vector path, one more round trip)
   resolve_sample_params(sp);
   const int step = *sp.step;
@@ -719,8 +756,8 @@ __global__ void __launch_bounds__(512) k_lmhead_sample16(const uint4* __restrict
     const unsigned xs0 = __builtin_amdgcn_readfirstlane(lds_addr16(xs));
     for (int b = wave * 64; b < KS * 256; b += 512) dma16_lds(Xp + b + lane, xs0 + (unsigned)b * 16u);
   }
-  if (ssq_quarters) ssq_publish_few(sq, ssq_parts, s_part);
-  else ssq_publish(sq, ssq_parts, s_part);
+  if (ssq_quarters) ssq_publish_few(sq, s_part);
+  else ssq_publish(sq, s_part);
   wait_vmcnt_d<0>();   // this wave's blocks of the operand have landed ...
   __syncthreads();     // ... and everybody's
   if (tid < 64) s_scale[tid] = ssq_scale(s_part, tid, norm_dim, eps);
@@ -1103,10 +1140,15 @@ __global__ void __launch_bounds__(NW * 64) k_decode_attention16(const float* __r
     if ((int)blockIdx.x >= first) prefetch_role<NW>(pf, blockIdx.x - first, (int)gridDim.x - first);
     return;
   }
-  // what leads from the start of the kernel to its first requests arrives preloaded (see k_skinny16): 14 dwords
-  rm.step = step_; rm.Lp = lp_pages_ & 0xffff;
+  // What leads from the start of the kernel to its first requests arrives preloaded (see k_skinny16): 14 dwords.  What they point
+  // to - step counter, page table - is read through the scalar cache, all at once: behind one another and through the
+  // vector path, where the wait for the counter held the row's own values back as well, these reads were 1 us of a
+  // launch at any context.  us per step, with the last pair's handling below: 0.5B, 64 rows, contexts of 150 663 -> 648,
+  // 1 row, 1060 716 -> 682; 1.5B, 1 row, 160 1080 -> 1037.
+  const int step = load_uniform(step_);
   kv.page_table = page_table_; kv.pages_per_seq = lp_pages_ >> 16; kv.n_kv_heads = heads_ & 0xffff; kv.k = kpool_;
-  const int n_q_heads = ((heads_ >> 16) & 0xff) * kv.n_kv_heads;
+  const int rep = (heads_ >> 16) & 0xff, n_q_heads = rep * kv.n_kv_heads;
+  const int per_rep = (65536 + rep - 1) / rep;
   constexpr int KK = HD / 32;   // k steps of S^T = K Q^T
   constexpr int DT = HD / 16;   // 16-row tiles of O^T
   constexpr int NFRAG = 2 * KK + DT;                        // 1 KiB fragments of one page pair
@@ -1119,13 +1161,14 @@ __global__ void __launch_bounds__(NW * 64) k_decode_attention16(const float* __r
   if constexpr (SHARE) {
     static_assert(!LDS, "the shared-prompt variant reads K/V register-direct");
     if ((int)blockIdx.x < sh.n_prefix) {   // uniform over the workgroup
+      rm.step = step_; rm.Lp = lp_pages_ & 0xffff;
       attention_prefix_role<HD, NW>(qkv, rope, rm, kv, n_q_heads, sh, sm_o, (f16*)(sm_o + (size_t)NW * HD * 16), sm_m, sm_l);
       return;
     }
   }
   const int tid = threadIdx.x, wave = wave_index(tid), lane = tid & 63;
   const int qcol = lane & 15, grp = lane >> 4;
-  const int hkv = kv.n_kv_heads, rep = n_q_heads / hkv;
+  const int hkv = kv.n_kv_heads;
   // Siblings read the same prompt pages: the rows of a group (consecutive rows, one KV head) run on one XCD, whose L2 fetches
   // them once.  Block ids are dealt round-robin to the XCDs.
   int s, kvh;
@@ -1133,15 +1176,30 @@ __global__ void __launch_bounds__(NW * 64) k_decode_attention16(const float* __r
     const int bid = (int)blockIdx.x - sh.n_prefix;
     s = bid / hkv; kvh = bid % hkv;
   } else {
-    const int group_log2 = heads_ >> 24, j = (int)blockIdx.x >> 3, g = (j >> group_log2) * 8 + ((int)blockIdx.x & 7), p = g / hkv;
+    const int group_log2 = (heads_ >> 24) & 7, j = (int)blockIdx.x >> 3, g = (j >> group_log2) * 8 + ((int)blockIdx.x & 7), p = g / hkv;
     s = (p << group_log2) + (j & ((1 << group_log2) - 1)); kvh = g - p * hkv;
     if (s >= rows_) return;
   }
   const int pp0 = SHARE ? sh.prefix_pairs : 0;   // first page pair this workgroup covers
-  int seq, pos;
-  rm.get(s, seq, pos);
-  const int ctx = pos + 1;
+  // The row's sequence and prompt length.  Rows that are the sequences in order, all with one prompt length, are marked by the
+  // sign bit: the other arguments, a load each before what they point to can be asked for, are not touched for them.
+  int seq = s, pos = (lp_pages_ & 0xffff) + step - 1;
+  if (heads_ >= 0) {
+    if (rm.slot_seq) seq = load_uniform(rm.slot_seq + s);
+    if (rm.lens) pos = load_uniform(rm.lens + seq / rm.G) + step - 1;
+  }
   const int* pt = kv.page_table + (size_t)seq * kv.pages_per_seq;
+  // Entries of the wave's first pairs, asked for beside the step counter: clamped to the sequence's entries instead of its pages,
+  // which the counter decides.  A pair that does not exist is not requested below.
+  int first_pa[PD], first_pb[PD];
+#pragma unroll
+  for (int j = 0; j < PD; ++j) {
+    const int e = 2 * (pp0 + wave + NW * j);
+    first_pa[j] = load_uniform(pt + min(e, kv.pages_per_seq - 1));
+    first_pb[j] = load_uniform(pt + min(e + 1, kv.pages_per_seq - 1));
+  }
+  const int new_page = load_uniform(pt + pos / kPageTokens), new_slot = pos % kPageTokens;
+  const int ctx = pos + 1;
   f16* kpool = (f16*)kv.k;
   f16* vpool = (f16*)kv.v;
   const size_t page_elems = (size_t)hkv * kPageTokens * HD;
@@ -1162,7 +1220,7 @@ __global__ void __launch_bounds__(NW * 64) k_decode_attention16(const float* __r
     for (int dt = 0; dt < DT; ++dt) vf[dt].u = *(const uint4*)(vp + v_frag_at(dt, lane));
   };
   auto load_pair = [&](int pp, Frag16 (&kf)[2][KK], Frag16 (&vf)[DT]) {
-    load_pages(pt[2 * pp], pt[min(2 * pp + 1, last_page)], kf, vf);
+    load_pages(load_uniform(pt + 2 * pp), load_uniform(pt + min(2 * pp + 1, last_page)), kf, vf);
   };
   // the same requests into slot j of this wave's staging area
   const unsigned stage0 = LDS ? __builtin_amdgcn_readfirstlane(lds_addr16(sm_o) + (unsigned)wave * PD * NFRAG * 1024u) : 0u;
@@ -1178,7 +1236,7 @@ __global__ void __launch_bounds__(NW * 64) k_decode_attention16(const float* __r
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt) dma16_lds(vp + v_frag_at(dt, lane), dst + (unsigned)(2 * KK + dt) * 1024u);
   };
-  auto stage_pair = [&](int pp, int j) { stage_pages(pt[2 * pp], pt[min(2 * pp + 1, last_page)], j); };
+  auto stage_pair = [&](int pp, int j) { stage_pages(load_uniform(pt + 2 * pp), load_uniform(pt + min(2 * pp + 1, last_page)), j); };
   auto read_pair = [&](int j, Frag16 (&kf)[2][KK], Frag16 (&vf)[DT]) {
     const uint4* src = (const uint4*)sm_o + ((size_t)(wave * PD + j) * NFRAG) * 64 + lane;
 #pragma unroll
@@ -1195,7 +1253,6 @@ __global__ void __launch_bounds__(NW * 64) k_decode_attention16(const float* __r
   constexpr int NQ = 16 * half / (NW * 64);   // query elements per thread
   static_assert(NQ * NW * 64 == 16 * half && half <= NW * 64 && HD <= NW * 64, "whole passes over the 16 query rows");
   const float* row = qkv + (size_t)s * (n_q_heads + 2 * hkv) * HD;
-  const int new_page = pt[pos / kPageTokens], new_slot = pos % kPageTokens;
   // every thread asks (clamped to a valid row or element) so that nothing here sits under a branch
   float qx1[NQ], qx2[NQ];
   float2 qcs[NQ];
@@ -1222,19 +1279,14 @@ __global__ void __launch_bounds__(NW * 64) k_decode_attention16(const float* __r
   // copy the compiler knows how many requests stand behind the row's own values and waits for those alone, while
   // the pages are still on their way.  (Requests under a branch each would leave it a wait for everything; asking
   // for a page again in place of a missing pair costs more than it saves: a compute unit's ingest is the bound.)
-  int first_pa[PD], first_pb[PD];   // looked up here (a missing pair: the last one's entries, unused) rather than in the copies
-#pragma unroll
-  for (int j = 0; j < PD; ++j) {
-    const int pp = min(pp0 + wave + NW * j, npairs - 1);
-    first_pa[j] = pt[2 * pp];
-    first_pb[j] = pt[min(2 * pp + 1, last_page)];
-  }
   auto first_pairs_and_rotary = [&](auto n_c) {
     constexpr int n_req = decltype(n_c)::value;
 #pragma unroll
     for (int j = 0; j < n_req; ++j) {
-      if constexpr (LDS) stage_pages(first_pa[j], first_pb[j], j);
-      else load_pages(first_pa[j], first_pb[j], kf[j], vf[j]);
+      // a last pair of one page: that page for both
+      const int pa = first_pa[j], pb = 2 * (pp0 + wave + NW * j) < last_page ? first_pb[j] : pa;
+      if constexpr (LDS) stage_pages(pa, pb, j);
+      else load_pages(pa, pb, kf[j], vf[j]);
     }
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -1302,20 +1354,38 @@ __global__ void __launch_bounds__(NW * 64) k_decode_attention16(const float* __r
         asm volatile("" ::: "memory");
         read_pair(jj, kf[0], vf[0]);
       }
-      // the token appended by this workgroup comes from LDS, not from the global copy written above
+      // The pair with the token that this workgroup appends, which comes from LDS and not from the global copy written above.
+      // Tokens past it may hold anything in V (even NaN bit patterns): zero.  Both on whole dwords under masks - as
+      // 16-bit elements under a running index this was 150 instructions of the wave that ends last.
       if (pp == pos / 32) {
+        const int at = pos & 31;
+        uint4 kn[KK];
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) kn[kk] = *(const uint4*)(knew + kk * 32 + grp * 8);
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
           const int r = lane & 15;
-          const int ptok = 8 * (r >> 2) + 4 * t + (r & 3);
-          if (ptok == pos % 32) {
+          const bool mine = 8 * (r >> 2) + 4 * t + (r & 3) == at;
 #pragma unroll
-            for (int kk = 0; kk < KK; ++kk) kf[j][t][kk].u = *(const uint4*)(knew + kk * 32 + grp * 8);
+          for (int kk = 0; kk < KK; ++kk) {
+            kf[j][t][kk].u.x = mine ? kn[kk].x : kf[j][t][kk].u.x;
+            kf[j][t][kk].u.y = mine ? kn[kk].y : kf[j][t][kk].u.y;
+            kf[j][t][kk].u.z = mine ? kn[kk].z : kf[j][t][kk].u.z;
+            kf[j][t][kk].u.w = mine ? kn[kk].w : kf[j][t][kk].u.w;
           }
         }
-        if (grp == (pos % 32) / 8) {
+        unsigned keep[4], put[4];   // of the lane's tokens 8 grp + 2 d, + 1: those before the new one, and it
 #pragma unroll
-          for (int dt = 0; dt < DT; ++dt) vf[j][dt].h[pos % 8] = vnew[dt * 16 + (lane & 15)];
+        for (int d = 0; d < 4; ++d) {
+          const int n = at - (8 * grp + 2 * d);
+          keep[d] = n >= 2 ? 0xffffffffu : n == 1 ? 0x0000ffffu : 0u;
+          put[d] = n == 1 ? 0xffff0000u : n == 0 ? 0x0000ffffu : 0u;
+        }
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) {
+          const unsigned v = ((const unsigned short*)vnew)[dt * 16 + (lane & 15)], vv = v | v << 16;
+#pragma unroll
+          for (int d = 0; d < 4; ++d) vf[j][dt].n[d] = (vf[j][dt].n[d] & keep[d]) | (vv & put[d]);
         }
       }
       f32x4 sc[2];
@@ -1349,17 +1419,6 @@ __global__ void __launch_bounds__(NW * 64) k_decode_attention16(const float* __r
       }
       l_run = l_run * alpha + psum;
       m_run = m_new;
-      // tokens past the context may hold anything in V (even NaN bit patterns): zero them
-      {
-        const int nvalid = ctx - (pp * 32 + 8 * grp);   // lane's 8 tokens: first nvalid are real
-        if (nvalid < 8) {
-#pragma unroll
-          for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-              if (e >= nvalid) vf[j][dt].h[e] = (f16)0.f;
-        }
-      }
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt) {
 #pragma unroll
@@ -1380,7 +1439,7 @@ __global__ void __launch_bounds__(NW * 64) k_decode_attention16(const float* __r
     // wall clock, until its flag shows this launch's number; a wait that gives up sets the fault word, which makes the
     // sampler emit -1 for the step
     if (tid == 0) {
-      const unsigned launch_no = (unsigned)(*rm.step) * (unsigned)sh.n_layers + (unsigned)sh.layer + 1u;
+      const unsigned launch_no = (unsigned)step * (unsigned)sh.n_layers + (unsigned)sh.layer + 1u;
       const unsigned* flag = sh.flags + (size_t)(s / sh.G) * hkv + kvh;
       const unsigned long long t0 = wall_clock64();
       while ((int)(__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - launch_no) < 0) {
@@ -1398,8 +1457,9 @@ __global__ void __launch_bounds__(NW * 64) k_decode_attention16(const float* __r
   // whole merge, 80 dependent LDS reads each: 0.8 us at the end of a 4.5 us kernel.  Waves that had no page pair
   // carry (m = -inf, l = 0, o = 0) and drop out of the merge.
   const int KSo = (n_q_heads * HD) >> 5;
+  static_assert(16 * HD * 16 < 65536, "idx / rep by a multiplication: idx times the remainder of 65536 stays below 65536");
   for (int idx = tid; idx < rep * HD; idx += NW * 64) {
-    const int q = idx % rep, d = idx / rep;
+    const int d = idx * per_rep >> 16, q = idx - d * rep;
     float mx = -INFINITY;
 #pragma unroll
     for (int w = 0; w < NW; ++w) mx = fmaxf(mx, sm_m[w][q]);
@@ -1450,11 +1510,12 @@ static hipError_t launch_decode_attention(const float* qkv, const float2* rope, 
   if (kv.n_kv_heads > 0xffff || n_q_heads / kv.n_kv_heads > 16 || rm.Lp > 0xffff || kv.pages_per_seq > 0x7fff) return hipErrorInvalidValue;
   return launch(SHARE ? KID_DECODE_ATTN_SHARED : KID_DECODE_ATTN, k_decode_attention16<HD, NW, PD, LDS, SHARE>, dim3(blocks),
                 dim3(NW * 64), smem, st, qkv, rope, rm.step, kv.page_table, rm.Lp | (kv.pages_per_seq << 16), S,
-                kv.n_kv_heads | (n_q_heads / kv.n_kv_heads << 16) | (group_log2 << 24), n_main, kv.k, rm, kv, (uint4*)out, sh, pf);
+                kv.n_kv_heads | (n_q_heads / kv.n_kv_heads << 16) | (group_log2 << 24) | (rm.slot_seq || rm.lens ? 0 : INT_MIN), n_main, kv.k, rm, kv, (uint4*)out, sh, pf);
 }
 
 hipError_t d_decode_attention(const float* qkv, const float2* rope, RowMap rm, KVCache kv, void* out, int S, int n_q_heads,
                               const ShareArgs* share, const Prefetch& pf, hipStream_t st) {
+  if (!rm.decode) return hipErrorInvalidValue;
   if (share && share->prefix_pairs > 0) {
     // what the two-role launch assumes: rows are P x G sequences in order, all at one position, with their own
     // page-table rows; the columns of all siblings fit the prefix workgroup's four MFMA tiles
