@@ -422,16 +422,22 @@ struct Prefetch {
   const uint4* p = nullptr;
   int KS = 0, n_tiles = 0, nt_log2 = 0, ks1 = 0;   // ks1 = 0: nothing
 };
-constexpr int kPrefetchKb = 18;   // blocks of 1 KiB that a prefetching wave has in flight
-// In the gate/up launch of at most 16 rows half of that: its own workgroups take in 57 KB, and one that prefetched 144 KB was
-// the last to end.  us per step with 18 and 9, 0.5B: 1 row 588, 570; 16 rows 602, 585; 1.5B: 1126, 1110; 1196, 1167.  With 12 or 7
-// within 3 of 9.  Elsewhere 18: gate/up of 32 rows 614, 621; attention 1 row 588, 606 (its few workgroups' dependent loads wait
-// longer behind more requests); down 64 rows 658, 677.
-constexpr int kPrefetchKbFew = 9;
+constexpr int kPrefetchKb = 28;       // blocks of 1 KiB per prefetching wave: at most (36 instead of 28 us per step + 5 to 32) ...
+constexpr int kPrefetchKbFew = 6;     // ... beside gate/up of at most 16 rows ...
+constexpr int kPrefetchKbRows = 18;   // ... and beside down of more than 64
 // workgroups of `waves` waves for it, a multiple of 8
-inline int prefetch_blocks(const Prefetch& pf, int waves, int per_wave = kPrefetchKb) {
+inline int prefetch_blocks(const Prefetch& pf, int waves, int per_wave) {
   const long kb = (long)pf.ks1 * pf.n_tiles;
   return (int)((kb + waves * per_wave - 1) / (waves * per_wave) + 7) / 8 * 8;
+}
+// Blocks per wave, from `lo` up, with which the workgroups of both fit into `room` compute units; none of them: otherwise.
+// A launch's own workgroups and the prefetching ones belong on a compute unit each: one workgroup too many and two of them share
+// one, the launch's own among them (us per step of a decode at the two sides of that line, attention launch: 0.5B, 64 rows, 248 and
+// 264 workgroups 656, 691; 1.5B, 16 rows, 240 and 264 1098, 1173; 1.5B, 64 rows, 256 and 272 1619, 1678).
+inline int prefetch_per_wave(const Prefetch& pf, const Prefetch& pf2, int waves, int room, int lo, int otherwise) {
+  for (int per = lo; per <= kPrefetchKb; ++per)
+    if (prefetch_blocks(pf, waves, per) + prefetch_blocks(pf2, waves, per) <= room) return per;
+  return otherwise;
 }
 // All of a weight matrix, or the leading blocks of every tile where it is more than the L2s hold next to everything else
 // (32 MB: 1.5B gate/up, 55 MB, of which half: 73.9 ms per call of 64 rows against 76.6 with all and 74.6 with none).
@@ -443,7 +449,6 @@ inline Prefetch make_prefetch(const void* w, int KS, int n_tiles, int nt_log2) {
   pf.ks1 = kb <= cap_kb ? KS : (int)(KS * cap_kb / kb);
   return pf;
 }
-typedef unsigned int prefetch_u32x4 __attribute__((ext_vector_type(4)));
 // ---------------------------------------------------------------------------------------
 // Prefetch workgroup: workgroups behind a launch's own that bring weights of a later launch into the L2s.
 // A decode step is a chain of short launches, and the launches that stream (gate/up 17 MB, down 9 MB on the 0.5B
@@ -452,32 +457,24 @@ typedef unsigned int prefetch_u32x4 __attribute__((ext_vector_type(4)));
 // whose workgroups will read the weights (block ids are dealt round-robin): XCD x prefetches the tiles of the units
 // x, x + 8, ... of the consumer.  0.5B, 64 rows: gate/up 8.8 -> 6.8 us, down 7.4 -> 6.3, attention (which carries
 // gate/up's 17 MB on the compute units it leaves idle) 5.8 -> 7.0; on the wrong XCD the gain is lost.
-// A wave asks for KB blocks of 1 KiB at once and waits for them once: with 8 in flight and several rounds the
-// launch that carries them got longer by what the consumer gained.
+// A wave asks for all of its blocks of 1 KiB at once and waits for them once: with 8 in flight and several rounds the
+// launch that carries them got longer by what the consumer gained.  How many that are is the launch's to choose.  They go
+// to LDS, all to the same KiB, which nobody reads: as register loads (18 or 28 of them unrolled) the role was most of a
+// launch's code and up to half of its registers.  us per step, 0.5B, 24, 48 and 64 rows: 595, 613, 649 -> 591, 602, 640.
 // ---------------------------------------------------------------------------------------
-template <int NW, int KB = kPrefetchKb>   // waves of a workgroup
-__device__ __forceinline__ void prefetch_role(const Prefetch& pf, int block, int n_blocks) {
+template <int NW>   // waves of a workgroup
+__device__ __forceinline__ void prefetch_role(const Prefetch& pf, int block, int n_blocks, void* lds_1k) {   // lds_1k: 1 KiB of LDS
   const int xcd = block & 7, wv = (block >> 3) * NW + wave_index(threadIdx.x), nw = (n_blocks >> 3) * NW;   // waves per XCD
   const uint4* base = pf.p + (threadIdx.x & 63);
-  prefetch_u32x4 all = {0, 0, 0, 0};
   const int n_units = pf.n_tiles >> pf.nt_log2, mine = ((n_units - xcd + 7) >> 3) << pf.nt_log2;   // tiles of this XCD
   const int span = pf.ks1, total = mine * span, nt1 = (1 << pf.nt_log2) - 1;
-  for (int k = wv; k < total; k += nw * KB) {
-    prefetch_u32x4 v[KB];
-#pragma unroll
-    for (int r = 0; r < KB; ++r) {
-      const int kk = k + r * nw;
-      if (kk < total) {
-        const int m = kk / span, tile = ((((m >> pf.nt_log2) << 3) + xcd) << pf.nt_log2) + (m & nt1);
-        v[r] = *(const prefetch_u32x4*)(base + ((size_t)tile * pf.KS + (kk - m * span)) * 64);
-      } else {
-        v[r] = prefetch_u32x4{0, 0, 0, 0};
-      }
-    }
-#pragma unroll
-    for (int r = 0; r < KB; ++r) all |= v[r];
+  for (int k = wv; k < total; k += nw) {
+    const int m = k / span, tile = ((((m >> pf.nt_log2) << 3) + xcd) << pf.nt_log2) + (m & nt1);
+    const uint4* p = base + ((size_t)tile * pf.KS + (k - m * span)) * 64;
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)p,
+                                     (__attribute__((address_space(3))) void*)lds_1k, 16, 0, 0);
   }
-  asm volatile("" ::"v"(all));   // the loads are wanted for what they leave behind
+  __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): the workgroup's LDS is given back when its waves have ended
 }
 
 // uint4 index of the chunk that holds x[tok][k .. k+7] (k a multiple of 8) in X16 order.

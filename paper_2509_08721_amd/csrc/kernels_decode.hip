@@ -73,12 +73,11 @@ __device__ __forceinline__ float ssq_scale(const float* s_part, int tok_local, i
   return 1.0f / sqrtf(s / (float)norm_dim + eps);
 }
 
-template <int KB = kPrefetchKb>
-__device__ __forceinline__ void prefetch_behind(const SkinnyArgs& a, int first) {
+__device__ __forceinline__ void prefetch_behind(const SkinnyArgs& a, int first, void* lds_1k) {
   const int block = (int)blockIdx.x - first;
   if (block < 0) return;
-  if (block < a.pf_blocks) prefetch_role<8, KB>(a.pf, block, a.pf_blocks);
-  else prefetch_role<8, KB>(a.pf2, block - a.pf_blocks, (int)gridDim.x - first - a.pf_blocks);
+  if (block < a.pf_blocks) prefetch_role<8>(a.pf, block, a.pf_blocks, lds_1k);
+  else prefetch_role<8>(a.pf2, block - a.pf_blocks, (int)gridDim.x - first - a.pf_blocks, lds_1k);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -137,7 +136,7 @@ __global__ void __launch_bounds__(512) k_skinny16(const uint4* Wp_, const uint4*
   const int tg0 = (inner % TS) * TG;
   if (unit >= n_units) {
     const int first = (n_units + 7) / 8 * 8 * TS * nblk;
-    prefetch_behind(a_rest, first);
+    prefetch_behind(a_rest, first, red);
     return;
   }
   const int tile0 = unit * NT;
@@ -314,7 +313,6 @@ __global__ void __launch_bounds__(512) k_skinny16(const uint4* Wp_, const uint4*
 // TS: workgroups per (tile unit, token block); TG x TS covers the token groups of a block
 template <int NT, int TG, int TS, int R, int MODE>
 static hipError_t launch_skinny(SkinnyArgs a, hipStream_t st) {
-  a.pf_blocks = prefetch_blocks(a.pf, 8);
   constexpr int CH = (NT * TG > 16) ? 16 / TG : NT;
   static bool attr_done = false;
   const size_t smem = (size_t)8 * CH * TG * 64 * sizeof(float4);
@@ -329,7 +327,14 @@ static hipError_t launch_skinny(SkinnyArgs a, hipStream_t st) {
   const int blocks = (a.n_rows + 63) / 64;
   if (TG * TS * 16 < 64 && (blocks > 1 || a.n_rows > TG * TS * 16)) return hipErrorInvalidValue;
   if (a.s_pad != blocks * 64) return hipErrorInvalidValue;
-  const int gx = (units + 7) / 8 * 8 * TS * blocks + a.pf_blocks + prefetch_blocks(a.pf2, 8);
+  // Blocks per wave that prefetches.  Beside O and down as many workgroups as compute units are left.  Beside gate/up 18 (14 to 18 the
+  // same) - except where its own workgroups are more than the units: with up to 2 token groups two of them share a unit and 9 is
+  // best (1.5B, 24 and 32 rows 1195, 1213 -> 1184, 1202 us per step), with 3 and 4 a unit holds one (150 registers and
+  // more), the prefetching ones start behind the last, and few and long ones are best (28: 48 and 64 rows 1538, 1612 -> 1532, 1572).
+  const int main = (units + 7) / 8 * 8 * TS * blocks, cu = n_compute_units();
+  const int per = MODE != SKM_SWIGLU ? prefetch_per_wave(a.pf, a.pf2, 8, cu - main, 10, kPrefetchKb) : main <= cu ? 18 : TG <= 2 ? 9 : kPrefetchKb;
+  a.pf_blocks = prefetch_blocks(a.pf, 8, per);
+  const int gx = main + a.pf_blocks + prefetch_blocks(a.pf2, 8, per);
   return launch(KID_GEMM_SKINNY, k_skinny16<NT, TG, TS, R, MODE>, dim3(gx), dim3(512), smem, st, a.Wp, a.Xp, a.ssq_in, a.h, a.gain_next,
                 a.N, a.K, a.n_rows, a.ssq_parts, a);
 }
@@ -429,7 +434,7 @@ __global__ void __launch_bounds__(512) k_skinny_few(const uint4* Wp_, const uint
   const int unit = (j / PT) * 8 + (blockIdx.x & 7);
   if (unit >= n_units) {
     const int first = (n_units + 7) / 8 * 8 * PT;
-    prefetch_behind<MODE == SKM_SWIGLU ? kPrefetchKbFew : kPrefetchKb>(a_rest, first);
+    prefetch_behind(a_rest, first, red);
     return;
   }
   const int row = lane & 15, kg = lane >> 4;
@@ -512,11 +517,17 @@ __global__ void __launch_bounds__(512) k_skinny_few(const uint4* Wp_, const uint
   }
 }
 
+template <int FR> static int few_blocks(int units) { return (units + 7) / 8 * 8 * (16 / FR); }
+// Blocks of 1 KiB per wave that prefetches, us per step: beside gate/up (0.5B 304 workgroups, 1.5B 560) 9 -> 6, 0.5B, 1 and 16
+// rows 560, 566 -> 555, 561; 1.5B 1028, 1077 -> 1019, 1069 (4: 1014, 1060, but 578, 584 on the 0.5B decoder, where two workgroups
+// per compute unit no longer hold them all).  Beside down as many workgroups as compute units are left, of 10 blocks at least: 18 ->
+// 10 573, 575 -> 569, 571 (0.5B); 18 -> 24 1044, 1173 -> 1034, 1146 (1.5B, which takes half tiles then).
 template <int FR, int R, int MODE>
 static hipError_t launch_few(SkinnyArgs a, hipStream_t st) {
-  a.pf_blocks = prefetch_blocks(a.pf, 8, MODE == SKM_SWIGLU ? kPrefetchKbFew : kPrefetchKb);
-  const int units = a.N / (MODE == SKM_SWIGLU ? 32 : 16);
-  return launch(KID_GEMM_SKINNY, k_skinny_few<FR, R, MODE>, dim3((units + 7) / 8 * 8 * (16 / FR) + a.pf_blocks + prefetch_blocks(a.pf2, 8)), dim3(512), 0, st, a.Wp, a.Xp,
+  const int units = a.N / (MODE == SKM_SWIGLU ? 32 : 16), main = few_blocks<FR>(units);
+  const int per = MODE == SKM_SWIGLU ? kPrefetchKbFew : prefetch_per_wave(a.pf, a.pf2, 8, n_compute_units() - main, 10, kPrefetchKb);
+  a.pf_blocks = prefetch_blocks(a.pf, 8, per);
+  return launch(KID_GEMM_SKINNY, k_skinny_few<FR, R, MODE>, dim3(main + a.pf_blocks + prefetch_blocks(a.pf2, 8, per)), dim3(512), 0, st, a.Wp, a.Xp,
                 a.ssq_in, a.h, a.gain_next, a.N, a.K, a.n_rows, a.ssq_parts, a);
 }
 template <int FR, int MODE>
@@ -590,8 +601,8 @@ hipError_t d_gemm_skinny(const SkinnyArgs& a, int mode, hipStream_t st) {
     // 24 layers, us per layer against whole tiles at 16 rows (1 .. 8 rows: within 0.1 either way): 56 tiles of 155 KB -0.24,
     // of 287 KB -0.52, 80 tiles of 287 KB -0.76 (160 + 56 workgroups); 96 tiles +0.9 .. +1.8 (192 + 72: some compute
     // units get two).
-    const int halves = 2 * ((tiles + 7) / 8 * 8) + prefetch_blocks(a.pf, 8) + prefetch_blocks(a.pf2, 8);
-    return halves <= 256 && per_wave > 8 ? launch_few_r<8, SKM_RESID>(a, st) : launch_few_r<16, SKM_RESID>(a, st);
+    const int room = n_compute_units() - few_blocks<8>(tiles);
+    return room >= 0 && prefetch_per_wave(a.pf, a.pf2, 8, room, 10, 0) > 0 && per_wave > 8 ? launch_few_r<8, SKM_RESID>(a, st) : launch_few_r<16, SKM_RESID>(a, st);
   }
   const int groups = multi ? 4 : (a.n_rows + 15) / 16;   // 16-token groups of a block that hold rows (2 .. 4)
   if (mode == SKM_SWIGLU) {
@@ -1135,9 +1146,10 @@ __global__ void __launch_bounds__(NW * 64) k_decode_attention16(const float* __r
                                                                const int* page_table_, int lp_pages_, int rows_,
                                                                int heads_, int n_main, void* kpool_, RowMap rm,
                                                                KVCache kv, uint4* __restrict__ out, ShareArgs sh, Prefetch pf) {
+  extern __shared__ float sm_o[];   // [NW][HD][16]; LDS: [NW][PD][NFRAG] KiB of staged pairs, a wave's output over its slot 0
   if ((int)blockIdx.x >= n_main) {   // uniform over the workgroup
     const int first = (n_main + 7) & ~7;
-    if ((int)blockIdx.x >= first) prefetch_role<NW>(pf, blockIdx.x - first, (int)gridDim.x - first);
+    if ((int)blockIdx.x >= first) prefetch_role<NW>(pf, blockIdx.x - first, (int)gridDim.x - first, sm_o);
     return;
   }
   // What leads from the start of the kernel to its first requests arrives preloaded (see k_skinny16): 14 dwords.  What they point
@@ -1153,7 +1165,6 @@ __global__ void __launch_bounds__(NW * 64) k_decode_attention16(const float* __r
   constexpr int DT = HD / 16;   // 16-row tiles of O^T
   constexpr int NFRAG = 2 * KK + DT;                        // 1 KiB fragments of one page pair
   constexpr size_t kOStride = LDS ? (size_t)PD * NFRAG * 256 : (size_t)HD * 16;   // floats between two waves' outputs
-  extern __shared__ float sm_o[];   // [NW][HD][16]; LDS: [NW][PD][NFRAG] KiB of staged pairs, a wave's output over its slot 0
   __shared__ __attribute__((aligned(16))) f16 qs[16 * HD];
   __shared__ __attribute__((aligned(16))) f16 knew[HD];
   __shared__ __attribute__((aligned(16))) f16 vnew[HD];
@@ -1504,7 +1515,11 @@ static hipError_t launch_decode_attention(const float* qkv, const float2* rope, 
   }
   const int group_log2 = sibling_group_log2(rm.G), group = 1 << group_log2;
   const int n_main = SHARE ? sh.n_prefix + S * kv.n_kv_heads : ((S + group - 1) / group * kv.n_kv_heads + 7) / 8 * 8 * group;
-  const int n_pf = prefetch_blocks(pf, NW);
+  // Prefetching workgroups: at most 5 / 8 of the compute units, more of them only held up the few that attend (us per step with
+  // 120, 136, 152, 168, 200, 240 of them: 0.5B, 1 row 573, 568, 566, 568, 576, 584; 1.5B, 1 row 128, 152, 176, 200, 224: 1053, 1038,
+  // 1035, 1044, 1051), and as many as these leave.
+  const int room = std::min(n_compute_units() * 5 / 8, n_compute_units() - n_main);
+  const int n_pf = prefetch_blocks(pf, NW, prefetch_per_wave(pf, Prefetch(), NW, room, 8, 18));
   const int blocks = n_pf > 0 ? ((n_main + 7) & ~7) + n_pf : n_main;
   // fields of the packed arguments (max_seq is at most 3584, 16 query heads per KV head: both checked when the handle is made)
   if (kv.n_kv_heads > 0xffff || n_q_heads / kv.n_kv_heads > 16 || rm.Lp > 0xffff || kv.pages_per_seq > 0x7fff) return hipErrorInvalidValue;

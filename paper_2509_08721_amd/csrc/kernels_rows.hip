@@ -242,7 +242,7 @@ __global__ void __launch_bounds__(256, 2) k_rows_down(const uint4* __restrict__ 
                                                       float4* __restrict__ partial, int main_blocks, Prefetch pf) {
   extern __shared__ uint4 smem[];
   if ((int)blockIdx.x >= main_blocks) {
-    prefetch_role<4>(pf, blockIdx.x - main_blocks, (int)gridDim.x - main_blocks);
+    prefetch_role<4>(pf, blockIdx.x - main_blocks, (int)gridDim.x - main_blocks, smem);
     return;
   }
   const int n_tblk = (M + 31) >> 5, token_tiles = (n_tblk + 3) >> 2;
@@ -341,7 +341,7 @@ template <int NB>
 static hipError_t down(const void* Xp, const void* Wp, int M, int n_fblk, int K, float* partial, const Prefetch& pf, hipStream_t st) {
   static bool attr_done = false;
   const int grid = kRowSplits * ((n_fblk + NB - 1) / NB) * ((M + 127) / 128);
-  return launch_rows<NB>(k_rows_down<NB>, attr_done, grid + prefetch_blocks(pf, 4), st, (const uint4*)Xp, (const uint4*)Wp, M, n_fblk, K,
+  return launch_rows<NB>(k_rows_down<NB>, attr_done, grid + prefetch_blocks(pf, 4, kPrefetchKbRows), st, (const uint4*)Xp, (const uint4*)Wp, M, n_fblk, K,
                          (float4*)partial, grid, pf);
 }
 
