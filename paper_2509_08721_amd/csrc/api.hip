@@ -700,7 +700,8 @@ static int run_layers_decode16(const sapo_weights* w, const FwdBufs& b, const De
   }
   // Which launch carries the prefetch of which weights: attention, which leaves most compute units idle, gate/up's;
   // gate/up (152 .. 304 workgroups) down's; down the next layer's QKV and O.  In QKV and O, 3 us each with hardly any
-  // bytes of their own, any prefetch lengthened the launch by more than it saved (50.2 against 46.8 ms per call).  With
+  // bytes of their own, any prefetch lengthened the launch by more than it saved (50.2 against 46.8 ms per call; down's in O's
+  // instead of gate/up's, 3 to 24 KiB per wave: 12 to 65 us per step more at 0.5B, 84 to 126 at 1.5B).  With
   // more than 64 rows only QKV's weights are prefetched: attention fills the chip there, and gate/up's in its launch took
   // the step from 928 to 995 us at 96 rows, 1106 to 1127 at 192 (0.5B), 2162 to 2269 at 256 (1.5B); down's in gate/up's
   // changed nothing (930, 1135, 2191).
