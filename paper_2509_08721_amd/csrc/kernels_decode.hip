@@ -444,6 +444,10 @@ __global__ void __launch_bounds__(512) k_skinny_few(const uint4* Wp_, const uint
   // lie in neighbouring lanes
   const int tok = lane >> 2, f = unit * 16 + part * FR + wave * 4 + (lane & 3);
   const bool live = tok < a.n_rows;
+  // Of one or two rows the next operand's other rows are written as well, whatever they hold (nobody reads them): lines of which
+  // 16 or 32 bytes in 256 were written leave the L2 slower than whole ones.  0.5B, us per step with 1 and 2 rows 551, 555 ->
+  // 546, 548; from 3 rows on (535) no difference.
+  const bool whole = a.n_rows <= 2;
   float h_old = 0.f, g_next = 0.f;
   if (MODE == SKM_RESID && wave < EW) {
     h_old = a.h[(size_t)min(tok, a.n_rows - 1) * a.N + f];   // clamped, so that the request sits under no lane mask
@@ -500,7 +504,7 @@ __global__ void __launch_bounds__(512) k_skinny_few(const uint4* Wp_, const uint
   float s = sum8(0);
   if (MODE == SKM_SWIGLU) {
     const float us = sum8(NA - 1), sc = ssq_scale(s_part, tok, a.norm_dim, a.eps);
-    if (live) ((f16*)a.xp_out)[x16_chunk(tok, f, a.N >> 6) * 8 + (f & 7)] = from_f32<f16>(silu_f(s * sc) * (us * sc));
+    if (live || whole) ((f16*)a.xp_out)[x16_chunk(tok, f, a.N >> 6) * 8 + (f & 7)] = from_f32<f16>(silu_f(s * sc) * (us * sc));
   } else if (MODE == SKM_STORE) {
 #pragma clang fp contract(off)   // rounded before the bias is added, as with more rows
     float o = s * ssq_scale(s_part, tok, a.norm_dim, a.eps);
@@ -509,9 +513,9 @@ __global__ void __launch_bounds__(512) k_skinny_few(const uint4* Wp_, const uint
   } else {
     s += h_old;
     const float4 all = make_float4(dpp_quad<0>(s), dpp_quad<1>(s), dpp_quad<2>(s), dpp_quad<3>(s));
+    if (live || whole) ((f16*)a.xp_out)[x16_chunk(tok, f, a.N >> 5) * 8 + (f & 7)] = from_f32<f16>(s * g_next);
     if (live) {
       a.h[(size_t)tok * a.N + f] = s;
-      ((f16*)a.xp_out)[x16_chunk(tok, f, a.N >> 5) * 8 + (f & 7)] = from_f32<f16>(s * g_next);
       if ((lane & 3) == 0) a.ssq_out[unit * 64 + (part * EW + wave) * 16 + tok] = sum_squares4(all);
     }
   }
