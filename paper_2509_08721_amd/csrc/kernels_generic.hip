@@ -985,16 +985,27 @@ hipError_t g_packed_prompts(const int* lens, int P, int G, const int* page_table
                             hipStream_t st) {
   return launch(KID_MISC, k_packed_prompts, dim3(P), dim3(256), 0, st, lens, P, G, page_table, pages_per_seq, first, packed);
 }
-// a workgroup per sequence and four positions: the packed rows of h <- their tokens' embeddings
+// The packed rows of h <- their tokens' embeddings.  A wave takes a row (d a multiple of 8, rows of 16 bytes), a workgroup four
+// positions of a sequence.  us per launch with one value per lane at a time (two bytes in, four out), and with eight: 10 x 256 rows of
+// 896 values 11.8, 7.8; 16 x 512 14.5, 12.2 (not packed, a workgroup per row: 9.2, 16.5).
 __global__ void __launch_bounds__(256) k_embed_packed(const int32_t* __restrict__ tokens, int T, const int* __restrict__ first,
-                                                      const bf16* __restrict__ embed, float* __restrict__ h, int d) {
-  const int s = blockIdx.y, t = blockIdx.x * 4 + (threadIdx.x >> 6), row0 = first[s];
+                                                      const uint4* __restrict__ embed, float4* __restrict__ h, int d8) {
+  const int s = blockIdx.x, t = blockIdx.y * 4 + wave_index(threadIdx.x), row0 = first[s];
   if (t >= first[s + 1] - row0) return;
-  const bf16* e = embed + (size_t)tokens[(size_t)s * T + t] * d;
-  for (int i = threadIdx.x & 63; i < d; i += 64) h[(size_t)(row0 + t) * d + i] = to_f32(e[i]);
+  const uint4* e = embed + (size_t)tokens[(size_t)s * T + t] * d8;
+  float4* o = h + (size_t)(row0 + t) * d8 * 2;
+  const auto low = [](unsigned u) { return __uint_as_float(u << 16); };          // of a pair of bf16 values, exactly
+  const auto high = [](unsigned u) { return __uint_as_float(u & 0xffff0000u); };
+  for (int i = threadIdx.x & 63; i < d8; i += 64) {
+    const uint4 v = e[i];
+    o[2 * i] = make_float4(low(v.x), high(v.x), low(v.y), high(v.y));
+    o[2 * i + 1] = make_float4(low(v.z), high(v.z), low(v.w), high(v.w));
+  }
 }
 hipError_t g_embed_packed(const int32_t* tokens, int T, int ns, const int* first, const void* embed, float* h, int d, hipStream_t st) {
-  return launch(KID_EMBED, k_embed_packed, dim3((T + 3) / 4, ns), dim3(256), 0, st, tokens, T, first, (const bf16*)embed, h, d);
+  if (d % 8 != 0) return hipErrorInvalidValue;
+  const PackedEmbedGrid g(ns, T);
+  return launch(KID_EMBED, k_embed_packed, dim3(g.x, g.y), dim3(256), 0, st, tokens, T, first, (const uint4*)embed, (float4*)h, d / 8);
 }
 
 // src_rows for a list of (s, t) positions: row s * T + t (debug logits).

@@ -144,6 +144,13 @@ inline X3Split x3_split(int NP, int rows, int cols, int KB, int stage, size_t pa
   return best;
 }
 
+// Blocks of k_embed_packed: sequences in x, four positions of a sequence each in y.  A grid's second dimension ends at 65535; a pass
+// has up to 131072 sequences, and a sequence fewer than 4096 positions.
+struct PackedEmbedGrid {
+  unsigned x, y;
+  constexpr PackedEmbedGrid(int n_seq, int T) : x((unsigned)n_seq), y((unsigned)(T + 3) / 4) {}
+};
+
 // Do two buffers of n bytes each share a byte?
 constexpr bool overlap(uintptr_t a, uintptr_t b, size_t n) { return a < b ? b - a < n : a - b < n; }
 

@@ -68,6 +68,21 @@ def test_scores_keep_their_bits_without_the_padding(model, S, T, kind):
         assert np.all(lp[~on] == 0.0) and np.all(lp[on] < 0.0)
 
 
+# more sequences in a pass than the second dimension of a grid holds
+def test_scores_of_many_short_sequences(model):
+    shape, gw = model
+    S, T = 65600, 2
+    rng = np.random.default_rng(3)
+    tokens = torch.from_numpy(rng.integers(0, shape.vocab, size=(S, T)).astype(np.int32)).cuda()
+    mask = torch.from_numpy((rng.random((S, T)) < 0.7).astype(np.uint8)).cuda()
+    rewards = torch.zeros(S, device="cuda")
+    lp = sapo.sapo_score_logprobs(gw, tokens, mask, rewards, 1)[0]
+    for s in (0, 30000, 65500):
+        part = slice(s, s + 100)
+        ref = sapo.sapo_score_logprobs(gw, tokens[part].contiguous(), mask[part].contiguous(), rewards[part].contiguous(), 1)[0]
+        assert torch.equal(lp[part], ref) and (ref[:, 1] < 0).any()
+
+
 # the workspace of a call before does not show: the same bits from memory full of NaN patterns
 def test_scores_do_not_depend_on_what_the_workspace_holds(model):
     shape, gw = model

@@ -199,3 +199,18 @@ int main() {
   return bad != 0;
 }
 """)
+
+
+def test_packed_embedding_grid_takes_every_number_of_sequences(tmp_path):
+    """k_embed_packed: a block for every four positions of every sequence, in a grid whose second dimension is at most 65535."""
+    run(tmp_path, r"""
+int main() {
+  int bad = 0;
+  for (int T : {1, 2, 3, 4, 5, 127, 300, 3583, 3584})
+    for (int n : {1, 2, 65535, 65536, 65537, 131072, 1 << 20}) {
+      const PackedEmbedGrid g(n, T);
+      if (g.x != (unsigned)n || g.y * 4 < (unsigned)T || g.y > 65535 || (g.y - 1) * 4 >= (unsigned)T) { ++bad; printf("%d x %d: %u %u\n", n, T, g.x, g.y); }
+    }
+  return bad != 0;
+}
+""")
