@@ -144,6 +144,20 @@ inline X3Split x3_split(int NP, int rows, int cols, int KB, int stage, size_t pa
   return best;
 }
 
+// Rows that a sequence of T positions has among packed rows when its last scored token is at `last` (0: it has none): the positions in
+// front of it, which the token's log-prob depends on, and as many more as make whole units, where the sequence has them.
+// The QKV launch writes 8 values of a page at once where 8 rows in a run begin at a slot divisible by 8, and two bytes at a
+// time elsewhere.  Answers up to the row's end have T - 1 rows, which for an even T left every sequence behind the first
+// askew.  A scoring pass takes units of 2: such a call lies as it would without packing, and a ragged one has half a row more
+// per sequence.  us per call not packed, in units of 1 and of 2, 0.5B, every answer up to the row's end: 10 x 256 3313, 3381, 3335; 16 x
+// 512 8226, 8335, 8259; ragged: 3142, 2944, 2934; 7717, 6279, 6256.  Units of 4 and 8 gain 1 to 2 % more on some ragged calls and
+// lose up to 11 % on sequences of few tokens (128 x 24 3136 -> 3247, 3493).
+constexpr int kPackedUnit = 2;
+SAPO_HD constexpr int packed_rows(int last, int T, int unit) {
+  const int n = (last + unit - 1) / unit * unit;
+  return n < T ? n : T;
+}
+
 // Blocks of k_embed_packed: sequences in x, four positions of a sequence each in y.  A grid's second dimension ends at 65535; a pass
 // has up to 131072 sequences, and a sequence fewer than 4096 positions.
 struct PackedEmbedGrid {
