@@ -158,6 +158,19 @@ SAPO_HD constexpr int packed_rows(int last, int T, int unit) {
   return n < T ? n : T;
 }
 
+// Are there enough rows to leave out?  With a few fewer than a row tile of 128 a pass keeps its tiles, while aligned sizes become
+// ragged ones, with blocks that are filled in part and fewer splits of the products over tokens.  So a sixteenth of the rows and
+// at least `least` of them (needed 0: nothing depends on any row, all run as they lie).
+// Prompts, a call of two tokens, all and packed, 0.5B: 72 of 1024 positions fewer 2345, 2352 us; 154 fewer 2335, 2299; 1.5B: 5500, 5515; 5477, 5262.
+// Update, 0.5B, three pieces: 512 -> 440 rows 18.46, 18.63 ms; 640 -> 600 19.77, 20.05; 768 -> 720 20.51, 20.87; 512 -> 384 18.34, 17.43; 640 -> 505 4 % less; 1024
+// -> 890 22.70, 22.53.  With one piece, a third of the work per row, it takes more rows: 1024 -> 890 16.78, 17.17; 768 -> 600 15.59,
+// 16.05; 1152 -> 890 0.3 % more; 512 -> 300 3 % less; 2048 -> 1792 21.31, 20.30.
+constexpr size_t kLeastPromptRows = 128;
+constexpr size_t least_update_rows(int pieces) { return pieces == 1 ? 192 : 128; }
+constexpr bool leaves_rows_out(size_t all, size_t needed, size_t least) {
+  return needed > 0 && needed <= all && all - needed >= all / 16 && all - needed >= least;
+}
+
 // Blocks of k_embed_packed: sequences in x, four positions of a sequence each in y.  A grid's second dimension ends at 65535; a pass
 // has up to 131072 sequences, and a sequence fewer than 4096 positions.
 struct PackedEmbedGrid {

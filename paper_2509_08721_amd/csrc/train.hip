@@ -2991,8 +2991,8 @@ extern "C" int sapo_policy_update(sapo_trainer* tr, const int32_t* tokens, const
     const int n = (int)(S - s0 < S_mb ? S - s0 : S_mb);
     if (n_rows[i] < 0 || (size_t)n_rows[i] > (size_t)n * T || n_needed[i] < 0 || (size_t)n_needed[i] > (size_t)n * T)
       return set_error(SAPO_EHIP, "row count read back from the device is out of range");
-    // without the rows that nothing depends on, where they are a sixteenth or more (with fewer, and with none at all: all rows as they lie)
-    const bool packs = fused_attention(c) && n_needed[i] > 0 && (size_t)n_needed[i] + (size_t)n * T / 16 <= (size_t)n * T;
+    // without the rows that nothing depends on, where they are enough
+    const bool packs = fused_attention(c) && leaves_rows_out((size_t)n * T, (size_t)n_needed[i], least_update_rows(tr->pieces));
     const int rc = update_rows(tr, p, tokens + s0 * T, completion_mask + s0 * T, logp_old + s0 * T, advantages + s0, n, T_,
                                eps_low, eps_high, p.logp_all + s0 * T, p.mrows + s0 * T, n_rows[i], packs ? n_needed[i] : 0, i == 0, st);
     if (rc != SAPO_OK) return rc;

@@ -107,7 +107,7 @@ def test_rollouts_keep_their_bits_without_the_prompts_padding(model, P, Lp, G, f
     rng = np.random.default_rng(P * 100 + Lp)
     lens = [Lp] * P if full else [1, Lp] + [int(x) for x in rng.integers(1, Lp + 1, size=P - 2)]
     prompts = torch.from_numpy(rng.integers(0, shape.vocab, size=(P, Lp)).astype(np.int32)).cuda()
-    assert P * Lp >= (512 if full else 1024) and Lp < 512 and (full or sum(lens) <= P * Lp * 15 // 16)
+    assert P * Lp >= (512 if full else 1024) and Lp < 512 and (full or P * Lp - sum(lens) >= max(128, P * Lp // 16))
     tok, lp, _ = sapo.sapo_rollout_generate_ragged(gw, prompts, lens, G, 3, 0.0, 5)
     for p in range(P):
         t, ref, _ = sapo.sapo_rollout_generate_ragged(gw, prompts[p:p + 1].contiguous(), lens[p:p + 1], G, 3, 0.0, 5)

@@ -231,3 +231,26 @@ int main() {
   return bad != 0;
 }
 """)
+
+
+def test_rows_are_left_out_only_where_a_tile_of_them_goes(tmp_path):
+    """leaves_rows_out: never where nothing is needed, never for fewer rows than a row tile or a sixteenth, and once enough for some
+    number of needed rows, enough for every smaller one."""
+    run(tmp_path, r"""
+int main() {
+  int bad = 0;
+  for (int pieces : {1, 2, 3})
+    for (size_t all = 1; all <= 4200; all += all < 300 ? 1 : 37) {
+      const size_t least = least_update_rows(pieces);
+      if (leaves_rows_out(all, 0, least) || leaves_rows_out(all, all, least) || leaves_rows_out(all, all + 1, least)) { ++bad; printf("%zu: ends\n", all); }
+      bool before = true;
+      for (size_t needed = 1; needed < all; ++needed) {
+        const bool out = leaves_rows_out(all, needed, least);
+        if (out && (all - needed < 128 || (all - needed) * 16 < all - 15)) { ++bad; printf("%zu needed of %zu\n", needed, all); }
+        if (out && !before) { ++bad; printf("%zu of %zu: not below\n", needed, all); }
+        before = out;
+      }
+    }
+  return bad != 0;
+}
+""")
