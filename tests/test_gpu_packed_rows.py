@@ -18,16 +18,29 @@ pytestmark = pytest.mark.gpu
 
 SHAPES = {
     "hd64": replace(W.MINI_BF16, d_model=384, d_ff=576, n_layers=3, max_seq=1024),
-    "hd128": replace(W.MINI_BF16_HD128, max_seq=1024),
+    "hd128": replace(W.MINI_BF16_HD128, d_ff=832, max_seq=1024),
+    # more query features than an FFN is wide: the last layer runs for all rows, and a scoring pass as its rows lie
+    "wide_queries": replace(W.MINI_BF16_HD128, max_seq=1024),
 }
+NARROWS = {"hd64": True, "hd128": True, "wide_queries": False}
 
 
-@pytest.fixture(scope="module", params=sorted(SHAPES))
-def model(request):
-    shape = SHAPES[request.param]
+def make(name):
+    shape = SHAPES[name]
+    assert (shape.d_model <= shape.q_dim + 2 * shape.kv_dim and shape.q_dim <= shape.d_ff) == NARROWS[name]
     gw = sapo.sapo_weights_create(shape, W.perturb_norm_gains(W.make_weights(shape, 41, std=0.05), 41))
     assert gw.uses_mfma
     return shape, gw
+
+
+@pytest.fixture(scope="module", params=[n for n in sorted(SHAPES) if NARROWS[n]])
+def model(request):
+    return make(request.param)
+
+
+@pytest.fixture(scope="module", params=sorted(SHAPES))
+def any_model(request):
+    return make(request.param)
 
 
 def masks(S, T, kind, rng):
@@ -98,16 +111,22 @@ def test_scores_do_not_depend_on_what_the_workspace_holds(model):
     assert np.array_equal(a, b) and np.isfinite(a).all()
 
 
-# P prompts of up to Lp tokens, packed where they are shorter (P Lp >= 1024) and with the last layer for their last rows only
-# (P Lp >= 512), against the same prompts one at a time, which run neither
-@pytest.mark.parametrize("P,Lp,G,full", [(9, 120, 4, False), (5, 257, 3, False), (40, 33, 1, False), (5, 120, 2, True), (3, 257, 3, True),
-                                         (17, 31, 1, True), (33, 32, 1, True)])
-def test_rollouts_keep_their_bits_without_the_prompts_padding(model, P, Lp, G, full):
-    shape, gw = model
+# P prompts of up to Lp tokens, packed where they are shorter (P Lp >= 1024 and a row tile of 128 or a sixteenth less) and with the
+# last layer for their last rows only (P Lp >= 512, also where rows of padding lie between), against the same prompts one at a time,
+# which run neither
+@pytest.mark.parametrize("P,Lp,G,kind", [(9, 120, 4, "packed"), (5, 257, 3, "packed"), (40, 33, 1, "packed"), (5, 120, 2, "full"),
+                                         (3, 257, 3, "full"), (17, 31, 1, "full"), (33, 32, 1, "full"), (7, 100, 3, "padded"),
+                                         (20, 31, 1, "padded"), (9, 120, 2, "padded"), (5, 300, 1, "padded")])
+def test_rollouts_keep_their_bits_without_the_prompts_padding(any_model, P, Lp, G, kind):
+    shape, gw = any_model
     rng = np.random.default_rng(P * 100 + Lp)
-    lens = [Lp] * P if full else [1, Lp] + [int(x) for x in rng.integers(1, Lp + 1, size=P - 2)]
+    lens = [Lp] * P if kind == "full" else [1, Lp] + [int(x) for x in rng.integers(1, Lp + 1, size=P - 2)]
+    if kind == "padded" and P * Lp >= 1024:   # fewer rows of padding than a tile
+        lens = [Lp - int(x) for x in rng.integers(0, 127 // P + 1, size=P)]
+    left_out = P * Lp - sum(lens)
+    packed = P * Lp >= 1024 and left_out >= max(128, P * Lp // 16)
     prompts = torch.from_numpy(rng.integers(0, shape.vocab, size=(P, Lp)).astype(np.int32)).cuda()
-    assert P * Lp >= (512 if full else 1024) and Lp < 512 and (full or P * Lp - sum(lens) >= max(128, P * Lp // 16))
+    assert P * Lp >= 512 and Lp < 512 and packed == (kind == "packed") and (left_out > 0) == (kind != "full")
     tok, lp, _ = sapo.sapo_rollout_generate_ragged(gw, prompts, lens, G, 3, 0.0, 5)
     for p in range(P):
         t, ref, _ = sapo.sapo_rollout_generate_ragged(gw, prompts[p:p + 1].contiguous(), lens[p:p + 1], G, 3, 0.0, 5)
