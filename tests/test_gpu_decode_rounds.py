@@ -45,10 +45,11 @@ def test_rows_by_table_and_in_order_are_the_same(model, rows):
     up each row's sequence and length; neither may change a bit."""
     shape, gw, _ = model
     prompts = np.random.default_rng(rows).integers(0, shape.vocab, size=(rows, 33)).astype(np.int32)
-    toks, lps = sapo.sapo_rollout_generate(gw, dev(prompts), 1, 20, 1.0, 5)
-    by_length = sapo.sapo_rollout_generate_ragged(gw, dev(prompts), [33] * rows, 1, 20, 1.0, 5)
+    n_new = min(20, (shape.vocab - 1) // rows)   # fewer draws than ids: one of them is not drawn
+    assert n_new >= 4
+    toks, lps = sapo.sapo_rollout_generate(gw, dev(prompts), 1, n_new, 1.0, 5)
+    by_length = sapo.sapo_rollout_generate_ragged(gw, dev(prompts), [33] * rows, 1, n_new, 1.0, 5)
     assert torch.equal(by_length[0], toks) and torch.equal(by_length[1], lps)
-    unused = int(np.setdiff1d(np.arange(shape.vocab), toks.cpu().numpy())[0]) if rows * 20 < shape.vocab else None
-    if unused is not None:
-        stopped = sapo.sapo_rollout_generate_stop(gw, dev(prompts), 1, 20, 1.0, 5, unused)
-        assert torch.equal(stopped[0], toks) and torch.equal(stopped[1], lps)
+    unused = int(np.setdiff1d(np.arange(shape.vocab), toks.cpu().numpy())[0])
+    stopped = sapo.sapo_rollout_generate_stop(gw, dev(prompts), 1, n_new, 1.0, 5, unused)
+    assert torch.equal(stopped[0], toks) and torch.equal(stopped[1], lps)
