@@ -49,8 +49,21 @@ def algorithmic_bytes_rollout(shape, P, G, Lp, N):
     return {"weights": (N - 1) * W, "kv_read_shared": shared, "kv_read_unshared": unshared, "kv_write": write}
 
 
-def algorithmic_flops_score(shape, S, T, Tm):
-    layers = 2 * shape.n_layers * shape.matmul_params_per_layer() * S * T
+def wanted_rows(shape, mfma, rows, wanted, at_least):
+    """Rows that the last layer's O, gate/up and down projections run for (run_layers_big in csrc/api.hip): of a prefill of 512
+    positions and more the prompts' last ones, of a scoring pass of 2560 and more those that predict a scored token."""
+    narrows = mfma and rows >= at_least and shape.d_model <= shape.q_dim + 2 * shape.kv_dim and shape.q_dim <= shape.d_ff
+    return wanted if narrows else rows
+
+
+def projection_flops(shape, rows, last_rows):
+    """The projections of `rows` rows through every layer, behind the last layer's attention of `last_rows` only."""
+    behind_attention = shape.q_dim * shape.d_model + 3 * shape.d_model * shape.d_ff
+    return 2 * (shape.n_layers * shape.matmul_params_per_layer() * rows - behind_attention * (rows - last_rows))
+
+
+def algorithmic_flops_score(shape, S, T, Tm, last_rows):
+    layers = projection_flops(shape, S * T, last_rows)
     lm = 2 * shape.vocab * shape.d_model * S * Tm
     attn = 2 * T * T * shape.q_dim * shape.n_layers * S
     return {"layers": layers, "lm_head": lm, "attention": attn, "total": layers + lm + attn}
@@ -63,7 +76,6 @@ def per_launch_work(shape, plan, kernel, launches):
     S, N, Lp, P = plan["S"], plan["N"], plan["Lp"], plan["P"]
     T, Tm, Ss = plan["T"], plan["Tm"], plan["S_score"]
     dec_steps = max(N - 1, 0) if plan["rollout"] else 0
-    big_tokens = (P * Lp if plan["rollout"] else 0) + (Ss * T if plan["score"] else 0)
     ffn_params = 3.0 * d * shape.d_ff
     if kernel == "k_gemm_skinny":       # the projection GEMMs of a decode layer that run on the register-direct kernel
         params = shape.matmul_params_per_layer() - (ffn_params if plan["ffn_big"] else 0.0)
@@ -85,7 +97,8 @@ def per_launch_work(shape, plan, kernel, launches):
         tot = kv_layer * L * sum(P * shared_tokens + S * (Lp + t - shared_tokens) for t in range(1, N))
         return "hbm", tot / launches
     if kernel == "k_gemm_big":          # projection GEMMs of prefill + scoring (+ LM head where logits are materialised)
-        fl = 2.0 * L * shape.matmul_params_per_layer() * big_tokens
+        fl = float((projection_flops(shape, P * Lp, plan["prefill_last"]) if plan["rollout"] else 0)
+                   + (projection_flops(shape, Ss * T, plan["score_last"]) if plan["score"] else 0))
         if plan["rollout"] and not plan["fused_lm"]:
             fl += 2.0 * V * d * S * N
         return "mfma", fl / launches
@@ -411,7 +424,9 @@ def run_workload(args, workload, n_steps, n_warmup, cpu_baseline, probes):
     prompts = torch.from_numpy(prompts_np).cuda()
     plan = {"S": S, "N": N, "Lp": Lp, "P": P, "T": T, "Tm": Tm, "S_score": S_score, "rollout": do_rollout,
             "score": do_score, "fused_lm": S <= 64 and shape.d_model <= 1024,
-            "ffn_big": 64 < S <= 256 and bool(gw.uses_mfma)}
+            "ffn_big": 64 < S <= 256 and bool(gw.uses_mfma),
+            "prefill_last": wanted_rows(shape, bool(gw.uses_mfma), P * Lp, P, 512),
+            "score_last": wanted_rows(shape, bool(gw.uses_mfma), S_score * T, S_score * Tm, 2560)}
 
     if do_rollout:
         ws_r = torch.empty(sapo.sapo_rollout_workspace_bytes(gw, P, Lp, G, N) + 256, dtype=torch.uint8, device="cuda")
@@ -534,7 +549,7 @@ def run_workload(args, workload, n_steps, n_warmup, cpu_baseline, probes):
                                     "achieved_GBs": round(roll_gbs, 1), "peak_GBs": HBM_PEAK_GBS,
                                     "frac": round(roll_gbs / HBM_PEAK_GBS, 4)}})
     if do_score:
-        fl = algorithmic_flops_score(shape, S_score, T, Tm)
+        fl = algorithmic_flops_score(shape, S_score, T, Tm, plan["score_last"])
         score_tflops = fl["total"] / (s_ms * 1e-3) / 1e12
         out.update({"scored_tokens_per_s": round(scored_tokens / (s_ms * 1e-3), 1), "score_ms": round(s_ms, 3),
                     "masked_tokens_per_s": round(S_score * Tm / (s_ms * 1e-3), 1),

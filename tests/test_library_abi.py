@@ -97,3 +97,22 @@ def test_boost_token_scales_one_head_row_exactly():
                 assert b[other] is w[other]
     wl = W.WORKLOADS["onehalfb_stop"]
     assert 0 <= wl.stop_token < wl.shape.vocab and wl.stop_boost > 0 and wl.n_seqs == 256
+
+
+def test_bench_counts_the_products_that_run():
+    """The work behind the token-parallel products' rate: every row through every layer, but behind the last layer's attention the
+    prompts' last rows and the scored ones alone."""
+    import bench
+    from paper_2509_08721_amd import workloads as W
+    s = W.HALF_B
+    P, Lp, S, T, Tm = 8, 128, 64, 768, 512
+    assert bench.wanted_rows(s, True, P * Lp, P, 512) == P and bench.wanted_rows(s, True, 511, P, 512) == 511
+    assert bench.wanted_rows(s, False, P * Lp, P, 512) == P * Lp
+    assert bench.wanted_rows(W.MINI_BF16_HD128, True, 4096, 8, 512) == 4096      # more query features than its FFN is wide
+    qkv, rest = s.d_model * (s.q_dim + 2 * s.kv_dim), s.q_dim * s.d_model + 3 * s.d_model * s.d_ff
+    want = 2 * 23 * (qkv + rest) * (P * Lp + S * T) + 2 * qkv * (P * Lp + S * T) + 2 * rest * (P + S * Tm)
+    plan = {"S": S, "N": 256, "Lp": Lp, "P": P, "T": T, "Tm": Tm, "S_score": S, "rollout": True, "score": True, "fused_lm": True,
+            "ffn_big": False, "prefill_last": P, "score_last": S * Tm}
+    bound, work = bench.per_launch_work(s, plan, "k_gemm_big", 10)
+    assert bound == "mfma" and abs(work * 10 / want - 1) < 1e-12
+    assert bench.algorithmic_flops_score(s, S, T, Tm, S * Tm)["layers"] == 2 * 24 * (qkv + rest) * S * T - 2 * rest * S * (T - Tm)
