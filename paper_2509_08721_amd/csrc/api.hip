@@ -1254,7 +1254,8 @@ static void plan_score(const sapo_weights* w, int S, int T, int chunk_seqs, size
 // 0.5B) have few tiles per token tile, so the pass size decides how full their rounds are.  The size is the one
 // that minimises the summed rounds x contraction length of a layer's four GEMMs over the whole call (for 64 x 768
 // tokens at 0.5B: one pass of 192 token tiles, 3 rounds for the narrow GEMMs, instead of two passes of 2 rounds
-// each), among passes of at most 131072 tokens.
+// each), among passes of at most 131072 tokens.  All positions are counted, also those that a packed pass leaves out (score_packs_rows):
+// only the device knows how many they are.
 static int score_chunk_seqs(const sapo_weights* w, int S, int T) {
   if (!w->mfma) {
     int cs = 32768 / T;

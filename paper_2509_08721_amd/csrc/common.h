@@ -423,6 +423,7 @@ struct Prefetch {
   const uint4* p = nullptr;
   int KS = 0, n_tiles = 0, nt_log2 = 0, ks1 = 0;   // ks1 = 0: nothing
 };
+// Measured on the two decoders of the workloads (0.5B, 1.5B), as the lines of the rules that choose between them
 constexpr int kPrefetchKb = 28;       // blocks of 1 KiB per prefetching wave: at most (36 instead of 28 us per step + 5 to 32) ...
 constexpr int kPrefetchKbFew = 6;     // ... beside gate/up of at most 16 rows ...
 constexpr int kPrefetchKbRows = 18;   // ... and beside down of more than 64

@@ -603,8 +603,9 @@ hipError_t d_gemm_skinny(const SkinnyArgs& a, int mode, hipStream_t st) {
     if (mode == SKM_STORE) return launch_few_r<16, SKM_STORE>(a, st);
     // Half tiles where twice the workgroups, with those that prefetch, still have a compute unit each, and a tile is long.
     // 24 layers, us per layer against whole tiles at 16 rows (1 .. 8 rows: within 0.1 either way): 56 tiles of 155 KB -0.24,
-    // of 287 KB -0.52, 80 tiles of 287 KB -0.76 (160 + 56 workgroups); 96 tiles +0.9 .. +1.8 (192 + 72: some compute
-    // units get two).
+    // of 287 KB -0.52, 80 tiles of 287 KB -0.76 (160 + 56 workgroups).  96 tiles were +0.9 .. +1.8 as long as 72 prefetched beside
+    // the 192; with the 64 that prefetch_per_wave leaves them (1.5B's down) a step of 1, 4, 8 and 16 rows takes 1027, 1038,
+    // 1066, 1153 us, with whole tiles 1041, 1059, 1085, 1188.
     const int room = n_compute_units() - few_blocks<8>(tiles);
     return room >= 0 && prefetch_per_wave(a.pf, a.pf2, 8, room, 10, 0) > 0 && per_wave > 8 ? launch_few_r<8, SKM_RESID>(a, st) : launch_few_r<16, SKM_RESID>(a, st);
   }

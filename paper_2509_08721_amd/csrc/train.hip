@@ -2548,10 +2548,6 @@ extern "C" int sapo_trainer_export(const sapo_trainer* tr, void* const* tensors_
   return SAPO_OK;
 }
 
-// Forward, LM head and backward over one micro-batch of S_ sequences: gradients are written to tr->grad by the first one of
-// an update (first) and added by the others (zeroing the buffer and adding to the zeros moved 6 GB at 0.5B: 21 x 301 tokens,
-// one piece, 43.0 -> 42.0 ms), the log-probs go to logp_new [S_, T_].  p.n_masked holds the count of masked tokens of the whole training set and
-// the LM head is packed (p.head_nt, p.head_t).
 // The rows of a micro-batch that the loss depends on.  Attention is causal and a row's gradient is zero behind its sequence's last
 // masked token, so what lies behind it (answers that end before their row does) needs neither pass.  Sequence s goes on with
 // lens[s].x positions, side by side with the others': row first[s] + t is token tokens[first[s] + t] at position t; rows: those that
@@ -2607,6 +2603,10 @@ __global__ void __launch_bounds__(256) k_packed_count(const int2* __restrict__ l
   if (threadIdx.x == 0) *count = (part[0] + part[1]) + (part[2] + part[3]);
 }
 
+// Forward, LM head and backward over one micro-batch of S_ sequences: gradients are written to tr->grad by the first one of
+// an update (first) and added by the others (zeroing the buffer and adding to the zeros moved 6 GB at 0.5B: 21 x 301 tokens,
+// one piece, 43.0 -> 42.0 ms), the log-probs go to logp_new [S_, T_].  p.n_masked holds the count of masked tokens of the whole training set and
+// the LM head is packed (p.head_nt, p.head_t).  n_packed: rows that go on (PackedUpdate), 0: all as they lie.
 static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* tokens, const uint8_t* completion_mask,
                        const float* logp_old, const float* advantages, int S_, int T_, float eps_low, float eps_high,
                        float* logp_new, const int* rows, int n_rows, int n_packed, bool first, hipStream_t st) {
