@@ -959,7 +959,7 @@ hipError_t g_packed_lens(const uint8_t* mask, int T, int s0, int ns, int unit, i
 }
 hipError_t g_packed_rows(const uint8_t* mask, int T, int s0, int ns, const int* page_table, int pages_per_seq, int2* lens, int* first,
                          int2* packed, int* rows, int* src_rows, int* count, hipStream_t st) {
-  const hipError_t e = g_packed_lens(mask, T, s0, ns, kPackedUnit, lens, st);
+  const hipError_t e = g_packed_lens(mask, T, s0, ns, packed_unit(T), lens, st);
   if (e != hipSuccess) return e;
   return launch(KID_MISC, k_packed_rows, dim3(ns), dim3(256), 0, st, mask, T, s0, ns, (const int2*)lens, page_table, pages_per_seq, first,
                 packed, rows, src_rows, count);

@@ -151,8 +151,10 @@ inline X3Split x3_split(int NP, int rows, int cols, int KB, int stage, size_t pa
 // askew.  A scoring pass takes units of 2: such a call lies as it would without packing, and a ragged one has half a row more
 // per sequence.  us per call not packed, in units of 1 and of 2, 0.5B, every answer up to the row's end: 10 x 256 3313, 3381, 3335; 16 x
 // 512 8226, 8335, 8259; ragged: 3142, 2944, 2934; 7717, 6279, 6256.  Units of 4 and 8 gain 1 to 2 % more on some ragged calls and
-// lose up to 11 % on sequences of few tokens (128 x 24 3136 -> 3247, 3493).
-constexpr int kPackedUnit = 2;
+// lose up to 11 % on sequences of few tokens (128 x 24 3136 -> 3247, 3493).  Below 64 positions a row is more of a sequence than the
+// alignment is worth: 8192 x 2 16738, 11913, 16698; 1000 x 8 8110, 7627, 8123; 600 x 16 9615, 8923, 9585; 400 x 32 11985, 11878, 11931; but 40 x 64
+// 3242, 3317, 3259.
+constexpr int packed_unit(int T) { return T < 64 ? 1 : 2; }
 SAPO_HD constexpr int packed_rows(int last, int T, int unit) {
   const int n = (last + unit - 1) / unit * unit;
   return n < T ? n : T;
