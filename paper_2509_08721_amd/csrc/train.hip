@@ -829,7 +829,8 @@ inline size_t x3_pack_bytes(int NP, size_t rows, size_t K) {
   return ((rows + 127) / 128 * 128) * ((K + 63) / 64 * 64) * 2 * x3_parts(NP);
 }
 inline int x3_steps(int K) { return (K + 63) / 64 * 4; }   // padded k steps: whole stages, whole waves of the packing
-struct X3Bufs { void* a; void* b; size_t a_cap, b_cap; int NP; float* parts; size_t parts_cap; };
+// left_out: rows (tokens) that the products at hand do without (PackedUpdate)
+struct X3Bufs { void* a; void* b; size_t a_cap, b_cap; int NP; float* parts; size_t parts_cap; int left_out; };
 __global__ void k_sum_parts(const float* __restrict__ part, int n_part, size_t n, float beta, const float* in, float* out);
 
 hipError_t x3_pack(const X3Op& op, void* dst, size_t cap, int NP, hipStream_t st) {
@@ -843,10 +844,11 @@ hipError_t x3_pack(const X3Op& op, void* dst, size_t cap, int NP, hipStream_t st
   if (op.trans) return NP == 3 ? go(k_pack_x3_t<3>) : NP == 2 ? go(k_pack_x3_t<2>) : go(k_pack_x3_t<1>);
   return NP == 3 ? go(k_pack_x3_max) : NP == 2 ? go(k_pack_x3<2>) : go(k_pack_x3<1>);
 }
-// Tile, grid and split of a product with `rows` x `cols` outputs and KB k steps in stages of `stage` (x3_split in ranges.h).
+// Tile, grid and split of a product with `rows` x `cols` outputs and KB k steps in stages of `stage`, all_rows and all_KB of them had no
+// row been left out (x3_split, x3_split_packed in ranges.h).
 struct X3Grid { int TJ, splits, per_split; dim3 grid; };
-X3Grid x3_grid(int NP, int rows, int cols, int KB, int stage, size_t parts_cap) {
-  const X3Split s = x3_split(NP, rows, cols, KB, stage, parts_cap);
+X3Grid x3_grid(int NP, int rows, int cols, int KB, int all_rows, int all_KB, int stage, size_t parts_cap) {
+  const X3Split s = x3_split_packed(NP, rows, cols, KB, all_rows, all_KB, stage, parts_cap);
   return X3Grid{s.TJ, s.parts, s.per_part, dim3(raster_grid((cols + kGM - 1) / kGM, (rows + kGM * s.TJ - 1) / (kGM * s.TJ)), 1, s.parts)};
 }
 hipError_t x3_sum_parts(const X3Bufs& bufs, int splits, size_t n, float beta, const float* Cin, float* C, hipStream_t st) {
@@ -854,9 +856,9 @@ hipError_t x3_sum_parts(const X3Bufs& bufs, int splits, size_t n, float beta, co
                 Cin, C);
 }
 // C[M, N] = beta C + op(A) op(B)^T-style product of two operands given row-wise over the same K; an operand packed earlier
-// (a_packed, b_packed) is used as it is
+// (a_packed, b_packed) is used as it is.  The tokens are A's rows, or (over_tokens) what is contracted over
 hipError_t gemm_x3(const X3Op& A, const X3Op& B, float* C, const float* Cin, int ldc, float beta, const X3Bufs& bufs, hipStream_t st,
-                   const void* b_packed = nullptr, bool split_ok = true, const void* a_packed = nullptr) {
+                   const void* b_packed = nullptr, bool split_ok = true, const void* a_packed = nullptr, bool over_tokens = false) {
   if (A.K != B.K || A.rows <= 0 || B.rows <= 0 || A.K <= 0 || (bufs.NP == 3 && (!A.row_mx || !B.row_mx))) return hipErrorInvalidValue;
   hipError_t e;
   if (!a_packed && (e = x3_pack(A, bufs.a, bufs.a_cap, bufs.NP, st)) != hipSuccess) return e;
@@ -864,7 +866,8 @@ hipError_t gemm_x3(const X3Op& A, const X3Op& B, float* C, const float* Cin, int
   const u32x4_t* pa_ = (const u32x4_t*)(a_packed ? a_packed : bufs.a);
   const u32x4_t* pb_ = (const u32x4_t*)(b_packed ? b_packed : bufs.b);
   const int KB = x3_steps(A.K);
-  const X3Grid g = x3_grid(bufs.NP, A.rows, B.rows, KB, x3_stage(bufs.NP), split_ok && ldc == B.rows ? bufs.parts_cap : 0);
+  const int all_rows = over_tokens ? A.rows : A.rows + bufs.left_out, all_KB = over_tokens ? x3_steps(A.K + bufs.left_out) : KB;
+  const X3Grid g = x3_grid(bufs.NP, A.rows, B.rows, KB, all_rows, all_KB, x3_stage(bufs.NP), split_ok && ldc == B.rows ? bufs.parts_cap : 0);
   float* out = g.splits > 1 ? bufs.parts : C;
   const size_t c_split = g.splits > 1 ? (size_t)A.rows * B.rows : 0;
   const float b_ = g.splits > 1 ? 0.f : beta;
@@ -883,7 +886,7 @@ hipError_t gemm_x3_tn(const float* A, int lda, const float* B, int ldb, float* C
                       const X3Bufs& bufs, hipStream_t st, const uint32_t* amx, const uint32_t* bmx) {   // maxima of their columns
   if (M <= 0 || N <= 0 || K <= 0 || (bufs.NP == 3 && (!amx || !bmx))) return hipErrorInvalidValue;
   const int KB = (K + 15) / 16;
-  const X3Grid g = x3_grid(bufs.NP, M, N, KB, x3_tn_stage(bufs.NP), bufs.parts_cap);
+  const X3Grid g = x3_grid(bufs.NP, M, N, KB, M, (K + bufs.left_out + 15) / 16, x3_tn_stage(bufs.NP), bufs.parts_cap);
   float* out = g.splits > 1 ? bufs.parts : C;
   const size_t c_split = g.splits > 1 ? (size_t)M * N : 0;
   const float b_ = g.splits > 1 ? 0.f : beta;
@@ -2653,24 +2656,26 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
 
   // The projections and the LM head run on the packed GEMM (k_gemm_x3); forms as in sgemm<TA, TB>.
   const int NP = tr->pieces;
-  const X3Bufs xb{p.packa, p.packb, p.packa_cap, p.packb_cap, NP, p.kparts, split_parts_floats(D)};
+  const X3Bufs xh{p.packa, p.packb, p.packa_cap, p.packb_cap, NP, p.kparts, split_parts_floats(D), 0};   // of the LM head's products
+  X3Bufs xb = xh;                                                                                       // of the layers'
+  xb.left_out = (int)(S * T - M);
   // Forward products are split over K with three pieces only: with two and one a sequence's log-probs do not depend on the
   // batch around it (where operands are rounded to bf16 a last bit decides roundings downstream, about 1e-2 of a log-prob
   // after 24 layers).
   const bool split_fwd = NP == 3;
   struct Mat { const float* x; int ld; uint32_t *row_mx, *col_mx; };   // a matrix by rows, with its maxima
   auto mm_nt = [&](const Mat& X, const Mat& W, float* C, int ldc, int M_, int N_, int K_, float beta,
-                   const float* Cin = nullptr, const void* w_packed = nullptr) {   // C = beta Cin + X W^T
+                   const float* Cin = nullptr, const X3Bufs* bufs = nullptr, const void* w_packed = nullptr) {   // C = beta Cin + X W^T
     return gemm_x3(X3Op{X.x, X.ld, M_, K_, false, X.row_mx, X.col_mx}, X3Op{W.x, W.ld, N_, K_, false, W.row_mx, W.col_mx}, C, Cin, ldc,
-                   beta, xb, st, w_packed, split_fwd);
+                   beta, bufs ? *bufs : xb, st, w_packed, split_fwd);
   };
   auto mm_nn = [&](const Mat& A_, const Mat& B_, float* C, int ldc, int M_, int N_, int K_, float beta,
-                   const void* b_packed = nullptr) {   // C = beta C + A B
+                   const X3Bufs* bufs = nullptr, const void* b_packed = nullptr) {   // C = beta C + A B
     return gemm_x3(X3Op{A_.x, A_.ld, M_, K_, false, A_.row_mx, A_.col_mx}, X3Op{B_.x, B_.ld, N_, K_, true, B_.col_mx, nullptr}, C, C, ldc,
-                   beta, xb, st, b_packed);
+                   beta, bufs ? *bufs : xb, st, b_packed);
   };
-  auto mm_tn = [&](const Mat& A_, const Mat& B_, float* C, int Mg, int Ng, int Kg, float beta) {   // C = beta C + A^T B
-    return gemm_x3_tn(A_.x, A_.ld, B_.x, B_.ld, C, Mg, Ng, Kg, beta, xb, st, A_.col_mx, B_.col_mx);
+  auto mm_tn = [&](const Mat& A_, const Mat& B_, float* C, int Mg, int Ng, int Kg, float beta, const X3Bufs* bufs = nullptr) {   // C = beta C + A^T B
+    return gemm_x3_tn(A_.x, A_.ld, B_.x, B_.ld, C, Mg, Ng, Kg, beta, bufs ? *bufs : xb, st, A_.col_mx, B_.col_mx);
   };
   auto rows_max = [&](const float* x, int K_, uint32_t* out) { return NP == 3 ? row_max(x, Mi, K_, out, st) : hipSuccess; };
   if (NP == 3 && !first) T_CK(g_fill_f32((float*)p.mx_zero, 0.f, p.mx_zero_n, st));   // the first micro-batch: with head_c
@@ -2756,11 +2761,11 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
     for (size_t r0 = 0; r0 < (size_t)n_rows; r0 += p.chunk) {
       const int R = (int)(((size_t)n_rows - r0 < p.chunk) ? (size_t)n_rows - r0 : p.chunk);
       const Mat xfc{p.xfc + r0 * D.d, d, p.xfc_r + r0, p.xfc_c}, logits{p.logits, V, p.dl_r, p.dl_c}, head{TH(t_head), d, p.head_r, p.head_c};
-      T_CK(mm_nt(xfc, head, p.logits, V, R, V, d, 0.f, nullptr, p.head_nt));
+      T_CK(mm_nt(xfc, head, p.logits, V, R, V, d, 0.f, nullptr, &xh, p.head_nt));
       T_CK(launch(KID_SCORE_ROWS, k_logp_dlogits, dim3(R), dim3(kLogpThreads), 0, st, p.logits, V, token_rows + r0, (int)T, tokens, completion_mask,
                   logp_old, advantages, eps_low, eps_high, (const long long*)p.n_masked, logp_new, p.dl_r));
-      T_CK(mm_nn(logits, head, p.dh + r0 * D.d, d, R, d, V, 0.f, p.head_t));
-      T_CK(mm_tn(logits, xfc, GR(t_head), V, d, R, r0 == 0 ? keep : 1.f));
+      T_CK(mm_nn(logits, head, p.dh + r0 * D.d, d, R, d, V, 0.f, &xh, p.head_t));
+      T_CK(mm_tn(logits, xfc, GR(t_head), V, d, R, r0 == 0 ? keep : 1.f, &xh));
     }
     T_CK(launch(KID_MISC, k_move_rows, dim3(n_rows), dim3(256), 0, st, (const float*)p.dh, rows, d, 1, p.dx, (const uint32_t*)nullptr,
                 (uint32_t*)nullptr));
@@ -2811,9 +2816,9 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
       T_CK(gemm_x3(X3Op{nullptr, 0, Mi, 2 * F, false, mx.dgu_r, nullptr}, X3Op{TH(t0 + 6), d, d, 2 * F, true, mx.wgu_c, nullptr}, p.dx, p.dx, d,
                    0.f, xb, st, nullptr, true, p.packa));
       T_CK(gemm_x3(X3Op{nullptr, 0, 2 * F, Mi, true, mx.dgu_c, nullptr}, X3Op{a.xn2, d, d, Mi, true, mx.xn2_c, nullptr}, GR(t0 + 6), GR(t0 + 6), d,
-                   keep, xb, st, nullptr, true, p.dgu));
+                   keep, xb, st, nullptr, true, p.dgu, true));
       T_CK(gemm_x3(X3Op{p.dh, d, d, Mi, true, mx.dh1_c, nullptr}, X3Op{nullptr, 0, F, Mi, true, mx.act_c, nullptr}, GR(t0 + 8), GR(t0 + 8), F, keep,
-                   xb, st, p.act_cols));
+                   xb, st, p.act_cols, true, nullptr, true));
     } else {
       T_CK(mm_tn(dh1, Mat{a.act, F, mx.act_r, mx.act_c}, GR(t0 + 8), d, F, Mi, keep));
       if (F % 4 == 0 && M <= 65535) {

@@ -255,3 +255,48 @@ int main() {
   return bad != 0;
 }
 """)
+
+
+def test_products_of_packed_updates_have_no_longer_chains(tmp_path):
+    """x3_split_packed: a product of an update that leaves rows out covers its contraction, fits the parts' buffer and adds up no
+    chain longer than the same product with all rows does (32 steps and fewer apart); with all rows it is x3_split."""
+    run(tmp_path, r"""
+int main() {
+  int bad = 0;
+  const int shapes[][3] = {{896, 1152, 9728}, {1536, 2048, 17920}, {64, 128, 384}};   // d, q + 2 kv, 2 F
+  for (const auto& sh : shapes) {
+    const int d = sh[0], nqkv = sh[1], F2 = sh[2];
+    const size_t most = (size_t)F2 * d, cap = 8 * (most > (size_t)192 * 128 * 128 ? most : (size_t)192 * 128 * 128);
+    for (int NP : {1, 3})
+      for (int all = 256; all <= 40000; all += all < 2000 ? 97 : 1531)
+        for (int left = all; left >= 1; left -= left > 2000 ? 911 : left > 64 ? 61 : 1) {
+          auto check = [&](int rows, int all_rows, int cols, int KB, int all_KB, int stage, size_t parts_cap) {
+            const X3Split a = x3_split(NP, all_rows, cols, all_KB, stage, parts_cap);
+            const X3Split s = x3_split_packed(NP, rows, cols, KB, all_rows, all_KB, stage, parts_cap);
+            const bool same = rows != all_rows || KB != all_KB || (s.TJ == a.TJ && s.parts == a.parts && s.per_part == a.per_part);
+            const bool covers = s.parts * s.per_part >= KB && (s.parts - 1) * s.per_part < KB;
+            const bool fits = s.parts == 1 || (size_t)s.parts * rows * cols <= parts_cap;
+            const int most_steps = a.per_part > kShortChain ? a.per_part : kShortChain;
+            if (!same || !covers || !fits || (s.per_part > most_steps && all_rows + all_KB != rows + KB)) {
+              if (++bad < 20) printf("NP %d rows %d of %d cols %d steps %d of %d: %d x %d, with all %d x %d\n", NP, rows, all_rows, cols, KB, all_KB, s.parts, s.per_part, a.parts, a.per_part);
+            }
+          };
+          const int st = NP == 1 ? 4 : 2, st_tn = NP == 1 ? 2 : 1;
+          auto steps = [](int K) { return (K + 63) / 64 * 4; };
+          // d-input and forward products, split or not: the tokens are rows
+          for (size_t c : {cap, (size_t)0}) {
+            check(left, all, d, steps(F2), steps(F2), st, c);
+            check(left, all, d, steps(F2 / 2), steps(F2 / 2), st, c);
+            check(left, all, d, steps(nqkv), steps(nqkv), st, c);
+            check(left, all, F2 / 2, steps(d), steps(d), st, c);
+            check(left, all, F2, steps(d), steps(d), st, c);
+          }
+          // weight gradients: the tokens are contracted over
+          check(F2, F2, d, steps(left), steps(all), st, cap);
+          check(d, d, F2 / 2, steps(left), steps(all), st, cap);
+          check(nqkv, nqkv, d, (left + 15) / 16, (all + 15) / 16, st_tn, cap);
+        }
+  }
+  return bad != 0;
+}
+""")
