@@ -1035,8 +1035,10 @@ static int rollout_impl(const sapo_weights* w, const int32_t* prompts, const int
     } else {
       HIP_CK(g_embed(dt, prompts, 1, nullptr, w->embed, pl.fwd.h, M, d, st));
     }
-    // Of the last layer's output only the prompts' last rows are wanted.  us of a call of two tokens with all rows and with those, 0.5B:
-    // 33 positions 1976, 1988; 128 1866, 1872; 1024 2466, 2455; 16000 14112, 13736; 1.5B: 8192 23396, 22872.
+    // Of the last layer's output only the prompts' last rows are wanted.  Below about 300 positions the two launches that prepare them
+    // cost what is saved (the chip is not full), above it the saving grows with the positions.  us of a call of one token with all rows
+    // and with those, 0.5B: 16 positions 1224, 1227; 128 1298, 1298; 256 1332, 1332; 384 1386, 1384; 512 1595, 1589; 640 1630, 1620; 1024 1790, 1777;
+    // 4096 4176, 4092; 1.5B: 16 2300, 2304; 128 2431, 2435; 256 2627, 2625; 384 2935, 2925; 512 3194, 3172; 1024 4521, 4460; 4096 11790, 11554.
     const bool narrow = w->mfma && M >= 512 && can_narrow(c);
     const WantedRows last{pl.last_rows, nullptr, P, pl.fwd.qkv};
     if (narrow) HIP_CK(g_last_rows(pl.last_rows, P, Lp, ragged ? pl.lens : nullptr, packed ? pl.first : nullptr, st));
