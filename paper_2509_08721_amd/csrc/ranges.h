@@ -117,43 +117,50 @@ constexpr bool small_offsets_fit(uint64_t d, uint64_t q, uint64_t kv, uint64_t c
 // 407.7 and 406.1 ms.
 constexpr int kMaxSplits = 16, kChainSteps = 608;
 struct X3Split { int TJ, parts, per_part; };
+inline double x3_split_us(int NP, int TJ, int rows, int cols, int parts, int per_part) {
+  const int gnx = (cols + 127) / 128, gty = ((rows + 127) / 128 + TJ - 1) / TJ;
+  const long tiles = (long)gnx * gty, slots = TJ == 2 ? 512 : 768;
+  // one 16-k step of a full round (measured: 1.35 PFLOP/s with three products, 0.9 with one; 10 % more for the small tile)
+  const double step_us = (TJ == 2 ? 1.0 : 0.825) * 0.336 * (NP == 1 ? 1.0 : 3.0) * (NP == 1 ? 1.8 : 1.2);
+  const long rounds = (tiles * parts + slots - 1) / slots;
+  const double sum_us = parts > 1 ? 4.0 + (parts + 2) * 4e-6 * rows * cols : 0.0;   // at 1 MB per us
+  return rounds * (per_part * step_us + (TJ == 2 ? 14.0 : 10.5)) + sum_us / 4.0;
+}
 inline X3Split x3_split(int NP, int rows, int cols, int KB, int stage, size_t parts_cap, int chain = kChainSteps) {
-  const int gnx = (cols + 127) / 128, gny = (rows + 127) / 128;
-  const double terms = NP == 1 ? 1.0 : 3.0;
   X3Split best{2, 1, (KB + stage - 1) / stage * stage};
   double best_us = 0.0;
-  for (int TJ = 2; TJ >= 1; --TJ) {
-    const int gty = (gny + TJ - 1) / TJ;
-    const long tiles = (long)gnx * gty, slots = TJ == 2 ? 512 : 768;
-    // one 16-k step of a full round (measured: 1.35 PFLOP/s with three products, 0.9 with one; 10 % more for the small tile)
-    const double step_us = (TJ == 2 ? 1.0 : 0.825) * 0.336 * terms * (NP == 1 ? 1.8 : 1.2);
+  for (int TJ = 2; TJ >= 1; --TJ)
     for (int s = 1; s <= kMaxSplits; ++s) {
       if (s > 1 && (KB / s < 16 || (size_t)s * rows * cols > parts_cap)) break;
       if ((KB + s - 1) / s > chain && s < kMaxSplits && (size_t)(s + 1) * rows * cols <= parts_cap) continue;
       const int per = ((KB + s - 1) / s + stage - 1) / stage * stage;
       if ((KB + per - 1) / per != s) continue;
-      const long rounds = (tiles * s + slots - 1) / slots;
-      const double sum_us = s > 1 ? 4.0 + (s + 2) * 4e-6 * rows * cols : 0.0;   // at 1 MB per us
-      const double us = rounds * (per * step_us + (TJ == 2 ? 14.0 : 10.5)) + sum_us / 4.0;
+      const double us = x3_split_us(NP, TJ, rows, cols, s, per);
       if (best_us == 0.0 || us < best_us * 0.98) {
         best_us = us;
         best = X3Split{TJ, s, per};
       }
     }
-  }
   return best;
 }
 
-// The same for an update that leaves rows out (leaves_rows_out): chains no longer than the product would have with all of them
-// (all_rows, all_KB; 32 steps and fewer are short anyhow), so that a gradient is no further off for rows that it does not depend on.
-// Chosen by the rows that are left alone, the d-input product of gate/up had 608 steps at 18209 of 24576 rows (0.5B, 64 x 384) in place
-// of 204: the gradient's error against 64 bits, three pieces, was 1.11e-5 where all rows left 7.2e-6.
+// The same for an update that leaves rows out (leaves_rows_out): no chain is longer than with all of them (all_rows, all_KB; 32 steps and
+// fewer are short anyhow), so that a gradient is no further off.  Chosen by the rows that are left, gate/up's d-input product had 608
+// steps at 18209 of 24576 rows (0.5B, 64 x 384) in place of 204, and the gradient's error against 64 bits, three pieces, was 1.11e-5 where all
+// rows left 7.2e-6 (7.2e-6 now; 48 x 300 5.4e-6, all rows 9.4e-6).
+// With one and two pieces a product whose rows are the tokens is split exactly as with all of them, so that a row keeps its bits
+// whatever is left out: a last bit decides how operands are rounded in all layers in front.  One piece, 21 x 301, the weights after
+// one update against those of an update of all rows: 1.8e-3 off with splits of its own, 4e-6 with theirs, in the same time (35.3, 34.9 ms).
 constexpr int kShortChain = 32;
 inline X3Split x3_split_packed(int NP, int rows, int cols, int KB, int all_rows, int all_KB, int stage, size_t parts_cap) {
-  if (rows == all_rows && KB == all_KB) return x3_split(NP, rows, cols, KB, stage, parts_cap);
-  int chain = x3_split(NP, all_rows, cols, all_KB, stage, parts_cap).per_part;
-  if (chain < kShortChain) chain = kShortChain;
-  return x3_split(NP, rows, cols, KB, stage, parts_cap, chain < kChainSteps ? chain : kChainSteps);
+  X3Split all = x3_split(NP, all_rows, cols, all_KB, stage, parts_cap);
+  if (rows == all_rows && KB == all_KB) return all;
+  if (NP == 3 || KB != all_KB) {
+    const int chain = all.per_part < kShortChain ? kShortChain : all.per_part < kChainSteps ? all.per_part : kChainSteps;
+    return x3_split(NP, rows, cols, KB, stage, parts_cap, chain);
+  }
+  all.TJ = x3_split_us(NP, 1, rows, cols, all.parts, all.per_part) < 0.98 * x3_split_us(NP, 2, rows, cols, all.parts, all.per_part) ? 1 : 2;
+  return all;
 }
 
 // Rows that a sequence of T positions has among packed rows when its last scored token is at `last` (0: it has none): the positions in

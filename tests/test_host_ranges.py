@@ -257,9 +257,10 @@ int main() {
 """)
 
 
-def test_products_of_packed_updates_have_no_longer_chains(tmp_path):
+def test_products_of_packed_updates_add_up_as_with_all_rows(tmp_path):
     """x3_split_packed: a product of an update that leaves rows out covers its contraction, fits the parts' buffer and adds up no
-    chain longer than the same product with all rows does (32 steps and fewer apart); with all rows it is x3_split."""
+    chain longer than the same product with all rows does (32 steps and fewer apart).  With one and two pieces one whose rows are the
+    tokens has the parts that it has with all rows (a row keeps its bits); with all rows it is x3_split."""
     run(tmp_path, r"""
 int main() {
   int bad = 0;
@@ -267,7 +268,7 @@ int main() {
   for (const auto& sh : shapes) {
     const int d = sh[0], nqkv = sh[1], F2 = sh[2];
     const size_t most = (size_t)F2 * d, cap = 8 * (most > (size_t)192 * 128 * 128 ? most : (size_t)192 * 128 * 128);
-    for (int NP : {1, 3})
+    for (int NP : {1, 2, 3})
       for (int all = 256; all <= 40000; all += all < 2000 ? 97 : 1531)
         for (int left = all; left >= 1; left -= left > 2000 ? 911 : left > 64 ? 61 : 1) {
           auto check = [&](int rows, int all_rows, int cols, int KB, int all_KB, int stage, size_t parts_cap) {
@@ -277,7 +278,8 @@ int main() {
             const bool covers = s.parts * s.per_part >= KB && (s.parts - 1) * s.per_part < KB;
             const bool fits = s.parts == 1 || (size_t)s.parts * rows * cols <= parts_cap;
             const int most_steps = a.per_part > kShortChain ? a.per_part : kShortChain;
-            if (!same || !covers || !fits || (s.per_part > most_steps && all_rows + all_KB != rows + KB)) {
+            const bool as_all = NP == 3 || KB != all_KB ? s.per_part <= most_steps : s.parts == a.parts && s.per_part == a.per_part;
+            if (!same || !covers || !fits || !as_all) {
               if (++bad < 20) printf("NP %d rows %d of %d cols %d steps %d of %d: %d x %d, with all %d x %d\n", NP, rows, all_rows, cols, KB, all_KB, s.parts, s.per_part, a.parts, a.per_part);
             }
           };
