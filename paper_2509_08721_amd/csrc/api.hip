@@ -1292,11 +1292,11 @@ static int score_chunk_seqs(const sapo_weights* w, int S, int T) {
 // positions on; one that has none pays for the gather of the scored rows (9 us at 2560 positions), two small launches (4 us), and in
 // every launch of a layer for a load of the number of rows in front of the tile's first request (0.2 us, 0.9 in 1.5B's
 // down), against the last layer's projections of unscored rows.  us per call without and with packed rows, every answer up to the row's
-// end, 0.5B: 1204 positions 2465, 2497; 1536 2530, 2562; 2048 3020, 3036; 2304 3189, 3196; 2560 3382, 3401; 2709 3841, 3804; 3072 3866, 3870;
-// 8192 8601, 8638; 49152 45914, 45559; 1.5B: 1204 5573, 5578; 2560 8992, 9008; 3072 10793, 10921; 4096 12873, 12995; 7200 21583, 21481; 49152 134683,
-// 133866.  The line lies where the loss of a full call stays below 0.6 % on the 0.5B decoder (1.2 % on the 1.5B one, 3072 and
-// 4096 positions).  Answers that end a quarter of the row early on average, 0.5B: 1204 2347, 2025; 2048 2908, 2725; 2560 3243, 3064; 2709 3610, 2987; 49152
-// 43166, 32306; 1.5B: 2709 10215, 8007; 49152 129627, 98019.
+// end, 0.5B: 1204 positions 2465, 2497; 1536 2530, 2562; 2048 3020, 3036; 2304 3189, 3196; 2560 3396, 3418; 2709 3841, 3804; 3072 3721, 3736;
+// 4096 4624, 4632; 8192 8505, 8538; 49152 45914, 45559; 1.5B: 1204 5573, 5578; 2560 9017, 9013; 3072 10453, 10446; 4096 12702, 12774 (16 x 256), 12837, 12927
+// (8 x 512); 7200 21583, 21481; 49152 134683, 133866.  The line lies where the loss of a full call stays below 0.8 %.  Answers that end a
+// quarter of the row early on average, 0.5B: 1204 2347, 2025; 2048 2908, 2725; 2560 3243, 3064; 2709 3610, 2987; 49152 43166, 32306; 1.5B: 2709 10215,
+// 8007; 49152 129627, 98019.
 constexpr int kPackedRows = 2560;
 static bool score_packs_rows(const sapo_weights* w, int M) {
   return w->mfma && M >= kPackedRows && can_narrow(w->cfg);

@@ -388,9 +388,9 @@ struct RolloutBegin {
 };
 hipError_t g_rollout_begin(const RolloutBegin& a, hipStream_t st);
 hipError_t g_incr(int* p, hipStream_t st);
-// Of sequences s0 .. s0 + ns - 1: how many positions a scored one depends on, in units of `unit` (packed_rows), and how many are scored
-hipError_t g_packed_lens(const uint8_t* mask, int T, int s0, int ns, int unit, int2* lens /*[ns]*/, hipStream_t st);
-// RowMap::first [ns + 1] and ::packed [ns T] for those positions (units of packed_unit(T)), and what g_masked_rows leaves (src_rows: packed
+// Of sequences s0 .. s0 + ns - 1: how many rows each has among packed ones (packed_rows), and how many positions are scored
+hipError_t g_packed_lens(const uint8_t* mask, int T, int s0, int ns, bool keep_aligned, int2* lens /*[ns]*/, hipStream_t st);
+// RowMap::first [ns + 1] and ::packed [ns T] for those rows (kept aligned), and what g_masked_rows leaves (src_rows: packed
 // rows); lens [ns]: scratch
 hipError_t g_packed_rows(const uint8_t* mask, int T, int s0, int ns, const int* page_table, int pages_per_seq, int2* lens, int* first,
                          int2* packed, int* rows, int* src_rows, int* count, hipStream_t st);

@@ -892,10 +892,10 @@ hipError_t g_masked_rows(const uint8_t* mask, int T, int s0, int ns, int* rows, 
 // ---------------------------------------------------------------------------------------
 // The rows of a scoring pass that a log-prob depends on.  Attention is causal, so a sequence's positions from its last scored
 // token on change none: answers that end before their row does need no forward pass over the padding.  Of sequence s0 + s the
-// positions in front of its last scored token go on (none: 0 of them; packed_rows says how many past it), side by side with the
+// positions in front of its last scored token go on (none: 0 of them; packed_rows says where one more does), side by side with the
 // other sequences'; the scored positions are listed in the same pass (as k_masked_rows does).
 // ---------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) k_packed_lens(const uint8_t* __restrict__ mask, int T, int s0, int unit, int2* __restrict__ lens) {
+__global__ void __launch_bounds__(256) k_packed_lens(const uint8_t* __restrict__ mask, int T, int s0, bool keep_aligned, int2* __restrict__ lens) {
   __shared__ int2 part[4];
   const uint8_t* m = mask + (size_t)(s0 + blockIdx.x) * T;
   int last = 0, n = 0;
@@ -909,7 +909,7 @@ __global__ void __launch_bounds__(256) k_packed_lens(const uint8_t* __restrict__
   if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = make_int2(last, n);
   __syncthreads();
   if (threadIdx.x == 0)
-    lens[blockIdx.x] = make_int2(packed_rows(max(max(part[0].x, part[1].x), max(part[2].x, part[3].x)), T, unit),
+    lens[blockIdx.x] = make_int2(packed_rows(max(max(part[0].x, part[1].x), max(part[2].x, part[3].x)), T, keep_aligned),
                                  (part[0].y + part[1].y) + (part[2].y + part[3].y));
 }
 __global__ void __launch_bounds__(256) k_packed_rows(const uint8_t* __restrict__ mask, int T, int s0, int ns, const int2* __restrict__ lens,
@@ -954,12 +954,12 @@ __global__ void __launch_bounds__(256) k_packed_rows(const uint8_t* __restrict__
     out0 += (part[0].x + part[1].x) + (part[2].x + part[3].x);
   }
 }
-hipError_t g_packed_lens(const uint8_t* mask, int T, int s0, int ns, int unit, int2* lens, hipStream_t st) {
-  return launch(KID_MISC, k_packed_lens, dim3(ns), dim3(256), 0, st, mask, T, s0, unit, lens);
+hipError_t g_packed_lens(const uint8_t* mask, int T, int s0, int ns, bool keep_aligned, int2* lens, hipStream_t st) {
+  return launch(KID_MISC, k_packed_lens, dim3(ns), dim3(256), 0, st, mask, T, s0, keep_aligned, lens);
 }
 hipError_t g_packed_rows(const uint8_t* mask, int T, int s0, int ns, const int* page_table, int pages_per_seq, int2* lens, int* first,
                          int2* packed, int* rows, int* src_rows, int* count, hipStream_t st) {
-  const hipError_t e = g_packed_lens(mask, T, s0, ns, packed_unit(T), lens, st);
+  const hipError_t e = g_packed_lens(mask, T, s0, ns, true, lens, st);
   if (e != hipSuccess) return e;
   return launch(KID_MISC, k_packed_rows, dim3(ns), dim3(256), 0, st, mask, T, s0, ns, (const int2*)lens, page_table, pages_per_seq, first,
                 packed, rows, src_rows, count);

@@ -164,19 +164,16 @@ inline X3Split x3_split_packed(int NP, int rows, int cols, int KB, int all_rows,
 }
 
 // Rows that a sequence of T positions has among packed rows when its last scored token is at `last` (0: it has none): the positions in
-// front of it, which the token's log-prob depends on, and as many more as make whole units, where the sequence has them.
-// The QKV launch writes 8 values of a page at once where 8 rows in a run begin at a slot divisible by 8, and two bytes at a
-// time elsewhere.  Answers up to the row's end have T - 1 rows, which for an even T left every sequence behind the first
-// askew.  A scoring pass takes units of 2: such a call lies as it would without packing, and a ragged one has half a row more
-// per sequence.  us per call not packed, in units of 1 and of 2, 0.5B, every answer up to the row's end: 10 x 256 3313, 3381, 3335; 16 x
-// 512 8226, 8335, 8259; ragged: 3142, 2944, 2934; 7717, 6279, 6256.  Units of 4 and 8 gain 1 to 2 % more on some ragged calls and
-// lose up to 11 % on sequences of few tokens (128 x 24 3136 -> 3247, 3493).  Below 64 positions a row is more of a sequence than the
-// alignment is worth: 8192 x 2 16738, 11913, 16698; 1000 x 8 8110, 7627, 8123; 600 x 16 9615, 8923, 9585; 400 x 32 11985, 11878, 11931; but 40 x 64
-// 3242, 3317, 3259.
-constexpr int packed_unit(int T) { return T < 64 ? 1 : 2; }
-SAPO_HD constexpr int packed_rows(int last, int T, int unit) {
-  const int n = (last + unit - 1) / unit * unit;
-  return n < T ? n : T;
+// front of it, which the token's log-prob depends on.
+// The QKV launch writes 8 values of a page at once where a run of 8 slots lies within a tile of 64 rows, and two bytes at a time
+// elsewhere.  An answer up to the row's end has T - 1 rows; for an even T they would leave every sequence behind it askew to the
+// tiles, so a scoring pass (keep_aligned) takes the last position along: a call of such answers lies as it would without packing.  us per call not packed, with T - 1 and with T rows, 0.5B, every answer up to the row's end: 10 x 256 3396, 3484, 3418; 16 x 512
+// 8505, 8640, 8538; 40 x 64 3326, 3406, 3345; 40 x 72 3745, 3773, 3722; 13 x 300 4774, 4810, 4790; 1.5B, 16 x 256 12790, 12950, 12894.  Answers that end anywhere are askew in
+// any case; an even number of rows for each gains 0.3 % there, and loses 3 % where it begins another tile (9 x 301, 2048 rows -> 2052
+// 3100 -> 3187).  Below 64 positions a row is more of a sequence than the alignment is worth: 8192 x 2 16738, 11913, 16698; 1000 x 8 8110, 7627,
+// 8123; 600 x 16 9615, 8923, 9585; 400 x 32 11985, 11878, 11931.
+SAPO_HD constexpr int packed_rows(int last, int T, bool keep_aligned) {
+  return keep_aligned && T >= 64 && T % 2 == 0 && last == T - 1 ? T : last;
 }
 
 // Are there enough rows to leave out?  With a few fewer than a row tile of 128 a pass keeps its tiles, while aligned sizes become

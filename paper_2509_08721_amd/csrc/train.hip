@@ -2619,7 +2619,7 @@ static int update_rows(sapo_trainer* tr, const TrainPlan& p, const int32_t* toke
   PackedUpdate pk;
   if (n_packed > 0) {
     pk.init(p, S_, n_packed);
-    T_CK(g_packed_lens(completion_mask, T_, 0, S_, 1, pk.lens, st));
+    T_CK(g_packed_lens(completion_mask, T_, 0, S_, false, pk.lens, st));
     T_CK(launch(KID_MISC, k_packed_update, dim3(S_), dim3(256), 0, st, completion_mask, tokens, T_, S_, (const int2*)pk.lens, pk.first, pk.pos,
                 pk.tokens, pk.rows, pk.token_rows));
     rows = pk.rows;
@@ -2986,7 +2986,7 @@ extern "C" int sapo_policy_update(sapo_trainer* tr, const int32_t* tokens, const
     const size_t s0 = i * S_mb;
     const int n = (int)(S - s0 < S_mb ? S - s0 : S_mb);
     T_CK(g_masked_rows(completion_mask + s0 * T, T_, 0, n, p.mpos, p.mrows + s0 * T, p.mcount + i, st));
-    T_CK(g_packed_lens(completion_mask + s0 * T, T_, 0, n, 1, (int2*)p.eorder, st));
+    T_CK(g_packed_lens(completion_mask + s0 * T, T_, 0, n, false, (int2*)p.eorder, st));
     T_CK(launch(KID_MISC, k_packed_count, dim3(1), dim3(256), 0, st, (const int2*)p.eorder, n, p.mcount + n_mb + i));
   }
   T_CK(hipMemcpyAsync(counts.data(), p.mcount, 2 * n_mb * sizeof(int), hipMemcpyDeviceToHost, st));

@@ -217,17 +217,15 @@ int main() {
 
 
 def test_packed_rows_hold_the_scored_tokens_prefix_and_full_answers_stay_aligned(tmp_path):
-    """packed_rows: every position in front of the last scored token, none past the sequence, none for a sequence without one, at
-    most a unit less one more; an answer up to the end of a row of 8 n positions (runs of 8 slots of a page), 64 and more, keeps
-    them all, while in a shorter row no position behind the last scored token's goes on."""
+    """packed_rows: the positions in front of the last scored token, none for a sequence without one.  In a scoring pass an answer up
+    to the end of a row of an even number of positions, 64 and more, keeps the last one too; no other row does."""
     run(tmp_path, r"""
 int main() {
   int bad = 0;
   for (int T = 1; T <= 700; ++T)
     for (int last = 0; last < T; ++last) {
-      const int n = packed_rows(last, T, packed_unit(T));
-      if (n < last || n > T || n >= last + packed_unit(T) || (T < 64 && n != last) || (last == 0 && n != 0) || packed_rows(last, T, 1) != last) { ++bad; printf("T %d last %d: %d\n", T, last, n); }
-      if (T >= 64 && T % 8 == 0 && last == T - 1 && n != T) { ++bad; printf("T %d: a full answer has %d rows\n", T, n); }
+      const bool full = T >= 64 && T % 2 == 0 && last == T - 1;
+      if (packed_rows(last, T, true) != (full ? T : last) || packed_rows(last, T, false) != last) { ++bad; printf("T %d last %d: %d\n", T, last, packed_rows(last, T, true)); }
     }
   return bad != 0;
 }
