@@ -1290,13 +1290,12 @@ static int score_chunk_seqs(const sapo_weights* w, int S, int T) {
 
 // Does a scoring pass of M positions leave out those that no log-prob depends on?  A call that has some to leave out is faster from 1204
 // positions on; one that has none pays for the gather of the scored rows (9 us at 2560 positions), two small launches (4 us), and in
-// every launch of a layer for a load of the number of rows in front of the tile's first request (0.2 us, 0.9 in 1.5B's
-// down), against the last layer's projections of unscored rows.  us per call without and with packed rows, every answer up to the row's
-// end, 0.5B: 1204 positions 2465, 2497; 1536 2530, 2562; 2048 3020, 3036; 2304 3189, 3196; 2560 3396, 3418; 2709 3841, 3804; 3072 3721, 3736;
-// 4096 4624, 4632; 8192 8505, 8538; 49152 45914, 45559; 1.5B: 1204 5573, 5578; 2560 9017, 9013; 3072 10453, 10446; 4096 12702, 12774 (16 x 256), 12837, 12927
-// (8 x 512); 7200 21583, 21481; 49152 134683, 133866.  The line lies where the loss of a full call stays below 0.8 %.  Answers that end a
-// quarter of the row early on average, 0.5B: 1204 2347, 2025; 2048 2908, 2725; 2560 3243, 3064; 2709 3610, 2987; 49152 43166, 32306; 1.5B: 2709 10215,
-// 8007; 49152 129627, 98019.
+// every launch of a layer for a load of the number of rows in front of the tile's first request, against the last layer's
+// projections of unscored rows.  us per call without and with packed rows, every answer up to the row's end, 0.5B: 4 x 301 2424, 2430; 6
+// x 256 2502, 2518; 8 x 256 2983, 3000; 9 x 256 3132, 3148; 10 x 256 3335, 3351; 9 x 301 3759, 3741; 12 x 256 3769, 3789; 16 x 256 4668, 4680; 8 x 512 4809, 4852;
+// 4 x 1000 5088, 5143; 16 x 384 6701, 6661; 64 x 768 45870, 45560; 1.5B: 4 x 301 5414, 5393; 8 x 256 7483, 7505; 10 x 256 8846, 8883; 12 x 256 10455, 10393; 16 x
+// 256 12612, 12536; 4 x 1000 12928, 12882; 64 x 768 134730, 133640.  Answers that end a quarter of the row early on average, 0.5B: 4 x 301 2289, 1979; 8 x 256
+// 2810, 2591; 10 x 256 3162, 2946; 9 x 301 3533, 2899; 64 x 768 43020, 32250; 1.5B: 4 x 301 5203, 4110; 9 x 301 9880, 7664; 64 x 768 129980, 98330.
 constexpr int kPackedRows = 2560;
 static bool score_packs_rows(const sapo_weights* w, int M) {
   return w->mfma && M >= kPackedRows && can_narrow(w->cfg);

@@ -121,12 +121,13 @@ constexpr int kRing = 3;                                            // stages of
 constexpr int ring_bytes(int H) { return kRing * 4 * H * 1024; }     // 4 H fragments of 1 KiB per stage
 constexpr int kBigLds = ring_bytes(4);
 
-// Rows of a launch for at most M (PK: as many as `rows`, on the device, says): a scalar load, the same for every lane.  A template
-// parameter of the kernels, because what they execute before their first requests counts: with a test of the pointer a scoring call of
-// 301 tokens took 1.465 ms instead of 1.444.
+// Rows of a launch for at most M (PK: as many as `rows`, on the device, says).  A template parameter of the kernels, because what
+// they execute before their first requests counts: with a test of the pointer a scoring call of 301 tokens took 1.465 ms instead of 1.444.
+// Through the vector path: a scalar load, the same for every lane, would be waited for with all other scalar loads on their way,
+// and those of the arguments that are not preloaded take longer.  16 x 256 tokens, 1.5B, us without a row count, with it as a
+// scalar load, and like this: down 131.1, 135.2, 131.8; gate/up 200.2, 201.5, 200.4; the scoring call 12570, 12677, 12525.
 template <bool PK> __device__ __forceinline__ int rows_there(const int* rows, int M) {
-  typedef const __attribute__((address_space(4))) int* ConstInt;
-  if constexpr (PK) return min(M, *(ConstInt)(uintptr_t)rows);
+  if constexpr (PK) return min(M, __builtin_amdgcn_readfirstlane(__hip_atomic_load(rows, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)));
   return M;
 }
 __device__ __forceinline__ bool big_raster(int NX, int NY, int& bx, int& by) {
